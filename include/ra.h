@@ -321,10 +321,11 @@ ra_status ra_index_configure(ra_index* idx, int what, int64_t value);
 /* ---- TEST-ONLY settings -------------------------------------------------------------
  * Not for callers of the library: they exist so that the test-suite can reach code paths that
  * inputs alone cannot select. Results never depend on them beyond what is stated.
- *   RA_TEST_KNN_SELECTION   (idx = NULL; process-wide) which of the two top-knn selections
- *                           ra_knn uses for bf16 lists of up to 32 keys: RA_TEST_KNN_AUTO
- *                           (default: chosen by N), RA_TEST_KNN_REG, RA_TEST_KNN_LDS. Same lists
- *                           either way.
+ *   RA_TEST_KNN_SELECTION   (idx = NULL; process-wide) whether ra_knn takes the later part of its key
+ *                           stream through 8-bit products that rule keys out: RA_TEST_KNN_AUTO
+ *                           (default: chosen by the sizes), RA_TEST_KNN_LDS (never),
+ *                           RA_TEST_KNN_FILTER (from the 129th key on; RA_TEST_KNN_REG is another
+ *                           name of it). Same lists either way.
  *   RA_TEST_HELPERS_SILENT  (per handle) 1: the helper and seed workgroups of ra_decode_step are
  *                           launched but write nothing, so every head's bounded wait runs out and
  *                           the fall-back is taken; 0: normal. Synchronises the device and clears
@@ -332,7 +333,8 @@ ra_status ra_index_configure(ra_index* idx, int what, int64_t value);
 #define RA_TEST_KNN_SELECTION 100
 #define RA_TEST_HELPERS_SILENT 101
 #define RA_TEST_KNN_AUTO 0
-#define RA_TEST_KNN_REG 1
+#define RA_TEST_KNN_FILTER 1
+#define RA_TEST_KNN_REG RA_TEST_KNN_FILTER
 #define RA_TEST_KNN_LDS 2
 ra_status ra_test_configure(ra_index* idx, int what, int64_t value);
 

@@ -214,7 +214,7 @@ extern "C" ra_status ra_index_configure(ra_index* ix, int what, int64_t value) {
 extern "C" ra_status ra_test_configure(ra_index* ix, int what, int64_t value) {
     switch (what) {
         case RA_TEST_KNN_SELECTION:
-            if (value != RA_TEST_KNN_AUTO && value != RA_TEST_KNN_REG && value != RA_TEST_KNN_LDS)
+            if (value != RA_TEST_KNN_AUTO && value != RA_TEST_KNN_FILTER && value != RA_TEST_KNN_LDS)
                 RA_FAIL(RA_EINVAL, "knn selection %lld", (long long)value);
             ra_knn_set_selection_override((int)value);
             return RA_OK;
@@ -335,8 +335,8 @@ extern "C" ra_status ra_knn(const void* K, const void* Q, ra_dtype dt, int n_seq
     RA_TRY(check_heads(n_seq, n_q, n_kv));
     RA_TRY(check_dim(d));
     RA_TRY(check_build_args(N, M, 2, knn, false));
-    void* ws = nullptr;                                    // the order the keys are streamed in
-    RA_HIP(hipMalloc(&ws, ra_knn_order_bytes(n_seq * n_q, N)));
+    void* ws = nullptr;
+    RA_HIP(hipMalloc(&ws, ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn)));
     ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, (hipStream_t)stream, L_out);
     hipError_t e = hipStreamSynchronize((hipStream_t)stream);
     (void)hipFree(ws);
@@ -375,7 +375,7 @@ extern "C" ra_status ra_build_index(const void* K, const void* Q, ra_dtype dt, i
     int32_t* L = nullptr;
     void* order_ws = nullptr;
     hipError_t e = hipMalloc((void**)&L, (size_t)graphs * M * knn * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&order_ws, ra_knn_order_bytes(graphs, N));
+    if (e == hipSuccess) e = hipMalloc(&order_ws, ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn));
     if (e != hipSuccess) {
         ra_set_error("allocating the KNN lists failed: %s", hipGetErrorString(e));
         if (L) (void)hipFree(L);

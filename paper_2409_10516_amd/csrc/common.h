@@ -139,11 +139,21 @@ ra_status ra_launch_flat_topk(const void* q, const void* K, ra_dtype dt, int n_s
                               int64_t N, int sink, int window, int topk, uint32_t* keys_ws,
                               hipStream_t st, int32_t* ids);
 
-// `workspace`: ra_knn_order_bytes(n_seq * n_q, N) bytes of device memory, free again once the
-// stream has run the launch
+// `workspace`: ra_knn_workspace_bytes(...) bytes of device memory, free again once the stream has run
+// the launch
 ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
                         int64_t N, int64_t M, int knn, void* workspace, hipStream_t st, int32_t* L);
-void ra_knn_set_selection_override(int v);      // RA_TEST_KNN_AUTO / _REG / _LDS
+// the long part of the key stream through 8-bit products (knn_filter.hip)
+size_t ra_knn_filter_bytes(int graphs, int64_t N, int64_t M, int knn);
+float* ra_knn_filter_scores(void* workspace, int graphs, int64_t N, int64_t M, int knn);
+ra_status ra_launch_knn_filter_scales(const void* K, ra_dtype dt, int n_seq_kv, int64_t N, uint32_t* maxabs,
+                                      hipStream_t st);
+ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const void* order, int g0, int n_graphs,
+                               int n_q, int n_kv, int64_t N, int64_t M, int knn, int64_t first,
+                               const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
+                               const int** resume, int* resume_queries, int* resume_blocks);
+void ra_knn_set_selection_override(int v);      // RA_TEST_KNN_AUTO / _FILTER / _LDS
+size_t ra_knn_workspace_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn);
 size_t ra_knn_order_bytes(int n_graphs, int64_t N);
 int64_t ra_knn_order_stride(int64_t N);
 ra_status ra_launch_knn_order(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,

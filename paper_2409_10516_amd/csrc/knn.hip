@@ -9,18 +9,13 @@
 // selection threshold of a query is a single per-lane register: the common case is a
 // max-tree over the lane's 16 scores and one compare. Only scores that reach the threshold go
 // further (about knn * ln(N / knn) per query over a stream in storage order, a third of that in
-// the order the keys are streamed in here: see knn_order.hip). Three ways to keep them:
+// the order the keys are streamed in here: see knn_order.hip). Two ways to keep them:
 //   KN_SEL_LDS (knn <= KN_BUFFERED_KNN): a query owns KN_CAP list slots in LDS, its best knn keys
 //     so far, then two runs of pending slots, one per lane that scores for it. A lane appends a
 //     key to its own run with a single LDS write (its fill count is a register); when a run cannot
 //     take what a lane is about to append (keys come four at a time) the wavefront sorts the 64
 //     slots of that query across its lanes (bitonic network), keeps the best knn and raises the
 //     threshold.
-//   KN_SEL_REG (knn <= KN_REG_KNN, bf16): a lane keeps its pending keys (KN_REG_PEND per query
-//     set) in registers and a query's list takes 32 slots, so LDS holds the lists of twice as many
-//     queries and a wavefront owns two sets of 32: every key operand read from LDS feeds two
-//     independent MFMA chains. Merging a query's few pending keys into its sorted list takes no
-//     sort (knn_fold_reg).
 //   KN_SEL_INSERT (longer lists): sorted insertion, one key at a time, by the whole wavefront.
 // Between two merges a threshold is stale but valid (never above the true one), so nothing is
 // lost.
@@ -44,15 +39,9 @@
 
 #define KN_CAP 64                 // list slots of a query in the buffered selection (one per lane)
 #define KN_BUFFERED_KNN 48        // longest list that leaves room for pending slots
-#define KN_REG_KNN 32             // longest list of the selection that keeps pending keys in registers
-#define KN_REG_MIN_KEYS 49152     // fewest keys for which that selection is the faster one (see ra_launch_knn)
-#ifndef KN_REG_PEND
-#define KN_REG_PEND 4             // pending keys a lane holds there (at least 4: a group of scores)
-#endif
 // how the top-knn selection keeps keys that reached a threshold until they are merged into a list
 #define KN_SEL_INSERT 0           // not at all: sorted insertion, one key at a time
 #define KN_SEL_LDS 1              // in pending runs behind the list in LDS (KN_CAP slots per query)
-#define KN_SEL_REG 2              // in registers of the lane that scored them (32 slots per query in LDS)
 
 typedef unsigned long long u64;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -111,44 +100,6 @@ __device__ __forceinline__ float knn_fold(u64* lst, int knn, int lane) {
     const u64 v = wave_sort_desc(lst[lane], lane);
     lst[lane] = lane < knn ? v : 0ull;
     const u64 last = readlane64(v, knn - 1);
-    return last == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(last >> 32));
-}
-
-// The same for a query (number jq of its set) whose pending keys sit in registers: p[] and fill
-// are every lane's own, the query's are those of lanes jq and jq + 32. With a few keys to merge
-// into a sorted list of 32 a sort is not needed: the list goes to the lower half-wave, the pending
-// keys (zero where a lane holds fewer than it could) to lanes 32.. and, one by one as scalars, to
-// everyone; a list entry moves down by the number of pending keys above it, a pending key lands at
-// the number of keys above it, and every slot below 32 is written exactly once (keys are distinct
-// or zero; a zero pending key writes nothing). The caller resets the fill counts of the query's lanes.
-__device__ __forceinline__ float knn_fold_reg(u64* lst, int knn, int lane, int jq,
-                                              const u64 (&p)[KN_REG_PEND], int fill) {
-    constexpr int P = KN_REG_PEND;
-    u64 v = lane < 32 ? lst[lane & 31] : 0ull;
-    const int f_lo = __builtin_amdgcn_readlane(fill, jq), f_hi = __builtin_amdgcn_readlane(fill, jq + 32);
-    u64 x[2 * P];
-#pragma unroll
-    for (int k = 0; k < P; ++k) {
-        x[k] = readlane64(p[k], jq);
-        x[P + k] = readlane64(p[k], jq + 32);
-    }
-#pragma unroll
-    for (int k = 0; k < 2 * P; ++k) {
-        if (!(k < P ? k < f_lo : k - P < f_hi)) x[k] = 0ull;
-        if (lane == 32 + k) v = x[k];
-    }
-    int pos = lane;
-#pragma unroll
-    for (int k = 0; k < 2 * P; ++k) {
-        const int above = __popcll(__ballot(v > x[k]));      // keys that beat pending key k
-        if (lane < 32) pos += v < x[k] ? 1 : 0;
-        if (lane == 32 + k) pos = above;
-    }
-    const bool writes = lane < 32 || (lane < 32 + 2 * P && v != 0ull);
-    if (writes && pos < 32) lst[pos] = pos < knn ? v : 0ull;
-    const u64 at_end = __ballot(writes && pos == knn - 1);
-    const int src = at_end ? __ffsll((long long)at_end) - 1 : 0;
-    const u64 last = readlane64(v, src);
     return last == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(last >> 32));
 }
 
@@ -263,17 +214,20 @@ __device__ __forceinline__ void store_chunk(unsigned char* buf, int tid, int i, 
     *reinterpret_cast<u32x4*>(buf + row * ROWB + ((c ^ (row & 15)) << 4)) = v;
 }
 
-// grid: x = block of NQ * 32 * WAVES queries, y = graph (seq * n_q + h). A wavefront owns NQ sets
-// of 32 queries, so every key operand it reads feeds NQ MFMA chains.
+// grid: x = block of NQ * 32 * WAVES queries, y = graph (seq * n_q + h) - g0. The keys are the first
+// n_stream of the graph's stream order. With `scores` and no `resume` the lists' scores are written
+// too, for knn_filter.hip, which takes the rest of the stream; with `resume` (first stream position not
+// yet seen, per graph and block of resume_queries queries) the lists are read from L_out and scores and
+// the stream goes on from there. A wavefront owns NQ sets of 32 queries, so every key operand it reads
+// feeds NQ MFMA chains.
 // LDS: [NQ * 32 * WAVES][list slots] lists, then two stage buffers of STAGE bytes.
-// SEL (KN_SEL_*) selects how keys wait for their list: KN_SEL_REG (knn <= KN_REG_KNN) leaves LDS for
-// the lists of twice as many queries, so NQ = 2 and every operand read from LDS feeds two MFMAs;
-// KN_SEL_LDS (knn <= KN_BUFFERED_KNN) and sorted insertion run with NQ = 1.
+// SEL (KN_SEL_*) selects how keys wait for their list.
 template <int DT, int NQ, int WAVES, int SEL, int STAGE>
 __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     const void* __restrict__ K, const void* __restrict__ Q, const u64* __restrict__ order,
-    int64_t order_stride, int n_q, int n_kv, int64_t N, int64_t M, int knn,
-    int32_t* __restrict__ L_out) {
+    int64_t order_stride, int g0, int n_q, int n_kv, int64_t N, int64_t n_stream, int64_t M, int knn,
+    int32_t* __restrict__ L_out, float* __restrict__ scores, const int* __restrict__ resume, int resume_queries,
+    int resume_blocks) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     constexpr int KN_THREADS = WAVES * RA_WAVE;
     constexpr int QPW = 32 * NQ, QPB = QPW * WAVES;
@@ -285,14 +239,14 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     static_assert(SBLK == 1 || SBLK == 2, "a stage holds one or two key blocks");
     static_assert(CPT * KN_THREADS * 16 == STAGE, "threads must tile a stage");
     static_assert(KN_THREADS % CPR == 0, "a thread keeps its 16-byte column");
-    constexpr bool BUF = SEL != KN_SEL_INSERT, REGP = SEL == KN_SEL_REG;
-    const int lstride = REGP ? KN_REG_KNN : BUF ? KN_CAP : knn;           // list slots per query
-    const int pend = REGP ? KN_REG_PEND : (KN_CAP - knn) / 2;             // pending keys a lane can hold (BUF)
+    constexpr bool BUF = SEL != KN_SEL_INSERT;
+    const int lstride = BUF ? KN_CAP : knn;           // list slots per query
+    const int pend = (KN_CAP - knn) / 2;                      // pending keys a lane can hold (BUF)
     u64* lists = reinterpret_cast<u64*>(lds_raw);           // [QPB][lstride]
     unsigned char* stage_buf = lds_raw + (size_t)QPB * lstride * sizeof(u64);   // 16-byte aligned: QPB is even
     const int tid = threadIdx.x, wv = tid / RA_WAVE, lane = tid % RA_WAVE;
     const int col = lane & 31, half = lane >> 5;
-    const int graph = blockIdx.y, seq = graph / n_q, h = graph % n_q, kvh = h / (n_q / n_kv);
+    const int graph = g0 + (int)blockIdx.y, seq = graph / n_q, h = graph % n_q, kvh = h / (n_q / n_kv);
     const size_t esz = DT == RA_BF16 ? 2 : 4;
     const char* Kh = reinterpret_cast<const char*>(K) + ((size_t)seq * n_kv + kvh) * N * RA_D * esz;
     const char* Qh = reinterpret_cast<const char*>(Q) + (size_t)graph * M * RA_D * esz;
@@ -300,10 +254,27 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     // the key streamed p-th: the low word of the head's p-th order entry (used as loaded: arithmetic
     // on it would sit right behind the load and wait for it)
     const int* ord = reinterpret_cast<const int*>(order + (size_t)graph * order_stride);
-    const int last_pos = (int)N - 1;               // ids and stream positions fit 31 bits
+    const int last_pos = (int)n_stream - 1;               // ids and stream positions fit 31 bits
     auto stream_id = [&](int p) __attribute__((always_inline)) { return ord[2 * (size_t)(unsigned)(p < last_pos ? p : last_pos)]; };
 
-    for (int i = tid; i < QPB * lstride; i += KN_THREADS) lists[i] = 0ull;
+    int64_t st0 = 0;                               // first stage
+    if (resume) {
+        const int64_t pos0 = resume[(size_t)blockIdx.y * resume_blocks + (int64_t)blockIdx.x * QPB / resume_queries];
+        if (pos0 >= n_stream) return;              // (the whole workgroup)
+        st0 = pos0 / SROWS;
+    }
+    for (int i = tid; i < QPB * lstride; i += KN_THREADS) {
+        u64 k = 0ull;
+        if (resume) {
+            const int64_t qr = (int64_t)blockIdx.x * QPB + i / lstride;
+            const int e = i % lstride;
+            if (qr < M && e < knn) {
+                const float sc = scores[((size_t)blockIdx.y * M + qr) * knn + e];
+                if (sc > -INFINITY) k = knn_key(sc, L_out[((size_t)graph * M + qr) * knn + e]);
+            }
+        }
+        lists[i] = k;
+    }
     u64* my_lists = lists + (size_t)wv * QPW * lstride;
 
     Operand<DT> b[NQ];
@@ -319,17 +290,15 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
 
     float tau[NQ];
     int fill[NQ];                                  // BUF: keys in this lane's pending run
-    u64 pr[NQ][KN_REG_PEND];                       // REGP: the run itself
 #pragma unroll
     for (int sidx = 0; sidx < NQ; ++sidx) {
-        tau[sidx] = -INFINITY;
+        const u64 last = my_lists[(sidx * 32 + col) * lstride + knn - 1];     // (zero but for a resumed stream)
+        tau[sidx] = last == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(last >> 32));
         fill[sidx] = 0;
-#pragma unroll
-        for (int k = 0; k < KN_REG_PEND; ++k) pr[sidx][k] = 0ull;
     }
 
     static_assert(CPT == 2 || CPT == 4, "two or four chunks per thread and stage");
-    const int64_t nstage = (N + SROWS - 1) / SROWS;
+    const int64_t nstage = (n_stream + SROWS - 1) / SROWS;
     struct Held { u32x4 c0, c1, c2, c3; };         // a thread's share of one stage, in registers
     struct Rows { int r0, r1, r2, r3; };           // key ids of the rows that share comes from
     constexpr int RSTEP = KN_THREADS / CPR;        // rows between two chunks of a thread
@@ -374,10 +343,10 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
 #pragma unroll
         for (int sidx = 0; sidx < NQ; ++sidx) {
             f32x16& cs = c[sidx];
-            if (kbase + 32 > N) {                  // ragged tail: rows beyond N never qualify
+            if (kbase + 32 > n_stream) {           // ragged tail: rows beyond the stream never qualify
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    if (kbase + (r / 4) * 8 + half * 4 + (r % 4) >= N) cs[r] = -INFINITY;
+                    if (kbase + (r / 4) * 8 + half * 4 + (r % 4) >= n_stream) cs[r] = -INFINITY;
             }
             if constexpr (BUF) {
                 float gm[4];
@@ -399,11 +368,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
                     u64 need = __ballot(fill[sidx] + n4 > pend);
                     while (need) {
                         const int jq = (__ffsll((long long)need) - 1) & 31;
-                        float nt;
-                        if constexpr (REGP)
-                            nt = knn_fold_reg(set_lists + (size_t)jq * KN_REG_KNN, knn, lane, jq, pr[sidx], fill[sidx]);
-                        else
-                            nt = knn_fold(set_lists + (size_t)jq * KN_CAP, knn, lane);
+                        const float nt = knn_fold(set_lists + (size_t)jq * KN_CAP, knn, lane);
                         if (col == jq) { tau[sidx] = nt; fill[sidx] = 0; }
                         need &= need - 1;
                         need &= ~(1ull << (jq + 32)) & ~(1ull << jq);
@@ -417,14 +382,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
                             const int lo = __builtin_amdgcn_readlane(ids, row);
                             const int hi = __builtin_amdgcn_readlane(ids, row + 4);
                             const u64 nk = knn_key(cs[r], lo ^ ((lo ^ hi) & -half));
-                            if constexpr (REGP) {
-#pragma unroll
-                                for (int k = 0; k < KN_REG_PEND; ++k)
-                                    pr[sidx][k] = fill[sidx] == k ? nk : pr[sidx][k];
-                                fill[sidx]++;
-                            } else if (fill[sidx] < pend) {      // always, for scores that are numbers
-                                mine[fill[sidx]++] = nk;
-                            }
+                            if (fill[sidx] < pend) mine[fill[sidx]++] = nk;      // always, for scores that are numbers
                         }
                     }
                 }
@@ -463,7 +421,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
             Operand<DT> a1;
             read_operand<DT>(lds_raw, a_at, cur + 32 * ROWB, a1);
             process(a0, st * 2, ids, 0);
-            process(a1, st * 2 + 1, ids, 32);   // a block at or beyond N is all masked
+            process(a1, st * 2 + 1, ids, 32);   // a block beyond the stream is all masked
         } else {
             process(a0, st, ids, 0);
         }
@@ -482,17 +440,17 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     int ida, idb;
     {
         Rows r1, r2;
-        load_rows(ra, 0);
-        load_rows(r1, 1);
-        load_rows(r2, 2);
+        load_rows(ra, st0);
+        load_rows(r1, st0 + 1);
+        load_rows(r2, st0 + 2);
         fetch_stage(ha, ra);
         store_stage(ha, stage_buf);
-        ida = stage_ids(0);
+        ida = stage_ids(st0);
         fetch_stage(ha, r1);
-        load_rows(ra, 3);
-        idb = stage_ids(1);
+        load_rows(ra, st0 + 3);
+        idb = stage_ids(st0 + 1);
         fetch_stage(hb, r2);
-        load_rows(rb, 4);
+        load_rows(rb, st0 + 4);
         if constexpr (CPT == 4)
             asm volatile("; lead-in loads complete" ::"v"(ha.c0), "v"(ha.c1), "v"(ha.c2), "v"(ha.c3),
                          "v"(hb.c0), "v"(hb.c1), "v"(hb.c2), "v"(hb.c3), "v"(ra.r0), "v"(ra.r1), "v"(ra.r2),
@@ -502,7 +460,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
                          "v"(ra.r0), "v"(ra.r1), "v"(rb.r0), "v"(rb.r1), "v"(ida), "v"(idb));
     }
     __syncthreads();
-    for (int64_t st = 0; st < nstage; st += 2) {
+    for (int64_t st = st0; st < nstage; st += 2) {
         multiply_stage(0, st, ida);
         store_stage(ha, stage_buf + STAGE);             // stage st + 1
         __syncthreads();
@@ -525,61 +483,126 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
             const int64_t qr = q0 + jq;
             if (qr >= M) break;
             u64* lst = my_lists + (size_t)jq * lstride;
-            if constexpr (REGP)
-                knn_fold_reg(lst, knn, lane, j, pr[sidx], fill[sidx]);
-            else if constexpr (BUF)
+            if constexpr (BUF)
                 knn_fold(lst, knn, lane);
-            if (lane < knn) L_out[((size_t)graph * M + qr) * knn + lane] = knn_key_id(lst[lane]);
+            if (lane < knn) {
+                const u64 k = lst[lane];
+                L_out[((size_t)graph * M + qr) * knn + lane] = knn_key_id(k);
+                if (scores && !resume)             // only the first part of the stream: it goes on with these
+                    scores[((size_t)blockIdx.y * M + qr) * knn + lane] =
+                        k == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(k >> 32));
+            }
         }
     }
 }
 
+// graphs [g0, g0 + n_graphs) of the call
+struct KnnCall {
+    const void *K, *Q, *order;
+    int g0, n_graphs, n_q, n_kv;
+    int64_t N, n_stream, M;
+    int knn;
+    int32_t* L;
+    float* scores;
+    hipStream_t st;
+    const int* resume;
+    int resume_queries, resume_blocks;
+};
 template <int DT, int NQ, int WAVES, int SEL, int STAGE>
-static ra_status knn_launch_as(const void* K, const void* Q, const void* order, int n_seq, int n_q, int n_kv,
-                               int64_t N, int64_t M, int knn, hipStream_t st, int32_t* L) {
+static ra_status knn_launch_as(const KnnCall& c) {
     constexpr int QPB = 32 * NQ * WAVES;
-    const int slots = SEL == KN_SEL_REG ? KN_REG_KNN : SEL == KN_SEL_LDS ? KN_CAP : knn;
+    const int slots = SEL == KN_SEL_LDS ? KN_CAP : c.knn;
     const size_t lds = (size_t)QPB * slots * sizeof(u64) + 2 * STAGE;
     if (lds > RA_LDS_LIMIT)
-        RA_FAIL(RA_EUNSUP, "knn %d needs %zu bytes of LDS (limit %d)", knn, lds, RA_LDS_LIMIT);
+        RA_FAIL(RA_EUNSUP, "knn %d needs %zu bytes of LDS (limit %d)", c.knn, lds, RA_LDS_LIMIT);
     RA_LDS_OPT_IN((knn_kernel<DT, NQ, WAVES, SEL, STAGE>), lds);
-    const dim3 grid((unsigned)((M + QPB - 1) / QPB), (unsigned)(n_seq * n_q));
-    hipLaunchKernelGGL((knn_kernel<DT, NQ, WAVES, SEL, STAGE>), grid, dim3(WAVES * RA_WAVE), lds, st, K, Q,
-                       reinterpret_cast<const u64*>(order), ra_knn_order_stride(N), n_q, n_kv, N, M, knn, L);
+    const dim3 grid((unsigned)((c.M + QPB - 1) / QPB), (unsigned)c.n_graphs);
+    hipLaunchKernelGGL((knn_kernel<DT, NQ, WAVES, SEL, STAGE>), grid, dim3(WAVES * RA_WAVE), lds, c.st, c.K, c.Q,
+                       reinterpret_cast<const u64*>(c.order), ra_knn_order_stride(c.N), c.g0, c.n_q, c.n_kv, c.N,
+                       c.n_stream, c.M, c.knn, c.L, c.scores, c.resume, c.resume_queries, c.resume_blocks);
     RA_HIP(hipGetLastError());
     return RA_OK;
 }
 
-// RA_TEST_KNN_SELECTION (ra_test_configure): which top-knn selection bf16 lists of up to 32 keys use
+// RA_TEST_KNN_SELECTION (ra_test_configure): whether the 8-bit products take the rest of the stream
 static int g_knn_selection_override = RA_TEST_KNN_AUTO;
 void ra_knn_set_selection_override(int v) { g_knn_selection_override = v; }
 
-// bf16: 8 wavefronts per workgroup (one workgroup per compute unit, two wavefronts per SIMD). Lists of
-// up to 32 keys: two sets of 32 queries per wavefront, 512 queries x 32 slots x 8 bytes of lists
-// beside the stage buffers, pending keys in registers. Up to 48 keys: one set per wavefront, 256
-// queries x 64 slots. fp32 operands take twice the registers: 4 wavefronts, one set each.
+// bf16: 8 wavefronts per workgroup (one workgroup per compute unit, two wavefronts per SIMD), 256
+// queries x 64 list slots of 8 bytes beside the stage buffers for lists of up to 48 keys, knn slots for
+// longer ones. fp32 operands take twice the registers: 4 wavefronts.
+static ra_status knn_launch(const KnnCall& c, ra_dtype dt) {
+    const bool buf = c.knn <= KN_BUFFERED_KNN;
+    if (dt == RA_BF16) {
+        if (buf) return knn_launch_as<RA_BF16, 1, 8, KN_SEL_LDS, 16384>(c);
+        return knn_launch_as<RA_BF16, 1, 8, KN_SEL_INSERT, 16384>(c);
+    }
+    if (buf) return knn_launch_as<RA_F32, 1, 4, KN_SEL_LDS, 16384>(c);
+    return knn_launch_as<RA_F32, 1, 4, KN_SEL_INSERT, 16384>(c);
+}
+
+// Keys of the stream that are multiplied as they are before knn_filter.hip takes over (N: all of them).
+// A thirty-second of the stream, and at least enough that thresholds are near final (in the filter a
+// kept key costs about ten ruled-out ones). The filter pays where what it saves on N x M products
+// exceeds what packing N keys and M queries costs: bf16 halves the time of a product (32 heads of 36 K
+// keys: 10.6 -> 7.0 ms with 32 K queries, 3.4 -> 2.7 ms with 8 K, but 1.2 -> 1.5 ms with 2 K; 72 K keys
+// gain with 512 queries already, 2.8 -> 2.3 ms), float32 products cost sixteen times the 8-bit ones
+// (9 K keys, 512 queries: 0.95 -> 0.67 ms; 4 K keys gain little either way).
+static int64_t knn_first_keys(ra_dtype dt, int64_t N, int64_t M) {
+    int64_t first = dt == RA_BF16 ? 4096 : 2048;
+    if (g_knn_selection_override == RA_TEST_KNN_LDS) return N;
+    if (g_knn_selection_override == RA_TEST_KNN_FILTER) return N > 128 ? 128 : N;
+    if (dt == RA_BF16 ? !(N >= 49152 || (N >= 16384 && M >= 8192)) : N < 8192) return N;
+    if (first < N / 32) first = N / 32;
+    return (first + 127) & ~(int64_t)127;
+}
+// graphs whose 8-bit copies and scores are in memory at one time
+static int knn_graphs_at_once(int graphs, int64_t N, int64_t M, int knn) {
+    const size_t one = ra_knn_filter_bytes(1, N, M, knn), most = (size_t)3 << 29;
+    const size_t fit = most / one < 1 ? 1 : most / one;
+    const int calls = (int)((graphs + fit - 1) / fit);
+    return (graphs + calls - 1) / calls;
+}
+static size_t align_256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// the stream order, then (where the filter is used) the column maxima of the KV heads and the
+// filter's own workspace
+size_t ra_knn_workspace_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn) {
+    const int graphs = n_seq * n_q;
+    size_t b = align_256(ra_knn_order_bytes(graphs, N));
+    if (knn_first_keys(dt, N, M) < N)
+        b += align_256((size_t)n_seq * n_kv * RA_D * 4) +
+             ra_knn_filter_bytes(knn_graphs_at_once(graphs, N, M, knn), N, M, knn);
+    return b;
+}
+
 ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
                         int64_t N, int64_t M, int knn, void* workspace, hipStream_t st, int32_t* L) {
     // the order the keys are streamed in (knn_order.hip), at the start of the workspace
     ra_status rc = ra_launch_knn_order(K, Q, dt, n_seq, n_q, n_kv, N, M, workspace, st);
     if (rc != RA_OK) return rc;
-    const bool buf = knn <= KN_BUFFERED_KNN;
-    // Pending keys in registers: a fold takes 8 keys at most instead of 32, so the start of the stream,
-    // where nearly every key reaches the thresholds, costs more (about 14 ms instead of 6 ms for
-    // 32 heads x 131072 queries), and every later key less (0.80 us instead of 0.95 us): it pays
-    // from about 50 K keys on. The test-only setting RA_TEST_KNN_SELECTION overrides the choice (the
-    // tests run both on small inputs).
-    bool reg = knn <= KN_REG_KNN && N >= KN_REG_MIN_KEYS;
-    if (g_knn_selection_override == RA_TEST_KNN_REG) reg = knn <= KN_REG_KNN;
-    else if (g_knn_selection_override == RA_TEST_KNN_LDS) reg = false;
-    if (dt == RA_BF16) {
-        if (reg)
-            return knn_launch_as<RA_BF16, 2, 8, KN_SEL_REG, 16384>(K, Q, workspace, n_seq, n_q, n_kv, N, M, knn, st, L);
-        if (buf)
-            return knn_launch_as<RA_BF16, 1, 8, KN_SEL_LDS, 16384>(K, Q, workspace, n_seq, n_q, n_kv, N, M, knn, st, L);
-        return knn_launch_as<RA_BF16, 1, 8, KN_SEL_INSERT, 16384>(K, Q, workspace, n_seq, n_q, n_kv, N, M, knn, st, L);
+    const int graphs = n_seq * n_q;
+    const int64_t first = knn_first_keys(dt, N, M);
+    KnnCall c{K, Q, workspace, 0, graphs, n_q, n_kv, N, first, M, knn, L, nullptr, st, nullptr, 0, 0};
+    if (first == N) return knn_launch(c, dt);
+    char* ws = reinterpret_cast<char*>(workspace) + align_256(ra_knn_order_bytes(graphs, N));
+    uint32_t* maxabs = reinterpret_cast<uint32_t*>(ws);
+    ws += align_256((size_t)n_seq * n_kv * RA_D * 4);
+    rc = ra_launch_knn_filter_scales(K, dt, n_seq * n_kv, N, maxabs, st);
+    const int most = knn_graphs_at_once(graphs, N, M, knn);
+    for (int g0 = 0; g0 < graphs && rc == RA_OK; g0 += most) {
+        c.g0 = g0;
+        c.n_graphs = graphs - g0 < most ? graphs - g0 : most;
+        c.scores = ra_knn_filter_scores(ws, c.n_graphs, N, M, knn);
+        c.n_stream = first;
+        c.resume = nullptr;
+        rc = knn_launch(c, dt);
+        if (rc != RA_OK) return rc;
+        rc = ra_launch_knn_filter(K, Q, dt, workspace, g0, c.n_graphs, n_q, n_kv, N, M, knn, first, maxabs, ws, st, L,
+                                  &c.resume, &c.resume_queries, &c.resume_blocks);
+        if (rc != RA_OK) return rc;
+        c.n_stream = N;                            // where the filter gave up (seldom): the stream to its end
+        rc = knn_launch(c, dt);
     }
-    if (buf)
-        return knn_launch_as<RA_F32, 1, 4, KN_SEL_LDS, 16384>(K, Q, workspace, n_seq, n_q, n_kv, N, M, knn, st, L);
-    return knn_launch_as<RA_F32, 1, 4, KN_SEL_INSERT, 16384>(K, Q, workspace, n_seq, n_q, n_kv, N, M, knn, st, L);
+    return rc;
 }

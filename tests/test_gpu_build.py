@@ -259,3 +259,28 @@ def test_build_argument_errors():
     with pytest.raises(ra.RaError) as e:
         ra.ra_build_index(Kd[..., :64].contiguous(), Qd[..., :64].contiguous(), 8, 4)   # d != 128
     assert e.value.status == 6
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("N,M,knn", [(129, 1, 1), (160, 255, 32), (255, 257, 64), (4097, 300, 48), (1024, 1025, 33),
+                                     (70000, 96, 32)])
+def test_knn_through_8bit_products(dtype, N, M, knn):
+    """The later part of the key stream ruled out by 8-bit products (from the 129th key on): one key or a
+    ragged stage past the first part, fewer queries than a set, sets and workgroups that end
+    ragged, lists of every selection, and (knn 64 of 255 keys) keys the bound cannot rule out, where the
+    filter gives up and the stream goes on without it. The lists are those of the whole stream, bit for
+    bit, and the oracle's."""
+    from paper_2409_10516_amd import binding as B
+    w = synth.make_llama_layer(N + knn, N, M, n_seq=2, n_q=2, n_kv=1, dtype=dtype)
+    K, Q = w.K.to(DEV), w.Q_prefill.to(DEV)
+    L = {}
+    try:
+        for how in (B.RA_TEST_KNN_LDS, B.RA_TEST_KNN_REG):
+            ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, how)
+            L[how] = ra.ra_knn(K, Q, knn).cpu().numpy()
+    finally:
+        ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_AUTO)
+    assert np.array_equal(L[B.RA_TEST_KNN_LDS], L[B.RA_TEST_KNN_REG])
+    assert np.array_equal(L[B.RA_TEST_KNN_LDS], ra.ra_knn(K, Q, knn).cpu().numpy())
+    Kn, Qn = to_np(w.K[1, 0]), to_np(w.Q_prefill[1, 1][:40])
+    knn_equivalent(L[B.RA_TEST_KNN_REG][1, 1][:40], OM.knn_lists(Qn, Kn, knn)[0], Qn, Kn)
