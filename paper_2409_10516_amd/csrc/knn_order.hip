@@ -22,30 +22,50 @@ typedef unsigned long long u64;
 #define KO_CHUNK 8192             // sort keys a workgroup holds in LDS (64 KB)
 #define KO_THREADS 1024
 
-// grid: x = head. thread = (slice, dimension): slice s sums samples s, s + 8, ... in that order,
-// then the 8 slices are added in order.
+template <int DT>
+__device__ __forceinline__ void ko_row8(const void* base, size_t at, float (&v)[8]) {
+    if constexpr (DT == RA_BF16) {
+        const uint4 u = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(base) + at);
+        v[0] = bf16_lo(u.x); v[1] = bf16_hi(u.x); v[2] = bf16_lo(u.y); v[3] = bf16_hi(u.y);
+        v[4] = bf16_lo(u.z); v[5] = bf16_hi(u.z); v[6] = bf16_lo(u.w); v[7] = bf16_hi(u.w);
+    } else {
+        const float4 a = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + at);
+        const float4 b = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + at + 4);
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    }
+}
+
+// grid: x = head. 16 lanes per query row; lane group s sums samples s, s + 64, ... eight rows in flight
+// (a serial sum of rows, one at a time, was 265 us of latency whatever the size of the input).
 template <int DT>
 __global__ __launch_bounds__(KO_THREADS) void ko_meanq_kernel(const void* __restrict__ Q, int64_t M,
                                                               float* __restrict__ mq) {
-    __shared__ float part[KO_THREADS];
-    const int graph = blockIdx.x, d = threadIdx.x % RA_D, s = threadIdx.x / RA_D;
-    constexpr int SLICES = KO_THREADS / RA_D;
-    const int64_t n_s = M < KO_SAMPLE ? M : KO_SAMPLE;
-    float acc = 0.f;
-    for (int64_t k = s; k < n_s; k += SLICES) {
-        const int64_t j = k * M / n_s;
-        const size_t at = ((size_t)graph * M + j) * RA_D + d;
-        if constexpr (DT == RA_BF16)
-            acc += __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(Q)[at] << 16);
-        else
-            acc += reinterpret_cast<const float*>(Q)[at];
+    constexpr int GROUPS = KO_THREADS / 16, FLY = 8;
+    __shared__ float part[GROUPS][RA_D];
+    const int graph = blockIdx.x, l16 = threadIdx.x & 15, s = threadIdx.x / 16;
+    const int n_s = M < KO_SAMPLE ? (int)M : KO_SAMPLE;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int k0 = s; k0 < n_s; k0 += FLY * GROUPS) {
+        float v[FLY][8];
+#pragma unroll
+        for (int u = 0; u < FLY; ++u) {
+            const int k = k0 + u * GROUPS < n_s ? k0 + u * GROUPS : k0;
+            const int64_t j = M <= KO_SAMPLE ? k : (int64_t)k * M / KO_SAMPLE;
+            ko_row8<DT>(Q, ((size_t)graph * M + j) * RA_D + 8 * l16, v[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < FLY; ++u)
+            if (k0 + u * GROUPS < n_s)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) acc[c] += v[u][c];
     }
-    part[threadIdx.x] = acc;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) part[s][8 * l16 + c] = acc[c];
     __syncthreads();
-    if (s == 0) {
+    if (threadIdx.x < RA_D) {
         float t = 0.f;
-        for (int i = 0; i < SLICES; ++i) t += part[i * RA_D + d];
-        mq[(size_t)graph * RA_D + d] = t;
+        for (int i = 0; i < GROUPS; ++i) t += part[i][threadIdx.x];
+        mq[(size_t)graph * RA_D + threadIdx.x] = t;
     }
 }
 
@@ -63,15 +83,7 @@ __global__ __launch_bounds__(KO_THREADS) void ko_proxy_kernel(const void* __rest
     const float* m = mq + (size_t)graph * RA_D + 8 * l16;
     const size_t at = (((size_t)seq * n_kv + kvh) * N + row) * RA_D + 8 * l16;
     float k[8];
-    if constexpr (DT == RA_BF16) {
-        const uint4 u = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(K) + at);
-        k[0] = bf16_lo(u.x); k[1] = bf16_hi(u.x); k[2] = bf16_lo(u.y); k[3] = bf16_hi(u.y);
-        k[4] = bf16_lo(u.z); k[5] = bf16_hi(u.z); k[6] = bf16_lo(u.w); k[7] = bf16_hi(u.w);
-    } else {
-        const float4 a = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(K) + at);
-        const float4 b = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(K) + at + 4);
-        k[0] = a.x; k[1] = a.y; k[2] = a.z; k[3] = a.w; k[4] = b.x; k[5] = b.y; k[6] = b.z; k[7] = b.w;
-    }
+    ko_row8<DT>(K, at, k);
     float p = 0.f;
 #pragma unroll
     for (int c = 0; c < 8; ++c) p += k[c] * m[c];
@@ -94,15 +106,30 @@ __device__ __forceinline__ void ko_exchange(u64* s, int e, int j, bool ascending
     if ((a > b) == ascending) { s[e] = b; s[e | j] = a; }
 }
 
-// grid: x = chunk, y = head. k_first == 0: sorts the chunk (all k up to its length); otherwise
+// How many keys of array y there are to sort: `counts` (one int every count_stride) or all N_pad. The
+// network runs over the smallest power of two of them; what it would do beyond is skipped, and the
+// first pass over a chunk takes places beyond the count for all-ones keys.
+__device__ __forceinline__ int64_t ko_count(const int32_t* counts, size_t count_stride, int64_t N_pad) {
+    return counts ? counts[(size_t)blockIdx.y * count_stride] : N_pad;
+}
+__device__ __forceinline__ int64_t ko_run(int64_t n) {
+    return n <= 1 ? 1 : (int64_t)1 << (64 - __clzll((long long)(n - 1)));
+}
+
+// grid: x = chunk, y = array. k_first == 0: sorts the chunk (all k up to its length); otherwise
 // finishes stage k_first of the global network (j from half a chunk down to 1).
-__global__ __launch_bounds__(KO_THREADS) void ko_sort_chunk_kernel(u64* __restrict__ keys, int64_t N_pad,
-                                                                   int chunk, int64_t k_first) {
+__global__ __launch_bounds__(KO_THREADS) void ko_sort_chunk_kernel(u64* __restrict__ keys, size_t stride,
+                                                                   int64_t N_pad, int chunk, int64_t k_first,
+                                                                   const int32_t* __restrict__ counts,
+                                                                   size_t count_stride) {
     extern __shared__ __align__(16) unsigned char ko_lds[];
     u64* s = reinterpret_cast<u64*>(ko_lds);
     const int64_t base = (int64_t)blockIdx.x * chunk;
-    u64* g = keys + (size_t)blockIdx.y * N_pad + base;
-    for (int e = threadIdx.x; e < chunk; e += KO_THREADS) s[e] = g[e];
+    const int64_t n = ko_count(counts, count_stride, N_pad), run = ko_run(n);
+    if (base >= run || k_first > run) return;            // (the whole workgroup)
+    if (chunk > run) chunk = (int)run;
+    u64* g = keys + (size_t)blockIdx.y * stride + base;
+    for (int e = threadIdx.x; e < chunk; e += KO_THREADS) s[e] = k_first || base + e < n ? g[e] : ~0ull;
     __syncthreads();
     const int pairs = chunk / 2;
     for (int64_t k = k_first ? k_first : 2; k_first ? k == k_first : k <= chunk; k <<= 1) {
@@ -118,19 +145,45 @@ __global__ __launch_bounds__(KO_THREADS) void ko_sort_chunk_kernel(u64* __restri
     for (int e = threadIdx.x; e < chunk; e += KO_THREADS) g[e] = s[e];
 }
 
-// grid: x = block of KO_THREADS pairs, y = head: the exchange at distance j >= chunk of stage k.
-__global__ __launch_bounds__(KO_THREADS) void ko_sort_far_kernel(u64* __restrict__ keys, int64_t N_pad,
-                                                                 int64_t k, int64_t j) {
+// grid: x = block of KO_THREADS pairs, y = array: the exchange at distance j >= chunk of stage k.
+__global__ __launch_bounds__(KO_THREADS) void ko_sort_far_kernel(u64* __restrict__ keys, size_t stride,
+                                                                 int64_t N_pad, int64_t k, int64_t j,
+                                                                 const int32_t* __restrict__ counts,
+                                                                 size_t count_stride) {
     const int64_t t = (int64_t)blockIdx.x * KO_THREADS + threadIdx.x;
-    if (t >= N_pad / 2) return;
+    const int64_t run = ko_run(ko_count(counts, count_stride, N_pad));
+    if (k > run || t >= run / 2) return;
     const int64_t e = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-    u64* g = keys + (size_t)blockIdx.y * N_pad;
+    u64* g = keys + (size_t)blockIdx.y * stride;
     const u64 a = g[e], b = g[e | j];
     const bool ascending = (e & k) == 0;
     if ((a > b) == ascending) { g[e] = b; g[e | j] = a; }
 }
 
-static int64_t ko_padded(int64_t N) {
+// Ascending sort of n_arrays arrays of 64-bit keys, `stride` keys apart, of N_pad (a power of two)
+// places each; `counts` (device, one int every count_stride): how many keys each holds, or null: N_pad.
+ra_status ra_launch_sort(void* keys, size_t stride, int n_arrays, int64_t N_pad, const int32_t* counts,
+                         size_t count_stride, hipStream_t st) {
+    u64* k64 = reinterpret_cast<u64*>(keys);
+    const int chunk = (int)(N_pad < KO_CHUNK ? N_pad : KO_CHUNK);
+    const size_t lds = (size_t)chunk * sizeof(u64);
+    const dim3 cgrid((unsigned)(N_pad / chunk), (unsigned)n_arrays);
+    const dim3 fgrid((unsigned)((N_pad / 2 + KO_THREADS - 1) / KO_THREADS), (unsigned)n_arrays);
+    RA_LDS_OPT_IN(ko_sort_chunk_kernel, lds);
+    hipLaunchKernelGGL(ko_sort_chunk_kernel, cgrid, dim3(KO_THREADS), lds, st, k64, stride, N_pad, chunk, (int64_t)0,
+                       counts, count_stride);
+    for (int64_t k = 2 * (int64_t)chunk; k <= N_pad; k <<= 1) {
+        for (int64_t j = k / 2; j >= chunk; j >>= 1)
+            hipLaunchKernelGGL(ko_sort_far_kernel, fgrid, dim3(KO_THREADS), 0, st, k64, stride, N_pad, k, j, counts,
+                               count_stride);
+        hipLaunchKernelGGL(ko_sort_chunk_kernel, cgrid, dim3(KO_THREADS), lds, st, k64, stride, N_pad, chunk, k,
+                           counts, count_stride);
+    }
+    RA_HIP(hipGetLastError());
+    return RA_OK;
+}
+
+int64_t ra_sort_padded(int64_t N) {
     int64_t p = 2;
     while (p < N) p <<= 1;
     return p;
@@ -138,10 +191,10 @@ static int64_t ko_padded(int64_t N) {
 
 // [n_graphs][N_pad] sort keys, then [n_graphs][RA_D] query sums
 size_t ra_knn_order_bytes(int n_graphs, int64_t N) {
-    return (size_t)n_graphs * ((size_t)ko_padded(N) * sizeof(u64) + RA_D * sizeof(float));
+    return (size_t)n_graphs * ((size_t)ra_sort_padded(N) * sizeof(u64) + RA_D * sizeof(float));
 }
 
-int64_t ra_knn_order_stride(int64_t N) { return ko_padded(N); }
+int64_t ra_knn_order_stride(int64_t N) { return ra_sort_padded(N); }
 
 // Fills workspace with the stream order of every head: entry p of head g, at
 // workspace[g * ra_knn_order_stride(N) + p], holds the id of the key streamed p-th in its low word.
@@ -149,7 +202,7 @@ ra_status ra_launch_knn_order(const void* K, const void* Q, ra_dtype dt, int n_s
                               int64_t N, int64_t M, void* workspace, hipStream_t st) {
     const int graphs = n_seq * n_q;
     if (graphs > 65535) RA_FAIL(RA_EUNSUP, "more than 65535 (sequence, query head) pairs");
-    const int64_t N_pad = ko_padded(N);
+    const int64_t N_pad = ra_sort_padded(N);
     u64* keys = reinterpret_cast<u64*>(workspace);
     float* mq = reinterpret_cast<float*>(keys + (size_t)graphs * N_pad);
     const dim3 pgrid((unsigned)((N_pad + KO_THREADS / 16 - 1) / (KO_THREADS / 16)), (unsigned)graphs);
@@ -162,17 +215,6 @@ ra_status ra_launch_knn_order(const void* K, const void* Q, ra_dtype dt, int n_s
         hipLaunchKernelGGL(ko_proxy_kernel<RA_F32>, pgrid, dim3(KO_THREADS), 0, st, K, mq, n_q, n_kv, N,
                            N_pad, keys);
     }
-    const int chunk = (int)(N_pad < KO_CHUNK ? N_pad : KO_CHUNK);
-    const size_t lds = (size_t)chunk * sizeof(u64);
-    const dim3 cgrid((unsigned)(N_pad / chunk), (unsigned)graphs);
-    const dim3 fgrid((unsigned)((N_pad / 2 + KO_THREADS - 1) / KO_THREADS), (unsigned)graphs);
-    RA_LDS_OPT_IN(ko_sort_chunk_kernel, lds);
-    hipLaunchKernelGGL(ko_sort_chunk_kernel, cgrid, dim3(KO_THREADS), lds, st, keys, N_pad, chunk, (int64_t)0);
-    for (int64_t k = 2 * (int64_t)chunk; k <= N_pad; k <<= 1) {
-        for (int64_t j = k / 2; j >= chunk; j >>= 1)
-            hipLaunchKernelGGL(ko_sort_far_kernel, fgrid, dim3(KO_THREADS), 0, st, keys, N_pad, k, j);
-        hipLaunchKernelGGL(ko_sort_chunk_kernel, cgrid, dim3(KO_THREADS), lds, st, keys, N_pad, chunk, k);
-    }
     RA_HIP(hipGetLastError());
-    return RA_OK;
+    return ra_launch_sort(keys, (size_t)N_pad, graphs, N_pad, nullptr, 0, st);
 }

@@ -12,152 +12,180 @@
 // Device plan, all stream-ordered, no host round trip:
 //   1. pop by atomic histogram over the list cells, through a per-workgroup LDS table so that a
 //      hub costs one atomic per workgroup instead of one per list.
-//   2. one workgroup per graph: prefix sums over the keys (CSR offsets of the inverted lists,
-//      compaction of the keys with pop > 0), a stable 4-bit LSD radix sort of those keys by
-//      descending pop, and from it pi, its inverse pos, pop by position, and the entry point.
+//   2. pi: the populated keys are compacted in id order (a count per block of keys, then every block
+//      adds up the counts before its own), their [M - pop : id] keys sorted (bitonic, the network of
+//      knn_order.hip: as many stages as the number of populated keys needs, which only the device
+//      knows), and pi, its inverse pos and the popularity by position written from that. Keys without
+//      a list follow in id order.
 //   3. inverted lists (key -> the lists that hold it) filled through per-key cursors (ranges
 //      reserved per workgroup through the same kind of LDS table), and a copy of the lists with
 //      every key replaced by its position in pi.
-//   4. backbone children and -1 padding for every row (fully coalesced).
-//   5. rows of the populated keys, in pi order (largest first). For key a: stream the lists that
-//      hold a (whole rows of the translated lists, coalesced), count each co-listed key, collect
-//      the candidates with (count, popularity, id), and select the best 64 in rank order: 64
-//      candidates at a time go through a bitonic network across the lanes of a wavefront
-//      (fractions compared by 64-bit cross-multiplication) and are merged into its running best
-//      64; chunks that cannot beat the 64th are skipped. Three regimes by the number of lists:
-//        - few (lists x knn <= 1024): one key per wavefront, counts in an LDS hash table, no
-//          workgroup barrier (pj_rows_small_kernel);
-//        - the rest: one key per workgroup (pj_rows_kernel), counts in an LDS table indexed by
-//          position when the graph has at most 8192 populated keys, else in an LDS hash table
-//          (moderate keys) or in the workgroup's scratch in device memory (hubs); the four
-//          wavefronts share the candidates and the first one merges their results;
-//        - hubs (thousands of lists) run their lists through a three-deep load pipeline.
-// No global sort of the M*knn*(knn-1) co-occurrence pairs is needed: the skewed keys that sit
-// in nearly every list are simply the longest-running work items and are scheduled first.
+//   4. backbone children and -1 padding for every row.
+//   5. rows of the populated keys. For key a: stream the lists that hold a (whole rows of the
+//      translated lists, coalesced), count each co-listed key, and select the best 64. Positions
+//      stand for ids throughout: among keys of equal overlap and count (which are equally popular)
+//      the lower position is the lower id. By the number of list cells (lists x knn):
+//        - few (up to 2048): one key per wavefront, counts in an LDS hash table sized by
+//          the key's class, no workgroup barrier (pj_rows_small_kernel);
+//        - the rest, in a graph of at most 8192 populated keys (the common case: the queries share
+//          their favourite keys): one key per workgroup, counts in an LDS table indexed by
+//          position (pj_rows_kernel); hubs run their thousands of lists through a three-deep load pipeline;
+//        - the rest in a larger graph: one key per workgroup, counts in an LDS hash table, in a few
+//          passes over the lists where they hold more keys than the table (pj_rows_hash_kernel), and
+//          for the keys with most lists in counters in device memory, the low positions still in LDS
+//          (pj_rows_hub_kernel).
+// No global sort of the M*knn*(knn-1) co-occurrence pairs is needed.
 #include <type_traits>
 
 #include "common.h"
 
-#define PJ_T 1024                 // threads of the ordering kernel
 #define PJ_ROW_T 256              // threads of the row kernel
-#define PJ_MAX_WG 2048
+#define PJ_LDS_TAB 8192           // words of the workgroup row kernel's table
+#define PJ_BLOCK 2048             // keys a workgroup of the compaction kernels owns
+#define PJ_CELL_T 256
 
 typedef unsigned long long u64;
 
 struct ProjWs {                   // per-graph device arrays, carved from one workspace
     int32_t* pop;                 // [N]
+    int32_t* cur;                 // [N]   fill cursors
+    int32_t* off;                 // [N]   start of each key's inverted list
     int32_t* pos;                 // [N]   position of key in pi
     int32_t* pi;                  // [N]
-    int32_t* off;                 // [N+1] CSR offsets of inverted lists
-    int32_t* cur;                 // [N]   fill cursors
     int32_t* inv;                 // [M*knn]
     int32_t* lp;                  // [M*knn] the lists with every key replaced by its position in pi (-1: none)
-    int32_t* hk[2];               // [cap] radix ping-pong: keys
-    int32_t* hi[2];               // [cap] radix ping-pong: ids
-    int32_t* H;                   // [1]   number of populated keys
+    u64* keys;                    // [cap padded to a power of two] sort keys of the populated keys
+    int32_t* ppop;                // [cap] popularity by position
+    int32_t* blk;                 // [blocks] populated keys per block, then [blocks] list cells per block
+    int32_t* H;                   // [0] number of populated keys, [1] number of keys in over
+    int32_t* over;                // [cap] positions whose lists overflowed a hash table
 };
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct ProjLayout {
-    size_t per_graph, o_pop, o_pos, o_pi, o_off, o_cur, o_inv, o_lp, o_hk0, o_hk1, o_hi0, o_hi1, o_H;
+    size_t per_graph, o_pop, o_cur, o_off, o_pos, o_pi, o_inv, o_lp, o_keys, o_ppop, o_blk, o_H, o_over;
     size_t scratch_per_wg, o_scratch;
-    int n_wg;
-    int64_t cap;
+    int n_hub_wg, n_blk;
+    int64_t cap, cap_pad;
 };
 
 static ProjLayout proj_layout(int n_graphs, int64_t N, int64_t M, int knn) {
     ProjLayout l;
     const int64_t cells = M * knn;
     l.cap = N < cells ? N : cells;
+    l.cap_pad = ra_sort_padded(l.cap);
+    l.n_blk = (int)((N + PJ_BLOCK - 1) / PJ_BLOCK);
     size_t o = 0;
     l.o_pop = o; o += align256((size_t)N * 4);
+    l.o_cur = o; o += align256((size_t)N * 4);
+    l.o_off = o; o += align256((size_t)N * 4);
     l.o_pos = o; o += align256((size_t)N * 4);
     l.o_pi = o; o += align256((size_t)N * 4);
-    l.o_off = o; o += align256((size_t)(N + 1) * 4);
-    l.o_cur = o; o += align256((size_t)N * 4);
     l.o_inv = o; o += align256((size_t)cells * 4);
     l.o_lp = o; o += align256((size_t)cells * 4);
-    l.o_hk0 = o; o += align256((size_t)l.cap * 4);
-    l.o_hk1 = o; o += align256((size_t)l.cap * 4);
-    l.o_hi0 = o; o += align256((size_t)l.cap * 4);
-    l.o_hi1 = o; o += align256((size_t)l.cap * 4);
+    l.o_keys = o; o += align256((size_t)l.cap_pad * 8);
+    l.o_ppop = o; o += align256((size_t)l.cap * 4);
+    l.o_blk = o; o += align256((size_t)l.n_blk * 8);
     l.o_H = o; o += 256;
+    l.o_over = o; o += l.cap > PJ_LDS_TAB ? align256((size_t)l.cap * 4) : 0;
     l.per_graph = o;
-    // row kernel scratch: per workgroup four int arrays of `cap` entries
-    l.scratch_per_wg = align256((size_t)l.cap * 4) * 4;     // counters, candidates, two tuple columns
-    int per_graph_wg = 128;
-    while (per_graph_wg > 1 &&
-           ((size_t)per_graph_wg * n_graphs > PJ_MAX_WG ||
-            (size_t)per_graph_wg * n_graphs * l.scratch_per_wg > ((size_t)8 << 30)))
-        per_graph_wg >>= 1;
-    l.n_wg = per_graph_wg;
+    // counters of the hub kernel's workgroups (graphs of more than PJ_LDS_TAB populated keys), at most
+    // 1 GiB of them
+    l.scratch_per_wg = l.cap > PJ_LDS_TAB ? align256((size_t)l.cap * 4) : 0;
+    l.n_hub_wg = 64;
+    while (l.n_hub_wg > 1 && ((size_t)l.n_hub_wg * n_graphs > 512 ||
+                              (size_t)l.n_hub_wg * n_graphs * l.scratch_per_wg > ((size_t)1 << 30)))
+        l.n_hub_wg >>= 1;
     l.o_scratch = l.per_graph * n_graphs;
     return l;
 }
 
 size_t ra_project_workspace_bytes(int n_graphs, int64_t N, int64_t M, int knn) {
     const ProjLayout l = proj_layout(n_graphs, N, M, knn);
-    return l.o_scratch + (size_t)l.n_wg * n_graphs * l.scratch_per_wg;
+    return l.o_scratch + (size_t)l.n_hub_wg * n_graphs * l.scratch_per_wg;
 }
 
 __device__ __forceinline__ ProjWs carve(char* ws, const ProjLayout& l, int g) {
     char* b = ws + (size_t)g * l.per_graph;
     ProjWs w;
-    w.pop = (int32_t*)(b + l.o_pop); w.pos = (int32_t*)(b + l.o_pos); w.pi = (int32_t*)(b + l.o_pi);
-    w.off = (int32_t*)(b + l.o_off); w.cur = (int32_t*)(b + l.o_cur); w.inv = (int32_t*)(b + l.o_inv);
-    w.lp = (int32_t*)(b + l.o_lp);
-    w.hk[0] = (int32_t*)(b + l.o_hk0); w.hk[1] = (int32_t*)(b + l.o_hk1);
-    w.hi[0] = (int32_t*)(b + l.o_hi0); w.hi[1] = (int32_t*)(b + l.o_hi1);
-    w.H = (int32_t*)(b + l.o_H);
+    w.pop = (int32_t*)(b + l.o_pop); w.cur = (int32_t*)(b + l.o_cur); w.off = (int32_t*)(b + l.o_off);
+    w.pos = (int32_t*)(b + l.o_pos); w.pi = (int32_t*)(b + l.o_pi);
+    w.inv = (int32_t*)(b + l.o_inv); w.lp = (int32_t*)(b + l.o_lp);
+    w.keys = (u64*)(b + l.o_keys); w.ppop = (int32_t*)(b + l.o_ppop);
+    w.blk = (int32_t*)(b + l.o_blk); w.H = (int32_t*)(b + l.o_H);
+    w.over = (int32_t*)(b + l.o_over);
     return w;
 }
 
 // ---- 0. clear --------------------------------------------------------------------------
-__global__ void pj_zero_kernel(char* ws, ProjLayout l, int64_t N, int n_graphs) {
-    const int g = blockIdx.y;
-    ProjWs w = carve(ws, l, g);
+__global__ void pj_zero_kernel(char* ws, ProjLayout l, int64_t N) {
+    ProjWs w = carve(ws, l, blockIdx.y);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N;
          i += (int64_t)gridDim.x * blockDim.x) {
         w.pop[i] = 0;
         w.cur[i] = 0;
     }
-    // counter tables of the row kernel must start at zero
-    uint32_t* sc = (uint32_t*)(ws + l.o_scratch);
-    const size_t words = (size_t)l.n_wg * n_graphs * l.scratch_per_wg / 4;
-    const size_t stride = (size_t)gridDim.x * gridDim.y * blockDim.x;
-    for (size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-         i < words; i += stride)
-        sc[i] = 0u;
 }
 
 // ---- 1. pop ----------------------------------------------------------------------------
 // The queries share their favourite keys (a hub is in nearly every list), so plain atomic adds
 // would queue up on a handful of addresses. Each workgroup counts in a small direct-mapped table
-// in LDS first (slot = key mod PJ_HOT, owned by the first key that claims it; other keys that
-// map there go straight to memory) and adds every owned slot to memory once at the end.
+// in LDS first (a slot is owned by the first key that claims it; a key looks at PJ_PROBE neighbouring
+// slots and goes straight to memory when others own them all) and adds every owned slot to memory once
+// at the end. Adds to memory are what the counting costs (they go past the per-XCD L2: about 25 per
+// ns), so a launch has no more workgroups than fill the part (128K: 1.30 -> 0.32 ms with a
+// quarter of them). Slots are read before they are claimed (after the first few lists they are nearly
+// always taken) and four cells per thread are in flight.
 #define PJ_HOT 2048
-__global__ __launch_bounds__(256) void pj_pop_kernel(const int32_t* __restrict__ L, char* ws,
-                                                     ProjLayout l, int64_t cells, int64_t N) {
+#define PJ_PROBE 4
+#define PJ_FLY 4
+__device__ __forceinline__ int hot_tag(int* s_tag, int x) {
+    return __hip_atomic_load(&s_tag[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// the slot of key k, -1: none; `first` is what its first slot held (read ahead for several keys at once)
+__device__ __forceinline__ int hot_slot(int* s_tag, int k, int first) {
+    const int x0 = k & (PJ_HOT - 1);
+    if (first == k) return x0;
+    for (int u = 0; u < PJ_PROBE; ++u) {
+        const int x = (x0 + u) & (PJ_HOT - 1);
+        int owner = hot_tag(s_tag, x);
+        if (owner == -1) {
+            owner = atomicCAS(&s_tag[x], -1, k);
+            if (owner == -1) owner = k;
+        }
+        if (owner == k) return x;
+    }
+    return -1;
+}
+__global__ __launch_bounds__(PJ_CELL_T) void pj_pop_kernel(const int32_t* __restrict__ L, char* ws,
+                                                           ProjLayout l, int64_t cells, int64_t N) {
     __shared__ int s_tag[PJ_HOT];
     __shared__ int s_num[PJ_HOT];
-    const int g = blockIdx.y;
-    ProjWs w = carve(ws, l, g);
-    const int32_t* Lg = L + (size_t)g * cells;
-    for (int x = threadIdx.x; x < PJ_HOT; x += blockDim.x) { s_tag[x] = -1; s_num[x] = 0; }
+    ProjWs w = carve(ws, l, blockIdx.y);
+    for (int x = threadIdx.x; x < PJ_HOT; x += PJ_CELL_T) { s_tag[x] = -1; s_num[x] = 0; }
     __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cells;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t k = Lg[i];
-        if (k >= 0 && k < N) {
-            const int x = k & (PJ_HOT - 1);
-            const int owner = atomicCAS(&s_tag[x], -1, k);
-            if (owner == -1 || owner == k) atomicAdd(&s_num[x], 1);
-            else atomicAdd(&w.pop[k], 1);
+    const int32_t* Lg = L + (size_t)blockIdx.y * cells;
+    const int64_t stride = (int64_t)gridDim.x * PJ_CELL_T;
+    for (int64_t i0 = (int64_t)blockIdx.x * PJ_CELL_T + threadIdx.x; i0 < cells; i0 += PJ_FLY * stride) {
+        int32_t k[PJ_FLY], tag[PJ_FLY];
+#pragma unroll
+        for (int u = 0; u < PJ_FLY; ++u) {
+            const int64_t i = i0 + u * stride;
+            k[u] = i < cells ? Lg[i] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < PJ_FLY; ++u) tag[u] = hot_tag(s_tag, k[u] & (PJ_HOT - 1));
+#pragma unroll
+        for (int u = 0; u < PJ_FLY; ++u) {
+            if (k[u] < 0 || k[u] >= N) continue;
+            const int x = hot_slot(s_tag, k[u], tag[u]);
+            if (x >= 0) atomicAdd(&s_num[x], 1);
+            else atomicAdd(&w.pop[k[u]], 1);
         }
     }
     __syncthreads();
-    for (int x = threadIdx.x; x < PJ_HOT; x += blockDim.x)
+    for (int x = threadIdx.x; x < PJ_HOT; x += PJ_CELL_T)
         if (s_tag[x] >= 0) atomicAdd(&w.pop[s_tag[x]], s_num[x]);
 }
 
@@ -184,111 +212,85 @@ __device__ __forceinline__ int block_exscan(int v, int* wsum, int* total) {
     return base + inc - v;
 }
 
-__global__ __launch_bounds__(PJ_T) void pj_order_kernel(char* ws, ProjLayout l, int64_t N, int64_t M,
-                                                        int32_t* __restrict__ entry) {
-    __shared__ int wsum[PJ_T / 64];
-    __shared__ int wtot[PJ_T / 64][16];
-    __shared__ int base[16];
-    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    ProjWs w = carve(ws, l, g);
-
-    // A. compaction of populated keys (ascending id), CSR offsets, zero-pop ranks
-    int hot_run = 0, off_run = 0;
-    for (int64_t b0 = 0; b0 < N; b0 += PJ_T) {
-        const int64_t i = b0 + tid;
+// populated keys and list cells of every block of PJ_BLOCK keys
+__global__ __launch_bounds__(256) void pj_count_kernel(char* ws, ProjLayout l, int64_t N) {
+    __shared__ int wsum[4];
+    ProjWs w = carve(ws, l, blockIdx.y);
+    int hot = 0, sum = 0;
+    for (int x = threadIdx.x; x < PJ_BLOCK; x += 256) {
+        const int64_t i = (int64_t)blockIdx.x * PJ_BLOCK + x;
         const int p = i < N ? w.pop[i] : 0;
-        const int hot = p > 0 ? 1 : 0;
-        int th, tp;
-        const int eh = block_exscan(hot, wsum, &th);
-        const int ep = block_exscan(p, wsum, &tp);
-        if (i < N) {
-            w.off[i] = off_run + ep;
-            const int hr = hot_run + eh;
-            if (hot) {
-                w.hi[0][hr] = (int)i;
-                w.hk[0][hr] = (int)(M - p);          // ascending key = descending pop
-            } else {
-                w.pos[i] = (int)i - hr;              // rank among zero-pop keys (H added below)
-            }
-        }
-        hot_run += th;
-        off_run += tp;
+        hot += p > 0 ? 1 : 0;
+        sum += p;
     }
-    const int H = hot_run;
-    if (tid == 0) {
-        w.off[N] = off_run;
-        *w.H = H;
+    int th, ts;
+    block_exscan(hot, wsum, &th);
+    block_exscan(sum, wsum, &ts);
+    if (threadIdx.x == 0) {
+        w.blk[blockIdx.x] = th;
+        w.blk[l.n_blk + blockIdx.x] = ts;
     }
-    __syncthreads();
+}
 
-    // B. stable LSD radix sort of (key, id) by key, 4 bits per pass
-    int bits = 1;
-    while (((int64_t)1 << bits) < M) ++bits;
-    int src = 0;
-    for (int shift = 0; shift < bits; shift += 4) {
-        if (tid < 16) base[tid] = 0;
-        __syncthreads();
-        for (int b0 = 0; b0 < H; b0 += PJ_T) {
-            const int i = b0 + tid;
-            if (i < H) atomicAdd(&base[(w.hk[src][i] >> shift) & 15], 1);
-        }
-        __syncthreads();
-        if (tid == 0) {
-            int run = 0;
-            for (int v = 0; v < 16; ++v) {
-                const int c = base[v];
-                base[v] = run;
-                run += c;
-            }
-        }
-        __syncthreads();
-        for (int b0 = 0; b0 < H; b0 += PJ_T) {
-            const int i = b0 + tid;
-            const bool valid = i < H;
-            const int key = valid ? w.hk[src][i] : 0, id = valid ? w.hi[src][i] : 0;
-            const int dg = (key >> shift) & 15;
-            int wrank = 0;
+// sort keys of the populated keys (compacted in id order), positions of the others, starts of the
+// inverted lists. A thread owns PJ_BLOCK / 256 consecutive keys.
+__global__ __launch_bounds__(256) void pj_compact_kernel(char* ws, ProjLayout l, int64_t N, int64_t M) {
+    __shared__ int wsum[4];
+    ProjWs w = carve(ws, l, blockIdx.y);
+    const int tid = threadIdx.x;
+    int h_before = 0, h_all = 0, c_before = 0;
+    for (int b = tid; b < l.n_blk; b += 256) {
+        const int h = w.blk[b];
+        h_all += h;
+        if (b < (int)blockIdx.x) { h_before += h; c_before += w.blk[l.n_blk + b]; }
+    }
+    int H, hb, cb;
+    block_exscan(h_all, wsum, &H);
+    block_exscan(h_before, wsum, &hb);
+    block_exscan(c_before, wsum, &cb);
+    constexpr int PER = PJ_BLOCK / 256;
+    const int64_t i0 = (int64_t)blockIdx.x * PJ_BLOCK + tid * PER;
+    int p[PER], hot = 0, sum = 0;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const u64 mask = __ballot(valid && dg == v);
-                if (dg == v) wrank = __popcll(mask & ((1ull << lane) - 1ull));
-                if (lane == 0) wtot[wv][v] = __popcll(mask);
-            }
-            __syncthreads();
-            if (valid) {
-                int before = 0;
-                for (int x = 0; x < wv; ++x) before += wtot[x][dg];
-                const int dst = base[dg] + before + wrank;
-                w.hk[src ^ 1][dst] = key;
-                w.hi[src ^ 1][dst] = id;
-            }
-            __syncthreads();
-            if (tid < 16) {
-                int add = 0;
-                for (int x = 0; x < PJ_T / 64; ++x) add += wtot[x][tid];
-                base[tid] += add;
-            }
-            __syncthreads();
-        }
-        src ^= 1;
+    for (int u = 0; u < PER; ++u) {
+        p[u] = i0 + u < N ? w.pop[i0 + u] : 0;
+        hot += p[u] > 0 ? 1 : 0;
+        sum += p[u];
     }
-    __syncthreads();
+    int tot;
+    int hr = hb + block_exscan(hot, wsum, &tot);
+    int off = cb + block_exscan(sum, wsum, &tot);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t i = i0 + u;
+        if (i >= N) break;
+        w.off[i] = off;
+        off += p[u];
+        if (p[u] > 0) {
+            w.keys[hr++] = ((u64)(uint32_t)(M - p[u]) << 32) | (u64)(uint32_t)i;    // ascending = descending pop
+        } else {
+            const int t = H + (int)i - hr;               // after the populated ones, in id order
+            w.pos[i] = t;
+            w.pi[t] = (int)i;
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) { w.H[0] = H; w.H[1] = 0; }
+}
 
-    // C. pi, pos, entry
-    for (int t = tid; t < H; t += PJ_T) {
-        const int id = w.hi[src][t];
+// pi, pos and popularity by position of the populated keys; the entry point
+__global__ __launch_bounds__(256) void pj_pi_kernel(char* ws, ProjLayout l, int64_t M,
+                                                    int32_t* __restrict__ entry) {
+    ProjWs w = carve(ws, l, blockIdx.y);
+    const int H = *w.H;
+    for (int t = blockIdx.x * 256 + threadIdx.x; t < H; t += gridDim.x * 256) {
+        const u64 k = w.keys[t];
+        const int id = (int)(uint32_t)k;
         w.pi[t] = id;
         w.pos[id] = t;
-        w.hk[0][t] = w.pop[id];        // from here on hk[0] is the popularity by position
+        w.ppop[t] = (int)(M - (int64_t)(k >> 32));
+        if (t == 0) entry[blockIdx.y] = id;
     }
-    for (int64_t i = tid; i < N; i += PJ_T) {
-        if (w.pop[i] == 0) {
-            const int p = H + w.pos[i];
-            w.pos[i] = p;
-            w.pi[p] = (int)i;
-        }
-    }
-    if (tid == 0) entry[g] = H > 0 ? w.hi[src][0] : 0;
+    if (H == 0 && blockIdx.x == 0 && threadIdx.x == 0) entry[blockIdx.y] = 0;
 }
 
 // ---- 3. inverted lists -----------------------------------------------------------------
@@ -296,104 +298,155 @@ __global__ __launch_bounds__(PJ_T) void pj_order_kernel(char* ws, ProjLayout l, 
 // one range of every such key's inverted list with a single atomic add, and hands out the places
 // inside its ranges with LDS atomics in a second pass over the same cells. The order of the
 // entries inside an inverted list is immaterial (only co-occurrence counts come out of them).
-__global__ __launch_bounds__(256) void pj_inv_kernel(const int32_t* __restrict__ L, char* ws,
-                                                     ProjLayout l, int64_t cells, int knn, int64_t N) {
+// Lists are read whole, a run of `kp` (32 or 64) lanes per list, so that no cell divides by knn.
+__global__ __launch_bounds__(PJ_CELL_T) void pj_inv_kernel(const int32_t* __restrict__ L, char* ws,
+                                                           ProjLayout l, int64_t M, int knn, int64_t N) {
     __shared__ int s_tag[PJ_HOT];
     __shared__ int s_num[PJ_HOT];
     __shared__ int s_base[PJ_HOT];
-    const int g = blockIdx.y;
-    ProjWs w = carve(ws, l, g);
-    const int32_t* Lg = L + (size_t)g * cells;
-    for (int x = threadIdx.x; x < PJ_HOT; x += blockDim.x) { s_tag[x] = -1; s_num[x] = 0; }
+    ProjWs w = carve(ws, l, blockIdx.y);
+    const int32_t* Lg = L + (size_t)blockIdx.y * M * knn;
+    const int kp = knn <= 32 ? 32 : 64, e = threadIdx.x & (kp - 1), lpp = PJ_CELL_T / kp;
+    const bool has = e < knn;
+    const int64_t stride = (int64_t)gridDim.x * lpp, first = (int64_t)blockIdx.x * lpp + threadIdx.x / kp;
+    for (int x = threadIdx.x; x < PJ_HOT; x += PJ_CELL_T) { s_tag[x] = -1; s_num[x] = 0; }
     __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cells;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t k = Lg[i];
-        if (k >= 0 && k < N) {
-            const int x = k & (PJ_HOT - 1);
-            const int owner = atomicCAS(&s_tag[x], -1, k);
-            if (owner == -1 || owner == k) atomicAdd(&s_num[x], 1);
+    auto lists = [&](auto f) {
+        for (int64_t j0 = first; j0 < M; j0 += PJ_FLY * stride) {
+            int32_t k[PJ_FLY];
+#pragma unroll
+            for (int u = 0; u < PJ_FLY; ++u) {
+                const int64_t j = j0 + u * stride;
+                k[u] = Lg[(j < M ? j : j0) * knn + (has ? e : 0)];
+            }
+            f(j0, k);
         }
-    }
+    };
+    lists([&](int64_t j0, const int32_t (&k)[PJ_FLY]) {
+        int tag[PJ_FLY];
+#pragma unroll
+        for (int u = 0; u < PJ_FLY; ++u) tag[u] = hot_tag(s_tag, k[u] & (PJ_HOT - 1));
+#pragma unroll
+        for (int u = 0; u < PJ_FLY; ++u) {
+            if (!has || j0 + u * stride >= M || k[u] < 0 || k[u] >= N) continue;
+            const int x = hot_slot(s_tag, k[u], tag[u]);
+            if (x >= 0) atomicAdd(&s_num[x], 1);
+        }
+    });
     __syncthreads();
-    for (int x = threadIdx.x; x < PJ_HOT; x += blockDim.x) {
-        if (s_tag[x] >= 0) s_base[x] = atomicAdd(&w.cur[s_tag[x]], s_num[x]);
+    for (int x = threadIdx.x; x < PJ_HOT; x += PJ_CELL_T) {
+        const int k = s_tag[x];
+        if (k >= 0) s_base[x] = w.off[k] + atomicAdd(&w.cur[k], s_num[x]);
         s_num[x] = 0;                                  // now the cursor inside the range
     }
     __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cells;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t k = Lg[i];
-        int32_t p = -1;
-        if (k >= 0 && k < N) {
-            const int x = k & (PJ_HOT - 1);
-            const int slot = s_tag[x] == k ? s_base[x] + atomicAdd(&s_num[x], 1)
-                                           : atomicAdd(&w.cur[k], 1);
-            w.inv[w.off[k] + slot] = (int32_t)(i / knn);
-            p = w.pos[k];
+    lists([&](int64_t j0, const int32_t (&k)[PJ_FLY]) {
+        int p[PJ_FLY], tag[PJ_FLY], at[PJ_FLY];
+#pragma unroll
+        for (int u = 0; u < PJ_FLY; ++u) {
+            p[u] = w.pos[k[u] >= 0 && k[u] < N ? k[u] : 0];
+            tag[u] = s_tag[k[u] & (PJ_HOT - 1)];         // (final by now: owners sit where they claimed)
         }
-        w.lp[i] = p;
-    }
+#pragma unroll
+        for (int u = 0; u < PJ_FLY; ++u) {
+            at[u] = -1;
+            if (!has || j0 + u * stride >= M || k[u] < 0 || k[u] >= N) continue;
+            int x = k[u] & (PJ_HOT - 1);
+            if (tag[u] != k[u]) {
+                for (int v = 1; v < PJ_PROBE && s_tag[x] != k[u]; ++v) x = (k[u] + v) & (PJ_HOT - 1);
+                if (s_tag[x] != k[u]) x = -1;
+            }
+            at[u] = x >= 0 ? s_base[x] + atomicAdd(&s_num[x], 1) : w.off[k[u]] + atomicAdd(&w.cur[k[u]], 1);
+        }
+#pragma unroll
+        for (int u = 0; u < PJ_FLY; ++u) {
+            const int64_t j = j0 + u * stride;
+            if (!has || j >= M) continue;
+            if (at[u] >= 0) w.inv[at[u]] = (int32_t)j;
+            w.lp[j * knn + e] = at[u] >= 0 ? p[u] : -1;
+        }
+    });
 }
 
 // ---- 4. backbone + padding for every row -----------------------------------------------
-__global__ void pj_backbone_kernel(char* ws, ProjLayout l, int64_t N, int deg,
-                                   int32_t* __restrict__ adj) {
-    const int g = blockIdx.y;
-    ProjWs w = carve(ws, l, g);
-    int32_t* adj_g = adj + (size_t)g * N * deg;
-    const int64_t cells = N * deg;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cells;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t a = i / deg;
-        const int slot = (int)(i % deg);
-        int32_t v = -1;
+// V: cells a thread writes at a time (4 where deg allows 16-byte stores)
+template <int V>
+__global__ __launch_bounds__(256) void pj_backbone_kernel(char* ws, ProjLayout l, int64_t N, int deg,
+                                                          int32_t* __restrict__ adj) {
+    ProjWs w = carve(ws, l, blockIdx.y);
+    const int per = deg / V, rows = 256 / per, slot = (threadIdx.x % per) * V, r = threadIdx.x / per;
+    if (r >= rows) return;
+    for (int64_t a = (int64_t)blockIdx.x * rows + r; a < N; a += (int64_t)gridDim.x * rows) {
+        int32_t v[V];
+#pragma unroll
+        for (int u = 0; u < V; ++u) v[u] = -1;
         if (slot < 2) {
-            const int64_t ch = 2 * (int64_t)w.pos[a] + 1 + slot;
-            if (ch < N) v = w.pi[ch];
+            const int64_t ch = 2 * (int64_t)w.pos[a] + 1;
+#pragma unroll
+            for (int u = 0; u < V; ++u)
+                if (slot + u < 2 && ch + slot + u < N) v[u] = w.pi[ch + slot + u];
         }
-        adj_g[i] = v;
+        int32_t* dst = adj + ((size_t)blockIdx.y * N + a) * deg + slot;
+        if constexpr (V == 4) *reinterpret_cast<int4*>(dst) = make_int4(v[0], v[1], v[2], v[3]);
+        else dst[0] = v[0];
     }
 }
 
 // ---- 5. rows of populated keys ---------------------------------------------------------
-struct Cand { uint32_t c, pb; int32_t b; };
+// A ranked candidate: larger k first, then (WIDE) larger c, then lower position. k holds the Jaccard
+// fraction c / d, d = pop(a) + pop(b) - c. Two different fractions with denominators below 2^b differ
+// by more than 2^-2b:
+//   M <= 2^19: k = [floor(c / d * 2^42) : 43][c : 21]. d < 2^20, so different fractions are four
+//     units apart and the rounding of the double division (under 2^-10 of a unit) cannot close the gap;
+//     equal fractions round alike, and then the larger c is first.
+//   WIDE: k = floor(c / d * 2^62) exactly (d < 2^31), c on its own.
+// Zero: no candidate (a real one has c >= 1, k > 0).
+template <bool WIDE> struct Cand { u64 k; uint32_t pos; };
+template <> struct Cand<true> { u64 k; uint32_t c, pos; };
 
-// is x ranked before y for a key of popularity pa?  (Jaccard desc, count desc, id asc)
-__device__ __forceinline__ bool cand_before(const Cand& x, const Cand& y, uint32_t pa) {
-    const u64 lhs = (u64)x.c * (u64)(pa + y.pb - y.c);
-    const u64 rhs = (u64)y.c * (u64)(pa + x.pb - x.c);
-    if (lhs != rhs) return lhs > rhs;
-    if (x.c != y.c) return x.c > y.c;
-    return x.b < y.b;
-}
-
-// "no candidate": count 0 ranks after every real candidate (whose count is at least 1)
-__device__ __forceinline__ Cand cand_none() {
-    Cand x; x.c = 0u; x.pb = 0u; x.b = 0x7fffffff;
+template <bool WIDE>
+__device__ __forceinline__ Cand<WIDE> cand_none() {
+    Cand<WIDE> x;
+    x.k = 0ull;
+    x.pos = 0x7fffffffu;
+    if constexpr (WIDE) x.c = 0u;
     return x;
 }
-__device__ __forceinline__ Cand cand_lane(const Cand& x, int src) {
-    Cand y;
-    y.c = (uint32_t)__builtin_amdgcn_readlane((int)x.c, src);
-    y.pb = (uint32_t)__builtin_amdgcn_readlane((int)x.pb, src);
-    y.b = __builtin_amdgcn_readlane(x.b, src);
-    return y;
+template <bool WIDE>
+__device__ __forceinline__ Cand<WIDE> cand_make(uint32_t c, uint32_t pa, uint32_t pb, uint32_t pos) {
+    Cand<WIDE> x;
+    const uint32_t d = pa + pb - c;
+    if constexpr (WIDE) {
+        const u64 hi = ((u64)c << 31) / d, rem = ((u64)c << 31) % d;
+        x.k = (hi << 31) + (rem << 31) / d;
+        x.c = c;
+    } else {
+        x.k = ((u64)((double)c / (double)d * 4398046511104.0) << 21) | (u64)c;
+    }
+    x.pos = pos;
+    return x;
+}
+template <bool WIDE>
+__device__ __forceinline__ bool cand_before(const Cand<WIDE>& x, const Cand<WIDE>& y) {
+    if (x.k != y.k) return x.k > y.k;
+    if constexpr (WIDE)
+        if (x.c != y.c) return x.c > y.c;
+    return x.pos < y.pos;
 }
 // one compare-exchange step of a bitonic network over the 64 lanes: partner lane ^ J; the lane
 // keeps the better of the two when keep_best, else the worse
-template <int J>
-__device__ __forceinline__ Cand cand_exchange(const Cand& v, bool keep_best, uint32_t pa, int lane) {
-    Cand o;
-    o.c = lane_xor32<J>(v.c, lane);
-    o.pb = lane_xor32<J>(v.pb, lane);
-    o.b = (int32_t)lane_xor32<J>((uint32_t)v.b, lane);
-    return (cand_before(o, v, pa) == keep_best) ? o : v;
+template <int J, bool WIDE>
+__device__ __forceinline__ Cand<WIDE> cand_exchange(const Cand<WIDE>& v, bool keep_best, int lane) {
+    Cand<WIDE> o;
+    o.k = ((u64)lane_xor32<J>((uint32_t)(v.k >> 32), lane) << 32) | (u64)lane_xor32<J>((uint32_t)v.k, lane);
+    o.pos = lane_xor32<J>(v.pos, lane);
+    if constexpr (WIDE) o.c = lane_xor32<J>(v.c, lane);
+    return (cand_before(o, v) == keep_best) ? o : v;
 }
 // 64 candidates, one per lane, into rank order (DESC: lane 0 the best; else lane 63 the best)
-template <bool DESC>
-__device__ __forceinline__ Cand cand_sort64(Cand v, uint32_t pa, int lane) {
-#define PJ_STEP(K_, J_) v = cand_exchange<J_>(v, (((lane & J_) == 0) == ((lane & K_) == 0)) == DESC, pa, lane);
+template <bool DESC, bool WIDE>
+__device__ __forceinline__ Cand<WIDE> cand_sort64(Cand<WIDE> v, int lane) {
+#define PJ_STEP(K_, J_) v = cand_exchange<J_>(v, (((lane & J_) == 0) == ((lane & K_) == 0)) == DESC, lane);
     PJ_STEP(2, 1)
     PJ_STEP(4, 2) PJ_STEP(4, 1)
     PJ_STEP(8, 4) PJ_STEP(8, 2) PJ_STEP(8, 1)
@@ -403,352 +456,553 @@ __device__ __forceinline__ Cand cand_sort64(Cand v, uint32_t pa, int lane) {
 #undef PJ_STEP
     return v;
 }
-// a bitonic sequence of 64 into descending rank order
-__device__ __forceinline__ Cand cand_merge64(Cand v, uint32_t pa, int lane) {
-    v = cand_exchange<32>(v, (lane & 32) == 0, pa, lane);
-    v = cand_exchange<16>(v, (lane & 16) == 0, pa, lane);
-    v = cand_exchange<8>(v, (lane & 8) == 0, pa, lane);
-    v = cand_exchange<4>(v, (lane & 4) == 0, pa, lane);
-    v = cand_exchange<2>(v, (lane & 2) == 0, pa, lane);
-    v = cand_exchange<1>(v, (lane & 1) == 0, pa, lane);
-    return v;
+// the better 64 of `best` (descending) and of v (ascending), descending
+template <bool WIDE>
+__device__ __forceinline__ Cand<WIDE> cand_merge64(Cand<WIDE> best, const Cand<WIDE>& v, int lane) {
+    if (cand_before(v, best)) best = v;                // bitonic: the best 64 of the 128
+    best = cand_exchange<32>(best, (lane & 32) == 0, lane);
+    best = cand_exchange<16>(best, (lane & 16) == 0, lane);
+    best = cand_exchange<8>(best, (lane & 8) == 0, lane);
+    best = cand_exchange<4>(best, (lane & 4) == 0, lane);
+    best = cand_exchange<2>(best, (lane & 2) == 0, lane);
+    best = cand_exchange<1>(best, (lane & 1) == 0, lane);
+    return best;
+}
+
+__device__ __forceinline__ void pj_wave_sync() {         // LDS written by one lane, read by another
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The best 64 of n candidates, merged into `best` (one wavefront; lane l of best: the l-th best).
+// get(x, pos, c): position and count of candidate x in [0, n) (count 0: none). Sorting 64 candidates
+// costs hundreds of instructions, and of a few hundred candidates most are nowhere near the best 64: up
+// to 64 CH of them at a time have their overlap computed in float32 (CH per lane, in registers), a
+// bisection over its bits finds a value that at least 64 and hardly more of them reach, and only
+// those (a margin of a few units below it covers the float32 division) get the exact key and are
+// sorted. `surv` holds 128 ints of LDS.
+template <int CH, bool WIDE, class Get>
+__device__ __forceinline__ void select_best(Cand<WIDE>& best, int n, uint32_t pa, const int32_t* ppop, int* surv,
+                                            int lane, Get get) {
+    for (int base = 0; base < n; base += 64 * CH) {
+        const int m = n - base < 64 * CH ? n - base : 64 * CH;
+        uint32_t f[CH];
+        int np = 0;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            f[i] = 0u;
+            if (i * 64 < m) {                            // uniform
+                const int x = i * 64 + lane;
+                uint32_t pos = 0u, c = 0u;
+                if (x < m) get(base + x, pos, c);
+                const uint32_t pb = (uint32_t)ppop[pos];
+                if (c) f[i] = __float_as_uint((float)c * __builtin_amdgcn_rcpf((float)(pa + pb - c)));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+            if (i * 64 < m) np += __popcll(__ballot(f[i] != 0u));
+        uint32_t floor_ = 1u;
+        if (np > 128) {
+            uint32_t lo = 1u, hi = 0x3f800100u;          // an overlap is at most 1
+            int at_lo = np;
+            while (hi - lo > 1u && at_lo > 96) {
+                const uint32_t mid = lo + (hi - lo) / 2u;
+                int cnt = 0;
+#pragma unroll
+                for (int i = 0; i < CH; ++i)
+                    if (i * 64 < m) cnt += __popcll(__ballot(f[i] >= mid));
+                if (cnt >= 64) { lo = mid; at_lo = cnt; } else hi = mid;
+            }
+            floor_ = lo > 16u ? lo - 16u : 1u;
+        }
+        int have = 0;
+        auto rank = [&](int take) __attribute__((always_inline)) {
+            Cand<WIDE> v = cand_none<WIDE>();
+            if (lane < take) {
+                uint32_t pos = 0u, c = 0u;
+                get(surv[lane], pos, c);
+                v = cand_make<WIDE>(c, pa, (uint32_t)ppop[pos], pos);
+            }
+            Cand<WIDE> last;
+            last.k = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(best.k >> 32), 63) << 32) |
+                     (u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best.k, 63);
+            last.pos = (uint32_t)__builtin_amdgcn_readlane((int)best.pos, 63);
+            if constexpr (WIDE) last.c = (uint32_t)__builtin_amdgcn_readlane((int)best.c, 63);
+            if (__ballot(cand_before(v, last)) == 0ull) return;            // nothing here makes the 64
+            v = cand_sort64<false>(v, lane);
+            best = cand_merge64(best, v, lane);
+        };
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            if (i * 64 >= m) break;
+            const bool in = f[i] >= floor_;
+            const u64 mask = __ballot(in);
+            if (mask == 0ull) continue;
+            if (in) surv[have + __popcll(mask & ((1ull << lane) - 1ull))] = base + i * 64 + lane;
+            have += __popcll(mask);
+            pj_wave_sync();
+            if (have >= 64) {
+                rank(64);
+                have -= 64;
+                const int more = surv[64 + lane];
+                pj_wave_sync();
+                if (lane < have) surv[lane] = more;
+                pj_wave_sync();
+            }
+        }
+        if (have) rank(have);
+        pj_wave_sync();
+    }
 }
 
 // Row of the key at position t: its backbone children pi[2t+1], pi[2t+2], then the ranked
-// candidates (lane l of `best` holds the l-th best, `want` of them count) that are not among
-// the children, until deg entries; -1 beyond. One wavefront.
-__device__ __forceinline__ void write_row(int32_t* row, const Cand& best, int want, int t,
-                                          const int32_t* pi, int64_t N, int deg, int lane) {
-    int32_t kids[2] = {-1, -1};
-    int nk = 0;
-    for (int s = 0; s < 2 && nk < deg; ++s) {
-        const int64_t ch = 2 * (int64_t)t + 1 + s;
-        if (ch < N) kids[nk++] = pi[ch];
-    }
-    const bool keep = best.c > 0u && lane < want && best.b != kids[0] && best.b != kids[1];
-    const unsigned long long km = __ballot(keep);
+// candidates (lane l of `best` holds the l-th best) that are not among the children, until deg
+// entries; -1 beyond. One wavefront.
+template <bool WIDE>
+__device__ __forceinline__ void write_row(int32_t* row, const Cand<WIDE>& best, int t, const int32_t* pi, int64_t N,
+                                          int deg, int lane) {
+    const int64_t ch = 2 * (int64_t)t + 1;
+    int nk = (int)(N - ch < 0 ? 0 : N - ch < 2 ? N - ch : 2);
+    if (nk > deg) nk = deg;
+    const bool keep = best.k != 0ull && lane < deg && ((int64_t)best.pos < ch || (int64_t)best.pos >= ch + nk);
+    const u64 km = __ballot(keep);
     const int at = nk + __popcll(km & ((1ull << lane) - 1ull));
     const int total = nk + __popcll(km);
-    if (lane < nk) row[lane] = kids[lane];
-    if (keep && at < deg) row[at] = best.b;
+    if (lane < nk) row[lane] = pi[ch + lane];
+    if (keep && at < deg) row[at] = pi[best.pos];
     if (lane >= total && lane < deg) row[lane] = -1;
 }
 
 // Keys with few lists are handled one per wavefront (pj_rows_small_kernel), the others one per
-// workgroup: the first position in pi (popularity descending) whose key has at most `limit` lists.
-#define PJ_SMALL_TOUCH 2048       // list cells (lists x knn) of a key the wavefront kernel takes
-#define PJ_SMALL_SLOTS 4096       // its hash table: at most half full
-#define PJ_SMALL_WAVES 4
-__device__ __forceinline__ int small_limit(int knn) {
-    const int lim = PJ_SMALL_TOUCH / knn;
-    return lim < 127 ? lim : 127;                 // a count must fit the 7 bits of a table entry
-}
-__device__ __forceinline__ int first_small(const int32_t* pop_by_pos, int H, int knn) {
-    if (H >= (1 << 24)) return H;                 // a position must fit the other 25 bits
-    const int limit = small_limit(knn);
+// workgroup. first_within: the first position in pi (popularity descending) whose key has at most
+// `limit` lists.
+__device__ __forceinline__ int first_within(const int32_t* ppop, int H, int limit) {
     int lo = 0, hi = H;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (pop_by_pos[mid] > limit) lo = mid + 1; else hi = mid;
+        if (ppop[mid] > limit) lo = mid + 1; else hi = mid;
     }
     return lo;
 }
+// most lists of a key whose list cells (lists x knn) number at most `touch` (a count must fit the 7
+// bits of a small table's entry)
+__device__ __forceinline__ int small_limit(int touch, int knn) {
+    const int lim = touch / knn;
+    return lim < 127 ? lim : 127;
+}
 
 // One more co-occurrence of the key at position `key - 1` in an open-addressing table of `slots`
-// (a power of two) LDS words, entry = key << 7 | count; the table is never more than half full.
-__device__ __forceinline__ void lds_table_bump(uint32_t* tab, int slots, uint32_t key) {
+// (a power of two) LDS words, entry = key << cb | count. False when no slot is left.
+__device__ __forceinline__ bool lds_table_bump(uint32_t* tab, int slots, uint32_t key, int cb) {
     const uint32_t mask = (uint32_t)slots - 1u;
     uint32_t h = ((key * 2654435761u) >> 12) & mask;
     for (int probe = 0; probe < slots; ++probe) {
         uint32_t v = __hip_atomic_load(&tab[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (v == 0u) {
-            v = atomicCAS(&tab[h], 0u, (key << 7) | 1u);
-            if (v == 0u) return;                      // claimed, count 1
+            v = atomicCAS(&tab[h], 0u, (key << cb) | 1u);
+            if (v == 0u) return true;                 // claimed, count 1
         }
-        if ((v >> 7) == key) { atomicAdd(&tab[h], 1u); return; }
+        if ((v >> cb) == key) { atomicAdd(&tab[h], 1u); return true; }
         h = (h + 1u) & mask;
     }
+    return false;
 }
 
-#define PJ_LDS_CNT 8192           // co-occurrence counters kept in LDS when the populated set fits
-#define PJ_LDS_TUP 2048           // candidate tuples kept in LDS when the candidate list fits
-
-// Rows of the populated keys of one graph. LDSCNT: the counter table (indexed by pi-position,
-// < H) lives in LDS instead of the workgroup's global scratch; LDS atomics are an order of
-// magnitude cheaper than L2 atomics and the table is small whenever the queries share their
-// favourite keys (H is a few thousand at 128K context).
-template <bool LDSCNT>
-__device__ __forceinline__ void rows_for_graph(const int32_t* __restrict__ Lg, const ProjWs& w,
-                                               uint32_t* cnt, int32_t* cand, uint32_t* tc_g,
-                                               uint32_t* tp_g, uint32_t* tc_l, uint32_t* tp_l,
-                                               int32_t* tb_l, int64_t N, int knn, int deg, int H,
-                                               int32_t* __restrict__ adj_g, int* s_ncand,
-                                               Cand (*s_best)[64], uint32_t* lds_tab) {
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int kp = knn <= 32 ? 32 : 64;
-    const int t_end = first_small(w.hk[0], H, knn);       // the rest is pj_rows_small_kernel's
-    for (int t = blockIdx.x; t < t_end; t += gridDim.x) {
-        const int a = w.pi[t];
-        const uint32_t pa = (uint32_t)w.pop[a];
-        const int o0 = w.off[a];
-        // With more populated keys than LDS counters, a key of moderate size still counts in LDS:
-        // the counter array serves as an open-addressing table (entry = (position + 1) << 7 |
-        // count, at most half full); only the hubs of such a graph count in device memory.
-        const bool hashed = !LDSCNT && pa <= 127u && (int)pa * knn <= PJ_LDS_CNT / 2 && H < (1 << 24);
-        if (tid == 0) *s_ncand = 0;
-        __syncthreads();
-        // count co-listed keys; the first touch of a counter appends the key (its position in pi)
-        // to the candidates. A run of kp lanes (kp = 32 or 64 >= knn) reads one list, lane e its
-        // e-th entry (one coalesced row of the position-translated lists, so no lookup per
-        // entry is left).
-        {
-            const int e = tid & (kp - 1), r0 = tid / kp, rstep = PJ_ROW_T / kp;
-            auto count_lists = [&](auto unroll_tag, int li_begin, int li_end) {
-                constexpr int U = decltype(unroll_tag)::value;
-                for (int li0 = li_begin + r0; li0 < li_end; li0 += U * rstep) {
-                    int pp[U];
+// f(position) for the entries of the lists [begin, end) of a key (inv: its inverted list), U lists in
+// flight per run of kp lanes; e: this lane's entry, r0 / rstep: this run's first list and the distance
+// to its next
+template <int U, class F>
+__device__ __forceinline__ void walk_lists(const int32_t* inv, const int32_t* lp, int begin, int end, int knn, int e,
+                                           int r0, int rstep, F f) {
+    const int ec = e < knn ? e : 0;
+    for (int li0 = begin + r0; li0 < end; li0 += U * rstep) {
+        int pp[U];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int li = li0 + u * rstep;
-                        const int j = w.inv[o0 + (li < li_end ? li : li_end - 1)];
-                        pp[u] = (li < li_end && e < knn) ? w.lp[(size_t)j * knn + (e < knn ? e : 0)] : -1;
-                    }
+        for (int u = 0; u < U; ++u) {
+            const int li = li0 + u * rstep;
+            pp[u] = inv[li < end ? li : end - 1];
+        }
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        if (pp[u] < 0 || pp[u] == t) continue;
-                        if (hashed) {
-                            lds_table_bump(lds_tab, PJ_LDS_CNT, (uint32_t)pp[u] + 1u);
-                        } else if (atomicAdd(&cnt[pp[u]], 1u) == 0u) {
-                            cand[atomicAdd(s_ncand, 1)] = pp[u];
-                        }
-                    }
-                }
-            };
-            // A hub sits in tens of thousands of lists and one workgroup walks them all. Its lists
-            // go through a three-deep pipeline, sixteen per lane and stage: the list numbers of
-            // pass i + 2 and the rows of pass i + 1 are in flight while pass i bumps its counters
-            // (a pass that ran list number -> row -> counters in sequence would be two memory
-            // latencies long). Indices past the end are clamped, never branched around.
-            constexpr int UB = 16;
-            const int per_pass = UB * rstep;
-            const int n_pass = (int)pa >= 8 * per_pass ? (int)pa / per_pass : 0;
-            if (n_pass) {
-                int j0[UB], j1[UB], j2[UB], p0[UB], p1[UB];
-                auto load_inv = [&](int pass, int (&jj)[UB]) {
-                    if (pass >= n_pass) pass = n_pass - 1;
+        for (int u = 0; u < U; ++u) pp[u] = lp[(size_t)pp[u] * knn + ec];
 #pragma unroll
-                    for (int u = 0; u < UB; ++u) jj[u] = w.inv[o0 + pass * per_pass + r0 + u * rstep];
-                };
-                auto load_rows = [&](const int (&jj)[UB], int (&pp)[UB]) {
-#pragma unroll
-                    for (int u = 0; u < UB; ++u) pp[u] = w.lp[(size_t)jj[u] * knn + (e < knn ? e : 0)];
-                };
-                load_inv(0, j0);
-                load_inv(1, j1);
-                load_rows(j0, p0);
-                for (int pass = 0; pass < n_pass; ++pass) {
-                    load_inv(pass + 2, j2);
-                    load_rows(j1, p1);
-#pragma unroll
-                    for (int u = 0; u < UB; ++u) {
-                        if (e < knn && p0[u] >= 0 && p0[u] != t && atomicAdd(&cnt[p0[u]], 1u) == 0u)
-                            cand[atomicAdd(s_ncand, 1)] = p0[u];
-                    }
-#pragma unroll
-                    for (int u = 0; u < UB; ++u) { p0[u] = p1[u]; j1[u] = j2[u]; }
-                }
-            }
-            count_lists(std::integral_constant<int, 4>{}, n_pass * per_pass, (int)pa);
-        }
-        __syncthreads();
-        if (hashed) {                    // empty the table into the candidate list (entries as they are)
-            for (int q = tid; q < PJ_LDS_CNT; q += PJ_ROW_T) {
-                const uint32_t v = lds_tab[q];
-                if (v != 0u) {
-                    lds_tab[q] = 0u;
-                    cand[atomicAdd(s_ncand, 1)] = (int32_t)v;
-                }
-            }
-            __syncthreads();
-        }
-        const int nc = *s_ncand;
-        const int want = nc < deg ? nc : deg;
-        // gather (count, popularity, id) of every candidate once; reset its counter on the way
-        const bool tl = nc <= PJ_LDS_TUP;
-        uint32_t* tc = tl ? tc_l : tc_g;
-        uint32_t* tp = tl ? tp_l : tp_g;
-        int32_t* tb = tl ? tb_l : cand;
-        for (int x = tid; x < nc; x += PJ_ROW_T) {
-            int pb = cand[x];
-            if (hashed) {
-                tc[x] = (uint32_t)pb & 127u;
-                pb = (int)((uint32_t)pb >> 7) - 1;
-            } else {
-                tc[x] = cnt[pb];
-                cnt[pb] = 0u;
-            }
-            tp[x] = (uint32_t)w.hk[0][pb];
-            tb[x] = w.pi[pb];            // the candidate list itself, when the tuples stay in global memory
-        }
-        __syncthreads();
-        // best 64 of this wavefront's chunks, sorted: lane l holds its l-th best
-        Cand best = cand_none();
-        for (int x0 = wv * 64; x0 < nc; x0 += PJ_ROW_T) {
-            Cand cd = cand_none();
-            if (x0 + lane < nc) { cd.b = tb[x0 + lane]; cd.c = tc[x0 + lane]; cd.pb = tp[x0 + lane]; }
-            const Cand last = cand_lane(best, 63);
-            if (__ballot(cand_before(cd, last, pa)) == 0ull) continue;     // nothing here makes the 64
-            cd = cand_sort64<false>(cd, pa, lane);                          // ascending: lane l = (63-l)-th best
-            if (cand_before(cd, best, pa)) best = cd;                      // bitonic: the best 64 of the 128
-            best = cand_merge64(best, pa, lane);
-        }
-        if (wv > 0) {
-            s_best[wv - 1][lane] = best;
-        }
-        __syncthreads();
-        // row = backbone children, then ranked candidates not already present
-        if (wv == 0) {
-            for (int o = 0; o < PJ_ROW_T / 64 - 1; ++o) {
-                Cand cd = s_best[o][63 - lane];                             // descending list, reversed
-                if (cand_before(cd, best, pa)) best = cd;
-                best = cand_merge64(best, pa, lane);
-            }
-            write_row(adj_g + (size_t)a * deg, best, want, t, w.pi, N, deg, lane);
-        }
-        __syncthreads();
+        for (int u = 0; u < U; ++u)
+            if (li0 + u * rstep < end && e < knn && pp[u] >= 0) f(pp[u]);
     }
 }
 
-__global__ __launch_bounds__(PJ_ROW_T) void pj_rows_kernel(const int32_t* __restrict__ L, char* ws,
-                                                           ProjLayout l, int64_t N, int64_t M,
-                                                           int knn, int deg,
+#define PJ_SMALL_WAVES 4
+#define PJ_TOUCH_A 256            // list cells of a key in each class of the wavefront kernel
+#define PJ_TOUCH_B 1024
+#define PJ_TOUCH_C 2048
+#define PJ_HASH_T 512             // threads of the hash kernel
+#define PJ_HASH_TAB 16384         // words of its table
+#define PJ_HASH_FILL 10240        // list cells one of its passes puts in there
+#define PJ_HASH_PASSES 4          // most passes; a key with more cells than they take is the hub kernel's
+#define PJ_HUB_T 1024             // threads of the hub kernel
+
+// first position of the keys that are not the wavefront kernels'
+__device__ __forceinline__ int large_end(const int32_t* ppop, int H, int knn) {
+    return H < (1 << 24) ? first_within(ppop, H, small_limit(PJ_TOUCH_C, knn)) : H;
+}
+
+// the best 64 of a workgroup's wavefronts, and the row of the key at position t
+template <int T, bool WIDE>
+__device__ __forceinline__ void finish_row(Cand<WIDE> best, Cand<WIDE> (*s_best)[64], int32_t* adj_g, int t,
+                                           const ProjWs& w, int64_t N, int deg) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // pairs of wavefronts, then pairs of those
+#pragma unroll
+    for (int step = 1; step < T / 64; step <<= 1) {
+        if ((wv & (2 * step - 1)) == step) s_best[wv][lane] = best;
+        __syncthreads();
+        if ((wv & (2 * step - 1)) == 0)
+            best = cand_merge64(best, s_best[wv + step][63 - lane], lane);          // (descending list, reversed)
+    }
+    // row = backbone children, then ranked candidates not already present
+    if (wv == 0) write_row(adj_g + (size_t)w.pi[t] * deg, best, t, w.pi, N, deg, lane);
+    __syncthreads();
+}
+
+// Rows of the populated keys with more than PJ_TOUCH_C list cells, one per workgroup, of a graph with
+// at most PJ_LDS_TAB populated keys. The counters are indexed by position: bumps return nothing and are
+// never waited for (a returning add per cell, to notice first touches, was bound by its latency: 7.0
+// against 2.9 ms at 128K), and the candidates are the non-zero words.
+// grid: x = graph, y = worker of the graph (hubs are first in pi: every graph's come first this way)
+template <bool WIDE>
+__global__ __launch_bounds__(PJ_ROW_T) void pj_rows_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
                                                            int32_t* __restrict__ adj) {
-    __shared__ int s_ncand;
-    __shared__ Cand s_best[PJ_ROW_T / 64 - 1][64];
-    __shared__ uint32_t s_cnt[PJ_LDS_CNT];
-    __shared__ uint32_t s_tc[PJ_LDS_TUP], s_tp[PJ_LDS_TUP];
-    __shared__ int32_t s_tb[PJ_LDS_TUP];
-    const int g = blockIdx.y;
-    ProjWs w = carve(ws, l, g);
-    const int32_t* Lg = L + (size_t)g * M * knn;
-    int32_t* adj_g = adj + (size_t)g * N * deg;
-    char* sc = ws + l.o_scratch + ((size_t)g * gridDim.x + blockIdx.x) * l.scratch_per_wg;
-    const size_t quarter = l.scratch_per_wg / 4;
-    uint32_t* cnt_g = (uint32_t*)sc;                               // [cap] indexed by pos, zero at rest
-    int32_t* cand = (int32_t*)(sc + quarter);                      // [cap]
-    uint32_t* tc_g = (uint32_t*)(sc + 2 * quarter);                // [cap]
-    uint32_t* tp_g = (uint32_t*)(sc + 3 * quarter);                // [cap]
+    constexpr int WV = PJ_ROW_T / 64;
+    __shared__ Cand<WIDE> s_best[WV][64];
+    __shared__ int s_surv[WV][128];
+    __shared__ uint32_t tab[PJ_LDS_TAB];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    ProjWs w = carve(ws, l, blockIdx.x);
+    int32_t* adj_g = adj + (size_t)blockIdx.x * N * deg;
     const int H = *w.H;
-    if (H <= PJ_LDS_CNT) {
-        for (int i = threadIdx.x; i < H; i += PJ_ROW_T) s_cnt[i] = 0u;
+    if (H > PJ_LDS_TAB) return;
+    const int t_end = large_end(w.ppop, H, knn);
+    if ((int)blockIdx.y >= t_end) return;
+    for (int i = tid; i < H; i += PJ_ROW_T) tab[i] = 0u;
+    __syncthreads();
+    const int kp = knn <= 32 ? 32 : 64;
+    const int e = tid & (kp - 1), r0 = tid / kp, rstep = PJ_ROW_T / kp;
+    for (int t = blockIdx.y; t < t_end; t += gridDim.y) {
+        const int pa = w.ppop[t];
+        const int32_t* inv = w.inv + w.off[w.pi[t]];
+        auto bump = [&](int p) { atomicAdd(&tab[p], 1u); };
+        // A hub sits in tens of thousands of lists and one workgroup walks them all. Its lists
+        // go through a three-deep pipeline, sixteen per lane and stage: the list numbers of
+        // pass i + 2 and the rows of pass i + 1 are in flight while pass i bumps its counters
+        // (a pass that ran list number -> row -> counters in sequence would be two memory
+        // latencies long). Indices past the end are clamped, never branched around.
+        constexpr int UB = 16;
+        const int per_pass = UB * rstep;
+        const int n_pass = pa >= 8 * per_pass ? pa / per_pass : 0;
+        if (n_pass) {
+            int j1[UB], j2[UB], p0[UB], p1[UB];
+            auto load_inv = [&](int pass, int (&jj)[UB]) {
+                if (pass >= n_pass) pass = n_pass - 1;
+#pragma unroll
+                for (int u = 0; u < UB; ++u) jj[u] = inv[pass * per_pass + r0 + u * rstep];
+            };
+            auto load_rows = [&](const int (&jj)[UB], int (&pp)[UB]) {
+#pragma unroll
+                for (int u = 0; u < UB; ++u) pp[u] = w.lp[(size_t)jj[u] * knn + (e < knn ? e : 0)];
+            };
+            load_inv(0, j2);
+            load_inv(1, j1);
+            load_rows(j2, p0);
+            for (int pass = 0; pass < n_pass; ++pass) {
+                load_inv(pass + 2, j2);
+                load_rows(j1, p1);
+#pragma unroll
+                for (int u = 0; u < UB; ++u)
+                    if (e < knn && p0[u] >= 0) bump(p0[u]);
+#pragma unroll
+                for (int u = 0; u < UB; ++u) { p0[u] = p1[u]; j1[u] = j2[u]; }
+            }
+        }
+        walk_lists<4>(inv, w.lp, n_pass * per_pass, pa, knn, e, r0, rstep, bump);
         __syncthreads();
-        rows_for_graph<true>(Lg, w, s_cnt, cand, tc_g, tp_g, s_tc, s_tp, s_tb, N, knn, deg, H, adj_g,
-                             &s_ncand, s_best, s_cnt);
-    } else {
-        for (int i = threadIdx.x; i < PJ_LDS_CNT; i += PJ_ROW_T) s_cnt[i] = 0u;
+        if (tid == 0) tab[t] = 0u;                           // the key itself
         __syncthreads();
-        rows_for_graph<false>(Lg, w, cnt_g, cand, tc_g, tp_g, s_tc, s_tp, s_tb, N, knn, deg, H, adj_g,
-                              &s_ncand, s_best, s_cnt);
+        // a wavefront ranks its share of the positions (chunks of 64 dealt in turn)
+        Cand<WIDE> best = cand_none<WIDE>();
+        const int chunks = (H + 63) / 64, mine = (chunks - wv + WV - 1) / WV;
+        select_best<8>(best, mine * 64, (uint32_t)pa, w.ppop, s_surv[wv], lane,
+                       [&](int x, uint32_t& pos, uint32_t& c) {
+                           const int p = ((x >> 6) * WV + wv) * 64 + (x & 63);
+                           if (p < H) { pos = (uint32_t)p; c = tab[p]; }
+                       });
+        __syncthreads();
+        for (int i = tid; i < H; i += PJ_ROW_T) tab[i] = 0u;
+        finish_row<PJ_ROW_T>(best, s_best, adj_g, t, w, N, deg);
+    }
+}
+
+// The same for graphs with more populated keys: entries are hashed, [position + 1 : count] in one
+// word. A key with more cells than the table takes is done in passes over its lists, each counting the
+// positions of its own residue. What fits neither way (too many passes, count and position beyond 32
+// bits, a crowd in one residue) is left to pj_rows_hub_kernel: its first positions, or the overflow list.
+// bits of a count, and whether position and count share a word
+__device__ __forceinline__ bool hash_fits(int pa, int H, int* cb) {
+    int b = 1;
+    while ((pa >> b) != 0) ++b;
+    *cb = b;
+    return ((u64)(H + 1) << b) <= 0xffffffffull;
+}
+// first position the hash kernel takes: the lists of keys before it are too long (both conditions can
+// only get easier with fewer lists)
+__device__ __forceinline__ int hash_begin(const int32_t* ppop, int H, int knn) {
+    int lim = PJ_HASH_FILL * PJ_HASH_PASSES / knn, cb;
+    while (lim > 0 && !hash_fits(lim, H, &cb)) lim >>= 1;
+    return first_within(ppop, H, lim);
+}
+template <bool WIDE>
+__global__ __launch_bounds__(PJ_HASH_T) void pj_rows_hash_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
+                                                                 int32_t* __restrict__ adj) {
+    constexpr int WV = PJ_HASH_T / 64;
+    __shared__ Cand<WIDE> s_best[WV][64];
+    __shared__ int s_surv[WV][128];
+    __shared__ uint32_t tab[PJ_HASH_TAB];
+    __shared__ int s_over;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    ProjWs w = carve(ws, l, blockIdx.x);
+    int32_t* adj_g = adj + (size_t)blockIdx.x * N * deg;
+    const int H = *w.H;
+    if (H <= PJ_LDS_TAB) return;
+    const int t_begin = hash_begin(w.ppop, H, knn), t_end = large_end(w.ppop, H, knn);
+    if (t_begin + (int)blockIdx.y >= t_end) return;
+    for (int i = tid; i < PJ_HASH_TAB; i += PJ_HASH_T) tab[i] = 0u;
+    if (tid == 0) s_over = 0;
+    __syncthreads();
+    const int kp = knn <= 32 ? 32 : 64;
+    const int e = tid & (kp - 1), r0 = tid / kp, rstep = PJ_HASH_T / kp;
+    uint32_t* mine = tab + wv * (PJ_HASH_TAB / WV);
+    for (int t = t_begin + blockIdx.y; t < t_end; t += gridDim.y) {
+        const int pa = w.ppop[t];
+        const int32_t* inv = w.inv + w.off[w.pi[t]];
+        int cb;
+        (void)hash_fits(pa, H, &cb);
+        const int passes = (pa * knn + PJ_HASH_FILL - 1) / PJ_HASH_FILL;
+        // words the passes spread over: a key with few lists does not clear and scan the whole table
+        int slots = 64 * WV;
+        while (slots < PJ_HASH_TAB && slots < 2 * pa * knn) slots <<= 1;
+        const int quarter = slots / WV;
+        uint32_t* part = passes > 1 ? mine : tab + wv * quarter;
+        Cand<WIDE> best = cand_none<WIDE>();
+        for (int r = 0; r < passes; ++r) {
+            walk_lists<8>(inv, w.lp, 0, pa, knn, e, r0, rstep, [&](int p) {
+                // residue classes of a multiplicative hash: neighbouring positions spread out
+                if (p == t || (passes > 1 && (int)(((uint32_t)p * 2246822519u >> 16) % (uint32_t)passes) != r)) return;
+                if (!lds_table_bump(tab, slots, (uint32_t)p + 1u, cb)) s_over = 1;
+            });
+            __syncthreads();
+            const bool over = s_over != 0;                     // (uniform; set by this pass or one before)
+            // every wavefront packs its share of the table in place and ranks it
+            int nc = 0;
+            for (int q0 = 0; q0 < quarter; q0 += 64) {
+                const uint32_t v = part[q0 + lane];
+                part[q0 + lane] = 0u;
+                const u64 m = __ballot(v != 0u);
+                if (v != 0u) part[nc + __popcll(m & ((1ull << lane) - 1ull))] = v;
+                nc += __popcll(m);
+            }
+            pj_wave_sync();
+            if (!over)
+                select_best<16>(best, nc, (uint32_t)pa, w.ppop, s_surv[wv], lane,
+                                [&](int x, uint32_t& pos, uint32_t& c) {
+                                    const uint32_t v = part[x];
+                                    pos = (v >> cb) - 1u;
+                                    c = v & ((1u << cb) - 1u);
+                                });
+            pj_wave_sync();
+            for (int x = lane; x < nc; x += 64) part[x] = 0u;
+            __syncthreads();
+        }
+        if (s_over) {                                          // (uniform)
+            __syncthreads();
+            if (tid == 0) {
+                w.over[atomicAdd(&w.H[1], 1)] = t;
+                s_over = 0;
+            }
+            __syncthreads();
+        } else {
+            finish_row<PJ_HASH_T>(best, s_best, adj_g, t, w, N, deg);
+        }
+    }
+}
+
+// The keys pj_rows_hash_kernel leaves: counters of positions below PJ_LDS_TAB in LDS, of the others in
+// device memory (adds that return nothing), then every counter is looked at.
+// grid: x = graph, y = worker
+template <bool WIDE>
+__global__ __launch_bounds__(PJ_HUB_T) void pj_rows_hub_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
+                                                               int32_t* __restrict__ adj) {
+    constexpr int WV = PJ_HUB_T / 64;
+    __shared__ Cand<WIDE> s_best[WV][64];
+    __shared__ int s_surv[WV][128];
+    __shared__ uint32_t tab[PJ_LDS_TAB];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    ProjWs w = carve(ws, l, blockIdx.x);
+    int32_t* adj_g = adj + (size_t)blockIdx.x * N * deg;
+    const int H = *w.H;
+    if (H <= PJ_LDS_TAB) return;
+    const int t_hub = min(hash_begin(w.ppop, H, knn), large_end(w.ppop, H, knn)), n = t_hub + w.H[1];
+    if ((int)blockIdx.y >= n) return;
+    uint32_t* cnt = (uint32_t*)(ws + l.o_scratch + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * l.scratch_per_wg);
+    for (int i = tid; i < PJ_LDS_TAB; i += PJ_HUB_T) tab[i] = 0u;
+    for (int i = tid; i < H; i += PJ_HUB_T)
+        __hip_atomic_store(&cnt[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    const int kp = knn <= 32 ? 32 : 64;
+    const int e = tid & (kp - 1), r0 = tid / kp, rstep = PJ_HUB_T / kp;
+    for (int x = blockIdx.y; x < n; x += gridDim.y) {
+        const int t = x < t_hub ? x : w.over[x - t_hub];
+        const int pa = w.ppop[t];
+        walk_lists<8>(w.inv + w.off[w.pi[t]], w.lp, 0, pa, knn, e, r0, rstep, [&](int p) {
+            if (p == t) return;
+            if (p < PJ_LDS_TAB) atomicAdd(&tab[p], 1u);
+            else __hip_atomic_fetch_add(&cnt[p], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        });
+        __builtin_amdgcn_s_waitcnt(0);                       // the adds have been made before anyone reads
+        __syncthreads();
+        Cand<WIDE> best = cand_none<WIDE>();
+        const int chunks = (H + 63) / 64, mine = (chunks - wv + WV - 1) / WV;
+        select_best<16>(best, mine * 64, (uint32_t)pa, w.ppop, s_surv[wv], lane,
+                        [&](int y, uint32_t& pos, uint32_t& c) {
+                            const int p = ((y >> 6) * WV + wv) * 64 + (y & 63);
+                            if (p >= H) return;
+                            pos = (uint32_t)p;
+                            c = p < PJ_LDS_TAB ? tab[p]
+                                               : __hip_atomic_load(&cnt[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        });
+        __syncthreads();
+        for (int i = tid; i < PJ_LDS_TAB; i += PJ_HUB_T) tab[i] = 0u;
+        for (int i = PJ_LDS_TAB + tid; i < H; i += PJ_HUB_T)
+            __hip_atomic_store(&cnt[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        finish_row<PJ_HUB_T>(best, s_best, adj_g, t, w, N, deg);
     }
 }
 
 // Rows of the keys with few lists, one key per wavefront, no workgroup barrier. Co-occurrence
-// counts go into an open-addressing table in LDS (entry = (position + 1) << 7 | count, sized to
-// twice the key's list cells), which is then packed in place into the candidate list; the same
-// bitonic selection as above ranks the candidates, whose popularity and id are fetched by position
-// one chunk ahead.
+// counts go into an open-addressing table in LDS (entry = (position + 1) << 7 | count, twice the
+// key's list cells at least), which is then packed in place into the candidate list. TOUCH: most
+// list cells of a key of this launch's class, more than BELOW: small classes have small tables, and a
+// compute unit holds more wavefronts, whose trips to memory (list numbers, lists, popularities) hide
+// behind each other.
+// grid: x = graph, y = worker
+template <int TOUCH, int BELOW, bool WIDE>
 __global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_small_kernel(
     char* ws, ProjLayout l, int64_t N, int knn, int deg, int32_t* __restrict__ adj) {
-    __shared__ uint32_t s_slot[PJ_SMALL_WAVES][PJ_SMALL_SLOTS];
-    const int g = blockIdx.y;
+    constexpr int SLOTS = 2 * TOUCH;
+    __shared__ uint32_t s_slot[PJ_SMALL_WAVES][SLOTS];
+    __shared__ int s_surv[PJ_SMALL_WAVES][128];
+    const int g = blockIdx.x;
     ProjWs w = carve(ws, l, g);
     int32_t* adj_g = adj + (size_t)g * N * deg;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     uint32_t* slot = s_slot[wv];
     const int H = *w.H;
-    const int32_t* ppop = w.hk[0];
+    if (H >= (1 << 24)) return;                          // a position must fit the other 25 bits: pj_rows_kernel's
     const int kp = knn <= 32 ? 32 : 64, e = lane & (kp - 1), lpp = 64 / kp;     // lists per pass
-    for (int x = lane; x < PJ_SMALL_SLOTS; x += 64) slot[x] = 0u;
-    const int t_small = first_small(ppop, H, knn);
-    for (int t = t_small + blockIdx.x * PJ_SMALL_WAVES + wv; t < H; t += gridDim.x * PJ_SMALL_WAVES) {
+    for (int x = lane; x < SLOTS; x += 64) slot[x] = 0u;
+    pj_wave_sync();
+    const int t0 = first_within(w.ppop, H, small_limit(TOUCH, knn));
+    const int t1 = BELOW ? first_within(w.ppop, H, small_limit(BELOW, knn)) : H;
+    for (int t = t0 + blockIdx.y * PJ_SMALL_WAVES + wv; t < t1; t += gridDim.y * PJ_SMALL_WAVES) {
         const int a = w.pi[t];
-        const int pa = ppop[t];
-        const int o0 = w.off[a];
+        const int pa = w.ppop[t];
         int slots = 128;
-        while (slots < 2 * pa * knn) slots <<= 1;           // <= PJ_SMALL_SLOTS by small_limit()
-        // count
-        for (int li0 = lane / kp; li0 < pa; li0 += 4 * lpp) {
-            int pp[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int li = li0 + u * lpp;
-                const int j = w.inv[o0 + (li < pa ? li : pa - 1)];
-                pp[u] = (li < pa && e < knn) ? w.lp[(size_t)j * knn + (e < knn ? e : 0)] : -1;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (pp[u] < 0 || pp[u] == t) continue;
-                lds_table_bump(slot, slots, (uint32_t)pp[u] + 1u);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
+        while (slots < 2 * pa * knn) slots <<= 1;        // <= SLOTS by small_limit()
+        walk_lists<4>(w.inv + w.off[a], w.lp, 0, pa, knn, e, lane / kp, lpp, [&](int p) {
+            if (p != t) lds_table_bump(slot, slots, (uint32_t)p + 1u, 7);
+        });
+        pj_wave_sync();
         // pack the table in place: entry q moves to the number of entries before it
         int nc = 0;
         for (int q0 = 0; q0 < slots; q0 += 64) {
             const uint32_t v = slot[q0 + lane];
             slot[q0 + lane] = 0u;
-            const unsigned long long m = __ballot(v != 0u);
+            const u64 m = __ballot(v != 0u);
             if (v != 0u) slot[nc + __popcll(m & ((1ull << lane) - 1ull))] = v;
             nc += __popcll(m);
         }
-        __builtin_amdgcn_wave_barrier();
-        // rank the candidates 64 at a time; a chunk's popularity and id are fetched (by position)
-        // while the chunk before it is sorted and merged
-        auto fetch = [&](int x0, Cand& cd) {
-            cd = cand_none();
-            const int x = x0 + lane < nc ? x0 + lane : (nc > 0 ? nc - 1 : 0);
-            const uint32_t v = nc > 0 ? slot[x] : 0u;
-            const int pb = v ? (int)(v >> 7) - 1 : 0;
-            const uint32_t pbv = (uint32_t)ppop[pb];
-            const int32_t bv = w.pi[pb];
-            if (x0 + lane < nc) { cd.c = v & 127u; cd.pb = pbv; cd.b = bv; }
-        };
-        Cand best = cand_none(), cur, nxt;
-        fetch(0, cur);
-        for (int x0 = 0; x0 < nc; x0 += 64) {
-            fetch(x0 + 64, nxt);
-            const Cand last = cand_lane(best, 63);
-            if (__ballot(cand_before(cur, last, (uint32_t)pa)) != 0ull) {
-                cur = cand_sort64<false>(cur, (uint32_t)pa, lane);
-                if (cand_before(cur, best, (uint32_t)pa)) best = cur;
-                best = cand_merge64(best, (uint32_t)pa, lane);
-            }
-            cur = nxt;
-        }
-        __builtin_amdgcn_wave_barrier();
+        pj_wave_sync();
+        Cand<WIDE> best = cand_none<WIDE>();
+        select_best<(TOUCH + 63) / 64 < 16 ? (TOUCH + 63) / 64 : 16>(
+            best, nc, (uint32_t)pa, w.ppop, s_surv[wv], lane, [&](int x, uint32_t& pos, uint32_t& c) {
+                const uint32_t v = slot[x];
+                pos = (v >> 7) - 1u;
+                c = v & 127u;
+            });
+        pj_wave_sync();
         for (int x = lane; x < nc; x += 64) slot[x] = 0u;       // the table is empty again
-        write_row(adj_g + (size_t)a * deg, best, nc < deg ? nc : deg, t, w.pi, N, deg, lane);
+        pj_wave_sync();
+        write_row(adj_g + (size_t)a * deg, best, t, w.pi, N, deg, lane);
     }
+}
+
+template <bool WIDE>
+static void project_rows(const ProjLayout& l, char* ws, int n_graphs, int64_t N, int knn, int deg, hipStream_t st,
+                         int32_t* adj) {
+    // workgroups that fill the part: 4 per compute unit by position, 2 of the hash kernel, 2, 4 and 8 of
+    // the small classes (LDS), all with a share of keys each
+    auto wgs = [&](int all) { return (unsigned)(n_graphs >= all ? 1 : all / n_graphs); };
+    // (a hub takes its workgroup long: enough workers that no other key waits behind one)
+    hipLaunchKernelGGL(pj_rows_kernel<WIDE>, dim3(n_graphs, wgs(4096) < 128 ? wgs(4096) : 128u), dim3(PJ_ROW_T), 0, st,
+                       ws, l, N, knn, deg, adj);
+    if (l.cap > PJ_LDS_TAB) {
+        hipLaunchKernelGGL(pj_rows_hash_kernel<WIDE>, dim3(n_graphs, wgs(2048)), dim3(PJ_HASH_T), 0, st, ws, l, N,
+                           knn, deg, adj);
+        hipLaunchKernelGGL(pj_rows_hub_kernel<WIDE>, dim3(n_graphs, l.n_hub_wg), dim3(PJ_HUB_T), 0, st, ws, l, N,
+                           knn, deg, adj);
+    }
+    const dim3 threads(PJ_SMALL_WAVES * 64);
+    hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_C, PJ_TOUCH_B, WIDE>), dim3(n_graphs, wgs(512)), threads, 0, st,
+                       ws, l, N, knn, deg, adj);
+    hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_B, PJ_TOUCH_A, WIDE>), dim3(n_graphs, wgs(1024)), threads, 0, st,
+                       ws, l, N, knn, deg, adj);
+    hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_A, 0, WIDE>), dim3(n_graphs, wgs(2048)), threads, 0, st, ws, l,
+                       N, knn, deg, adj);
 }
 
 ra_status ra_launch_project(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg,
                             void* workspace, hipStream_t st, int32_t* adj, int32_t* entry) {
     if (M * (int64_t)knn >= ((int64_t)1 << 31))
         RA_FAIL(RA_EUNSUP, "M * knn must stay below 2^31 list cells");
+    if (n_graphs > 65535) RA_FAIL(RA_EUNSUP, "more than 65535 graphs");
     const ProjLayout l = proj_layout(n_graphs, N, M, knn);
     char* ws = (char*)workspace;
     const int64_t cells = M * knn;
     const unsigned gx = 256;
-    hipLaunchKernelGGL(pj_zero_kernel, dim3(gx, n_graphs), dim3(256), 0, st, ws, l, N, n_graphs);
-    hipLaunchKernelGGL(pj_pop_kernel, dim3(gx, n_graphs), dim3(256), 0, st, L, ws, l, cells, N);
-    hipLaunchKernelGGL(pj_order_kernel, dim3(n_graphs), dim3(PJ_T), 0, st, ws, l, N, M, entry);
-    hipLaunchKernelGGL(pj_inv_kernel, dim3(gx, n_graphs), dim3(256), 0, st, L, ws, l, cells, knn, N);
-    hipLaunchKernelGGL(pj_backbone_kernel, dim3(gx, n_graphs), dim3(256), 0, st, ws, l, N, deg, adj);
-    hipLaunchKernelGGL(pj_rows_kernel, dim3(l.n_wg, n_graphs), dim3(PJ_ROW_T), 0, st, L, ws, l, N, M,
-                       knn, deg, adj);
-    const unsigned small_wg = n_graphs >= 512 ? 1u : (unsigned)(512 / n_graphs);   // 2 per compute unit
-    hipLaunchKernelGGL(pj_rows_small_kernel, dim3(small_wg, n_graphs), dim3(PJ_SMALL_WAVES * 64), 0, st,
-                       ws, l, N, knn, deg, adj);
+    const unsigned zx = N < 256 * 256 ? (unsigned)((N + 255) / 256) : gx;
+    hipLaunchKernelGGL(pj_zero_kernel, dim3(zx, n_graphs), dim3(256), 0, st, ws, l, N);
+    // a workgroup of the cell kernels has at least a few thousand cells, so that its table pays
+    unsigned cx = (unsigned)((cells + 8191) / 8192);
+    const unsigned fill = n_graphs >= 2048 ? 1u : (unsigned)(2048 / n_graphs);
+    if (cx > fill) cx = fill;
+    hipLaunchKernelGGL(pj_pop_kernel, dim3(cx, n_graphs), dim3(PJ_CELL_T), 0, st, L, ws, l, cells, N);
+    hipLaunchKernelGGL(pj_count_kernel, dim3(l.n_blk, n_graphs), dim3(256), 0, st, ws, l, N);
+    hipLaunchKernelGGL(pj_compact_kernel, dim3(l.n_blk, n_graphs), dim3(256), 0, st, ws, l, N, M);
+    ra_status rc = ra_launch_sort(ws + l.o_keys, l.per_graph / 8, n_graphs, l.cap_pad, (const int32_t*)(ws + l.o_H),
+                                  l.per_graph / 4, st);
+    if (rc != RA_OK) return rc;
+    const unsigned px = l.cap < 64 * 256 ? (unsigned)((l.cap + 255) / 256) : 64u;
+    hipLaunchKernelGGL(pj_pi_kernel, dim3(px, n_graphs), dim3(256), 0, st, ws, l, M, entry);
+    // (24 KB of LDS: six of these workgroups per compute unit)
+    const unsigned fill_inv = n_graphs >= 1536 ? 1u : (unsigned)(1536 / n_graphs);
+    hipLaunchKernelGGL(pj_inv_kernel, dim3(cx < fill_inv ? cx : fill_inv, n_graphs), dim3(PJ_CELL_T), 0, st, L, ws, l, M, knn, N);
+    if (deg % 4 == 0)
+        hipLaunchKernelGGL(pj_backbone_kernel<4>, dim3(zx, n_graphs), dim3(256), 0, st, ws, l, N, deg, adj);
+    else
+        hipLaunchKernelGGL(pj_backbone_kernel<1>, dim3(zx, n_graphs), dim3(256), 0, st, ws, l, N, deg, adj);
+    if (M <= (1 << 19)) project_rows<false>(l, ws, n_graphs, N, knn, deg, st, adj);
+    else project_rows<true>(l, ws, n_graphs, N, knn, deg, st, adj);
     RA_HIP(hipGetLastError());
     return RA_OK;
 }

@@ -23,52 +23,88 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
 // Root sets (see run_search): per head [0] the number of ids, [1] 1 + the number of the entry
 // point's neighbours, then the ids: the entry point, its distinct valid neighbours in row order,
 // then the distinct valid neighbours of those that are not among the former, in row order.
-// One workgroup per head; a build-time step, written for clarity rather than speed.
-#define RT_THREADS 256
+// One workgroup per head. Which of two equal ids comes first is decided in a hash table in LDS: every
+// id leaves the smallest place it occurs at (level 1 before level 2), and only the occurrence at that
+// place is kept; prefix sums over the kept ones give the order.
+#define RT_THREADS 1024
+#define RT_SLOTS 8192             // at most RA_MAX_DEG + 1 + RA_MAX_DEG^2 = 4161 ids
+__device__ __forceinline__ int rt_slot(int* ids, int id) {
+    uint32_t h = ((uint32_t)id * 2654435761u) >> 19;
+    while (true) {                                       // (the table is never more than half full)
+        const int seen = atomicCAS(&ids[h], -1, id);
+        if (seen == -1 || seen == id) return (int)h;
+        h = (h + 1u) & (RT_SLOTS - 1);
+    }
+}
 __global__ __launch_bounds__(RT_THREADS) void roots_kernel(const int32_t* __restrict__ adj,
                                                            const int32_t* __restrict__ entry, int64_t N,
                                                            int deg, int32_t* __restrict__ roots, int cap) {
     __shared__ int l1[RA_MAX_DEG + 1];
-    __shared__ int l2[RA_MAX_DEG * RA_MAX_DEG];
-    __shared__ unsigned char keep[RA_MAX_DEG * RA_MAX_DEG];
+    __shared__ int tab_id[RT_SLOTS], tab_at[RT_SLOTS];
+    __shared__ int wsum[RT_THREADS / RA_WAVE];
     __shared__ int n1s;
-    const int tid = threadIdx.x, head = blockIdx.x;
+    const int tid = threadIdx.x, head = blockIdx.x, lane = tid & (RA_WAVE - 1), wv = tid / RA_WAVE;
     const int32_t* adj_h = adj + (size_t)head * N * deg;
     int32_t* out = roots + (size_t)head * cap;
     const int e0 = entry[head];
-    if (tid == 0) {
-        int n1 = 1;
-        l1[0] = e0;
-        for (int j = 0; j < deg; ++j) {
-            const int nb = adj_h[(size_t)e0 * deg + j];
-            bool ok = nb >= 0 && nb < N;
-            for (int x = 0; ok && x < n1; ++x) ok = l1[x] != nb;
-            if (ok) l1[n1++] = nb;
+    for (int x = tid; x < RT_SLOTS; x += RT_THREADS) { tab_id[x] = -1; tab_at[x] = 0x7fffffff; }
+    __syncthreads();
+    // level 1 (one wavefront: deg <= 64): the entry point at place 0, cell j of its row at place 1 + j
+    if (wv == 0) {
+        const int nb = lane < deg ? adj_h[(size_t)e0 * deg + lane] : -1;
+        const bool ok = nb >= 0 && nb < N && nb != e0;
+        int slot = 0;
+        if (lane == 0) tab_at[rt_slot(tab_id, e0)] = 0;
+        if (ok) {
+            slot = rt_slot(tab_id, nb);
+            atomicMin(&tab_at[slot], 1 + lane);
         }
-        n1s = n1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const bool first = ok && tab_at[slot] == 1 + lane;
+        const unsigned long long m = __ballot(first);
+        if (first) l1[1 + __popcll(m & ((1ull << lane) - 1ull))] = nb;
+        if (lane == 0) { l1[0] = e0; n1s = 1 + __popcll(m); }
     }
     __syncthreads();
     const int n1 = n1s, cells = (n1 - 1) * deg;
-    for (int x = tid; x < cells; x += RT_THREADS) {
-        int nb = adj_h[(size_t)l1[1 + x / deg] * deg + x % deg];
-        if (nb < 0 || nb >= N) nb = -1;
-        for (int y = 0; nb >= 0 && y < n1; ++y)
-            if (l1[y] == nb) nb = -1;
-        l2[x] = nb;
+    for (int x = tid; x < n1; x += RT_THREADS) out[2 + x] = l1[x];
+    // level 2: cell x at place 1 + deg + x
+    constexpr int PER = (RA_MAX_DEG * RA_MAX_DEG + RT_THREADS - 1) / RT_THREADS;
+    int nb[PER], slot[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const int x = r * RT_THREADS + tid;
+        nb[r] = x < cells ? adj_h[(size_t)l1[1 + x / deg] * deg + x % deg] : -1;
+    }
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        if (nb[r] >= N) nb[r] = -1;
+        slot[r] = 0;
+        if (nb[r] >= 0) {
+            slot[r] = rt_slot(tab_id, nb[r]);
+            atomicMin(&tab_at[slot[r]], 1 + deg + r * RT_THREADS + tid);
+        }
     }
     __syncthreads();
-    for (int x = tid; x < cells; x += RT_THREADS) {
-        const int nb = l2[x];
-        bool k = nb >= 0;
-        for (int y = 0; k && y < x; ++y) k = l2[y] != nb;
-        keep[x] = k;
+    int n = n1;
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        if (r * RT_THREADS >= cells) break;              // uniform
+        const bool keep = nb[r] >= 0 && tab_at[slot[r]] == 1 + deg + r * RT_THREADS + tid;
+        const unsigned long long m = __ballot(keep);
+        if (lane == 0) wsum[wv] = __popcll(m);
+        __syncthreads();
+        int before = n, all = 0;
+        for (int y = 0; y < RT_THREADS / RA_WAVE; ++y) {
+            if (y < wv) before += wsum[y];
+            all += wsum[y];
+        }
+        if (keep) out[2 + before + __popcll(m & ((1ull << lane) - 1ull))] = nb[r];
+        n += all;
+        __syncthreads();
     }
-    __syncthreads();
     if (tid == 0) {
-        int n = 0;
-        for (int x = 0; x < n1; ++x) out[2 + n++] = l1[x];
-        for (int x = 0; x < cells; ++x)
-            if (keep[x]) out[2 + n++] = l2[x];
         out[0] = n;
         out[1] = n1;
     }
@@ -94,10 +130,12 @@ __global__ __launch_bounds__(SD_THREADS) void seeds_kernel(const int32_t* __rest
                                                            int cap) {
     __shared__ int pos[RA_MAX_SEEDS];
     __shared__ int keep[RA_MAX_SEEDS];
+    __shared__ int tab_id[RT_SLOTS], tab_at[RT_SLOTS];
     __shared__ int wsum[SD_THREADS / RA_WAVE];
     const int tid = threadIdx.x, head = blockIdx.x;
     const int32_t* adj_h = adj + (size_t)head * N * deg;
     int32_t* out = seeds + (size_t)head * cap;
+    for (int x = tid; x < RT_SLOTS; x += SD_THREADS) { tab_id[x] = -1; tab_at[x] = 0x7fffffff; }
     for (int p = tid; p < n_seeds; p += SD_THREADS) {
         // the path from the root to position p: the bits of p + 1 below its leading one, high to low
         int cur = entry[head];
@@ -110,12 +148,16 @@ __global__ __launch_bounds__(SD_THREADS) void seeds_kernel(const int32_t* __rest
         pos[p] = cur;
     }
     __syncthreads();
+    // of equal nodes the one at the lowest position stays
     for (int p = tid; p < n_seeds; p += SD_THREADS) {
         const int id = pos[p];
-        bool k = id >= 0;
-        for (int y = 0; k && y < p; ++y) k = pos[y] != id;
-        keep[p] = k;
+        if (id < 0) continue;
+        const int slot = rt_slot(tab_id, id);
+        keep[p] = slot;
+        atomicMin(&tab_at[slot], p);
     }
+    __syncthreads();
+    for (int p = tid; p < n_seeds; p += SD_THREADS) keep[p] = pos[p] >= 0 && tab_at[keep[p]] == p;
     __syncthreads();
     // ordered compaction: RA_MAX_SEEDS <= 2 * SD_THREADS, two rounds of a workgroup-wide prefix sum
     int base = 0;

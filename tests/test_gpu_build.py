@@ -261,6 +261,64 @@ def test_build_argument_errors():
     assert e.value.status == 6
 
 
+def _project_case(kind):
+    rng = np.random.default_rng(23)
+    if kind == "wide":                # more queries than a packed candidate key takes (2^19)
+        N, M, knn, deg = 300, (1 << 19) + 5, 3, 12
+        p = 1.0 / np.arange(1, N + 1)
+        first = rng.choice(N, M, p=p / p.sum())
+        L = (first[:, None] + np.cumsum(rng.integers(1, 40, (M, knn)), 1)) % N
+        L[:, 0] = first
+        bad = (np.diff(np.sort(L, 1), axis=1) == 0).any(1)
+        L[bad] = (L[bad][:, :1] + np.arange(knn)) % N
+        return N, L, deg, np.arange(0, N, 9)
+    if kind == "passes":              # keys whose lists take two, three and four passes of the hash table, and hubs
+        N, M, knn, deg = 60000, 9000, 48, 33
+        mids = np.arange(40)
+        share = np.repeat([250, 430, 650, 850], 10)          # lists of each
+        L = np.stack([40 + rng.choice(N - 40, knn, replace=False) for _ in range(M)])
+        for a, n in zip(mids, share):
+            j = rng.choice(M, n, replace=False)
+            L[j, a] = a                                      # (its own column: rows stay distinct)
+        L[:3000, 47] = 59999
+        keep = ~((L[:, :47] == 59999).any(1) & (L[:, 47] == 59999))
+        return N, L[keep], deg, np.concatenate([mids, [59999], rng.choice(N, 150, replace=False)])
+    # "overflow": one key's co-listed keys all in one residue class of its two passes, more of them than slots
+    knn, deg, hub_lists = 48, 32, 425
+    N = 42000
+    ids = np.arange(1, N)                                    # every other key is in one list: position = id
+    res = (((ids.astype(np.uint64) * 2246822519) & 0xffffffff) >> 16) % 2
+    crowd = ids[res == 0][:hub_lists * (knn - 1)]
+    assert crowd.size == hub_lists * (knn - 1) > 16384
+    rest = np.setdiff1d(ids, crowd)
+    rest = rest[:rest.size // knn * knn]
+    L = np.concatenate([np.concatenate([np.zeros((hub_lists, 1), np.int64), crowd.reshape(hub_lists, knn - 1)], 1),
+                        rest.reshape(-1, knn)])
+    return N, L, deg, np.concatenate([[0], rng.choice(N, 60, replace=False)])
+
+
+@pytest.mark.parametrize("kind", ["wide", "passes", "overflow"])
+def test_projection_row_kernels_at_their_limits(kind):
+    """The ends of what each row kernel takes: more queries than a packed candidate key orders, lists that
+    go through the hash table in several passes, a crowd of keys that overflows it and falls to the
+    counters in device memory. Sampled rows against the oracle, bit for bit."""
+    N, L, deg, rows = _project_case(kind)
+    L = np.ascontiguousarray(L.astype(np.int32))
+    assert (np.diff(np.sort(L[:5000], 1), axis=1) > 0).all()
+    adj, entry = ra.ra_project(torch.from_numpy(L[None]).to(DEV), N, deg)
+    adj = adj[0].cpu().numpy()
+    pop = np.bincount(L.ravel(), minlength=N)
+    pi = np.lexsort((np.arange(N), -pop))
+    pos = np.empty(N, np.int64)
+    pos[pi] = np.arange(N)
+    assert int(entry[0]) == pi[0]
+    order = np.argsort(L.ravel(), kind="stable")
+    begin = np.searchsorted(L.ravel()[order], np.arange(N + 1))
+    for a in rows:
+        members = order[begin[a]:begin[a + 1]] // L.shape[1]
+        assert adj[a].tolist() == OP.adjacency_row(L, int(a), pop, pos, pi, deg, members), a
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("N,M,knn", [(129, 1, 1), (160, 255, 32), (255, 257, 64), (4097, 300, 48), (1024, 1025, 33),
                                      (70000, 96, 32)])
