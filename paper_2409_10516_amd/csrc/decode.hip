@@ -471,12 +471,6 @@ bool ra_decode_needs_global_bitset(int64_t N, int deg, int ef, int expand, int t
            decode_lds_bytes(N, deg, ef, expand, topk, false, &off) > SR_LDS_LIMIT;
 }
 
-__global__ void dc_fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (size_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
 // helper workgroups in front of the heads' in a decode launch: one per (sequence, KV head), for
 // GQA groups of 1, 2, 4 or 8 while the handle has them switched on
 static int decode_helper_slots(const float* coop, int coop_mode, int n_seq, int n_q, int n_kv) {
@@ -532,11 +526,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
     if (lds > SR_LDS_LIMIT)
         RA_FAIL(RA_EUNSUP, "decode state needs %zu B of LDS (limit %d): lower ef or expand", lds,
                 SR_LDS_LIMIT);
-    if (gb) {
-        if (!bitset) RA_FAIL(RA_EINVAL, "global visited bitset missing");
-        const size_t words = (size_t)heads * ((Ng + 31) >> 5);
-        hipLaunchKernelGGL(dc_fill_u32_kernel, dim3(1024), dim3(256), 0, st, bitset, words, 0u);
-    }
+    if (gb && !bitset) RA_FAIL(RA_EINVAL, "global visited bitset missing");
     const float scale = 1.0f / sqrtf((float)RA_D);
     // one helper workgroup per (sequence, KV head) in front of the heads' (GQA groups of 1, 2, 4 or 8)
     if (!coop) RA_FAIL(RA_EINVAL, "hand-over area missing");

@@ -13,13 +13,6 @@ __global__ __launch_bounds__(T) void search_kernel(
                           expand, gbits, ids, stats, nullptr, roots, root_cap, kscale, NoHook());
 }
 
-__global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (size_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
-
 // Root sets (see run_search): per head [0] the number of ids, [1] 1 + the number of the entry
 // point's neighbours, then the ids: the entry point, its distinct valid neighbours in row order,
 // then the distinct valid neighbours of those that are not among the former, in row order.
@@ -215,11 +208,7 @@ ra_status ra_launch_search(const void* q, const int32_t* adj, const int32_t* ent
         RA_FAIL(RA_EUNSUP, "search state needs %zu B of LDS (limit %d): lower ef or expand", lds,
                 SR_LDS_LIMIT);
     const int heads = n_seq * n_q;
-    if (gb) {
-        if (!bitset) RA_FAIL(RA_EINVAL, "global visited bitset missing");
-        const size_t words = (size_t)heads * ((N + 31) >> 5);
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(1024), dim3(256), 0, st, bitset, words, 0u);
-    }
+    if (gb && !bitset) RA_FAIL(RA_EINVAL, "global visited bitset missing");
     const int threads = search_threads(heads, ef);
 #define RA_SR_LAUNCH_T(DTV, KTV, GB, TV)                                                          \
     do {                                                                                          \

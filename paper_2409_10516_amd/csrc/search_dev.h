@@ -41,6 +41,7 @@
 
 enum { C_MISSED = 0, C_NCAND = 1, C_NKEEP = 2, C_NUNEXP = 3, C_LO = 4, C_HI = 5, C_NSURV = 6, C_BIN = 7, C_WTOT = 8,
        C_COUNT = 8 + SR_THREADS / RA_WAVE };
+#define SR_HSUM 33                // blocks of 64 beam slots: ef + 1 <= 2049 of them
 #define SR_PREFILTER_SLACK 64     // a step that keeps more than ef + this many candidates drops the hopeless ones first
 #define SR_PREFILTER_REGS 8       // ... when a thread can hold its share of them (nk <= 8 T)
 
@@ -342,6 +343,13 @@ __device__ __forceinline__ int xcd_aware_head(int block, int heads, int G) {
     return (block % n_groups) * G + block / n_groups;
 }
 
+// Sets key id's bit of the visited set and returns the word as it was. One workgroup owns the bitset, in
+// LDS or in device memory, so workgroup scope is enough (and the workgroup clears it itself: no launch
+// ahead of the walk).
+__device__ __forceinline__ uint32_t claim_key(uint32_t* bits, int id) {
+    return __hip_atomic_fetch_or(&bits[id >> 5], 1u << (id & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // The whole search of one (sequence, query head) by one workgroup of T threads.
 // N is the number of keys the graph covers; the key rows of a (sequence, KV head) start every
 // kv_stride rows (kv_stride >= N: the cache may hold tokens appended after the index was built).
@@ -406,7 +414,7 @@ __device__ __forceinline__ void score_seed_share(int head, int part, int parts, 
     const int c_beg = part * per;
     // (twice the rows in flight per lane group where the workgroup is small: the walk's own registers
     // are not live here, and a share is then one trip to memory again)
-    constexpr int R = (T <= 512 && KT != RA_F32) ? 2 * SR_UNROLL : SR_UNROLL, PER = T / 16;
+    constexpr int R = (T <= 512 && KT != RA_F32) ? 16 : SR_UNROLL, PER = T / 16;
     const char* Kh = reinterpret_cast<const char*>(K) + ((size_t)seq * n_kv + kvh) * kv_stride * RA_D * ksz;
     ScoreQuery<KT> qv;
     load_score_query<DT, KT>(reinterpret_cast<const char*>(q) + (size_t)head * RA_D * esz, lane16, qv);
@@ -469,6 +477,10 @@ __device__ __forceinline__ int run_search(
     const int maxc = expand * deg;
     const int nwords = (int)((N + 31) >> 5);
 
+    // A beam entry's place needs the number of candidates in the beam slots before its wavefront's 64. A
+    // large workgroup (wide beams are its only ones) keeps sums per 64 slots; with 512 threads or fewer
+    // the beam is a few blocks and adding them up is cheaper than one more LDS add per candidate.
+    constexpr bool HSUM = T == 1024;
     SR_TICK_INIT;
 #ifdef SR_WAVE_CLOCKS
     if (head == 0 && tid == 0) sr_wave_ticks[0] = wall_clock64();      // search entered
@@ -480,7 +492,9 @@ __device__ __forceinline__ int run_search(
     int* cnt = cid + maxc;           // [maxc] merge counters of the candidates, zero between steps
     int* hist = cnt + maxc;          // [ef + 1] candidates per beam slot, zero between steps
     int* hist_nxt = hist + ef + 1;   // [ef + 1] the one the next step fills
-    int* picks = hist_nxt + ef + 1;  // [RA_MAX_EXPAND]
+    int* hsum = hist_nxt + ef + 1;   // [SR_HSUM] candidates per 64 beam slots, zero between steps
+    int* hsum_nxt = hsum + SR_HSUM;  // [SR_HSUM]
+    int* picks = hsum_nxt + SR_HSUM; // [RA_MAX_EXPAND]
     int* ctr = picks + RA_MAX_EXPAND;
     int* wtot = ctr + C_WTOT;
     // urank[i], i in [0, bn]: unexpanded entries among the first i of the beam, as of the last pick
@@ -514,9 +528,8 @@ __device__ __forceinline__ int run_search(
         my_root = root[2 + (tid < root_cap - 2 ? tid : 0)];      // unconditional: same trip as the header
     }
     // (the loads above are in flight while the LDS state is cleared)
-    if (!GBITS)
-        for (int i = tid; i < nwords; i += T) bits[i] = 0u;
-    for (int i = tid; i < maxc + 2 * ef + 2; i += T) cnt[i] = 0;      // cnt, hist, hist_nxt
+    for (int i = tid; i < nwords; i += T) bits[i] = 0u;
+    for (int i = tid; i < maxc + 2 * ef + 2 + 2 * SR_HSUM; i += T) cnt[i] = 0;      // cnt, hist, hsum and their twins
     // A seed set (ra_launch_seeds) has the same layout with [1] = 0: the walk starts from all of its
     // keys at once, scored in one gather, the best ef of them in the beam and none of them expanded.
     // That is a start of its own, not a shortcut for steps of the single-entry walk: no step is
@@ -535,7 +548,7 @@ __device__ __forceinline__ int run_search(
         for (int c = tid; c < n_root; c += T) {
             const int id = c == tid ? my_root : root[2 + c];
             cid[c] = id;
-            atomicOr(&bits[id >> 5], 1u << (id & 31));
+            (void)claim_key(bits, id);
         }
         if (tid == 0) {
             urank[0] = 0;
@@ -561,7 +574,7 @@ __device__ __forceinline__ int run_search(
                 ctr[C_NCAND] = 0;
                 ctr[C_NKEEP] = 0;
                 ctr[C_NUNEXP] = 1;
-                atomicOr(&bits[e0 >> 5], 1u << (e0 & 31));
+                (void)claim_key(bits, e0);
             }
         }
         bn = 1; n_visited = 1; n_expanded = 0; n_iters = 0;
@@ -583,7 +596,7 @@ __device__ __forceinline__ int run_search(
         //      the rows in flight of a step's gather (a seed set of a thousand keys is one trip to
         //      memory for 1024 threads). The beam is empty, so every key is kept; the first
         //      n_first of a root set enter as expanded.
-        constexpr int SEED_ROWS = KT == RA_F32 ? SR_UNROLL : 2 * SR_UNROLL;
+        constexpr int SEED_ROWS = KT == RA_F32 ? SR_UNROLL : 16;
         uint32_t lo = 0xffffffffu, hi = 0u;                  // of the ordered score bits (see the pre-filter)
         // R rows per 16-lane group with no branch between them: the ids leave LDS in one batch, the
         // rows are all requested before the first is scored, and each is scored as it arrives
@@ -756,7 +769,7 @@ __device__ __forceinline__ int run_search(
                         const int nb = nbv[u];
                         if (nb >= 0 && nb < N) {
                             const uint32_t bit = 1u << (nb & 31);
-                            const uint32_t old = atomicOr(&bits[nb >> 5], bit);
+                            const uint32_t old = claim_key(bits, nb);
                             if (!(old & bit)) cid[atomicAdd(&ctr[C_NCAND], 1)] = nb;
                         }
                     }
@@ -969,6 +982,7 @@ __device__ __forceinline__ int run_search(
                 const int b = count_better(cur, bn, ckey[c]);
                 if (b) atomicAdd(&cnt[c], b << 16);           // high half: beam entries above it
                 atomicAdd(&hist[b], 1);
+                if constexpr (HSUM) atomicAdd(&hsum[b >> 6], 1);
             }
             SR_TICK(8);
             const float inv_nk = 1.0f / (float)nk;
@@ -997,6 +1011,8 @@ __device__ __forceinline__ int run_search(
                 ctr[C_NKEEP] = 0;
             }
             for (int i = tid; i <= ef; i += T) hist_nxt[i] = 0;
+            if constexpr (HSUM)
+                if (tid < SR_HSUM) hsum_nxt[tid] = 0;
             SR_TICK(10);
             for (int e0 = 0; e0 < E; e0 += T) {                   // T elements per round
                 const int e = e0 + tid;
@@ -1005,7 +1021,11 @@ __device__ __forceinline__ int run_search(
                 int cbeam = 0;
                 if (e0 + wv * RA_WAVE < bn) {                     // this wavefront has beam entries
                     int before = 0;
-                    for (int x = 0; x < e0 / RA_WAVE + wv; ++x) before += hist[x * RA_WAVE + lane];
+                    if constexpr (HSUM) {
+                        if (lane < e0 / RA_WAVE + wv) before = hsum[lane];      // (below SR_HSUM: e < bn)
+                    } else {
+                        for (int x = 0; x < e0 / RA_WAVE + wv; ++x) before += hist[x * RA_WAVE + lane];
+                    }
                     before = __builtin_amdgcn_readlane(wave_incl_scan(before), RA_WAVE - 1);
                     cbeam = before + wave_incl_scan(e < bn ? hist[e] : 0);
                 }
@@ -1060,6 +1080,7 @@ __device__ __forceinline__ int run_search(
         u64* t = cur; cur = nxt; nxt = t;
         uint16_t* tu = urank; urank = urank_nxt; urank_nxt = tu;
         int* th = hist; hist = hist_nxt; hist_nxt = th;
+        if constexpr (HSUM) { int* ts = hsum; hsum = hsum_nxt; hsum_nxt = ts; }
         picked = true;
         first = false;
     }
@@ -1067,7 +1088,10 @@ __device__ __forceinline__ int run_search(
     hook.before_output();
     early_acc ^= early_a ^ early_b;
     if (early_acc == 0x9e3779b9u && N < 0) ids[(size_t)head * topk] = -1;    // never: keeps the early touches alive
-    // ---- result: best-first beam entries outside the static set W = [0,s) u [N-w,N)
+    // ---- result: best-first beam entries outside the static set W = [0,s) u [N-w,N). A short list is the
+    //      first wavefront's alone (the others wait at the closing barrier); of a long one (a wavefront
+    //      would be 32 rounds over 2048 entries) every wavefront takes rounds, T entries at a time.
+    if (T < 1024 || topk <= 256) {
     if (tid < RA_WAVE) {
         int32_t* out = ids + (size_t)head * topk;
         int cnt = 0;
@@ -1090,14 +1114,44 @@ __device__ __forceinline__ int run_search(
             if (lds_ids) lds_ids[i] = -1;
         }
         if (tid == 0) ctr[C_NKEEP] = cnt;
-        if (stats && tid == 0) {
-            ra_stats st;
-            st.n_visited = n_visited;
-            st.n_expanded = n_expanded;
-            st.n_iters = n_iters;
-            st.n_returned = cnt;
-            stats[head] = st;
+    }
+    } else {
+        int32_t* out = ids + (size_t)head * topk;
+        int cnt = 0;
+        for (int base = 0; base < bn && cnt < take; base += T) {        // (uniform)
+            const int i = base + tid;
+            const int id = i < bn ? key_id(cur[i]) : -1;
+            const bool ok = i < bn && id >= s && id < N - w;
+            const u64 mask = __ballot(ok);
+            if (lane == 0) wtot[wv] = __popcll(mask);
+            __syncthreads();
+            int pos = cnt;
+            for (int x = 0; x < T / RA_WAVE; ++x) {
+                const int c = wtot[x];
+                if (x < wv) pos += c;
+                cnt += c;
+            }
+            pos += __popcll(mask & ((1ull << lane) - 1ull));
+            if (ok && pos < take) {
+                out[pos] = id;
+                if (lds_ids) lds_ids[pos] = id;
+            }
+            __syncthreads();
         }
+        if (cnt > take) cnt = take;
+        for (int i = cnt + tid; i < topk; i += T) {
+            out[i] = -1;
+            if (lds_ids) lds_ids[i] = -1;
+        }
+        if (tid == 0) ctr[C_NKEEP] = cnt;
+    }
+    if (stats && tid == 0) {
+        ra_stats st;
+        st.n_visited = n_visited;
+        st.n_expanded = n_expanded;
+        st.n_iters = n_iters;
+        st.n_returned = ctr[C_NKEEP];
+        stats[head] = st;
     }
     __syncthreads();
     SR_TICK(6);
@@ -1119,7 +1173,7 @@ static inline int search_threads(int heads, int ef) {
 static inline size_t search_lds_bytes(int64_t N, int deg, int ef, int expand, bool global_bitset) {
     const int maxc = expand * deg;
     size_t b = (size_t)2 * ef * 8 + (size_t)(maxc + 16) * 8 + (size_t)maxc * 4 + (size_t)(maxc + 2 * ef + 2) * 4 +
-               (RA_MAX_EXPAND + C_COUNT) * 4 + (size_t)(ef + 1) * 4;
+               (RA_MAX_EXPAND + C_COUNT + 2 * SR_HSUM) * 4 + (size_t)(ef + 1) * 4;
     if (!global_bitset) b += (size_t)((N + 31) >> 5) * 4;
     return b;
 }
