@@ -127,13 +127,18 @@ def _dev(*ts):
             raise ValueError("tensors must be contiguous")
 
 
+# (ctypes turns plain integers into the pointers of the argtypes: no wrapper objects on the call path)
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> C.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    """The stream's handle; by default the current device's current stream. torch's own accessor of the
+    raw handle is used where it exists: building a Stream object costs as much as the rest of a call."""
+    if stream is not None:
+        return stream.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 class Index:
@@ -242,8 +247,8 @@ def ra_index_export(idx: Index, seq: int, q_head: int):
     return adj, int(entry[0])
 
 
-def _stats_tensor(n_heads, device):
-    return torch.zeros((n_heads, 4), dtype=torch.int32, device=device)
+def _stats_tensor(n_seq, n_q, device):
+    return torch.empty((n_seq, n_q, 4), dtype=torch.int32, device=device)     # every walk writes its row
 
 
 def ra_quantize_keys(K, stream=None):
@@ -264,7 +269,7 @@ def ra_search(q, idx: Index, K, sink: int, window: int, topk: int, ef: int, expa
     (ra_search_q8) and K may be None."""
     n_seq, n_q, d = q.shape
     ids = torch.empty((n_seq, n_q, topk), dtype=torch.int32, device=q.device)
-    st = _stats_tensor(n_seq * n_q, q.device) if with_stats else None
+    st = _stats_tensor(n_seq, n_q, q.device) if with_stats else None
     if k8 is None:
         _dev(q, K)
         _check(lib().ra_search(_ptr(q), idx.handle, _ptr(K), _dt(K), K.shape[2], sink, window, topk,
@@ -274,7 +279,7 @@ def ra_search(q, idx: Index, K, sink: int, window: int, topk: int, ef: int, expa
         _dev(q, K8, scale)
         _check(lib().ra_search_q8(_ptr(q), idx.handle, _ptr(K8), _ptr(scale), _dt(q), K8.shape[2], sink,
                                   window, topk, ef, expand, _stream(stream), _ptr(ids), _ptr(st)))
-    return ids, (st.view(n_seq, n_q, 4) if with_stats else None)
+    return ids, st
 
 
 def ra_rerank(q, K, cand, topk: int, stream=None):
@@ -331,7 +336,7 @@ def ra_decode_step(q, idx: Index, K, V, sink: int, window: int, topk: int, ef: i
     if ids is None:
         ids = torch.empty((n_seq, n_q, topk), dtype=torch.int32, device=q.device)
     if stats is None:
-        stats = _stats_tensor(n_seq * n_q, q.device).view(n_seq, n_q, 4)
+        stats = _stats_tensor(n_seq, n_q, q.device)
     if topk_per_head is not None:
         if topk_per_head.dtype != torch.int32 or tuple(topk_per_head.shape) != (n_seq, n_q) \
                 or not topk_per_head.is_contiguous():
