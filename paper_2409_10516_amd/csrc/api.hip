@@ -105,7 +105,11 @@ static ra_status grow(void** p, size_t* have, size_t need) {
 // records, ready words and the "helpers off" word of the fused decode kernel's hand-over area
 static size_t coop_bytes(const ra_index* ix) {
     const size_t heads = (size_t)ix->n_seq * ix->n_q;
-    return heads * RA_COOP_REC * sizeof(float) + (heads + 1) * sizeof(uint32_t);
+    return heads * RA_COOP_REC * sizeof(float) + (2 * heads + 1) * sizeof(uint32_t);
+}
+static uint32_t* attend_tickets(const ra_index* ix) {
+    const size_t heads = (size_t)ix->n_seq * ix->n_q;
+    return reinterpret_cast<uint32_t*>(ix->coop + heads * RA_COOP_REC) + heads + 1;
 }
 
 static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra_index** out) {
@@ -457,8 +461,8 @@ extern "C" ra_status ra_attend(const void* q, const ra_index* idx, const void* K
         ra_attend_partial_floats(ix->n_seq, ix->n_q, ix->n_kv, N, sink, window, topk) * sizeof(float);
     RA_TRY(grow((void**)&ix->partials, &ix->partials_bytes, need));
     return ra_launch_attend(q, K, V, dt, ix->n_seq, ix->n_q, ix->n_kv, N, sink, window, topk, ids,
-                            ix->partials, (hipStream_t)stream, out, lse, o_omega, lse_omega, o_w,
-                            lse_w);
+                            ix->partials, attend_tickets(ix), (hipStream_t)stream, out, lse, o_omega,
+                            lse_omega, o_w, lse_w);
 }
 
 extern "C" ra_status ra_attend_noalloc(const void* q, const ra_index* idx, const void* K, const void* V,
@@ -568,8 +572,8 @@ extern "C" ra_status ra_rerank(const void* q, const void* K, ra_dtype dt, int n_
 extern "C" size_t ra_flat_workspace_bytes(int n_seq, int n_q_heads, int64_t N) {
     if (n_seq < 1 || n_q_heads < 1 || N < 1) return 0;
     // one order-preserving key per (head, key), then 16 tile maxima per (head, chunk of 512 keys),
-    // then the candidate counters of the second pass
-    return (size_t)n_seq * n_q_heads * (N + 16 * ((N + 511) / 512) + RA_FLAT_SLICES) * sizeof(uint32_t);
+    // then the candidate counters and the ticket of the second pass
+    return (size_t)n_seq * n_q_heads * (N + 16 * ((N + 511) / 512) + RA_FLAT_SLICES + 1) * sizeof(uint32_t);
 }
 
 extern "C" ra_status ra_flat_topk(const void* q, const void* K, ra_dtype dt, int n_seq, int n_q,
@@ -610,15 +614,9 @@ extern "C" ra_status ra_hbm_gather_probe(const void* buf, size_t bytes, size_t n
 extern "C" size_t ra_full_attention_workspace_bytes(int n_seq, int n_q_heads, int n_kv_heads,
                                                      int64_t N) {
     if (n_seq < 1 || n_q_heads < 1 || n_kv_heads < 1 || N < 1) return 0;
-    // partial records of a fully static context, preceded by one padded id per head
-    return 256 + (size_t)n_seq * n_q_heads * sizeof(int32_t) +
-           ra_attend_partial_floats(n_seq, n_q_heads, n_kv_heads, N, (int)(N > 0x7fffffff ? 0x7fffffff : N),
+    // partial records of a fully static context
+    return 256 + ra_attend_partial_floats(n_seq, n_q_heads, n_kv_heads, N, (int)(N > 0x7fffffff ? 0x7fffffff : N),
                                     0, 1) * sizeof(float);
-}
-
-__global__ void api_fill_i32_kernel(int32_t* p, int n, int32_t v) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
 }
 
 extern "C" ra_status ra_full_attention(const void* q, const void* K, const void* V, ra_dtype dt,
@@ -634,12 +632,8 @@ extern "C" ra_status ra_full_attention(const void* q, const void* K, const void*
     if (workspace_bytes < ra_full_attention_workspace_bytes(n_seq, n_q, n_kv, N))
         RA_FAIL(RA_ESHAPE, "workspace of %zu B is smaller than ra_full_attention_workspace_bytes",
                 workspace_bytes);
-    const int heads = n_seq * n_q;
-    int32_t* ids = (int32_t*)workspace;                       // one id per head, all -1: Omega is empty
-    float* partials = (float*)((char*)workspace + ((heads * sizeof(int32_t) + 255) & ~(size_t)255));
-    hipLaunchKernelGGL(api_fill_i32_kernel, dim3((heads + 255) / 256), dim3(256), 0,
-                       (hipStream_t)stream, ids, heads, -1);
-    // the whole context as the "static" set of Eq. 2: W = [0, N), Omega empty
-    return ra_launch_attend(q, K, V, dt, n_seq, n_q, n_kv, N, (int)N, 0, 1, ids, partials,
+    // the whole context as the "static" set of Eq. 2: W = [0, N), Omega empty. (The records are combined by
+    // a launch of their own: the caller's workspace holds no tickets that are zero between calls.)
+    return ra_launch_attend(q, K, V, dt, n_seq, n_q, n_kv, N, (int)N, 0, 1, nullptr, (float*)workspace, nullptr,
                             (hipStream_t)stream, out, lse, nullptr, nullptr, nullptr, nullptr);
 }

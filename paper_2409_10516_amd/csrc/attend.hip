@@ -1,14 +1,49 @@
 // Stand-alone attention launches (ra_attend); the device code is in attend_dev.h.
 #include "attend_dev.h"
 
+// Folds the slices' (max, sum, weighted sum) of a head through LDS, in slice order, and closes it (called by
+// all threads; slice 0 writes).
+#define AT_MERGE_SLICES 8
+__device__ __forceinline__ void merge_slices(float* part, int slice, int n_slices, int t, float (&M)[2], float (&L)[2],
+                                             float (&A)[2], size_t head, float* out, float* lse, float* o_om,
+                                             float* lse_om, float* o_w, float* lse_w) {
+    if (n_slices > 1) {
+        auto at = [&](int sl, int set, int what) -> float& { return part[((sl * 2 + set) * 3 + what) * RA_D + t]; };
+#pragma unroll
+        for (int set = 0; set < 2; ++set) {
+            at(slice, set, 0) = M[set];
+            at(slice, set, 1) = L[set];
+            at(slice, set, 2) = A[set];
+        }
+        __syncthreads();
+        if (slice == 0)
+            for (int b = 1; b < n_slices; ++b)
+#pragma unroll
+                for (int set = 0; set < 2; ++set)
+                    merge_fold(M[set], L[set], A[set], at(b, set, 0), at(b, set, 1), at(b, set, 2));
+    }
+    if (slice == 0) merge_finish(M, L, A, t, head, out, lse, o_om, lse_om, o_w, lse_w);
+}
+
+// Where a partial launch's records are combined: by the launch itself (tickets: one word per query head,
+// zero between launches), or, with tickets null, by attend_merge_kernel afterwards.
+struct AttendOut {
+    uint32_t* tickets;
+    float *out, *lse, *o_om, *lse_om, *o_w, *lse_w;
+};
+
 // grid: x = record slot (nS static chunks, then G x nG gathered chunks), y = KV head, z = seq.
-// GQA groups of another size than the kernel is built for run as G = 1 with one grid row per query
-// head, kv_div of which share a KV head (kv_div = 1 otherwise).
-template <int DT, int G>
+// With kv_div > 1 the kernel runs as G = 1 with one grid row per query head, kv_div of which share a KV
+// head (GQA groups of another size than the kernel is built for, and small launches: see
+// ra_launch_attend).
+// TICKETS: whoever writes a head's last record combines them all: a workgroup stores its records past the
+// L2, waits for the stores, and takes a ticket of each of its heads; the one that gets the last ticket
+// reads the P records back the same way. That saves a launch (4 us of 13.5 us for the decode step's sets).
+template <int DT, int G, bool TICKETS>
 __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
     const void* __restrict__ q, const void* __restrict__ K, const void* __restrict__ V,
     const int32_t* __restrict__ ids, float* __restrict__ partials, int n_q, int n_kv, int64_t N,
-    int s, int w, int topk, int nS, int nG, int sub, float scale, int kv_div) {
+    int s, int w, int topk, int nS, int nG, int sub, float scale, int kv_div, AttendOut o) {
     extern __shared__ float smem[];
     const int kvh = blockIdx.y / kv_div, seq = blockIdx.z, x = blockIdx.x;
     const int P = nS + nG;
@@ -18,22 +53,54 @@ __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
     const int h0 = blockIdx.y * G;
     const char* qg = reinterpret_cast<const char*>(q) + ((size_t)seq * n_q + h0) * RA_D * esz;
     float* rec_g = partials + ((size_t)seq * n_q + h0) * P * AT_RS;
+    int first = 0, n_mine = G;                  // heads of the group this workgroup has a record of
     if (x < nS) {
         RowSrc src{nullptr, N, s, w, s + w, 0};
+        bool done = false;
         if constexpr (DT == RA_BF16 && G <= 4) {
             if (sub > 1) {                      // a long dense range (full attention): logits on the matrix cores
-                attend_chunk_mfma<G>(threadIdx.x, qg, Kh, Vh, src, x, sub, scale, rec_g + (size_t)x * AT_RS,
-                                     (int64_t)P * AT_RS, smem);
-                return;
+                attend_chunk_mfma<G, TICKETS>(threadIdx.x, qg, Kh, Vh, src, x, sub, scale, rec_g + (size_t)x * AT_RS,
+                                              (int64_t)P * AT_RS, smem);
+                done = true;
             }
         }
-        attend_chunk<DT, G>(threadIdx.x, true, qg, Kh, Vh, src, x, sub, scale, rec_g + (size_t)x * AT_RS,
-                            (int64_t)P * AT_RS, smem);
+        if (!done)
+            attend_chunk<DT, G, TICKETS>(threadIdx.x, true, qg, Kh, Vh, src, x, sub, scale, rec_g + (size_t)x * AT_RS,
+                                         (int64_t)P * AT_RS, smem);
     } else {
         const int t = x - nS, g = t / nG, c = t % nG;
         RowSrc src{ids + ((size_t)seq * n_q + h0 + g) * topk, N, 0, 0, topk, 0};
-        attend_chunk<DT, 1>(threadIdx.x, true, qg + (size_t)g * RA_D * esz, Kh, Vh, src, c, 1, scale,
-                            rec_g + ((size_t)g * P + nS + c) * AT_RS, 0, smem);
+        attend_chunk<DT, 1, TICKETS>(threadIdx.x, true, qg + (size_t)g * RA_D * esz, Kh, Vh, src, c, 1, scale,
+                                     rec_g + ((size_t)g * P + nS + c) * AT_RS, 0, smem);
+        first = g;
+        n_mine = 1;
+    }
+    if constexpr (TICKETS) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): this wavefront's record stores have completed
+        __syncthreads();                        // ... and every other's (and the LDS of the chunk is free)
+        uint32_t* last = reinterpret_cast<uint32_t*>(smem);
+        const size_t head0 = (size_t)seq * n_q + h0 + first;
+        if ((int)threadIdx.x < n_mine)
+            last[threadIdx.x] = __hip_atomic_fetch_add(o.tickets + head0 + threadIdx.x, 1u, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)P - 1u;
+        __syncthreads();
+        bool mine[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) mine[g] = g < n_mine && last[g] != 0u;
+        __syncthreads();                        // (read before the merge reuses the LDS)
+        constexpr int SL = AT_THREADS / RA_D;
+        const int t = threadIdx.x % RA_D, slice = threadIdx.x / RA_D;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (!mine[g]) continue;             // (uniform)
+            const size_t head = head0 + g;
+            float M[2] = {-INFINITY, -INFINITY}, L[2] = {0.f, 0.f}, A[2] = {0.f, 0.f};
+            merge_accumulate<true>(partials + head * P * AT_RS, nS, nG, t, slice, SL, M, L, A);
+            merge_slices(smem, slice, SL, t, M, L, A, head, o.out, o.lse, o.o_om, o.lse_om, o.o_w, o.lse_w);
+            if (threadIdx.x == 0)
+                __hip_atomic_store(o.tickets + head, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (g + 1 < G) __syncthreads();
+        }
     }
 }
 
@@ -41,106 +108,89 @@ __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
 // output dimension). A head with more than sixteen records (a long static range: full attention)
 // has its batches of sixteen dealt to up to AT_MERGE_SLICES slices that run side by side and are
 // folded through LDS, in slice order, by the first.
-#define AT_MERGE_SLICES 8
 __global__ __launch_bounds__(AT_MERGE_SLICES * RA_D) void attend_merge_kernel(
-    const float* __restrict__ partials, int n_q, int nS, int nG, float* __restrict__ out,
-    float* __restrict__ lse, float* __restrict__ o_om, float* __restrict__ lse_om,
-    float* __restrict__ o_w, float* __restrict__ lse_w) {
-    __shared__ float part[AT_MERGE_SLICES][2][3][RA_D];          // [slice][set][M, L, A][dimension]
+    const float* __restrict__ partials, int n_q, int nS, int nG, AttendOut o) {
+    __shared__ float part[AT_MERGE_SLICES * 2 * 3 * RA_D];       // [slice][set][M, L, A][dimension]
     const size_t head = (size_t)blockIdx.y * n_q + blockIdx.x;
     const int t = threadIdx.x % RA_D, slice = threadIdx.x / RA_D, n_slices = blockDim.x / RA_D;
     float M[2] = {-INFINITY, -INFINITY}, L[2] = {0.f, 0.f}, A[2] = {0.f, 0.f};
     merge_accumulate<false>(partials + head * (nS + nG) * AT_RS, nS, nG, t, slice, n_slices, M, L, A);
-    if (n_slices > 1) {
-#pragma unroll
-        for (int set = 0; set < 2; ++set) {
-            part[slice][set][0][t] = M[set];
-            part[slice][set][1][t] = L[set];
-            part[slice][set][2][t] = A[set];
-        }
-        __syncthreads();
-        if (slice != 0) return;
-        for (int b = 1; b < n_slices; ++b)
-#pragma unroll
-            for (int set = 0; set < 2; ++set)
-                merge_fold(M[set], L[set], A[set], part[b][set][0][t], part[b][set][1][t], part[b][set][2][t]);
-    }
-    merge_finish(M, L, A, t, head, out, lse, o_om, lse_om, o_w, lse_w);
+    merge_slices(part, slice, n_slices, t, M, L, A, head, o.out, o.lse, o.o_om, o.lse_om, o.o_w, o.lse_w);
 }
 
-// 64-row sub-chunks per static workgroup: 1 for the decode step's few hundred static rows, more
-// when the static range is long (full attention), so that a head has at most AT_MAX_STATIC_RECORDS
-// static records to combine. Measured for full attention over 131072 tokens, 8 KV heads (us per
-// layer): 32 records 178, 64 records 115, 128 records 123, 256 records 136 (the kernel's 178 vector
-// registers allow two workgroups per compute unit: 512 workgroups run side by side from start to end;
-// builds held to fewer registers spill and take 150 us and more).
-#ifndef AT_MAX_STATIC_RECORDS
-#define AT_MAX_STATIC_RECORDS 64
-#endif
-static int static_sub(int rows) {
-    int sub = 1;
-    while (sub < 64 && (rows + AT_CH * sub - 1) / (AT_CH * sub) > AT_MAX_STATIC_RECORDS) sub <<= 1;
-    return sub;
+// Static chunks: 64 rows each for the decode step's few hundred static rows; a long static range (full
+// attention) is cut so that its workgroups are about two per compute unit (the kernel's vector
+// registers allow two side by side), all running from start to end. Measured for full attention
+// over 131072 tokens, 8 KV heads (us per layer): 32 records per head 178, 64 records 115, 128 records 123,
+// 256 records 136; with the number of sub-chunks rounded up to a power of two a context of 100003
+// tokens had 392 workgroups on 512 places (88 us; 74 us with 504).
+#define AT_MAX_STATIC_CHUNKS 64     // most chunks of 64 rows that get a record each
+#define AT_LONG_WORKGROUPS 512
+static int static_sub(int rows, int kv_heads) {
+    const int chunks = (rows + AT_CH - 1) / AT_CH;
+    if (chunks <= AT_MAX_STATIC_CHUNKS) return 1;
+    int records = AT_LONG_WORKGROUPS / kv_heads;
+    if (records < 4) records = 4;
+    if (records > chunks / 2) records = chunks / 2;
+    return (chunks + records - 1) / records;
 }
 
 size_t ra_attend_partial_floats(int n_seq, int n_q, int n_kv, int64_t N, int sink, int window,
                                 int topk) {
     int s, w;
     static_ranges(N, sink, window, &s, &w);
-    const int sub = static_sub(s + w);
+    const int sub = static_sub(s + w, n_seq * n_kv);
     const int nS = (s + w + AT_CH * sub - 1) / (AT_CH * sub), nG = (topk + AT_CH - 1) / AT_CH;
     return (size_t)n_seq * n_q * (nS + nG) * AT_RS;
 }
 
-template <int DT>
-static ra_status launch_partial(int G, dim3 grid, size_t lds, hipStream_t st, const void* q,
-                                const void* K, const void* V, const int32_t* ids, float* partials,
-                                int n_q, int n_kv, int64_t N, int s, int w, int topk, int nS, int nG,
-                                int sub, float scale) {
-#define RA_AT_CASE(GG)                                                                          \
-    case GG:                                                                                    \
-        hipLaunchKernelGGL((attend_partial_kernel<DT, GG>), grid, dim3(AT_THREADS), lds, st, q, K, \
-                           V, ids, partials, n_q, n_kv, N, s, w, topk, nS, nG, sub, scale, 1);  \
-        break;
-    switch (G) {
-        RA_AT_CASE(1)
-        RA_AT_CASE(2)
-        RA_AT_CASE(4)
-        RA_AT_CASE(8)
-        default:                 // any other group size: every query head reads its rows itself
-            grid.x = nS + nG;
-            grid.y = n_q;
-            hipLaunchKernelGGL((attend_partial_kernel<DT, 1>), grid, dim3(AT_THREADS), lds, st, q, K, V,
-                               ids, partials, n_q, n_kv, N, s, w, topk, nS, nG, sub, scale, G);
-    }
-#undef RA_AT_CASE
-    return RA_OK;
-}
+// A launch of few workgroups is bound by its latency, and a static chunk for four heads takes four times
+// the arithmetic and closes four records one after the other: up to this many workgroups every query
+// head reads its static rows itself (the four of a group find them in the L2).
+#define AT_SPLIT_WORKGROUPS 1024
 
 ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype dt, int n_seq,
                            int n_q, int n_kv, int64_t N, int sink, int window, int topk,
-                           const int32_t* ids, float* partials, hipStream_t st, float* out,
+                           const int32_t* ids, float* partials, uint32_t* tickets, hipStream_t st, float* out,
                            float* lse, float* o_omega, float* lse_omega, float* o_w,
                            float* lse_w) {
     int s, w;
     static_ranges(N, sink, window, &s, &w);
     const int G = n_q / n_kv;
-    const int sub = static_sub(s + w);
-    const int nS = (s + w + AT_CH * sub - 1) / (AT_CH * sub), nG = (topk + AT_CH - 1) / AT_CH;
+    const int sub = static_sub(s + w, n_seq * n_kv);
+    const int nS = (s + w + AT_CH * sub - 1) / (AT_CH * sub), nG = ids ? (topk + AT_CH - 1) / AT_CH : 0;
     const float scale = 1.0f / sqrtf((float)RA_D);
-    dim3 grid(nS + G * nG, n_kv, n_seq);
     const size_t lds = (size_t)AT_TEAM_LDS_FLOATS * sizeof(float);
-    ra_status rc = dt == RA_BF16
-        ? launch_partial<RA_BF16>(G, grid, lds, st, q, K, V, ids, partials, n_q, n_kv, N, s, w,
-                                  topk, nS, nG, sub, scale)
-        : launch_partial<RA_F32>(G, grid, lds, st, q, K, V, ids, partials, n_q, n_kv, N, s, w,
-                                 topk, nS, nG, sub, scale);
-    if (rc != RA_OK) return rc;
-    RA_HIP(hipGetLastError());
+    const AttendOut o{tickets, out, lse, o_omega, lse_omega, o_w, lse_w};
+    const bool grouped = (G == 1 || G == 2 || G == 4 || G == 8) &&
+                         (G == 1 || sub > 1 || (int64_t)(nS + nG) * n_q * n_seq > AT_SPLIT_WORKGROUPS);
+    const dim3 grid = grouped ? dim3(nS + G * nG, n_kv, n_seq) : dim3(nS + nG, n_q, n_seq);
+    if (nS + nG > 0) {
+#define RA_AT_GO(DTV, GG, TK, DIV)                                                                                \
+    hipLaunchKernelGGL((attend_partial_kernel<DTV, GG, TK>), grid, dim3(AT_THREADS), lds, st, q, K, V, ids, partials, \
+                       n_q, n_kv, N, s, w, topk, nS, nG, sub, scale, DIV, o)
+#define RA_AT_TK(DTV, GG, DIV)                                                                                    \
+    do { if (tickets) RA_AT_GO(DTV, GG, true, DIV); else RA_AT_GO(DTV, GG, false, DIV); } while (0)
+#define RA_AT_DT(DTV)                                                                                             \
+    do {                                                                                                          \
+        if (!grouped) RA_AT_TK(DTV, 1, G);          /* every query head reads its rows itself */                  \
+        else if (G == 1) RA_AT_TK(DTV, 1, 1);                                                                     \
+        else if (G == 2) RA_AT_TK(DTV, 2, 1);                                                                     \
+        else if (G == 4) RA_AT_TK(DTV, 4, 1);                                                                     \
+        else RA_AT_TK(DTV, 8, 1);                                                                                 \
+    } while (0)
+        if (dt == RA_BF16) RA_AT_DT(RA_BF16); else RA_AT_DT(RA_F32);
+#undef RA_AT_DT
+#undef RA_AT_TK
+#undef RA_AT_GO
+        RA_HIP(hipGetLastError());
+    }
+    if (tickets && nS + nG > 0) return RA_OK;
     int slices = (nS + nG + 15) / 16;                     // one per batch of sixteen records, at most 8
     if (slices > AT_MERGE_SLICES) slices = AT_MERGE_SLICES;
+    if (slices < 1) slices = 1;
     hipLaunchKernelGGL(attend_merge_kernel, dim3(n_q, n_seq), dim3(slices * RA_D), 0, st, partials, n_q, nS,
-                       nG, out, lse, o_omega, lse_omega, o_w, lse_w);
+                       nG, o);
     RA_HIP(hipGetLastError());
     return RA_OK;
 }
@@ -152,9 +202,12 @@ ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype
 // host code never passes the array's name to a kernel, only the address hipGetSymbolAddress gives
 // for the current device (looked up once per device and kept).
 static __device__ __align__(256) unsigned char scratch[RA_ATTEND_NOALLOC_SCRATCH_BYTES];
+// one ticket per head that fits (a head has a record at least); zero between calls
+static __device__ uint32_t scratch_tickets[RA_ATTEND_NOALLOC_SCRATCH_BYTES / (AT_RS * 4)];
 static void* g_scratch_addr[RA_MAX_DEVICES];
+static uint32_t* g_ticket_addr[RA_MAX_DEVICES];
 
-static ra_status scratch_address(void** out) {
+static ra_status scratch_address(void** out, uint32_t** tickets) {
     int dev = 0;
     RA_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= RA_MAX_DEVICES) RA_FAIL(RA_EUNSUP, "device %d out of range", dev);
@@ -162,9 +215,13 @@ static ra_status scratch_address(void** out) {
         void* p = nullptr;
         RA_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
         if (!p) RA_FAIL(RA_EHIP, "the scratch array has no address on device %d", dev);
+        void* t = nullptr;
+        RA_HIP(hipGetSymbolAddress(&t, HIP_SYMBOL(scratch_tickets)));
+        g_ticket_addr[dev] = reinterpret_cast<uint32_t*>(t);
         g_scratch_addr[dev] = p;
     }
     *out = g_scratch_addr[dev];
+    *tickets = g_ticket_addr[dev];
     return RA_OK;
 }
 
@@ -177,9 +234,11 @@ ra_status ra_launch_attend_noalloc(const void* q, const void* K, const void* V, 
         RA_FAIL(RA_EUNSUP, "the partial records of this call take %zu bytes, above the %u bytes "
                 "ra_attend_noalloc keeps (use ra_attend)", need, (unsigned)RA_ATTEND_NOALLOC_SCRATCH_BYTES);
     void* ptr = nullptr;
-    ra_status rc = scratch_address(&ptr);
+    uint32_t* tickets = nullptr;
+    ra_status rc = scratch_address(&ptr, &tickets);
     if (rc != RA_OK) return rc;
-    // nothing to clear: every record the merge reads is written by this call's first kernel
+    // nothing to clear: every record the merge reads is written by this call, which also leaves the
+    // tickets at zero
     return ra_launch_attend(q, K, V, dt, n_seq, n_q, n_kv, N, sink, window, topk, ids,
-                            reinterpret_cast<float*>(ptr), st, out, lse, o_omega, lse_omega, o_w, lse_w);
+                            reinterpret_cast<float*>(ptr), tickets, st, out, lse, o_omega, lse_omega, o_w, lse_w);
 }

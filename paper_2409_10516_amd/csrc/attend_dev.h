@@ -115,7 +115,14 @@ __device__ __forceinline__ float at_exp(float x) { return DT == RA_BF16 ? __expf
 
 // The closing step of a chunk: the (max, sum, weighted sum) states of the 16 lane groups of a team,
 // each lane holding 8 of the 128 outputs of its group, become one partial record per head.
-template <int NH>
+// COHERENT: the record is read by another workgroup of the same launch (relaxed agent-scope stores, which go
+// around the cache levels that are not coherent across the part's XCDs).
+template <bool COHERENT>
+__device__ __forceinline__ void rec_store(float* p, float v) {
+    if (COHERENT) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+template <int NH, bool COHERENT>
 __device__ __forceinline__ void chunk_records(int tid, bool active, const float (&m)[NH], const float (&l)[NH],
                                               const float (&acc)[NH][8], float* rec0, int64_t rec_stride,
                                               float* smem) {
@@ -147,10 +154,10 @@ __device__ __forceinline__ void chunk_records(int tid, bool active, const float 
                 }
             }
             float* rec = rec0 + g * rec_stride;
-            rec[tid] = a;
+            rec_store<COHERENT>(rec + tid, a);
             if (tid == 0) {
-                rec[RA_D] = mx;
-                rec[RA_D + 1] = ll;
+                rec_store<COHERENT>(rec + RA_D, mx);
+                rec_store<COHERENT>(rec + RA_D + 1, ll);
             }
         }
     }
@@ -163,7 +170,7 @@ __device__ __forceinline__ void chunk_records(int tid, bool active, const float 
 // several teams, each with its own `smem`; every team must call this the same number of
 // times because it contains workgroup barriers). An inactive team computes on an empty row
 // source and writes nothing.
-template <int DT, int NH>
+template <int DT, int NH, bool COHERENT>
 __device__ void attend_chunk(int tid, bool active, const void* q0, const void* Kh, const void* Vh,
                              const RowSrc& src, int chunk, int n_sub, float scale, float* rec0,
                              int64_t rec_stride, float* smem) {
@@ -280,7 +287,7 @@ __device__ void attend_chunk(int tid, bool active, const void* q0, const void* K
             consume(rid_b, k_b, v_b);
         }
     }
-    chunk_records<NH>(tid, active, m, l, acc, rec0, rec_stride, smem);
+    chunk_records<NH, COHERENT>(tid, active, m, l, acc, rec0, rec_stride, smem);
 }
 
 // The same chunk for a long dense range of bf16 rows and up to four heads, with the logits on the
@@ -300,7 +307,7 @@ __device__ __forceinline__ float first_lane_f32(float v) {        // the builtin
 }
 typedef __bf16 at_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float at_f32x4 __attribute__((ext_vector_type(4)));
-template <int NH>
+template <int NH, bool COHERENT>
 __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const void* Vh, const RowSrc& src,
                                   int chunk, int n_sub, float scale, float* rec0, int64_t rec_stride,
                                   float* smem) {
@@ -408,7 +415,7 @@ __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const
         const float tot = first_lane_f32(v);
         l[h] = c == 0 ? tot : 0.f;
     }
-    chunk_records<NH>(tid, true, m, l, acc, rec0, rec_stride, smem);
+    chunk_records<NH, COHERENT>(tid, true, m, l, acc, rec0, rec_stride, smem);
 }
 
 // Combination of one head's P = nS + nG partial records: Eq. 4-5 with the re-scaling factors

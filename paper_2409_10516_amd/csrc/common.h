@@ -63,7 +63,8 @@ struct ra_index {
     size_t bitset_bytes;
     // hand-over area of the fused decode kernel: per head a record (RA_COOP_REC floats: max, sum,
     // 2 unused, 128 weighted sums) that a helper workgroup fills with the attention over the
-    // static set, then per head a ready word, then one "helpers off" word
+    // static set, then per head a ready word, then one "helpers off" word, then per head a ticket of
+    // ra_attend's combination (see attend.hip)
     float* coop;
     int coop_mode;      // RA_HELPERS_*
     int coop_spin;      // polls of the ready word before a head gives up on its helper
@@ -112,9 +113,9 @@ size_t ra_attend_partial_floats(int n_seq, int n_q, int n_kv, int64_t N, int sin
                                 int topk);
 ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype dt, int n_seq,
                            int n_q, int n_kv, int64_t N, int sink, int window, int topk,
-                           const int32_t* ids, float* partials, hipStream_t st, float* out,
-                           float* lse, float* o_omega, float* lse_omega, float* o_w,
-                           float* lse_w);
+                           const int32_t* ids, float* partials, uint32_t* tickets, hipStream_t st,
+                           float* out, float* lse, float* o_omega, float* lse_omega, float* o_w,
+                           float* lse_w);       // ids null: Omega is empty; tickets: see attend.hip
 
 ra_status ra_launch_attend_noalloc(const void* q, const void* K, const void* V, ra_dtype dt, int n_seq,
                                    int n_q, int n_kv, int64_t N, int sink, int window, int topk,

@@ -6,20 +6,19 @@
 // Flat top-k, two kernels:
 //   1. flat_scores_kernel: streams K once per KV head and scores every key against the query
 //      heads of its GQA group (16 lanes per key row, the same fixed-order float32 inner product
-//      as the graph search, so both rank keys identically); writes one order-preserving uint32
-//      per (head, key), 0 for keys of the static set W, which retrieval must not return, and
-//      the largest of them per tile: the FL_TILE keys that one 16-lane group scores in a chunk
-//      of FL_CHUNK (FL_ROWS consecutive keys out of every 16 x FL_ROWS), so a tile maximum
-//      stays in registers until it is written.
-//   2. flat_select_kernel: one workgroup per head. The topk-th largest tile maximum is a
-//      threshold that at least topk keys reach, so every key of the answer (and every tie of
-//      its last one) lies at or above it, in a tile whose maximum does: only those tiles (about
-//      topk of them) are read again, their keys at or above the threshold are collected and
-//      sorted by (score descending, id ascending) with a bitonic network in LDS. With too few
-//      tiles for that, a threshold placed from a strided sample and one pass over all keys do
-//      the same; when neither can place a safe threshold, an exact radix select over all keys
-//      (four 8-bit histogram passes) finds the k-th largest key, and the keys above it plus the
-//      lowest ids among its ties are taken.
+//      as the graph search, so both rank keys identically); writes the largest order-preserving
+//      uint32 (0 for keys of the static set W, which retrieval must not return) per tile: the FL_TILE
+//      keys that one 16-lane group scores in a chunk of FL_CHUNK (FL_ROWS consecutive keys out of every
+//      16 x FL_ROWS), so a tile maximum stays in registers until it is written.
+//   2. flat_rescore_kernel: a threshold that at least topk tile maxima reach; the tiles at or above it
+//      are scored again, and the last of a head's workgroups to finish orders the candidates (a launch
+//      of its own for that was 5 us and its gap; 70.4 -> 66.3 us with the attention that follows).
+// Inputs with too few or too many tiles for that store every key in the first kernel and
+// flat_select_kernel picks the answer from them: from the tiles at or above the topk-th largest tile
+// maximum, else from a threshold placed from a strided sample and one pass over all keys; when
+// neither can place a safe threshold, an exact radix select over all keys (four 8-bit histogram
+// passes) finds the k-th largest key, and the keys above it plus the lowest ids among its ties are
+// taken.
 #include "search_dev.h"
 
 #define FL_THREADS 256
@@ -36,9 +35,11 @@
 template <int DT, int G, bool STORE>
 __global__ __launch_bounds__(FL_THREADS) void flat_scores_kernel(
     const void* __restrict__ q, const void* __restrict__ K, int n_q, int n_kv, int64_t N, int s, int w,
-    uint32_t* __restrict__ keys, uint32_t* __restrict__ tile_max, int64_t n_tiles, int kv_div) {
+    uint32_t* __restrict__ keys, uint32_t* __restrict__ tile_max, int64_t n_tiles, int kv_div,
+    uint32_t* __restrict__ tickets) {
     const int tid = threadIdx.x, grp = tid >> 4, lane16 = tid & 15;
     const int kvh = blockIdx.y / kv_div, seq = blockIdx.z, h0 = seq * n_q + blockIdx.y * G;
+    if (blockIdx.x == 0 && tid < G) tickets[h0 + tid] = 0u;      // the second pass takes them
     const size_t esz = DT == RA_BF16 ? 2 : 4;
     const char* Kh = reinterpret_cast<const char*>(K) + ((size_t)seq * n_kv + kvh) * N * RA_D * esz;
     ScoreQuery<DT> qv[G];
@@ -169,147 +170,6 @@ __device__ __forceinline__ void radix_select(const uint32_t* __restrict__ kh, in
 #define FL_SLICES RA_FLAT_SLICES    // workgroups per head that score the listed tiles again
 #define FL_SLICE_CAND 1024         // candidates one of them can hold
 
-// Second pass of the scan that stores no keys. Every workgroup of a head finds T0, a tile maximum
-// that at least topk tile maxima reach (so at least topk keys reach it, and the answer and all ties
-// of its last key lie in tiles whose maximum does), lists those tiles, and scores its share of them
-// again - the same rows through the same instructions as the first pass, hence the same bits -
-// appending every key at or above T0 to its own list: pairs (key, id) in the slice's eighth of the
-// head's key area, their number in cand_count[head][slice]. A head with T0 = 0 (fewer than topk
-// tiles hold an eligible key) or a slice with more candidates than it can hold (a crowd of ties)
-// sets the top bit of the count instead: the select kernel then scores the whole head itself.
-// grid: x = slice, y = head; a wavefront takes one tile at a time (a 16-lane group one run of 8 rows).
-// BIG: more tiles than fit LDS (over 256K keys): the maxima are read where they are, in device memory
-// (a few passes over at most 128 KB that the cache holds), and only the list of tiles is in LDS.
-template <int DT, bool BIG>
-__global__ __launch_bounds__(FL_SEL_T) void flat_rescore_kernel(
-    const void* __restrict__ q, const void* __restrict__ K, int n_q, int n_kv, int64_t N, int s, int w,
-    const uint32_t* __restrict__ tile_max, int64_t n_tiles, int topk, uint32_t* __restrict__ keys,
-    uint32_t* __restrict__ cand_count, int cand_cap) {
-    __shared__ unsigned hist[256];
-    __shared__ unsigned s_ntl, s_prefix, s_cnt, s_lo, s_hi, s_t0;
-    __shared__ uint32_t tm_lds[BIG ? 1 : FL_TILES_MAX];
-    __shared__ unsigned short s_tl[FL_TILES_MAX];
-    __shared__ unsigned long long mine[FL_SLICE_CAND];        // this workgroup's candidates: (key, id)
-    const int tid = threadIdx.x, lane = tid & (RA_WAVE - 1), wv = tid / RA_WAVE, g4 = lane >> 4, lane16 = tid & 15;
-    const int head = blockIdx.y, slice = blockIdx.x;
-    const int seq = head / n_q, kvh = (head % n_q) / (n_q / n_kv);
-    const size_t esz = DT == RA_BF16 ? 2 : 4;
-    const char* Kh = reinterpret_cast<const char*>(K) + ((size_t)seq * n_kv + kvh) * N * RA_D * esz;
-    ScoreQuery<DT> qv;
-    load_score_query<DT, DT>(reinterpret_cast<const char*>(q) + (size_t)head * RA_D * esz, lane16, qv);
-    const uint32_t* tm_mem = tile_max + (size_t)head * n_tiles;
-    if constexpr (!BIG)
-        for (int64_t t = tid; t < n_tiles; t += FL_SEL_T) tm_lds[t] = tm_mem[t];
-    auto tm = [&](int64_t t) -> uint32_t { if constexpr (BIG) return tm_mem[t]; else return tm_lds[t]; };
-    if (tid == 0) { s_ntl = 0u; s_cnt = 0u; s_lo = 0xffffffffu; s_hi = 0u; s_t0 = 0xffffffffu; }
-    if (tid < 256) hist[tid] = 0u;
-    __syncthreads();
-    // A threshold that at least topk tile maxima reach, without an exact selection: the maxima are
-    // cut into 255 equal-width bins between the smallest and the largest (bin 0 is for tiles with no
-    // eligible key, whose maximum is 0), b is the highest bin such that the bins from b up hold at
-    // least topk maxima, and T0 is the smallest maximum in those bins. It is at or below the
-    // topk-th largest maximum, so nothing of the answer is lost, and a tile whose maximum reaches
-    // T0 lies in those bins (the binning is monotone), so "maximum >= T0" lists exactly them.
-    {
-        uint32_t lo = 0xffffffffu, hi = 0u;
-        for (int64_t t = tid; t < n_tiles; t += FL_SEL_T) {
-            const uint32_t v = tm(t);
-            if (v) { lo = v < lo ? v : lo; hi = v > hi ? v : hi; }
-        }
-#pragma unroll
-        for (int d = 1; d < RA_WAVE; d <<= 1) {
-            const uint32_t ol = __shfl_xor(lo, d), oh = __shfl_xor(hi, d);
-            lo = ol < lo ? ol : lo;
-            hi = oh > hi ? oh : hi;
-        }
-        if (lane == 0) { atomicMin(&s_lo, lo); atomicMax(&s_hi, hi); }
-    }
-    __syncthreads();
-    const float lo_f = f32_from_ordered(s_lo);
-    const float width = s_hi ? f32_from_ordered(s_hi) - lo_f : 0.f;
-    const float to_bin = width > 0.f && width < INFINITY ? 254.0f / width : 0.f;
-    auto bin_of = [&](uint32_t v) {
-        if (!v) return 0;
-        const float b = (f32_from_ordered(v) - lo_f) * to_bin;
-        return 1 + (b >= 254.f ? 254 : b > 0.f ? (int)b : 0);
-    };
-    for (int64_t t = tid; t < n_tiles; t += FL_SEL_T) atomicAdd(&hist[bin_of(tm(t))], 1u);
-    __syncthreads();
-    if (wv == 0) {
-        // lane l owns bins 4l .. 4l + 3; maxima in the bins from b up = total - (those below b)
-        const int b0 = (int)hist[4 * lane], b1 = (int)hist[4 * lane + 1], b2 = (int)hist[4 * lane + 2],
-                  b3 = (int)hist[4 * lane + 3];
-        const int incl = wave_incl_scan(b0 + b1 + b2 + b3);
-        const int total = __builtin_amdgcn_readlane(incl, RA_WAVE - 1);
-        const int from3 = total - incl + b3, from2 = from3 + b2, from1 = from2 + b1, from0 = from1 + b0;
-        const int best = from3 >= topk ? 3 : from2 >= topk ? 2 : from1 >= topk ? 1 : from0 >= topk ? 0 : -1;
-        const unsigned long long has = __ballot(best >= 0);     // never empty: n_tiles >= 2 topk
-        if (lane == 63 - __clzll(has)) s_prefix = (unsigned)(4 * lane + best);
-    }
-    __syncthreads();
-    const int bstar = (int)s_prefix;
-    if (bstar > 0) {
-        uint32_t m = 0xffffffffu;
-        for (int64_t t = tid; t < n_tiles; t += FL_SEL_T) {
-            const uint32_t v = tm(t);
-            if (bin_of(v) >= bstar) m = v < m ? v : m;
-        }
-#pragma unroll
-        for (int d = 1; d < RA_WAVE; d <<= 1) {
-            const uint32_t o = __shfl_xor(m, d);
-            m = o < m ? o : m;
-        }
-        if (lane == 0) atomicMin(&s_t0, m);
-    }
-    __syncthreads();
-    const uint32_t T0 = bstar > 0 ? s_t0 : 0u;
-    if (T0 == 0u) {
-        if (tid == 0) cand_count[head * FL_SLICES + slice] = 0x80000000u;
-        return;
-    }
-    // this workgroup's share: the listed tiles whose number is congruent to its slice (the order of
-    // a list differs from workgroup to workgroup, the tile numbers do not)
-    for (int64_t t = tid; t < n_tiles; t += FL_SEL_T)
-        if ((int)(t % FL_SLICES) == slice && tm(t) >= T0) {
-            const unsigned at = atomicAdd(&s_ntl, 1u);
-            if (at < FL_TILES_MAX) s_tl[at] = (unsigned short)t;
-        }
-    __syncthreads();
-    if (s_ntl > FL_TILES_MAX) {              // (only with more tiles than the list holds: a crowd of ties)
-        if (tid == 0) cand_count[head * FL_SLICES + slice] = 0x80000000u;
-        return;
-    }
-    const int ntl = (int)s_ntl;
-    for (int l = wv; l < ntl; l += FL_SEL_T / RA_WAVE) {
-        const int64_t tl = s_tl[l];
-        const int64_t id0 = (tl / 16) * FL_CHUNK + g4 * (16 * FL_ROWS) + (tl % 16) * FL_ROWS;
-        RowBits<DT> rows[FL_ROWS];
-#pragma unroll
-        for (int u = 0; u < FL_ROWS; ++u) rows[u] = load_key<DT>(Kh, id0 + u < N ? id0 + u : N - 1, lane16);
-        float part[FL_ROWS];
-#pragma unroll
-        for (int u = 0; u < FL_ROWS; ++u) part[u] = score_share<DT>(rows[u], qv);
-        const float sc = rows_tree<FL_ROWS>(part, lane16);
-        const int64_t id = id0 + (lane16 & (FL_ROWS - 1));
-        const bool counts = id < N && id >= s && id < N - w;
-        const uint32_t key = counts ? f32_ordered(sc) : 0u;
-        if (lane16 < FL_ROWS && key >= T0) {
-            const unsigned at = atomicAdd(&s_cnt, 1u);
-            if (at < FL_SLICE_CAND) mine[at] = ((unsigned long long)key << 32) | (uint32_t)id;
-        }
-    }
-    __syncthreads();
-    const unsigned cnt = s_cnt;
-    const bool fits = cnt <= (unsigned)cand_cap;
-    if (tid == 0) cand_count[head * FL_SLICES + slice] = fits ? cnt : 0x80000000u;
-    if (!fits) return;
-    uint32_t* region = keys + (size_t)head * N + (size_t)slice * (N / FL_SLICES);
-    for (unsigned i = tid; i < cnt; i += FL_SEL_T) {
-        region[2 * (size_t)i] = (uint32_t)(mine[i] >> 32);
-        region[2 * (size_t)i + 1] = (uint32_t)mine[i];
-    }
-}
-
 // Every key of one head scored by one workgroup into kh[0..N) (0 for the static set W): what the
 // select kernel falls back on when the second pass could not place a threshold.
 template <int DT>
@@ -337,67 +197,38 @@ __device__ __forceinline__ void flat_score_head(const void* q, const void* K, in
 
 #define FL_SAMPLE 4096             // keys sampled to place the threshold
 
-// grid: x = head; block = FL_SEL_T threads. ids_out [heads][topk], padded with -1.
+// LDS of a workgroup that selects a head's answer
+struct FlatLds {
+    unsigned hist[256], wsum4[4];
+    unsigned s_ntl, s_prefix, s_need, s_cnt, s_eq_total, s_run;
+    int wtot[FL_SEL_T / RA_WAVE];
+    unsigned short s_tl[FL_TILES_MAX];
+    unsigned long long sel[FL_CAND];
+};
+
+// The answer of one head from the keys kh[0..N) (FL_SEL_T threads; out [topk], padded with -1), or, with
+// n >= 0, from the n candidates already in lds.sel, which are known to hold it.
 // Fast path: a threshold is placed from a strided sample so that about four times topk keys
 // lie above it (the rank-r key of a 1-in-`stride` sample sits near rank r * stride of the
 // whole); one pass collects every key at or above it; if at least topk and at most FL_CAND were
 // collected, sorting them gives the exact answer (all ties of the k-th key are in the set).
 // Otherwise (tiny or adversarial inputs) the exact radix select over all keys decides.
-// two_pass: the keys were not stored; the candidates come from flat_rescore_kernel (q, K, n_q, n_kv,
-// s, w are for the head that has to score itself after all, see there).
-template <int DT>
-__global__ __launch_bounds__(FL_SEL_T) void flat_select_kernel(uint32_t* __restrict__ keys,
-                                                               const uint32_t* __restrict__ tile_max,
-                                                               int64_t n_tiles, int64_t N, int topk,
-                                                               int32_t* __restrict__ ids_out, bool two_pass,
-                                                               const uint32_t* __restrict__ cand_count,
-                                                               const void* __restrict__ q,
-                                                               const void* __restrict__ K, int n_q, int n_kv,
-                                                               int s, int w) {
-    __shared__ unsigned hist[256], wsum4[4];
-    __shared__ unsigned s_ntl;
-    __shared__ unsigned short s_tl[FL_TILES_MAX];
-    __shared__ unsigned s_prefix, s_need, s_cnt, s_eq_total, s_run;
-    __shared__ unsigned long long sel[FL_CAND];
-    __shared__ int wtot[FL_SEL_T / RA_WAVE];
+// tile_max null: no tile maxima to start from.
+__device__ __forceinline__ void flat_select(FlatLds& lds, uint32_t* kh, const uint32_t* tile_max, int64_t n_tiles,
+                                            int64_t N, int topk, int32_t* out, int n) {
+    unsigned* const hist = lds.hist;
+    unsigned* const wsum4 = lds.wsum4;
+    unsigned &s_ntl = lds.s_ntl, &s_prefix = lds.s_prefix, &s_need = lds.s_need, &s_cnt = lds.s_cnt,
+             &s_eq_total = lds.s_eq_total, &s_run = lds.s_run;
+    int* const wtot = lds.wtot;
+    unsigned short* const s_tl = lds.s_tl;
+    unsigned long long* const sel = lds.sel;
     const int tid = threadIdx.x, lane = tid & (RA_WAVE - 1), wv = tid / RA_WAVE;
-    uint32_t* kh = keys + (size_t)blockIdx.x * N;
-    int32_t* out = ids_out + (size_t)blockIdx.x * topk;
-    int n = -1;                                  // number of selected entries once known
-    if (two_pass) {
-        unsigned c = 0u, bad = 0u, start[FL_SLICES + 1];
-#pragma unroll
-        for (int j = 0; j < FL_SLICES; ++j) {
-            const unsigned cj = cand_count[blockIdx.x * FL_SLICES + j];
-            bad |= cj & 0x80000000u;
-            start[j] = c;
-            c += cj & 0x7fffffffu;
-        }
-        start[FL_SLICES] = c;
-        if (!bad && c >= (unsigned)topk && c <= FL_CAND) {
-            // entry i of the eight lists laid end to end (all loads in one trip)
-            for (unsigned i = tid; i < c; i += FL_SEL_T) {
-                int j = 0;
-#pragma unroll
-                for (int x = 1; x < FL_SLICES; ++x) j += i >= start[x] ? 1 : 0;
-                unsigned first = 0u;
-#pragma unroll
-                for (int x = 1; x < FL_SLICES; ++x) first = j == x ? start[x] : first;
-                const uint32_t* e = kh + (size_t)j * (N / FL_SLICES) + 2 * (size_t)(i - first);
-                sel[i] = ((unsigned long long)e[0] << 32) | (0xffffffffu - e[1]);
-            }
-            n = (int)c;
-        } else {
-            __syncthreads();                     // (every thread has read the counts)
-            flat_score_head<DT>(q, K, (int)blockIdx.x, n_q, n_kv, N, s, w, kh);
-        }
-        __syncthreads();
-    }
-    if (!two_pass && n_tiles >= 2 * (int64_t)topk && n_tiles <= FL_TILES_MAX) {
+    if (n < 0 && tile_max && n_tiles >= 2 * (int64_t)topk && n_tiles <= FL_TILES_MAX) {
         // ---- tile path: T0 = the topk-th largest tile maximum (exact), then only the tiles at or above it
         // the head's tile maxima, copied into LDS (the candidate array is not in use yet)
         uint32_t* tm = reinterpret_cast<uint32_t*>(sel);
-        for (int64_t t = tid; t < n_tiles; t += FL_SEL_T) tm[t] = tile_max[(size_t)blockIdx.x * n_tiles + t];
+        for (int64_t t = tid; t < n_tiles; t += FL_SEL_T) tm[t] = tile_max[t];
         __syncthreads();
         radix_select(tm, n_tiles, 1, (unsigned)topk, hist, wsum4, &s_prefix, &s_need, &s_eq_total);
         const uint32_t T0 = s_prefix;
@@ -509,11 +340,17 @@ __global__ __launch_bounds__(FL_SEL_T) void flat_select_kernel(uint32_t* __restr
     }
     // ---- order by (score descending, id ascending) = 64-bit key descending
     if (n <= FL_SEL_T) {
-        // few candidates (the usual case): a thread's candidate goes where the count of larger keys says
-        const unsigned long long mine = tid < n ? sel[tid] : 0ull;
-        int rank = 0;
-        for (int x = 0; x < n; ++x) rank += sel[x] > mine ? 1 : 0;
-        if (tid < n && rank < topk) out[rank] = (int32_t)(0xffffffffu - (uint32_t)mine);
+        // few candidates (the usual case): a candidate goes where the count of larger keys says; four
+        // threads count for each
+        const int part = tid & 3;
+        for (int c = tid >> 2; c < n; c += FL_SEL_T / 4) {
+            const unsigned long long mine = sel[c];
+            int rank = 0;
+            for (int x = part; x < n; x += 4) rank += sel[x] > mine ? 1 : 0;
+            rank += __shfl_xor(rank, 1);
+            rank += __shfl_xor(rank, 2);
+            if (part == 0 && rank < topk) out[rank] = (int32_t)(0xffffffffu - (uint32_t)mine);
+        }
         for (int i = n + tid; i < topk; i += FL_SEL_T) out[i] = -1;
         return;
     }
@@ -538,11 +375,218 @@ __global__ __launch_bounds__(FL_SEL_T) void flat_select_kernel(uint32_t* __restr
         out[i] = i < n ? (int32_t)(0xffffffffu - (uint32_t)sel[i]) : -1;
 }
 
+// Selection of a scan that stored its keys. grid: x = head; block = FL_SEL_T threads.
+__global__ __launch_bounds__(FL_SEL_T) void flat_select_kernel(uint32_t* __restrict__ keys,
+                                                               const uint32_t* __restrict__ tile_max,
+                                                               int64_t n_tiles, int64_t N, int topk,
+                                                               int32_t* __restrict__ ids_out) {
+    __shared__ FlatLds lds;
+    flat_select(lds, keys + (size_t)blockIdx.x * N, tile_max + (size_t)blockIdx.x * n_tiles, n_tiles, N, topk,
+                ids_out + (size_t)blockIdx.x * topk, -1);
+}
+
+// Second pass of the scan that stores no keys. Every workgroup of a head finds T0, a tile maximum
+// that at least topk tile maxima reach (so at least topk keys reach it, and the answer and all ties
+// of its last key lie in tiles whose maximum does), lists those tiles, and scores its share of them
+// again - the same rows through the same instructions as the first pass, hence the same bits -
+// appending every key at or above T0 to its own list: pairs (key, id) in the slice's eighth of the
+// head's key area, their number in cand_count[head][slice]. A head with T0 = 0 (fewer than topk
+// tiles hold an eligible key) or a slice with more candidates than it can hold (a crowd of ties)
+// sets the top bit of the count instead. The workgroup of a head that is done last (a ticket) picks the
+// head's answer out of the eight lists, or scores the whole head itself if one of them is not there: what
+// crosses workgroups is stored and read past the L2.
+// grid: x = slice, y = head; a wavefront takes one tile at a time (a 16-lane group one run of 8 rows).
+// BIG: more tiles than fit LDS (over 256K keys): the maxima are read where they are, in device memory
+// (a few passes over at most 128 KB that the cache holds), and only the list of tiles is in LDS.
+template <int DT, bool BIG>
+__global__ __launch_bounds__(FL_SEL_T) void flat_rescore_kernel(
+    const void* __restrict__ q, const void* __restrict__ K, int n_q, int n_kv, int64_t N, int s, int w,
+    const uint32_t* __restrict__ tile_max, int64_t n_tiles, int topk, uint32_t* keys,
+    uint32_t* cand_count, int cand_cap, uint32_t* tickets, int32_t* __restrict__ ids_out) {
+    __shared__ FlatLds lds;
+    __shared__ unsigned s_lo, s_hi, s_t0, s_last;
+    unsigned* const hist = lds.hist;
+    unsigned &s_ntl = lds.s_ntl, &s_prefix = lds.s_prefix, &s_cnt = lds.s_cnt;
+    unsigned short* const s_tl = lds.s_tl;
+    unsigned long long* const mine = lds.sel;                 // this workgroup's candidates: (key, id)
+    const int tid = threadIdx.x, lane = tid & (RA_WAVE - 1), wv = tid / RA_WAVE, g4 = lane >> 4, lane16 = tid & 15;
+    const int head = blockIdx.y, slice = blockIdx.x;
+    const int seq = head / n_q, kvh = (head % n_q) / (n_q / n_kv);
+    const size_t esz = DT == RA_BF16 ? 2 : 4;
+    const char* Kh = reinterpret_cast<const char*>(K) + ((size_t)seq * n_kv + kvh) * N * RA_D * esz;
+    ScoreQuery<DT> qv;
+    load_score_query<DT, DT>(reinterpret_cast<const char*>(q) + (size_t)head * RA_D * esz, lane16, qv);
+    const uint32_t* tm_mem = tile_max + (size_t)head * n_tiles;
+    // the maxima of a thread's tiles tid, tid + FL_SEL_T, ... : in registers unless there are too many
+    constexpr int PER = FL_TILES_MAX / FL_SEL_T;
+    uint32_t tv[BIG ? 1 : PER];
+    if constexpr (!BIG) {
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+            const int64_t t = tid + r * FL_SEL_T;
+            tv[r] = t < n_tiles ? tm_mem[t] : 0u;
+        }
+    }
+    auto for_tiles = [&](auto f) __attribute__((always_inline)) {      // f(tile, maximum)
+        if constexpr (BIG) {
+            for (int64_t t = tid; t < n_tiles; t += FL_SEL_T) f(t, tm_mem[t]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < PER; ++r)
+                if (tid + r * FL_SEL_T < n_tiles) f((int64_t)(tid + r * FL_SEL_T), tv[r]);
+        }
+    };
+    if (tid == 0) { s_ntl = 0u; s_cnt = 0u; s_lo = 0xffffffffu; s_hi = 0u; s_t0 = 0xffffffffu; }
+    if (tid < 256) hist[tid] = 0u;
+    __syncthreads();
+    // A threshold that at least topk tile maxima reach, without an exact selection: the maxima are
+    // cut into 255 equal-width bins between the smallest and the largest (bin 0 is for tiles with no
+    // eligible key, whose maximum is 0), b is the highest bin such that the bins from b up hold at
+    // least topk maxima, and T0 is the smallest maximum in those bins. It is at or below the
+    // topk-th largest maximum, so nothing of the answer is lost, and a tile whose maximum reaches
+    // T0 lies in those bins (the binning is monotone), so "maximum >= T0" lists exactly them.
+    {
+        uint32_t lo = 0xffffffffu, hi = 0u;
+        for_tiles([&](int64_t, uint32_t v) {
+            if (v) { lo = v < lo ? v : lo; hi = v > hi ? v : hi; }
+        });
+#pragma unroll
+        for (int d = 1; d < RA_WAVE; d <<= 1) {
+            const uint32_t ol = __shfl_xor(lo, d), oh = __shfl_xor(hi, d);
+            lo = ol < lo ? ol : lo;
+            hi = oh > hi ? oh : hi;
+        }
+        if (lane == 0) { atomicMin(&s_lo, lo); atomicMax(&s_hi, hi); }
+    }
+    __syncthreads();
+    const float lo_f = f32_from_ordered(s_lo);
+    const float width = s_hi ? f32_from_ordered(s_hi) - lo_f : 0.f;
+    const float to_bin = width > 0.f && width < INFINITY ? 254.0f / width : 0.f;
+    auto bin_of = [&](uint32_t v) {
+        if (!v) return 0;
+        const float b = (f32_from_ordered(v) - lo_f) * to_bin;
+        return 1 + (b >= 254.f ? 254 : b > 0.f ? (int)b : 0);
+    };
+    for_tiles([&](int64_t, uint32_t v) { atomicAdd(&hist[bin_of(v)], 1u); });
+    __syncthreads();
+    if (wv == 0) {
+        // lane l owns bins 4l .. 4l + 3; maxima in the bins from b up = total - (those below b)
+        const int b0 = (int)hist[4 * lane], b1 = (int)hist[4 * lane + 1], b2 = (int)hist[4 * lane + 2],
+                  b3 = (int)hist[4 * lane + 3];
+        const int incl = wave_incl_scan(b0 + b1 + b2 + b3);
+        const int total = __builtin_amdgcn_readlane(incl, RA_WAVE - 1);
+        const int from3 = total - incl + b3, from2 = from3 + b2, from1 = from2 + b1, from0 = from1 + b0;
+        const int best = from3 >= topk ? 3 : from2 >= topk ? 2 : from1 >= topk ? 1 : from0 >= topk ? 0 : -1;
+        const unsigned long long has = __ballot(best >= 0);     // never empty: n_tiles >= 2 topk
+        if (lane == 63 - __clzll(has)) s_prefix = (unsigned)(4 * lane + best);
+    }
+    __syncthreads();
+    const int bstar = (int)s_prefix;
+    if (bstar > 0) {
+        uint32_t m = 0xffffffffu;
+        for_tiles([&](int64_t, uint32_t v) {
+            if (bin_of(v) >= bstar) m = v < m ? v : m;
+        });
+#pragma unroll
+        for (int d = 1; d < RA_WAVE; d <<= 1) {
+            const uint32_t o = __shfl_xor(m, d);
+            m = o < m ? o : m;
+        }
+        if (lane == 0) atomicMin(&s_t0, m);
+    }
+    __syncthreads();
+    const uint32_t T0 = bstar > 0 ? s_t0 : 0u;
+    unsigned cnt = 0x80000000u;
+    if (T0 != 0u) {                          // (uniform)
+        // this workgroup's share: the listed tiles whose number is congruent to its slice (the order of
+        // a list differs from workgroup to workgroup, the tile numbers do not)
+        for_tiles([&](int64_t t, uint32_t v) {
+            if ((int)(t % FL_SLICES) == slice && v >= T0) {
+                const unsigned at = atomicAdd(&s_ntl, 1u);
+                if (at < FL_TILES_MAX) s_tl[at] = (unsigned short)t;
+            }
+        });
+        __syncthreads();
+        const int ntl = (int)s_ntl;
+        // (more tiles than the list holds: a crowd of ties)
+        for (int l = wv; l < ntl && ntl <= FL_TILES_MAX; l += FL_SEL_T / RA_WAVE) {
+            const int64_t tl = s_tl[l];
+            const int64_t id0 = (tl / 16) * FL_CHUNK + g4 * (16 * FL_ROWS) + (tl % 16) * FL_ROWS;
+            RowBits<DT> rows[FL_ROWS];
+#pragma unroll
+            for (int u = 0; u < FL_ROWS; ++u) rows[u] = load_key<DT>(Kh, id0 + u < N ? id0 + u : N - 1, lane16);
+            float part[FL_ROWS];
+#pragma unroll
+            for (int u = 0; u < FL_ROWS; ++u) part[u] = score_share<DT>(rows[u], qv);
+            const float sc = rows_tree<FL_ROWS>(part, lane16);
+            const int64_t id = id0 + (lane16 & (FL_ROWS - 1));
+            const bool counts = id < N && id >= s && id < N - w;
+            const uint32_t key = counts ? f32_ordered(sc) : 0u;
+            if (lane16 < FL_ROWS && key >= T0) {
+                const unsigned at = atomicAdd(&s_cnt, 1u);
+                if (at < FL_SLICE_CAND) mine[at] = ((unsigned long long)key << 32) | (uint32_t)id;
+            }
+        }
+        __syncthreads();
+        if (ntl <= FL_TILES_MAX && s_cnt <= (unsigned)cand_cap) {
+            cnt = s_cnt;
+            uint32_t* region = keys + (size_t)head * N + (size_t)slice * (N / FL_SLICES);
+            for (unsigned i = tid; i < cnt; i += FL_SEL_T) {
+                xwg_store(region + 2 * (size_t)i, (uint32_t)(mine[i] >> 32));
+                xwg_store(region + 2 * (size_t)i + 1, (uint32_t)mine[i]);
+            }
+        }
+    }
+    if (tid == 0) xwg_store(cand_count + head * FL_SLICES + slice, cnt);
+    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): this wavefront's stores have completed
+    __syncthreads();                          // ... and every other's
+    if (tid == 0)
+        s_last = __hip_atomic_fetch_add(tickets + head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_last != FL_SLICES - 1) return;
+    // ---- the last of the head's workgroups: the answer out of the eight lists
+    uint32_t* kh = keys + (size_t)head * N;
+    unsigned c = 0u, bad = 0u, start[FL_SLICES + 1], cj[FL_SLICES];
+#pragma unroll
+    for (int j = 0; j < FL_SLICES; ++j) cj[j] = xwg_load(cand_count + head * FL_SLICES + j);
+#pragma unroll
+    for (int j = 0; j < FL_SLICES; ++j) {
+        bad |= cj[j] & 0x80000000u;
+        start[j] = c;
+        c += cj[j] & 0x7fffffffu;
+    }
+    start[FL_SLICES] = c;
+    int n = -1;
+    if (!bad && c >= (unsigned)topk && c <= FL_CAND) {
+        // entry i of the eight lists laid end to end (all loads in one trip)
+        for (unsigned i = tid; i < c; i += FL_SEL_T) {
+            int j = 0;
+#pragma unroll
+            for (int x = 1; x < FL_SLICES; ++x) j += i >= start[x] ? 1 : 0;
+            unsigned first = 0u;
+#pragma unroll
+            for (int x = 1; x < FL_SLICES; ++x) first = j == x ? start[x] : first;
+            const uint32_t* e = kh + (size_t)j * (N / FL_SLICES) + 2 * (size_t)(i - first);
+            const uint32_t key = xwg_load(e), id = xwg_load(e + 1);
+            lds.sel[i] = ((unsigned long long)key << 32) | (0xffffffffu - id);
+        }
+        n = (int)c;
+    } else {
+        flat_score_head<DT>(q, K, head, n_q, n_kv, N, s, w, kh);
+    }
+    __syncthreads();
+    flat_select(lds, kh, nullptr, n_tiles, N, topk, ids_out + (size_t)head * topk, n);
+}
+
 // Re-ranking of a candidate list with the keys themselves (what follows a walk over 8-bit keys):
 // one workgroup per (sequence, query head) scores its candidates with the search's fixed-order
-// inner product (16 lanes per key row), ranks them by counting, and writes the best topk.
-#define RR_THREADS 256
+// inner product (16 lanes per key row), ranks them by counting, and writes the best topk. A launch is a
+// few dependent trips and little else, so a short list is one trip for its ids and one for its rows
+// (1024 threads, 4 rows per lane group: 256 candidates), and four threads count for each candidate
+// (200 candidates of 32 heads: 10.9 -> 6.2 us).
+#define RR_THREADS 1024
 #define RR_ROWS 4                  // key rows in flight per 16-lane group
+#define RR_COUNT 4                 // threads that count for one candidate
 template <int DT>
 __global__ __launch_bounds__(RR_THREADS) void rerank_kernel(const void* __restrict__ q,
                                                             const void* __restrict__ K, int n_q, int n_kv,
@@ -560,19 +604,21 @@ __global__ __launch_bounds__(RR_THREADS) void rerank_kernel(const void* __restri
     load_score_query<DT, DT>(reinterpret_cast<const char*>(q) + (size_t)head * RA_D * esz, lane16, qv);
     if (tid == 0) n_valid = 0;
     __syncthreads();
-    for (int c0 = 0; c0 < n_cand; c0 += 16 * RR_ROWS) {
+    constexpr int PER = RR_THREADS / 16;
+    for (int c0 = 0; c0 < n_cand; c0 += PER * RR_ROWS) {
         RowBits<DT> rows[RR_ROWS];
         int id[RR_ROWS];
 #pragma unroll
         for (int u = 0; u < RR_ROWS; ++u) {
-            const int c = c0 + u * 16 + grp;
-            id[u] = c < n_cand ? ch[c] : -1;
-            if (id[u] >= N) id[u] = -1;
-            rows[u] = load_key<DT>(Kh, id[u] >= 0 ? id[u] : 0, lane16);       // loads stay unconditional
+            const int c = c0 + u * PER + grp;
+            id[u] = ch[c < n_cand ? c : 0];
+            if (c >= n_cand || id[u] >= N) id[u] = -1;
         }
 #pragma unroll
+        for (int u = 0; u < RR_ROWS; ++u) rows[u] = load_key<DT>(Kh, id[u] >= 0 ? id[u] : 0, lane16);
+#pragma unroll
         for (int u = 0; u < RR_ROWS; ++u) {
-            const int c = c0 + u * 16 + grp;
+            const int c = c0 + u * PER + grp;
             const float sc = score_fixed<DT>(rows[u], qv);
             if (lane16 == 0 && c < n_cand) {
                 // [ordered(score)][~id]: larger key = (score descending, id ascending); 0 = no candidate
@@ -584,12 +630,14 @@ __global__ __launch_bounds__(RR_THREADS) void rerank_kernel(const void* __restri
     }
     __syncthreads();
     const int nv = n_valid;
-    for (int c = tid; c < n_cand; c += RR_THREADS) {
+    const int part = tid % RR_COUNT;
+    for (int c = tid / RR_COUNT; c < n_cand; c += RR_THREADS / RR_COUNT) {
         const unsigned long long k = keys[c];
-        if (k == 0ull) continue;
         int rank = 0;
-        for (int x = 0; x < n_cand; ++x) rank += keys[x] > k ? 1 : 0;
-        if (rank < topk) out[rank] = (int32_t)(0xffffffffu - (uint32_t)k);
+        for (int x = part; x < n_cand; x += RR_COUNT) rank += keys[x] > k ? 1 : 0;
+#pragma unroll
+        for (int d = 1; d < RR_COUNT; d <<= 1) rank += __shfl_xor(rank, d);
+        if (part == 0 && k != 0ull && rank < topk) out[rank] = (int32_t)(0xffffffffu - (uint32_t)k);
     }
     for (int i = (nv < topk ? nv : topk) + tid; i < topk; i += RR_THREADS) out[i] = -1;
 }
@@ -618,6 +666,7 @@ ra_status ra_launch_flat_topk(const void* q, const void* K, ra_dtype dt, int n_s
     const int G = n_q / n_kv;
     const int heads = n_seq * n_q;
     uint32_t* cand_count = tile_max + (size_t)heads * n_tiles;   // [heads][FL_SLICES], after the tile maxima
+    uint32_t* tickets = cand_count + (size_t)heads * FL_SLICES;  // [heads]
     // Two passes without stored keys whenever the tile maxima can place the threshold: writing the
     // 16.8 MB of keys of a 128K layer costs the scan a fifth of its time, and all but a few thousand
     // of them are never read again. Candidate pairs (key, id) live in the head's key area.
@@ -632,10 +681,10 @@ ra_status ra_launch_flat_topk(const void* q, const void* K, ra_dtype dt, int n_s
     do {                                                                                                      \
         if (two_pass)                                                                                         \
             hipLaunchKernelGGL((flat_scores_kernel<DTV, GG, false>), GRID, dim3(FL_THREADS), 0, st, q, K, n_q,  \
-                               n_kv, N, (int)ss, (int)ww, keys_ws, tile_max, n_tiles, DIV);                   \
+                               n_kv, N, (int)ss, (int)ww, keys_ws, tile_max, n_tiles, DIV, tickets);                   \
         else                                                                                                  \
             hipLaunchKernelGGL((flat_scores_kernel<DTV, GG, true>), GRID, dim3(FL_THREADS), 0, st, q, K, n_q,   \
-                               n_kv, N, (int)ss, (int)ww, keys_ws, tile_max, n_tiles, DIV);                   \
+                               n_kv, N, (int)ss, (int)ww, keys_ws, tile_max, n_tiles, DIV, tickets);                   \
     } while (0)
 #define RA_FL_DT(DTV)                                                                                         \
     do {                                                                                                      \
@@ -650,15 +699,16 @@ ra_status ra_launch_flat_topk(const void* q, const void* K, ra_dtype dt, int n_s
         if (two_pass && big) {                                                                                \
             hipLaunchKernelGGL((flat_rescore_kernel<DTV, true>), dim3(FL_SLICES, heads), dim3(FL_SEL_T), 0, st, \
                                q, K, n_q, n_kv, N, (int)ss, (int)ww, tile_max, n_tiles, topk, keys_ws,        \
-                               cand_count, cand_cap);                                                         \
+                               cand_count, cand_cap, tickets, ids);                                                         \
         } else if (two_pass) {                                                                                \
             hipLaunchKernelGGL((flat_rescore_kernel<DTV, false>), dim3(FL_SLICES, heads), dim3(FL_SEL_T), 0, st, \
                                q, K, n_q, n_kv, N, (int)ss, (int)ww, tile_max, n_tiles, topk, keys_ws,        \
-                               cand_count, cand_cap);                                                         \
+                               cand_count, cand_cap, tickets, ids);                                                         \
             RA_HIP(hipGetLastError());                                                                        \
         }                                                                                                     \
-        hipLaunchKernelGGL((flat_select_kernel<DTV>), dim3(heads), dim3(FL_SEL_T), 0, st, keys_ws, tile_max,    \
-                           n_tiles, N, topk, ids, two_pass, cand_count, q, K, n_q, n_kv, (int)ss, (int)ww);   \
+        if (!two_pass)                                                                                        \
+            hipLaunchKernelGGL(flat_select_kernel, dim3(heads), dim3(FL_SEL_T), 0, st, keys_ws, tile_max, n_tiles, \
+                               N, topk, ids);                                                                 \
     } while (0)
     if (dt == RA_BF16) RA_FL_DT(RA_BF16); else RA_FL_DT(RA_F32);
 #undef RA_FL_DT
