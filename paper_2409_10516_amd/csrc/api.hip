@@ -376,18 +376,22 @@ extern "C" ra_status ra_build_index(const void* K, const void* Q, ra_dtype dt, i
     const int graphs = n_seq * n_q;
     ra_index* ix = nullptr;
     RA_TRY(new_handle(n_seq, n_q, n_kv, N, deg, &ix));
+    // One piece of scratch memory: the lists, then the workspace of the two stages, which do not use it at
+    // the same time (an allocation or a free of a large piece is a quarter of a millisecond).
+    const size_t l_bytes = ((size_t)graphs * M * knn * sizeof(int32_t) + 255) & ~(size_t)255;
+    const size_t knn_bytes = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn);
+    const size_t proj_bytes = ra_project_workspace_bytes(graphs, N, M, knn);
     int32_t* L = nullptr;
-    void* order_ws = nullptr;
-    hipError_t e = hipMalloc((void**)&L, (size_t)graphs * M * knn * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc(&order_ws, ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn));
+    hipError_t e = hipMalloc((void**)&L, l_bytes + (knn_bytes > proj_bytes ? knn_bytes : proj_bytes));
     if (e != hipSuccess) {
         ra_set_error("allocating the KNN lists failed: %s", hipGetErrorString(e));
-        if (L) (void)hipFree(L);
         ra_index_free(ix);
         return e == hipErrorOutOfMemory ? RA_ENOMEM : RA_EHIP;
     }
-    ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, order_ws, (hipStream_t)stream, L);
-    if (rc == RA_OK) rc = ra_project(L, graphs, N, M, knn, deg, stream, ix->adj, ix->entry);
+    void* ws = reinterpret_cast<char*>(L) + l_bytes;
+    ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, (hipStream_t)stream, L);
+    if (rc == RA_OK)
+        rc = ra_launch_project(L, graphs, N, M, knn, deg, ws, (hipStream_t)stream, ix->adj, ix->entry);
     if (rc == RA_OK)
         rc = ra_launch_roots(ix->adj, ix->entry, graphs, N, deg, ix->roots, ix->root_cap, (hipStream_t)stream);
     if (rc == RA_OK && hipStreamSynchronize((hipStream_t)stream) != hipSuccess) {
@@ -395,7 +399,6 @@ extern "C" ra_status ra_build_index(const void* K, const void* Q, ra_dtype dt, i
         rc = RA_EHIP;
     }
     (void)hipFree(L);
-    (void)hipFree(order_ws);
     if (rc != RA_OK) {
         ra_index_free(ix);
         return rc;
