@@ -8,6 +8,12 @@
 //         [ordered(score) : 32][0x7fffffff - id : 31][not-yet-expanded : 1]
 //     so that "larger key" is exactly "(score descending, id ascending)" and one integer
 //     compare decides; ids are unique in the beam, so the flag bit never decides.
+// A walk of narrow steps is bound by the length of a step's dependent chain: LDS round trips, a trip to
+// L2 for the adjacency rows and one to memory for the key rows, barriers, and on the way every
+// instruction, taken branches above all: there are one or two wavefronts per SIMD to hide them. So the
+// common step is laid out as straight code (__builtin_expect), what the next phase needs first is read
+// along with the counter that says how much of it there is, and key rows take as few trips as they can.
+// 16 picks per step over 64K keys: 68.6 -> 51.1 us; one pick per step: 248 -> 185 us.
 // Each step expands the `expand` best unexpanded entries at once: their adjacency rows
 // are read with one coalesced load per row, unvisited neighbours are claimed with an LDS
 // atomic-or (which also removes duplicates), their key rows are gathered by 16-lane
@@ -15,7 +21,8 @@
 // beam's worst entry, and merged into the beam by rank: a kept candidate's place is the
 // number of beam entries above it (binary search) plus the number of candidates above it
 // (counted); a beam entry's place is its index plus a prefix sum over the candidates' slots.
-// No sort, no serial insertion, and the next step's picks fall out of the same numbers. The
+// No sort, no serial insertion, and the next step's picks fall out of the same numbers. (A step that
+// keeps few candidates finds the same places without the counters.) The
 // beam after a step is the top-ef of a set union, so it does not depend on the order in which
 // candidates were claimed.
 //
@@ -39,9 +46,11 @@
 #endif
 
 
-enum { C_MISSED = 0, C_NCAND = 1, C_NKEEP = 2, C_NUNEXP = 3, C_LO = 4, C_HI = 5, C_NSURV = 6, C_BIN = 7, C_WTOT = 8,
-       C_COUNT = 8 + SR_THREADS / RA_WAVE };
-#define SR_HSUM 33                // blocks of 64 beam slots: ef + 1 <= 2049 of them
+enum { C_MISSED = 0, C_LO = 1, C_HI = 2, C_NSURV = 3, C_BIN = 4, C_STEP = 5, C_STEP2 = 8, C_WTOT = 11,
+       C_COUNT = C_WTOT + SR_THREADS / RA_WAVE };
+enum { S_NCAND = 0, S_NKEEP = 1, S_NUNEXP = 2 };      // of the three words at C_STEP and at C_STEP2
+#define SR_NARROW 64              // most candidates of a merge without counters (one per lane)
+#define SR_TOUCH_BYTES (4 * RA_WAVE) // where touched words land (touch_line)
 #define SR_PREFILTER_SLACK 64     // a step that keeps more than ef + this many candidates drops the hopeless ones first
 #define SR_PREFILTER_REGS 8       // ... when a thread can hold its share of them (nk <= 8 T)
 
@@ -171,6 +180,11 @@ __device__ __forceinline__ RowBits<DT> load_key_stream(const void* Kh, int64_t r
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_i32(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
 }
 
 // The fixed-order inner product described in the file header, in two parts: a lane's share (its 8
@@ -350,6 +364,14 @@ __device__ __forceinline__ uint32_t claim_key(uint32_t* bits, int id) {
     return __hip_atomic_fetch_or(&bits[id >> 5], 1u << (id & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// Brings p's line into this XCD's L2 (p 4-byte aligned, in bounds): a load of one word that goes straight to
+// LDS, to 4 bytes per lane at lds_off that nothing reads, so that no register waits for it. (Ordinary loads
+// whose words fed a test that never held were waited for when the walk's loop turned: 700 of 7500 ticks
+// of a step that expands 16 nodes.) A wavefront waits for its own before the search ends.
+__device__ __forceinline__ void touch_line(const void* p, uint32_t lds_off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_off), "v"(p) : "m0");
+}
+
 // The whole search of one (sequence, query head) by one workgroup of T threads.
 // N is the number of keys the graph covers; the key rows of a (sequence, KV head) start every
 // kv_stride rows (kv_stride >= N: the cache may hold tokens appended after the index was built).
@@ -485,17 +507,24 @@ __device__ __forceinline__ int run_search(
 #ifdef SR_WAVE_CLOCKS
     if (head == 0 && tid == 0) sr_wave_ticks[0] = wall_clock64();      // search entered
 #endif
-    u64* cur = reinterpret_cast<u64*>(lds_raw);
+    // (the piece touched words land in comes first: its LDS address has to fit 16 bits)
+    const uint32_t touch_off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_raw;
+    u64* cur = reinterpret_cast<u64*>(lds_raw + SR_TOUCH_BYTES);
     u64* nxt = cur + ef;
     u64* ckey = nxt + ef;            // [maxc + 16] candidates that passed the beam threshold
     int* cid = reinterpret_cast<int*>(ckey + maxc + 16);  // [maxc] claimed neighbour ids
     int* cnt = cid + maxc;           // [maxc] merge counters of the candidates, zero between steps
-    int* hist = cnt + maxc;          // [ef + 1] candidates per beam slot, zero between steps
-    int* hist_nxt = hist + ef + 1;   // [ef + 1] the one the next step fills
-    int* hsum = hist_nxt + ef + 1;   // [SR_HSUM] candidates per 64 beam slots, zero between steps
-    int* hsum_nxt = hsum + SR_HSUM;  // [SR_HSUM]
-    int* picks = hsum_nxt + SR_HSUM; // [RA_MAX_EXPAND]
-    int* ctr = picks + RA_MAX_EXPAND;
+    int* hist = cnt + maxc;          // [ef + 1] candidates per beam slot, zero when a wide merge begins
+    int* hsum = hist + ef + 1;       // [(ef + 64) / 64] candidates per 64 beam slots, likewise
+    const int nhist = ef + 1 + (ef + 64) / 64;
+    int* picks = hist + nhist;       // [expand]
+    int* ctr = picks + expand;
+    // A step's counters: candidates claimed and kept, and the unexpanded entries of the beam it starts
+    // from. The next step uses the other three words, which are cleared at the start of this one (no
+    // barrier has to part a counter's last reader from its clearing).
+    int* cc = ctr + C_STEP;
+    int* cc_nxt = ctr + C_STEP2;
+    bool hist_used = false;
     int* wtot = ctr + C_WTOT;
     // urank[i], i in [0, bn]: unexpanded entries among the first i of the beam, as of the last pick
     // but before its picks were marked expanded (two buffers, swapped with the beam's)
@@ -529,7 +558,7 @@ __device__ __forceinline__ int run_search(
     }
     // (the loads above are in flight while the LDS state is cleared)
     for (int i = tid; i < nwords; i += T) bits[i] = 0u;
-    for (int i = tid; i < maxc + 2 * ef + 2 + 2 * SR_HSUM; i += T) cnt[i] = 0;      // cnt, hist, hsum and their twins
+    for (int i = tid; i < maxc + nhist; i += T) cnt[i] = 0;      // cnt, hist and hsum
     // A seed set (ra_launch_seeds) has the same layout with [1] = 0: the walk starts from all of its
     // keys at once, scored in one gather, the best ef of them in the beam and none of them expanded.
     // That is a start of its own, not a shortcut for steps of the single-entry walk: no step is
@@ -552,10 +581,10 @@ __device__ __forceinline__ int run_search(
         }
         if (tid == 0) {
             urank[0] = 0;
-            ctr[C_NCAND] = n_root;
-            ctr[C_NKEEP] = n_root;           // every key of a start set is kept (scored below)
-            ctr[C_NUNEXP] = 0;
-            ctr[C_LO] = -1;
+            cc[S_NCAND] = n_root;
+            cc[S_NKEEP] = n_root;            // every key of a start set is kept (scored below)
+            cc[S_NUNEXP] = 0;
+            ctr[C_LO] = -1;                  // as unsigned: the largest value; see the pre-filter below
             ctr[C_HI] = 0;
             ctr[C_NSURV] = 0;
             ctr[C_MISSED] = 0;
@@ -571,21 +600,28 @@ __device__ __forceinline__ int run_search(
                 cur[0] = make_key(sc, e0) & ~1ull;
                 picks[0] = e0;
                 urank[0] = 0;
-                ctr[C_NCAND] = 0;
-                ctr[C_NKEEP] = 0;
-                ctr[C_NUNEXP] = 1;
+                cc[S_NCAND] = 0;
+                cc[S_NKEEP] = 0;
+                cc[S_NUNEXP] = 1;
                 (void)claim_key(bits, e0);
             }
         }
         bn = 1; n_visited = 1; n_expanded = 0; n_iters = 0;
     }
+    // The adjacency cells of a step are dealt to the threads in order (cell x is slot x % deg of pick x / deg):
+    // the pick and the slot of a thread's first two cells are the same in every step. (The quotient by a
+    // multiplication, exact while x * deg < 2^32: there are at most RA_MAX_EXPAND * deg cells.)
+    const uint32_t deg_m = 0xffffffffu / (uint32_t)deg + 1u;
+    const int xr0 = min((int)__umulhi((uint32_t)tid, deg_m), expand - 1), xr1 = min((int)__umulhi((uint32_t)(tid + T), deg_m), expand - 1);
+    const int xs0 = min(tid - xr0 * deg, deg - 1), xs1 = min(tid + T - xr1 * deg, deg - 1);
+    const int gi0 = min(grp, maxc - 1), gi1 = min(grp + T / 16, maxc - 1);
+    int pk0 = e0, pk1 = e0;          // the picks of those cells
     bool picked = true;              // the merge of the last step already chose this step's picks
     // Adjacency rows likely to be expanded soon are touched ahead of time (one word of the row's
     // first line), so that the row is in this XCD's L2 when its step reads it: the rows of the
     // candidates a step keeps, touched while they are merged, and the rows of the beam entries that
-    // are next in line after the coming step's picks. The words land in early_a / early_b and only
-    // feed a test that never holds; they are consumed one phase later, when they have long arrived.
-    uint32_t early_a = 0u, early_b = 0u, early_acc = 0u;
+    // are next in line after the coming step's picks. The words land in a spare piece of LDS and are
+    // read by nothing (touch_line).
     __syncthreads();
     SR_TICK(13);
 #ifdef SR_WAVE_CLOCKS
@@ -685,9 +721,9 @@ __device__ __forceinline__ int run_search(
     for (;;) {
         SR_TICK_ITER(n_iters);
         int np;
-        if (first) {
+        if (__builtin_expect(first, 0)) {
             np = 0;                  // nothing of the (empty) beam is expanded: see the set-up
-        } else if (!picked) {
+        } else if (__builtin_expect(!picked, 0)) {
             // ---- pick the `expand` best unexpanded entries: the beam is sorted, so the picks are
             //      the first `expand` set flags in beam order. T entries per round, one per
             //      thread: ballot prefix inside a wavefront, wavefront totals through LDS, the
@@ -701,9 +737,8 @@ __device__ __forceinline__ int run_search(
                 const u64 unmask = __ballot(un);
                 if (lane == 0) wtot[wv] = __popcll(unmask);
                 if (tid == 0) {
-                    ctr[C_NCAND] = 0;
-                    ctr[C_NKEEP] = 0;
-                    ctr[C_NUNEXP] = 0;
+                    cc[S_NCAND] = 0;
+                    cc[S_NKEEP] = 0;
                 }
                 __syncthreads();
                 int before = total;
@@ -722,11 +757,15 @@ __device__ __forceinline__ int run_search(
             }
             np = total < expand ? total : expand;
             if (np == 0) break;
+            pk0 = picks[xr0];
+            pk1 = picks[xr1];
         } else {
             // the merge left the picks in place and counted the unexpanded entries
-            const int total = ctr[C_NUNEXP];
+            pk0 = picks[xr0];            // (past the last pick: some earlier one or anything, not used)
+            pk1 = picks[xr1];
+            const int total = __builtin_amdgcn_readfirstlane(cc[S_NUNEXP]);
             np = total < expand ? total : expand;
-            if (np == 0) break;
+            if (__builtin_expect(np == 0, 0)) break;
             if (tid == 0) urank[bn] = (uint16_t)total;
         }
         SR_TICK(0);
@@ -740,98 +779,116 @@ __device__ __forceinline__ int run_search(
             n_expanded += np;
         }
 
-        // ---- read the picked adjacency rows (all loads issued before any is consumed),
-        //      claim unvisited neighbours (the doubled first step has its candidates already)
-        if (!first) {
-            const int cells = np * deg;
-            // cell x is slot x % deg of pick x / deg; the quotient by a multiplication (exact while
-            // x * deg < 2^32: there are at most RA_MAX_EXPAND * deg cells), because a division per
-            // cell costs more than everything else in this loop
-            const uint32_t deg_m = 0xffffffffu / (uint32_t)deg + 1u;
-            // L cells per thread and pass, all L loads issued before the first claim: 8 for a wide
-            // step (8192 cells), fewer for a narrow one, where the loads past the last cell are waste
-            auto claim_cells = [&](auto loads_c) __attribute__((always_inline)) {
-                constexpr int L = decltype(loads_c)::value;
-                for (int x0 = 0; x0 < cells; x0 += T * L) {
-                    int nbv[L];
-#pragma unroll
-                    for (int u = 0; u < L; ++u) {
-                        // out-of-range slots re-read the last cell: loads without a branch around
-                        // them can all be issued before the first one is consumed
-                        const int x = x0 + u * T + tid;
-                        const int xc = x < cells ? x : cells - 1;
-                        const int xr = (int)__umulhi((uint32_t)xc, deg_m);       // xc / deg
-                        const int v = adj_h[(size_t)picks[xr] * deg + (xc - xr * deg)];
-                        nbv[u] = x < cells ? v : -1;
-                    }
-#pragma unroll
-                    for (int u = 0; u < L; ++u) {
-                        const int nb = nbv[u];
-                        if (nb >= 0 && nb < N) {
-                            const uint32_t bit = 1u << (nb & 31);
-                            const uint32_t old = claim_key(bits, nb);
-                            if (!(old & bit)) cid[atomicAdd(&ctr[C_NCAND], 1)] = nb;
-                        }
-                    }
-                }
-            };
-            if (cells > 4 * T) claim_cells(sr_int<SR_ADJ_LOADS>{});
-            else claim_cells(sr_int<2>{});
-        }
-        __syncthreads();
-        const int nc = ctr[C_NCAND];
-        n_visited += nc;
-        SR_TICK(1);
-        if (tid == 0) {
-            ctr[C_NUNEXP] = 0;               // everyone read it before the barrier above
+        if (tid == 0) {                      // (read for the last time before the barrier that ended the last merge)
+            cc_nxt[S_NCAND] = 0;
+            cc_nxt[S_NKEEP] = 0;
+            cc_nxt[S_NUNEXP] = 0;
             if (!first) {                    // (a start set's extremes were collected while it was scored)
-                ctr[C_LO] = -1;              // as unsigned: the largest value; see the pre-filter below
+                ctr[C_LO] = -1;
                 ctr[C_HI] = 0;
                 ctr[C_NSURV] = 0;
             }
         }
-        early_acc ^= early_a ^ early_b;      // issued a phase or more ago
-        early_a = early_b = 0u;
+        if (hist_used) {
+            for (int i = tid; i < nhist; i += T) hist[i] = 0;
+            hist_used = false;
+        }
+        // ---- read the picked adjacency rows (all loads issued before any is consumed),
+        //      claim unvisited neighbours (the doubled first step has its candidates already)
+        if (!first) {
+            const int cells = np * deg;
+            auto claim = [&](int nb) __attribute__((always_inline)) {
+                if (nb >= 0 && nb < N) {
+                    const uint32_t bit = 1u << (nb & 31);
+                    const uint32_t old = claim_key(bits, nb);
+                    if (!(old & bit)) cid[atomicAdd(&cc[S_NCAND], 1)] = nb;
+                }
+            };
+            // out-of-range cells read a cell of the entry row: loads without a branch around them can all be
+            // issued before the first is consumed
+            if (__builtin_expect(cells <= 2 * T, 1)) {
+                const int v0 = adj_h[(size_t)(tid < cells ? pk0 : e0) * deg + xs0];
+                int v1 = -1;
+                if (cells > T) v1 = adj_h[(size_t)(tid + T < cells ? pk1 : e0) * deg + xs1];
+                claim(tid < cells ? v0 : -1);
+                if (cells > T) claim(tid + T < cells ? v1 : -1);
+            } else {
+                // L cells per thread and pass: as many as a step needs, up to SR_ADJ_LOADS
+                auto claim_cells = [&](auto loads_c) __attribute__((always_inline)) {
+                    constexpr int L = decltype(loads_c)::value;
+                    for (int x0 = 0; x0 < cells; x0 += T * L) {
+                        int nbv[L];
+#pragma unroll
+                        for (int u = 0; u < L; ++u) {
+                            const int x = x0 + u * T + tid;
+                            const int xc = x < cells ? x : cells - 1;
+                            const int xr = (int)__umulhi((uint32_t)xc, deg_m);       // xc / deg
+                            const int v = adj_h[(size_t)picks[xr] * deg + (xc - xr * deg)];
+                            nbv[u] = x < cells ? v : -1;
+                        }
+#pragma unroll
+                        for (int u = 0; u < L; ++u) claim(nbv[u]);
+                    }
+                };
+                if (cells > 4 * T) claim_cells(sr_int<SR_ADJ_LOADS>{});
+                else claim_cells(sr_int<4>{});
+            }
+        }
+        // (the first rows' ids are read with the counter that says how many there are)
+        __syncthreads();
+        const int id0 = cid[gi0], id1 = cid[gi1];
+        const int nc = __builtin_amdgcn_readfirstlane(cc[S_NCAND]);
+        n_visited += nc;
+        SR_TICK(1);
 
         // ---- gather and score the new candidates; keep those that can enter the beam
         const u64 worst = bn == ef ? (cur[bn - 1] >> 1) : 0ull;
-        // (R rows per 16-lane group with no branch between them, as for a start set)
-        auto gather_rows = [&](auto rows_c, int c0) __attribute__((always_inline)) {
+        // (R rows per 16-lane group with no branch between them, as for a start set; groups without a
+        // candidate re-read the entry row instead of branching)
+        auto gather_ids = [&](auto rows_c, const int* ids_u, int cw, int idw) __attribute__((always_inline)) {
             constexpr int R = decltype(rows_c)::value;
             RowBits<KT> rows[R];
-            int cidv[R];
 #pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const int c = c0 + u * (T / 16) + grp;
-                cidv[u] = c < nc ? cid[c] : -1;
-            }
-            // groups without a candidate re-read the entry row instead of branching
-#pragma unroll
-            for (int u = 0; u < R; ++u) rows[u] = load_key<KT>(Kh, cidv[u] >= 0 ? cidv[u] : e0, lane16);
+            for (int u = 0; u < R; ++u) rows[u] = load_key<KT>(Kh, ids_u[u] >= 0 ? ids_u[u] : e0, lane16);
             float part[R];
 #pragma unroll
             for (int u = 0; u < R; ++u) part[u] = score_share<KT>(rows[u], qv);
             const float sc = rows_tree<R>(part, lane16);     // of row lane16 & (R - 1)
-            const int c = c0 + (lane16 & (R - 1)) * (T / 16) + grp;
-            if (lane16 < R && c < nc) {
-                const u64 key = make_key(sc, cid[c]);
-                if ((key >> 1) > worst) ckey[atomicAdd(&ctr[C_NKEEP], 1)] = key;
+            if (lane16 < R && cw < nc) {
+                const u64 key = make_key(sc, idw);
+                if ((key >> 1) > worst) ckey[atomicAdd(&cc[S_NKEEP], 1)] = key;
             }
         };
+        constexpr int PER = T / 16;
+        auto gather_rows = [&](auto rows_c, int c0) __attribute__((always_inline)) {
+            constexpr int R = decltype(rows_c)::value;
+            int cidv[R];
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const int c = c0 + u * PER + grp;
+                cidv[u] = c < nc ? cid[c] : -1;
+            }
+            const int cw = c0 + (lane16 & (R - 1)) * PER + grp;  // the candidate this lane will keep or drop
+            gather_ids(rows_c, cidv, cw, cid[cw < nc ? cw : 0]);
+        };
         if (!first) {                                        // (a start set is scored already)
-            constexpr int PER = T / 16;
-            int c0 = 0;
-            for (; nc - c0 >= SR_UNROLL * PER; c0 += SR_UNROLL * PER) gather_rows(sr_int<SR_UNROLL>{}, c0);
-            if constexpr (SR_UNROLL > 4)
-                if (nc - c0 >= 4 * PER) { gather_rows(sr_int<4>{}, c0); c0 += 4 * PER; }
-            if (nc - c0 >= 2 * PER) { gather_rows(sr_int<2>{}, c0); c0 += 2 * PER; }
-            if (nc - c0 >= PER) { gather_rows(sr_int<1>{}, c0); c0 += PER; }
-            if (nc - c0 > 0) gather_rows(sr_int<1>{}, c0);
+            // as few trips to memory as there can be: the last one takes the number of rows in flight that
+            // covers what is left (a trip is 1300 ticks or more, a re-read of the entry row nothing)
+            if (__builtin_expect(nc <= 2 * PER, 1)) {
+                const int ids_u[2] = {grp < nc ? id0 : -1, grp + PER < nc ? id1 : -1};
+                if (nc > PER) gather_ids(sr_int<2>{}, ids_u, (lane16 & 1) * PER + grp, lane16 & 1 ? id1 : id0);
+                else if (nc > 0) gather_ids(sr_int<1>{}, ids_u, grp, id0);
+            } else {
+                int c0 = 0;
+                for (; nc - c0 > SR_UNROLL / 2 * PER; c0 += SR_UNROLL * PER) gather_rows(sr_int<SR_UNROLL>{}, c0);
+                if (nc - c0 > 2 * PER) gather_rows(sr_int<4>{}, c0);
+                else if (nc - c0 > 0) gather_rows(sr_int<2>{}, c0);
+            }
         }
         __syncthreads();
-        int nk = ctr[C_NKEEP];
+        int nk = __builtin_amdgcn_readfirstlane(cc[S_NKEEP]);
         SR_TICK(2);
-        if (nk == 0) {               // uniform: nothing enters the beam
+        if (__builtin_expect(nk == 0, 0)) {               // uniform: nothing enters the beam
             picked = false;
             continue;
         }
@@ -854,7 +911,7 @@ __device__ __forceinline__ int run_search(
         // beam, picks and counters come out as the merge would leave them (all entries unexpanded:
         // the unexpanded entries above a key are its position).
         bool bucketed = false;
-        if (nk > ef + SR_PREFILTER_SLACK && nk <= SR_PREFILTER_REGS * T && maxc >= 256) {
+        if (__builtin_expect(nk > ef + SR_PREFILTER_SLACK, 0) && nk <= SR_PREFILTER_REGS * T && maxc >= 256) {
             const bool buckets = first && seeded && maxc >= 768;
             u64 mine[SR_PREFILTER_REGS];
             uint32_t lo = 0xffffffffu, hi = 0u;
@@ -934,9 +991,7 @@ __device__ __forceinline__ int run_search(
                     if (pos < ef) {
                         if (pos < expand) {                  // this step's picks: the first `expand` entries
                             picks[pos] = key_id(k);
-#ifndef SR_NO_EARLY_TOUCH
-                            early_a = *reinterpret_cast<const uint32_t*>(adj_h + (size_t)key_id(k) * deg);
-#endif
+                            touch_line(adj_h + (size_t)key_id(k) * deg, touch_off);
                             k &= ~1ull;
                         }
                         nxt[pos] = k;
@@ -944,9 +999,7 @@ __device__ __forceinline__ int run_search(
                     }
                 }
                 if (tid == 0) {
-                    ctr[C_NUNEXP] = ef;                      // every entry of the new beam (nsurv >= ef)
-                    ctr[C_NCAND] = 0;
-                    ctr[C_NKEEP] = 0;
+                    cc_nxt[S_NUNEXP] = ef;                      // every entry of the new beam (nsurv >= ef)
                 }
                 nk = nsurv;
                 bucketed = true;
@@ -970,14 +1023,113 @@ __device__ __forceinline__ int run_search(
         //      count of *unexpanded* elements above each element (every candidate is unexpanded;
         //      for the beam's part urank has it), so the next step's picks, the elements with
         //      fewer than `expand` unexpanded ones above them, fall out of the merge.
-        if (!bucketed) {
+        //      Few candidates (SR_NARROW, and not many among any 64 beam entries) take the shorter way below.
+        const bool narrow = !first && nk <= SR_NARROW && nk <= 16 + bn / 16;
+        auto sum16 = [&](int v) __attribute__((always_inline)) {       // over the 16 lanes of the group, in each of them
+            v += dpp_i32<0xB1>(v);
+            v += dpp_i32<0x4E>(v);
+            v += dpp_i32<0x141>(v);
+            return v + dpp_i32<0x140>(v);
+        };
+        // number of beam entries above k (the same for the 16 lanes of a group): a 16-way search, two
+        // dependent reads for a beam of up to 256 entries and three for a longer one; and the unexpanded
+        // ones of them (this step's picks, the first unexpanded entries, are marked expanded by now)
+        auto search16 = [&](u64 k, int& b, int& ub) __attribute__((always_inline)) {
+            b = 0;
+            if (bn > 256) {
+                const int at = lane16 * 256 + 255;
+                b = 256 * sum16(at < bn && cur[at < bn ? at : 0] > k ? 1 : 0);
+            }
+            const int at = b + lane16 * 16 + 15;
+            b += 16 * sum16(at < bn && cur[at < bn ? at : 0] > k ? 1 : 0);
+            const int last = b + lane16;
+            const u64 e = cur[last < bn ? last : 0];
+            ub = (int)urank[b] - np;
+            ub = ub > 0 ? ub : 0;
+            const int up = last < bn && e > k ? 1 : 0;
+            const int n = sum16(up + ((up & (int)e) << 16));         // (low half: above; high half: of them unexpanded)
+            ub += n >> 16;
+            b += n & 0xffff;
+        };
+        if (__builtin_expect(narrow, 1)) {
+            // ---- a step that keeps few candidates is merged without counters in LDS and without a barrier
+            //      in between: 16 lanes find a candidate's place (its beam slot by a 16-way search,
+            //      two or three dependent reads; the candidates above it by one comparison per lane and 16
+            //      of them), and a wavefront finds its 64 beam entries' places from the candidates held
+            //      one per lane: those above all of the 64 count for every entry, those inside their
+            //      range are compared one by one (45 ticks each, so a beam of 256 takes this way up to 32
+            //      candidates: with 48, 16 picks per step ran 4 % slower, with 16 no faster).
+            //      The wide merge below is three chains of LDS round trips and a barrier whatever the
+            //      number of candidates: 3900 ticks of a step that this does in 1450.
+            const int wn = T / RA_WAVE - 1 - wv;              // the last wavefronts take the first candidates
+            if (tid < nk) touch_line(adj_h + (size_t)key_id(ckey[tid]) * deg, touch_off);
+            for (int c0 = wn * 4; c0 < nk; c0 += T / 16) {
+                const int c = c0 + (lane >> 4);
+                const bool live = c < nk;
+                const u64 k = ckey[live ? c : 0];
+                u64 other[SR_NARROW / 16];
+#pragma unroll
+                for (int i = 0; i < SR_NARROW / 16; ++i) other[i] = ckey[i * 16 + lane16 < nk ? i * 16 + lane16 : 0];
+                int b, ub;                                    // beam entries above it; the unexpanded ones of them
+                search16(k, b, ub);
+                int above = 0;
+#pragma unroll
+                for (int i = 0; i < SR_NARROW / 16; ++i) above += i * 16 + lane16 < nk && other[i] > k ? 1 : 0;
+                above = sum16(above);
+                const int pos = b + above;
+                const bool un = live && lane16 == 0 && pos < ef;
+                const u64 um = __builtin_amdgcn_ballot_w64(un);
+                if (lane == 0 && um) atomicAdd(&cc_nxt[S_NUNEXP], __popcll(um));
+                if (un) {
+                    const int ur = above + ub;
+                    const bool pick = ur < expand;
+                    if (pick) picks[ur] = key_id(k);
+                    nxt[pos] = pick ? k & ~1ull : k;
+                    urank_nxt[pos] = (uint16_t)ur;
+                }
+            }
+            for (int e0 = wv * RA_WAVE; e0 < bn; e0 += T) {
+                const int e = e0 + lane;
+                const u64 ck = ckey[lane < nk ? lane : 0];
+                u64 k = cur[e < bn ? e : bn - 1];
+                const int ub = (int)urank[e < bn ? e : bn - 1] - np;
+                const uint32_t klo = (uint32_t)k, khi = (uint32_t)(k >> 32);
+                const u64 hi = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)khi, 0) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)klo, 0);
+                const u64 lo = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)khi, RA_WAVE - 1) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)klo, RA_WAVE - 1);
+                const u64 all = __builtin_amdgcn_ballot_w64(lane < nk && ck > hi);
+                u64 inside = __builtin_amdgcn_ballot_w64(lane < nk && ck > lo) & ~all;
+                int c = __popcll(all);
+                const int clo = (int)(uint32_t)ck, chi = (int)(uint32_t)(ck >> 32);
+                while (inside) {
+                    const int l = __builtin_ctzll(inside);
+                    inside &= inside - 1ull;
+                    const u64 x = ((u64)(uint32_t)__builtin_amdgcn_readlane(chi, l) << 32) |
+                                  (uint32_t)__builtin_amdgcn_readlane(clo, l);
+                    c += x > k ? 1 : 0;
+                }
+                const int pos = e + c, ur = c + (ub > 0 ? ub : 0);
+                const bool un = e < bn && pos < ef && (k & 1ull);
+                const u64 um = __builtin_amdgcn_ballot_w64(un);
+                if (lane == 0 && um) atomicAdd(&cc_nxt[S_NUNEXP], __popcll(um));
+                if (un && ur < expand) {
+                    picks[ur] = key_id(k);
+                    k &= ~1ull;
+                } else if (un && ur < 2 * expand) {           // next in line after those picks
+                    touch_line(adj_h + (size_t)key_id(k) * deg, touch_off);
+                }
+                if (e < bn && pos < ef) {
+                    nxt[pos] = k;
+                    urank_nxt[pos] = (uint16_t)ur;
+                }
+            }
+        } else if (!bucketed) {
             const int E = bn + nk;
             const int nch = (nk + 15) >> 4;
             const int items = nk * nch;
-#ifndef SR_NO_EARLY_TOUCH
-            if (tid < nk)
-                early_a = *reinterpret_cast<const uint32_t*>(adj_h + (size_t)key_id(ckey[tid]) * deg);
-#endif
+            hist_used = true;
+            if (tid < nk) touch_line(adj_h + (size_t)key_id(ckey[tid]) * deg, touch_off);
             for (int c = tid; c < nk; c += T) {
                 const int b = count_better(cur, bn, ckey[c]);
                 if (b) atomicAdd(&cnt[c], b << 16);           // high half: beam entries above it
@@ -1006,13 +1158,6 @@ __device__ __forceinline__ int run_search(
             SR_TICK(9);
             __syncthreads();
             SR_TICK(3);
-            if (tid == 0) {
-                ctr[C_NCAND] = 0;
-                ctr[C_NKEEP] = 0;
-            }
-            for (int i = tid; i <= ef; i += T) hist_nxt[i] = 0;
-            if constexpr (HSUM)
-                if (tid < SR_HSUM) hsum_nxt[tid] = 0;
             SR_TICK(10);
             for (int e0 = 0; e0 < E; e0 += T) {                   // T elements per round
                 const int e = e0 + tid;
@@ -1060,18 +1205,16 @@ __device__ __forceinline__ int run_search(
                         picks[ur] = key_id(k);
                         k &= ~1ull;
                     }
-#ifndef SR_NO_EARLY_TOUCH
                     else if (beam && un && ur < 2 * expand) {     // next in line after those picks
-                        early_b = *reinterpret_cast<const uint32_t*>(adj_h + (size_t)key_id(k) * deg);
+                        touch_line(adj_h + (size_t)key_id(k) * deg, touch_off);
                     }
-#endif
                     if (pos < ef) {
                         nxt[pos] = k;
                         urank_nxt[pos] = (uint16_t)ur;
                     }
                 }
                 const u64 um = __ballot(un);
-                if (lane == 0 && um) atomicAdd(&ctr[C_NUNEXP], __popcll(um));
+                if (lane == 0 && um) atomicAdd(&cc_nxt[S_NUNEXP], __popcll(um));
             }
         }
         __syncthreads();
@@ -1079,15 +1222,13 @@ __device__ __forceinline__ int run_search(
         bn = bn + nk < ef ? bn + nk : ef;
         u64* t = cur; cur = nxt; nxt = t;
         uint16_t* tu = urank; urank = urank_nxt; urank_nxt = tu;
-        int* th = hist; hist = hist_nxt; hist_nxt = th;
-        if constexpr (HSUM) { int* ts = hsum; hsum = hsum_nxt; hsum_nxt = ts; }
+        int* tc = cc; cc = cc_nxt; cc_nxt = tc;
         picked = true;
         first = false;
     }
 
     hook.before_output();
-    early_acc ^= early_a ^ early_b;
-    if (early_acc == 0x9e3779b9u && N < 0) ids[(size_t)head * topk] = -1;    // never: keeps the early touches alive
+    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): no touch of this wavefront still has to land in LDS
     // ---- result: best-first beam entries outside the static set W = [0,s) u [N-w,N). A short list is the
     //      first wavefront's alone (the others wait at the closing barrier); of a long one (a wavefront
     //      would be 32 rounds over 2048 entries) every wavefront takes rounds, T entries at a time.
@@ -1113,7 +1254,7 @@ __device__ __forceinline__ int run_search(
             out[i] = -1;
             if (lds_ids) lds_ids[i] = -1;
         }
-        if (tid == 0) ctr[C_NKEEP] = cnt;
+        if (tid == 0) ctr[C_BIN] = cnt;
     }
     } else {
         int32_t* out = ids + (size_t)head * topk;
@@ -1143,20 +1284,20 @@ __device__ __forceinline__ int run_search(
             out[i] = -1;
             if (lds_ids) lds_ids[i] = -1;
         }
-        if (tid == 0) ctr[C_NKEEP] = cnt;
+        if (tid == 0) ctr[C_BIN] = cnt;
     }
     if (stats && tid == 0) {
         ra_stats st;
         st.n_visited = n_visited;
         st.n_expanded = n_expanded;
         st.n_iters = n_iters;
-        st.n_returned = ctr[C_NKEEP];
+        st.n_returned = ctr[C_BIN];
         stats[head] = st;
     }
     __syncthreads();
     SR_TICK(6);
     SR_TICK_FLUSH;
-    return ctr[C_NKEEP];
+    return ctr[C_BIN];
 }
 
 
@@ -1172,8 +1313,8 @@ static inline int search_threads(int heads, int ef) {
 // LDS bytes run_search needs.
 static inline size_t search_lds_bytes(int64_t N, int deg, int ef, int expand, bool global_bitset) {
     const int maxc = expand * deg;
-    size_t b = (size_t)2 * ef * 8 + (size_t)(maxc + 16) * 8 + (size_t)maxc * 4 + (size_t)(maxc + 2 * ef + 2) * 4 +
-               (RA_MAX_EXPAND + C_COUNT + 2 * SR_HSUM) * 4 + (size_t)(ef + 1) * 4;
+    size_t b = SR_TOUCH_BYTES + (size_t)2 * ef * 8 + (size_t)(maxc + 16) * 8 + (size_t)maxc * 4 +
+               (size_t)(maxc + ef + 1 + (ef + 64) / 64) * 4 + (expand + C_COUNT) * 4 + (size_t)(ef + 1) * 4;
     if (!global_bitset) b += (size_t)((N + 31) >> 5) * 4;
     return b;
 }

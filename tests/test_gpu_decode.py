@@ -308,6 +308,24 @@ def test_beam_wider_than_the_workgroup(expand):
     idx.free()
 
 
+@pytest.mark.parametrize("ef", [1, 15, 16, 17, 64, 65, 256, 257, 300, 769, 1024])
+def test_merges_at_the_limits_of_beam_and_candidates(ef):
+    """The two ways of merging a step's candidates and the 16-way search of the narrow one, at beams that
+    end on, before and after a block of 16, 64 and 256 entries, with one to many picks per step (one to
+    hundreds of candidates): ids and counters bit-exact, stand-alone and fused."""
+    w, adj, ent, idx, Kd, Vd = _prepared("config0_small")
+    K, W, topk = to_np(w.K[0, 0]), OA.static_ids(w.K.shape[2], w.sink, w.window), min(ef, 10)
+    for t, expand in enumerate((1, 3, 7, 64)):
+        q = w.q_decode[t].to(DEV)
+        ids, st = ra.ra_search(q, idx, Kd, w.sink, w.window, topk, ef, expand)
+        out, lse, ids_d, st_d = ra.ra_decode_step(q, idx, Kd, Vd, w.sink, w.window, topk, ef, expand)
+        assert torch.equal(ids, ids_d) and torch.equal(st, st_d)
+        ref, rst = OS.greedy_search(to_np(w.q_decode[t, 0, 0]), K, adj[0], ent[0], ef, topk, expand, exclude=W,
+                                    score_fn=OS.score32)
+        assert ids[0, 0].tolist() == ref.tolist(), (ef, expand)
+        assert st[0, 0].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]]
+
+
 @pytest.mark.parametrize("n_q,n_kv,dtype", [(8, 1, torch.bfloat16), (4, 2, torch.bfloat16), (8, 1, torch.float32),
                                             (4, 1, torch.float32)])
 def test_decode_step_other_group_sizes(n_q, n_kv, dtype):
