@@ -11,8 +11,8 @@
 //      keys that one 16-lane group scores in a chunk of FL_CHUNK (FL_ROWS consecutive keys out of every
 //      16 x FL_ROWS), so a tile maximum stays in registers until it is written.
 //   2. flat_rescore_kernel: a threshold that at least topk tile maxima reach; the tiles at or above it
-//      are scored again, and the last of a head's workgroups to finish orders the candidates (a launch
-//      of its own for that was 5 us and its gap; 70.4 -> 66.3 us with the attention that follows).
+//      are scored again, and the last of a head's workgroups to finish orders the candidates (with few heads: a
+//      launch of its own for that was 5 us and its gap; 70.4 -> 66.3 us with the attention that follows).
 // Inputs with too few or too many tiles for that store every key in the first kernel and
 // flat_select_kernel picks the answer from them: from the tiles at or above the topk-th largest tile
 // maximum, else from a threshold placed from a strided sample and one pass over all keys; when
@@ -20,6 +20,35 @@
 // passes) finds the k-th largest key, and the keys above it plus the lowest ids among its ties are
 // taken.
 #include "search_dev.h"
+
+// Sorts a[0 .. n) in LDS in descending order, by a workgroup of T threads (all call it; ends past a
+// barrier). The array is filled up with zeros to a power of two. Bitonic: a thread has the pair (i, i + j) of
+// a stage, and with j up to 64 the pairs of a wavefront are its own 128 entries, so only the few stages
+// with a longer stride need a barrier. (Counting the larger keys of each key, as done for the usual
+// short list, is quadratic: 1000 keys took 60 us, sorting them takes 5.)
+#define SORT_COUNT_MAX 256
+template <int T>
+__device__ __forceinline__ void sort_descending(unsigned long long* a, int n) {
+    const int tid = threadIdx.x;
+    int n2 = 128;
+    while (n2 < n) n2 <<= 1;
+    for (int i = n + tid; i < n2; i += T) a[i] = 0ull;
+    __syncthreads();
+    for (int k = 2; k <= n2; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int p = tid; p < n2 / 2; p += T) {
+                const int i = 2 * p - (p & (j - 1));
+                const unsigned long long x = a[i], y = a[i + j];
+                const bool swap = (i & k) == 0 ? x < y : x > y;
+                if (swap) { a[i] = y; a[i + j] = x; }
+            }
+            // the next stage's stride: j / 2, or k after the last one of a k
+            if (j > 64 || (j == 1 && k > 64)) __syncthreads();
+            else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    }
+    __syncthreads();
+}
 
 #define FL_THREADS 256
 #define FL_CHUNK 512               // keys per workgroup of the scoring kernel
@@ -339,7 +368,7 @@ __device__ __forceinline__ void flat_select(FlatLds& lds, uint32_t* kh, const ui
         n = (int)s_cnt;                          // <= topk (fewer when W leaves fewer eligible keys)
     }
     // ---- order by (score descending, id ascending) = 64-bit key descending
-    if (n <= FL_SEL_T) {
+    if (n <= SORT_COUNT_MAX) {
         // few candidates (the usual case): a candidate goes where the count of larger keys says; four
         // threads count for each
         const int part = tid & 3;
@@ -354,23 +383,7 @@ __device__ __forceinline__ void flat_select(FlatLds& lds, uint32_t* kh, const ui
         for (int i = n + tid; i < topk; i += FL_SEL_T) out[i] = -1;
         return;
     }
-    int n2 = 1;
-    while (n2 < n) n2 <<= 1;
-    for (int i = n + tid; i < n2; i += FL_SEL_T) sel[i] = 0ull;
-    __syncthreads();
-    for (int k = 2; k <= n2; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = tid; i < n2; i += FL_SEL_T) {
-                const int ixj = i ^ j;
-                if (ixj > i) {
-                    const unsigned long long a = sel[i], b = sel[ixj];
-                    const bool desc = (i & k) == 0;
-                    if (desc ? (a < b) : (a > b)) { sel[i] = b; sel[ixj] = a; }
-                }
-            }
-            __syncthreads();
-        }
-    }
+    sort_descending<FL_SEL_T>(sel, n);
     for (int i = tid; i < topk; i += FL_SEL_T)
         out[i] = i < n ? (int32_t)(0xffffffffu - (uint32_t)sel[i]) : -1;
 }
@@ -383,6 +396,45 @@ __global__ __launch_bounds__(FL_SEL_T) void flat_select_kernel(uint32_t* __restr
     __shared__ FlatLds lds;
     flat_select(lds, keys + (size_t)blockIdx.x * N, tile_max + (size_t)blockIdx.x * n_tiles, n_tiles, N, topk,
                 ids_out + (size_t)blockIdx.x * topk, -1);
+}
+
+// A head's answer out of the eight lists of its slices (what the slices stored past the L2 is read the same way).
+template <int DT>
+__device__ __forceinline__ void flat_finish(FlatLds& lds, const void* q, const void* K, int head, int n_q, int n_kv, int64_t N, int s,
+                            int w, uint32_t* keys, int64_t n_tiles, int topk, const uint32_t* cand_count,
+                            int32_t* ids_out) {
+    const int tid = threadIdx.x;
+    uint32_t* kh = keys + (size_t)head * N;
+    unsigned c = 0u, bad = 0u, start[FL_SLICES + 1], cj[FL_SLICES];
+#pragma unroll
+    for (int j = 0; j < FL_SLICES; ++j) cj[j] = xwg_load(cand_count + head * FL_SLICES + j);
+#pragma unroll
+    for (int j = 0; j < FL_SLICES; ++j) {
+        bad |= cj[j] & 0x80000000u;
+        start[j] = c;
+        c += cj[j] & 0x7fffffffu;
+    }
+    start[FL_SLICES] = c;
+    int n = -1;
+    if (!bad && c >= (unsigned)topk && c <= FL_CAND) {
+        // entry i of the eight lists laid end to end (all loads in one trip)
+        for (unsigned i = tid; i < c; i += FL_SEL_T) {
+            int j = 0;
+#pragma unroll
+            for (int x = 1; x < FL_SLICES; ++x) j += i >= start[x] ? 1 : 0;
+            unsigned first = 0u;
+#pragma unroll
+            for (int x = 1; x < FL_SLICES; ++x) first = j == x ? start[x] : first;
+            const uint32_t* e = kh + (size_t)j * (N / FL_SLICES) + 2 * (size_t)(i - first);
+            const uint32_t key = xwg_load(e), id = xwg_load(e + 1);
+            lds.sel[i] = ((unsigned long long)key << 32) | (0xffffffffu - id);
+        }
+        n = (int)c;
+    } else {
+        flat_score_head<DT>(q, K, head, n_q, n_kv, N, s, w, kh);
+    }
+    __syncthreads();
+    flat_select(lds, kh, nullptr, n_tiles, N, topk, ids_out + (size_t)head * topk, n);
 }
 
 // Second pass of the scan that stores no keys. Every workgroup of a head finds T0, a tile maximum
@@ -398,7 +450,7 @@ __global__ __launch_bounds__(FL_SEL_T) void flat_select_kernel(uint32_t* __restr
 // grid: x = slice, y = head; a wavefront takes one tile at a time (a 16-lane group one run of 8 rows).
 // BIG: more tiles than fit LDS (over 256K keys): the maxima are read where they are, in device memory
 // (a few passes over at most 128 KB that the cache holds), and only the list of tiles is in LDS.
-template <int DT, bool BIG>
+template <int DT, bool BIG, bool LAST>
 __global__ __launch_bounds__(FL_SEL_T) void flat_rescore_kernel(
     const void* __restrict__ q, const void* __restrict__ K, int n_q, int n_kv, int64_t N, int s, int w,
     const uint32_t* __restrict__ tile_max, int64_t n_tiles, int topk, uint32_t* keys,
@@ -538,44 +590,24 @@ __global__ __launch_bounds__(FL_SEL_T) void flat_rescore_kernel(
         }
     }
     if (tid == 0) xwg_store(cand_count + head * FL_SLICES + slice, cnt);
+    if constexpr (!LAST) return;
     __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): this wavefront's stores have completed
     __syncthreads();                          // ... and every other's
     if (tid == 0)
         s_last = __hip_atomic_fetch_add(tickets + head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (s_last != FL_SLICES - 1) return;
-    // ---- the last of the head's workgroups: the answer out of the eight lists
-    uint32_t* kh = keys + (size_t)head * N;
-    unsigned c = 0u, bad = 0u, start[FL_SLICES + 1], cj[FL_SLICES];
-#pragma unroll
-    for (int j = 0; j < FL_SLICES; ++j) cj[j] = xwg_load(cand_count + head * FL_SLICES + j);
-#pragma unroll
-    for (int j = 0; j < FL_SLICES; ++j) {
-        bad |= cj[j] & 0x80000000u;
-        start[j] = c;
-        c += cj[j] & 0x7fffffffu;
-    }
-    start[FL_SLICES] = c;
-    int n = -1;
-    if (!bad && c >= (unsigned)topk && c <= FL_CAND) {
-        // entry i of the eight lists laid end to end (all loads in one trip)
-        for (unsigned i = tid; i < c; i += FL_SEL_T) {
-            int j = 0;
-#pragma unroll
-            for (int x = 1; x < FL_SLICES; ++x) j += i >= start[x] ? 1 : 0;
-            unsigned first = 0u;
-#pragma unroll
-            for (int x = 1; x < FL_SLICES; ++x) first = j == x ? start[x] : first;
-            const uint32_t* e = kh + (size_t)j * (N / FL_SLICES) + 2 * (size_t)(i - first);
-            const uint32_t key = xwg_load(e), id = xwg_load(e + 1);
-            lds.sel[i] = ((unsigned long long)key << 32) | (0xffffffffu - id);
-        }
-        n = (int)c;
-    } else {
-        flat_score_head<DT>(q, K, head, n_q, n_kv, N, s, w, kh);
-    }
-    __syncthreads();
-    flat_select(lds, kh, nullptr, n_tiles, N, topk, ids_out + (size_t)head * topk, n);
+    flat_finish<DT>(lds, q, K, head, n_q, n_kv, N, s, w, keys, n_tiles, topk, cand_count, ids_out);
+}
+
+// The same as a launch of its own (see ra_launch_flat_topk). grid: x = head.
+template <int DT>
+__global__ __launch_bounds__(FL_SEL_T, 8) void flat_finish_kernel(const void* __restrict__ q, const void* __restrict__ K,
+                                                               int n_q, int n_kv, int64_t N, int s, int w, uint32_t* keys,
+                                                               int64_t n_tiles, int topk, const uint32_t* cand_count,
+                                                               int32_t* __restrict__ ids_out) {
+    __shared__ FlatLds lds;
+    flat_finish<DT>(lds, q, K, (int)blockIdx.x, n_q, n_kv, N, s, w, keys, n_tiles, topk, cand_count, ids_out);
 }
 
 // Re-ranking of a candidate list with the keys themselves (what follows a walk over 8-bit keys):
@@ -586,7 +618,7 @@ __global__ __launch_bounds__(FL_SEL_T) void flat_rescore_kernel(
 // (200 candidates of 32 heads: 10.9 -> 6.2 us).
 #define RR_THREADS 1024
 #define RR_ROWS 4                  // key rows in flight per 16-lane group
-#define RR_COUNT 4                 // threads that count for one candidate
+#define RR_COUNT 4                 // threads that count for one candidate of a short list
 template <int DT>
 __global__ __launch_bounds__(RR_THREADS) void rerank_kernel(const void* __restrict__ q,
                                                             const void* __restrict__ K, int n_q, int n_kv,
@@ -630,6 +662,11 @@ __global__ __launch_bounds__(RR_THREADS) void rerank_kernel(const void* __restri
     }
     __syncthreads();
     const int nv = n_valid;
+    if (n_cand > SORT_COUNT_MAX) {
+        sort_descending<RR_THREADS>(keys, n_cand);
+        for (int i = tid; i < topk; i += RR_THREADS) out[i] = i < nv ? (int32_t)(0xffffffffu - (uint32_t)keys[i]) : -1;
+        return;
+    }
     const int part = tid % RR_COUNT;
     for (int c = tid / RR_COUNT; c < n_cand; c += RR_THREADS / RR_COUNT) {
         const unsigned long long k = keys[c];
@@ -673,6 +710,10 @@ ra_status ra_launch_flat_topk(const void* q, const void* K, ra_dtype dt, int n_s
     // (pairs a slice can hold: its eighth of the key area, and what its workgroup keeps in LDS)
     const int cand_cap = (int)(N / FL_SLICES / 2 < FL_SLICE_CAND ? N / FL_SLICES / 2 : FL_SLICE_CAND);
     const bool two_pass = n_tiles >= 2 * (int64_t)topk && n_tiles <= 4 * FL_TILES_MAX && cand_cap >= 64;
+    // Up to so many heads (a workgroup of the second pass per compute unit) the last workgroup of a head orders
+    // its candidates. That part takes registers that leave one workgroup per compute unit instead of two,
+    // so with more heads it is a launch of its own (64 heads of 20000 keys: 37 us against 31).
+    const bool last = heads <= 32;
     const bool big = n_tiles > FL_TILES_MAX;                     // (tile numbers stay below 2^16 in the lists)
     const dim3 grid((unsigned)((N + FL_CHUNK - 1) / FL_CHUNK), n_kv, n_seq);
     // any other group size than 1, 2, 4, 8: one grid row per query head, every head scans its keys itself
@@ -686,6 +727,10 @@ ra_status ra_launch_flat_topk(const void* q, const void* K, ra_dtype dt, int n_s
             hipLaunchKernelGGL((flat_scores_kernel<DTV, GG, true>), GRID, dim3(FL_THREADS), 0, st, q, K, n_q,   \
                                n_kv, N, (int)ss, (int)ww, keys_ws, tile_max, n_tiles, DIV, tickets);                   \
     } while (0)
+#define RA_FL_RESCORE(DTV, BIGV, LASTV)                                                                       \
+    hipLaunchKernelGGL((flat_rescore_kernel<DTV, BIGV, LASTV>), dim3(FL_SLICES, heads), dim3(FL_SEL_T), 0, st, q, K, \
+                       n_q, n_kv, N, (int)ss, (int)ww, tile_max, n_tiles, topk, keys_ws, cand_count, cand_cap,  \
+                       tickets, ids)
 #define RA_FL_DT(DTV)                                                                                         \
     do {                                                                                                      \
         switch (G) {                                                                                          \
@@ -697,21 +742,21 @@ ra_status ra_launch_flat_topk(const void* q, const void* K, ra_dtype dt, int n_s
         }                                                                                                     \
         RA_HIP(hipGetLastError());                                                                            \
         if (two_pass && big) {                                                                                \
-            hipLaunchKernelGGL((flat_rescore_kernel<DTV, true>), dim3(FL_SLICES, heads), dim3(FL_SEL_T), 0, st, \
-                               q, K, n_q, n_kv, N, (int)ss, (int)ww, tile_max, n_tiles, topk, keys_ws,        \
-                               cand_count, cand_cap, tickets, ids);                                                         \
+            if (last) RA_FL_RESCORE(DTV, true, true); else RA_FL_RESCORE(DTV, true, false);                   \
         } else if (two_pass) {                                                                                \
-            hipLaunchKernelGGL((flat_rescore_kernel<DTV, false>), dim3(FL_SLICES, heads), dim3(FL_SEL_T), 0, st, \
-                               q, K, n_q, n_kv, N, (int)ss, (int)ww, tile_max, n_tiles, topk, keys_ws,        \
-                               cand_count, cand_cap, tickets, ids);                                                         \
-            RA_HIP(hipGetLastError());                                                                        \
+            if (last) RA_FL_RESCORE(DTV, false, true); else RA_FL_RESCORE(DTV, false, false);                 \
         }                                                                                                     \
+        RA_HIP(hipGetLastError());                                                                            \
+        if (two_pass && !last)                                                                                \
+            hipLaunchKernelGGL((flat_finish_kernel<DTV>), dim3(heads), dim3(FL_SEL_T), 0, st, q, K, n_q, n_kv, N,  \
+                               (int)ss, (int)ww, keys_ws, n_tiles, topk, cand_count, ids);                    \
         if (!two_pass)                                                                                        \
             hipLaunchKernelGGL(flat_select_kernel, dim3(heads), dim3(FL_SEL_T), 0, st, keys_ws, tile_max, n_tiles, \
                                N, topk, ids);                                                                 \
     } while (0)
     if (dt == RA_BF16) RA_FL_DT(RA_BF16); else RA_FL_DT(RA_F32);
 #undef RA_FL_DT
+#undef RA_FL_RESCORE
 #undef RA_FL_GO
     RA_HIP(hipGetLastError());
     return RA_OK;

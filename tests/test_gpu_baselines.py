@@ -215,3 +215,34 @@ def test_gather_probe_reads_the_hashed_rows(rows_in_buf, n_rows, seed):
     assert int(out.cpu().numpy().view(np.uint64)[0]) == _fold16(host.reshape(rows_in_buf, 64)[rows])
     with pytest.raises(ra.RaError):
         ra.ra_hbm_gather_probe(buf, 0, out)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n_seq,n_q,n_kv,topk", [(1, 32, 4, 300), (1, 33, 33, 20), (9, 8, 1, 257)])
+def test_flat_topk_where_the_order_of_candidates_is_found(n_seq, n_q, n_kv, topk, dtype):
+    """Up to 32 heads and more, candidates that are counted and ones that are sorted: exact, integer scores."""
+    w = synth.make_integer_case(8, N=20011, M=4, T=1, d=128, n_q=n_q, n_kv=n_kv, dtype=dtype, sink=3, window=10)
+    K = w.K.expand(n_seq, *w.K.shape[1:]).contiguous()
+    q = w.q_decode[0].expand(n_seq, n_q, 128).contiguous().clone()
+    for s in range(n_seq):
+        q[s] = torch.roll(q[s], s, dims=-1)
+    ids = ra.ra_flat_topk(q.to(DEV), K.to(DEV), w.sink, w.window, topk).cpu().numpy()
+    W = OA.static_ids(20011, w.sink, w.window)
+    for s in range(n_seq):
+        for h in range(0, n_q, 5):
+            ref = OM.topk_bruteforce(to_np(q[s, h]), to_np(K[s, h // (n_q // n_kv)]), topk, exclude=W)
+            assert ids[s, h].tolist() == ref.tolist(), (s, h)
+
+
+@pytest.mark.parametrize("n_cand,topk", [(256, 256), (257, 100), (1000, 1000), (2048, 7)])
+def test_rerank_of_long_lists(n_cand, topk):
+    """The longest list whose order is counted, sorted ones, a full array, and holes in the list."""
+    w = synth.make_integer_case(9, N=5000, M=4, T=1, d=128, n_q=2, n_kv=1, dtype=torch.bfloat16)
+    g = torch.Generator().manual_seed(n_cand)
+    cand = torch.stack([torch.randperm(5000, generator=g)[:n_cand] for _ in range(2)]).view(1, 2, n_cand).int()
+    cand[0, 1, 3::5] = -1
+    ids = ra.ra_rerank(w.q_decode[0].to(DEV), w.K.to(DEV), cand.to(DEV), topk).cpu().numpy()
+    for h in range(2):
+        want = OM.rerank(to_np(w.q_decode[0, 0, h]), to_np(w.K[0, 0]), cand[0, h].numpy(), topk)
+        want = np.pad(want, (0, topk - len(want)), constant_values=-1)
+        assert ids[0, h].tolist() == want.tolist(), h
