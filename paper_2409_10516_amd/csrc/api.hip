@@ -461,7 +461,7 @@ extern "C" ra_status ra_attend(const void* q, const ra_index* idx, const void* K
     RA_TRY(check_decode_args(idx, N, sink, window, topk));
     ra_index* ix = const_cast<ra_index*>(idx);
     const size_t need =
-        ra_attend_partial_floats(ix->n_seq, ix->n_q, ix->n_kv, N, sink, window, topk) * sizeof(float);
+        ra_attend_partial_floats(dt, ix->n_seq, ix->n_q, ix->n_kv, N, sink, window, topk) * sizeof(float);
     RA_TRY(grow((void**)&ix->partials, &ix->partials_bytes, need));
     return ra_launch_attend(q, K, V, dt, ix->n_seq, ix->n_q, ix->n_kv, N, sink, window, topk, ids,
                             ix->partials, attend_tickets(ix), (hipStream_t)stream, out, lse, o_omega,
@@ -618,8 +618,10 @@ extern "C" size_t ra_full_attention_workspace_bytes(int n_seq, int n_q_heads, in
                                                      int64_t N) {
     if (n_seq < 1 || n_q_heads < 1 || n_kv_heads < 1 || N < 1) return 0;
     // partial records of a fully static context
-    return 256 + ra_attend_partial_floats(n_seq, n_q_heads, n_kv_heads, N, (int)(N > 0x7fffffff ? 0x7fffffff : N),
-                                    0, 1) * sizeof(float);
+    const int rows = (int)(N > 0x7fffffff ? 0x7fffffff : N);
+    const size_t b = ra_attend_partial_floats(RA_BF16, n_seq, n_q_heads, n_kv_heads, N, rows, 0, 1);
+    const size_t f = ra_attend_partial_floats(RA_F32, n_seq, n_q_heads, n_kv_heads, N, rows, 0, 1);
+    return 256 + (b > f ? b : f) * sizeof(float);
 }
 
 extern "C" ra_status ra_full_attention(const void* q, const void* K, const void* V, ra_dtype dt,

@@ -32,10 +32,8 @@ struct AttendOut {
     float *out, *lse, *o_om, *lse_om, *o_w, *lse_w;
 };
 
-// grid: x = record slot (nS static chunks, then G x nG gathered chunks), y = KV head, z = seq.
-// With kv_div > 1 the kernel runs as G = 1 with one grid row per query head, kv_div of which share a KV
-// head (GQA groups of another size than the kernel is built for, and small launches: see
-// ra_launch_attend).
+// grid: x = record slot (nS static chunks, then G x nG gathered chunks), y = G query heads, z = seq.
+// kv_div consecutive grid rows share a KV head (a GQA group of more heads than a workgroup takes).
 // TICKETS: whoever writes a head's last record combines them all: a workgroup stores its records past the
 // L2, waits for the stores, and takes a ticket of each of its heads; the one that gets the last ticket
 // reads the P records back the same way. That saves a launch (4 us of 13.5 us for the decode step's sets).
@@ -120,34 +118,54 @@ __global__ __launch_bounds__(AT_MERGE_SLICES * RA_D) void attend_merge_kernel(
 
 // Static chunks: 64 rows each for the decode step's few hundred static rows; a long static range (full
 // attention) is cut so that its workgroups are about two per compute unit (the kernel's vector
-// registers allow two side by side), all running from start to end. Measured for full attention
-// over 131072 tokens, 8 KV heads (us per layer): 32 records per head 178, 64 records 115, 128 records 123,
-// 256 records 136; with the number of sub-chunks rounded up to a power of two a context of 100003
-// tokens had 392 workgroups on 512 places (88 us; 74 us with 504).
+// registers allow two side by side; one for the float32 kernel of eight heads), all running from start
+// to end. Measured for full attention over 131072 tokens, 8 KV heads (us per layer): 32 records per
+// head 178, 64 records 115, 128 records 123, 256 records 136; with the number of sub-chunks rounded up to
+// a power of two a context of 100003 tokens had 392 workgroups on 512 places (88 us; 74 us with 504).
 #define AT_MAX_STATIC_CHUNKS 64     // most chunks of 64 rows that get a record each
-#define AT_LONG_WORKGROUPS 512
-static int static_sub(int rows, int kv_heads) {
+
+// Query heads that one workgroup of a long static range serves, of a group of G. bf16 goes through the
+// matrix cores, which the kernel does for up to four heads: a group of eight takes two workgroups, which
+// find each other's rows in the L2 (131072 tokens, 32 heads on 4: 110 us with eight heads on the vector
+// units, 81 us); float32 is bound by the loads (180 us with four heads, 145 us with eight).
+static int long_heads(ra_dtype dt, int G) { return G == 2 || G == 4 ? G : G == 8 ? (dt == RA_BF16 ? 4 : 8) : 1; }
+
+// The same for the decode step's sets, in a launch of `records` records. A launch of few workgroups is
+// bound by its latency, and a static chunk for g heads takes g times the arithmetic and closes g
+// records one after the other: every query head reads its static rows itself then (the heads of a
+// group find them in the L2). Beyond, bf16 takes two heads (32 heads on 8, 16 sequences, 640 static rows
+// and 100 more: 31 us; four heads 38, one 35; 32 on 4: 31 against 59 us with eight), float32 as many as
+// its wider rows make worth while (same sizes: 42.7 us with four heads, 44.8 with two, 60 with one).
+static int short_heads(ra_dtype dt, int G, int64_t records) {
+    if (G != 2 && G != 4 && G != 8) return 1;
+    if (records <= (dt == RA_BF16 ? 512 * G : 32 * G * G)) return 1;
+    if (dt == RA_BF16 || G == 2) return 2;
+    return G == 4 && records <= 1024 ? 2 : 4;
+}
+
+static int static_sub(ra_dtype dt, int rows, int n_seq, int n_q, int n_kv) {
     const int chunks = (rows + AT_CH - 1) / AT_CH;
     if (chunks <= AT_MAX_STATIC_CHUNKS) return 1;
-    int records = AT_LONG_WORKGROUPS / kv_heads;
+    const int g = long_heads(dt, n_q / n_kv);
+    int records = (g == 8 ? 256 : 512) / (n_seq * n_q / g);
     if (records < 4) records = 4;
     if (records > chunks / 2) records = chunks / 2;
     return (chunks + records - 1) / records;
 }
 
-size_t ra_attend_partial_floats(int n_seq, int n_q, int n_kv, int64_t N, int sink, int window,
+size_t ra_attend_partial_floats(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int sink, int window,
                                 int topk) {
     int s, w;
     static_ranges(N, sink, window, &s, &w);
-    const int sub = static_sub(s + w, n_seq * n_kv);
+    const int sub = static_sub(dt, s + w, n_seq, n_q, n_kv);
     const int nS = (s + w + AT_CH * sub - 1) / (AT_CH * sub), nG = (topk + AT_CH - 1) / AT_CH;
     return (size_t)n_seq * n_q * (nS + nG) * AT_RS;
 }
 
-// A launch of few workgroups is bound by its latency, and a static chunk for four heads takes four times
-// the arithmetic and closes four records one after the other: up to this many workgroups every query
-// head reads its static rows itself (the four of a group find them in the L2).
-#define AT_SPLIT_WORKGROUPS 1024
+// Up to so many records the last workgroup of a head combines them (13 records of 32 heads: 12.4 -> 10.3 us).
+// Storing records past the L2 and taking tickets costs each workgroup more than a launch costs all
+// of them when there are many: 2900 records took twice as long that way.
+#define AT_TICKET_RECORDS 512
 
 ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype dt, int n_seq,
                            int n_q, int n_kv, int64_t N, int sink, int window, int topk,
@@ -157,14 +175,15 @@ ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype
     int s, w;
     static_ranges(N, sink, window, &s, &w);
     const int G = n_q / n_kv;
-    const int sub = static_sub(s + w, n_seq * n_kv);
+    const int sub = static_sub(dt, s + w, n_seq, n_q, n_kv);
     const int nS = (s + w + AT_CH * sub - 1) / (AT_CH * sub), nG = ids ? (topk + AT_CH - 1) / AT_CH : 0;
     const float scale = 1.0f / sqrtf((float)RA_D);
     const size_t lds = (size_t)AT_TEAM_LDS_FLOATS * sizeof(float);
+    const int64_t records = (int64_t)(nS + nG) * n_q * n_seq;
+    if (records > AT_TICKET_RECORDS) tickets = nullptr;
     const AttendOut o{tickets, out, lse, o_omega, lse_omega, o_w, lse_w};
-    const bool grouped = (G == 1 || G == 2 || G == 4 || G == 8) &&
-                         (G == 1 || sub > 1 || (int64_t)(nS + nG) * n_q * n_seq > AT_SPLIT_WORKGROUPS);
-    const dim3 grid = grouped ? dim3(nS + G * nG, n_kv, n_seq) : dim3(nS + nG, n_q, n_seq);
+    const int g = sub > 1 ? long_heads(dt, G) : short_heads(dt, G, records);
+    const dim3 grid(nS + g * nG, n_q / g, n_seq);
     if (nS + nG > 0) {
 #define RA_AT_GO(DTV, GG, TK, DIV)                                                                                \
     hipLaunchKernelGGL((attend_partial_kernel<DTV, GG, TK>), grid, dim3(AT_THREADS), lds, st, q, K, V, ids, partials, \
@@ -173,10 +192,9 @@ ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype
     do { if (tickets) RA_AT_GO(DTV, GG, true, DIV); else RA_AT_GO(DTV, GG, false, DIV); } while (0)
 #define RA_AT_DT(DTV)                                                                                             \
     do {                                                                                                          \
-        if (!grouped) RA_AT_TK(DTV, 1, G);          /* every query head reads its rows itself */                  \
-        else if (G == 1) RA_AT_TK(DTV, 1, 1);                                                                     \
-        else if (G == 2) RA_AT_TK(DTV, 2, 1);                                                                     \
-        else if (G == 4) RA_AT_TK(DTV, 4, 1);                                                                     \
+        if (g == 1) RA_AT_TK(DTV, 1, G);                                                                          \
+        else if (g == 2) RA_AT_TK(DTV, 2, G / 2);                                                                 \
+        else if (g == 4) RA_AT_TK(DTV, 4, G / 4);                                                                 \
         else RA_AT_TK(DTV, 8, 1);                                                                                 \
     } while (0)
         if (dt == RA_BF16) RA_AT_DT(RA_BF16); else RA_AT_DT(RA_F32);
@@ -229,7 +247,7 @@ ra_status ra_launch_attend_noalloc(const void* q, const void* K, const void* V, 
                                    int n_q, int n_kv, int64_t N, int sink, int window, int topk,
                                    const int32_t* ids, hipStream_t st, float* out, float* lse,
                                    float* o_omega, float* lse_omega, float* o_w, float* lse_w) {
-    const size_t need = ra_attend_partial_floats(n_seq, n_q, n_kv, N, sink, window, topk) * sizeof(float);
+    const size_t need = ra_attend_partial_floats(dt, n_seq, n_q, n_kv, N, sink, window, topk) * sizeof(float);
     if (need > RA_ATTEND_NOALLOC_SCRATCH_BYTES)
         RA_FAIL(RA_EUNSUP, "the partial records of this call take %zu bytes, above the %u bytes "
                 "ra_attend_noalloc keeps (use ra_attend)", need, (unsigned)RA_ATTEND_NOALLOC_SCRATCH_BYTES);

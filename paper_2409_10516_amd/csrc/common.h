@@ -109,7 +109,7 @@ ra_status ra_launch_seeds(const int32_t* adj, const int32_t* entry, int heads, i
 size_t ra_search_lds_bytes(int64_t N, int deg, int ef, int expand, bool global_bitset);
 bool ra_search_needs_global_bitset(int64_t N, int deg, int ef, int expand);
 
-size_t ra_attend_partial_floats(int n_seq, int n_q, int n_kv, int64_t N, int sink, int window,
+size_t ra_attend_partial_floats(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int sink, int window,
                                 int topk);
 ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype dt, int n_seq,
                            int n_q, int n_kv, int64_t N, int sink, int window, int topk,

@@ -246,3 +246,30 @@ def test_rerank_of_long_lists(n_cand, topk):
         want = OM.rerank(to_np(w.q_decode[0, 0, h]), to_np(w.K[0, 0]), cand[0, h].numpy(), topk)
         want = np.pad(want, (0, topk - len(want)), constant_values=-1)
         assert ids[0, h].tolist() == want.tolist(), h
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n_seq,n_q,n_kv,window,topk", [(1, 8, 2, 60, 9), (2, 32, 8, 500, 64), (4, 32, 8, 1000, 70),
+                                                        (3, 32, 4, 200, 65), (20, 32, 4, 640, 100), (2, 16, 2, 5000, 40)])
+def test_attend_in_small_and_large_launches(n_seq, n_q, n_kv, window, topk, dtype):
+    """Every number of query heads per workgroup and both ways of combining the records, twice in a row
+    (what one call leaves behind is the next one's start), against the oracle in float64."""
+    N = 6000
+    g = torch.Generator().manual_seed(n_seq)
+    K, V = (torch.randn(n_seq, n_kv, N, 128, generator=g).to(dtype) for _ in range(2))
+    q = torch.randn(n_seq, n_q, 128, generator=g).to(dtype)
+    ids = torch.stack([4 + torch.randperm(N - window - 8, generator=g)[:topk] for _ in range(n_seq * n_q)])
+    ids = ids.view(n_seq, n_q, topk).int()
+    idx = ra.ra_index_import(torch.full((n_seq * n_q, N, 1), -1, dtype=torch.int32),
+                             torch.zeros(n_seq * n_q, dtype=torch.int32), n_seq, n_q, n_kv)
+    for _ in range(2):
+        out, lse = ra.ra_attend(q.to(DEV), idx, K.to(DEV), V.to(DEV), 4, window, ids.to(DEV))
+    W = OA.static_ids(N, 4, window)
+    for s, h in [(0, 0), (0, n_q - 1), (n_seq - 1, 1), (n_seq - 1, n_q - 2)]:
+        rows = np.concatenate([W, ids[s, h].numpy()])
+        Kh, Vh = to_np(K[s, h // (n_q // n_kv)])[rows], to_np(V[s, h // (n_q // n_kv)])[rows]
+        z = Kh @ to_np(q[s, h]) / np.sqrt(128.0)
+        p = np.exp(z - z.max())
+        np.testing.assert_allclose(out[s, h].cpu().numpy(), p @ Vh / p.sum(), rtol=2e-4, atol=2e-5)
+        assert abs(float(lse[s, h]) - (z.max() + np.log(p.sum()))) < 2e-5 * (1 + abs(z.max()))
+    idx.free()
