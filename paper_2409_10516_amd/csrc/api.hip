@@ -102,14 +102,14 @@ static ra_status grow(void** p, size_t* have, size_t need) {
     return RA_OK;
 }
 
-// records, ready words and the "helpers off" word of the fused decode kernel's hand-over area
+// records and the "helpers off" word of the fused decode kernel's hand-over area, and ra_attend's tickets
 static size_t coop_bytes(const ra_index* ix) {
     const size_t heads = (size_t)ix->n_seq * ix->n_q;
-    return heads * RA_COOP_REC * sizeof(float) + (2 * heads + 1) * sizeof(uint32_t);
+    return heads * RA_COOP_REC * sizeof(*ix->coop) + (heads + 1) * sizeof(uint32_t);
 }
 static uint32_t* attend_tickets(const ra_index* ix) {
     const size_t heads = (size_t)ix->n_seq * ix->n_q;
-    return reinterpret_cast<uint32_t*>(ix->coop + heads * RA_COOP_REC) + heads + 1;
+    return reinterpret_cast<uint32_t*>(ix->coop + heads * RA_COOP_REC) + 1;
 }
 
 static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra_index** out) {
@@ -162,7 +162,7 @@ extern "C" ra_status ra_index_configure(ra_index* ix, int what, int64_t value) {
         case RA_CFG_HELPERS: {
             if (value != RA_HELPERS_OFF && value != RA_HELPERS_ON)
                 RA_FAIL(RA_EINVAL, "helpers mode %lld", (long long)value);
-            // also forgets a wait that ran out: ready words and the off word start from zero
+            // also forgets a wait that ran out: records and the off word start from zero
             RA_HIP(hipDeviceSynchronize());
             RA_HIP(hipMemset(ix->coop, 0, coop_bytes(ix)));
             if (ix->seedx) RA_HIP(hipMemset(ix->seedx, 0, ix->seedx_bytes));
@@ -254,9 +254,7 @@ extern "C" int64_t ra_index_info(const ra_index* ix, int what) {
             const size_t heads = (size_t)ix->n_seq * ix->n_q;
             uint32_t off = 1u;
             if (hipDeviceSynchronize() != hipSuccess ||
-                hipMemcpy(&off, reinterpret_cast<const char*>(ix->coop) + heads * RA_COOP_REC * sizeof(float) +
-                                    heads * sizeof(uint32_t),
-                          sizeof(off), hipMemcpyDeviceToHost) != hipSuccess)
+                hipMemcpy(&off, ix->coop + heads * RA_COOP_REC, sizeof(off), hipMemcpyDeviceToHost) != hipSuccess)
                 return -1;
             return off == 0u;
         }

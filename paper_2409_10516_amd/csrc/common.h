@@ -61,13 +61,13 @@ struct ra_index {
     size_t ids_bytes;
     uint32_t* bitset;   // global visited bitsets for contexts too long for LDS
     size_t bitset_bytes;
-    // hand-over area of the fused decode kernel: per head a record (RA_COOP_REC floats: max, sum,
-    // 2 unused, 128 weighted sums) that a helper workgroup fills with the attention over the
-    // static set, then per head a ready word, then one "helpers off" word, then per head a ticket of
-    // ra_attend's combination (see attend.hip)
-    float* coop;
+    // hand-over area of the fused decode kernel: per head a record of RA_COOP_REC 64-bit words (max, sum,
+    // 128 weighted sums; the value's bits, and 1 in the upper half) that a helper workgroup fills with the
+    // attention over the static set and that is zero between launches, then one "helpers off" word,
+    // then per head a ticket of ra_attend's combination (see attend.hip)
+    unsigned long long* coop;
     int coop_mode;      // RA_HELPERS_*
-    int coop_spin;      // polls of the ready word before a head gives up on its helper
+    int coop_spin;      // polls of a record's words before a head gives up on its helper
     int coop_silent;    // test-only (RA_TEST_HELPERS_SILENT): helpers are launched but write nothing
     // seed sets (RA_CFG_SEEDS): [n_seq*n_q][seed_cap] in the layout of the root sets, or null
     int32_t* seeds;
@@ -83,7 +83,7 @@ struct ra_index {
     size_t graph_bytes;
 };
 
-#define RA_COOP_REC 132
+#define RA_COOP_REC 130
 #define RA_SEED_PARTS_MAX 8    /* most shares a head's start set is scored in */
 #ifndef RA_SEED_PARTS_DEFAULT
 #define RA_SEED_PARTS_DEFAULT 6
@@ -126,7 +126,7 @@ bool ra_decode_needs_global_bitset(int64_t N, int deg, int ef, int expand, int t
 ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* entry, const void* K,
                            const void* V, ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t Ng, int64_t N,
                            int64_t kv_stride, int deg, int sink, int window, int topk, int ef, int expand,
-                           uint32_t* bitset, float* coop, int coop_mode, int coop_spin,
+                           uint32_t* bitset, unsigned long long* coop, int coop_mode, int coop_spin,
                            const int32_t* roots, int root_cap, const void* K8, const float* kscale,
                            const int32_t* budgets, uint32_t* seedx, int seed_parts, hipStream_t st,
                            float* out, float* lse, int32_t* ids, ra_stats* stats);

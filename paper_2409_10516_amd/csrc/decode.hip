@@ -20,12 +20,11 @@
 // has one L2 per XCD, so those fences write back and invalidate L2, about 18 us per launch, more
 // than the whole attention. Instead the few words that cross workgroups are written and read with
 // relaxed agent-scope atomics, which go around the non-coherent cache levels on their own: the
-// helper stores its records, waits until the stores have completed (s_waitcnt vmcnt(0), barrier),
-// then stores the ready word; the head polls the ready word, then loads the record, then clears
-// the ready word for the next launch. The wait is bounded: a head that does not see its ready word
-// within the limit attends to W itself (the same code that runs when helpers are off) and turns
-// the helpers off for later launches, so a ready word that arrives late is never taken for the
-// next launch's. Query heads of a GQA group still run on one XCD (xcd_aware_head) so that the key
+// helper stores its record in 64-bit words that say themselves whether they have come (a float and a
+// 1), and the head polls them, then zeroes them for the next launch: no order between different words
+// is needed. The wait is bounded: a head that does not see its record within the limit attends to W
+// itself and turns the helpers off for later launches, so words that arrive late are never taken for
+// the next launch's. Query heads of a GQA group still run on one XCD (xcd_aware_head) so that the key
 // rows their searches have in common are served by that XCD's L2.
 //
 // A walk that starts from a seed set first scores the whole set, and what bounds that is the rate
@@ -124,6 +123,18 @@ template <> struct LaneQuery<RA_F32> {
     }
 };
 
+// x of lane ^ 16 or lane ^ 32, by the vector unit's row and half exchanges (a shuffle is a trip through LDS:
+// the twenty of a combination were a sixth of the attention over 100 rows).
+__device__ __forceinline__ float lane_xor_rows(float x, int d, int lane) {
+    const unsigned v = __float_as_uint(x);
+    if (d == 16) {
+        const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return __uint_as_float((lane & 16) ? p[0] : p[1]);
+    }
+    const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return __uint_as_float((lane & 32) ? p[0] : p[1]);
+}
+
 // Combine the online-softmax states of the lane groups of a workgroup of T threads into one (max,
 // sum, weighted sum for output `tid`), valid in threads tid < 128 (T >= 128): first the four
 // groups of each wavefront by lane exchange, then the T/64 wavefronts through LDS (T/64 * 130
@@ -133,10 +144,10 @@ __device__ __forceinline__ void sm_combine(Softmax8 st, float* lds, int tid, flo
     const int lane = tid & (RA_WAVE - 1), wv = tid / RA_WAVE;
 #pragma unroll
     for (int d = 16; d <= 32; d <<= 1) {
-        const float mo = __shfl_xor(st.m, d), lo = __shfl_xor(st.l, d);
+        const float mo = lane_xor_rows(st.m, d, lane), lo = lane_xor_rows(st.l, d, lane);
         float ao[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ao[e] = __shfl_xor(st.acc[e], d);
+        for (int e = 0; e < 8; ++e) ao[e] = lane_xor_rows(st.acc[e], d, lane);
         sm_merge(st, mo, lo, ao);
     }
     float* sm = lds;                                         // [16]
@@ -159,9 +170,11 @@ __device__ __forceinline__ void sm_combine(Softmax8 st, float* lds, int tid, flo
 #pragma unroll
         for (int j = 0; j < T / RA_WAVE; ++j) mx = fmaxf(mx, sm[j]);
         if (mx > -INFINITY) {
+            // (a lane works out the weight of one wavefront's share; each weight is then read from its lane)
+            const float own = expf(sm[lane & (T / RA_WAVE - 1)] - mx);
 #pragma unroll
             for (int j = 0; j < T / RA_WAVE; ++j) {
-                const float wgt = expf(sm[j] - mx);
+                const float wgt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own), j));
                 a = fmaf(sa[j * RA_D + tid], wgt, a);
                 l = fmaf(sl[j], wgt, l);
             }
@@ -169,12 +182,17 @@ __device__ __forceinline__ void sm_combine(Softmax8 st, float* lds, int tid, flo
     }
 }
 
+// A word of a helper's record: a float's bits, and in the upper half a 1 that says it has come.
+__device__ __forceinline__ u64 rec_word(float v) { return (1ull << 32) | __float_as_uint(v); }
+__device__ __forceinline__ bool rec_came(u64 w) { return (w >> 32) != 0ull; }
+__device__ __forceinline__ float rec_value(u64 w) { return __uint_as_float((uint32_t)w); }
+
 // Helper workgroup: Eq. 2 over W for NH query heads that share one KV head (heads head0 ..
-// head0 + NH - 1), each row of W read once; leaves one record per head and then its ready word.
+// head0 + NH - 1), each row of W read once; leaves one record per head.
 template <int DT, int NH, int T>
 __device__ __forceinline__ void static_helper(unsigned char* lds_raw, const void* q, int head0, const char* Kh,
                                               const char* Vh, int s, int64_t wstart, int64_t N, float scale,
-                                              float* rec, uint32_t* ready) {
+                                              u64* rec, bool off) {
     const int tid = threadIdx.x, grp = tid >> 4, lane16 = tid & 15;
     const size_t esz = DT == RA_BF16 ? 2 : 4;
     constexpr int ROWS = DT == RA_BF16 ? 4 : 2;              // rows in flight per 16-lane group
@@ -220,36 +238,28 @@ __device__ __forceinline__ void static_helper(unsigned char* lds_raw, const void
     for (int h = 0; h < NH; ++h) {
         float mx, l, a;
         sm_combine<T>(st[h], reinterpret_cast<float*>(lds_raw), tid, mx, l, a);
-        if (tid < RA_D) {
-            float* r = rec + (size_t)(head0 + h) * RA_COOP_REC;
+        if (tid < RA_D && !off) {
+            u64* r = rec + (size_t)(head0 + h) * RA_COOP_REC;
             if (tid == 0) {
-                xwg_store(r, mx);
-                xwg_store(r + 1, l);
+                xwg_store(r, rec_word(mx));
+                xwg_store(r + 1, rec_word(l));
             }
-            xwg_store(r + 4 + tid, a);
+            xwg_store(r + 2 + tid, rec_word(a));
         }
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): this wavefront's record stores have completed
-    __syncthreads();                          // ... and every other wavefront's
-    if (tid < NH) xwg_store(ready + head0 + tid, 1u);
 }
 
-// The head's wait for its helper, run while the search writes its result (see NoHook): one thread
-// of the second wavefront polls the ready word, a bounded number of times, and leaves in LDS
-// whether it came; if it did not, helpers are turned off for later launches.
-struct AwaitHelper {
-    const uint32_t* ready_word;
-    uint32_t* off_word;
-    uint32_t* lds_word;
+// What the walk asks of the fused launch (see NoHook): the keys of its start set, scored by other workgroups.
+struct SeedHook {
     int spin;
-    bool on;
     // this head's keys in the seed hand-over area, the area's "shares off" word, whether the launch
     // has seed workgroups
     u64* seed_keys;
     uint32_t* seed_off;
     bool seed_on;
+    uint32_t seed_is_off;
     static constexpr bool kSeedShare = true;
-    __device__ __forceinline__ bool seeds_shared() const { return seed_on; }
+    __device__ __forceinline__ bool seeds_shared() const { return seed_on && seed_is_off == 0u; }
     // Keys c0 and c1 of the head's start set (c1 < 0: only c0, and k1 = k0), polled together a bounded
     // number of times, the slots zeroed for the next launch once the keys are taken; a key that did
     // not come reads 0. A poll is a trip to memory (agent-scope loads go around the caches); more
@@ -271,17 +281,6 @@ struct AwaitHelper {
     // a key did not come: later launches score in the head again, so that keys that arrive late
     // are never taken for a later launch's
     __device__ __forceinline__ void seeds_missed() const { xwg_store(seed_off, 1u); }
-    __device__ __forceinline__ void before_output() const {
-        if (!on || threadIdx.x != RA_WAVE) return;
-        uint32_t f = 0u;
-        for (int i = 0; i < spin; ++i) {
-            f = xwg_load(ready_word);
-            if (f) break;
-            __builtin_amdgcn_s_sleep(32);
-        }
-        if (!f) xwg_store(off_word, 1u);
-        *lds_word = f;
-    }
 };
 
 // BUDGETS: every head keeps its own number of ids (budgets[head]) instead of topk. A variant of
@@ -294,7 +293,7 @@ __global__ __launch_bounds__(T) void decode_kernel(
     int64_t kv_stride, int64_t wstart, int deg, int s, int topk, int ef, int expand,
     uint32_t* __restrict__ gbits,
     int32_t* __restrict__ ids, ra_stats* __restrict__ stats, int ids_off, float scale,
-    float* __restrict__ out, float* __restrict__ lse, float* coop, int n_helpers, int coop_mode,
+    float* __restrict__ out, float* __restrict__ lse, u64* coop, int n_helpers, int coop_mode,
     int coop_spin, const int32_t* __restrict__ roots, int root_cap, const void* __restrict__ Ksearch,
     const float* __restrict__ kscale, const int32_t* __restrict__ budgets, uint32_t* seedx, int seed_parts,
     int seed_stride, int helper_heads) {
@@ -303,12 +302,16 @@ __global__ __launch_bounds__(T) void decode_kernel(
     const size_t esz = DT == RA_BF16 ? 2 : 4;
     const int G = n_q / n_kv;
     const int n_heads = ((int)gridDim.x - n_helpers) / (1 + seed_parts);
-    // hand-over area: records, ready words, "helpers off" word (set by a head whose wait ran out)
-    uint32_t* ready = reinterpret_cast<uint32_t*>(coop + (size_t)n_heads * RA_COOP_REC);
-    const bool helpers = n_helpers > 0 && xwg_load(ready + n_heads) == 0u;
+    // hand-over area: records, "helpers off" word (set by a head whose wait ran out); seed hand-over area: [0]
+    // the "shares off" word, then (from byte RA_SEEDX_KEYS_OFF) seed_stride 64-bit keys per head, zero
+    // between launches. Both words are asked for here, together, and looked at where they are needed: a
+    // trip past the caches is a microsecond.
+    uint32_t* helpers_off_word = reinterpret_cast<uint32_t*>(coop + (size_t)n_heads * RA_COOP_REC);
+    const uint32_t helpers_off = xwg_load(helpers_off_word);
+    const uint32_t shares_off = xwg_load(seedx ? seedx : helpers_off_word);
     if ((int)blockIdx.x < n_helpers) {
         // ---- helper workgroup of (sequence, KV head) blockIdx.x: attention over W for its G heads
-        if (!helpers || coop_mode == RA_HELPERS_SILENT_) return;
+        if (coop_mode == RA_HELPERS_SILENT_) return;
         // helper_heads of the group's G query heads per helper workgroup (G: one helper per group, W
         // read once; fewer where the launch leaves compute units idle: the helpers of a group then
         // run side by side on one XCD and share the rows in its L2)
@@ -321,20 +324,17 @@ __global__ __launch_bounds__(T) void decode_kernel(
         const int h_end = (part + 1) * helper_heads;
         for (int h0 = part * helper_heads; h0 < h_end; h0 += PASS) {
             const int head0 = g * G + h0;
-            if (h_end - h0 >= PASS) static_helper<DT, PASS, T>(lds_raw, q, head0, Kg, Vg, s, wstart, N, scale, coop, ready);
-            else if (h_end - h0 == 2) static_helper<DT, 2, T>(lds_raw, q, head0, Kg, Vg, s, wstart, N, scale, coop, ready);
-            else static_helper<DT, 1, T>(lds_raw, q, head0, Kg, Vg, s, wstart, N, scale, coop, ready);
+            if (h_end - h0 >= PASS) static_helper<DT, PASS, T>(lds_raw, q, head0, Kg, Vg, s, wstart, N, scale, coop, helpers_off != 0u);
+            else if (h_end - h0 == 2) static_helper<DT, 2, T>(lds_raw, q, head0, Kg, Vg, s, wstart, N, scale, coop, helpers_off != 0u);
+            else static_helper<DT, 1, T>(lds_raw, q, head0, Kg, Vg, s, wstart, N, scale, coop, helpers_off != 0u);
         }
         return;
     }
-    // seed hand-over area: [0] the "shares off" word, then (from byte RA_SEEDX_KEYS_OFF) seed_stride
-    // 64-bit keys per head, zero between launches
     u64* seed_keys_all = reinterpret_cast<u64*>(reinterpret_cast<char*>(seedx) + RA_SEEDX_KEYS_OFF);
-    const bool shares = seed_parts > 0 && xwg_load(seedx) == 0u;
     if ((int)blockIdx.x < n_helpers + n_heads * seed_parts) {
         // ---- seed workgroup: one share of one head's start set (on the XCD of the head's workgroup
         //      when the number of heads is a multiple of 8)
-        if (!shares || coop_mode == RA_HELPERS_SILENT_) return;
+        if (coop_mode == RA_HELPERS_SILENT_ || shares_off != 0u) return;
         const int i = (int)blockIdx.x - n_helpers;
         const int part = i / n_heads, hd = xcd_aware_head(i % n_heads, n_heads, G);
         score_seed_share<DT, KT, T>(hd, part, seed_parts, q, Ksearch, n_q, n_kv, kv_stride, roots, root_cap,
@@ -359,68 +359,102 @@ __global__ __launch_bounds__(T) void decode_kernel(
     const int cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
                                           s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
                                           lds_ids, roots, root_cap, kscale,
-                                          AwaitHelper{ready + head, ready + n_heads, lds_word,
-                                                      coop_spin, helpers,
-                                                      seed_keys_all + (size_t)head * seed_stride, seedx,
-                                                      shares});
+                                          SeedHook{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx,
+                                                   seed_parts > 0, shares_off});
 #ifdef SR_PHASE_CLOCKS
     const long long t_attn = clock64();
 #endif
-    // ---- the helper's record for this head, if its ready word came (AwaitHelper)
-    bool have_w = false;
-    float mw = -INFINITY, lw = 0.f, aw = 0.f;
-    if (helpers) {
-        have_w = *lds_word != 0u;
-        if (have_w && tid < RA_D) {
-            const float* r = coop + (size_t)head * RA_COOP_REC;
-            mw = xwg_load(r);
-            lw = xwg_load(r + 1);
-            aw = xwg_load(r + 4 + tid);
-        }
-    }
-    // ---- Eq. 2 over Omega (rows [0, cnt): ids in LDS) and, without a record, W (rows
-    //      [cnt, cnt + s + N - wstart))
+    // ---- Eq. 2 over Omega (rows [0, cnt): ids in LDS) and, in a launch without helpers, W (the n_w rows after
+    //      them). The helper's record is asked for behind the first rows, so that its trip past the caches
+    //      is over when they have been attended to (asking for a ready word first, when the walk had
+    //      ended, and then for the record took a microsecond of every step).
+    const bool helpers = n_helpers > 0 && helpers_off == 0u;
+    u64* rec = coop + (size_t)head * RA_COOP_REC;
+    u64 w_mx = 0ull, w_l = 0ull, w_a = 0ull;
     LaneQuery<DT> ql;
     ql.load(reinterpret_cast<const char*>(q) + (size_t)head * RA_D * esz, lane16);
     constexpr int DC_ROWS = DT == RA_BF16 ? 6 : 3;       // rows in flight per 16-lane group
-    const int R = cnt + (have_w ? 0 : s + (int)(N - wstart));
-    Softmax8 st;
-    st.m = -INFINITY;
-    st.l = 0.f;
+    // attention over the R rows row_id(0 ..) of K and V; `behind` is called once, after the first loads
+    auto attend_rows = [&](int R, auto row_id, auto behind) __attribute__((always_inline)) {
+        Softmax8 st;
+        st.m = -INFINITY;
+        st.l = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) st.acc[e] = 0.f;
-    for (int r0 = 0; r0 < R; r0 += (T / 16) * DC_ROWS) {
-        int64_t rid[DC_ROWS];
-        RowBits<DT> kb[DC_ROWS], vb[DC_ROWS];
+        for (int e = 0; e < 8; ++e) st.acc[e] = 0.f;
+        if (R <= 0) behind();
+        for (int r0 = 0; r0 < R; r0 += (T / 16) * DC_ROWS) {
+            int64_t rid[DC_ROWS];
+            RowBits<DT> kb[DC_ROWS], vb[DC_ROWS];
 #pragma unroll
-        for (int u = 0; u < DC_ROWS; ++u) {
-            if (r0 + u * (T / 16) >= R) break;          // uniform: no group has a row in this slot
-            const int r = r0 + u * (T / 16) + grp;
-            int64_t id = -1;
-            if (r < cnt) id = lds_ids[r];
-            else if (r < R) id = r - cnt < s ? (int64_t)(r - cnt) : wstart + (r - cnt - s);
-            rid[u] = id;
-            const int64_t safe = id >= 0 ? id : 0;      // loads stay unconditional
-            kb[u] = load_key<DT>(Kh, safe, lane16);
-            vb[u] = load_key<DT>(Vh, safe, lane16);
+            for (int u = 0; u < DC_ROWS; ++u) {
+                if (r0 + u * (T / 16) >= R) break;          // uniform: no group has a row in this slot
+                const int r = r0 + u * (T / 16) + grp;
+                const int64_t id = r < R ? row_id(r) : -1;
+                rid[u] = id;
+                const int64_t safe = id >= 0 ? id : 0;      // loads stay unconditional
+                kb[u] = load_key<DT>(Kh, safe, lane16);
+                vb[u] = load_key<DT>(Vh, safe, lane16);
+            }
+            if (r0 == 0) behind();
+#pragma unroll
+            for (int u = 0; u < DC_ROWS; ++u) {
+                if (r0 + u * (T / 16) >= R) break;
+                if (rid[u] < 0) continue;
+                float dot = ql.dot(kb[u]);
+                dot += at_dpp<0xB1>(dot);
+                dot += at_dpp<0x4E>(dot);
+                dot += at_dpp<0x141>(dot);
+                dot += at_dpp<0x140>(dot);
+                float v[8];
+                row_floats<DT>(vb[u], v);
+                sm_row<DT>(st, dot * scale, v);
+            }
         }
-#pragma unroll
-        for (int u = 0; u < DC_ROWS; ++u) {
-            if (r0 + u * (T / 16) >= R) break;
-            if (rid[u] < 0) continue;
-            float dot = ql.dot(kb[u]);
-            dot += at_dpp<0xB1>(dot);
-            dot += at_dpp<0x4E>(dot);
-            dot += at_dpp<0x141>(dot);
-            dot += at_dpp<0x140>(dot);
-            float v[8];
-            row_floats<DT>(vb[u], v);
-            sm_row<DT>(st, dot * scale, v);
+        return st;
+    };
+    const int n_w = s + (int)(N - wstart);
+    auto w_row = [&](int r) { return r < s ? (int64_t)r : wstart + (r - s); };
+    if (tid == 0) *lds_word = 0u;
+    const Softmax8 st_om = attend_rows(
+        cnt + (helpers ? 0 : n_w), [&](int r) { return r < cnt ? (int64_t)lds_ids[r] : w_row(r - cnt); },
+        [&]() {
+            if (helpers && tid < RA_D) {
+                w_mx = xwg_load(rec);
+                w_l = xwg_load(rec + 1);
+                w_a = xwg_load(rec + 2 + tid);
+            }
+        });
+    float mx, l, a;
+    sm_combine<T>(st_om, reinterpret_cast<float*>(lds_raw), tid, mx, l, a);
+    // ---- the record, waited for a bounded number of polls; without it, W by this workgroup itself, and
+    //      no helpers in later launches
+    float mw = -INFINITY, lw = 0.f, aw = 0.f;
+    bool have_w = false;
+    if (helpers) {
+        if (tid < RA_D) {
+            for (int i = 0; i < coop_spin && !(rec_came(w_mx) && rec_came(w_l) && rec_came(w_a)); ++i) {
+                __builtin_amdgcn_s_sleep(6);
+                w_mx = xwg_load(rec);
+                w_l = xwg_load(rec + 1);
+                w_a = xwg_load(rec + 2 + tid);
+            }
+            if (rec_came(w_mx) && rec_came(w_l) && rec_came(w_a)) {
+                mw = rec_value(w_mx);
+                lw = rec_value(w_l);
+                aw = rec_value(w_a);
+            } else {
+                *lds_word = 1u;
+            }
+        }
+        __syncthreads();
+        have_w = *lds_word == 0u;
+        if (!have_w) {
+            if (tid == 0) xwg_store(helpers_off_word, 1u);
+            const Softmax8 st_w = attend_rows(n_w, w_row, []() {});
+            sm_combine<T>(st_w, reinterpret_cast<float*>(lds_raw), tid, mw, lw, aw);
         }
     }
-    // ---- Eq. 4-5: the lane groups' partial results and the helper's record, re-scaled to one maximum
-    float mx, l, a;
-    sm_combine<T>(st, reinterpret_cast<float*>(lds_raw), tid, mx, l, a);
+    // ---- Eq. 4-5: the two sets re-scaled to one maximum
     if (tid < RA_D) {
         const float m2 = fmaxf(mx, mw);
         if (m2 > -INFINITY) {
@@ -430,9 +464,10 @@ __global__ __launch_bounds__(T) void decode_kernel(
         }
         const bool empty = !(l > 0.f);
         out[(size_t)head * RA_D + tid] = empty ? 0.f : a / l;
-        if (tid == 0) {
-            lse[head] = empty ? -INFINITY : m2 + logf(l);
-            if (have_w) xwg_store(ready + head, 0u);     // taken: the next launch starts from "not ready"
+        if (tid == 0) lse[head] = empty ? -INFINITY : m2 + logf(l);
+        if (have_w) {                                        // taken: the next launch starts from zero
+            xwg_store(rec + 2 + tid, 0ull);
+            if (tid < 2) xwg_store(rec + tid, 0ull);
         }
     }
 #ifdef SR_PHASE_CLOCKS
@@ -462,7 +497,7 @@ static size_t decode_lds_bytes(int64_t N, int deg, int ef, int expand, int topk,
     if (b > a) a = b;
     a = (a + 15) & ~(size_t)15;
     *ids_off = (int)a;
-    return a + (size_t)topk * sizeof(int32_t) + 16;        // ids, then a word for the ready flag
+    return a + (size_t)topk * sizeof(int32_t) + 16;        // ids, then a word for the record that did not come
 }
 
 bool ra_decode_needs_global_bitset(int64_t N, int deg, int ef, int expand, int topk) {
@@ -473,7 +508,7 @@ bool ra_decode_needs_global_bitset(int64_t N, int deg, int ef, int expand, int t
 
 // helper workgroups in front of the heads' in a decode launch: one per (sequence, KV head), for
 // GQA groups of 1, 2, 4 or 8 while the handle has them switched on
-static int decode_helper_slots(const float* coop, int coop_mode, int n_seq, int n_q, int n_kv) {
+static int decode_helper_slots(const unsigned long long* coop, int coop_mode, int n_seq, int n_q, int n_kv) {
     const int G = n_q / n_kv;
     const bool coop_on = coop && coop_mode != RA_HELPERS_OFF && (G == 1 || G == 2 || G == 4 || G == 8);
     return coop_on ? n_seq * n_kv : 0;
@@ -507,7 +542,7 @@ static int decode_compute_units() {
 ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* entry, const void* K,
                            const void* V, ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t Ng, int64_t N,
                            int64_t kv_stride, int deg, int sink, int window, int topk, int ef, int expand,
-                           uint32_t* bitset, float* coop, int coop_mode, int coop_spin,
+                           uint32_t* bitset, unsigned long long* coop, int coop_mode, int coop_spin,
                            const int32_t* roots, int root_cap, const void* K8, const float* kscale,
                            const int32_t* budgets, uint32_t* seedx, int seed_parts, hipStream_t st,
                            float* out, float* lse, int32_t* ids, ra_stats* stats) {

@@ -49,7 +49,6 @@
 enum { C_MISSED = 0, C_LO = 1, C_HI = 2, C_NSURV = 3, C_BIN = 4, C_STEP = 5, C_STEP2 = 8, C_WTOT = 11,
        C_COUNT = C_WTOT + SR_THREADS / RA_WAVE };
 enum { S_NCAND = 0, S_NKEEP = 1, S_NUNEXP = 2 };      // of the three words at C_STEP and at C_STEP2
-#define SR_NARROW 64              // most candidates of a merge without counters (one per lane)
 #define SR_TOUCH_BYTES (4 * RA_WAVE) // where touched words land (touch_line)
 #define SR_PREFILTER_SLACK 64     // a step that keeps more than ef + this many candidates drops the hopeless ones first
 #define SR_PREFILTER_REGS 8       // ... when a thread can hold its share of them (nk <= 8 T)
@@ -311,6 +310,22 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
     return v;
 }
 
+// Smallest lo and largest hi of the wavefront, in lane 63 (lane permutations inside the rows of 16, then the
+// rows: no trips through LDS).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ void min_max_step(uint32_t& lo, uint32_t& hi) {
+    lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, CTRL, ROW_MASK, 0xF, false));
+    hi = max(hi, (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, CTRL, ROW_MASK, 0xF, false));
+}
+__device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
+    min_max_step<0xB1, 0xF>(lo, hi);
+    min_max_step<0x4E, 0xF>(lo, hi);
+    min_max_step<0x141, 0xF>(lo, hi);
+    min_max_step<0x140, 0xF>(lo, hi);
+    min_max_step<0x142, 0xA>(lo, hi);        // lane 15 of a row into the next one, then lane 31 to the upper half
+    min_max_step<0x143, 0xC>(lo, hi);
+}
+
 // the same, counting only entries whose not-yet-expanded flag is clear
 __device__ __forceinline__ int count_above16_expanded(const u64* arr, int n, u64 k) {
     u64 v[16];
@@ -378,17 +393,13 @@ __device__ __forceinline__ void touch_line(const void* p, uint32_t lds_off) {
 // `lds_raw` is the workgroup's dynamic LDS (ra_search_lds_bytes of it). Writes ids/stats of
 // `head`; when `lds_ids` is not null the ids are also left there (LDS) for a fused consumer.
 // Returns the number of valid ids. Ends with the whole workgroup past a barrier.
-// A caller's hook into run_search: before_output() is called by every thread when the walk has
-// ended, ahead of the phase in which the first wavefront writes the result (the others idle until
-// the closing barrier, which also publishes whatever the hook left in LDS).
-// Its kSeedShare says whether the start set of a seeded walk may be scored by other workgroups of
+// A caller's hook into run_search: kSeedShare says whether the start set of a seeded walk may be scored by other workgroups of
 // the launch (score_seed_share below): then seeds_shared() says whether it is in this launch,
 // take_seed_keys(c0, c1, k0, k1) waits (bounded) for keys c0 and c1 of the set (c1 < 0: only c0; k1 is
 // then k0 again) and leaves 0 for one that did not come, and seeds_missed() is called by one thread
 // when some key did not.
 struct NoHook {
     static constexpr bool kSeedShare = false;
-    __device__ __forceinline__ void before_output() const {}
 };
 
 // Words that cross workgroups inside one launch: relaxed agent-scope atomics, which go around the
@@ -703,12 +714,8 @@ __device__ __forceinline__ int run_search(
             if (n_root - c0 > 0) score_rows(sr_int<1>{}, c0);
         }
         // every lane may hold extremes of its keys: fold the wavefront
-#pragma unroll
-        for (int d = 1; d < RA_WAVE; d <<= 1) {
-            lo = min(lo, (uint32_t)__shfl_xor((int)lo, d));
-            hi = max(hi, (uint32_t)__shfl_xor((int)hi, d));
-        }
-        if (lane == 0) {
+        wave_min_max(lo, hi);
+        if (lane == RA_WAVE - 1) {
             atomicMin(reinterpret_cast<unsigned int*>(&ctr[C_LO]), lo);
             atomicMax(reinterpret_cast<unsigned int*>(&ctr[C_HI]), hi);
         }
@@ -926,13 +933,8 @@ __device__ __forceinline__ int run_search(
                 }
             }
             if (!first) {                    // (a start set's extremes are known already)
-#pragma unroll
-                for (int d = 1; d < RA_WAVE; d <<= 1) {
-                    const uint32_t ol = __shfl_xor(lo, d), oh = __shfl_xor(hi, d);
-                    lo = ol < lo ? ol : lo;
-                    hi = oh > hi ? oh : hi;
-                }
-                if (lane == 0) {
+                wave_min_max(lo, hi);
+                if (lane == RA_WAVE - 1) {
                     atomicMin(reinterpret_cast<unsigned int*>(&ctr[C_LO]), lo);
                     atomicMax(reinterpret_cast<unsigned int*>(&ctr[C_HI]), hi);
                 }
@@ -1023,8 +1025,9 @@ __device__ __forceinline__ int run_search(
         //      count of *unexpanded* elements above each element (every candidate is unexpanded;
         //      for the beam's part urank has it), so the next step's picks, the elements with
         //      fewer than `expand` unexpanded ones above them, fall out of the merge.
-        //      Few candidates (SR_NARROW, and not many among any 64 beam entries) take the shorter way below.
-        const bool narrow = !first && nk <= SR_NARROW && nk <= 16 + bn / 16;
+        //      Few candidates (NARROW, and not many among any 64 beam entries) take the shorter way below.
+        constexpr int NARROW = 64;                           // one candidate per lane
+        const bool narrow = !first && nk <= NARROW && nk <= 16 + bn / 16;
         auto sum16 = [&](int v) __attribute__((always_inline)) {       // over the 16 lanes of the group, in each of them
             v += dpp_i32<0xB1>(v);
             v += dpp_i32<0x4E>(v);
@@ -1067,14 +1070,14 @@ __device__ __forceinline__ int run_search(
                 const int c = c0 + (lane >> 4);
                 const bool live = c < nk;
                 const u64 k = ckey[live ? c : 0];
-                u64 other[SR_NARROW / 16];
+                u64 other[NARROW / 16];
 #pragma unroll
-                for (int i = 0; i < SR_NARROW / 16; ++i) other[i] = ckey[i * 16 + lane16 < nk ? i * 16 + lane16 : 0];
+                for (int i = 0; i < NARROW / 16; ++i) other[i] = ckey[i * 16 + lane16 < nk ? i * 16 + lane16 : 0];
                 int b, ub;                                    // beam entries above it; the unexpanded ones of them
                 search16(k, b, ub);
                 int above = 0;
 #pragma unroll
-                for (int i = 0; i < SR_NARROW / 16; ++i) above += i * 16 + lane16 < nk && other[i] > k ? 1 : 0;
+                for (int i = 0; i < NARROW / 16; ++i) above += i * 16 + lane16 < nk && other[i] > k ? 1 : 0;
                 above = sum16(above);
                 const int pos = b + above;
                 const bool un = live && lane16 == 0 && pos < ef;
@@ -1090,7 +1093,6 @@ __device__ __forceinline__ int run_search(
             }
             for (int e0 = wv * RA_WAVE; e0 < bn; e0 += T) {
                 const int e = e0 + lane;
-                const u64 ck = ckey[lane < nk ? lane : 0];
                 u64 k = cur[e < bn ? e : bn - 1];
                 const int ub = (int)urank[e < bn ? e : bn - 1] - np;
                 const uint32_t klo = (uint32_t)k, khi = (uint32_t)(k >> 32);
@@ -1098,6 +1100,7 @@ __device__ __forceinline__ int run_search(
                                (uint32_t)__builtin_amdgcn_readlane((int)klo, 0);
                 const u64 lo = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)khi, RA_WAVE - 1) << 32) |
                                (uint32_t)__builtin_amdgcn_readlane((int)klo, RA_WAVE - 1);
+                const u64 ck = ckey[lane < nk ? lane : 0];
                 const u64 all = __builtin_amdgcn_ballot_w64(lane < nk && ck > hi);
                 u64 inside = __builtin_amdgcn_ballot_w64(lane < nk && ck > lo) & ~all;
                 int c = __popcll(all);
@@ -1227,7 +1230,6 @@ __device__ __forceinline__ int run_search(
         first = false;
     }
 
-    hook.before_output();
     __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): no touch of this wavefront still has to land in LDS
     // ---- result: best-first beam entries outside the static set W = [0,s) u [N-w,N). A short list is the
     //      first wavefront's alone (the others wait at the closing barrier); of a long one (a wavefront
