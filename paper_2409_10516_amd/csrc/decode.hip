@@ -514,18 +514,6 @@ static int decode_helper_slots(const unsigned long long* coop, int coop_mode, in
     return coop_on ? n_seq * n_kv : 0;
 }
 
-// Threads per workgroup of the fused launch. With the start sets scored by seed workgroups and the
-// static set by helpers, what a head's workgroup is left with is mostly merges and barriers, which
-// 512 threads get through sooner than 1024 (128K layer, 32 searches: 28.4 against 29.6 us; 27.3 against
-// 29.6 us for 128 searches of 32K keys, and still 37.5 against 49.1 us when 256 searches and their 64
-// helpers outnumber the compute units); a beam of more than 256 entries keeps 1024 threads (its steps
-// gather thousands of rows: 215 against 200 us on the 1M-key configuration). From 512 searches on,
-// 256 threads as in the stand-alone search (48.3 against 52.8 us).
-static int decode_threads(int heads, int ef) {
-    if (ef > 256) return search_threads(heads, ef);
-    return heads <= 384 ? 512 : 256;
-}
-
 // compute units of the current device (asked once per device)
 static int decode_compute_units() {
     static int cached[64];
@@ -566,7 +554,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
     // one helper workgroup per (sequence, KV head) in front of the heads' (GQA groups of 1, 2, 4 or 8)
     if (!coop) RA_FAIL(RA_EINVAL, "hand-over area missing");
     int n_helpers = decode_helper_slots(coop, coop_mode, n_seq, n_q, n_kv);
-    const int threads = decode_threads(heads, ef);
+    const int threads = search_threads(heads, ef, expand * deg);
     // One helper per query head instead of one per KV head where the launch leaves compute units idle
     // (few searches): with 512 threads a helper's pass over W for a whole group ends later than a
     // short walk does (128K layer: 26.5 against 27.25 us). The helpers of a group run side by side on

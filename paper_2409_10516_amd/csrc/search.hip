@@ -209,7 +209,7 @@ ra_status ra_launch_search(const void* q, const int32_t* adj, const int32_t* ent
                 SR_LDS_LIMIT);
     const int heads = n_seq * n_q;
     if (gb && !bitset) RA_FAIL(RA_EINVAL, "global visited bitset missing");
-    const int threads = search_threads(heads, ef);
+    const int threads = search_threads(heads, ef, expand * deg);
 #define RA_SR_LAUNCH_T(DTV, KTV, GB, TV)                                                          \
     do {                                                                                          \
         RA_LDS_OPT_IN((search_kernel<DTV, KTV, GB, TV>), lds);                                    \

@@ -1234,7 +1234,7 @@ __device__ __forceinline__ int run_search(
     // ---- result: best-first beam entries outside the static set W = [0,s) u [N-w,N). A short list is the
     //      first wavefront's alone (the others wait at the closing barrier); of a long one (a wavefront
     //      would be 32 rounds over 2048 entries) every wavefront takes rounds, T entries at a time.
-    if (T < 1024 || topk <= 256) {
+    if (topk <= 256) {
     if (tid < RA_WAVE) {
         int32_t* out = ids + (size_t)head * topk;
         int cnt = 0;
@@ -1303,13 +1303,20 @@ __device__ __forceinline__ int run_search(
 }
 
 
-// Threads per search. One search per compute unit or fewer (the latency-bound case): the largest
-// workgroup finishes a search soonest. More searches than compute units: smaller workgroups, so
-// that several searches share a compute unit and one's trips to HBM hide behind another's work
-// (measured at 512 searches of 32K keys: 111 us per launch with 1024 threads, 74 with 512, 68 with 256).
-static inline int search_threads(int heads, int ef) {
-    if (heads <= 256 || ef > 512) return 1024;
-    return ef > 256 ? 512 : 256;
+// Threads per search, of a launch of `heads` searches whose steps read up to `cells` adjacency cells. What a
+// narrow walk's steps consist of is merges and barriers, which 512 threads get through sooner than 1024
+// (128K layer, 32 searches: 28.4 against 29.6 us; 27.3 against 29.6 us for 128 searches of 32K keys, and
+// still 37.5 against 49.1 us when 256 searches and their 64 helpers outnumber the compute units); a beam
+// of more than 256 entries keeps 1024 (its steps gather and merge more: 215 against 200 us on the
+// 1M-key configuration), and above 384 searches 256 threads let several share a compute unit, one's trips
+// to HBM behind another's work (48.3 against 52.8 us for 512 searches of 32K keys). Steps of very few
+// cells go one size down: one node of degree 32 per step 184 -> 168 us (ef 128; of degree 64 slower), of
+// degree 48 2.91 -> 2.36 ms (ef 1024), four of degree 48 701 -> 676 us (ef 1024; slower with ef 2048).
+static inline int search_threads(int heads, int ef, int cells) {
+    if (cells <= 64 && heads <= 384) return ef > 256 || cells > 48 ? 512 : 256;
+    if (ef > 1024) return 1024;
+    if (ef > 256) return cells <= 256 || (heads > 256 && ef <= 512) ? 512 : 1024;
+    return heads <= 384 ? 512 : 256;
 }
 
 // LDS bytes run_search needs.
