@@ -13,12 +13,16 @@
 // and y_d the nearest integer. Then
 //     <q, k> = s <y, x> + s <f, x> + <q', e>,   |<q, k> - s <y, x>| <= s |f| |x| + |q'| |e|,
 // where <y, x> is an exact integer (at most 128 x 127 x 127) from v_mfma_i32_32x32x32_i8 and the
-// largest |x| and |e| over the head's keys are taken when the copy is made. What the floating point
-// sum of the exact path can be off by is added (2^-15 |q| |k|, several times what 128 additions in
-// float32 can lose), every norm is widened by 0.1 % and a little more for its own rounding. So a key
+// largest |x| and |e| over the head's keys are taken when the copy is made. Every norm is taken relative to
+// a power of two or to s (|q'| = s |y + f|), so none of them loses its terms where squares of the
+// inputs leave the range of float32, and every norm is widened by 0.1 % and a little more for its own rounding.
+// What the floating point sum of the exact path can be off by is added: 2^-15 |q| |k|, several times what
+// 128 additions in float32 can lose; and, should the matrix cores take denormal numbers for zero, 2^-126
+// sqrt(128) (|q| + |k|) for the inputs and 256 x 2^-126 for products and partial sums. So a key
 // whose score could reach a query's threshold tau has <y, x> >= (tau - bound) / s: one integer per
-// query, compared with the largest of a lane's 16 accumulators. Non-finite inputs make the bound
-// non-finite and the integer the smallest there is: everything is scored then.
+// query, compared with the largest of a lane's 16 accumulators. Where that does not hold nothing is ruled out
+// (an infinite bound: the integer is the smallest there is): non-finite inputs, norms whose product could
+// overflow a score (10^38), and s below 2^-100, where the quotients above would round in the denormal range.
 //
 // What it buys: the copy is half as many bytes and twice the multiply rate, and a wavefront holds
 // the 8-bit queries of four sets of 32 in the registers that one set of bf16 queries took, so a key
@@ -91,12 +95,22 @@ __global__ __launch_bounds__(256) void kf_maxabs_kernel(const void* __restrict__
 __device__ __forceinline__ float kf_scale(uint32_t maxabs_bits) {
     return maxabs_bits == 0u ? 1.f : __uint_as_float(maxabs_bits) * (1.0f / 127.0f);
 }
+// Exponent of the largest |k| of a head, from its column maxima (16 lanes hold 8 of them each). Norms of keys
+// are taken over k 2^-exponent: their squares neither overflow nor, for the largest of them, vanish.
+__device__ __forceinline__ int kf_exponent(const uint32_t (&maxabs_bits)[8]) {
+    uint32_t top = 0u;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) top = max(top, maxabs_bits[c]);
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) top = max(top, (uint32_t)__shfl_xor((int)top, d));
+    return __builtin_amdgcn_frexp_expf(__uint_as_float(top));       // (0 for zero, infinity and NaN)
+}
 
 // ---- the 8-bit copy of a head's keys in stream order ----------------------------------------------
 // Row p of a graph (128 bytes) holds the key streamed p-th, its 16-byte chunks at chunk ^ (p / 2 % 8):
 // the layout a stage has in LDS, so that a stage is one linear copy and operand reads (16 rows, the
 // same chunk) cover all 64 banks. Rows beyond N are zero. bounds[graph]: bits of the largest |e|^2,
-// |x|^2 and |k|^2 of the graph's keys.
+// |x|^2 and |k 2^-kf_exponent|^2 of the graph's keys.
 // grid (rows / 64, graphs); 16 lanes per row
 template <int DT>
 __global__ __launch_bounds__(1024) void kf_pack_kernel(const void* __restrict__ K, const u64* __restrict__ order,
@@ -110,11 +124,14 @@ __global__ __launch_bounds__(1024) void kf_pack_kernel(const void* __restrict__ 
     if (tid < 4) s_b[tid] = 0u;
     __syncthreads();
     float sc[8], inv[8];
+    uint32_t mx[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        sc[c] = kf_scale(maxabs[kv * RA_D + 8 * l16 + c]);
+        mx[c] = maxabs[kv * RA_D + 8 * l16 + c];
+        sc[c] = kf_scale(mx[c]);
         inv[c] = 1.0f / sc[c];
     }
+    const int k_exp = kf_exponent(mx);
     const u64* ord = order + (size_t)graph * order_stride;
     for (int64_t p = (int64_t)blockIdx.x * 64 + tid / 16; p < rows8; p += (int64_t)gridDim.x * 64) {
         uint32_t w[2] = {0u, 0u};
@@ -130,7 +147,8 @@ __global__ __launch_bounds__(1024) void kf_pack_kernel(const void* __restrict__ 
                 const float e = __fmaf_rn(-x, sc[c], v[c]) * inv[c];
                 e2 += e * e;
                 x2 += x * x;
-                k2 += v[c] * v[c];
+                const float k = __builtin_amdgcn_ldexpf(v[c], -k_exp);
+                k2 += k * k;
                 w[c / 4] |= ((uint32_t)(int)x & 255u) << (8 * (c % 4));
             }
         }
@@ -241,7 +259,7 @@ __device__ __forceinline__ int kf_floor(float tau, float bound, float inv_s) {
     return x > 1.0e9f ? 1000000000 : (int)floorf(x) - 2;
 }
 
-// ---- the queries in 8 bits: y (128 bytes per query, in order), and per query [s, bound, 1 / s, tau]
+// ---- the queries in 8 bits: y (128 bytes per query, in order), and per query [bound, 1 / s, tau, 0]
 // grid (rows / 16, graphs); 16 lanes per row
 template <int DT>
 __global__ __launch_bounds__(256) void kf_queries_kernel(const void* __restrict__ Q,
@@ -254,44 +272,57 @@ __global__ __launch_bounds__(256) void kf_queries_kernel(const void* __restrict_
     const int tid = threadIdx.x, l16 = tid & 15;
     const size_t kv = (size_t)seq * n_kv + kvh;
     float sc[8];
+    uint32_t mx[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) sc[c] = kf_scale(maxabs[kv * RA_D + 8 * l16 + c]);
+    for (int c = 0; c < 8; ++c) {
+        mx[c] = maxabs[kv * RA_D + 8 * l16 + c];
+        sc[c] = kf_scale(mx[c]);
+    }
     const float e_max = 1.001f * sqrtf(__uint_as_float(bounds[gl * 4])) + 1e-3f;
     const float x_max = 1.001f * sqrtf(__uint_as_float(bounds[gl * 4 + 1]));
-    const float k_max = 1.001f * sqrtf(__uint_as_float(bounds[gl * 4 + 2]));
+    const float k_max = __builtin_amdgcn_ldexpf(1.001f * sqrtf(__uint_as_float(bounds[gl * 4 + 2])), kf_exponent(mx));
     for (int64_t j = (int64_t)blockIdx.x * 16 + tid / 16; j < M; j += (int64_t)gridDim.x * 16) {
-        float v[8], p[8], top = 0.f, q2 = 0.f, p2 = 0.f;
+        float v[8], p[8], top = 0.f, q_top = 0.f;
         kf_row8<DT>(Q, ((size_t)graph * M + j) * RA_D + 8 * l16, v);
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             p[c] = v[c] * sc[c];
-            q2 += v[c] * v[c];
-            p2 += p[c] * p[c];
             top = fmaxf(top, fabsf(p[c]));
+            q_top = fmaxf(q_top, fabsf(v[c]));
         }
 #pragma unroll
         for (int d = 1; d < 16; d <<= 1) {
             top = fmaxf(top, __shfl_xor(top, d));
-            q2 += __shfl_xor(q2, d);
-            p2 += __shfl_xor(p2, d);
+            q_top = fmaxf(q_top, __shfl_xor(q_top, d));
         }
         const float s = top > 0.f ? top * (1.0f / 127.0f) : 1.f, inv = 1.0f / s;
-        float f2 = 0.f;
+        const int q_exp = __builtin_amdgcn_frexp_expf(q_top);
+        float f2 = 0.f, n2 = 0.f, q2 = 0.f;              // |f|^2, |q' / s|^2, |q 2^-q_exp|^2
         uint32_t w[2] = {0u, 0u};
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            float y = rintf(p[c] * inv);
+            const float r = p[c] * inv;
+            float y = rintf(r);
             y = fminf(fmaxf(y, -127.f), 127.f);
             const float f = __fmaf_rn(-y, s, p[c]) * inv;
+            const float q = __builtin_amdgcn_ldexpf(v[c], -q_exp);
             f2 += f * f;
+            n2 += r * r;
+            q2 += q * q;
             w[c / 4] |= ((uint32_t)(int)y & 255u) << (8 * (c % 4));
         }
 #pragma unroll
-        for (int d = 1; d < 16; d <<= 1) f2 += __shfl_xor(f2, d);
+        for (int d = 1; d < 16; d <<= 1) {
+            f2 += __shfl_xor(f2, d);
+            n2 += __shfl_xor(n2, d);
+            q2 += __shfl_xor(q2, d);
+        }
         Q8[((size_t)gl * M + j) * 16 + l16] = make_uint2(w[0], w[1]);
         if (l16 == 0) {
-            const float bound = 1.002f * (s * (1.001f * sqrtf(f2) + 1e-3f) * x_max + sqrtf(p2) * e_max) +
-                                3.1e-5f * sqrtf(q2) * k_max + 1e-35f;
+            const float q_norm = __builtin_amdgcn_ldexpf(1.001f * sqrtf(q2), q_exp), norms = q_norm * k_max;
+            float bound = 1.002f * s * ((1.001f * sqrtf(f2) + 1e-3f) * x_max + 1.001f * sqrtf(n2) * e_max) +
+                          3.1e-5f * norms + 1.4e-37f * (q_norm + k_max) + 1e-35f;
+            if (!(s >= 0x1p-100f && norms < 1e38f)) bound = INFINITY;
             qinfo[(size_t)gl * M + j] = make_float4(bound, inv, scores[((size_t)gl * M + j) * knn + knn - 1], 0.f);
         }
     }

@@ -342,3 +342,51 @@ def test_knn_through_8bit_products(dtype, N, M, knn):
     assert np.array_equal(L[B.RA_TEST_KNN_LDS], ra.ra_knn(K, Q, knn).cpu().numpy())
     Kn, Qn = to_np(w.K[1, 0]), to_np(w.Q_prefill[1, 1][:40])
     knn_equivalent(L[B.RA_TEST_KNN_REG][1, 1][:40], OM.knn_lists(Qn, Kn, knn)[0], Qn, Kn)
+
+
+# powers of two that queries and keys are multiplied by, down to where scores leave the normal range and up
+# to where squares do
+_SCALES = [(0, 0), (-84, 0), (0, -84), (-45, -45), (-59, -59), (-118, 0), (0, -110), (60, 40), (62, 62), (-126, 0),
+           (0, -126), (-70, -70)]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("knn", [20, 60])
+@pytest.mark.parametrize("q_exp,k_exp", _SCALES)
+def test_knn_8bit_bound_holds_at_any_scale(dtype, knn, q_exp, k_exp):
+    """The bound's worst pair: queries that are exact in 8 bits and keys that are nothing but rounding error,
+    aligned with them. One key of 127s sets every column's scale; the others are t / 256 times the signs of
+    the query, so their 8-bit copies are zero and their scores are all in the term |q'| |e|. Most queries
+    look at the second half of the dimensions, which makes the stream order; the rest look at the first
+    half, where the first 128 keys of the stream are middling, most later ones worse and a few, late, the best:
+    with that term lost they are ruled out. The lists of the stream without the filter, bit for bit, and
+    the oracle's while every product is a normal number (all sums are exact then: the scales are powers
+    of two)."""
+    from paper_2409_10516_amd import binding as B
+    rng = np.random.default_rng(31)
+    N, M = 1500, 96
+    u = rng.integers(1, 128, 128) * rng.choice([-1, 1], 128)
+    u[[0, 64]] = 127
+    place = rng.permutation(N)                       # in the stream
+    t = np.where(place < 128, rng.integers(40, 61, N), rng.integers(-115, 40, N))
+    late = rng.choice(np.nonzero((place > 300) & (place < N - 1))[0], 70, replace=False)
+    t[late] = rng.integers(90, 116, 70)
+    K = np.concatenate([np.repeat(t[:, None], 64, 1), np.repeat(100 - place[:, None] // 8, 64, 1)], 1) / 256.0 * np.sign(u)
+    K[place == N - 1] = -127.0 * np.sign(u)
+    Q = np.zeros((M, 128))
+    Q[:60, 64:] = u[64:]
+    Q[60:, :64] = u[:64]
+    Q[np.arange(60), 65 + np.arange(60)] = 0.0
+    Q[np.arange(60, M), 1 + np.arange(M - 60)] = 0.0
+    Kd = (torch.from_numpy(K) * 2.0 ** k_exp).to(dtype).to(DEV)[None, None]
+    Qd = (torch.from_numpy(Q) * 2.0 ** q_exp).to(dtype).to(DEV)[None, None]
+    L = {}
+    try:
+        for how in (B.RA_TEST_KNN_LDS, B.RA_TEST_KNN_REG):
+            ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, how)
+            L[how] = ra.ra_knn(Kd, Qd, knn).cpu().numpy()[0, 0]
+    finally:
+        ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_AUTO)
+    assert np.array_equal(L[B.RA_TEST_KNN_REG], L[B.RA_TEST_KNN_LDS])
+    if -118 <= q_exp + k_exp <= 100:                 # (the smallest product is 2^-8, the largest score 2^21)
+        assert np.array_equal(L[B.RA_TEST_KNN_LDS], OM.knn_lists(Q, K, knn)[0])
