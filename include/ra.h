@@ -123,8 +123,9 @@ ra_status ra_attend(const void* q, const ra_index* idx, const void* K, const voi
  * the array's address up, once). RA_EUNSUP, with the sizes in the message, when the records of the
  * call do not fit: n_seq * n_q_heads * (ceil((sink + window) / 64) + ceil(topk / 64)) * 528 bytes
  * for the decode step's static sets (a few thousand heads of the 128K configuration). All calls on
- * one device share the array: calls that overlap in time on one device race; calls in stream
- * order do not, and nothing has to be cleared between them. */
+ * one device share the array: calls that overlap in time on one device race (their results are
+ * undefined, those of later calls are not); calls in stream order do not, and nothing has to be cleared
+ * between them. */
 #define RA_ATTEND_NOALLOC_SCRATCH_BYTES (8u << 20)
 ra_status ra_attend_noalloc(const void* q, const ra_index* idx, const void* K, const void* V,
                             ra_dtype dt, int64_t N, int sink, int window, int topk,

@@ -1,5 +1,6 @@
 // Stand-alone attention launches (ra_attend); the device code is in attend_dev.h.
 #include "attend_dev.h"
+#include "ticket.h"
 
 // Folds the slices' (max, sum, weighted sum) of a head through LDS, in slice order, and closes it (called by
 // all threads; slice 0 writes).
@@ -25,8 +26,8 @@ __device__ __forceinline__ void merge_slices(float* part, int slice, int n_slice
     if (slice == 0) merge_finish(M, L, A, t, head, out, lse, o_om, lse_om, o_w, lse_w);
 }
 
-// Where a partial launch's records are combined: by the launch itself (tickets: one word per query head,
-// zero between launches), or, with tickets null, by attend_merge_kernel afterwards.
+// Where a partial launch's records are combined: by the launch itself (tickets: one word per query head, see
+// ticket.h), or, with tickets null, by attend_merge_kernel afterwards.
 struct AttendOut {
     uint32_t* tickets;
     float *out, *lse, *o_om, *lse_om, *o_w, *lse_w;
@@ -51,7 +52,7 @@ __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
     const int h0 = blockIdx.y * G;
     const char* qg = reinterpret_cast<const char*>(q) + ((size_t)seq * n_q + h0) * RA_D * esz;
     float* rec_g = partials + ((size_t)seq * n_q + h0) * P * AT_RS;
-    int first = 0, n_mine = G;                  // heads of the group this workgroup has a record of
+    int first = 0, n_mine = G, slot = x;        // heads of the group this workgroup has a record of, and which
     if (x < nS) {
         RowSrc src{nullptr, N, s, w, s + w, 0};
         bool done = false;
@@ -72,15 +73,18 @@ __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
                                      rec_g + ((size_t)g * P + nS + c) * AT_RS, 0, smem);
         first = g;
         n_mine = 1;
+        slot = nS + c;
     }
     if constexpr (TICKETS) {
         __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): this wavefront's record stores have completed
         __syncthreads();                        // ... and every other's (and the LDS of the chunk is free)
         uint32_t* last = reinterpret_cast<uint32_t*>(smem);
         const size_t head0 = (size_t)seq * n_q + h0 + first;
-        if ((int)threadIdx.x < n_mine)
-            last[threadIdx.x] = __hip_atomic_fetch_add(o.tickets + head0 + threadIdx.x, 1u, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)P - 1u;
+        if ((int)threadIdx.x < n_mine) {
+            const uint32_t step = ticket_step(slot, P);
+            last[threadIdx.x] = ticket_last(__hip_atomic_fetch_add(o.tickets + head0 + threadIdx.x, step, __ATOMIC_RELAXED,
+                                                                   __HIP_MEMORY_SCOPE_AGENT), step);
+        }
         __syncthreads();
         bool mine[G];
 #pragma unroll
@@ -95,8 +99,6 @@ __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
             float M[2] = {-INFINITY, -INFINITY}, L[2] = {0.f, 0.f}, A[2] = {0.f, 0.f};
             merge_accumulate<true>(partials + head * P * AT_RS, nS, nG, t, slice, SL, M, L, A);
             merge_slices(smem, slice, SL, t, M, L, A, head, o.out, o.lse, o.o_om, o.lse_om, o.o_w, o.lse_w);
-            if (threadIdx.x == 0)
-                __hip_atomic_store(o.tickets + head, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (g + 1 < G) __syncthreads();
         }
     }
@@ -220,7 +222,7 @@ ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype
 // host code never passes the array's name to a kernel, only the address hipGetSymbolAddress gives
 // for the current device (looked up once per device and kept).
 static __device__ __align__(256) unsigned char scratch[RA_ATTEND_NOALLOC_SCRATCH_BYTES];
-// one ticket per head that fits (a head has a record at least); zero between calls
+// one ticket per head that fits (a head has a record at least); they bring themselves back to zero (ticket.h)
 static __device__ uint32_t scratch_tickets[RA_ATTEND_NOALLOC_SCRATCH_BYTES / (AT_RS * 4)];
 static void* g_scratch_addr[RA_MAX_DEVICES];
 static uint32_t* g_ticket_addr[RA_MAX_DEVICES];
@@ -255,8 +257,8 @@ ra_status ra_launch_attend_noalloc(const void* q, const void* K, const void* V, 
     uint32_t* tickets = nullptr;
     ra_status rc = scratch_address(&ptr, &tickets);
     if (rc != RA_OK) return rc;
-    // nothing to clear: every record the merge reads is written by this call, which also leaves the
-    // tickets at zero
+    // nothing to clear: every record the merge reads is written by this call, and the tickets are zero
+    // whenever no call is running, also after calls that overlapped
     return ra_launch_attend(q, K, V, dt, n_seq, n_q, n_kv, N, sink, window, topk, ids,
                             reinterpret_cast<float*>(ptr), tickets, st, out, lse, o_omega, lse_omega, o_w, lse_w);
 }

@@ -64,7 +64,7 @@ struct ra_index {
     // hand-over area of the fused decode kernel: per head a record of RA_COOP_REC 64-bit words (max, sum,
     // 128 weighted sums; the value's bits, and 1 in the upper half) that a helper workgroup fills with the
     // attention over the static set and that is zero between launches, then one "helpers off" word,
-    // then per head a ticket of ra_attend's combination (see attend.hip)
+    // then per head a ticket of ra_attend's combination (ticket.h)
     unsigned long long* coop;
     int coop_mode;      // RA_HELPERS_*
     int coop_spin;      // polls of a record's words before a head gives up on its helper
@@ -115,7 +115,7 @@ ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype
                            int n_q, int n_kv, int64_t N, int sink, int window, int topk,
                            const int32_t* ids, float* partials, uint32_t* tickets, hipStream_t st,
                            float* out, float* lse, float* o_omega, float* lse_omega, float* o_w,
-                           float* lse_w);       // ids null: Omega is empty; tickets: see attend.hip
+                           float* lse_w);       // ids null: Omega is empty; tickets: see ticket.h, or null
 
 ra_status ra_launch_attend_noalloc(const void* q, const void* K, const void* V, ra_dtype dt, int n_seq,
                                    int n_q, int n_kv, int64_t N, int sink, int window, int topk,

@@ -78,3 +78,26 @@ def test_noalloc_attend_rejects_what_does_not_fit():
     assert e.value.status == 6 and "bytes" in str(e.value)
     ra.ra_attend(q, idx, K, K, 4, 640, ids)            # the allocating call takes it
     idx.free()
+
+
+@pytest.mark.parametrize("noalloc", [True, False])
+def test_calls_that_overlapped_leave_nothing_behind(noalloc):
+    """Calls that overlap in time share their records (one array per device, or one handle's workspace), so
+    their own results are undefined; what they must not do is spoil a later call, whatever number of
+    records each had."""
+    w, idx, ids, W = _case(73, N=3000, n_seq=1, n_q=8, n_kv=2, topk=200, window=640)
+    Kd, Vd, q = w.K.to(DEV), w.V.to(DEV), w.q_decode[0].to(DEV)
+    lists = [ids[..., :n].contiguous() for n in (200, 20, 64, 129)]
+    refs = [ra.ra_attend(q, idx, Kd, Vd, w.sink, w.window, i, noalloc=noalloc) for i in lists]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for turn in range(12):
+        for n, st in enumerate(streams):
+            ra.ra_attend(q, idx, Kd, Vd, w.sink, w.window, lists[(turn + 3 * n) % 4], noalloc=noalloc, stream=st,
+                         out=torch.empty_like(refs[0][0]), lse=torch.empty_like(refs[0][1]))
+    torch.cuda.synchronize()
+    for i, ref in zip(lists, refs):
+        got = ra.ra_attend(q, idx, Kd, Vd, w.sink, w.window, i, noalloc=noalloc,
+                           out=torch.full_like(ref[0], float("nan")), lse=torch.full_like(ref[1], float("nan")))
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    idx.free()
