@@ -620,10 +620,14 @@ __device__ __forceinline__ int run_search(
         bn = 1; n_visited = 1; n_expanded = 0; n_iters = 0;
     }
     // The adjacency cells of a step are dealt to the threads in order (cell x is slot x % deg of pick x / deg):
-    // the pick and the slot of a thread's first two cells are the same in every step. (The quotient by a
-    // multiplication, exact while x * deg < 2^32: there are at most RA_MAX_EXPAND * deg cells.)
-    const uint32_t deg_m = 0xffffffffu / (uint32_t)deg + 1u;
-    const int xr0 = min((int)__umulhi((uint32_t)tid, deg_m), expand - 1), xr1 = min((int)__umulhi((uint32_t)(tid + T), deg_m), expand - 1);
+    // the pick and the slot of a thread's first two cells are the same in every step. (The quotients by
+    // multiplications, exact while (x + 1) * deg < 2^32: there are at most RA_MAX_EXPAND * deg cells. x / deg is
+    // the upper half of (x + 1) * floor((2^32 - 1) / deg) for every degree; of x * deg_m for all but degree 1,
+    // whose steps, of two cells per thread at most, never come to the loop that uses deg_m.)
+    static_assert(RA_MAX_EXPAND <= 2 * T, "a step of a graph of degree 1 has at most two cells per thread");
+    const uint32_t deg_f = 0xffffffffu / (uint32_t)deg, deg_m = deg_f + 1u;
+    const int xr0 = min((int)__umulhi((uint32_t)tid + 1u, deg_f), expand - 1);
+    const int xr1 = min((int)__umulhi((uint32_t)(tid + T) + 1u, deg_f), expand - 1);
     const int xs0 = min(tid - xr0 * deg, deg - 1), xs1 = min(tid + T - xr1 * deg, deg - 1);
     const int gi0 = min(grp, maxc - 1), gi1 = min(grp + T / 16, maxc - 1);
     int pk0 = e0, pk1 = e0;          // the picks of those cells

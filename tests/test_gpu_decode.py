@@ -756,3 +756,32 @@ def test_root_set_much_larger_than_the_beam(dtype):
                                to_np(w.K[0, 0]), to_np(w.V[0, 0]), adj[h], ent[h], w.sink, w.window, w.topk,
                                w.ef, 64, tol, exact=exact)
         idx.free()
+
+
+@pytest.mark.parametrize("expand", [2, 8, 256])
+def test_graphs_of_degree_one(expand):
+    """The smallest degree an imported graph can have: one adjacency cell per pick. A walk has several picks
+    at once there only when it starts from a seed set (a chain of keys): each pick's own cell has to
+    be read. Integer inputs, so ids and counters are the oracle's."""
+    from paper_2409_10516_amd import binding as B
+    rng = np.random.default_rng(9)
+    N = 400
+    ring = rng.permutation(N)
+    adj = np.empty((1, N, 1), np.int32)
+    adj[0, ring, 0] = np.roll(ring, -1)
+    adj[0, ring[300], 0] = -1
+    ent = np.array([ring[0]], np.int32)
+    K = torch.from_numpy(rng.integers(-3, 4, size=(1, 1, N, 128)).astype(np.float32))
+    V = torch.from_numpy(rng.standard_normal((1, 1, N, 128)).astype(np.float32))
+    q = torch.from_numpy(rng.integers(-3, 4, size=(1, 1, 128)).astype(np.float32))
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.from_numpy(ent), 1, 1, 1)
+    for n_seeds in (0, 2, expand):
+        idx.configure(B.RA_CFG_SEEDS, n_seeds)
+        for ef in (16, 350):
+            out, lse, ids, st = ra.ra_decode_step(q.to(DEV), idx, K.to(DEV), V.to(DEV), 2, 5, 10, ef, expand)
+            ids_s, st_s = ra.ra_search(q.to(DEV), idx, K.to(DEV), 2, 5, 10, ef, expand)
+            assert torch.equal(ids_s, ids) and torch.equal(st_s, st)
+            decode_matches(out[0, 0].cpu().numpy(), float(lse[0, 0]), ids[0, 0].tolist(), st[0, 0].tolist(),
+                           to_np(q[0, 0]), to_np(K[0, 0]), to_np(V[0, 0]), adj[0], int(ent[0]), 2, 5, 10, ef, expand,
+                           1e-5, exact=True, n_seeds=n_seeds)
+    idx.free()
