@@ -131,6 +131,7 @@ static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra
     ix->seed_parts = RA_SEED_PARTS_DEFAULT;
     if (e != hipSuccess) {
         ra_set_error("allocating the graph (%zu B) failed: %s", ix->graph_bytes, hipGetErrorString(e));
+        (void)hipGetLastError();
         if (ix->adj) (void)hipFree(ix->adj);
         if (ix->entry) (void)hipFree(ix->entry);
         if (ix->coop) (void)hipFree(ix->coop);
@@ -299,6 +300,7 @@ extern "C" ra_status ra_index_import(const int32_t* adj_host, const int32_t* ent
         e = hipMemcpy(ix->entry, entries_host, graphs * sizeof(int32_t), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         ra_set_error("copying the graph to the device failed: %s", hipGetErrorString(e));
+        (void)hipGetLastError();
         ra_index_free(ix);
         return RA_EHIP;
     }
@@ -383,6 +385,7 @@ extern "C" ra_status ra_build_index(const void* K, const void* Q, ra_dtype dt, i
     hipError_t e = hipMalloc((void**)&L, l_bytes + (knn_bytes > proj_bytes ? knn_bytes : proj_bytes));
     if (e != hipSuccess) {
         ra_set_error("allocating the KNN lists failed: %s", hipGetErrorString(e));
+        (void)hipGetLastError();
         ra_index_free(ix);
         return e == hipErrorOutOfMemory ? RA_ENOMEM : RA_EHIP;
     }

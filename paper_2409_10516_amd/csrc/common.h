@@ -18,12 +18,15 @@ void ra_set_error(const char* fmt, ...);
         return (code);                \
     } while (0)
 
+// (the runtime keeps a thread's last error until it is asked for: a call that failed here must not be
+// found again by the check behind a later launch, of this library or of the caller's)
 #define RA_HIP(call)                                                              \
     do {                                                                          \
         hipError_t e_ = (call);                                                   \
         if (e_ != hipSuccess) {                                                   \
             ra_set_error("%s failed: %s (%s:%d)", #call, hipGetErrorString(e_),   \
                          __FILE__, __LINE__);                                     \
+            (void)hipGetLastError();                                              \
             return e_ == hipErrorOutOfMemory ? RA_ENOMEM : RA_EHIP;               \
         }                                                                         \
     } while (0)

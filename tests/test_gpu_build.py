@@ -390,3 +390,26 @@ def test_knn_8bit_bound_holds_at_any_scale(dtype, knn, q_exp, k_exp):
     assert np.array_equal(L[B.RA_TEST_KNN_REG], L[B.RA_TEST_KNN_LDS])
     if -118 <= q_exp + k_exp <= 100:                 # (the smallest product is 2^-8, the largest score 2^21)
         assert np.array_equal(L[B.RA_TEST_KNN_LDS], OM.knn_lists(Q, K, knn)[0])
+
+
+@pytest.mark.parametrize("call", ["ra_knn", "ra_project", "ra_build_index"])
+def test_a_call_without_enough_memory_spoils_no_later_one(call):
+    """Sizes no device has the scratch memory for: RA_ENOMEM before anything is read, and the calls that
+    follow, of this library and of torch, are as if it had not been made."""
+    import ctypes as C
+    lib = ra.lib()
+    w = synth.make_integer_case(3, N=64, M=16, d=128, n_q=2, n_kv=1, knn=4)
+    Kd, Qd = w.K.to(DEV), w.Q_prefill.to(DEV)
+    want = ra.ra_knn(Kd, Qd, 4).cpu()
+    big, p, h = 0x3fffffff, Kd.data_ptr(), C.c_void_p()
+    torch.cuda.synchronize()
+    if call == "ra_knn":
+        rc = lib.ra_knn(p, p, 0, 64, 1, 1, big, 1, 128, 8, None, p)
+    elif call == "ra_project":
+        rc = lib.ra_project(p, 64, big, 1, 8, 8, None, p, p)
+    else:
+        rc = lib.ra_build_index(p, p, 0, 64, 1, 1, big, 1, 128, 8, 8, None, C.byref(h))
+    assert rc == 4 and "memory" in lib.ra_last_error().decode()
+    assert not h.value
+    assert torch.equal(ra.ra_knn(Kd, Qd, 4).cpu(), want)
+    assert float((torch.ones(1000, device=DEV) * 2).sum()) == 2000.0
