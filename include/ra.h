@@ -70,8 +70,13 @@ typedef struct {
 /* Exact KNN of Sec. 3.2 / Fig. 2b: for every prefill query the ids of its `knn` keys of
  * largest inner product over ALL N keys of its KV head (non-causal, unscaled), ordered
  * best first; ties go to the lower id.  L_out: device int32 [n_seq][n_q_heads][M][knn].
- * Allocates scratch memory (8 bytes per key and query head, rounded up to a power of two of
- * keys) and synchronises `stream` before returning to free it. */
+ * Long key streams go through an 8-bit copy of keys and queries that rules out, by an error bound,
+ * keys that cannot be in a list; every key that enters one is scored from the inputs themselves, so the
+ * lists are those of the exact products.
+ * Allocates scratch memory and synchronises `stream` before returning to free it: 8 bytes per key and
+ * query head, rounded up to a power of two of keys, and for the 8-bit copies, where they are used, 128
+ * bytes per key and query head and 144 + 4 knn per query, for as many heads at a time as fit 1.5 GiB
+ * (at least one head). When the device has no room for the copies the lists are made without them. */
 ra_status ra_knn(const void* K, const void* Q_prefill, ra_dtype dt,
                  int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
                  int knn, void* stream, int32_t* L_out);
@@ -88,7 +93,8 @@ ra_status ra_project(const int32_t* L, int n_graphs, int64_t N, int64_t M, int k
                      void* stream, int32_t* adj, int32_t* entry);
 
 /* ra_knn followed by ra_project for every (sequence, query head); returns a handle that
- * owns the graphs. Synchronises `stream` before returning. */
+ * owns the graphs. Synchronises `stream` before returning. Scratch memory (freed before it returns): the
+ * lists, and what the larger of the two stages takes. */
 ra_status ra_build_index(const void* K, const void* Q_prefill, ra_dtype dt,
                          int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
                          int deg, int knn, void* stream, ra_index** out);

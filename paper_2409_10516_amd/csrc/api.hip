@@ -332,6 +332,19 @@ extern "C" ra_status ra_index_export(const ra_index* ix, int seq, int q_head, in
 }
 
 // ---- index build -----------------------------------------------------------------------
+// Scratch memory of a build: `most` bytes or, on a device that has not so much left, the `least` that
+// the stages can do with (*got: which).
+static hipError_t build_scratch(void** p, size_t most, size_t least, size_t* got) {
+    *got = most;
+    hipError_t e = hipMalloc(p, most);
+    if (e == hipErrorOutOfMemory && least < most) {
+        (void)hipGetLastError();
+        *got = least;
+        e = hipMalloc(p, least);
+    }
+    return e;
+}
+
 extern "C" ra_status ra_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
                             int64_t N, int64_t M, int d, int knn, void* stream, int32_t* L_out) {
     if (!K || !Q || !L_out) RA_FAIL(RA_EINVAL, "NULL argument");
@@ -340,8 +353,10 @@ extern "C" ra_status ra_knn(const void* K, const void* Q, ra_dtype dt, int n_seq
     RA_TRY(check_dim(d));
     RA_TRY(check_build_args(N, M, 2, knn, false));
     void* ws = nullptr;
-    RA_HIP(hipMalloc(&ws, ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn)));
-    ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, (hipStream_t)stream, L_out);
+    size_t ws_bytes = 0;
+    RA_HIP(build_scratch(&ws, ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false),
+                         ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, true), &ws_bytes));
+    ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, ws_bytes, (hipStream_t)stream, L_out);
     hipError_t e = hipStreamSynchronize((hipStream_t)stream);
     (void)hipFree(ws);
     if (rc != RA_OK) return rc;
@@ -379,10 +394,13 @@ extern "C" ra_status ra_build_index(const void* K, const void* Q, ra_dtype dt, i
     // One piece of scratch memory: the lists, then the workspace of the two stages, which do not use it at
     // the same time (an allocation or a free of a large piece is a quarter of a millisecond).
     const size_t l_bytes = ((size_t)graphs * M * knn * sizeof(int32_t) + 255) & ~(size_t)255;
-    const size_t knn_bytes = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn);
+    const size_t knn_bytes = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false);
+    const size_t knn_plain = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, true);
     const size_t proj_bytes = ra_project_workspace_bytes(graphs, N, M, knn);
     int32_t* L = nullptr;
-    hipError_t e = hipMalloc((void**)&L, l_bytes + (knn_bytes > proj_bytes ? knn_bytes : proj_bytes));
+    size_t got = 0;
+    hipError_t e = build_scratch((void**)&L, l_bytes + (knn_bytes > proj_bytes ? knn_bytes : proj_bytes),
+                                 l_bytes + (knn_plain > proj_bytes ? knn_plain : proj_bytes), &got);
     if (e != hipSuccess) {
         ra_set_error("allocating the KNN lists failed: %s", hipGetErrorString(e));
         (void)hipGetLastError();
@@ -390,7 +408,7 @@ extern "C" ra_status ra_build_index(const void* K, const void* Q, ra_dtype dt, i
         return e == hipErrorOutOfMemory ? RA_ENOMEM : RA_EHIP;
     }
     void* ws = reinterpret_cast<char*>(L) + l_bytes;
-    ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, (hipStream_t)stream, L);
+    ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, got - l_bytes, (hipStream_t)stream, L);
     if (rc == RA_OK)
         rc = ra_launch_project(L, graphs, N, M, knn, deg, ws, (hipStream_t)stream, ix->adj, ix->entry);
     if (rc == RA_OK)

@@ -144,9 +144,10 @@ ra_status ra_launch_flat_topk(const void* q, const void* K, ra_dtype dt, int n_s
                               hipStream_t st, int32_t* ids);
 
 // `workspace`: ra_knn_workspace_bytes(...) bytes of device memory, free again once the stream has run
-// the launch
+// the launch; with only as many as `plain` asks for, the lists come without 8-bit products
 ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
-                        int64_t N, int64_t M, int knn, void* workspace, hipStream_t st, int32_t* L);
+                        int64_t N, int64_t M, int knn, void* workspace, size_t workspace_bytes, hipStream_t st,
+                        int32_t* L);
 // the long part of the key stream through 8-bit products (knn_filter.hip)
 size_t ra_knn_filter_bytes(int graphs, int64_t N, int64_t M, int knn);
 float* ra_knn_filter_scores(void* workspace, int graphs, int64_t N, int64_t M, int knn);
@@ -157,7 +158,7 @@ ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const 
                                const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
                                const int** resume, int* resume_queries, int* resume_blocks);
 void ra_knn_set_selection_override(int v);      // RA_TEST_KNN_AUTO / _FILTER / _LDS
-size_t ra_knn_workspace_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn);
+size_t ra_knn_workspace_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn, bool plain);
 int64_t ra_sort_padded(int64_t N);                 // the power of two (at least 2) ra_launch_sort wants
 ra_status ra_launch_sort(void* keys, size_t stride, int n_arrays, int64_t N_pad, const int32_t* counts,
                          size_t count_stride, hipStream_t st);

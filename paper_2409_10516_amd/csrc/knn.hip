@@ -565,24 +565,27 @@ static int knn_graphs_at_once(int graphs, int64_t N, int64_t M, int knn) {
 }
 static size_t align_256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// the stream order, then (where the filter is used) the column maxima of the KV heads and the
-// filter's own workspace
-size_t ra_knn_workspace_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn) {
+// the stream order, then (where the filter is used, and not `plain`) the column maxima of the KV heads and
+// the filter's own workspace
+size_t ra_knn_workspace_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn, bool plain) {
     const int graphs = n_seq * n_q;
     size_t b = align_256(ra_knn_order_bytes(graphs, N));
-    if (knn_first_keys(dt, N, M) < N)
+    if (!plain && knn_first_keys(dt, N, M) < N)
         b += align_256((size_t)n_seq * n_kv * RA_D * 4) +
              ra_knn_filter_bytes(knn_graphs_at_once(graphs, N, M, knn), N, M, knn);
     return b;
 }
 
 ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
-                        int64_t N, int64_t M, int knn, void* workspace, hipStream_t st, int32_t* L) {
+                        int64_t N, int64_t M, int knn, void* workspace, size_t workspace_bytes, hipStream_t st,
+                        int32_t* L) {
     // the order the keys are streamed in (knn_order.hip), at the start of the workspace
     ra_status rc = ra_launch_knn_order(K, Q, dt, n_seq, n_q, n_kv, N, M, workspace, st);
     if (rc != RA_OK) return rc;
     const int graphs = n_seq * n_q;
-    const int64_t first = knn_first_keys(dt, N, M);
+    // (without room for the 8-bit copies the whole stream is multiplied as it is: the same lists)
+    const bool room = workspace_bytes >= ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false);
+    const int64_t first = room ? knn_first_keys(dt, N, M) : N;
     KnnCall c{K, Q, workspace, 0, graphs, n_q, n_kv, N, first, M, knn, L, nullptr, st, nullptr, 0, 0};
     if (first == N) return knn_launch(c, dt);
     char* ws = reinterpret_cast<char*>(workspace) + align_256(ra_knn_order_bytes(graphs, N));

@@ -413,3 +413,32 @@ def test_a_call_without_enough_memory_spoils_no_later_one(call):
     assert not h.value
     assert torch.equal(ra.ra_knn(Kd, Qd, 4).cpu(), want)
     assert float((torch.ones(1000, device=DEV) * 2).sum()) == 2000.0
+
+
+def test_knn_without_room_for_the_8bit_copies():
+    """A device too full for the copies the 8-bit products need, with room for the rest: the same lists."""
+    N, n_q, knn = 131072, 8, 32
+    w = synth.make_llama_layer(4, N, 1500, n_seq=1, n_q=n_q, n_kv=2, device=DEV)
+    want = ra.ra_knn(w.K, w.Q_prefill, knn)          # (the copies are used at this size)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    full, leave, step = [], 80 << 20, 64 << 30
+    try:
+        while step >= 4 << 20:
+            free = torch.cuda.mem_get_info()[0]
+            if free <= leave + (4 << 20):
+                break
+            step = min(step, free - leave)
+            try:
+                full.append(torch.empty(step, dtype=torch.uint8, device=DEV))
+            except torch.cuda.OutOfMemoryError:
+                step //= 2
+        free = torch.cuda.mem_get_info()[0]
+        assert 40 << 20 < free < n_q * N * 128       # (what the copies of the keys alone take)
+        got = torch.empty_like(want)
+        rc = ra.lib().ra_knn(w.K.data_ptr(), w.Q_prefill.data_ptr(), 1, 1, n_q, 2, N, 1500, 128, knn, None, got.data_ptr())
+        assert rc == 0, ra.lib().ra_last_error()
+        assert torch.equal(got, want)
+    finally:
+        full.clear()
+        torch.cuda.empty_cache()
