@@ -331,8 +331,7 @@ ra_status ra_index_configure(ra_index* idx, int what, int64_t value);
  *   RA_TEST_KNN_SELECTION   (idx = NULL; process-wide) whether ra_knn takes the later part of its key
  *                           stream through 8-bit products that rule keys out: RA_TEST_KNN_AUTO
  *                           (default: chosen by the sizes), RA_TEST_KNN_LDS (never),
- *                           RA_TEST_KNN_FILTER (from the 129th key on; RA_TEST_KNN_REG is another
- *                           name of it). Same lists either way.
+ *                           RA_TEST_KNN_FILTER (from the 129th key on). Same lists either way.
  *   RA_TEST_HELPERS_SILENT  (per handle) 1: the helper and seed workgroups of ra_decode_step are
  *                           launched but write nothing, so every head's bounded wait runs out and
  *                           the fall-back is taken; 0: normal. Synchronises the device and clears
@@ -341,7 +340,6 @@ ra_status ra_index_configure(ra_index* idx, int what, int64_t value);
 #define RA_TEST_HELPERS_SILENT 101
 #define RA_TEST_KNN_AUTO 0
 #define RA_TEST_KNN_FILTER 1
-#define RA_TEST_KNN_REG RA_TEST_KNN_FILTER
 #define RA_TEST_KNN_LDS 2
 ra_status ra_test_configure(ra_index* idx, int what, int64_t value);
 

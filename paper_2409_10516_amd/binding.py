@@ -22,7 +22,7 @@ RA_CFG_HELPERS, RA_CFG_HELPER_SPIN, RA_CFG_SEEDS, RA_CFG_SEED_SHARES = 0, 1, 2, 
 RA_HELPERS_OFF, RA_HELPERS_ON = 0, 1
 # test-only settings (ra_test_configure)
 RA_TEST_KNN_SELECTION, RA_TEST_HELPERS_SILENT = 100, 101
-RA_TEST_KNN_AUTO, RA_TEST_KNN_REG, RA_TEST_KNN_LDS = 0, 1, 2
+RA_TEST_KNN_AUTO, RA_TEST_KNN_FILTER, RA_TEST_KNN_LDS = 0, 1, 2
 STATUS = {0: "RA_OK", 1: "RA_EINVAL", 2: "RA_ESHAPE", 3: "RA_EDTYPE", 4: "RA_ENOMEM",
           5: "RA_EHIP", 6: "RA_EUNSUP"}
 

@@ -17,14 +17,14 @@ DEV = "cuda:0"
 GOLD = os.path.join(os.path.dirname(__file__), "golden")
 
 
-@pytest.fixture(params=["reg", "lds"])
+@pytest.fixture(params=["filter", "lds"])
 def knn_selection(request):
-    """Lists of up to 32 bf16 keys have two selections (pending keys in registers, two query sets per
-    wavefront / pending runs in LDS); the library picks by the number of keys, the tests force each
-    through the test-only setting."""
+    """The later part of a long key stream goes through 8-bit products that rule keys out; the library
+    decides by the sizes, the tests force them on (from the 129th key) or off through the test-only
+    setting."""
     from paper_2409_10516_amd import binding as B
     ra.ra_test_configure(B.RA_TEST_KNN_SELECTION,
-                         B.RA_TEST_KNN_REG if request.param == "reg" else B.RA_TEST_KNN_LDS)
+                         B.RA_TEST_KNN_FILTER if request.param == "filter" else B.RA_TEST_KNN_LDS)
     yield request.param
     ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_AUTO)
 
@@ -325,23 +325,54 @@ def test_projection_row_kernels_at_their_limits(kind):
 def test_knn_through_8bit_products(dtype, N, M, knn):
     """The later part of the key stream ruled out by 8-bit products (from the 129th key on): one key or a
     ragged stage past the first part, fewer queries than a set, sets and workgroups that end
-    ragged, lists of every selection, and (knn 64 of 255 keys) keys the bound cannot rule out, where the
-    filter gives up and the stream goes on without it. The lists are those of the whole stream, bit for
-    bit, and the oracle's."""
+    ragged, lists of every selection. The lists are those of the whole stream, bit for bit, and the
+    oracle's. (Streams that the products give up on: test_knn_filter_gives_up.)"""
     from paper_2409_10516_amd import binding as B
     w = synth.make_llama_layer(N + knn, N, M, n_seq=2, n_q=2, n_kv=1, dtype=dtype)
     K, Q = w.K.to(DEV), w.Q_prefill.to(DEV)
     L = {}
     try:
-        for how in (B.RA_TEST_KNN_LDS, B.RA_TEST_KNN_REG):
+        for how in (B.RA_TEST_KNN_LDS, B.RA_TEST_KNN_FILTER):
             ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, how)
             L[how] = ra.ra_knn(K, Q, knn).cpu().numpy()
     finally:
         ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_AUTO)
-    assert np.array_equal(L[B.RA_TEST_KNN_LDS], L[B.RA_TEST_KNN_REG])
+    assert np.array_equal(L[B.RA_TEST_KNN_LDS], L[B.RA_TEST_KNN_FILTER])
     assert np.array_equal(L[B.RA_TEST_KNN_LDS], ra.ra_knn(K, Q, knn).cpu().numpy())
     Kn, Qn = to_np(w.K[1, 0]), to_np(w.Q_prefill[1, 1][:40])
-    knn_equivalent(L[B.RA_TEST_KNN_REG][1, 1][:40], OM.knn_lists(Qn, Kn, knn)[0], Qn, Kn)
+    knn_equivalent(L[B.RA_TEST_KNN_FILTER][1, 1][:40], OM.knn_lists(Qn, Kn, knn)[0], Qn, Kn)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("knn", [32, 64])
+@pytest.mark.parametrize("N,ruled_out", [(384, 0), (385, 0), (511, 0), (900, 0), (1152, 256), (1153, 256), (2600, 256)])
+def test_knn_filter_gives_up(dtype, knn, N, ruled_out):
+    """Streams of which a workgroup cannot rule out an eighth: it stops after two stages of 128 keys, or, with
+    the first 256 keys ruled out, after eight, and the exact products go on from there. That they stop is
+    certain: for the queries that look at the first half of the dimensions (some in every set of 32) each
+    key past those 256 ties with the first part of the stream or beats it, and a key that reaches a
+    threshold may not be ruled out; the 256 score sum |u| below it and are exact in 8 bits. Nothing,
+    one key or many are left then, and the last keys of the stream are the best of all. Integer inputs:
+    the oracle's lists."""
+    from paper_2409_10516_amd import binding as B
+    rng = np.random.default_rng(32)
+    M = 300
+    u = rng.integers(1, 128, 128) * rng.choice([-1, 1], 128)
+    u[[0, 64]] = 127
+    place = rng.permutation(N)                       # in the stream
+    t = np.where(place < 128, 50, np.where(place < 128 + ruled_out, 49, np.where(place < N - 40, 50, 51 + place % 4)))
+    K = np.concatenate([np.repeat(t[:, None], 64, 1), np.repeat(100 - place[:, None] // 16, 64, 1)], 1) * np.sign(u)
+    K[place == 5] = 127 * np.sign(u)
+    first_half = np.arange(M) % 10 == 9              # (few: the mean query goes by the other half)
+    Q = np.where(first_half[:, None] == (np.arange(128) < 64)[None, :], u[None, :], 0)
+    try:
+        ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_FILTER)
+        got = ra.ra_knn(torch.from_numpy(K).to(dtype).to(DEV)[None, None],
+                        torch.from_numpy(Q).to(dtype).to(DEV)[None, None], knn).cpu().numpy()[0, 0]
+    finally:
+        ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_AUTO)
+    ref = OM.knn_lists(Q[:10], K, knn)[0]
+    assert np.array_equal(got, ref[np.arange(M) % 10])
 
 
 # powers of two that queries and keys are multiplied by, down to where scores leave the normal range and up
@@ -382,12 +413,12 @@ def test_knn_8bit_bound_holds_at_any_scale(dtype, knn, q_exp, k_exp):
     Qd = (torch.from_numpy(Q) * 2.0 ** q_exp).to(dtype).to(DEV)[None, None]
     L = {}
     try:
-        for how in (B.RA_TEST_KNN_LDS, B.RA_TEST_KNN_REG):
+        for how in (B.RA_TEST_KNN_LDS, B.RA_TEST_KNN_FILTER):
             ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, how)
             L[how] = ra.ra_knn(Kd, Qd, knn).cpu().numpy()[0, 0]
     finally:
         ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_AUTO)
-    assert np.array_equal(L[B.RA_TEST_KNN_REG], L[B.RA_TEST_KNN_LDS])
+    assert np.array_equal(L[B.RA_TEST_KNN_FILTER], L[B.RA_TEST_KNN_LDS])
     if -118 <= q_exp + k_exp <= 100:                 # (the smallest product is 2^-8, the largest score 2^21)
         assert np.array_equal(L[B.RA_TEST_KNN_LDS], OM.knn_lists(Q, K, knn)[0])
 
