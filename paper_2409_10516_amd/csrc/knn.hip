@@ -20,8 +20,8 @@
 // Between two merges a threshold is stale but valid (never above the true one), so nothing is
 // lost.
 //
-// A wavefront owns NQ x 32 queries for the whole key stream (their B operands stay in registers,
-// and every key operand fetched feeds NQ MFMA chains); a workgroup is WAVES wavefronts. Lists hold
+// A wavefront owns 32 queries for the whole key stream (their B operands stay in registers); a
+// workgroup is WAVES wavefronts. Lists hold
 // 64-bit keys [ordered(score):32][~id:32], so "larger key" is "(score descending, id ascending)".
 // The inner-product summation order is the hardware's; identical key rows still score
 // identically for a given query because they go through the same instruction sequence.
@@ -214,15 +214,14 @@ __device__ __forceinline__ void store_chunk(unsigned char* buf, int tid, int i, 
     *reinterpret_cast<u32x4*>(buf + row * ROWB + ((c ^ (row & 15)) << 4)) = v;
 }
 
-// grid: x = block of NQ * 32 * WAVES queries, y = graph (seq * n_q + h) - g0. The keys are the first
+// grid: x = block of 32 * WAVES queries, y = graph (seq * n_q + h) - g0. The keys are the first
 // n_stream of the graph's stream order. With `scores` and no `resume` the lists' scores are written
 // too, for knn_filter.hip, which takes the rest of the stream; with `resume` (first stream position not
 // yet seen, per graph and block of resume_queries queries) the lists are read from L_out and scores and
-// the stream goes on from there. A wavefront owns NQ sets of 32 queries, so every key operand it reads
-// feeds NQ MFMA chains.
-// LDS: [NQ * 32 * WAVES][list slots] lists, then two stage buffers of STAGE bytes.
+// the stream goes on from there.
+// LDS: [32 * WAVES][list slots] lists, then two stage buffers of STAGE bytes.
 // SEL (KN_SEL_*) selects how keys wait for their list.
-template <int DT, int NQ, int WAVES, int SEL, int STAGE>
+template <int DT, int WAVES, int SEL, int STAGE>
 __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     const void* __restrict__ K, const void* __restrict__ Q, const u64* __restrict__ order,
     int64_t order_stride, int g0, int n_q, int n_kv, int64_t N, int64_t n_stream, int64_t M, int knn,
@@ -230,7 +229,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     int resume_blocks) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     constexpr int KN_THREADS = WAVES * RA_WAVE;
-    constexpr int QPW = 32 * NQ, QPB = QPW * WAVES;
+    constexpr int QPB = 32 * WAVES;
     constexpr int ROWB = DT == RA_BF16 ? 256 : 512;          // bytes of a key row
     constexpr int CPR = ROWB / 16;                            // 16-byte chunks per row
     constexpr int SROWS = STAGE / ROWB;              // key rows per stage
@@ -250,7 +249,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     const size_t esz = DT == RA_BF16 ? 2 : 4;
     const char* Kh = reinterpret_cast<const char*>(K) + ((size_t)seq * n_kv + kvh) * N * RA_D * esz;
     const char* Qh = reinterpret_cast<const char*>(Q) + (size_t)graph * M * RA_D * esz;
-    const int64_t q0 = (int64_t)blockIdx.x * QPB + wv * QPW;   // first query of this wave
+    const int64_t q0 = (int64_t)blockIdx.x * QPB + wv * 32;   // first query of this wave
     // the key streamed p-th: the low word of the head's p-th order entry (used as loaded: arithmetic
     // on it would sit right behind the load and wait for it)
     const int* ord = reinterpret_cast<const int*>(order + (size_t)graph * order_stride);
@@ -275,27 +274,16 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
         }
         lists[i] = k;
     }
-    u64* my_lists = lists + (size_t)wv * QPW * lstride;
+    u64* my_lists = lists + (size_t)wv * 32 * lstride;
 
-    Operand<DT> b[NQ];
-#pragma unroll
-    for (int sidx = 0; sidx < NQ; ++sidx) {
-        int64_t qr = q0 + sidx * 32 + col;
-        if (qr >= M) qr = M - 1;                   // clamp loads; such columns are never written
-        load_operand<DT>(Qh, qr, half, b[sidx]);
-    }
-#pragma unroll
-    for (int sidx = 0; sidx < NQ; ++sidx) settle_operand<DT>(b[sidx]);
+    Operand<DT> b;                                 // (loads clamped: columns beyond M are never written)
+    load_operand<DT>(Qh, q0 + col < M ? q0 + col : M - 1, half, b);
+    settle_operand<DT>(b);
     __syncthreads();
 
-    float tau[NQ];
-    int fill[NQ];                                  // BUF: keys in this lane's pending run
-#pragma unroll
-    for (int sidx = 0; sidx < NQ; ++sidx) {
-        const u64 last = my_lists[(sidx * 32 + col) * lstride + knn - 1];     // (zero but for a resumed stream)
-        tau[sidx] = last == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(last >> 32));
-        fill[sidx] = 0;
-    }
+    const u64 last_key = my_lists[col * lstride + knn - 1];          // (zero but for a resumed stream)
+    float tau = last_key == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(last_key >> 32));
+    int fill = 0;                                  // BUF: keys in this lane's pending run
 
     static_assert(CPT == 2 || CPT == 4, "two or four chunks per thread and stage");
     const int64_t nstage = (n_stream + SROWS - 1) / SROWS;
@@ -333,81 +321,73 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
             store_chunk<DT, KN_THREADS>(buf, tid, 3, h.c3);
         }
     };
-    // scores of one 32-key block against the wave's NQ query sets, then the selection
+    // scores of one 32-key block against the wave's queries, then the selection
     // (kb: the block's place in the stream; ids: stage_ids of its stage; first: its first row there)
     auto process = [&](const Operand<DT>& a, int64_t kb, int ids, int first) __attribute__((always_inline)) {
-        f32x16 c[NQ];
-#pragma unroll
-        for (int sidx = 0; sidx < NQ; ++sidx) c[sidx] = block_scores<DT>(a, b[sidx]);
+        f32x16 cs = block_scores<DT>(a, b);
         const int64_t kbase = kb * 32;
+        if (kbase + 32 > n_stream) {               // ragged tail: rows beyond the stream never qualify
 #pragma unroll
-        for (int sidx = 0; sidx < NQ; ++sidx) {
-            f32x16& cs = c[sidx];
-            if (kbase + 32 > n_stream) {           // ragged tail: rows beyond the stream never qualify
+            for (int r = 0; r < 16; ++r)
+                if (kbase + (r / 4) * 8 + half * 4 + (r % 4) >= n_stream) cs[r] = -INFINITY;
+        }
+        if constexpr (BUF) {
+            float gm[4];
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (kbase + (r / 4) * 8 + half * 4 + (r % 4) >= n_stream) cs[r] = -INFINITY;
-            }
-            if constexpr (BUF) {
-                float gm[4];
+            for (int g = 0; g < 4; ++g)
+                gm[g] = fmaxf(fmaxf(cs[4 * g], cs[4 * g + 1]), fmaxf(cs[4 * g + 2], cs[4 * g + 3]));
+            const float mx = fmaxf(fmaxf(gm[0], gm[1]), fmaxf(gm[2], gm[3]));
+            if (__ballot(mx >= tau) == 0ull) return;
+            u64* mine = my_lists + (size_t)col * KN_CAP + knn + half * pend;     // KN_SEL_LDS
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    gm[g] = fmaxf(fmaxf(cs[4 * g], cs[4 * g + 1]), fmaxf(cs[4 * g + 2], cs[4 * g + 3]));
-                const float mx = fmaxf(fmaxf(gm[0], gm[1]), fmaxf(gm[2], gm[3]));
-                if (__ballot(mx >= tau[sidx]) == 0ull) continue;
-                u64* set_lists = my_lists + (size_t)sidx * 32 * lstride;
-                u64* mine = set_lists + (size_t)col * KN_CAP + knn + half * pend;    // KN_SEL_LDS
+            for (int g = 0; g < 4; ++g) {
+                if (__ballot(gm[g] >= tau) == 0ull) continue;
+                // a lane needs room for the keys of this group that reach its threshold: fold the
+                // queries short of it (the count can only fall when a fold raises the threshold)
+                int n4 = 0;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    if (__ballot(gm[g] >= tau[sidx]) == 0ull) continue;
-                    // a lane needs room for the keys of this group that reach its threshold: fold the
-                    // queries short of it (the count can only fall when a fold raises the threshold)
-                    int n4 = 0;
+                for (int r = 4 * g; r < 4 * g + 4; ++r) n4 += cs[r] >= tau ? 1 : 0;
+                u64 need = __ballot(fill + n4 > pend);
+                while (need) {
+                    const int jq = (__ffsll((long long)need) - 1) & 31;
+                    const float nt = knn_fold(my_lists + (size_t)jq * KN_CAP, knn, lane);
+                    if (col == jq) { tau = nt; fill = 0; }
+                    need &= need - 1;
+                    need &= ~(1ull << (jq + 32)) & ~(1ull << jq);
+                }
 #pragma unroll
-                    for (int r = 4 * g; r < 4 * g + 4; ++r) n4 += cs[r] >= tau[sidx] ? 1 : 0;
-                    u64 need = __ballot(fill[sidx] + n4 > pend);
-                    while (need) {
-                        const int jq = (__ffsll((long long)need) - 1) & 31;
-                        const float nt = knn_fold(set_lists + (size_t)jq * KN_CAP, knn, lane);
-                        if (col == jq) { tau[sidx] = nt; fill[sidx] = 0; }
-                        need &= need - 1;
-                        need &= ~(1ull << (jq + 32)) & ~(1ull << jq);
-                    }
-#pragma unroll
-                    for (int r = 4 * g; r < 4 * g + 4; ++r) {
-                        if (cs[r] >= tau[sidx] && cs[r] > -INFINITY) {
-                            // the row's id sits in lane `row` of ids (lower half-wave) or four lanes
-                            // on (upper): both are read as scalars, then chosen without a branch
-                            const int row = first + (r / 4) * 8 + (r % 4);
-                            const int lo = __builtin_amdgcn_readlane(ids, row);
-                            const int hi = __builtin_amdgcn_readlane(ids, row + 4);
-                            const u64 nk = knn_key(cs[r], lo ^ ((lo ^ hi) & -half));
-                            if (fill[sidx] < pend) mine[fill[sidx]++] = nk;      // always, for scores that are numbers
-                        }
+                for (int r = 4 * g; r < 4 * g + 4; ++r) {
+                    if (cs[r] >= tau && cs[r] > -INFINITY) {
+                        // the row's id sits in lane `row` of ids (lower half-wave) or four lanes
+                        // on (upper): both are read as scalars, then chosen without a branch
+                        const int row = first + (r / 4) * 8 + (r % 4);
+                        const int lo = __builtin_amdgcn_readlane(ids, row);
+                        const int hi = __builtin_amdgcn_readlane(ids, row + 4);
+                        const u64 nk = knn_key(cs[r], lo ^ ((lo ^ hi) & -half));
+                        if (fill < pend) mine[fill++] = nk;      // always, for scores that are numbers
                     }
                 }
-            } else {
+            }
+        } else {
             float mx = fmaxf(cs[0], cs[1]);
 #pragma unroll
             for (int r = 2; r < 16; ++r) mx = fmaxf(mx, cs[r]);
-            if (__ballot(mx >= tau[sidx]) == 0ull) continue;
+            if (__ballot(mx >= tau) == 0ull) return;
             // insertion path (rare after the first few blocks)
-            u64* set_lists = my_lists + (size_t)sidx * 32 * knn;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                u64 mask = __ballot(cs[r] >= tau[sidx] && cs[r] > -INFINITY);
+                u64 mask = __ballot(cs[r] >= tau && cs[r] > -INFINITY);
                 while (mask) {
                     const int src = __ffsll((long long)mask) - 1;
                     const float sc = __shfl(cs[r], src);
                     const int id =
                         __builtin_amdgcn_readlane(ids, first + (r / 4) * 8 + (src >> 5) * 4 + (r % 4));
                     const int jq = src & 31;
-                    const float nt = knn_insert(set_lists + (size_t)jq * knn, knn, sc, id, lane);
-                    if (col == jq) tau[sidx] = nt;
+                    const float nt = knn_insert(my_lists + (size_t)jq * knn, knn, sc, id, lane);
+                    if (col == jq) tau = nt;
                     mask &= mask - 1;
-                    mask &= __ballot(cs[r] >= tau[sidx] && cs[r] > -INFINITY);
+                    mask &= __ballot(cs[r] >= tau && cs[r] > -INFINITY);
                 }
-            }
             }
         }
     };
@@ -476,22 +456,18 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
         load_rows(rb, st + 6);
     }
     // write the ids, best first
-#pragma unroll
-    for (int sidx = 0; sidx < NQ; ++sidx) {
-        for (int j = 0; j < 32; ++j) {
-            const int jq = sidx * 32 + j;
-            const int64_t qr = q0 + jq;
-            if (qr >= M) break;
-            u64* lst = my_lists + (size_t)jq * lstride;
-            if constexpr (BUF)
-                knn_fold(lst, knn, lane);
-            if (lane < knn) {
-                const u64 k = lst[lane];
-                L_out[((size_t)graph * M + qr) * knn + lane] = knn_key_id(k);
-                if (scores && !resume)             // only the first part of the stream: it goes on with these
-                    scores[((size_t)blockIdx.y * M + qr) * knn + lane] =
-                        k == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(k >> 32));
-            }
+    for (int jq = 0; jq < 32; ++jq) {
+        const int64_t qr = q0 + jq;
+        if (qr >= M) break;
+        u64* lst = my_lists + (size_t)jq * lstride;
+        if constexpr (BUF)
+            knn_fold(lst, knn, lane);
+        if (lane < knn) {
+            const u64 k = lst[lane];
+            L_out[((size_t)graph * M + qr) * knn + lane] = knn_key_id(k);
+            if (scores && !resume)                 // only the first part of the stream: it goes on with these
+                scores[((size_t)blockIdx.y * M + qr) * knn + lane] =
+                    k == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(k >> 32));
         }
     }
 }
@@ -508,16 +484,16 @@ struct KnnCall {
     const int* resume;
     int resume_queries, resume_blocks;
 };
-template <int DT, int NQ, int WAVES, int SEL, int STAGE>
+template <int DT, int WAVES, int SEL, int STAGE>
 static ra_status knn_launch_as(const KnnCall& c) {
-    constexpr int QPB = 32 * NQ * WAVES;
+    constexpr int QPB = 32 * WAVES;
     const int slots = SEL == KN_SEL_LDS ? KN_CAP : c.knn;
     const size_t lds = (size_t)QPB * slots * sizeof(u64) + 2 * STAGE;
     if (lds > RA_LDS_LIMIT)
         RA_FAIL(RA_EUNSUP, "knn %d needs %zu bytes of LDS (limit %d)", c.knn, lds, RA_LDS_LIMIT);
-    RA_LDS_OPT_IN((knn_kernel<DT, NQ, WAVES, SEL, STAGE>), lds);
+    RA_LDS_OPT_IN((knn_kernel<DT, WAVES, SEL, STAGE>), lds);
     const dim3 grid((unsigned)((c.M + QPB - 1) / QPB), (unsigned)c.n_graphs);
-    hipLaunchKernelGGL((knn_kernel<DT, NQ, WAVES, SEL, STAGE>), grid, dim3(WAVES * RA_WAVE), lds, c.st, c.K, c.Q,
+    hipLaunchKernelGGL((knn_kernel<DT, WAVES, SEL, STAGE>), grid, dim3(WAVES * RA_WAVE), lds, c.st, c.K, c.Q,
                        reinterpret_cast<const u64*>(c.order), ra_knn_order_stride(c.N), c.g0, c.n_q, c.n_kv, c.N,
                        c.n_stream, c.M, c.knn, c.L, c.scores, c.resume, c.resume_queries, c.resume_blocks);
     RA_HIP(hipGetLastError());
@@ -534,11 +510,11 @@ void ra_knn_set_selection_override(int v) { g_knn_selection_override = v; }
 static ra_status knn_launch(const KnnCall& c, ra_dtype dt) {
     const bool buf = c.knn <= KN_BUFFERED_KNN;
     if (dt == RA_BF16) {
-        if (buf) return knn_launch_as<RA_BF16, 1, 8, KN_SEL_LDS, 16384>(c);
-        return knn_launch_as<RA_BF16, 1, 8, KN_SEL_INSERT, 16384>(c);
+        if (buf) return knn_launch_as<RA_BF16, 8, KN_SEL_LDS, 16384>(c);
+        return knn_launch_as<RA_BF16, 8, KN_SEL_INSERT, 16384>(c);
     }
-    if (buf) return knn_launch_as<RA_F32, 1, 4, KN_SEL_LDS, 16384>(c);
-    return knn_launch_as<RA_F32, 1, 4, KN_SEL_INSERT, 16384>(c);
+    if (buf) return knn_launch_as<RA_F32, 4, KN_SEL_LDS, 16384>(c);
+    return knn_launch_as<RA_F32, 4, KN_SEL_INSERT, 16384>(c);
 }
 
 // Keys of the stream that are multiplied as they are before knn_filter.hip takes over (N: all of them).
