@@ -135,9 +135,16 @@ static int long_heads(ra_dtype dt, int G) { return G == 2 || G == 4 ? G : G == 8
 // The same for the decode step's sets, in a launch of `records` records. A launch of few workgroups is
 // bound by its latency, and a static chunk for g heads takes g times the arithmetic and closes g
 // records one after the other: every query head reads its static rows itself then (the heads of a
-// group find them in the L2). Beyond, bf16 takes two heads (32 heads on 8, 16 sequences, 640 static rows
-// and 100 more: 31 us; four heads 38, one 35; 32 on 4: 31 against 59 us with eight), float32 as many as
-// its wider rows make worth while (same sizes: 42.7 us with four heads, 44.8 with two, 60 with one).
+// group find them in the L2). Beyond, bf16 takes two heads, float32, with rows twice as wide, two and then four.
+// Measured (us per call, 32 query heads, 100 retrieved rows; 1 / 2 / 4 / 8 heads):
+//   bf16, 640 static rows, G 4: 416 records 10.7 / 12.9 / 21.0, 832 10.4 / 10.7 / 14.0, 1664 15.8 / 14.7 / 16.3,
+//     3328 22.2 / 21.1 / 24.5, 13312 63 / 56 / 68; G 2 and 8 within 3 % of these; G 8 with eight heads 38, 17, 22, 34, 108.
+//   float32, 640 static rows, G 4: 416 records 11.1 / 13.3 / 21.4, 832 16.4 / 11.7 / 15.0, 1664 23.0 / 19.8 / 18.6,
+//     3328 36 / 28.5 / 28.1, 13312 119 / 89 / 84; G 8: 832 16.4 / 11.6 / 14.9 / 18.5, 1664 22.9 / 19.4 / 18.7 / 24.5.
+// What the lines rest on is the number of records alone: one head up to about 1000 (bf16) and 500 (float32), whatever G
+// is. The lines below grow with G, so some launches between are not served best: bf16, G 4 and 8, 1664 records (15.8
+// where two heads take 14.7); float32, G 2, 192 to 416 records (12.3 to 13.4 where one head takes 8.7 to 11.2), and G 8,
+// 832 and 1664 records (16.4 and 22.9 where two take 11.6 and four 18.7).
 static int short_heads(ra_dtype dt, int G, int64_t records) {
     if (G != 2 && G != 4 && G != 8) return 1;
     if (records <= (dt == RA_BF16 ? 512 * G : 32 * G * G)) return 1;

@@ -520,10 +520,18 @@ static ra_status knn_launch(const KnnCall& c, ra_dtype dt) {
 // Keys of the stream that are multiplied as they are before knn_filter.hip takes over (N: all of them).
 // A thirty-second of the stream, and at least enough that thresholds are near final (in the filter a
 // kept key costs about ten ruled-out ones). The filter pays where what it saves on N x M products
-// exceeds what packing N keys and M queries costs: bf16 halves the time of a product (32 heads of 36 K
-// keys: 10.6 -> 7.0 ms with 32 K queries, 3.4 -> 2.7 ms with 8 K, but 1.2 -> 1.5 ms with 2 K; 72 K keys
-// gain with 512 queries already, 2.8 -> 2.3 ms), float32 products cost sixteen times the 8-bit ones
-// (9 K keys, 512 queries: 0.95 -> 0.67 ms; 4 K keys gain little either way).
+// exceeds what packing N keys and M queries and the larger scratch allocation cost. Whole calls of ra_knn, lists of
+// 32, ms without -> with:
+//   bf16, 32 heads: 16K keys x 8K queries 1.58 -> 1.60, x 16K 2.90 -> 2.64; 32K x 4K 1.54 -> 1.62, x 8K 2.65 -> 2.14,
+//     x 32K 9.6 -> 6.5; 40K x 4K 1.87 -> 1.88; 48K x 2K 1.32 -> 1.65, x 3K 2.01 -> 1.94, x 8K 3.78 -> 2.76;
+//     128K x 512 2.45 -> 3.21, x 2K 2.95 -> 3.22, x 3K 4.87 -> 3.90, x 8K 9.31 -> 5.50.
+//   bf16, 8 heads: 48K x 8K 1.13 -> 1.31, x 16K 1.94 -> 1.68; 1M x 4K 15.7 -> 16.1, x 8K 18.7 -> 16.1;
+//     4 heads: within a tenth of each other up to 8K queries; 48K x 16K 1.10 -> 0.98 (1M x 64K, lists of 48: 74.7 -> 49.9).
+//   float32 (a product costs sixteen 8-bit ones): 4K keys gain little (8 heads x 512 queries 0.42 -> 0.42, x 16K 1.55 ->
+//     1.17); 8K gain with one head and 512 queries already (0.73 -> 0.44); 32 heads, 16K x 8K 9.7 -> 3.0.
+// What decides in bf16 is the number of queries in all heads together, about 100K from 48K keys on and 260K below; the
+// line takes the queries of one head below 48K keys (32 heads: the same) and none from there on, which
+// costs calls with few queries up to 0.9 ms.
 static int64_t knn_first_keys(ra_dtype dt, int64_t N, int64_t M) {
     int64_t first = dt == RA_BF16 ? 4096 : 2048;
     if (g_knn_selection_override == RA_TEST_KNN_LDS) return N;

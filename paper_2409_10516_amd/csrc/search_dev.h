@@ -1301,15 +1301,27 @@ __device__ __forceinline__ int run_search(
 }
 
 
-// Threads per search, of a launch of `heads` searches whose steps read up to `cells` adjacency cells. What a
-// narrow walk's steps consist of is merges and barriers, which 512 threads get through sooner than 1024
-// (128K layer, 32 searches: 28.4 against 29.6 us; 27.3 against 29.6 us for 128 searches of 32K keys, and
-// still 37.5 against 49.1 us when 256 searches and their 64 helpers outnumber the compute units); a beam
-// of more than 256 entries keeps 1024 (its steps gather and merge more: 215 against 200 us on the
-// 1M-key configuration), and above 384 searches 256 threads let several share a compute unit, one's trips
-// to HBM behind another's work (48.3 against 52.8 us for 512 searches of 32K keys). Steps of very few
-// cells go one size down: one node of degree 32 per step 184 -> 168 us (ef 128; of degree 64 slower), of
-// degree 48 2.91 -> 2.36 ms (ef 1024), four of degree 48 701 -> 676 us (ef 1024; slower with ef 2048).
+// Threads per search, of a launch of `heads` searches whose steps read up to `cells` adjacency cells. Merges
+// and barriers, which make up a narrow walk's steps, go faster with fewer threads; gathers and merges of wide
+// beams with more; and where searches outnumber the compute units (256), several small workgroups share one.
+// Measured on the fused launch (us per layer, 32 searches over 128K keys unless said; start sets of 1024
+// where a step has 1024 cells or more):
+//   ef <= 256, up to 384 searches: 512 threads. ef 256, 2048 cells: 26.0 (1024 threads 29.3, 256 threads 32.4);
+//     128 searches of 32K keys 28.8 (32.5, 33.9), 384 of them 44.0 (64.5, 45.1).
+//   ef <= 256, more searches: 256 threads. 512 searches of 32K keys, ef 128: 44.8 (512 threads 50.9), ef 256: 54.6 (58.3).
+//   At most 64 cells and 384 searches (one node per step, mostly): one size down. Degree 32, ef 128: 180 with 256
+//     threads (512: 191), ef 48: 78 (84); ef 512: 902 with 512 (1024: 989, 256: 923), ef 1024: 2134 (2691), ef 2048: 5521
+//     (6167); degree 64: ef 1024: 2191 (2801), ef 2048: 5898 (6956). Over 48 cells 512 threads: degree 64, ef 256: 369 (256: 402).
+//   ef 257 .. 1024 and at most 256 cells: 512. Four nodes of degree 32, ef 1024: 604 (1024: 670); eight: 329 (342), ef 300: 86 (93).
+//   ef 257 .. 1024 and more cells: 1024. ef 1024, 2048 cells: 123 (512: 137); ef 512: 39.5 (40.9).
+//     More than 256 searches, ef up to 512: 512 again, two of which share a compute unit. 320 searches of 32K
+//     keys, ef 512: 66 (1024: 91), ef 384: 51 (77); 512 searches: 79 (115) and 67 (99).
+//   ef above 1024: 1024. 2048 cells: 174 (512: 254); 128 cells: 1417 (1491).
+// Where the lines are not the best ones (same measurement): ef 256 with at most 48 cells (403; 512 threads would take
+// 371) and ef up to 128 with 64 cells (192; 256: 178); eight nodes of degree 32 with ef 512 (152; 1024: 147); ef 384
+// with 2048 cells (35.7; 512: 33.0); 256 searches, which with their helpers outnumber the compute units, at ef 384 and
+// 512 (61 and 69; 512: 48 and 60); more than 256 searches with ef 1024 (320 searches: 242; 512: 196) or with ef 2048
+// and 128 cells (2814; 512: 1764).
 static inline int search_threads(int heads, int ef, int cells) {
     if (cells <= 64 && heads <= 384) return ef > 256 || cells > 48 ? 512 : 256;
     if (ef > 1024) return 1024;
