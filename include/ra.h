@@ -279,12 +279,12 @@ int64_t ra_index_info(const ra_index* idx, int what);
  *                       tens of milliseconds).
  * Helpers are used only for GQA groups of 1, 2, 4 or 8 query heads per KV head; with any other
  * group size every head attends to W itself.
- * The hand-over is ordered without fences: the words that cross workgroups are relaxed
- * agent-scope atomic accesses (on gfx950 these bypass the per-XCD L2), the helper waits for its
- * record stores to complete (s_waitcnt vmcnt(0), workgroup barrier) before it stores the ready
- * word, and the head reads the record only after it has seen the ready word. That ordering is a
- * property of this part's memory system, not of the HIP memory model; the bounded wait and the
- * fall-back keep a launch correct if a ready word never arrives.
+ * The hand-over takes no fence and no order between different words: a record is 64-bit words, each the
+ * bits of a float and a 1 in the upper half, so that every word says itself whether it has come. They
+ * are written and read by relaxed agent-scope atomic accesses (on gfx950 these bypass the per-XCD L2);
+ * the head polls the words of its record and zeroes them again for the next launch. Words that come after
+ * a head has given up stay where they are: no launch of the handle looks at records until
+ * RA_CFG_HELPERS, which zeroes them, is set again.
  * Two ra_decode_step calls on one handle must not overlap in time (they share this memory,
  * like the handle's other workspaces). Returns RA_EINVAL for an unknown setting or value.
  *

@@ -476,8 +476,8 @@ __global__ __launch_bounds__(T) void decode_kernel(
 }
 
 #ifdef SR_PHASE_CLOCKS
-// Tuning builds only: copy the phase clocks of the fused kernel to `host` (64 x 16 x 8 values: workgroup,
-// search step, phase) and clear them.
+// Tuning builds only: copy the phase clocks of the fused kernel to `host` (64 x SR_NITER x SR_NPHASE values:
+// search, step, phase) and clear them.
 #ifdef SR_WAVE_CLOCKS
 extern "C" int ra_dbg_wave_ticks(long long* host) {
     return hipMemcpyFromSymbol(host, HIP_SYMBOL(sr_wave_ticks), sizeof(long long) * 64) != hipSuccess;

@@ -1,7 +1,7 @@
 // VectorSearch(q) of Algorithm 1: bounded best-first walk over one head's key graph
 // (Sec. 2.4 describes proximity-graph search as a greedy walk towards the most similar
 // vectors). One workgroup per (sequence, query head), of 1024, 512 or 256 threads (search_threads
-// below; the fused decode launch chooses for itself); the whole search state lives in LDS:
+// below, for the stand-alone and the fused launch); the whole search state lives in LDS:
 //   * visited: an exact bitset over the N keys (N/8 bytes; a global-memory bitset is used
 //     instead when the context is too long for LDS),
 //   * beam: at most ef entries, always sorted, as 64-bit keys
@@ -326,7 +326,7 @@ __device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
     min_max_step<0x143, 0xC>(lo, hi);
 }
 
-// the same, counting only entries whose not-yet-expanded flag is clear
+// number of the first min(n, 16) entries of arr that are larger than k and whose not-yet-expanded flag is clear
 __device__ __forceinline__ int count_above16_expanded(const u64* arr, int n, u64 k) {
     u64 v[16];
 #pragma unroll
@@ -337,7 +337,7 @@ __device__ __forceinline__ int count_above16_expanded(const u64* arr, int n, u64
     return cnt;
 }
 
-// the same when all 16 entries count
+// number of the 16 entries at arr that are larger than k
 __device__ __forceinline__ int count_above16_full(const u64* arr, u64 k) {
     u64 v[16];
 #pragma unroll
@@ -1168,7 +1168,7 @@ __device__ __forceinline__ int run_search(
                 if (e0 + wv * RA_WAVE < bn) {                     // this wavefront has beam entries
                     int before = 0;
                     if constexpr (HSUM) {
-                        if (lane < e0 / RA_WAVE + wv) before = hsum[lane];      // (below SR_HSUM: e < bn)
+                        if (lane < e0 / RA_WAVE + wv) before = hsum[lane];      // (there are such sums: e < bn)
                     } else {
                         for (int x = 0; x < e0 / RA_WAVE + wv; ++x) before += hist[x * RA_WAVE + lane];
                     }
