@@ -480,7 +480,7 @@ __global__ __launch_bounds__(T) void decode_kernel(
 // search, step, phase) and clear them.
 #ifdef SR_WAVE_CLOCKS
 extern "C" int ra_dbg_wave_ticks(long long* host) {
-    return hipMemcpyFromSymbol(host, HIP_SYMBOL(sr_wave_ticks), sizeof(long long) * 64) != hipSuccess;
+    return hipMemcpyFromSymbol(host, HIP_SYMBOL(sr_wave_ticks), sizeof(long long) * SR_NWAVE) != hipSuccess;
 }
 #endif
 extern "C" int ra_dbg_phase_ticks(long long* host) {

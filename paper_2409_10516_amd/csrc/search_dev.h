@@ -64,9 +64,11 @@ static __device__ long long sr_phase_ticks[64 * SR_NITER * SR_NPHASE];
 #ifdef SR_WAVE_CLOCKS
 // (with -DSR_WAVE_CLOCKS: wall-clock stamps of the first head's workgroup, [0..3] search entered,
 // state cleared, claims made, start set's keys in LDS, and of the first and last of its seed
-// workgroups, [8..11] and [16..19]: entered, header read, first rows scored, first keys stored;
-// ra_dbg_wave_ticks copies them out)
-static __device__ long long sr_wave_ticks[64];
+// workgroups, [8..11] and [16..19]: entered, header read, first rows scored, first keys stored; [24..31]
+// every 128th key taken; [32..] keys stored by each wavefront of each seed workgroup; ra_dbg_wave_ticks
+// copies SR_NWAVE of them out)
+#define SR_NWAVE (32 + 8 * RA_SEED_PARTS_MAX)
+static __device__ long long sr_wave_ticks[SR_NWAVE];
 #endif
 // ticks are added up in LDS (a fire-and-forget add) and copied out when the search has ended
 #define SR_TICK_INIT                                                                           \
