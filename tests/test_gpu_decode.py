@@ -195,8 +195,8 @@ def test_decode_step_helper_modes_agree_with_oracle(name):
     turn = [0]
 
     def check():
-        # a different query on every call: a record or ready word left over from the launch
-        # before would carry the other query's attention over W and fail the comparison
+        # a different query on every call: a record left over from the launch before
+        # would carry the other query's attention over W and fail the comparison
         t = turn[0] % w.q_decode.shape[0]
         turn[0] += 1
         out, lse, ids, st = ra.ra_decode_step(w.q_decode[t].to(DEV), idx, Kd, Vd, w.sink, w.window, w.topk,
@@ -211,7 +211,7 @@ def test_decode_step_helper_modes_agree_with_oracle(name):
 
     try:
         assert idx.helpers_active
-        check(); check(); check()             # back to back: the ready words are cleared by their readers
+        check(); check(); check()             # back to back: the records are cleared by their readers
         assert idx.helpers_active
         idx.configure(B.RA_CFG_HELPERS, B.RA_HELPERS_OFF)
         assert not idx.helpers_active
