@@ -188,9 +188,9 @@ ra_status ra_flat_topk(const void* q, const void* K, ra_dtype dt, int n_seq, int
                        void* workspace, size_t workspace_bytes, void* stream, int32_t* ids);
 
 /* Eq. 1: softmax attention over all N tokens (what the method approximates), as (out, lse).
- * float32 accumulation throughout; for bf16 inputs and GQA groups of up to four query heads the
- * logits of a long context come from the matrix cores (sums of exact bf16 products in the
- * hardware's order), otherwise from the vector units. Same tolerance either way.
+ * float32 accumulation throughout; for bf16 inputs the logits of a long context come from the matrix
+ * cores (sums of exact bf16 products in the hardware's order), otherwise from the vector units. Same
+ * tolerance either way.
  * workspace: device memory of at least ra_full_attention_workspace_bytes(...) bytes. */
 size_t ra_full_attention_workspace_bytes(int n_seq, int n_q_heads, int n_kv_heads, int64_t N);
 ra_status ra_full_attention(const void* q, const void* K, const void* V, ra_dtype dt, int n_seq,

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
     float* rec_g = partials + ((size_t)seq * n_q + h0) * P * AT_RS;
     int first = 0, n_mine = G, slot = x;        // heads of the group this workgroup has a record of, and which
     if (x < nS) {
-        RowSrc src{nullptr, N, s, w, s + w, 0};
+        RowSrc src{nullptr, N, s, w, s + w};
         bool done = false;
         if constexpr (DT == RA_BF16 && G <= 4) {
             if (sub > 1) {                      // a long dense range (full attention): logits on the matrix cores
@@ -64,12 +64,12 @@ __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
             }
         }
         if (!done)
-            attend_chunk<DT, G, TICKETS>(threadIdx.x, true, qg, Kh, Vh, src, x, sub, scale, rec_g + (size_t)x * AT_RS,
+            attend_chunk<DT, G, TICKETS>(threadIdx.x, qg, Kh, Vh, src, x, sub, scale, rec_g + (size_t)x * AT_RS,
                                          (int64_t)P * AT_RS, smem);
     } else {
         const int t = x - nS, g = t / nG, c = t % nG;
-        RowSrc src{ids + ((size_t)seq * n_q + h0 + g) * topk, N, 0, 0, topk, 0};
-        attend_chunk<DT, 1, TICKETS>(threadIdx.x, true, qg + (size_t)g * RA_D * esz, Kh, Vh, src, c, 1, scale,
+        RowSrc src{ids + ((size_t)seq * n_q + h0 + g) * topk, N, 0, 0, topk};
+        attend_chunk<DT, 1, TICKETS>(threadIdx.x, qg + (size_t)g * RA_D * esz, Kh, Vh, src, c, 1, scale,
                                      rec_g + ((size_t)g * P + nS + c) * AT_RS, 0, smem);
         first = g;
         n_mine = 1;
@@ -187,7 +187,7 @@ ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype
     const int sub = static_sub(dt, s + w, n_seq, n_q, n_kv);
     const int nS = (s + w + AT_CH * sub - 1) / (AT_CH * sub), nG = ids ? (topk + AT_CH - 1) / AT_CH : 0;
     const float scale = 1.0f / sqrtf((float)RA_D);
-    const size_t lds = (size_t)AT_TEAM_LDS_FLOATS * sizeof(float);
+    const size_t lds = (size_t)AT_CHUNK_LDS_FLOATS * sizeof(float);
     const int64_t records = (int64_t)(nS + nG) * n_q * n_seq;
     if (records > AT_TICKET_RECORDS) tickets = nullptr;
     const AttendOut o{tickets, out, lse, o_omega, lse_omega, o_w, lse_w};

@@ -5,10 +5,10 @@
 // Omega are cut into chunks of 64; one workgroup turns one chunk into a partial record
 // (un-normalised sum of exp(z - m) v, the local maximum m, the local sum l). W chunks
 // are shared by the query heads of a GQA group (K/V rows are read once for all of them,
-// Appendix C: one KV copy per group); Omega chunks belong to one query head. A second tiny
-// kernel combines all records of a head with the re-scaling of Eq. 5 generalised from two
-// sets to P sets, and can also emit the two set-level results (o_W, lse_W), (o_Omega,
-// lse_Omega) of Eq. 4.
+// Appendix C: one KV copy per group); Omega chunks belong to one query head. The writer of a head's
+// last record (in small launches) or a second tiny kernel combines all records of a head with the
+// re-scaling of Eq. 5 generalised from two sets to P sets, and can also emit the two set-level
+// results (o_W, lse_W), (o_Omega, lse_Omega) of Eq. 4.
 //
 // Device functions shared by the stand-alone attention kernels and the fused decode kernel.
 //
@@ -26,9 +26,6 @@ struct RowSrc {             // which context rows a chunk covers
     int64_t N;
     int s, w;               // static ranges [0,s) and [N-w,N)
     int count;              // rows available (Wn or topk)
-    int interleave;         // 0: chunk c covers rows [64c, 64c+64). T > 0: T teams share rows
-                            // round-robin, chunk c / local row j covers row
-                            // (c / T) * 64 T + (c % T) * 16 + j % 16 + 16 T (j / 16)
 };
 
 __device__ __forceinline__ int64_t chunk_row(const RowSrc& src, int r) {
@@ -113,7 +110,7 @@ __device__ __forceinline__ void row8_floats(const Row8<DT>& r, float* o) {
 template <int DT>
 __device__ __forceinline__ float at_exp(float x) { return DT == RA_BF16 ? __expf(x) : expf(x); }
 
-// The closing step of a chunk: the (max, sum, weighted sum) states of the 16 lane groups of a team,
+// The closing step of a chunk: the (max, sum, weighted sum) states of the workgroup's 16 lane groups,
 // each lane holding 8 of the 128 outputs of its group, become one partial record per head.
 // COHERENT: the record is read by another workgroup of the same launch (relaxed agent-scope stores, which go
 // around the cache levels that are not coherent across the part's XCDs).
@@ -123,7 +120,7 @@ __device__ __forceinline__ void rec_store(float* p, float v) {
     else *p = v;
 }
 template <int NH, bool COHERENT>
-__device__ __forceinline__ void chunk_records(int tid, bool active, const float (&m)[NH], const float (&l)[NH],
+__device__ __forceinline__ void chunk_records(int tid, const float (&m)[NH], const float (&l)[NH],
                                               const float (&acc)[NH][8], float* rec0, int64_t rec_stride,
                                               float* smem) {
     const int grp = tid >> 4, lane16 = tid & 15;
@@ -140,7 +137,7 @@ __device__ __forceinline__ void chunk_records(int tid, bool active, const float 
 #pragma unroll
         for (int e = 0; e < 8; ++e) sa[grp * RA_D + lane16 * 8 + e] = acc[g][e];
         __syncthreads();
-        if (tid < RA_D && active) {
+        if (tid < RA_D) {
             float mx = -INFINITY;
 #pragma unroll
             for (int j = 0; j < 16; ++j) mx = fmaxf(mx, sm[j]);
@@ -166,12 +163,9 @@ __device__ __forceinline__ void chunk_records(int tid, bool active, const float 
 // One chunk for NH query heads that share the same K/V rows.
 // A call covers `n_sub` consecutive sub-chunks of 64 rows (1 for the decode step; more when a
 // long dense range is streamed, so that the number of partial records stays small).
-// `tid` is the thread's index inside its team of AT_THREADS threads (a workgroup may hold
-// several teams, each with its own `smem`; every team must call this the same number of
-// times because it contains workgroup barriers). An inactive team computes on an empty row
-// source and writes nothing.
+// Called by all AT_THREADS threads (it contains workgroup barriers), with AT_CHUNK_LDS_FLOATS at `smem`.
 template <int DT, int NH, bool COHERENT>
-__device__ void attend_chunk(int tid, bool active, const void* q0, const void* Kh, const void* Vh,
+__device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void* Vh,
                              const RowSrc& src, int chunk, int n_sub, float scale, float* rec0,
                              int64_t rec_stride, float* smem) {
     const int grp = tid >> 4, lane16 = tid & 15;
@@ -193,13 +187,7 @@ __device__ void attend_chunk(int tid, bool active, const void* q0, const void* K
     auto rows_of = [&](int sub, int64_t (&rid)[RPG]) {
         if (sub >= sub_end) sub = sub_end - 1;
 #pragma unroll
-        for (int i = 0; i < RPG; ++i) {
-            const int r = src.interleave
-                ? (sub / src.interleave) * AT_CH * src.interleave + (sub % src.interleave) * 16 + grp +
-                      16 * src.interleave * i
-                : sub * AT_CH + grp + 16 * i;
-            rid[i] = chunk_row(src, r);
-        }
+        for (int i = 0; i < RPG; ++i) rid[i] = chunk_row(src, sub * AT_CH + grp + 16 * i);
     };
     auto fetch = [&](const int64_t (&rid)[RPG], Row8<DT> (&kr)[RPG], Row8<DT> (&vr)[RPG]) {
 #pragma unroll
@@ -287,7 +275,7 @@ __device__ void attend_chunk(int tid, bool active, const void* q0, const void* K
             consume(rid_b, k_b, v_b);
         }
     }
-    chunk_records<NH, COHERENT>(tid, active, m, l, acc, rec0, rec_stride, smem);
+    chunk_records<NH, COHERENT>(tid, m, l, acc, rec0, rec_stride, smem);
 }
 
 // The same chunk for a long dense range of bf16 rows and up to four heads, with the logits on the
@@ -415,7 +403,7 @@ __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const
         const float tot = first_lane_f32(v);
         l[h] = c == 0 ? tot : 0.f;
     }
-    chunk_records<NH, COHERENT>(tid, true, m, l, acc, rec0, rec_stride, smem);
+    chunk_records<NH, COHERENT>(tid, m, l, acc, rec0, rec_stride, smem);
 }
 
 // Combination of one head's P = nS + nG partial records: Eq. 4-5 with the re-scaling factors
@@ -521,4 +509,4 @@ static inline void static_ranges(int64_t N, int sink, int window, int* s, int* w
     *w = (int)ww;
 }
 
-#define AT_TEAM_LDS_FLOATS (32 + 16 * RA_D)      // LDS floats one team of attend_chunk needs
+#define AT_CHUNK_LDS_FLOATS (32 + 16 * RA_D)     // LDS floats a workgroup needs to close a chunk
