@@ -153,8 +153,8 @@ size_t ra_knn_filter_bytes(int graphs, int64_t N, int64_t M, int knn);
 float* ra_knn_filter_scores(void* workspace, int graphs, int64_t N, int64_t M, int knn);
 ra_status ra_launch_knn_filter_scales(const void* K, ra_dtype dt, int n_seq_kv, int64_t N, uint32_t* maxabs,
                                       hipStream_t st);
-ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const void* order, int g0, int n_graphs,
-                               int n_q, int n_kv, int64_t N, int64_t M, int knn, int64_t first,
+ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const void* order, int graphs, int g0,
+                               int n_graphs, int n_q, int n_kv, int64_t N, int64_t M, int knn, int64_t first,
                                const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
                                const int** resume, int* resume_queries, int* resume_blocks);
 void ra_knn_set_selection_override(int v);      // RA_TEST_KNN_AUTO / _FILTER / _LDS
@@ -164,6 +164,8 @@ ra_status ra_launch_sort(void* keys, size_t stride, int n_arrays, int64_t N_pad,
                          size_t count_stride, hipStream_t st);
 size_t ra_knn_order_bytes(int n_graphs, int64_t N);
 int64_t ra_knn_order_stride(int64_t N);
+// the sums of the heads' sampled queries behind an order workspace of `graphs` heads, and how many were summed
+const float* ra_knn_order_mean(const void* workspace, int graphs, int64_t N, int64_t M, int* samples);
 ra_status ra_launch_knn_order(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
                               int64_t N, int64_t M, void* workspace, hipStream_t st);
 

@@ -217,7 +217,7 @@ __device__ __forceinline__ void store_chunk(unsigned char* buf, int tid, int i, 
 // grid: x = block of 32 * WAVES queries, y = graph (seq * n_q + h) - g0. The keys are the first
 // n_stream of the graph's stream order. With `scores` and no `resume` the lists' scores are written
 // too, for knn_filter.hip, which takes the rest of the stream; with `resume` (first stream position not
-// yet seen, per graph and block of resume_queries queries) the lists are read from L_out and scores and
+// yet seen, per graph and block of resume_queries queries, a multiple of 32) the lists are read from L_out and scores and
 // the stream goes on from there.
 // LDS: [32 * WAVES][list slots] lists, then two stage buffers of STAGE bytes.
 // SEL (KN_SEL_*) selects how keys wait for their list.
@@ -256,11 +256,17 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     const int last_pos = (int)n_stream - 1;               // ids and stream positions fit 31 bits
     auto stream_id = [&](int p) __attribute__((always_inline)) { return ord[2 * (size_t)(unsigned)(p < last_pos ? p : last_pos)]; };
 
-    int64_t st0 = 0;                               // first stage
+    int64_t st0 = 0, my_st0 = 0;                   // first stage of the workgroup and of this wavefront
     if (resume) {
-        const int64_t pos0 = resume[(size_t)blockIdx.y * resume_blocks + (int64_t)blockIdx.x * QPB / resume_queries];
-        if (pos0 >= n_stream) return;              // (the whole workgroup)
-        st0 = pos0 / SROWS;
+        int64_t least = n_stream;
+        for (int w = 0; w < WAVES; ++w) {
+            const int64_t qw = (int64_t)blockIdx.x * QPB + 32 * w;
+            const int64_t pos = qw < M ? resume[(size_t)blockIdx.y * resume_blocks + qw / resume_queries] : n_stream;
+            if (pos < least) least = pos;
+            if (w == wv) my_st0 = __builtin_amdgcn_readfirstlane((int)(pos < n_stream ? pos / SROWS : 0x7fffffff));
+        }
+        if (least >= n_stream) return;             // (the whole workgroup)
+        st0 = least / SROWS;
     }
     for (int i = tid; i < QPB * lstride; i += KN_THREADS) {
         u64 k = 0ull;
@@ -395,6 +401,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     OperandAt<DT> a_at;                            // where this lane's key operand sits in a stage buffer
     operand_offsets<DT>((int)(stage_buf - lds_raw), col, half, a_at);
     auto multiply_stage = [&](int cur, int64_t st, int ids) __attribute__((always_inline)) {      // cur: byte offset of the stage buffer
+        if (st < my_st0) return;                    // (keys that this wavefront's queries have seen)
         Operand<DT> a0;
         read_operand<DT>(lds_raw, a_at, cur, a0);
         if constexpr (SBLK == 2) {
@@ -585,7 +592,7 @@ ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, in
         c.resume = nullptr;
         rc = knn_launch(c, dt);
         if (rc != RA_OK) return rc;
-        rc = ra_launch_knn_filter(K, Q, dt, workspace, g0, c.n_graphs, n_q, n_kv, N, M, knn, first, maxabs, ws, st, L,
+        rc = ra_launch_knn_filter(K, Q, dt, workspace, graphs, g0, c.n_graphs, n_q, n_kv, N, M, knn, first, maxabs, ws, st, L,
                                   &c.resume, &c.resume_queries, &c.resume_blocks);
         if (rc != RA_OK) return rc;
         c.n_stream = N;                            // where the filter gave up (seldom): the stream to its end

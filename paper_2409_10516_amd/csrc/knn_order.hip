@@ -196,6 +196,11 @@ size_t ra_knn_order_bytes(int n_graphs, int64_t N) {
 
 int64_t ra_knn_order_stride(int64_t N) { return ra_sort_padded(N); }
 
+const float* ra_knn_order_mean(const void* workspace, int graphs, int64_t N, int64_t M, int* samples) {
+    *samples = M < KO_SAMPLE ? (int)M : KO_SAMPLE;
+    return reinterpret_cast<const float*>(reinterpret_cast<const u64*>(workspace) + (size_t)graphs * ra_sort_padded(N));
+}
+
 // Fills workspace with the stream order of every head: entry p of head g, at
 // workspace[g * ra_knn_order_stride(N) + p], holds the id of the key streamed p-th in its low word.
 ra_status ra_launch_knn_order(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,

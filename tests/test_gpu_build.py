@@ -423,6 +423,36 @@ def test_knn_8bit_bound_holds_at_any_scale(dtype, knn, q_exp, k_exp):
         assert np.array_equal(L[B.RA_TEST_KNN_LDS], OM.knn_lists(Q, K, knn)[0])
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("N,M,knn,heads", [(640, 130, 32, 24), (1153, 600, 5, 128), (9001, 40, 33, 256), (30000, 65, 64, 2)])
+def test_knn_filter_looks_early(dtype, N, M, knn, heads):
+    """Queries with a large common component and keys and queries whose dimensions carry very different amounts: most
+    blocks are ruled out after the first dimensions, the end of the stream without a product, and how early a
+    wavefront looks changes along it. Among the queries: some opposite to the mean (their best keys come last),
+    some twenty times longer, the mean itself (nothing is left of it for the products) and zero. Lists of
+    the stream without the filter, bit for bit, for one, two and four query sets per wavefront (as many as leave
+    2048 wavefronts in the launch)."""
+    from paper_2409_10516_amd import binding as B
+    g = torch.Generator().manual_seed(N)
+    carry = torch.exp(torch.randn(128, generator=g))
+    mean = torch.randn(128, generator=g) * 4
+    K = torch.randn(1, 2, N, 128, generator=g) * carry
+    Q = mean + torch.randn(1, heads, M, 128, generator=g) * carry.flip(0).sqrt()
+    Q[:, :, 3::16] = -Q[:, :, 3::16]
+    Q[:, :, 5::16] *= 20.0
+    Q[:, :, 7::32] = mean
+    Q[:, :, 9::32] = 0.0
+    Kd, Qd = K.to(dtype).to(DEV), Q.to(dtype).to(DEV)
+    L = {}
+    try:
+        for how in (B.RA_TEST_KNN_LDS, B.RA_TEST_KNN_FILTER):
+            ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, how)
+            L[how] = ra.ra_knn(Kd, Qd, knn).cpu().numpy()
+    finally:
+        ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_AUTO)
+    assert np.array_equal(L[B.RA_TEST_KNN_LDS], L[B.RA_TEST_KNN_FILTER])
+
+
 @pytest.mark.parametrize("call", ["ra_knn", "ra_project", "ra_build_index"])
 def test_a_call_without_enough_memory_spoils_no_later_one(call):
     """Sizes no device has the scratch memory for: RA_ENOMEM before anything is read, and the calls that
