@@ -10,19 +10,23 @@
 // max-tree over the lane's 16 scores and one compare. Only scores that reach the threshold go
 // further (about knn * ln(N / knn) per query over a stream in storage order, a third of that in
 // the order the keys are streamed in here: see knn_order.hip). Two ways to keep them:
-//   KN_SEL_LDS (knn <= KN_BUFFERED_KNN): a query owns KN_CAP list slots in LDS, its best knn keys
-//     so far, then two runs of pending slots, one per lane that scores for it. A lane appends a
-//     key to its own run with a single LDS write (its fill count is a register); when a run cannot
-//     take what a lane is about to append (keys come four at a time) the wavefront sorts the 64
-//     slots of that query across its lanes (bitonic network), keeps the best knn and raises the
-//     threshold.
+//   KN_SEL_LDS* (knn <= KN_BUFFERED_KNN): a query owns KN_CAP slots in LDS: its best keys so far, then two runs of
+//     pending slots, one per lane that scores for it. A lane appends a score and an id to its own run with a single LDS
+//     write (its fill count is a register); when a run cannot take what a lane is about to append, the wavefront
+//     merges the runs of all its 32 queries into their lists at once, the two lanes of a query holding its keys in
+//     registers: sorting networks whose exchanges are one maximum and one minimum for 64 lanes, between the two
+//     lanes by half-wave swaps. (460 instructions for 32 queries; one query at a time, its 64 slots sorted across
+//     the lanes by a bitonic network, took 200 for each. First 4096 keys of 32 heads x 128K queries, lists of 32:
+//     12.5 -> 7.0 ms, of which writing scores and ids as they are, without a branch, instead of whole keys 0.8 ms.)
 //   KN_SEL_INSERT (longer lists): sorted insertion, one key at a time, by the whole wavefront.
 // Between two merges a threshold is stale but valid (never above the true one), so nothing is
 // lost.
 //
 // A wavefront owns 32 queries for the whole key stream (their B operands stay in registers); a
 // workgroup is WAVES wavefronts. Lists hold
-// 64-bit keys [ordered(score):32][~id:32], so "larger key" is "(score descending, id ascending)".
+// 64-bit keys [0:1][ordered(score):32][2^31 - 1 - id:31], so "larger key" is "(score descending, id ascending)". The
+// bits of a key are also those of a positive double of the same order (the scores that are numbers, and zero
+// for an empty slot, give neither NaNs nor denormals), whose maximum and minimum are single instructions.
 // The inner-product summation order is the hardware's; identical key rows still score
 // identically for a given query because they go through the same instruction sequence.
 //
@@ -37,11 +41,12 @@
 
 #include "common.h"
 
-#define KN_CAP 64                 // list slots of a query in the buffered selection (one per lane)
+#define KN_CAP 62                 // slots of a query in the buffered selection: what fits beside the stage buffers
 #define KN_BUFFERED_KNN 48        // longest list that leaves room for pending slots
 // how the top-knn selection keeps keys that reached a threshold until they are merged into a list
 #define KN_SEL_INSERT 0           // not at all: sorted insertion, one key at a time
-#define KN_SEL_LDS 1              // in pending runs behind the list in LDS (KN_CAP slots per query)
+#define KN_SEL_LDS32 1            // in pending runs behind the list in LDS (KN_CAP slots per query), lists of up to 32
+#define KN_SEL_LDS48 2            // ... and of 33 to 48 keys
 
 typedef unsigned long long u64;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -49,9 +54,14 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ u64 knn_key(float score, int id) {
-    return ((u64)f32_ordered(score) << 32) | (u64)(0xffffffffu - (uint32_t)id);
+    return ((u64)f32_ordered(score) << 31) | (u64)(0x7fffffffu - (uint32_t)id);
 }
-__device__ __forceinline__ int knn_key_id(u64 k) { return (int)(0xffffffffu - (uint32_t)k); }
+__device__ __forceinline__ int knn_key_id(u64 k) { return (int)(0x7fffffffu - ((uint32_t)k & 0x7fffffffu)); }
+// threshold of a list whose last key is `last`: what cannot be in it (minus infinity and what is no number) stays below
+__device__ __forceinline__ float knn_threshold(u64 last) {
+    return last == 0ull ? -3.402823466e38f : f32_from_ordered((uint32_t)(last >> 31));
+}
+__device__ __forceinline__ float knn_key_score(u64 k) { return f32_from_ordered((uint32_t)(k >> 31)); }
 
 // Insert (score, id) into the sorted list lst[0..knn) (all 64 lanes cooperate).
 // Returns the list's new threshold: the score of its last entry, or -inf while not full.
@@ -64,43 +74,131 @@ __device__ __forceinline__ float knn_insert(u64* lst, int knn, float score, int 
         if (lane == pos) lst[pos] = nk;
     }
     const u64 last = lst[knn - 1];
-    return last == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(last >> 32));
+    return last == 0ull ? -INFINITY : knn_key_score(last);
 }
 
-// 64 keys, one per lane, sorted descending across the wavefront (bitonic network). Keys are
-// distinct or zero, so "the other one is larger" decides every exchange.
-__device__ __forceinline__ u64 wave_sort_desc(u64 v, int lane) {
-#define KN_EXCHANGE(K_, J_)                                                                   \
-    {                                                                                         \
-        const u64 o = ((u64)lane_xor32<J_>((uint32_t)(v >> 32), lane) << 32) |                \
-                      (u64)lane_xor32<J_>((uint32_t)v, lane);                                 \
-        const bool keep_max = ((lane & J_) == 0) == ((lane & K_) == 0);                       \
-        v = ((o > v) == keep_max) ? o : v;                                                    \
+// ---- merging pending keys into lists, all 32 queries of a wavefront at once ------------------------------
+// Lane (col, half) holds a part of the keys of query col. In-lane exchanges work on registers of one lane, cross
+// exchanges between the register of a lane and that of the query's other lane.
+template <bool DESC>
+__device__ __forceinline__ void kn_exchange(double& a, double& b) {
+    const double lo = __builtin_fmin(a, b), hi = __builtin_fmax(a, b);
+    a = DESC ? hi : lo;
+    b = DESC ? lo : hi;
+}
+// Batcher's odd-even merge sort of N registers of each lane, descending
+template <int N>
+__device__ __forceinline__ void kn_sort(double (&v)[N]) {
+#pragma unroll
+    for (int p = 1; p < N; p *= 2)
+#pragma unroll
+        for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+            for (int j = k % p; j + k < N; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; ++i)
+                    if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) kn_exchange<true>(v[i + j], v[i + j + k]);
+}
+// the in-lane part of a bitonic merge: distances N / 2 down to 1
+template <int N, bool DESC>
+__device__ __forceinline__ void kn_merge(double (&v)[N]) {
+#pragma unroll
+    for (int d = N / 2; d >= 1; d /= 2)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if ((i & d) == 0) kn_exchange<DESC>(v[i], v[i | d]);
+}
+// Exchange between the two lanes of a query, register by register: the lower lane keeps the larger (DESC) or the
+// smaller. Two registers at a time: after a swap of the one's upper with the other's lower half the pairs
+// to compare sit in the same lane.
+__device__ __forceinline__ void kn_swap_halves(double& a, double& b) {
+    const u64 x = __builtin_bit_cast(u64, a), y = __builtin_bit_cast(u64, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    a = __builtin_bit_cast(double, ((u64)hi[0] << 32) | lo[0]);
+    b = __builtin_bit_cast(double, ((u64)hi[1] << 32) | lo[1]);
+}
+template <int N, bool DESC>
+__device__ __forceinline__ void kn_cross(double (&v)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; i += 2) {
+        kn_swap_halves(v[i], v[i + 1]);
+        kn_exchange<DESC>(v[i], v[i + 1]);
+        kn_swap_halves(v[i], v[i + 1]);
     }
-    KN_EXCHANGE(2, 1)
-    KN_EXCHANGE(4, 2) KN_EXCHANGE(4, 1)
-    KN_EXCHANGE(8, 4) KN_EXCHANGE(8, 2) KN_EXCHANGE(8, 1)
-    KN_EXCHANGE(16, 8) KN_EXCHANGE(16, 4) KN_EXCHANGE(16, 2) KN_EXCHANGE(16, 1)
-    KN_EXCHANGE(32, 16) KN_EXCHANGE(32, 8) KN_EXCHANGE(32, 4) KN_EXCHANGE(32, 2) KN_EXCHANGE(32, 1)
-    KN_EXCHANGE(64, 32) KN_EXCHANGE(64, 16) KN_EXCHANGE(64, 8) KN_EXCHANGE(64, 4) KN_EXCHANGE(64, 2)
-    KN_EXCHANGE(64, 1)
-#undef KN_EXCHANGE
-    return v;
+}
+// the pending keys of both lanes, sorted ascending over them (the lower lane holds the smaller ones)
+template <int N>
+__device__ __forceinline__ void kn_sort_pending(double (&v)[N], int half) {
+    // the upper lane sorts negated keys: its own come out ascending, and both together are bitonic
+    const u64 sign = (u64)half << 63;
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = __builtin_bit_cast(double, __builtin_bit_cast(u64, v[i]) ^ sign);
+    kn_sort<N>(v);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = __builtin_bit_cast(double, __builtin_bit_cast(u64, v[i]) ^ sign);
+    kn_cross<N, false>(v);
+    kn_merge<N, false>(v);
 }
 
-__device__ __forceinline__ u64 readlane64(u64 x, int l) {
-    return ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), l) << 32) |
-           (u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
-}
-
-// Fold the pending keys of one query into its list: afterwards slots [0, knn) hold its best knn
-// keys in descending order and the pending slots are empty (all 64 lanes cooperate).
-// Returns the new threshold: the score of slot knn - 1, or -inf while the list is not full.
-__device__ __forceinline__ float knn_fold(u64* lst, int knn, int lane) {
-    const u64 v = wave_sort_desc(lst[lane], lane);
-    lst[lane] = lane < knn ? v : 0ull;
-    const u64 last = readlane64(v, knn - 1);
-    return last == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(last >> 32));
+// Slots of the 32 queries of a wavefront: list slot s of query col at kn_slot(s, col) (32 slots of a query, like one
+// slot of the 32 queries, are in different banks: a list leaves one slot per lane); WIDE (lists of 33 to 48 keys): 48 list
+// slots and runs of 6, else 32 list slots (however short the list has to be) and runs of 14. Behind the list the
+// runs, as they come: place i of all lanes' runs is 64 scores, then 64 ids. A run has a place more than it holds: a lane
+// writes every score to the next free place, and only one that belongs there makes the place taken.
+__device__ __forceinline__ int kn_slot(int s, int col) { return s * 32 + (col ^ (s & 31)); }
+template <bool WIDE> struct KnSlots {
+    static constexpr int list = WIDE ? 48 : 32, pend = WIDE ? 6 : 14;
+    static_assert(list + 2 * (pend + 1) == KN_CAP, "lists and runs fill a query's slots");
+};
+// Merges the pending keys (`fill` of this lane) of all 32 queries into their lists, which stay in descending order.
+// Returns the query's new threshold: the score of its knn-th key, the lowest number while there is none.
+template <bool WIDE>
+__device__ __forceinline__ float knn_fold(u64* slots, int knn, int col, int half, int fill) {
+    constexpr int PEND = WIDE ? 8 : 16;               // (a power of two for the networks: two more than a run holds)
+    const uint32_t* run = reinterpret_cast<const uint32_t*>(slots + KnSlots<WIDE>::list * 32) + 32 * half + col;
+    double p[PEND];
+    p[PEND - 2] = p[PEND - 1] = 0.0;
+#pragma unroll
+    for (int i = 0; i < PEND - 2; ++i) {
+        const u64 k = knn_key(__uint_as_float(run[i * 128]), (int)run[i * 128 + 64]);
+        p[i] = __builtin_bit_cast(double, i < fill ? k : 0ull);
+    }
+    if constexpr (WIDE) {
+        // a bitonic sequence of 64 over the two lanes: the list's best 32 in the lower; in the upper its other 16, then
+        // the 16 pending keys ascending
+        double v[32];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) v[i] = __builtin_bit_cast(double, slots[i < 16 ? kn_slot(i, col) + half * (32 * 32) : kn_slot(i, col)]);
+        kn_sort_pending<PEND>(p, half);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            double low = p[i], same = p[i];
+            kn_swap_halves(low, same);                // low: the lower lane's value in both
+            v[16 + i] = half ? low : v[16 + i];
+            v[24 + i] = half ? p[i] : v[24 + i];
+        }
+        kn_cross<32, true>(v);
+        kn_merge<32, true>(v);
+#pragma unroll
+        for (int i = 0; i < 32; ++i)
+            if (i < 16 || half == 0) slots[kn_slot(i, col) + half * (32 * 32)] = __builtin_bit_cast(u64, v[i]);
+    } else {
+        // list descending against pending ascending: the larger of each pair are the best 32, a bitonic sequence
+        double v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = __builtin_bit_cast(double, slots[kn_slot(16 * half + i, col)]);
+        kn_sort_pending<PEND>(p, half);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = __builtin_fmax(v[i], p[i]);
+        kn_cross<16, true>(v);
+        kn_merge<16, true>(v);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) slots[kn_slot(16 * half + i, col)] = __builtin_bit_cast(u64, v[i]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");        // (the other lane's slot is read below)
+    __builtin_amdgcn_wave_barrier();
+    return knn_threshold(slots[kn_slot(knn - 1, col)]);
 }
 
 template <int DT> struct Operand;
@@ -219,7 +317,8 @@ __device__ __forceinline__ void store_chunk(unsigned char* buf, int tid, int i, 
 // too, for knn_filter.hip, which takes the rest of the stream; with `resume` (first stream position not
 // yet seen, per graph and block of resume_queries queries, a multiple of 32) the lists are read from L_out and scores and
 // the stream goes on from there.
-// LDS: [32 * WAVES][list slots] lists, then two stage buffers of STAGE bytes.
+// LDS: the lists (per wavefront 32 queries' slots), then two stage buffers of STAGE bytes, then (pending runs) the key
+// ids of a stage per wavefront.
 // SEL (KN_SEL_*) selects how keys wait for their list.
 template <int DT, int WAVES, int SEL, int STAGE>
 __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
@@ -238,10 +337,9 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     static_assert(SBLK == 1 || SBLK == 2, "a stage holds one or two key blocks");
     static_assert(CPT * KN_THREADS * 16 == STAGE, "threads must tile a stage");
     static_assert(KN_THREADS % CPR == 0, "a thread keeps its 16-byte column");
-    constexpr bool BUF = SEL != KN_SEL_INSERT;
+    constexpr bool BUF = SEL != KN_SEL_INSERT, WIDE = SEL == KN_SEL_LDS48;
     const int lstride = BUF ? KN_CAP : knn;           // list slots per query
-    const int pend = (KN_CAP - knn) / 2;                      // pending keys a lane can hold (BUF)
-    u64* lists = reinterpret_cast<u64*>(lds_raw);           // [QPB][lstride]
+    u64* lists = reinterpret_cast<u64*>(lds_raw);           // [QPB / 32][lstride][32] (BUF), [QPB][lstride]
     unsigned char* stage_buf = lds_raw + (size_t)QPB * lstride * sizeof(u64);   // 16-byte aligned: QPB is even
     const int tid = threadIdx.x, wv = tid / RA_WAVE, lane = tid % RA_WAVE;
     const int col = lane & 31, half = lane >> 5;
@@ -263,16 +361,17 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
             const int64_t qw = (int64_t)blockIdx.x * QPB + 32 * w;
             const int64_t pos = qw < M ? resume[(size_t)blockIdx.y * resume_blocks + qw / resume_queries] : n_stream;
             if (pos < least) least = pos;
-            if (w == wv) my_st0 = __builtin_amdgcn_readfirstlane((int)(pos < n_stream ? pos / SROWS : 0x7fffffff));
+            if (w == wv) my_st0 = pos < n_stream ? pos / SROWS : 0x7fffffff;
         }
         if (least >= n_stream) return;             // (the whole workgroup)
         st0 = least / SROWS;
+        my_st0 = __builtin_amdgcn_readfirstlane((int)my_st0);
     }
     for (int i = tid; i < QPB * lstride; i += KN_THREADS) {
         u64 k = 0ull;
         if (resume) {
-            const int64_t qr = (int64_t)blockIdx.x * QPB + i / lstride;
-            const int e = i % lstride;
+            const int e = BUF ? i / 32 % KN_CAP : i % lstride;
+            const int64_t qr = (int64_t)blockIdx.x * QPB + (BUF ? i / (32 * KN_CAP) * 32 + ((i ^ e) & 31) : i / lstride);
             if (qr < M && e < knn) {
                 const float sc = scores[((size_t)blockIdx.y * M + qr) * knn + e];
                 if (sc > -INFINITY) k = knn_key(sc, L_out[((size_t)graph * M + qr) * knn + e]);
@@ -281,14 +380,16 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
         lists[i] = k;
     }
     u64* my_lists = lists + (size_t)wv * 32 * lstride;
+    // the key ids of the stage's rows, where the lanes that keep some of them read them (BUF)
+    int* my_ids = reinterpret_cast<int*>(stage_buf + 2 * STAGE) + wv * SROWS;
 
     Operand<DT> b;                                 // (loads clamped: columns beyond M are never written)
     load_operand<DT>(Qh, q0 + col < M ? q0 + col : M - 1, half, b);
     settle_operand<DT>(b);
     __syncthreads();
 
-    const u64 last_key = my_lists[col * lstride + knn - 1];          // (zero but for a resumed stream)
-    float tau = last_key == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(last_key >> 32));
+    const u64 last_key = my_lists[BUF ? kn_slot(knn - 1, col) : col * lstride + knn - 1];          // (zero but for a resumed stream)
+    float tau = knn_threshold(last_key);
     int fill = 0;                                  // BUF: keys in this lane's pending run
 
     static_assert(CPT == 2 || CPT == 4, "two or four chunks per thread and stage");
@@ -344,34 +445,30 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
                 gm[g] = fmaxf(fmaxf(cs[4 * g], cs[4 * g + 1]), fmaxf(cs[4 * g + 2], cs[4 * g + 3]));
             const float mx = fmaxf(fmaxf(gm[0], gm[1]), fmaxf(gm[2], gm[3]));
             if (__ballot(mx >= tau) == 0ull) return;
-            u64* mine = my_lists + (size_t)col * KN_CAP + knn + half * pend;     // KN_SEL_LDS
+            constexpr int PEND = KnSlots<WIDE>::pend;
+            uint32_t* run = reinterpret_cast<uint32_t*>(my_lists + KnSlots<WIDE>::list * 32) + lane;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 if (__ballot(gm[g] >= tau) == 0ull) continue;
-                // a lane needs room for the keys of this group that reach its threshold: fold the
-                // queries short of it (the count can only fall when a fold raises the threshold)
-                int n4 = 0;
+                // a lane needs room for the keys of this group that reach its threshold (their number can
+                // only fall when a merge raises the threshold)
+                if (__ballot(fill > PEND - 4)) {
+                    int n = 0;
 #pragma unroll
-                for (int r = 4 * g; r < 4 * g + 4; ++r) n4 += cs[r] >= tau ? 1 : 0;
-                u64 need = __ballot(fill + n4 > pend);
-                while (need) {
-                    const int jq = (__ffsll((long long)need) - 1) & 31;
-                    const float nt = knn_fold(my_lists + (size_t)jq * KN_CAP, knn, lane);
-                    if (col == jq) { tau = nt; fill = 0; }
-                    need &= need - 1;
-                    need &= ~(1ull << (jq + 32)) & ~(1ull << jq);
-                }
-#pragma unroll
-                for (int r = 4 * g; r < 4 * g + 4; ++r) {
-                    if (cs[r] >= tau && cs[r] > -INFINITY) {
-                        // the row's id sits in lane `row` of ids (lower half-wave) or four lanes
-                        // on (upper): both are read as scalars, then chosen without a branch
-                        const int row = first + (r / 4) * 8 + (r % 4);
-                        const int lo = __builtin_amdgcn_readlane(ids, row);
-                        const int hi = __builtin_amdgcn_readlane(ids, row + 4);
-                        const u64 nk = knn_key(cs[r], lo ^ ((lo ^ hi) & -half));
-                        if (fill < pend) mine[fill++] = nk;      // always, for scores that are numbers
+                    for (int r = 4 * g; r < 4 * g + 4; ++r) n += cs[r] >= tau ? 1 : 0;
+                    if (__ballot(fill + n > PEND)) {
+                        tau = knn_fold<WIDE>(my_lists, knn, col, half, fill);
+                        fill = 0;
                     }
+                }
+                const int4 id4 = *reinterpret_cast<const int4*>(my_ids + first + 8 * g + 4 * half);
+                const int id[4] = {id4.x, id4.y, id4.z, id4.w};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int place = min(fill, PEND);        // (fill itself, for scores that are numbers)
+                    run[place * 128] = __float_as_uint(cs[4 * g + r]);
+                    run[place * 128 + 64] = (uint32_t)id[r];
+                    fill = place + (cs[4 * g + r] >= tau ? 1 : 0);
                 }
             }
         } else {
@@ -402,6 +499,9 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     operand_offsets<DT>((int)(stage_buf - lds_raw), col, half, a_at);
     auto multiply_stage = [&](int cur, int64_t st, int ids) __attribute__((always_inline)) {      // cur: byte offset of the stage buffer
         if (st < my_st0) return;                    // (keys that this wavefront's queries have seen)
+        if constexpr (BUF) {
+            if (SROWS == 64 || lane < SROWS) my_ids[lane] = ids;
+        }
         Operand<DT> a0;
         read_operand<DT>(lds_raw, a_at, cur, a0);
         if constexpr (SBLK == 2) {
@@ -463,18 +563,15 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
         load_rows(rb, st + 6);
     }
     // write the ids, best first
+    if constexpr (BUF) (void)knn_fold<WIDE>(my_lists, knn, col, half, fill);
     for (int jq = 0; jq < 32; ++jq) {
         const int64_t qr = q0 + jq;
         if (qr >= M) break;
-        u64* lst = my_lists + (size_t)jq * lstride;
-        if constexpr (BUF)
-            knn_fold(lst, knn, lane);
         if (lane < knn) {
-            const u64 k = lst[lane];
+            const u64 k = my_lists[BUF ? kn_slot(lane, jq) : jq * lstride + lane];
             L_out[((size_t)graph * M + qr) * knn + lane] = knn_key_id(k);
             if (scores && !resume)                 // only the first part of the stream: it goes on with these
-                scores[((size_t)blockIdx.y * M + qr) * knn + lane] =
-                    k == 0ull ? -INFINITY : f32_from_ordered((uint32_t)(k >> 32));
+                scores[((size_t)blockIdx.y * M + qr) * knn + lane] = k == 0ull ? -INFINITY : knn_key_score(k);
         }
     }
 }
@@ -494,8 +591,9 @@ struct KnnCall {
 template <int DT, int WAVES, int SEL, int STAGE>
 static ra_status knn_launch_as(const KnnCall& c) {
     constexpr int QPB = 32 * WAVES;
-    const int slots = SEL == KN_SEL_LDS ? KN_CAP : c.knn;
-    const size_t lds = (size_t)QPB * slots * sizeof(u64) + 2 * STAGE;
+    const int slots = SEL != KN_SEL_INSERT ? KN_CAP : c.knn;
+    const size_t lds = (size_t)QPB * slots * sizeof(u64) + 2 * STAGE +
+                       (SEL != KN_SEL_INSERT ? WAVES * (STAGE / (DT == RA_BF16 ? 256 : 512)) * sizeof(int) : 0);
     if (lds > RA_LDS_LIMIT)
         RA_FAIL(RA_EUNSUP, "knn %d needs %zu bytes of LDS (limit %d)", c.knn, lds, RA_LDS_LIMIT);
     RA_LDS_OPT_IN((knn_kernel<DT, WAVES, SEL, STAGE>), lds);
@@ -515,12 +613,13 @@ void ra_knn_set_selection_override(int v) { g_knn_selection_override = v; }
 // queries x 64 list slots of 8 bytes beside the stage buffers for lists of up to 48 keys, knn slots for
 // longer ones. fp32 operands take twice the registers: 4 wavefronts.
 static ra_status knn_launch(const KnnCall& c, ra_dtype dt) {
-    const bool buf = c.knn <= KN_BUFFERED_KNN;
     if (dt == RA_BF16) {
-        if (buf) return knn_launch_as<RA_BF16, 8, KN_SEL_LDS, 16384>(c);
+        if (c.knn <= 32) return knn_launch_as<RA_BF16, 8, KN_SEL_LDS32, 16384>(c);
+        if (c.knn <= KN_BUFFERED_KNN) return knn_launch_as<RA_BF16, 8, KN_SEL_LDS48, 16384>(c);
         return knn_launch_as<RA_BF16, 8, KN_SEL_INSERT, 16384>(c);
     }
-    if (buf) return knn_launch_as<RA_F32, 4, KN_SEL_LDS, 16384>(c);
+    if (c.knn <= 32) return knn_launch_as<RA_F32, 4, KN_SEL_LDS32, 16384>(c);
+    if (c.knn <= KN_BUFFERED_KNN) return knn_launch_as<RA_F32, 4, KN_SEL_LDS48, 16384>(c);
     return knn_launch_as<RA_F32, 4, KN_SEL_INSERT, 16384>(c);
 }
 

@@ -95,6 +95,26 @@ def test_knn_monotone_stream(dtype, knn, rising, knn_selection):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("knn", [1, 31, 32, 33, 47, 48])
+@pytest.mark.parametrize("half", [0, 1])
+def test_knn_runs_of_one_lane(dtype, knn, half):
+    """The keys that reach a threshold are all in the rows that one of a query's two lanes scores (four rows in eight; the
+    mean query is zero, so the stream is in storage order): that lane's pending run is full again and again, the
+    other's holds nothing or ties. Integer scores: the oracle's lists."""
+    N, M = 515, 70
+    i = np.arange(N)
+    rising = np.where(i // 4 % 2 == half, i, i % 3)
+    K = np.zeros((N, 128))
+    K[:, 0], K[:, 1] = rising % 128, rising // 128
+    Q = np.zeros((M, 128))
+    Q[:, 0] = np.where(np.arange(M) % 2 == 0, 1, -1)
+    Q[:, 1] = 128 * Q[:, 0]
+    got = ra.ra_knn(torch.from_numpy(K).to(dtype).to(DEV)[None, None],
+                    torch.from_numpy(Q).to(dtype).to(DEV)[None, None], knn).cpu().numpy()[0, 0]
+    assert np.array_equal(got, OM.knn_lists(Q[:2], K, knn)[0][np.arange(M) % 2])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("knn", [7, 32, 64])
 def test_knn_stream_order_against_a_minority_of_queries(dtype, knn, knn_selection):
     """The keys are streamed by descending inner product with the head's mean query. Here 60 % of
