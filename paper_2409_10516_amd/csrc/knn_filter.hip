@@ -110,6 +110,20 @@ __global__ __launch_bounds__(256) void kf_maxabs_kernel(const void* __restrict__
     if (tid < RA_D) atomicMax(&maxabs[(size_t)blockIdx.y * RA_D + tid], m[tid]);
 }
 
+// sum and maximum over the 16 lanes of a row
+__device__ __forceinline__ float kf_sum16(float x, int lane) {
+    x += __uint_as_float(lane_xor32<1>(__float_as_uint(x), lane));
+    x += __uint_as_float(lane_xor32<2>(__float_as_uint(x), lane));
+    x += __uint_as_float(lane_xor32<4>(__float_as_uint(x), lane));
+    return x + __uint_as_float(lane_xor32<8>(__float_as_uint(x), lane));
+}
+__device__ __forceinline__ uint32_t kf_max16(uint32_t x, int lane) {
+    x = max(x, lane_xor32<1>(x, lane));
+    x = max(x, lane_xor32<2>(x, lane));
+    x = max(x, lane_xor32<4>(x, lane));
+    return max(x, lane_xor32<8>(x, lane));
+}
+
 __device__ __forceinline__ float kf_scale(uint32_t maxabs_bits) {
     return maxabs_bits == 0u ? 1.f : __uint_as_float(maxabs_bits) * (1.0f / 127.0f);
 }
@@ -119,8 +133,7 @@ __device__ __forceinline__ int kf_exponent(const uint32_t (&maxabs_bits)[8]) {
     uint32_t top = 0u;
 #pragma unroll
     for (int c = 0; c < 8; ++c) top = max(top, maxabs_bits[c]);
-#pragma unroll
-    for (int d = 1; d < 16; d <<= 1) top = max(top, (uint32_t)__shfl_xor((int)top, d));
+    top = kf_max16(top, threadIdx.x % RA_WAVE);
     return __builtin_amdgcn_frexp_expf(__uint_as_float(top));       // (0 for zero, infinity and NaN)
 }
 
@@ -208,25 +221,24 @@ __global__ __launch_bounds__(1024) void kf_pack_kernel(const void* __restrict__ 
     for (int sg = blockIdx.x; sg < nseg; sg += gridDim.x) {
         if (tid < 6) s_top[tid] = 0u;
         __syncthreads();
+        uint32_t top[6] = {0u, 0u, 0u, 0u, 0u, 0u};      // of the rows of these 16 lanes: |e|^2, |x|^2, |k|^2, |x|^2 by step
         for (int64_t p = (int64_t)sg * KF_SEG + tid / 16; p < (int64_t)(sg + 1) * KF_SEG; p += 64) {
-            uint32_t w[2] = {0u, 0u};
-            float e2 = 0.f, x2 = 0.f, k2 = 0.f, xs[3] = {0.f, 0.f, 0.f};
-            const bool live = first + p < N;
-            if (live) {
+            uint2 w = make_uint2(0u, 0u);
+            if (first + p < N) {
                 const u64 entry = ord[first + p];
-                float v[8];
+                float v[8], sum[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                 kf_row8<DT>(K, (kv * N + (int64_t)(uint32_t)entry) * RA_D + 8 * l16, v);
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
                     float x = rintf(v[c] * inv[c]);
                     x = fminf(fmaxf(x, -127.f), 127.f);
                     const float e = __fmaf_rn(-x, sc[c], v[c]) * inv[c];
-                    e2 += e * e;
-                    x2 += x * x;
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) xs[t] += kf_step_of(at[c]) == t + 1 ? x * x : 0.f;
                     const float k = __builtin_amdgcn_ldexpf(v[c], -k_exp);
-                    k2 += k * k;
+                    sum[0] += e * e;
+                    sum[1] += x * x;
+                    sum[2] += k * k;
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) sum[3 + t] += kf_step_of(at[c]) == t + 1 ? x * x : 0.f;
                     s_row[tid / 16][at[c]] = (unsigned char)((uint32_t)(int)x & 255u);
                 }
                 if (l16 == 0) {
@@ -234,34 +246,21 @@ __global__ __launch_bounds__(1024) void kf_pack_kernel(const void* __restrict__ 
                     if (p == (int64_t)sg * KF_SEG) s_b[0] = b;
                     if (p == (int64_t)(sg + 1) * KF_SEG - 1 || first + p == N - 1) s_b[1] = b;
                 }
-            }
-            __syncthreads();
-            if (live) {
-                const uint2 u = *reinterpret_cast<const uint2*>(&s_row[tid / 16][8 * l16]);
-                w[0] = u.x;
-                w[1] = u.y;
+                // a NaN (from non-finite keys) has the largest bits of all
+#pragma unroll
+                for (int t = 0; t < 6; ++t) top[t] = max(top[t], __float_as_uint(kf_sum16(sum[t], tid % RA_WAVE)) & 0x7fffffffu);
+                kf_wave_sync();                          // (a row is a wavefront's own)
+                w = *reinterpret_cast<const uint2*>(&s_row[tid / 16][8 * l16]);
+                kf_wave_sync();
             }
             if (p < rows8)
                 K8[((size_t)gl * 4 + ((l16 >> 1) & 3)) * rows8 * 4 + (p >> 5) * 128 + ((int)(p & 31) + 32 * (l16 >> 3)) * 2 +
-                   (l16 & 1)] = make_uint2(w[0], w[1]);
-#pragma unroll
-            for (int d = 1; d < 16; d <<= 1) {
-                e2 += __shfl_xor(e2, d);
-                x2 += __shfl_xor(x2, d);
-#pragma unroll
-                for (int t = 0; t < 3; ++t) xs[t] += __shfl_xor(xs[t], d);
-                k2 += __shfl_xor(k2, d);
-            }
-            if (l16 == 0) {
-                // a NaN (from non-finite keys) has the largest bits of all
-                atomicMax(&s_top[0], __float_as_uint(e2) & 0x7fffffffu);
-                atomicMax(&s_top[1], __float_as_uint(x2) & 0x7fffffffu);
-                atomicMax(&s_top[2], __float_as_uint(k2) & 0x7fffffffu);
-#pragma unroll
-                for (int t = 0; t < 3; ++t) atomicMax(&s_top[3 + t], __float_as_uint(xs[t]) & 0x7fffffffu);
-            }
-            __syncthreads();
+                   (l16 & 1)] = w;
         }
+        if (l16 == 0)
+#pragma unroll
+            for (int t = 0; t < 6; ++t) atomicMax(&s_top[t], top[t]);
+        __syncthreads();
         if (tid == 0) {
             // (finite whatever the keys are: where one is not, every query's bound is infinite, and nothing
             // may turn that into a NaN)
@@ -400,8 +399,8 @@ __global__ __launch_bounds__(256) void kf_queries_kernel(const void* __restrict_
         at[c] = place[(size_t)gl * RA_D + 8 * l16 + c];
         mm += m[c] * m[c];
     }
-#pragma unroll
-    for (int d = 1; d < 16; d <<= 1) mm += __shfl_xor(mm, d);
+    const int lane = tid % RA_WAVE;
+    mm = kf_sum16(mm, lane);
     const float k_max = __builtin_amdgcn_ldexpf(1.001f * sqrtf(__uint_as_float(k_top[gl])), kf_exponent(mx));
     const float m_norm = 1.001f * sqrtf(mm);
     const bool mean = mm >= 1e-30f && mm <= 1e30f && m_norm * k_max < 1e36f;
@@ -412,8 +411,7 @@ __global__ __launch_bounds__(256) void kf_queries_kernel(const void* __restrict_
         kf_row8<DT>(Q, ((size_t)graph * M + j) * RA_D + 8 * l16, v);
 #pragma unroll
         for (int c = 0; c < 8; ++c) qm += v[c] * m[c];
-#pragma unroll
-        for (int d = 1; d < 16; d <<= 1) qm += __shfl_xor(qm, d);
+        qm = kf_sum16(qm, lane);
         float a = mean ? qm / mm : 0.f;
         if (!(fabsf(a) < 1e30f)) a = 0.f;
 #pragma unroll
@@ -422,11 +420,8 @@ __global__ __launch_bounds__(256) void kf_queries_kernel(const void* __restrict_
             top = fmaxf(top, fabsf(p[c]));
             q_top = fmaxf(q_top, fabsf(v[c]));
         }
-#pragma unroll
-        for (int d = 1; d < 16; d <<= 1) {
-            top = fmaxf(top, __shfl_xor(top, d));
-            q_top = fmaxf(q_top, __shfl_xor(q_top, d));
-        }
+        top = __uint_as_float(kf_max16(__float_as_uint(top), lane));          // (not negative: the bits order like the numbers)
+        q_top = __uint_as_float(kf_max16(__float_as_uint(q_top), lane));
         const float s = top > 0.f ? top * (1.0f / 127.0f) : 1.f, inv = 1.0f / s;
         const int q_exp = __builtin_amdgcn_frexp_expf(q_top);
         float f2 = 0.f, n2 = 0.f, q2 = 0.f, ys[3] = {0.f, 0.f, 0.f};      // |f|^2, |r' / s|^2, |q 2^-q_exp|^2, parts of |y|^2
@@ -444,15 +439,12 @@ __global__ __launch_bounds__(256) void kf_queries_kernel(const void* __restrict_
             for (int t = 0; t < 3; ++t) ys[t] += kf_step_of(at[c]) == t + 1 ? y * y : 0.f;
             s_row[tid / 16][at[c]] = (unsigned char)((uint32_t)(int)y & 255u);
         }
-        __syncthreads();
+        f2 = kf_sum16(f2, lane);
+        n2 = kf_sum16(n2, lane);
+        q2 = kf_sum16(q2, lane);
 #pragma unroll
-        for (int d = 1; d < 16; d <<= 1) {
-            f2 += __shfl_xor(f2, d);
-            n2 += __shfl_xor(n2, d);
-            q2 += __shfl_xor(q2, d);
-#pragma unroll
-            for (int t = 0; t < 3; ++t) ys[t] += __shfl_xor(ys[t], d);
-        }
+        for (int t = 0; t < 3; ++t) ys[t] = kf_sum16(ys[t], lane);
+        kf_wave_sync();                                  // (a row is a wavefront's own)
         if (row < M) {
             Q8[((size_t)gl * M + j) * 16 + l16] = *reinterpret_cast<const uint2*>(&s_row[tid / 16][8 * l16]);
             if (l16 == 0) {
@@ -470,7 +462,7 @@ __global__ __launch_bounds__(256) void kf_queries_kernel(const void* __restrict_
                 out[2] = make_float4(slack, 0.f, 0.f, 0.f);
             }
         }
-        __syncthreads();
+        kf_wave_sync();
     }
 }
 
