@@ -148,13 +148,15 @@ ra_status ra_launch_flat_topk(const void* q, const void* K, ra_dtype dt, int n_s
 ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
                         int64_t N, int64_t M, int knn, void* workspace, size_t workspace_bytes, hipStream_t st,
                         int32_t* L);
-// the long part of the key stream through 8-bit products (knn_filter.hip)
+// the long part of the key stream through 8-bit products (knn_filter.hip); it can go on from a place this many keys behind
+// its first, or a multiple
+#define KN_FILTER_SEGMENT 512
 size_t ra_knn_filter_bytes(int graphs, int64_t N, int64_t M, int knn);
 float* ra_knn_filter_scores(void* workspace, int graphs, int64_t N, int64_t M, int knn);
 ra_status ra_launch_knn_filter_scales(const void* K, ra_dtype dt, int n_seq_kv, int64_t N, uint32_t* maxabs,
                                       hipStream_t st);
 ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const void* order, int graphs, int g0,
-                               int n_graphs, int n_q, int n_kv, int64_t N, int64_t M, int knn, int64_t first,
+                               int n_graphs, int n_q, int n_kv, int64_t N, int64_t M, int knn, int64_t first, int64_t from,
                                const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
                                const int** resume, int* resume_queries, int* resume_blocks);
 void ra_knn_set_selection_override(int v);      // RA_TEST_KNN_AUTO / _FILTER / _LDS

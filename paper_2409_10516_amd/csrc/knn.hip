@@ -570,7 +570,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
         if (lane < knn) {
             const u64 k = my_lists[BUF ? kn_slot(lane, jq) : jq * lstride + lane];
             L_out[((size_t)graph * M + qr) * knn + lane] = knn_key_id(k);
-            if (scores && !resume)                 // only the first part of the stream: it goes on with these
+            if (scores)                            // (the filter goes on with these)
                 scores[((size_t)blockIdx.y * M + qr) * knn + lane] = k == 0ull ? -INFINITY : knn_key_score(k);
         }
     }
@@ -623,27 +623,33 @@ static ra_status knn_launch(const KnnCall& c, ra_dtype dt) {
     return knn_launch_as<RA_F32, 4, KN_SEL_INSERT, 16384>(c);
 }
 
-// Keys of the stream that are multiplied as they are before knn_filter.hip takes over (N: all of them).
-// A thirty-second of the stream, and at least enough that thresholds are near final (in the filter a
-// kept key costs about ten ruled-out ones). The filter pays where what it saves on N x M products
-// exceeds what packing N keys and M queries and the larger scratch allocation cost. Whole calls of ra_knn, lists of
-// 32, ms without -> with:
-//   bf16, 32 heads: 16K keys x 8K queries 1.58 -> 1.60, x 16K 2.90 -> 2.64; 32K x 4K 1.54 -> 1.62, x 8K 2.65 -> 2.14,
-//     x 32K 9.6 -> 6.5; 40K x 4K 1.87 -> 1.88; 48K x 2K 1.32 -> 1.65, x 3K 2.01 -> 1.94, x 8K 3.78 -> 2.76;
-//     128K x 512 2.45 -> 3.21, x 2K 2.95 -> 3.22, x 3K 4.87 -> 3.90, x 8K 9.31 -> 5.50.
-//   bf16, 8 heads: 48K x 8K 1.13 -> 1.31, x 16K 1.94 -> 1.68; 1M x 4K 15.7 -> 16.1, x 8K 18.7 -> 16.1;
-//     4 heads: within a tenth of each other up to 8K queries; 48K x 16K 1.10 -> 0.98 (1M x 64K, lists of 48: 74.7 -> 49.9).
-//   float32 (a product costs sixteen 8-bit ones): 4K keys gain little (8 heads x 512 queries 0.42 -> 0.42, x 16K 1.55 ->
-//     1.17); 8K gain with one head and 512 queries already (0.73 -> 0.44); 32 heads, 16K x 8K 9.7 -> 3.0.
+// Keys of the stream that are multiplied as they are before knn_filter.hip takes over (N: all of them): enough that
+// thresholds are near final for queries with much in common (in the filter a kept key costs about ten ruled-out
+// ones; where it keeps too many it gives up, and is tried again after an eighth of the stream). bf16: a
+// thirty-second of the stream and at least 4096. float32, whose products cost sixteen times as much: a sixty-fourth
+// and at least sixteen times a list's length. The filter pays where what it saves on N x M products exceeds what packing
+// N keys and M queries and the larger scratch allocation cost. Whole calls of ra_knn, lists of 32, ms without -> with:
+//   bf16, 32 heads: 8K keys x 8K queries 0.82 -> 1.05; 16K x 4K 0.78 -> 0.99, x 16K 2.55 -> 2.00; 32K x 4K 1.47 -> 1.37, x
+//     32K 8.7 -> 4.8; 128K x 2K 2.98 -> 3.33, x 32K 33.3 -> 13.1.
+//   bf16, fewer heads: 4 heads, 16K x 16K 0.42 -> 0.46; 8 heads, 64K x 64K 8.5 -> 4.0.
+//   bf16, first keys 1024 / 2048 / 4096 / 8192: 32K x 32K x 32 4.83 / 4.86 / 4.91 / 5.34; 128K x 64K x 4 of the mixture law, lists
+//     of 48: 11.8 / 11.5 / 10.5 / 10.3.
+//   float32: 32 heads, 2K x 2K 0.40 -> 0.35, 4K x 4K 1.42 -> 0.59, 16K x 4K 4.9 -> 1.26; 8 heads, 8K x 8K 1.41 -> 0.50; one head with 512
+//     queries gains from 8K keys on (0.73 -> 0.44). First keys 512 / 1024 / 2048: 16K x 4K x 32 1.26 / 1.33 / 1.58; 64K x 8K x 8 2.11 /
+//     1.50 / 1.61; lists of 64, 16K x 8K x 8 2.81 / 2.58 / 2.70.
 // What decides in bf16 is the number of queries in all heads together, about 100K from 48K keys on and 260K below; the
 // line takes the queries of one head below 48K keys (32 heads: the same) and none from there on, which
-// costs calls with few queries up to 0.9 ms.
-static int64_t knn_first_keys(ra_dtype dt, int64_t N, int64_t M) {
-    int64_t first = dt == RA_BF16 ? 4096 : 2048;
+// costs calls with few queries up to 0.4 ms. In float32 the number of products decides below 8K keys.
+static int64_t knn_first_keys(ra_dtype dt, int graphs, int64_t N, int64_t M, int knn) {
     if (g_knn_selection_override == RA_TEST_KNN_LDS) return N;
     if (g_knn_selection_override == RA_TEST_KNN_FILTER) return N > 128 ? 128 : N;
-    if (dt == RA_BF16 ? !(N >= 49152 || (N >= 16384 && M >= 8192)) : N < 8192) return N;
-    if (first < N / 32) first = N / 32;
+    if (dt == RA_BF16) {
+        if (N < 16384 || (N < 49152 && M < 8192)) return N;
+        const int64_t first = N / 32 > 4096 ? N / 32 : 4096;
+        return (first + 127) & ~(int64_t)127;
+    }
+    if (N < 2048 || (N < 8192 && (double)graphs * N * M < 1e8)) return N;
+    const int64_t first = N / 64 > 16 * knn ? N / 64 : 16 * knn;
     return (first + 127) & ~(int64_t)127;
 }
 // graphs whose 8-bit copies and scores are in memory at one time
@@ -660,7 +666,7 @@ static size_t align_256(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t ra_knn_workspace_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn, bool plain) {
     const int graphs = n_seq * n_q;
     size_t b = align_256(ra_knn_order_bytes(graphs, N));
-    if (!plain && knn_first_keys(dt, N, M) < N)
+    if (!plain && knn_first_keys(dt, graphs, N, M, knn) < N)
         b += align_256((size_t)n_seq * n_kv * RA_D * 4) +
              ra_knn_filter_bytes(knn_graphs_at_once(graphs, N, M, knn), N, M, knn);
     return b;
@@ -675,7 +681,7 @@ ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, in
     const int graphs = n_seq * n_q;
     // (without room for the 8-bit copies the whole stream is multiplied as it is: the same lists)
     const bool room = workspace_bytes >= ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false);
-    const int64_t first = room ? knn_first_keys(dt, N, M) : N;
+    const int64_t first = room ? knn_first_keys(dt, graphs, N, M, knn) : N;
     KnnCall c{K, Q, workspace, 0, graphs, n_q, n_kv, N, first, M, knn, L, nullptr, st, nullptr, 0, 0};
     if (first == N) return knn_launch(c, dt);
     char* ws = reinterpret_cast<char*>(workspace) + align_256(ra_knn_order_bytes(graphs, N));
@@ -691,11 +697,18 @@ ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, in
         c.resume = nullptr;
         rc = knn_launch(c, dt);
         if (rc != RA_OK) return rc;
-        rc = ra_launch_knn_filter(K, Q, dt, workspace, graphs, g0, c.n_graphs, n_q, n_kv, N, M, knn, first, maxabs, ws, st, L,
-                                  &c.resume, &c.resume_queries, &c.resume_blocks);
-        if (rc != RA_OK) return rc;
-        c.n_stream = N;                            // where the filter gave up (seldom): the stream to its end
-        rc = knn_launch(c, dt);
+        // what gives up in the filter goes on here up to the next place where it may pay again, then to the end
+        int64_t from = first;
+        for (int more : {32, 8, 1}) {
+            const int64_t next = more == 1 ? N : first + (N / more - first + KN_FILTER_SEGMENT - 1) / KN_FILTER_SEGMENT * KN_FILTER_SEGMENT;
+            if (more > 1 && (N / more < 2 * from || next >= N)) continue;
+            rc = ra_launch_knn_filter(K, Q, dt, workspace, graphs, g0, c.n_graphs, n_q, n_kv, N, M, knn, first, from, maxabs, ws,
+                                      st, L, &c.resume, &c.resume_queries, &c.resume_blocks);
+            if (rc != RA_OK) return rc;
+            c.n_stream = from = next;
+            rc = knn_launch(c, dt);
+            if (rc != RA_OK) return rc;
+        }
     }
     return rc;
 }

@@ -50,13 +50,14 @@ typedef int i32x16 __attribute__((ext_vector_type(16)));
 
 #define KF_WAVES 8
 #define KF_THREADS (KF_WAVES * RA_WAVE)
-#define KF_SEG 512                 // keys that share one bound
+#define KF_SEG KN_FILTER_SEGMENT   // keys that share one bound
 #define KF_SEG_BLOCKS (KF_SEG / 32)
 #define KF_OPERAND (RA_WAVE * 16)  // bytes of one step's operand of 32 keys
 #define KF_RING 8                  // operands a wavefront has in LDS or on their way there
 #define KF_RUN 3                   // scored keys a lane can hold for its query's list
 #define KF_RUNS (2 * KF_RUN)       // ... and the two lanes of a query together
 #define KF_PENDING 64              // keys a query set can have waiting to be scored (a batch is 32; a block may add to 31)
+#define KF_MEET 4                  // segments between two meetings of a workgroup's wavefronts
 #define KF_HOLD 16                 // segments at most between two trials of an earlier look
 #define KF_RANK_SAMPLE 512         // queries whose variance ranks the dimensions (at most)
 
@@ -474,7 +475,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     const void* __restrict__ K, const void* __restrict__ Q, const u64* __restrict__ order, int64_t order_stride,
     const unsigned char* __restrict__ K8, int64_t rows8, const unsigned char* __restrict__ Q8,
     const float4* __restrict__ qinfo, const KfSegment* __restrict__ seg, int nseg, int g0, int n_q, int n_kv, int64_t N,
-    int64_t M, int knn, int first, float* scores, int32_t* L, int* __restrict__ resume) {
+    int64_t M, int knn, int first, int from, float* scores, int32_t* L, int* resume) {
     __shared__ int s_pend[KF_WAVES][NQ][KF_PENDING];
     __shared__ int s_count[KF_WAVES][NQ];
     __shared__ u64 s_run[KF_WAVES][NQ][KF_RUN][RA_WAVE];
@@ -482,6 +483,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     __shared__ __align__(16) unsigned char s_ring[KF_WAVES][KF_RING * KF_OPERAND];
     __shared__ __align__(16) float4 s_query[KF_WAVES][NQ][2][32];      // of KfQuery: [a, f, r, inv], [y1, y2, y3, tau]
     __shared__ float s_slack[KF_WAVES][NQ][32];
+    __shared__ int s_kept, s_seen;                     // of the workgroup's sets: keys not ruled out, blocks looked at
     const int tid = threadIdx.x, wv = tid / RA_WAVE, lane = tid % RA_WAVE;
     const int col = lane & 31, half = lane >> 5;
     const int gl = blockIdx.y, graph = g0 + gl, seq = graph / n_q, h = graph % n_q, kvh = h / (n_q / n_kv);
@@ -493,6 +495,18 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     float* sc_g = scores + (size_t)gl * M * knn;
     int32_t* L_g = L + (size_t)graph * M * knn;
 
+    // the stream position this wavefront goes on from: `from`, or where it gave up behind that (knn.hip has
+    // multiplied what lies between); nothing is left where it came to the end in a launch before
+    int* my_resume = resume + ((size_t)gl * gridDim.x + blockIdx.x) * KF_WAVES + wv;
+    int begin = first;
+    if (from > first) {
+        begin = __builtin_amdgcn_readfirstlane(*my_resume);
+        if (begin < from) begin = from;
+        if (begin >= N) begin = -1;
+    }
+    if (tid == 0) s_kept = s_seen = 0;
+    __syncthreads();
+    if (begin < 0) return;                             // (there is no barrier behind this one)
     i32x4 b[NQ][4];
 #pragma unroll
     for (int s = 0; s < NQ; ++s) {
@@ -501,7 +515,9 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
         const i32x4* src = reinterpret_cast<const i32x4*>(Q8 + ((size_t)gl * M + qr) * RA_D + 64 * half);
 #pragma unroll
         for (int c = 0; c < 4; ++c) b[s][c] = src[c];
-        s_query[wv][s][half][col] = qinfo[KF_QUERY16 * ((size_t)gl * M + qr) + half];
+        float4 qi = qinfo[KF_QUERY16 * ((size_t)gl * M + qr) + half];
+        if (half == 1) qi.w = sc_g[(size_t)qr * knn + knn - 1];        // the threshold as it is now
+        s_query[wv][s][half][col] = qi;
         if (half == 0) s_slack[wv][s][col] = qinfo[KF_QUERY16 * ((size_t)gl * M + qr) + 2].x;
         s_count[wv][s] = 0;
         s_fill[wv][s][lane] = 0;
@@ -690,7 +706,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     //      it does not, tries again every so often (thresholds are the further away the later in the stream).
     // (The wavefront's own scalars; the compiler does not see that they are, through the loops of the rare path.)
     auto uniform = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
-    int blk = 0, look = 4, fails = 0, hold = 1, wait = 1;
+    int blk = uniform((begin - first) / 32), look = 4, fails = 0, hold = 1, wait = 1, counted = blk;
     // at the end of a segment: true when the wavefront goes on as it did
     auto same_look = [&]() __attribute__((always_inline)) -> bool {
         const int was = look = uniform(look);
@@ -708,13 +724,33 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
         fails = 0;
         return look == was;
     };
-    // Scoring a kept key costs about ten times what ruling it out does. Inputs whose scores the bound
-    // cannot tell apart (most keys tied, a few dimensions that dwarf the others) are better off in
-    // knn.hip's loop: a wavefront that has kept more than an eighth of what it has seen stops and leaves the rest
-    // of its stream there.
-    auto keeps_too_much = [&]() __attribute__((always_inline)) { return uniform(kept) > (int64_t)blk * (4 * NQ); };
+    // Scoring a kept key costs about ten times what ruling it out does. Where the bound cannot tell the keys apart (at the
+    // start of a stream whose queries have little in common, or all along: ties, a few dimensions that dwarf the
+    // others) they are better off in knn.hip's loop: when a workgroup's wavefronts have kept more than three keys in 32 (in
+    // float32, whose products cost sixteen times as much, more than eight), each stops at the end of its segment and
+    // leaves its queries' keys there. All of them, because that loop costs a workgroup's whole stream however few of
+    // its queries are left. Whole calls, 4 heads of the mixture law, lists of 48, lines at 1 / 2 / 3 / 4 in 32: 64K keys x
+    // 64K queries 7.8 / 7.8 / 8.0 / 9.8 ms, 128K 12.5 / 13.7 / 10.4 / 10.5, 256K 20.0 / 14.9 / 14.8 / 15.0; float32, 64K
+    // keys x 8K queries, 4 / 8 / 16 / 24 in 32: 7.7 / 3.2 / 5.6 / 3.4 ms.
+    auto keeps_too_much = [&]() __attribute__((always_inline)) -> bool {
+        const int seen = (blk - counted) * NQ;           // (blocks of 32 keys)
+        int all_kept = 0, all_seen = 0;
+        if (lane == 0) {
+            all_kept = atomicAdd(&s_kept, kept) + kept;
+            all_seen = atomicAdd(&s_seen, seen) + seen;
+        }
+        kept = 0;
+        counted = blk;
+        all_kept = uniform(all_kept);
+        all_seen = uniform(all_seen);
+        return all_seen >= KF_WAVES / 2 * KF_SEG_BLOCKS * NQ && (int64_t)all_kept > (int64_t)all_seen * (DT == RA_BF16 ? 3 : 8);
+    };
     // the floors of the segment that opens at block blk; false when none of its keys can reach a threshold
     auto open_segment = [&]() __attribute__((always_inline)) -> bool {
+        // The wavefronts meet every 2048 keys, so that they stay in reach of each other's lines in the caches (1M keys x
+        // 4 heads: 38.2 -> 35.4 ms; x 4 heads of 16K queries, one set per wavefront: 30 -> 16 ms; a meeting every 512
+        // keys: 38.0 and 17 ms). A barrier waits for no wavefront that has ended.
+        if ((blk / KF_SEG_BLOCKS) % KF_MEET == 0) __builtin_amdgcn_s_barrier();
         const float4 g0 = seg_g[2 * (blk / KF_SEG_BLOCKS)], g1 = seg_g[2 * (blk / KF_SEG_BLOCKS) + 1];
         sg_x = g0.x; sg_e = g0.y; sg_b_max = g0.z; sg_b_min = g0.w; sg_x1 = g1.x; sg_x2 = g1.y; sg_x3 = g1.z;
         return set_floors();
@@ -818,8 +854,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
         const u64 some = __ballot(fill > 0);
         fold(s, (uint32_t)some | (uint32_t)(some >> 32), tau, fill);
     }
-    if (lane == 0)
-        resume[((size_t)gl * gridDim.x + blockIdx.x) * KF_WAVES + wv] = stop < nblocks ? first + stop * 32 : 0x7fffffff;
+    if (lane == 0) *my_resume = stop < nblocks ? first + stop * 32 : 0x7fffffff;
 }
 
 static int64_t kf_rows(int64_t N) { return (N + 31) & ~(int64_t)31; }
@@ -861,9 +896,11 @@ ra_status ra_launch_knn_filter_scales(const void* K, ra_dtype dt, int n_seq_kv, 
 }
 
 // Graphs [g0, g0 + n_graphs) of the `graphs` that `order` holds: the rest of their streams from position
-// `first` on. L holds the lists of the first part, ra_knn_filter_scores(workspace, ...) their scores.
+// `from` on. L holds the lists of what came before, ra_knn_filter_scores(workspace, ...) their scores. The first
+// launch of a group of graphs (from == first) makes the 8-bit copies; later ones, whose `from` is a whole number of
+// segments on, are for the queries that gave up in one before (resume: where), for which knn.hip has gone on to `from`.
 ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const void* order, int graphs, int g0,
-                               int n_graphs, int n_q, int n_kv, int64_t N, int64_t M, int knn, int64_t first,
+                               int n_graphs, int n_q, int n_kv, int64_t N, int64_t M, int knn, int64_t first, int64_t from,
                                const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
                                const int** resume, int* resume_queries, int* resume_blocks) {
     const KfLayout l = kf_layout(n_graphs, N, M, knn);
@@ -878,7 +915,8 @@ ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const 
     const int64_t stride = ra_knn_order_stride(N);
     int mq_samples;
     const float* mq = ra_knn_order_mean(order, graphs, N, M, &mq_samples);
-    hipLaunchKernelGGL(kf_zero_kernel, dim3((n_graphs + 255) / 256), dim3(256), 0, st, k_top, n_graphs);
+    if (from == first)
+        hipLaunchKernelGGL(kf_zero_kernel, dim3((n_graphs + 255) / 256), dim3(256), 0, st, k_top, n_graphs);
     const dim3 pgrid((unsigned)(nseg < 128 ? nseg : 128), (unsigned)n_graphs);
     const dim3 qgrid((unsigned)(M / 16 < 255 ? M / 16 + 1 : 256), (unsigned)n_graphs);
     int* res = reinterpret_cast<int*>(ws + l.resume);
@@ -891,16 +929,19 @@ ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const 
     hipLaunchKernelGGL((knn_filter_kernel<DTV, NQV>), grid, dim3(KF_THREADS), 0, st, K, Q, ord, stride,         \
                        reinterpret_cast<unsigned char*>(ws + l.k8), rows8,                                      \
                        reinterpret_cast<unsigned char*>(ws + l.q8), reinterpret_cast<float4*>(ws + l.info),     \
-                       seg, nseg, g0, n_q, n_kv, N, M, knn, (int)first, scores, L, res)
+                       seg, nseg, g0, n_q, n_kv, N, M, knn, (int)first, (int)from, scores, L, res)
 #define KF_GO(DTV)                                                                                              \
     do {                                                                                                        \
-        hipLaunchKernelGGL(kf_rank_kernel<DTV>, dim3((unsigned)n_graphs), dim3(1024), 0, st, Q, mq, mq_samples, \
-                           maxabs, g0, n_q, n_kv, M, place);                                                    \
-        hipLaunchKernelGGL(kf_pack_kernel<DTV>, pgrid, dim3(1024), 0, st, K, ord, stride, maxabs, place, g0,    \
-                           n_q, n_kv, N, first, rows8, nseg, reinterpret_cast<uint2*>(ws + l.k8), seg, k_top);  \
-        hipLaunchKernelGGL(kf_queries_kernel<DTV>, qgrid, dim3(256), 0, st, Q, mq, maxabs, place, k_top, g0,    \
-                           n_q, n_kv, M, knn, scores, reinterpret_cast<uint2*>(ws + l.q8),                      \
-                           reinterpret_cast<float4*>(ws + l.info));                                             \
+        if (from == first) {                                                                                    \
+            hipLaunchKernelGGL(kf_rank_kernel<DTV>, dim3((unsigned)n_graphs), dim3(1024), 0, st, Q, mq,         \
+                               mq_samples, maxabs, g0, n_q, n_kv, M, place);                                    \
+            hipLaunchKernelGGL(kf_pack_kernel<DTV>, pgrid, dim3(1024), 0, st, K, ord, stride, maxabs, place,    \
+                               g0, n_q, n_kv, N, first, rows8, nseg, reinterpret_cast<uint2*>(ws + l.k8), seg,  \
+                               k_top);                                                                          \
+            hipLaunchKernelGGL(kf_queries_kernel<DTV>, qgrid, dim3(256), 0, st, Q, mq, maxabs, place, k_top,    \
+                               g0, n_q, n_kv, M, knn, scores, reinterpret_cast<uint2*>(ws + l.q8),              \
+                               reinterpret_cast<float4*>(ws + l.info));                                         \
+        }                                                                                                       \
         if (NQ == 4) KF_GO_N(DTV, 4); else if (NQ == 2) KF_GO_N(DTV, 2); else KF_GO_N(DTV, 1);                  \
     } while (0)
     if (dt == RA_BF16) KF_GO(RA_BF16); else KF_GO(RA_F32);
