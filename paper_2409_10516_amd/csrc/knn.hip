@@ -9,16 +9,15 @@
 // selection threshold of a query is a single per-lane register: the common case is a
 // max-tree over the lane's 16 scores and one compare. Only scores that reach the threshold go
 // further (about knn * ln(N / knn) per query over a stream in storage order, a third of that in
-// the order the keys are streamed in here: see knn_order.hip). Two ways to keep them:
-//   KN_SEL_LDS* (knn <= KN_BUFFERED_KNN): a query owns KN_CAP slots in LDS: its best keys so far, then two runs of
-//     pending slots, one per lane that scores for it. A lane appends a score and an id to its own run with a single LDS
-//     write (its fill count is a register); when a run cannot take what a lane is about to append, the wavefront
-//     merges the runs of all its 32 queries into their lists at once, the two lanes of a query holding its keys in
-//     registers: sorting networks whose exchanges are one maximum and one minimum for 64 lanes, between the two
-//     lanes by half-wave swaps. (460 instructions for 32 queries; one query at a time, its 64 slots sorted across
-//     the lanes by a bitonic network, took 200 for each. First 4096 keys of 32 heads x 128K queries, lists of 32:
-//     12.5 -> 7.0 ms, of which writing scores and ids as they are, without a branch, instead of whole keys 0.8 ms.)
-//   KN_SEL_INSERT (longer lists): sorted insertion, one key at a time, by the whole wavefront.
+// the order the keys are streamed in here: see knn_order.hip). The two lanes of a query hold its best keys so far in
+// registers, sorted, half of the list each, and a run of pending slots in LDS each: a lane appends a score and an
+// id to its own run with a single LDS write; when a run cannot take what a lane is about to append, the wavefront
+// merges the runs of all its 32 queries into their lists at once, by sorting networks whose exchanges are one
+// maximum and one minimum for 64 lanes, between the two lanes by half-wave swaps. (400 to 600 instructions for 32
+// queries; one query at a time, its 64 slots sorted across the lanes by a bitonic network, took 200 for each. First
+// 4096 keys of 32 heads x 128K queries, lists of 32: 12.5 -> 7.0 ms, of which writing scores and ids as they are, without
+// a branch, instead of whole keys 0.8 ms. Lists of 64, by sorted insertion before, 3000 keys x 3000 queries x 32 heads:
+// 2.0 -> 0.27 ms.)
 // Between two merges a threshold is stale but valid (never above the true one), so nothing is
 // lost.
 //
@@ -41,12 +40,9 @@
 
 #include "common.h"
 
-#define KN_CAP 62                 // slots of a query in the buffered selection: what fits beside the stage buffers
-#define KN_BUFFERED_KNN 48        // longest list that leaves room for pending slots
-// how the top-knn selection keeps keys that reached a threshold until they are merged into a list
-#define KN_SEL_INSERT 0           // not at all: sorted insertion, one key at a time
-#define KN_SEL_LDS32 1            // in pending runs behind the list in LDS (KN_CAP slots per query), lists of up to 32
-#define KN_SEL_LDS48 2            // ... and of 33 to 48 keys
+#define KN_PLACES 16              // places of a pending run: one more than it holds (see knn_kernel)
+#define KN_PEND (KN_PLACES - 1)
+#define KN_RUN_BYTES (KN_PLACES * RA_WAVE * 8)      // pending runs of a wavefront
 
 typedef unsigned long long u64;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -56,26 +52,14 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u64 knn_key(float score, int id) {
     return ((u64)f32_ordered(score) << 31) | (u64)(0x7fffffffu - (uint32_t)id);
 }
-__device__ __forceinline__ int knn_key_id(u64 k) { return (int)(0x7fffffffu - ((uint32_t)k & 0x7fffffffu)); }
-// threshold of a list whose last key is `last`: what cannot be in it (minus infinity and what is no number) stays below
-__device__ __forceinline__ float knn_threshold(u64 last) {
-    return last == 0ull ? -3.402823466e38f : f32_from_ordered((uint32_t)(last >> 31));
+__device__ __forceinline__ int knn_key_id(u64 k) { return k == 0ull ? -1 : (int)(0x7fffffffu - ((uint32_t)k & 0x7fffffffu)); }
+// memory that one lane of a wavefront wrote and another reads: the hardware keeps the wavefront's order,
+// this keeps the compiler's
+__device__ __forceinline__ void kn_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 __device__ __forceinline__ float knn_key_score(u64 k) { return f32_from_ordered((uint32_t)(k >> 31)); }
-
-// Insert (score, id) into the sorted list lst[0..knn) (all 64 lanes cooperate).
-// Returns the list's new threshold: the score of its last entry, or -inf while not full.
-__device__ __forceinline__ float knn_insert(u64* lst, int knn, float score, int id, int lane) {
-    const u64 nk = knn_key(score, id);
-    const u64 e = lane < knn ? lst[lane] : 0ull;
-    const int pos = __popcll(__ballot(lane < knn && e > nk));   // sorted: a prefix beats nk
-    if (pos < knn) {
-        if (lane >= pos && lane < knn - 1) lst[lane + 1] = e;
-        if (lane == pos) lst[pos] = nk;
-    }
-    const u64 last = lst[knn - 1];
-    return last == 0ull ? -INFINITY : knn_key_score(last);
-}
 
 // ---- merging pending keys into lists, all 32 queries of a wavefront at once ------------------------------
 // Lane (col, half) holds a part of the keys of query col. In-lane exchanges work on registers of one lane, cross
@@ -141,64 +125,47 @@ __device__ __forceinline__ void kn_sort_pending(double (&v)[N], int half) {
     kn_merge<N, false>(v);
 }
 
-// Slots of the 32 queries of a wavefront: list slot s of query col at kn_slot(s, col) (32 slots of a query, like one
-// slot of the 32 queries, are in different banks: a list leaves one slot per lane); WIDE (lists of 33 to 48 keys): 48 list
-// slots and runs of 6, else 32 list slots (however short the list has to be) and runs of 14. Behind the list the
-// runs, as they come: place i of all lanes' runs is 64 scores, then 64 ids. A run has a place more than it holds: a lane
-// writes every score to the next free place, and only one that belongs there makes the place taken.
-__device__ __forceinline__ int kn_slot(int s, int col) { return s * 32 + (col ^ (s & 31)); }
-template <bool WIDE> struct KnSlots {
-    static constexpr int list = WIDE ? 48 : 32, pend = WIDE ? 6 : 14;
-    static_assert(list + 2 * (pend + 1) == KN_CAP, "lists and runs fill a query's slots");
-};
-// Merges the pending keys (`fill` of this lane) of all 32 queries into their lists, which stay in descending order.
-// Returns the query's new threshold: the score of its knn-th key, the lowest number while there is none.
-template <bool WIDE>
-__device__ __forceinline__ float knn_fold(u64* slots, int knn, int col, int half, int fill) {
-    constexpr int PEND = WIDE ? 8 : 16;               // (a power of two for the networks: two more than a run holds)
-    const uint32_t* run = reinterpret_cast<const uint32_t*>(slots + KnSlots<WIDE>::list * 32) + 32 * half + col;
-    double p[PEND];
-    p[PEND - 2] = p[PEND - 1] = 0.0;
+// Merges the pending keys (`fill` of this lane; place i of all lanes' runs is 64 scores, then 64 ids) of all 32 queries
+// into their lists: the lower lane of a query holds its best LN keys, descending, the upper lane the next LN.
+template <int LN>
+__device__ __forceinline__ void knn_fold(double (&list)[LN], const uint32_t* run, int half, int fill) {
+    static_assert(LN == 16 || LN == 32, "lists of up to 32 or up to 64 keys");
+    double p[KN_PLACES];
+    p[KN_PLACES - 1] = 0.0;
 #pragma unroll
-    for (int i = 0; i < PEND - 2; ++i) {
+    for (int i = 0; i < KN_PEND; ++i) {
         const u64 k = knn_key(__uint_as_float(run[i * 128]), (int)run[i * 128 + 64]);
         p[i] = __builtin_bit_cast(double, i < fill ? k : 0ull);
     }
-    if constexpr (WIDE) {
-        // a bitonic sequence of 64 over the two lanes: the list's best 32 in the lower; in the upper its other 16, then
-        // the 16 pending keys ascending
-        double v[32];
+    kn_sort_pending<KN_PLACES>(p, half);
+    // list descending against pending ascending (none before its 32): the larger of each pair are the best 2 LN, a
+    // bitonic sequence over the two lanes
+    if constexpr (LN == 16) {
 #pragma unroll
-        for (int i = 0; i < 32; ++i) v[i] = __builtin_bit_cast(double, slots[i < 16 ? kn_slot(i, col) + half * (32 * 32) : kn_slot(i, col)]);
-        kn_sort_pending<PEND>(p, half);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            double low = p[i], same = p[i];
-            kn_swap_halves(low, same);                // low: the lower lane's value in both
-            v[16 + i] = half ? low : v[16 + i];
-            v[24 + i] = half ? p[i] : v[24 + i];
-        }
-        kn_cross<32, true>(v);
-        kn_merge<32, true>(v);
-#pragma unroll
-        for (int i = 0; i < 32; ++i)
-            if (i < 16 || half == 0) slots[kn_slot(i, col) + half * (32 * 32)] = __builtin_bit_cast(u64, v[i]);
+        for (int i = 0; i < 16; ++i) list[i] = __builtin_fmax(list[i], p[i]);
     } else {
-        // list descending against pending ascending: the larger of each pair are the best 32, a bitonic sequence
-        double v[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = __builtin_bit_cast(double, slots[kn_slot(16 * half + i, col)]);
-        kn_sort_pending<PEND>(p, half);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = __builtin_fmax(v[i], p[i]);
-        kn_cross<16, true>(v);
-        kn_merge<16, true>(v);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) slots[kn_slot(16 * half + i, col)] = __builtin_bit_cast(u64, v[i]);
+        for (int i = 0; i < 16; ++i) {
+            double low = p[i], own = p[i];
+            kn_swap_halves(low, own);                 // low: the lower lane's value in both
+            list[i] = __builtin_fmax(list[i], half ? low : 0.0);
+            list[16 + i] = __builtin_fmax(list[16 + i], half ? p[i] : 0.0);
+        }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");        // (the other lane's slot is read below)
-    __builtin_amdgcn_wave_barrier();
-    return knn_threshold(slots[kn_slot(knn - 1, col)]);
+    kn_cross<LN, true>(list);
+    kn_merge<LN, true>(list);
+}
+// The query's threshold, for both its lanes: the score of its knn-th key, or the next number below; the lowest
+// number while there is none (what cannot be in a list, minus infinity and what is no number, stays below).
+template <int LN>
+__device__ __forceinline__ float knn_threshold(const double (&list)[LN], int knn, int half, int lane) {
+    const int at = (knn - 1) & (LN - 1);
+    uint32_t hi = 0u;
+#pragma unroll
+    for (int i = 0; i < LN; ++i) hi = i == at ? (uint32_t)(__builtin_bit_cast(u64, list[i]) >> 32) : hi;
+    const uint32_t other = lane_xor32<32>(hi, lane);
+    if (half != (knn - 1) / LN) hi = other;
+    return hi == 0u ? -3.402823466e38f : f32_from_ordered(hi << 1);
 }
 
 template <int DT> struct Operand;
@@ -313,14 +280,13 @@ __device__ __forceinline__ void store_chunk(unsigned char* buf, int tid, int i, 
 }
 
 // grid: x = block of 32 * WAVES queries, y = graph (seq * n_q + h) - g0. The keys are the first
-// n_stream of the graph's stream order. With `scores` and no `resume` the lists' scores are written
+// n_stream of the graph's stream order. With `scores` the lists' scores are written
 // too, for knn_filter.hip, which takes the rest of the stream; with `resume` (first stream position not
 // yet seen, per graph and block of resume_queries queries, a multiple of 32) the lists are read from L_out and scores and
 // the stream goes on from there.
-// LDS: the lists (per wavefront 32 queries' slots), then two stage buffers of STAGE bytes, then (pending runs) the key
-// ids of a stage per wavefront.
-// SEL (KN_SEL_*) selects how keys wait for their list.
-template <int DT, int WAVES, int SEL, int STAGE>
+// LDS: the pending runs of the wavefronts, then two stage buffers of STAGE bytes, then the key ids of a stage per wavefront.
+// LN: keys of its query's list that a lane holds (16 or 32).
+template <int DT, int WAVES, int LN, int STAGE>
 __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     const void* __restrict__ K, const void* __restrict__ Q, const u64* __restrict__ order,
     int64_t order_stride, int g0, int n_q, int n_kv, int64_t N, int64_t n_stream, int64_t M, int knn,
@@ -337,10 +303,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     static_assert(SBLK == 1 || SBLK == 2, "a stage holds one or two key blocks");
     static_assert(CPT * KN_THREADS * 16 == STAGE, "threads must tile a stage");
     static_assert(KN_THREADS % CPR == 0, "a thread keeps its 16-byte column");
-    constexpr bool BUF = SEL != KN_SEL_INSERT, WIDE = SEL == KN_SEL_LDS48;
-    const int lstride = BUF ? KN_CAP : knn;           // list slots per query
-    u64* lists = reinterpret_cast<u64*>(lds_raw);           // [QPB / 32][lstride][32] (BUF), [QPB][lstride]
-    unsigned char* stage_buf = lds_raw + (size_t)QPB * lstride * sizeof(u64);   // 16-byte aligned: QPB is even
+    unsigned char* stage_buf = lds_raw + WAVES * KN_RUN_BYTES;
     const int tid = threadIdx.x, wv = tid / RA_WAVE, lane = tid % RA_WAVE;
     const int col = lane & 31, half = lane >> 5;
     const int graph = g0 + (int)blockIdx.y, seq = graph / n_q, h = graph % n_q, kvh = h / (n_q / n_kv);
@@ -367,20 +330,24 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
         st0 = least / SROWS;
         my_st0 = __builtin_amdgcn_readfirstlane((int)my_st0);
     }
-    for (int i = tid; i < QPB * lstride; i += KN_THREADS) {
+    // the list of query q0 + col: ranks half * LN + i
+    double list[LN];
+#pragma unroll
+    for (int i = 0; i < LN; ++i) {
         u64 k = 0ull;
         if (resume) {
-            const int e = BUF ? i / 32 % KN_CAP : i % lstride;
-            const int64_t qr = (int64_t)blockIdx.x * QPB + (BUF ? i / (32 * KN_CAP) * 32 + ((i ^ e) & 31) : i / lstride);
+            const int64_t qr = q0 + col;
+            const int e = half * LN + i;
             if (qr < M && e < knn) {
                 const float sc = scores[((size_t)blockIdx.y * M + qr) * knn + e];
                 if (sc > -INFINITY) k = knn_key(sc, L_out[((size_t)graph * M + qr) * knn + e]);
             }
         }
-        lists[i] = k;
+        list[i] = __builtin_bit_cast(double, k);
     }
-    u64* my_lists = lists + (size_t)wv * 32 * lstride;
-    // the key ids of the stage's rows, where the lanes that keep some of them read them (BUF)
+    uint32_t* run0 = reinterpret_cast<uint32_t*>(lds_raw + wv * KN_RUN_BYTES);
+    uint32_t* run = run0 + lane;
+    // the key ids of the stage's rows, where the lanes that keep some of them read them
     int* my_ids = reinterpret_cast<int*>(stage_buf + 2 * STAGE) + wv * SROWS;
 
     Operand<DT> b;                                 // (loads clamped: columns beyond M are never written)
@@ -388,9 +355,8 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     settle_operand<DT>(b);
     __syncthreads();
 
-    const u64 last_key = my_lists[BUF ? kn_slot(knn - 1, col) : col * lstride + knn - 1];          // (zero but for a resumed stream)
-    float tau = knn_threshold(last_key);
-    int fill = 0;                                  // BUF: keys in this lane's pending run
+    float tau = knn_threshold<LN>(list, knn, half, lane);      // (the lowest number but for a resumed stream)
+    int fill = 0;                                  // keys in this lane's pending run
 
     static_assert(CPT == 2 || CPT == 4, "two or four chunks per thread and stage");
     const int64_t nstage = (n_stream + SROWS - 1) / SROWS;
@@ -438,59 +404,36 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
             for (int r = 0; r < 16; ++r)
                 if (kbase + (r / 4) * 8 + half * 4 + (r % 4) >= n_stream) cs[r] = -INFINITY;
         }
-        if constexpr (BUF) {
-            float gm[4];
+        float gm[4];
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                gm[g] = fmaxf(fmaxf(cs[4 * g], cs[4 * g + 1]), fmaxf(cs[4 * g + 2], cs[4 * g + 3]));
-            const float mx = fmaxf(fmaxf(gm[0], gm[1]), fmaxf(gm[2], gm[3]));
-            if (__ballot(mx >= tau) == 0ull) return;
-            constexpr int PEND = KnSlots<WIDE>::pend;
-            uint32_t* run = reinterpret_cast<uint32_t*>(my_lists + KnSlots<WIDE>::list * 32) + lane;
+        for (int g = 0; g < 4; ++g)
+            gm[g] = fmaxf(fmaxf(cs[4 * g], cs[4 * g + 1]), fmaxf(cs[4 * g + 2], cs[4 * g + 3]));
+        const float mx = fmaxf(fmaxf(gm[0], gm[1]), fmaxf(gm[2], gm[3]));
+        if (__ballot(mx >= tau) == 0ull) return;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                if (__ballot(gm[g] >= tau) == 0ull) continue;
-                // a lane needs room for the keys of this group that reach its threshold (their number can
-                // only fall when a merge raises the threshold)
-                if (__ballot(fill > PEND - 4)) {
-                    int n = 0;
+        for (int g = 0; g < 4; ++g) {
+            if (__ballot(gm[g] >= tau) == 0ull) continue;
+            // a lane needs room for the keys of this group that reach its threshold (their number can
+            // only fall when a merge raises the threshold)
+            if (__ballot(fill > KN_PEND - 4)) {
+                int n = 0;
 #pragma unroll
-                    for (int r = 4 * g; r < 4 * g + 4; ++r) n += cs[r] >= tau ? 1 : 0;
-                    if (__ballot(fill + n > PEND)) {
-                        tau = knn_fold<WIDE>(my_lists, knn, col, half, fill);
-                        fill = 0;
-                    }
-                }
-                const int4 id4 = *reinterpret_cast<const int4*>(my_ids + first + 8 * g + 4 * half);
-                const int id[4] = {id4.x, id4.y, id4.z, id4.w};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int place = min(fill, PEND);        // (fill itself, for scores that are numbers)
-                    run[place * 128] = __float_as_uint(cs[4 * g + r]);
-                    run[place * 128 + 64] = (uint32_t)id[r];
-                    fill = place + (cs[4 * g + r] >= tau ? 1 : 0);
+                for (int r = 4 * g; r < 4 * g + 4; ++r) n += cs[r] >= tau ? 1 : 0;
+                if (__ballot(fill + n > KN_PEND)) {
+                    knn_fold<LN>(list, run, half, fill);
+                    tau = knn_threshold<LN>(list, knn, half, lane);
+                    fill = 0;
                 }
             }
-        } else {
-            float mx = fmaxf(cs[0], cs[1]);
+            const int4 id4 = *reinterpret_cast<const int4*>(my_ids + first + 8 * g + 4 * half);
+            const int id[4] = {id4.x, id4.y, id4.z, id4.w};
+            // a lane writes every score to the next free place, and only one that belongs there makes the place taken
 #pragma unroll
-            for (int r = 2; r < 16; ++r) mx = fmaxf(mx, cs[r]);
-            if (__ballot(mx >= tau) == 0ull) return;
-            // insertion path (rare after the first few blocks)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                u64 mask = __ballot(cs[r] >= tau && cs[r] > -INFINITY);
-                while (mask) {
-                    const int src = __ffsll((long long)mask) - 1;
-                    const float sc = __shfl(cs[r], src);
-                    const int id =
-                        __builtin_amdgcn_readlane(ids, first + (r / 4) * 8 + (src >> 5) * 4 + (r % 4));
-                    const int jq = src & 31;
-                    const float nt = knn_insert(my_lists + (size_t)jq * knn, knn, sc, id, lane);
-                    if (col == jq) tau = nt;
-                    mask &= mask - 1;
-                    mask &= __ballot(cs[r] >= tau && cs[r] > -INFINITY);
-                }
+            for (int r = 0; r < 4; ++r) {
+                const int place = min(fill, KN_PEND);         // (fill itself, for scores that are numbers)
+                run[place * 128] = __float_as_uint(cs[4 * g + r]);
+                run[place * 128 + 64] = (uint32_t)id[r];
+                fill = place + (cs[4 * g + r] >= tau ? 1 : 0);
             }
         }
     };
@@ -499,9 +442,7 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     operand_offsets<DT>((int)(stage_buf - lds_raw), col, half, a_at);
     auto multiply_stage = [&](int cur, int64_t st, int ids) __attribute__((always_inline)) {      // cur: byte offset of the stage buffer
         if (st < my_st0) return;                    // (keys that this wavefront's queries have seen)
-        if constexpr (BUF) {
-            if (SROWS == 64 || lane < SROWS) my_ids[lane] = ids;
-        }
+        if (SROWS == 64 || lane < SROWS) my_ids[lane] = ids;
         Operand<DT> a0;
         read_operand<DT>(lds_raw, a_at, cur, a0);
         if constexpr (SBLK == 2) {
@@ -562,16 +503,28 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
         fetch_stage(hb, rb);                            // stage st + 4
         load_rows(rb, st + 6);
     }
-    // write the ids, best first
-    if constexpr (BUF) (void)knn_fold<WIDE>(my_lists, knn, col, half, fill);
-    for (int jq = 0; jq < 32; ++jq) {
-        const int64_t qr = q0 + jq;
-        if (qr >= M) break;
-        if (lane < knn) {
-            const u64 k = my_lists[BUF ? kn_slot(lane, jq) : jq * lstride + lane];
-            L_out[((size_t)graph * M + qr) * knn + lane] = knn_key_id(k);
-            if (scores)                            // (the filter goes on with these)
-                scores[((size_t)blockIdx.y * M + qr) * knn + lane] = k == 0ull ? -INFINITY : knn_key_score(k);
+    // write ids and scores, best first, a query's list at a time, through the runs' place (word of rank e of query col at
+    // 32 e + (col ^ e % 32): a rank of the 32 queries, like 32 ranks of a query, is in different banks)
+    knn_fold<LN>(list, run, half, fill);
+    static_assert(2 * LN * 32 * 4 <= KN_RUN_BYTES, "the lists' words fit the runs' place");
+    for (int what = 0; what < (scores ? 2 : 1); ++what) {
+        kn_wave_sync();
+#pragma unroll
+        for (int i = 0; i < LN; ++i) {
+            const u64 k = __builtin_bit_cast(u64, list[i]);
+            const uint32_t word = what == 0 ? (uint32_t)knn_key_id(k)
+                                            : __float_as_uint(k == 0ull ? -INFINITY : knn_key_score(k));
+            run0[32 * (half * LN + i) + (col ^ (i & 31) ^ (LN == 16 ? 16 * half : 0))] = word;
+        }
+        kn_wave_sync();
+        for (int jq = 0; jq < 32; ++jq) {
+            const int64_t qr = q0 + jq;
+            if (qr >= M) break;
+            if (lane < knn) {
+                const uint32_t word = run0[32 * lane + (jq ^ (lane & 31))];
+                if (what == 0) L_out[((size_t)graph * M + qr) * knn + lane] = (int)word;
+                else scores[((size_t)blockIdx.y * M + qr) * knn + lane] = __uint_as_float(word);      // (the filter goes on with these)
+            }
         }
     }
 }
@@ -588,17 +541,13 @@ struct KnnCall {
     const int* resume;
     int resume_queries, resume_blocks;
 };
-template <int DT, int WAVES, int SEL, int STAGE>
+template <int DT, int WAVES, int LN, int STAGE>
 static ra_status knn_launch_as(const KnnCall& c) {
     constexpr int QPB = 32 * WAVES;
-    const int slots = SEL != KN_SEL_INSERT ? KN_CAP : c.knn;
-    const size_t lds = (size_t)QPB * slots * sizeof(u64) + 2 * STAGE +
-                       (SEL != KN_SEL_INSERT ? WAVES * (STAGE / (DT == RA_BF16 ? 256 : 512)) * sizeof(int) : 0);
-    if (lds > RA_LDS_LIMIT)
-        RA_FAIL(RA_EUNSUP, "knn %d needs %zu bytes of LDS (limit %d)", c.knn, lds, RA_LDS_LIMIT);
-    RA_LDS_OPT_IN((knn_kernel<DT, WAVES, SEL, STAGE>), lds);
+    const size_t lds = WAVES * KN_RUN_BYTES + 2 * STAGE + WAVES * (STAGE / (DT == RA_BF16 ? 256 : 512)) * sizeof(int);
+    RA_LDS_OPT_IN((knn_kernel<DT, WAVES, LN, STAGE>), lds);
     const dim3 grid((unsigned)((c.M + QPB - 1) / QPB), (unsigned)c.n_graphs);
-    hipLaunchKernelGGL((knn_kernel<DT, WAVES, SEL, STAGE>), grid, dim3(WAVES * RA_WAVE), lds, c.st, c.K, c.Q,
+    hipLaunchKernelGGL((knn_kernel<DT, WAVES, LN, STAGE>), grid, dim3(WAVES * RA_WAVE), lds, c.st, c.K, c.Q,
                        reinterpret_cast<const u64*>(c.order), ra_knn_order_stride(c.N), c.g0, c.n_q, c.n_kv, c.N,
                        c.n_stream, c.M, c.knn, c.L, c.scores, c.resume, c.resume_queries, c.resume_blocks);
     RA_HIP(hipGetLastError());
@@ -609,18 +558,11 @@ static ra_status knn_launch_as(const KnnCall& c) {
 static int g_knn_selection_override = RA_TEST_KNN_AUTO;
 void ra_knn_set_selection_override(int v) { g_knn_selection_override = v; }
 
-// bf16: 8 wavefronts per workgroup (one workgroup per compute unit, two wavefronts per SIMD), 256
-// queries x 64 list slots of 8 bytes beside the stage buffers for lists of up to 48 keys, knn slots for
-// longer ones. fp32 operands take twice the registers: 4 wavefronts.
+// bf16: 8 wavefronts per workgroup (two per SIMD: registers). fp32 operands take twice the registers: 4 wavefronts.
 static ra_status knn_launch(const KnnCall& c, ra_dtype dt) {
-    if (dt == RA_BF16) {
-        if (c.knn <= 32) return knn_launch_as<RA_BF16, 8, KN_SEL_LDS32, 16384>(c);
-        if (c.knn <= KN_BUFFERED_KNN) return knn_launch_as<RA_BF16, 8, KN_SEL_LDS48, 16384>(c);
-        return knn_launch_as<RA_BF16, 8, KN_SEL_INSERT, 16384>(c);
-    }
-    if (c.knn <= 32) return knn_launch_as<RA_F32, 4, KN_SEL_LDS32, 16384>(c);
-    if (c.knn <= KN_BUFFERED_KNN) return knn_launch_as<RA_F32, 4, KN_SEL_LDS48, 16384>(c);
-    return knn_launch_as<RA_F32, 4, KN_SEL_INSERT, 16384>(c);
+    if (dt == RA_BF16)
+        return c.knn <= 32 ? knn_launch_as<RA_BF16, 8, 16, 16384>(c) : knn_launch_as<RA_BF16, 8, 32, 16384>(c);
+    return c.knn <= 32 ? knn_launch_as<RA_F32, 4, 16, 16384>(c) : knn_launch_as<RA_F32, 4, 32, 16384>(c);
 }
 
 // Keys of the stream that are multiplied as they are before knn_filter.hip takes over (N: all of them): enough that

@@ -95,7 +95,28 @@ def test_knn_monotone_stream(dtype, knn, rising, knn_selection):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("knn", [1, 31, 32, 33, 47, 48])
+@pytest.mark.parametrize("knn", [32, 48, 64])
+def test_knn_scores_that_are_no_numbers(dtype, knn):
+    """Keys with a NaN or with scores of minus infinity are in no list; a list they leave short ends in -1."""
+    N, M = 200, 40
+    i = np.arange(N)
+    K = np.zeros((N, 128))
+    K[:, 0] = i % 7 + 1
+    K[i % 10 != 3, 5] = np.nan
+    K[i % 10 == 4, 5] = -np.inf
+    Q = np.zeros((M, 128))
+    Q[:, 0] = np.arange(M) % 5 + 1
+    Q[:, 5] = 1.0
+    got = ra.ra_knn(torch.from_numpy(K).to(dtype).to(DEV)[None, None],
+                    torch.from_numpy(Q).to(dtype).to(DEV)[None, None], knn).cpu().numpy()[0, 0]
+    numbers = i[i % 10 == 3]
+    want = numbers[np.lexsort((numbers, -K[numbers, 0]))]
+    assert np.array_equal(got[:, :20], np.broadcast_to(want, (M, 20)))
+    assert (got[:, 20:] == -1).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("knn", [1, 31, 32, 33, 48, 63, 64])
 @pytest.mark.parametrize("half", [0, 1])
 def test_knn_runs_of_one_lane(dtype, knn, half):
     """The keys that reach a threshold are all in the rows that one of a query's two lanes scores (four rows in eight; the
