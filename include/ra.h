@@ -99,6 +99,16 @@ ra_status ra_build_index(const void* K, const void* Q_prefill, ra_dtype dt,
                          int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
                          int deg, int knn, void* stream, ra_index** out);
 
+/* The same with scratch memory of the caller's (device, 256-byte aligned, his again when the call returns): what
+ * ra_build_workspace_bytes says, which is 0 for sizes that a build refuses. With workspace NULL the call
+ * allocates and frees it itself (freeing a piece of 150 MB or more is a quarter of a millisecond); with less
+ * than the 8-bit copies of ra_knn need, but enough for the rest, the index comes without them. */
+size_t ra_build_workspace_bytes(ra_dtype dt, int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
+                                int deg, int knn);
+ra_status ra_build_index_ws(const void* K, const void* Q_prefill, ra_dtype dt,
+                            int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
+                            int deg, int knn, void* workspace, size_t workspace_bytes, void* stream, ra_index** out);
+
 /* ---- decode step (Algorithm 1 with the fixed static pattern of Sec. 3.3) ----------- */
 
 /* VectorSearch(q): bounded best-first walk over each head's graph from its entry point.

@@ -119,12 +119,18 @@ static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra
     ix->n_seq = n_seq; ix->n_q = n_q; ix->n_kv = n_kv; ix->N = N; ix->deg = deg;
     const size_t graphs = (size_t)n_seq * n_q;
     ix->graph_bytes = graphs * N * deg * sizeof(int32_t);
-    hipError_t e = hipGetDevice(&ix->device);
-    if (e == hipSuccess) e = hipMalloc((void**)&ix->adj, ix->graph_bytes);
-    if (e == hipSuccess) e = hipMalloc((void**)&ix->entry, graphs * sizeof(int32_t));
     ix->root_cap = 3 + deg + deg * deg;
-    if (e == hipSuccess) e = hipMalloc((void**)&ix->roots, graphs * ix->root_cap * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&ix->coop, coop_bytes(ix));
+    // one allocation: the graphs, then entry points, root sets and the hand-over area
+    auto aligned = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
+    const size_t entry_at = aligned(ix->graph_bytes), roots_at = entry_at + aligned(graphs * sizeof(int32_t));
+    const size_t coop_at = roots_at + aligned(graphs * ix->root_cap * sizeof(int32_t));
+    char* base = nullptr;
+    hipError_t e = hipGetDevice(&ix->device);
+    if (e == hipSuccess) e = hipMalloc((void**)&base, coop_at + coop_bytes(ix));
+    ix->adj = reinterpret_cast<int32_t*>(base);
+    ix->entry = reinterpret_cast<int32_t*>(base + entry_at);
+    ix->roots = reinterpret_cast<int32_t*>(base + roots_at);
+    ix->coop = reinterpret_cast<unsigned long long*>(base + coop_at);
     if (e == hipSuccess) e = hipMemset(ix->coop, 0, coop_bytes(ix));
     ix->coop_mode = RA_HELPERS_ON;
     ix->coop_spin = RA_HELPER_SPIN_DEFAULT;
@@ -132,10 +138,7 @@ static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra
     if (e != hipSuccess) {
         ra_set_error("allocating the graph (%zu B) failed: %s", ix->graph_bytes, hipGetErrorString(e));
         (void)hipGetLastError();
-        if (ix->adj) (void)hipFree(ix->adj);
-        if (ix->entry) (void)hipFree(ix->entry);
-        if (ix->coop) (void)hipFree(ix->coop);
-        if (ix->roots) (void)hipFree(ix->roots);
+        if (base) (void)hipFree(base);
         delete ix;
         return e == hipErrorOutOfMemory ? RA_ENOMEM : RA_EHIP;
     }
@@ -145,13 +148,10 @@ static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra
 
 extern "C" void ra_index_free(ra_index* ix) {
     if (!ix) return;
-    if (ix->adj) (void)hipFree(ix->adj);
-    if (ix->entry) (void)hipFree(ix->entry);
+    if (ix->adj) (void)hipFree(ix->adj);                 // (and what lies behind the graphs)
     if (ix->partials) (void)hipFree(ix->partials);
     if (ix->ids_ws) (void)hipFree(ix->ids_ws);
     if (ix->bitset) (void)hipFree(ix->bitset);
-    if (ix->coop) (void)hipFree(ix->coop);
-    if (ix->roots) (void)hipFree(ix->roots);
     if (ix->seeds) (void)hipFree(ix->seeds);
     if (ix->seedx) (void)hipFree(ix->seedx);
     delete ix;
@@ -380,32 +380,52 @@ extern "C" ra_status ra_project(const int32_t* L, int n_graphs, int64_t N, int64
     return RA_OK;
 }
 
-extern "C" ra_status ra_build_index(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q,
-                                    int n_kv, int64_t N, int64_t M, int d, int deg, int knn,
-                                    void* stream, ra_index** out) {
+// One piece of scratch memory: the lists, then the workspace of the two stages, which do not use it at
+// the same time. `plain`: without 8-bit copies of the keys.
+static size_t build_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn, bool plain, size_t* lists) {
+    const int graphs = n_seq * n_q;
+    *lists = ((size_t)graphs * M * knn * sizeof(int32_t) + 255) & ~(size_t)255;
+    const size_t knn_bytes = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, plain);
+    const size_t proj_bytes = ra_project_workspace_bytes(graphs, N, M, knn);
+    return *lists + (knn_bytes > proj_bytes ? knn_bytes : proj_bytes);
+}
+
+extern "C" size_t ra_build_workspace_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int d, int deg,
+                                           int knn) {
+    if (check_dtype(dt) != RA_OK || check_heads(n_seq, n_q, n_kv) != RA_OK || check_dim(d) != RA_OK ||
+        check_build_args(N, M, deg, knn, true) != RA_OK)
+        return 0;
+    size_t lists;
+    return build_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false, &lists);
+}
+
+extern "C" ra_status ra_build_index_ws(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q,
+                                       int n_kv, int64_t N, int64_t M, int d, int deg, int knn,
+                                       void* workspace, size_t workspace_bytes, void* stream, ra_index** out) {
     if (!K || !Q || !out) RA_FAIL(RA_EINVAL, "NULL argument");
     RA_TRY(check_dtype(dt));
     RA_TRY(check_heads(n_seq, n_q, n_kv));
     RA_TRY(check_dim(d));
     RA_TRY(check_build_args(N, M, deg, knn, true));
     const int graphs = n_seq * n_q;
+    size_t l_bytes = 0, got = 0;
+    const size_t least = build_bytes(dt, n_seq, n_q, n_kv, N, M, knn, true, &l_bytes);
+    const size_t most = build_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false, &l_bytes);
+    if (workspace && workspace_bytes < least)
+        RA_FAIL(RA_ESHAPE, "workspace of %zu bytes, the build needs %zu", workspace_bytes, least);
     ra_index* ix = nullptr;
     RA_TRY(new_handle(n_seq, n_q, n_kv, N, deg, &ix));
-    // One piece of scratch memory: the lists, then the workspace of the two stages, which do not use it at
-    // the same time (an allocation or a free of a large piece is a quarter of a millisecond).
-    const size_t l_bytes = ((size_t)graphs * M * knn * sizeof(int32_t) + 255) & ~(size_t)255;
-    const size_t knn_bytes = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false);
-    const size_t knn_plain = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, true);
-    const size_t proj_bytes = ra_project_workspace_bytes(graphs, N, M, knn);
-    int32_t* L = nullptr;
-    size_t got = 0;
-    hipError_t e = build_scratch((void**)&L, l_bytes + (knn_bytes > proj_bytes ? knn_bytes : proj_bytes),
-                                 l_bytes + (knn_plain > proj_bytes ? knn_plain : proj_bytes), &got);
-    if (e != hipSuccess) {
-        ra_set_error("allocating the KNN lists failed: %s", hipGetErrorString(e));
-        (void)hipGetLastError();
-        ra_index_free(ix);
-        return e == hipErrorOutOfMemory ? RA_ENOMEM : RA_EHIP;
+    int32_t* L = reinterpret_cast<int32_t*>(workspace);
+    if (workspace) {
+        got = workspace_bytes < most ? workspace_bytes : most;
+    } else {
+        hipError_t e = build_scratch((void**)&L, most, least, &got);
+        if (e != hipSuccess) {
+            ra_set_error("allocating the KNN lists failed: %s", hipGetErrorString(e));
+            (void)hipGetLastError();
+            ra_index_free(ix);
+            return e == hipErrorOutOfMemory ? RA_ENOMEM : RA_EHIP;
+        }
     }
     void* ws = reinterpret_cast<char*>(L) + l_bytes;
     ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, got - l_bytes, (hipStream_t)stream, L);
@@ -413,17 +433,26 @@ extern "C" ra_status ra_build_index(const void* K, const void* Q, ra_dtype dt, i
         rc = ra_launch_project(L, graphs, N, M, knn, deg, ws, (hipStream_t)stream, ix->adj, ix->entry);
     if (rc == RA_OK)
         rc = ra_launch_roots(ix->adj, ix->entry, graphs, N, deg, ix->roots, ix->root_cap, (hipStream_t)stream);
-    if (rc == RA_OK && hipStreamSynchronize((hipStream_t)stream) != hipSuccess) {
-        ra_set_error("index build failed on the device: %s", hipGetErrorString(hipGetLastError()));
+    // (also after a stage that could not be launched: what was launched before it uses the memory)
+    const hipError_t es = hipStreamSynchronize((hipStream_t)stream);
+    if (rc == RA_OK && es != hipSuccess) {
+        ra_set_error("index build failed on the device: %s", hipGetErrorString(es));
+        (void)hipGetLastError();
         rc = RA_EHIP;
     }
-    (void)hipFree(L);
+    if (!workspace) (void)hipFree(L);
     if (rc != RA_OK) {
         ra_index_free(ix);
         return rc;
     }
     *out = ix;
     return RA_OK;
+}
+
+extern "C" ra_status ra_build_index(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q,
+                                    int n_kv, int64_t N, int64_t M, int d, int deg, int knn,
+                                    void* stream, ra_index** out) {
+    return ra_build_index_ws(K, Q, dt, n_seq, n_q, n_kv, N, M, d, deg, knn, nullptr, 0, stream, out);
 }
 
 // ---- decode step -----------------------------------------------------------------------

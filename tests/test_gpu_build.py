@@ -288,6 +288,37 @@ def test_build_index_then_decode(name):
     idx.free()
 
 
+@pytest.mark.parametrize("room", ["own", "full", "tight", "short"])
+def test_build_in_the_callers_workspace(room):
+    """A build in memory of the caller's gives the graphs of one in the library's own, with the 8-bit copies and
+    without room for them, and refuses less than that; the memory behind the workspace stays as it was."""
+    import ctypes as C
+    from paper_2409_10516_amd import binding as B
+    lib = ra.lib()
+    w = synth.make_llama_layer(9, 8192, 700, n_seq=1, n_q=4, n_kv=2, device=DEV, dtype=torch.float32)
+    knn, deg = 16, 16
+    sizes = (1, 4, 2, 8192, 700, 128, deg, knn)
+    need = lib.ra_build_workspace_bytes(B.RA_F32, *sizes)
+    assert need > 0 and lib.ra_build_workspace_bytes(B.RA_F32, *sizes[:-1], 0) == 0
+    copies = 4 * 8192 * 128                              # 8-bit copies of the keys: a row of 128 bytes each and head
+    have = {"own": 0, "full": need, "tight": need - copies // 2, "short": 1 << 16}[room]
+    piece = torch.full((have + 4096,), 77, dtype=torch.uint8, device=DEV)
+    ix = C.c_void_p()
+    rc = lib.ra_build_index_ws(w.K.data_ptr(), w.Q_prefill.data_ptr(), B.RA_F32, *sizes, piece.data_ptr() if have else None,
+                               have, torch.cuda.current_stream().cuda_stream, C.byref(ix))
+    if room == "short":
+        assert rc == 2 and not ix.value
+        return
+    assert rc == 0
+    assert bool((piece[have:] == 77).all())
+    got, want = B.Index(ix.value), ra.ra_build_index(w.K, w.Q_prefill, deg, knn)
+    for h in range(4):
+        (a, ea), (b, eb) = ra.ra_index_export(got, 0, h), ra.ra_index_export(want, 0, h)
+        assert ea == eb and torch.equal(a, b)
+    got.free()
+    want.free()
+
+
 def test_build_argument_errors():
     w = synth.make_integer_case(1, N=64, M=16, d=128)
     Kd, Qd = w.K.to(DEV), w.Q_prefill.to(DEV)
