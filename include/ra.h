@@ -99,10 +99,14 @@ ra_status ra_build_index(const void* K, const void* Q_prefill, ra_dtype dt,
                          int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
                          int deg, int knn, void* stream, ra_index** out);
 
-/* The same with scratch memory of the caller's (device, 256-byte aligned, his again when the call returns): what
- * ra_build_workspace_bytes says, which is 0 for sizes that a build refuses. With workspace NULL the call
- * allocates and frees it itself (freeing a piece of 150 MB or more is a quarter of a millisecond); with less
- * than the 8-bit copies of ra_knn need, but enough for the rest, the index comes without them. */
+/* The same, and ra_project, with scratch memory of the caller's (device, 256-byte aligned, theirs again when the call
+ * returns): what ra_build_workspace_bytes and ra_project_scratch_bytes say, which is 0 for sizes that are refused. With
+ * workspace NULL the call allocates and frees it itself (freeing a piece of 150 MB or more is a quarter of a
+ * millisecond); with too little it is refused, but a build that lacks no more than the 8-bit copies of ra_knn
+ * goes on without them. */
+size_t ra_project_scratch_bytes(int n_graphs, int64_t N, int64_t M, int deg, int knn);
+ra_status ra_project_ws(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg, void* workspace,
+                        size_t workspace_bytes, void* stream, int32_t* adj, int32_t* entry);
 size_t ra_build_workspace_bytes(ra_dtype dt, int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
                                 int deg, int knn);
 ra_status ra_build_index_ws(const void* K, const void* Q_prefill, ra_dtype dt,

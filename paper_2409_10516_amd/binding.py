@@ -53,6 +53,10 @@ def lib() -> C.CDLL:
     L.ra_project.argtypes = [vp, i32, i64, i64, i32, i32, vp, vp, vp]
     L.ra_build_index.argtypes = [vp, vp, i32, i32, i32, i32, i64, i64, i32, i32, i32, vp,
                                  C.POINTER(vp)]
+    L.ra_project_ws.argtypes = [vp, i32, i64, i64, i32, i32, vp, C.c_size_t, vp, vp, vp]
+    L.ra_project_ws.restype = i32
+    L.ra_project_scratch_bytes.argtypes = [i32, i64, i64, i32, i32]
+    L.ra_project_scratch_bytes.restype = C.c_size_t
     L.ra_build_index_ws.argtypes = [vp, vp, i32, i32, i32, i32, i64, i64, i32, i32, i32, vp, C.c_size_t, vp,
                                     C.POINTER(vp)]
     L.ra_build_index_ws.restype = i32
@@ -208,6 +212,26 @@ def ra_knn(K, Q_prefill, knn: int, stream=None) -> torch.Tensor:
     return L
 
 
+def _with_scratch(stream, need: int, call) -> None:
+    """call(workspace, its bytes, stream) -> status, for a call that returns when the stream is done. Up to
+    BUILD_POOLED_BYTES of scratch memory, for a call on the current stream, come from torch's allocator, which has the
+    piece of the last call at hand: the library's own allocation and free are 0.3 of the 1.6 ms that a build for two
+    prompts of 5K tokens took with them. Larger calls don't notice, and leave no large piece with torch; where
+    torch finds no room, the library allocates as for those."""
+    ws = None
+    if stream is None and 0 < need <= BUILD_POOLED_BYTES:
+        try:
+            ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+        except torch.cuda.OutOfMemoryError:
+            pass
+    rc = call(None, 0, _stream(stream)) if ws is None else call(_ptr(ws), need, _stream(None))
+    if STATUS.get(rc) == "RA_ENOMEM":      # pieces that torch keeps, such as an earlier call's, may be what is missing
+        del ws
+        torch.cuda.empty_cache()
+        rc = call(None, 0, _stream(stream))
+    _check(rc)
+
+
 def ra_project(L: torch.Tensor, N: int, deg: int, stream=None):
     """L: int32 [n_graphs][M][knn] on the GPU -> (adj [n_graphs][N][deg], entry [n_graphs])."""
     _dev(L)
@@ -216,8 +240,8 @@ def ra_project(L: torch.Tensor, N: int, deg: int, stream=None):
     n_graphs, M, knn = L.shape
     adj = torch.empty((n_graphs, N, deg), dtype=torch.int32, device=L.device)
     entry = torch.empty((n_graphs,), dtype=torch.int32, device=L.device)
-    _check(lib().ra_project(_ptr(L), n_graphs, N, M, knn, deg, _stream(stream), _ptr(adj),
-                            _ptr(entry)))
+    _with_scratch(stream, lib().ra_project_scratch_bytes(n_graphs, N, M, deg, knn),
+                  lambda ws, room, st: lib().ra_project_ws(_ptr(L), n_graphs, N, M, knn, deg, ws, room, st, _ptr(adj), _ptr(entry)))
     return adj, entry
 
 
@@ -229,26 +253,8 @@ def ra_build_index(K, Q_prefill, deg: int, knn: int, stream=None) -> Index:
     _, n_q, M, _ = Q_prefill.shape
     h = C.c_void_p()
     args = (_ptr(K), _ptr(Q_prefill), _dt(K), n_seq, n_q, n_kv, N, M, d, deg, knn)
-    # The scratch memory of a small build on the current stream comes from torch's allocator, which has the piece of
-    # the last build at hand: the library's own allocation and free are 0.3 of 1.6 ms for two prompts of 5K tokens.
-    # (The call returns when the stream is done, so the piece may go back at once.) Large builds don't notice, and
-    # leave no large piece with torch; where torch finds no room, the library allocates as for those.
-    need = lib().ra_build_workspace_bytes(*args[2:])
-    ws = None
-    if stream is None and 0 < need <= BUILD_POOLED_BYTES:
-        try:
-            ws = torch.empty(need, dtype=torch.uint8, device="cuda")
-        except torch.cuda.OutOfMemoryError:
-            pass
-    if ws is not None:
-        rc = lib().ra_build_index_ws(*args, _ptr(ws), need, _stream(None), C.byref(h))
-    else:
-        rc = lib().ra_build_index(*args, _stream(stream), C.byref(h))
-    if STATUS.get(rc) == "RA_ENOMEM":      # pieces that torch keeps, such as an earlier build's, may be what is missing
-        del ws
-        torch.cuda.empty_cache()
-        rc = lib().ra_build_index(*args, _stream(stream), C.byref(h))
-    _check(rc)
+    _with_scratch(stream, lib().ra_build_workspace_bytes(*args[2:]),
+                  lambda ws, room, st: lib().ra_build_index_ws(*args, ws, room, st, C.byref(h)))
     return Index(h.value)
 
 

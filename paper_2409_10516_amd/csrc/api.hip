@@ -364,20 +364,32 @@ extern "C" ra_status ra_knn(const void* K, const void* Q, ra_dtype dt, int n_seq
     return RA_OK;
 }
 
-extern "C" ra_status ra_project(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn,
-                                int deg, void* stream, int32_t* adj, int32_t* entry) {
+extern "C" size_t ra_project_scratch_bytes(int n_graphs, int64_t N, int64_t M, int deg, int knn) {
+    if (n_graphs < 1 || check_build_args(N, M, deg, knn, true) != RA_OK) return 0;
+    return ra_project_workspace_bytes(n_graphs, N, M, knn);
+}
+
+extern "C" ra_status ra_project_ws(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg, void* workspace,
+                                   size_t workspace_bytes, void* stream, int32_t* adj, int32_t* entry) {
     if (!L || !adj || !entry) RA_FAIL(RA_EINVAL, "NULL argument");
     if (n_graphs < 1) RA_FAIL(RA_EINVAL, "n_graphs must be positive");
     RA_TRY(check_build_args(N, M, deg, knn, true));
     const size_t ws_bytes = ra_project_workspace_bytes(n_graphs, N, M, knn);
-    void* ws = nullptr;
-    RA_HIP(hipMalloc(&ws, ws_bytes));
+    if (workspace && workspace_bytes < ws_bytes)
+        RA_FAIL(RA_ESHAPE, "workspace of %zu bytes, the projection needs %zu", workspace_bytes, ws_bytes);
+    void* ws = workspace;
+    if (!ws) RA_HIP(hipMalloc(&ws, ws_bytes));
     ra_status rc = ra_launch_project(L, n_graphs, N, M, knn, deg, ws, (hipStream_t)stream, adj, entry);
     hipError_t e = hipStreamSynchronize((hipStream_t)stream);
-    (void)hipFree(ws);
+    if (!workspace) (void)hipFree(ws);
     if (rc != RA_OK) return rc;
     RA_HIP(e);
     return RA_OK;
+}
+
+extern "C" ra_status ra_project(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn,
+                                int deg, void* stream, int32_t* adj, int32_t* entry) {
+    return ra_project_ws(L, n_graphs, N, M, knn, deg, nullptr, 0, stream, adj, entry);
 }
 
 // One piece of scratch memory: the lists, then the workspace of the two stages, which do not use it at

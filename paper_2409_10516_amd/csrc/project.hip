@@ -19,21 +19,27 @@
 //      a list follow in id order.
 //   3. inverted lists (key -> the lists that hold it) filled through per-key cursors (ranges
 //      reserved per workgroup through the same kind of LDS table), and a copy of the lists with
-//      every key replaced by its position in pi.
+//      every key replaced by its position in pi, in 16 bits in graphs of at most 8192 populated keys. In such a graph up to
+//      128 hubs (keys in more than a 64th of the lists) have a bitmap over the lists instead, and how many lists hold
+//      two of them both is counted by and + popcount.
 //   4. backbone children and -1 padding for every row.
 //   5. rows of the populated keys. For key a: stream the lists that hold a (whole rows of the
 //      translated lists, coalesced), count each co-listed key, and select the best 64. Positions
 //      stand for ids throughout: among keys of equal overlap and count (which are equally popular)
-//      the lower position is the lower id. By the number of list cells (lists x knn):
-//        - few (up to 2048): one key per wavefront, counts in an LDS hash table sized by
+//      the lower position is the lower id. By the numbers of populated keys and of the key's list cells (lists x knn):
+//        - keys of up to 256 lists in a graph of at most 1024 populated keys, and of those the ones with more than 2048 cells
+//          in one of at most 4096: one key per wavefront, counts in LDS by position (pj_rows_wave_kernel);
+//        - few cells (up to 2048): one key per wavefront, counts in an LDS hash table sized by
 //          the key's class, no workgroup barrier (pj_rows_small_kernel);
-//        - the rest, in a graph of at most 8192 populated keys (the common case: the queries share
-//          their favourite keys): one key per workgroup, counts in an LDS table indexed by
-//          position (pj_rows_kernel); hubs run their thousands of lists through a three-deep load pipeline;
+//        - the rest, in a graph of at most 8192 populated keys: one key per workgroup, counts in an LDS table indexed by
+//          position (pj_rows_kernel);
 //        - the rest in a larger graph: one key per workgroup, counts in an LDS hash table, in a few
 //          passes over the lists where they hold more keys than the table (pj_rows_hash_kernel), and
 //          for the keys with most lists in counters in device memory, the low positions still in LDS
-//          (pj_rows_hub_kernel).
+//          (pj_rows_hub_kernel);
+//        - hubs: from the pairs' counts and from what the other keys counted (c(a, b) = c(b, a)), last (pj_rows_hubs_kernel).
+//      A hub's own walk would be most of the work: of the 4.2 M cells of a Llama-shaped graph of 128K lists nine in ten are 128
+//      keys' (32 such graphs, whole projection: 5.3 -> 2.5 ms; 64 of 5003 lists: 0.54 -> 0.30).
 // No global sort of the M*knn*(knn-1) co-occurrence pairs is needed.
 #include <type_traits>
 
@@ -43,6 +49,25 @@
 #define PJ_LDS_TAB 8192           // words of the workgroup row kernel's table
 #define PJ_BLOCK 2048             // keys a workgroup of the compaction kernels owns
 #define PJ_CELL_T 256
+#define PJ_TOUCH_A 256            // list cells of a key in each class of the wavefront kernel
+#define PJ_TOUCH_B 1024
+#define PJ_TOUCH_C 2048
+#define PJ_HUBS 128               // most keys of a graph whose lists are kept as a bitmap
+#define PJ_SLAB_WORDS 64          // 32-list words of the bitmaps that a workgroup of the pair kernel takes, at least
+#define PJ_MOST_SLABS 16
+#define PJ_PAIR_T 192             // threads of the pair kernel
+#define PJ_HASH_T 512             // threads of the hash kernel
+#define PJ_HASH_TAB 16384         // words of its table
+#define PJ_HASH_FILL 10240        // list cells one of its passes puts in there
+#define PJ_HASH_PASSES 4          // most passes; a key with more cells than they take is the hub kernel's
+#define PJ_WAVE_TAB 4096          // words of a wavefront's table in pj_rows_wave_kernel, and the smaller size of it
+#define PJ_WAVE_SMALL_TAB 1024
+#define PJ_WAVE_LISTS 256         // most lists of a key there: it walks 64 at a time (with 2048: 32 graphs of 4283 lists of 48 1.25 ms instead of
+                                  // 1.12, of 128K lists of 32 2.29 instead of 2.24)
+
+// first positions that pj_pi_kernel leaves: a key's lists x knn at most PJ_TOUCH_A, _B, _C, its lists at most what the hash
+// kernel takes, at most PJ_WAVE_LISTS
+enum { PJ_CLASS_A, PJ_CLASS_B, PJ_CLASS_C, PJ_CLASS_HASH, PJ_CLASS_WAVE, PJ_CLASSES };
 
 typedef unsigned long long u64;
 
@@ -53,22 +78,28 @@ struct ProjWs {                   // per-graph device arrays, carved from one wo
     int32_t* pos;                 // [N]   position of key in pi
     int32_t* pi;                  // [N]
     int32_t* inv;                 // [M*knn]
-    int32_t* lp;                  // [M*knn] the lists with every key replaced by its position in pi (-1: none)
+    int32_t* lp;                  // [M*knn] the lists with every key replaced by its position in pi (-1: none);
+                                  // [M][row16(knn)] of 16 bits (0xffff: none) in graphs of at most PJ_LDS_TAB populated keys
+    uint32_t* bits;               // [words][PJ_HUBS] which of 32 lists hold a hub
+    uint32_t* pairs;              // [slabs][PJ_HUBS][PJ_HUBS] lists that hold two hubs
+    uint32_t* with_hubs;          // [position - hubs][PJ_HUBS] counts of the other keys with the hubs
     u64* keys;                    // [cap padded to a power of two] sort keys of the populated keys
     int32_t* ppop;                // [cap] popularity by position
     int32_t* blk;                 // [blocks] populated keys per block, then [blocks] list cells per block
-    int32_t* H;                   // [0] number of populated keys, [1] number of keys in over
+    int32_t* H;                   // [0] number of populated keys, [1] number of keys in over, [2] number of hubs,
+                                  // [3 + class] first position of keys with few enough lists (PJ_CLASS_*)
     int32_t* over;                // [cap] positions whose lists overflowed a hash table
 };
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct ProjLayout {
-    size_t per_graph, o_pop, o_cur, o_off, o_pos, o_pi, o_inv, o_lp, o_keys, o_ppop, o_blk, o_H, o_over;
+    size_t per_graph, o_pop, o_cur, o_off, o_pos, o_pi, o_inv, o_lp, o_bits, o_pairs, o_with_hubs, o_keys, o_ppop, o_blk, o_H, o_over;
     size_t scratch_per_wg, o_scratch;
-    int n_hub_wg, n_blk;
-    int64_t cap, cap_pad;
+    int n_hub_wg, n_blk, n_slabs;     // n_slabs 0: no hubs
+    int64_t cap, cap_pad, words, with_hubs;       // with_hubs: rows of that array
 };
+__host__ __device__ constexpr int row16(int knn) { return (knn + 7) & ~7; }      // (16-byte reads)
 
 static ProjLayout proj_layout(int n_graphs, int64_t N, int64_t M, int knn) {
     ProjLayout l;
@@ -83,8 +114,29 @@ static ProjLayout proj_layout(int n_graphs, int64_t N, int64_t M, int knn) {
     l.o_pos = o; o += align256((size_t)N * 4);
     l.o_pi = o; o += align256((size_t)N * 4);
     l.o_inv = o; o += align256((size_t)cells * 4);
-    l.o_lp = o; o += align256((size_t)cells * 4);
+    const size_t narrow = (size_t)M * row16(knn) * 2;
+    l.o_lp = o; o += align256(l.cap > PJ_LDS_TAB && (size_t)cells * 4 > narrow ? (size_t)cells * 4 : narrow);
+    l.words = (M + 31) / 32;
+    l.n_slabs = cells < 32768 ? 0 : (int)(l.words / PJ_SLAB_WORDS < 1 ? 1 : l.words / PJ_SLAB_WORDS > PJ_MOST_SLABS ? PJ_MOST_SLABS : l.words / PJ_SLAB_WORDS);
+    l.with_hubs = !l.n_slabs ? 0 : cells < 1 << 20 ? cells / 256 : PJ_LDS_TAB;
+    if (l.with_hubs > l.cap) l.with_hubs = l.cap;
     l.o_keys = o; o += align256((size_t)l.cap_pad * 8);
+    // What the hubs take is no more than the inverted lists (half of them for the counts, 16 bytes a list, a slab of pairs per
+    // 2048 lists), and lies where there is room in what is not read any more by then: the bitmaps on pop, the pairs on cur
+    // and the counts on keys (freeing a larger workspace costs up to 8 us a megabyte).
+    auto hubs_on = [&](size_t at, size_t room, size_t bytes) {
+        if (bytes <= room) return at;
+        at = o;
+        o += align256(bytes);
+        return at;
+    };
+    if (l.n_slabs) {
+        l.o_bits = hubs_on(l.o_pop, (size_t)N * 4, (size_t)l.words * PJ_HUBS * 4);
+        l.o_pairs = hubs_on(l.o_cur, (size_t)N * 4, (size_t)l.n_slabs * PJ_HUBS * PJ_HUBS * 4);
+        l.o_with_hubs = hubs_on(l.o_keys, (size_t)l.cap_pad * 8, (size_t)l.with_hubs * PJ_HUBS * 4);
+    } else {
+        l.o_bits = l.o_pairs = l.o_with_hubs = o;
+    }
     l.o_ppop = o; o += align256((size_t)l.cap * 4);
     l.o_blk = o; o += align256((size_t)l.n_blk * 8);
     l.o_H = o; o += 256;
@@ -112,10 +164,17 @@ __device__ __forceinline__ ProjWs carve(char* ws, const ProjLayout& l, int g) {
     w.pop = (int32_t*)(b + l.o_pop); w.cur = (int32_t*)(b + l.o_cur); w.off = (int32_t*)(b + l.o_off);
     w.pos = (int32_t*)(b + l.o_pos); w.pi = (int32_t*)(b + l.o_pi);
     w.inv = (int32_t*)(b + l.o_inv); w.lp = (int32_t*)(b + l.o_lp);
+    w.bits = (uint32_t*)(b + l.o_bits); w.pairs = (uint32_t*)(b + l.o_pairs);
+    w.with_hubs = (uint32_t*)(b + l.o_with_hubs);
     w.keys = (u64*)(b + l.o_keys); w.ppop = (int32_t*)(b + l.o_ppop);
     w.blk = (int32_t*)(b + l.o_blk); w.H = (int32_t*)(b + l.o_H);
     w.over = (int32_t*)(b + l.o_over);
     return w;
+}
+
+__device__ __forceinline__ void pj_wave_sync() {         // LDS written by one lane, read by another
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // ---- 0. clear --------------------------------------------------------------------------
@@ -143,7 +202,7 @@ __global__ void pj_zero_kernel(char* ws, ProjLayout l, int64_t N) {
 __device__ __forceinline__ int hot_tag(int* s_tag, int x) {
     return __hip_atomic_load(&s_tag[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-// the slot of key k, -1: none; `first` is what its first slot held (read ahead for several keys at once)
+// the slot of key k, claimed if it has none, -1: none; `first` is what its first slot held (read ahead for several keys at once)
 __device__ __forceinline__ int hot_slot(int* s_tag, int k, int first) {
     const int x0 = k & (PJ_HOT - 1);
     if (first == k) return x0;
@@ -157,6 +216,32 @@ __device__ __forceinline__ int hot_slot(int* s_tag, int k, int first) {
         if (owner == k) return x;
     }
     return -1;
+}
+// The slots of a thread's keys (k < 0: no key), -1: none. The looks are batched over the keys, without a branch per key:
+// each is a trip to LDS.
+template <int FLY>
+__device__ __forceinline__ void hot_find(int* s_tag, const int32_t (&k)[FLY], int (&x)[FLY]) {
+    int tag[FLY];
+#pragma unroll
+    for (int u = 0; u < FLY; ++u) tag[u] = hot_tag(s_tag, k[u] & (PJ_HOT - 1));
+    bool lost = false;
+#pragma unroll
+    for (int u = 0; u < FLY; ++u) {
+        x[u] = k[u] >= 0 && tag[u] == k[u] ? k[u] & (PJ_HOT - 1) : -1;
+        lost |= k[u] >= 0 && x[u] < 0;
+    }
+#pragma unroll
+    for (int v = 1; v < PJ_PROBE; ++v) {
+        if (__ballot(lost) == 0ull) return;
+#pragma unroll
+        for (int u = 0; u < FLY; ++u) tag[u] = hot_tag(s_tag, (k[u] + v) & (PJ_HOT - 1));
+        lost = false;
+#pragma unroll
+        for (int u = 0; u < FLY; ++u) {
+            if (k[u] >= 0 && x[u] < 0 && tag[u] == k[u]) x[u] = (k[u] + v) & (PJ_HOT - 1);
+            lost |= k[u] >= 0 && x[u] < 0;
+        }
+    }
 }
 __global__ __launch_bounds__(PJ_CELL_T) void pj_pop_kernel(const int32_t* __restrict__ L, char* ws,
                                                            ProjLayout l, int64_t cells, int64_t N) {
@@ -274,20 +359,57 @@ __global__ __launch_bounds__(256) void pj_compact_kernel(char* ws, ProjLayout l,
             w.pi[t] = (int)i;
         }
     }
-    if (blockIdx.x == 0 && tid == 0) { w.H[0] = H; w.H[1] = 0; }
+    if (blockIdx.x == 0 && tid == 0) {
+        w.H[0] = H;
+        for (int i = 1; i < 3 + PJ_CLASSES; ++i) w.H[i] = 0;
+    }
 }
 
-// pi, pos and popularity by position of the populated keys; the entry point
-__global__ __launch_bounds__(256) void pj_pi_kernel(char* ws, ProjLayout l, int64_t M,
+// most lists of a key whose list cells (lists x knn) number at most `touch` (a count must fit the 7
+// bits of a small table's entry)
+__device__ __forceinline__ int small_limit(int touch, int knn) {
+    const int lim = touch / knn;
+    return lim < 127 ? lim : 127;
+}
+
+// bits of a count, and whether position and count share a word
+__device__ __forceinline__ bool hash_fits(int pa, int H, int* cb) {
+    int b = 1;
+    while ((pa >> b) != 0) ++b;
+    *cb = b;
+    return ((u64)(H + 1) << b) <= 0xffffffffull;
+}
+// most lists of a key the hash kernel takes (both conditions can only get easier with fewer lists)
+__device__ __forceinline__ int hash_limit(int H, int knn) {
+    int lim = PJ_HASH_FILL * PJ_HASH_PASSES / knn, cb;
+    while (lim > 0 && !hash_fits(lim, H, &cb)) lim >>= 1;
+    return lim;
+}
+// Hubs: the first positions of a graph of at most PJ_LDS_TAB populated keys, those in more than a 64th of the lists (and
+// too many for the wavefront kernels), up to PJ_HUBS of them. Fewer than 65 are not worth it: a hub's
+// row is then never settled by the others alone (pj_rows_kernel).
+// pi, pos and popularity by position of the populated keys; the entry point; the number of hubs
+__global__ __launch_bounds__(256) void pj_pi_kernel(char* ws, ProjLayout l, int64_t M, int knn,
                                                     int32_t* __restrict__ entry) {
     ProjWs w = carve(ws, l, blockIdx.y);
     const int H = *w.H;
+    int hub_floor = small_limit(PJ_TOUCH_C, knn);
+    if (M / 64 > hub_floor) hub_floor = (int)(M / 64);
+    const int limit[PJ_CLASSES] = {small_limit(PJ_TOUCH_A, knn), small_limit(PJ_TOUCH_B, knn), small_limit(PJ_TOUCH_C, knn),
+                                   hash_limit(H, knn), PJ_WAVE_LISTS};
     for (int t = blockIdx.x * 256 + threadIdx.x; t < H; t += gridDim.x * 256) {
         const u64 k = w.keys[t];
         const int id = (int)(uint32_t)k;
         w.pi[t] = id;
         w.pos[id] = t;
-        w.ppop[t] = (int)(M - (int64_t)(k >> 32));
+        const int pop = (int)(M - (int64_t)(k >> 32)), next = t + 1 < H ? (int)(M - (int64_t)(w.keys[t + 1] >> 32)) : 0;
+        w.ppop[t] = pop;
+        if (l.n_slabs && H <= PJ_LDS_TAB && H - (t + 1) <= l.with_hubs && t >= 64 && t < PJ_HUBS && pop > hub_floor &&
+            (t + 1 == PJ_HUBS || next <= hub_floor))
+            w.H[2] = t + 1;
+#pragma unroll
+        for (int i = 0; i < PJ_CLASSES; ++i)
+            if (pop > limit[i] && next <= limit[i]) w.H[3 + i] = t + 1;
         if (t == 0) entry[blockIdx.y] = id;
     }
     if (H == 0 && blockIdx.x == 0 && threadIdx.x == 0) entry[blockIdx.y] = 0;
@@ -298,37 +420,61 @@ __global__ __launch_bounds__(256) void pj_pi_kernel(char* ws, ProjLayout l, int6
 // one range of every such key's inverted list with a single atomic add, and hands out the places
 // inside its ranges with LDS atomics in a second pass over the same cells. The order of the
 // entries inside an inverted list is immaterial (only co-occurrence counts come out of them).
-// Lists are read whole, a run of `kp` (32 or 64) lanes per list, so that no cell divides by knn.
+// Lists are read whole, a run of KP (32 or 64) lanes per list, so that no cell divides by knn; a wavefront
+// takes 32 consecutive lists, a word of the hubs' bitmaps, PJ_FLY per run at a time. The lists of a hub are that bitmap: nine
+// cells in ten of a Llama-shaped graph are hubs', and their places in inverted lists were most of this kernel's time (scattered
+// 4-byte writes; 32 graphs of 128K lists of 32: 1.95 ms, with bitmaps 0.88, with looks and positions read for
+// several cells at once, without branches, 0.74; a workgroup barrier per word of the bitmaps or none: the same. What is left is
+// the two passes' trips to LDS, a fifth of the time, and their instructions.)
+template <int KP>
 __global__ __launch_bounds__(PJ_CELL_T) void pj_inv_kernel(const int32_t* __restrict__ L, char* ws,
                                                            ProjLayout l, int64_t M, int knn, int64_t N) {
     __shared__ int s_tag[PJ_HOT];
     __shared__ int s_num[PJ_HOT];
     __shared__ int s_base[PJ_HOT];
+    __shared__ uint32_t s_bits[PJ_CELL_T / 64][PJ_HUBS];
+    constexpr int FLY = PJ_FLY, RUNS = 64 / KP, PASS = FLY * RUNS;      // PASS: lists a wavefront looks at together
     ProjWs w = carve(ws, l, blockIdx.y);
     const int32_t* Lg = L + (size_t)blockIdx.y * M * knn;
-    const int kp = knn <= 32 ? 32 : 64, e = threadIdx.x & (kp - 1), lpp = PJ_CELL_T / kp;
+    const int lane = threadIdx.x & 63, e = lane & (KP - 1), r = lane / KP;
+    uint32_t* bits = s_bits[threadIdx.x / 64];
     const bool has = e < knn;
-    const int64_t stride = (int64_t)gridDim.x * lpp, first = (int64_t)blockIdx.x * lpp + threadIdx.x / kp;
+    const bool narrow = w.H[0] <= PJ_LDS_TAB;
+    const int nh = w.H[2], stride = row16(knn);
+    uint16_t* lp16 = reinterpret_cast<uint16_t*>(w.lp);
     for (int x = threadIdx.x; x < PJ_HOT; x += PJ_CELL_T) { s_tag[x] = -1; s_num[x] = 0; }
+    bits[lane] = bits[64 + lane] = 0u;
     __syncthreads();
-    auto lists = [&](auto f) {
-        for (int64_t j0 = first; j0 < M; j0 += PJ_FLY * stride) {
-            int32_t k[PJ_FLY];
+    // (the next lists are on their way: without, every turn is a trip to memory for them)
+    const int64_t first = ((int64_t)blockIdx.x * (PJ_CELL_T / 64) + threadIdx.x / 64) * 32;
+    const int64_t after = ((int64_t)gridDim.x * (PJ_CELL_T / 64) - 1) * 32;    // from the end of a word to the wavefront's next
+    auto load = [&](int64_t j0, int32_t (&k)[FLY]) {
 #pragma unroll
-            for (int u = 0; u < PJ_FLY; ++u) {
-                const int64_t j = j0 + u * stride;
-                k[u] = Lg[(j < M ? j : j0) * knn + (has ? e : 0)];
-            }
-            f(j0, k);
+        for (int u = 0; u < FLY; ++u) {
+            const int64_t j = j0 + u * RUNS + r;
+            k[u] = Lg[(j < M ? j : M - 1) * knn + (has ? e : 0)];
         }
     };
-    lists([&](int64_t j0, const int32_t (&k)[PJ_FLY]) {
-        int tag[PJ_FLY];
+    auto lists = [&](auto f) {
+        int32_t k1[FLY];
+        load(first, k1);
+        for (int64_t j0 = first; j0 < l.words * 32;) {
+            int32_t k[FLY];
 #pragma unroll
-        for (int u = 0; u < PJ_FLY; ++u) tag[u] = hot_tag(s_tag, k[u] & (PJ_HOT - 1));
+            for (int u = 0; u < FLY; ++u) k[u] = !has || j0 + u * RUNS + r >= M || k1[u] >= N ? -1 : k1[u];
+            const int64_t next = j0 + PASS + ((j0 + PASS) % 32 == 0 ? after : 0);
+            load(next, k1);
+            f(j0, k);
+            j0 = next;
+        }
+    };
+    lists([&](int64_t, const int32_t (&k)[FLY]) {
+        int tag[FLY];
 #pragma unroll
-        for (int u = 0; u < PJ_FLY; ++u) {
-            if (!has || j0 + u * stride >= M || k[u] < 0 || k[u] >= N) continue;
+        for (int u = 0; u < FLY; ++u) tag[u] = hot_tag(s_tag, k[u] & (PJ_HOT - 1));
+#pragma unroll
+        for (int u = 0; u < FLY; ++u) {
+            if (k[u] < 0) continue;
             const int x = hot_slot(s_tag, k[u], tag[u]);
             if (x >= 0) atomicAdd(&s_num[x], 1);
         }
@@ -336,36 +482,96 @@ __global__ __launch_bounds__(PJ_CELL_T) void pj_inv_kernel(const int32_t* __rest
     __syncthreads();
     for (int x = threadIdx.x; x < PJ_HOT; x += PJ_CELL_T) {
         const int k = s_tag[x];
-        if (k >= 0) s_base[x] = w.off[k] + atomicAdd(&w.cur[k], s_num[x]);
+        if (k >= 0) {
+            const int p = nh ? w.pos[k] : 0;
+            s_base[x] = p < nh ? ~p : w.off[k] + atomicAdd(&w.cur[k], s_num[x]);
+        }
         s_num[x] = 0;                                  // now the cursor inside the range
     }
     __syncthreads();
-    lists([&](int64_t j0, const int32_t (&k)[PJ_FLY]) {
-        int p[PJ_FLY], tag[PJ_FLY], at[PJ_FLY];
+    lists([&](int64_t j0, const int32_t (&k)[FLY]) {
+        int p[FLY], at[FLY], slot[FLY];
+        hot_find(s_tag, k, slot);                        // (final by now: owners sit where they claimed)
 #pragma unroll
-        for (int u = 0; u < PJ_FLY; ++u) {
-            p[u] = w.pos[k[u] >= 0 && k[u] < N ? k[u] : 0];
-            tag[u] = s_tag[k[u] & (PJ_HOT - 1)];         // (final by now: owners sit where they claimed)
+        for (int u = 0; u < FLY; ++u) at[u] = s_base[slot[u] >= 0 ? slot[u] : 0];
+#pragma unroll
+        for (int u = 0; u < FLY; ++u) {
+            const bool hub = slot[u] >= 0 && at[u] < 0;
+            p[u] = w.pos[hub || k[u] < 0 ? 0 : k[u]];    // (no branch: all in flight)
         }
 #pragma unroll
-        for (int u = 0; u < PJ_FLY; ++u) {
-            at[u] = -1;
-            if (!has || j0 + u * stride >= M || k[u] < 0 || k[u] >= N) continue;
-            int x = k[u] & (PJ_HOT - 1);
-            if (tag[u] != k[u]) {
-                for (int v = 1; v < PJ_PROBE && s_tag[x] != k[u]; ++v) x = (k[u] + v) & (PJ_HOT - 1);
-                if (s_tag[x] != k[u]) x = -1;
+        for (int u = 0; u < FLY; ++u) {
+            if (slot[u] >= 0 && at[u] < 0) p[u] = ~at[u];
+            if (k[u] < 0) p[u] = -1;
+        }
+#pragma unroll
+        for (int u = 0; u < FLY; ++u) {
+            const int64_t j = j0 + u * RUNS + r;
+            if (k[u] >= 0) {
+                if (p[u] < nh) atomicOr(&bits[p[u]], 1u << ((int)j & 31));
+                else w.inv[slot[u] >= 0 ? at[u] + atomicAdd(&s_num[slot[u]], 1) : w.off[k[u]] + atomicAdd(&w.cur[k[u]], 1)] = (int32_t)j;
             }
-            at[u] = x >= 0 ? s_base[x] + atomicAdd(&s_num[x], 1) : w.off[k[u]] + atomicAdd(&w.cur[k[u]], 1);
+            if (narrow) {
+                if (e < stride && j < M) lp16[j * stride + e] = (uint16_t)p[u];
+            } else if (has && j < M) {
+                w.lp[j * knn + e] = p[u];
+            }
         }
-#pragma unroll
-        for (int u = 0; u < PJ_FLY; ++u) {
-            const int64_t j = j0 + u * stride;
-            if (!has || j >= M) continue;
-            if (at[u] >= 0) w.inv[at[u]] = (int32_t)j;
-            w.lp[j * knn + e] = at[u] >= 0 ? p[u] : -1;
+        if (nh && (j0 + PASS) % 32 == 0) {               // (uniform) the word is whole
+            pj_wave_sync();
+            uint32_t* word = w.bits + j0 / 32 * PJ_HUBS;
+            word[lane] = bits[lane];
+            word[64 + lane] = bits[64 + lane];
+            bits[lane] = bits[64 + lane] = 0u;
+            pj_wave_sync();
         }
     });
+}
+
+// How many lists hold both of two hubs: and + popcount over their bitmaps, 8 x 8 pairs per thread, a slab of the
+// words per workgroup. Two instructions per 32 lists and pair, which is what bounds it: 32 graphs x 128K lists 0.16 ms, 64 x 5003
+// lists 29 us (59 with one slab per graph).
+// grid: x = slab, y = graph
+__global__ __launch_bounds__(PJ_PAIR_T) void pj_pairs_kernel(char* ws, ProjLayout l) {
+    constexpr int CH = 32;                               // words in LDS at a time
+    __shared__ __align__(16) uint32_t s_bits[CH][PJ_HUBS];
+    ProjWs w = carve(ws, l, blockIdx.y);
+    const int nh = w.H[2];
+    if (nh == 0) return;
+    // tile (ti, tj), ti <= tj, of the 16 x 16: thread (r, c) of 8 x 17 takes row r from the diagonal on, then row 15 - r
+    const int tid = threadIdx.x, tr = tid / 17, tc = tid % 17;
+    const int ti = tc < 16 - tr ? tr : 15 - tr, tj = tc < 16 - tr ? tr + tc : tc - 1;
+    const int64_t begin = l.words * blockIdx.x / l.n_slabs, end = l.words * (blockIdx.x + 1) / l.n_slabs;
+    const bool mine = tid < 136 && 8 * tj < nh;
+    uint32_t acc[8][8] = {};
+    for (int64_t w0 = begin; w0 < end; w0 += CH) {
+        const int n = (int)(end - w0 < CH ? end - w0 : CH);
+        const uint4* src = reinterpret_cast<const uint4*>(w.bits + w0 * PJ_HUBS);
+        __syncthreads();
+        for (int x = tid; x < n * (PJ_HUBS / 4); x += PJ_PAIR_T) reinterpret_cast<uint4*>(&s_bits[0][0])[x] = src[x];
+        __syncthreads();
+        if (!mine) continue;
+        for (int i = 0; i < n; ++i) {
+            uint32_t a[8], b[8];
+            *reinterpret_cast<uint4*>(a) = *reinterpret_cast<const uint4*>(&s_bits[i][8 * ti]);
+            *reinterpret_cast<uint4*>(a + 4) = *reinterpret_cast<const uint4*>(&s_bits[i][8 * ti + 4]);
+            *reinterpret_cast<uint4*>(b) = *reinterpret_cast<const uint4*>(&s_bits[i][8 * tj]);
+            *reinterpret_cast<uint4*>(b + 4) = *reinterpret_cast<const uint4*>(&s_bits[i][8 * tj + 4]);
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+#pragma unroll
+                for (int y = 0; y < 8; ++y) acc[x][y] += __popc(a[x] & b[y]);
+        }
+    }
+    if (!mine) return;
+    uint32_t* out = w.pairs + (size_t)blockIdx.x * PJ_HUBS * PJ_HUBS;
+#pragma unroll
+    for (int x = 0; x < 8; ++x)
+#pragma unroll
+        for (int y = 0; y < 8; ++y) {
+            out[(8 * ti + x) * PJ_HUBS + 8 * tj + y] = acc[x][y];
+            if (ti < tj) out[(8 * tj + y) * PJ_HUBS + 8 * ti + x] = acc[x][y];
+        }
 }
 
 // ---- 4. backbone + padding for every row -----------------------------------------------
@@ -469,11 +675,6 @@ __device__ __forceinline__ Cand<WIDE> cand_merge64(Cand<WIDE> best, const Cand<W
     return best;
 }
 
-__device__ __forceinline__ void pj_wave_sync() {         // LDS written by one lane, read by another
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // The best 64 of n candidates, merged into `best` (one wavefront; lane l of best: the l-th best).
 // get(x, pos, c): position and count of candidate x in [0, n) (count 0: none). Sorting 64 candidates
 // costs hundreds of instructions, and of a few hundred candidates most are nowhere near the best 64: up
@@ -574,24 +775,6 @@ __device__ __forceinline__ void write_row(int32_t* row, const Cand<WIDE>& best, 
     if (lane >= total && lane < deg) row[lane] = -1;
 }
 
-// Keys with few lists are handled one per wavefront (pj_rows_small_kernel), the others one per
-// workgroup. first_within: the first position in pi (popularity descending) whose key has at most
-// `limit` lists.
-__device__ __forceinline__ int first_within(const int32_t* ppop, int H, int limit) {
-    int lo = 0, hi = H;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (ppop[mid] > limit) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-// most lists of a key whose list cells (lists x knn) number at most `touch` (a count must fit the 7
-// bits of a small table's entry)
-__device__ __forceinline__ int small_limit(int touch, int knn) {
-    const int lim = touch / knn;
-    return lim < 127 ? lim : 127;
-}
-
 // One more co-occurrence of the key at position `key - 1` in an open-addressing table of `slots`
 // (a power of two) LDS words, entry = key << cb | count. False when no slot is left.
 __device__ __forceinline__ bool lds_table_bump(uint32_t* tab, int slots, uint32_t key, int cb) {
@@ -631,19 +814,46 @@ __device__ __forceinline__ void walk_lists(const int32_t* inv, const int32_t* lp
     }
 }
 
+// The same over n lists with rows of 16-bit positions (stride = row16(knn)), by T threads (`at` of them this one): a lane
+// takes eight positions of a row, U rows are in flight, and the numbers of the next ones.
+template <int U, int T, class F>
+__device__ __forceinline__ void walk_narrow(const int32_t* inv, const uint16_t* lp, int n, int stride, int at, F f) {
+    const int shift = stride <= 8 ? 0 : stride <= 16 ? 1 : stride <= 32 ? 2 : 3;       // log2 of the lanes of a row
+    const int q = 8 * (at & ((1 << shift) - 1)), r = at >> shift, step = T >> shift;
+    const bool has = q < stride;
+    int j[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) j[u] = inv[r + u * step < n ? r + u * step : n - 1];
+    for (int i0 = r; i0 < n; i0 += U * step) {
+        uint4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const uint4*>(lp + (size_t)j[u] * stride + (has ? q : 0));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int next = i0 + (U + u) * step;
+            j[u] = inv[next < n ? next : n - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!has || i0 + u * step >= n) continue;
+            const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+                const int p = (int)((w[x / 2] >> (16 * (x & 1))) & 0xffffu);
+                if (p != 0xffff) f(p);
+            }
+        }
+    }
+}
+
 #define PJ_SMALL_WAVES 4
-#define PJ_TOUCH_A 256            // list cells of a key in each class of the wavefront kernel
-#define PJ_TOUCH_B 1024
-#define PJ_TOUCH_C 2048
-#define PJ_HASH_T 512             // threads of the hash kernel
-#define PJ_HASH_TAB 16384         // words of its table
-#define PJ_HASH_FILL 10240        // list cells one of its passes puts in there
-#define PJ_HASH_PASSES 4          // most passes; a key with more cells than they take is the hub kernel's
 #define PJ_HUB_T 1024             // threads of the hub kernel
 
-// first position of the keys that are not the wavefront kernels'
-__device__ __forceinline__ int large_end(const int32_t* ppop, int H, int knn) {
-    return H < (1 << 24) ? first_within(ppop, H, small_limit(PJ_TOUCH_C, knn)) : H;
+// Keys with few lists are handled one per wavefront, the others one per workgroup: first position of the former (they
+// are pj_rows_small_kernel's; in graphs of at most PJ_WAVE_TAB populated keys pj_rows_wave_kernel's, after the hubs)
+__device__ __forceinline__ int large_end(const ProjWs& w, int H) {
+    if (H <= PJ_WAVE_TAB) return w.H[2] > w.H[3 + PJ_CLASS_WAVE] ? w.H[2] : w.H[3 + PJ_CLASS_WAVE];
+    return H < (1 << 24) ? w.H[3 + PJ_CLASS_C] : H;
 }
 
 // the best 64 of a workgroup's wavefronts, and the row of the key at position t
@@ -664,11 +874,11 @@ __device__ __forceinline__ void finish_row(Cand<WIDE> best, Cand<WIDE> (*s_best)
     __syncthreads();
 }
 
-// Rows of the populated keys with more than PJ_TOUCH_C list cells, one per workgroup, of a graph with
+// Rows of the populated keys but hubs with more list cells than the wavefront kernels take, one per workgroup, of a graph with
 // at most PJ_LDS_TAB populated keys. The counters are indexed by position: bumps return nothing and are
 // never waited for (a returning add per cell, to notice first touches, was bound by its latency: 7.0
 // against 2.9 ms at 128K), and the candidates are the non-zero words.
-// grid: x = graph, y = worker of the graph (hubs are first in pi: every graph's come first this way)
+// grid: x = graph, y = worker of the graph
 template <bool WIDE>
 __global__ __launch_bounds__(PJ_ROW_T) void pj_rows_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
                                                            int32_t* __restrict__ adj) {
@@ -681,52 +891,19 @@ __global__ __launch_bounds__(PJ_ROW_T) void pj_rows_kernel(char* ws, ProjLayout 
     int32_t* adj_g = adj + (size_t)blockIdx.x * N * deg;
     const int H = *w.H;
     if (H > PJ_LDS_TAB) return;
-    const int t_end = large_end(w.ppop, H, knn);
-    if ((int)blockIdx.y >= t_end) return;
+    const int t_end = large_end(w, H);
+    const int nh = w.H[2];
+    if (nh + (int)blockIdx.y >= t_end) return;
     for (int i = tid; i < H; i += PJ_ROW_T) tab[i] = 0u;
     __syncthreads();
-    const int kp = knn <= 32 ? 32 : 64;
-    const int e = tid & (kp - 1), r0 = tid / kp, rstep = PJ_ROW_T / kp;
-    for (int t = blockIdx.y; t < t_end; t += gridDim.y) {
+    for (int t = nh + blockIdx.y; t < t_end; t += gridDim.y) {
         const int pa = w.ppop[t];
-        const int32_t* inv = w.inv + w.off[w.pi[t]];
-        auto bump = [&](int p) { atomicAdd(&tab[p], 1u); };
-        // A hub sits in tens of thousands of lists and one workgroup walks them all. Its lists
-        // go through a three-deep pipeline, sixteen per lane and stage: the list numbers of
-        // pass i + 2 and the rows of pass i + 1 are in flight while pass i bumps its counters
-        // (a pass that ran list number -> row -> counters in sequence would be two memory
-        // latencies long). Indices past the end are clamped, never branched around.
-        constexpr int UB = 16;
-        const int per_pass = UB * rstep;
-        const int n_pass = pa >= 8 * per_pass ? pa / per_pass : 0;
-        if (n_pass) {
-            int j1[UB], j2[UB], p0[UB], p1[UB];
-            auto load_inv = [&](int pass, int (&jj)[UB]) {
-                if (pass >= n_pass) pass = n_pass - 1;
-#pragma unroll
-                for (int u = 0; u < UB; ++u) jj[u] = inv[pass * per_pass + r0 + u * rstep];
-            };
-            auto load_rows = [&](const int (&jj)[UB], int (&pp)[UB]) {
-#pragma unroll
-                for (int u = 0; u < UB; ++u) pp[u] = w.lp[(size_t)jj[u] * knn + (e < knn ? e : 0)];
-            };
-            load_inv(0, j2);
-            load_inv(1, j1);
-            load_rows(j2, p0);
-            for (int pass = 0; pass < n_pass; ++pass) {
-                load_inv(pass + 2, j2);
-                load_rows(j1, p1);
-#pragma unroll
-                for (int u = 0; u < UB; ++u)
-                    if (e < knn && p0[u] >= 0) bump(p0[u]);
-#pragma unroll
-                for (int u = 0; u < UB; ++u) { p0[u] = p1[u]; j1[u] = j2[u]; }
-            }
-        }
-        walk_lists<4>(inv, w.lp, n_pass * per_pass, pa, knn, e, r0, rstep, bump);
+        walk_narrow<4, PJ_ROW_T>(w.inv + w.off[w.pi[t]], reinterpret_cast<const uint16_t*>(w.lp), pa, row16(knn), tid,
+                                 [&](int p) { atomicAdd(&tab[p], 1u); });
         __syncthreads();
         if (tid == 0) tab[t] = 0u;                           // the key itself
         __syncthreads();
+        if (tid < nh) w.with_hubs[(size_t)(t - nh) * PJ_HUBS + tid] = tab[tid];
         // a wavefront ranks its share of the positions (chunks of 64 dealt in turn)
         Cand<WIDE> best = cand_none<WIDE>();
         const int chunks = (H + 63) / 64, mine = (chunks - wv + WV - 1) / WV;
@@ -745,20 +922,6 @@ __global__ __launch_bounds__(PJ_ROW_T) void pj_rows_kernel(char* ws, ProjLayout 
 // word. A key with more cells than the table takes is done in passes over its lists, each counting the
 // positions of its own residue. What fits neither way (too many passes, count and position beyond 32
 // bits, a crowd in one residue) is left to pj_rows_hub_kernel: its first positions, or the overflow list.
-// bits of a count, and whether position and count share a word
-__device__ __forceinline__ bool hash_fits(int pa, int H, int* cb) {
-    int b = 1;
-    while ((pa >> b) != 0) ++b;
-    *cb = b;
-    return ((u64)(H + 1) << b) <= 0xffffffffull;
-}
-// first position the hash kernel takes: the lists of keys before it are too long (both conditions can
-// only get easier with fewer lists)
-__device__ __forceinline__ int hash_begin(const int32_t* ppop, int H, int knn) {
-    int lim = PJ_HASH_FILL * PJ_HASH_PASSES / knn, cb;
-    while (lim > 0 && !hash_fits(lim, H, &cb)) lim >>= 1;
-    return first_within(ppop, H, lim);
-}
 template <bool WIDE>
 __global__ __launch_bounds__(PJ_HASH_T) void pj_rows_hash_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
                                                                  int32_t* __restrict__ adj) {
@@ -772,7 +935,7 @@ __global__ __launch_bounds__(PJ_HASH_T) void pj_rows_hash_kernel(char* ws, ProjL
     int32_t* adj_g = adj + (size_t)blockIdx.x * N * deg;
     const int H = *w.H;
     if (H <= PJ_LDS_TAB) return;
-    const int t_begin = hash_begin(w.ppop, H, knn), t_end = large_end(w.ppop, H, knn);
+    const int t_begin = w.H[3 + PJ_CLASS_HASH], t_end = large_end(w, H);
     if (t_begin + (int)blockIdx.y >= t_end) return;
     for (int i = tid; i < PJ_HASH_TAB; i += PJ_HASH_T) tab[i] = 0u;
     if (tid == 0) s_over = 0;
@@ -849,7 +1012,7 @@ __global__ __launch_bounds__(PJ_HUB_T) void pj_rows_hub_kernel(char* ws, ProjLay
     int32_t* adj_g = adj + (size_t)blockIdx.x * N * deg;
     const int H = *w.H;
     if (H <= PJ_LDS_TAB) return;
-    const int t_hub = min(hash_begin(w.ppop, H, knn), large_end(w.ppop, H, knn)), n = t_hub + w.H[1];
+    const int t_hub = min(w.H[3 + PJ_CLASS_HASH], large_end(w, H)), n = t_hub + w.H[1];
     if ((int)blockIdx.y >= n) return;
     uint32_t* cnt = (uint32_t*)(ws + l.o_scratch + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * l.scratch_per_wg);
     for (int i = tid; i < PJ_LDS_TAB; i += PJ_HUB_T) tab[i] = 0u;
@@ -908,20 +1071,26 @@ __global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_small_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     uint32_t* slot = s_slot[wv];
     const int H = *w.H;
+    if (H <= PJ_WAVE_SMALL_TAB) return;                  // pj_rows_wave_kernel's
     if (H >= (1 << 24)) return;                          // a position must fit the other 25 bits: pj_rows_kernel's
+    const int nh = w.H[2];
     const int kp = knn <= 32 ? 32 : 64, e = lane & (kp - 1), lpp = 64 / kp;     // lists per pass
     for (int x = lane; x < SLOTS; x += 64) slot[x] = 0u;
     pj_wave_sync();
-    const int t0 = first_within(w.ppop, H, small_limit(TOUCH, knn));
-    const int t1 = BELOW ? first_within(w.ppop, H, small_limit(BELOW, knn)) : H;
+    const int t0 = w.H[3 + (TOUCH == PJ_TOUCH_A ? PJ_CLASS_A : TOUCH == PJ_TOUCH_B ? PJ_CLASS_B : PJ_CLASS_C)];
+    const int t1 = BELOW == 0 ? H : w.H[3 + (BELOW == PJ_TOUCH_A ? PJ_CLASS_A : PJ_CLASS_B)];
     for (int t = t0 + blockIdx.y * PJ_SMALL_WAVES + wv; t < t1; t += gridDim.y * PJ_SMALL_WAVES) {
         const int a = w.pi[t];
         const int pa = w.ppop[t];
         int slots = 128;
         while (slots < 2 * pa * knn) slots <<= 1;        // <= SLOTS by small_limit()
-        walk_lists<4>(w.inv + w.off[a], w.lp, 0, pa, knn, e, lane / kp, lpp, [&](int p) {
+        auto bump = [&](int p) {
             if (p != t) lds_table_bump(slot, slots, (uint32_t)p + 1u, 7);
-        });
+        };
+        if (H <= PJ_LDS_TAB)
+            walk_narrow<4, 64>(w.inv + w.off[a], reinterpret_cast<const uint16_t*>(w.lp), pa, row16(knn), lane, bump);
+        else
+            walk_lists<4>(w.inv + w.off[a], w.lp, 0, pa, knn, e, lane / kp, lpp, bump);
         pj_wave_sync();
         // pack the table in place: entry q moves to the number of entries before it
         int nc = 0;
@@ -933,6 +1102,18 @@ __global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_small_kernel(
             nc += __popcll(m);
         }
         pj_wave_sync();
+        if (nh) {                                            // (uniform)
+            int* row = s_surv[wv];
+            row[lane] = row[64 + lane] = 0;
+            pj_wave_sync();
+            for (int x = lane; x < nc; x += 64) {
+                const uint32_t v = slot[x];
+                if ((int)(v >> 7) <= nh) row[(v >> 7) - 1u] = (int)(v & 127u);
+            }
+            pj_wave_sync();
+            for (int x = lane; x < nh; x += 64) w.with_hubs[(size_t)(t - nh) * PJ_HUBS + x] = (uint32_t)row[x];
+            pj_wave_sync();
+        }
         Cand<WIDE> best = cand_none<WIDE>();
         select_best<(TOUCH + 63) / 64 < 16 ? (TOUCH + 63) / 64 : 16>(
             best, nc, (uint32_t)pa, w.ppop, s_surv[wv], lane, [&](int x, uint32_t& pos, uint32_t& c) {
@@ -947,28 +1128,163 @@ __global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_small_kernel(
     }
 }
 
+// Rows of the keys with at most PJ_WAVE_LISTS lists in a graph of at most PJ_WAVE_TAB populated keys, one per wavefront,
+// without a barrier; the counters are indexed by position. (With a workgroup per key, its four wavefronts' rankings
+// and their merges were most of a row: 64 graphs of about 350 populated keys 76 us, now 55 with all their smaller keys, which
+// the small kernels took another 90 for; 32 graphs of 1000 to 3000, the larger keys but hubs 0.65 -> 0.58 ms.) Above
+// PJ_WAVE_SMALL_TAB the smaller keys stay the small kernels': looking through a table of H counters for a key of a few
+// lists costs more than a hash table (the same 32 graphs: 0.60 ms here, without them 0.30, and 0.22 there).
+// grid: x = graph, y = worker
+template <int TAB, int ABOVE, bool WIDE>
+__global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_wave_kernel(char* ws, ProjLayout l, int64_t N, int knn,
+                                                                           int deg, int32_t* __restrict__ adj) {
+    __shared__ uint32_t s_tab[PJ_SMALL_WAVES][TAB];
+    __shared__ int s_surv[PJ_SMALL_WAVES][128];
+    ProjWs w = carve(ws, l, blockIdx.x);
+    int32_t* adj_g = adj + (size_t)blockIdx.x * N * deg;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    uint32_t* tab = s_tab[wv];
+    const int H = *w.H;
+    if (H > TAB || H <= ABOVE) return;
+    const int nh = w.H[2];
+    for (int x = lane; x < H; x += 64) tab[x] = 0u;
+    pj_wave_sync();
+    const int t_end = TAB == PJ_WAVE_SMALL_TAB ? H : w.H[3 + PJ_CLASS_C];
+    for (int t = large_end(w, H) + blockIdx.y * PJ_SMALL_WAVES + wv; t < t_end; t += gridDim.y * PJ_SMALL_WAVES) {
+        const int a = w.pi[t];
+        const int pa = w.ppop[t];
+        walk_narrow<4, 64>(w.inv + w.off[a], reinterpret_cast<const uint16_t*>(w.lp), pa, row16(knn), lane,
+                           [&](int p) { atomicAdd(&tab[p], 1u); });
+        pj_wave_sync();
+        if (lane == 0) tab[t] = 0u;                          // the key itself
+        pj_wave_sync();
+        for (int x = lane; x < nh; x += 64) w.with_hubs[(size_t)(t - nh) * PJ_HUBS + x] = tab[x];
+        // pack the table in place, position and count in a word (a count is at most PJ_WAVE_LISTS x 64)
+        static_assert(PJ_WAVE_TAB <= 1 << 12 && PJ_WAVE_LISTS * 64 < 1 << 20, "a position and a count share a word");
+        int nc = 0;
+        for (int q0 = 0; q0 < H; q0 += 64) {
+            const int q = q0 + lane;
+            const uint32_t c = q < H ? tab[q] : 0u;
+            if (q < H) tab[q] = 0u;
+            const u64 m = __ballot(c != 0u);
+            if (c != 0u) tab[nc + __popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)q << 20 | c;
+            nc += __popcll(m);
+        }
+        pj_wave_sync();
+        Cand<WIDE> best = cand_none<WIDE>();
+        select_best<8>(best, nc, (uint32_t)pa, w.ppop, s_surv[wv], lane, [&](int x, uint32_t& pos, uint32_t& c) {
+            const uint32_t v = tab[x];
+            pos = v >> 20;
+            c = v & 0xfffffu;
+        });
+        pj_wave_sync();
+        for (int x = lane; x < nc; x += 64) tab[x] = 0u;
+        pj_wave_sync();
+        write_row(adj_g + (size_t)a * deg, best, t, w.pi, N, deg, lane);
+    }
+}
+
+// Rows of the hubs, one per wavefront: their counts with each other are pj_pairs_kernel's, those with the other keys what
+// these found on their own walks. 32 graphs of 128K lists 0.08 ms; a walk per hub, over the front of each of its lists' rows
+// only, and only where the other hubs did not settle its row, 1.0 ms; over whole rows 1.7.
+// grid: x = graph, y = workers
+template <bool WIDE>
+__global__ __launch_bounds__(PJ_ROW_T) void pj_rows_hubs_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
+                                                                int32_t* __restrict__ adj) {
+    constexpr int WV = PJ_ROW_T / 64;
+    __shared__ uint32_t s_with[WV][PJ_HUBS];
+    __shared__ int s_surv[WV][128];
+    __shared__ int s_n, s_twice;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    ProjWs w = carve(ws, l, blockIdx.x);
+    const int H = *w.H, nh = w.H[2], t0 = blockIdx.y * WV, t = t0 + wv;
+    if (t0 >= nh) return;
+    if (tid == 0) s_twice = 0;
+    __syncthreads();
+    for (int x = lane; x < nh; x += 64) {
+        uint32_t c = 0u, own = 0u;
+#pragma unroll 4
+        for (int i = 0; i < l.n_slabs; ++i) {
+            const uint32_t* slab = w.pairs + (size_t)i * PJ_HUBS * PJ_HUBS;
+            c += slab[(t < nh ? t : t0) * PJ_HUBS + x];
+            own += slab[x * PJ_HUBS + x];
+        }
+        s_with[wv][x] = c;
+        if ((int)own != w.ppop[x]) s_twice = 1;
+    }
+    __syncthreads();
+    if (s_twice) {
+        // A list holds a hub more than once, and every pair of places counts: the lists of this workgroup's hubs are
+        // looked at one by one, their numbers written to where the hub's inverted list would be.
+        const uint16_t* lp = reinterpret_cast<const uint16_t*>(w.lp);
+        const int kp = knn <= 32 ? 32 : 64, e = tid & (kp - 1), rstep = PJ_ROW_T / kp, stride = row16(knn);
+        for (int h = t0; h < t0 + WV && h < nh; ++h) {
+            int32_t* inv = w.inv + w.off[w.pi[h]];
+            __syncthreads();
+            if (tid == 0) s_n = 0;
+            if (tid < nh) s_with[h - t0][tid] = 0u;
+            __syncthreads();
+            for (int64_t word = tid; word < l.words; word += PJ_ROW_T) {
+                uint32_t b = w.bits[word * PJ_HUBS + h];
+                for (int at = b ? atomicAdd(&s_n, __popc(b)) : 0; b != 0u; b &= b - 1u) inv[at++] = (int)(word * 32) + __ffs(b) - 1;
+            }
+            __syncthreads();
+            const int n = s_n;
+            for (int i0 = 0; i0 < n; i0 += rstep) {          // (uniform)
+                const int i = i0 + tid / kp;
+                uint32_t p = 0xffffu;
+                if (i < n && e < knn) p = lp[(size_t)inv[i] * stride + e];
+                const u64 same = __ballot(p == (uint32_t)h);
+                const int times = __popcll(kp == 64 ? same : same >> (lane & 32) & 0xffffffffull);
+                if (p < (uint32_t)nh) atomicAdd(&s_with[h - t0][p], (uint32_t)times);
+            }
+        }
+        __syncthreads();
+    }
+    if (t >= nh) return;
+    if (lane == 0) s_with[wv][t] = 0u;                       // the key itself
+    pj_wave_sync();
+    Cand<WIDE> best = cand_none<WIDE>();
+    select_best<8>(best, H, (uint32_t)w.ppop[t], w.ppop, s_surv[wv], lane, [&](int x, uint32_t& pos, uint32_t& c) {
+        pos = (uint32_t)x;
+        c = x < nh ? s_with[wv][x] : w.with_hubs[(size_t)(x - nh) * PJ_HUBS + t];
+    });
+    write_row(adj + ((size_t)blockIdx.x * N + w.pi[t]) * deg, best, t, w.pi, N, deg, lane);
+}
+
 template <bool WIDE>
 static void project_rows(const ProjLayout& l, char* ws, int n_graphs, int64_t N, int knn, int deg, hipStream_t st,
                          int32_t* adj) {
-    // workgroups that fill the part: 4 per compute unit by position, 2 of the hash kernel, 2, 4 and 8 of
-    // the small classes (LDS), all with a share of keys each
+    // workgroups that fill the part: 4 per compute unit by position, 2 of the hash kernel, 2, 4 and 8 of the small
+    // classes (LDS), all with a share of keys each; twice as many of the wavefront kernels, which not every graph needs
     auto wgs = [&](int all) { return (unsigned)(n_graphs >= all ? 1 : all / n_graphs); };
-    // (a hub takes its workgroup long: enough workers that no other key waits behind one)
+    // (a key of many lists takes its workgroup long: enough workers that no other key waits behind one)
+    const dim3 threads(PJ_SMALL_WAVES * 64);
     hipLaunchKernelGGL(pj_rows_kernel<WIDE>, dim3(n_graphs, wgs(4096) < 128 ? wgs(4096) : 128u), dim3(PJ_ROW_T), 0, st,
                        ws, l, N, knn, deg, adj);
+    hipLaunchKernelGGL((pj_rows_wave_kernel<PJ_WAVE_SMALL_TAB, 0, WIDE>), dim3(n_graphs, wgs(4096)), threads, 0, st, ws, l,
+                       N, knn, deg, adj);
+    if (l.cap > PJ_WAVE_SMALL_TAB)
+        hipLaunchKernelGGL((pj_rows_wave_kernel<PJ_WAVE_TAB, PJ_WAVE_SMALL_TAB, WIDE>), dim3(n_graphs, wgs(1024)), threads, 0,
+                           st, ws, l, N, knn, deg, adj);
     if (l.cap > PJ_LDS_TAB) {
         hipLaunchKernelGGL(pj_rows_hash_kernel<WIDE>, dim3(n_graphs, wgs(2048)), dim3(PJ_HASH_T), 0, st, ws, l, N,
                            knn, deg, adj);
         hipLaunchKernelGGL(pj_rows_hub_kernel<WIDE>, dim3(n_graphs, l.n_hub_wg), dim3(PJ_HUB_T), 0, st, ws, l, N,
                            knn, deg, adj);
     }
-    const dim3 threads(PJ_SMALL_WAVES * 64);
-    hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_C, PJ_TOUCH_B, WIDE>), dim3(n_graphs, wgs(512)), threads, 0, st,
-                       ws, l, N, knn, deg, adj);
-    hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_B, PJ_TOUCH_A, WIDE>), dim3(n_graphs, wgs(1024)), threads, 0, st,
-                       ws, l, N, knn, deg, adj);
-    hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_A, 0, WIDE>), dim3(n_graphs, wgs(2048)), threads, 0, st, ws, l,
-                       N, knn, deg, adj);
+    if (l.cap > PJ_WAVE_SMALL_TAB) {
+        hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_C, PJ_TOUCH_B, WIDE>), dim3(n_graphs, wgs(512)), threads, 0, st,
+                           ws, l, N, knn, deg, adj);
+        hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_B, PJ_TOUCH_A, WIDE>), dim3(n_graphs, wgs(1024)), threads, 0, st,
+                           ws, l, N, knn, deg, adj);
+        hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_A, 0, WIDE>), dim3(n_graphs, wgs(4096)), threads, 0, st, ws, l,
+                           N, knn, deg, adj);
+    }
+    // (after the other rows: it reads their counts)
+    if (l.n_slabs)
+        hipLaunchKernelGGL(pj_rows_hubs_kernel<WIDE>, dim3(n_graphs, PJ_HUBS * 64 / PJ_ROW_T), dim3(PJ_ROW_T), 0, st, ws, l, N,
+                           knn, deg, adj);
 }
 
 ra_status ra_launch_project(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg,
@@ -993,10 +1309,13 @@ ra_status ra_launch_project(const int32_t* L, int n_graphs, int64_t N, int64_t M
                                   l.per_graph / 4, st);
     if (rc != RA_OK) return rc;
     const unsigned px = l.cap < 64 * 256 ? (unsigned)((l.cap + 255) / 256) : 64u;
-    hipLaunchKernelGGL(pj_pi_kernel, dim3(px, n_graphs), dim3(256), 0, st, ws, l, M, entry);
+    hipLaunchKernelGGL(pj_pi_kernel, dim3(px, n_graphs), dim3(256), 0, st, ws, l, M, knn, entry);
     // (24 KB of LDS: six of these workgroups per compute unit)
     const unsigned fill_inv = n_graphs >= 1536 ? 1u : (unsigned)(1536 / n_graphs);
-    hipLaunchKernelGGL(pj_inv_kernel, dim3(cx < fill_inv ? cx : fill_inv, n_graphs), dim3(PJ_CELL_T), 0, st, L, ws, l, M, knn, N);
+    const dim3 inv_grid(cx < fill_inv ? cx : fill_inv, n_graphs);
+    if (knn <= 32) hipLaunchKernelGGL(pj_inv_kernel<32>, inv_grid, dim3(PJ_CELL_T), 0, st, L, ws, l, M, knn, N);
+    else hipLaunchKernelGGL(pj_inv_kernel<64>, inv_grid, dim3(PJ_CELL_T), 0, st, L, ws, l, M, knn, N);
+    if (l.n_slabs) hipLaunchKernelGGL(pj_pairs_kernel, dim3(l.n_slabs, n_graphs), dim3(PJ_PAIR_T), 0, st, ws, l);
     if (deg % 4 == 0)
         hipLaunchKernelGGL(pj_backbone_kernel<4>, dim3(zx, n_graphs), dim3(256), 0, st, ws, l, N, deg, adj);
     else

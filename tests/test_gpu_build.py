@@ -391,6 +391,70 @@ def test_projection_row_kernels_at_their_limits(kind):
         assert adj[a].tolist() == OP.adjacency_row(L, int(a), pop, pos, pi, deg, members), a
 
 
+def _hub_lists(rng, M, knn, hubs, per_list, others):
+    """M lists of knn keys: per_list of the first `hubs` keys, the rest of `others` keys in turn (each of them is in some)."""
+    n = knn - per_list
+    L = np.empty((M, knn), np.int32)
+    L[:, :per_list] = np.argsort(rng.random((M, hubs)), 1)[:, :per_list]
+    turn = np.concatenate([rng.permutation(others) for _ in range(-(-M * n // others))])[:M * n].reshape(M, n)
+    same = (np.diff(np.sort(turn, 1), axis=1) == 0).any(1)             # (where two turns meet)
+    turn[same] = (turn[same][:, :1] + np.arange(n)) % others
+    L[:, per_list:] = hubs + turn
+    return L[:, rng.permutation(knn)]
+
+
+@pytest.mark.parametrize("M,knn,hubs,per_list,others,form", [
+    (5000, 24, 64, 14, 400, ""), (5000, 24, 65, 14, 400, ""),          # one too few, just enough for bitmaps
+    (5003, 21, 128, 14, 301, "none"), (5001, 24, 129, 14, 400, ""),    # as many as there are bitmaps, one more; places without a key
+    (9000, 32, 100, 14, 924, "pad"), (9000, 33, 100, 20, 925, ""),     # 1024 and 1025 populated keys
+    (5000, 24, 128, 14, 1200, ""),                                     # more other keys than their counts have room
+    (17000, 24, 100, 18, 1500, ""), (17000, 24, 100, 23, 1590, ""),    # other keys of every small class
+    (26000, 40, 200, 21, 3896, ""), (26000, 40, 200, 21, 3897, ""),    # 4096, 4097; keys beyond the bitmaps in thousands of lists
+    (34011, 64, 90, 24, 8102, ""), (26000, 40, 90, 20, 8103, ""),      # 8192, 8193
+    (5000, 24, 128, 14, 300, "twice"), (5000, 40, 100, 14, 500, "twice"),
+])
+def test_projection_of_lists_with_hubs(M, knn, hubs, per_list, others, form):
+    """Graphs whose most popular keys' lists are kept as bitmaps, at the ends of what each row kernel takes, and lists that
+    hold a key twice. Every hub and a sample of the other rows, bit for bit, against counts from the lists' sparse
+    matrix, ranked in whole numbers."""
+    from scipy.sparse import csr_matrix
+    rng = np.random.default_rng(M + knn + hubs + others)
+    L = _hub_lists(rng, M, knn, hubs, per_list, others)
+    N, deg = hubs + others, 32
+    if form == "pad":                                    # ids spread over a larger context
+        N = 20001
+        L = np.sort(rng.choice(N - 1, hubs + others - 1, replace=False).astype(np.int32))[np.minimum(L, hubs + others - 2)]
+        L[0, 0] = N - 1
+    if form == "none":
+        L[rng.random(L.shape) < 0.02] = -1
+    if form == "twice":
+        j = rng.choice(M, M // 10, replace=False)
+        L[j, 1] = L[j, 0]
+    L = np.ascontiguousarray(L)
+    adj, entry = ra.ra_project(torch.from_numpy(L[None]).to(DEV), N, deg)
+    adj = adj[0].cpu().numpy()
+    has = L >= 0
+    B = csr_matrix((np.ones(has.sum(), np.int64), (np.nonzero(has)[0], L[has])), shape=(M, N))
+    pop = np.bincount(L[has], minlength=N)
+    if form != "twice" and form != "none":
+        assert (pop > 0).sum() == hubs + others - (1 if form == "pad" and pop[N - 1] == 0 else 0)
+    pi = np.lexsort((np.arange(N), -pop))
+    pos = np.empty(N, np.int64)
+    pos[pi] = np.arange(N)
+    assert int(entry[0]) == pi[0]
+    rows = np.concatenate([pi[:min(hubs, 140)], rng.choice(pi[hubs:hubs + others], 60, replace=False)])
+    C = np.asarray((B[:, rows].T @ B).todense())
+    for a, c in zip(rows, C):
+        t = int(pos[a])
+        want = [int(pi[x]) for x in (2 * t + 1, 2 * t + 2) if x < N]
+        b = np.nonzero(c)[0]
+        b = b[(b != a) & ~np.isin(b, want)]
+        # (fractions of whole numbers below 2^20 that differ, differ by more than 2^-40)
+        rank = sorted((-(int(c[x]) << 60) // int(pop[a] + pop[x] - c[x]), -int(c[x]), int(x)) for x in b)
+        want += [x for _, _, x in rank[:deg - len(want)]]
+        assert adj[a].tolist() == want + [-1] * (deg - len(want)), (a, t)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("N,M,knn", [(129, 1, 1), (160, 255, 32), (255, 257, 64), (4097, 300, 48), (1024, 1025, 33),
                                      (70000, 96, 32)])
