@@ -58,18 +58,18 @@ __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
         bool done = false;
         if constexpr (DT == RA_BF16 && G <= 4) {
             if (sub > 1) {                      // a long dense range (full attention): logits on the matrix cores
-                attend_chunk_mfma<G, TICKETS>(threadIdx.x, qg, Kh, Vh, src, x, sub, scale, rec_g + (size_t)x * AT_RS,
+                attend_chunk_mfma<G, TICKETS>(threadIdx.x, qg, Kh, Vh, src, x, sub, nS, scale, rec_g + (size_t)x * AT_RS,
                                               (int64_t)P * AT_RS, smem);
                 done = true;
             }
         }
         if (!done)
-            attend_chunk<DT, G, TICKETS>(threadIdx.x, qg, Kh, Vh, src, x, sub, scale, rec_g + (size_t)x * AT_RS,
+            attend_chunk<DT, G, TICKETS>(threadIdx.x, qg, Kh, Vh, src, x, sub, nS, scale, rec_g + (size_t)x * AT_RS,
                                          (int64_t)P * AT_RS, smem);
     } else {
         const int t = x - nS, g = t / nG, c = t % nG;
         RowSrc src{ids + ((size_t)seq * n_q + h0 + g) * topk, N, 0, 0, topk};
-        attend_chunk<DT, 1, TICKETS>(threadIdx.x, qg + (size_t)g * RA_D * esz, Kh, Vh, src, c, 1, scale,
+        attend_chunk<DT, 1, TICKETS>(threadIdx.x, qg + (size_t)g * RA_D * esz, Kh, Vh, src, c, 1, 1, scale,
                                      rec_g + ((size_t)g * P + nS + c) * AT_RS, 0, smem);
         first = g;
         n_mine = 1;

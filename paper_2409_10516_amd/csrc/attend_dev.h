@@ -77,7 +77,10 @@ __device__ __forceinline__ Row8<DT> load_row8_raw(const void* base, int64_t row,
     }
     return r;
 }
-// the same with non-temporal loads, for long dense ranges that are streamed once
+// The same for long dense ranges that are streamed once: non-temporal where one instruction takes whole cache lines
+// (bf16: plain loads cost full attention over 100003 tokens 8 us of 75). A float32 row is two instructions that touch the same
+// lines, and the second would fetch them again (8 KV heads, 60001 tokens: 101 -> 96 us with plain loads; one
+// head, 100000 tokens: 42 -> 33).
 typedef unsigned int at_u32x4 __attribute__((ext_vector_type(4)));
 template <int DT>
 __device__ __forceinline__ Row8<DT> load_row8_stream(const void* base, int64_t row, int lane16) {
@@ -87,11 +90,7 @@ __device__ __forceinline__ Row8<DT> load_row8_stream(const void* base, int64_t r
             reinterpret_cast<const uint16_t*>(base) + row * RA_D + lane16 * 8));
         r.a = make_uint4(v.x, v.y, v.z, v.w);
     } else {
-        const at_u32x4* p = reinterpret_cast<const at_u32x4*>(reinterpret_cast<const float*>(base) +
-                                                              row * RA_D + lane16 * 8);
-        const at_u32x4 a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 1);
-        r.a = make_float4(__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w));
-        r.b = make_float4(__uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w));
+        r = load_row8_raw<DT>(base, row, lane16);
     }
     return r;
 }
@@ -161,12 +160,15 @@ __device__ __forceinline__ void chunk_records(int tid, const float (&m)[NH], con
 }
 
 // One chunk for NH query heads that share the same K/V rows.
-// A call covers `n_sub` consecutive sub-chunks of 64 rows (1 for the decode step; more when a
-// long dense range is streamed, so that the number of partial records stays small).
+// A call covers `n_sub` sub-chunks of 64 rows (1 for the decode step; more when a
+// long dense range is streamed, so that the number of partial records stays small): chunk, chunk + n_chunks, ... The
+// workgroups of a head move through its rows side by side, as one front, which the memory serves better than as
+// many streams as there are workgroups (100003 tokens, 8 KV heads, bf16: the whole call 77.5 -> 75.5 us, and 74 with plain loads of K, below; three tiles in
+// flight instead of two +1.2, 640, 768 or 1024 workgroups instead of 504 +11, +4 and +6).
 // Called by all AT_THREADS threads (it contains workgroup barriers), with AT_CHUNK_LDS_FLOATS at `smem`.
 template <int DT, int NH, bool COHERENT>
 __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void* Vh,
-                             const RowSrc& src, int chunk, int n_sub, float scale, float* rec0,
+                             const RowSrc& src, int chunk, int n_sub, int n_chunks, float scale, float* rec0,
                              int64_t rec_stride, float* smem) {
     const int grp = tid >> 4, lane16 = tid & 15;
     float qv[NH][8], acc[NH][8], m[NH], l[NH];
@@ -179,15 +181,13 @@ __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void
         for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
     }
     constexpr int RPG = AT_CH / 16;    // rows per 16-lane group and sub-chunk
-    // The call covers sub-chunks [chunk * n_sub, (chunk + 1) * n_sub) of 64 rows each. The rows of
-    // the next sub-chunk are requested (raw, 16 or 32 bytes per lane and row) before the current
+    // The rows of the next sub-chunk are requested (raw, 16 or 32 bytes per lane and row) before the current
     // one is worked through. Loads are never branched around: a row that does not exist reads
     // row 0 and is skipped, a sub-chunk past the end repeats the last one and is not used.
-    const int sub_end = (chunk + 1) * n_sub;
     auto rows_of = [&](int sub, int64_t (&rid)[RPG]) {
-        if (sub >= sub_end) sub = sub_end - 1;
+        if (sub >= n_sub) sub = n_sub - 1;
 #pragma unroll
-        for (int i = 0; i < RPG; ++i) rid[i] = chunk_row(src, sub * AT_CH + grp + 16 * i);
+        for (int i = 0; i < RPG; ++i) rid[i] = chunk_row(src, (chunk + sub * n_chunks) * AT_CH + grp + 16 * i);
     };
     auto fetch = [&](const int64_t (&rid)[RPG], Row8<DT> (&kr)[RPG], Row8<DT> (&vr)[RPG]) {
 #pragma unroll
@@ -258,18 +258,18 @@ __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void
     {
         int64_t rid_a[RPG], rid_b[RPG];
         Row8<DT> k_a[RPG], v_a[RPG], k_b[RPG], v_b[RPG];
-        int sub = chunk * n_sub;
+        int sub = 0;
         rows_of(sub, rid_a);
         fetch(rid_a, k_a, v_a);
         if (n_sub == 1) {                     // the decode step's short sets: nothing to run ahead of
             consume(rid_a, k_a, v_a);
-            sub = sub_end;
+            sub = n_sub;
         }
-        for (; sub < sub_end; sub += 2) {
+        for (; sub < n_sub; sub += 2) {
             rows_of(sub + 1, rid_b);
             fetch(rid_b, k_b, v_b);
             consume(rid_a, k_a, v_a);
-            if (sub + 1 >= sub_end) break;
+            if (sub + 1 >= n_sub) break;
             rows_of(sub + 2, rid_a);
             fetch(rid_a, k_a, v_a);
             consume(rid_b, k_b, v_b);
@@ -297,7 +297,7 @@ typedef __bf16 at_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float at_f32x4 __attribute__((ext_vector_type(4)));
 template <int NH, bool COHERENT>
 __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const void* Vh, const RowSrc& src,
-                                  int chunk, int n_sub, float scale, float* rec0, int64_t rec_stride,
+                                  int chunk, int n_sub, int n_chunks, float scale, float* rec0, int64_t rec_stride,
                                   float* smem) {
     static_assert(NH >= 1 && NH <= 4, "the heads sit in the first four rows of the query operand");
     const int wv = tid >> 6, lane = tid & 63, n = lane & 15, c = lane >> 4, lane16 = n;
@@ -320,16 +320,14 @@ __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const
         for (int e = 0; e < 8; ++e) acc[h][e] = 0.f;
     }
     struct Tile { int64_t rk; uint4 kb[4]; Row8<RA_BF16> vb[4]; };
-    const int sub_end = (chunk + 1) * n_sub;
     auto fetch = [&](int sub, Tile& t) {
-        if (sub >= sub_end) sub = sub_end - 1;       // past the end: the last one again, unused
-        const int rb = sub * AT_CH + 16 * wv;
+        if (sub >= n_sub) sub = n_sub - 1;           // past the end: the last one again, unused
+        const int rb = (chunk + sub * n_chunks) * AT_CH + 16 * wv;
         t.rk = chunk_row(src, rb + n);
         const char* kp = reinterpret_cast<const char*>(Kh) + (size_t)(t.rk >= 0 ? t.rk : 0) * (RA_D * 2) + 16 * c;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const at_u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const at_u32x4*>(kp + 64 * j));
-            t.kb[j] = make_uint4(v.x, v.y, v.z, v.w);
+            t.kb[j] = *reinterpret_cast<const uint4*>(kp + 64 * j);    // (half a line each: load_row8_stream)
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -380,12 +378,12 @@ __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const
     };
     {
         Tile a, b;
-        int sub = chunk * n_sub;
+        int sub = 0;
         fetch(sub, a);
-        for (; sub < sub_end; sub += 2) {
+        for (; sub < n_sub; sub += 2) {
             fetch(sub + 1, b);
             consume(a);
-            if (sub + 1 >= sub_end) break;
+            if (sub + 1 >= n_sub) break;
             fetch(sub + 2, a);
             consume(b);
         }

@@ -152,7 +152,8 @@ __device__ __forceinline__ RowBits<DT> load_key(const void* Kh, int64_t row, int
 }
 
 // The same for a kernel that streams every row once (a scan): non-temporal loads, which leave the
-// caches to data that is read again (measured on a plain read of 1 GiB: 7.1 against 6.2 TB/s).
+// caches to data that is read again (measured on a plain read of 1 GiB: 7.1 against 6.2 TB/s). Not in float32, where two
+// instructions touch the same cache lines and the second would fetch them again (8 KV heads, 60001 tokens: 64 -> 54 us with plain loads; one head, 400000: 60 -> 52).
 typedef unsigned int ra_u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int ra_u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint4 load16_stream(const void* p) {
@@ -171,9 +172,7 @@ __device__ __forceinline__ RowBits<DT> load_key_stream(const void* Kh, int64_t r
         r.a = load16_stream(reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(Kh) + row * RA_D) + lane16);
         r.b = r.a;
     } else {
-        const uint4* p = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(Kh) + row * RA_D);
-        r.a = load16_stream(p + lane16 * 2);
-        r.b = load16_stream(p + lane16 * 2 + 1);
+        r = load_key<DT>(Kh, row, lane16);
     }
     return r;
 }
