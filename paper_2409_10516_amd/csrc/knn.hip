@@ -32,16 +32,22 @@
 // Key rows reach the matrix cores through LDS. In the operand layout a lane holds 16 bytes of
 // its own row per step, so a load straight from memory touches 64 cache lines per instruction
 // and the vector cache's line rate, not the matrix cores, sets the pace. Instead the workgroup
-// copies the key stream in 16 KB stages with fully coalesced loads (16 lanes per 256-byte row,
-// each stage fetched once for all its wavefronts and two stages ahead of its use), stores
-// them with the 16-byte chunks of a row XOR-swizzled by the row number, and every wavefront
-// reads its operands from there with conflict-free 16-byte LDS reads. Two stage buffers
-// alternate; one barrier per stage.
+// copies the key stream in 16 KB stages straight to LDS (16 lanes per 256-byte row, each stage fetched once for all
+// its wavefronts, two stages ahead of its use in bf16 and one in float32), a lane taking the chunk that belongs at its place
+// with the 16-byte chunks of a row XOR-swizzled by the row number, and every wavefront
+// reads its operands from there with conflict-free 16-byte LDS reads; one barrier per stage. What a stage of 64 keys costs 256
+// queries: 1.1 us, of which the products alone with a barrier take 0.76 (two wavefronts per SIMD, 1.4 PFLOP/s); the first eight
+// stages 26 instead of 9, for the merges of keys that are nearly all kept, and 9 us go before and after the stream. Through
+// registers, with the loop unrolled twice and a merge in each of 16 places, whole calls took 2.5 to 4 % longer (32 heads: 2 x
+// 5003 keys x 5003 queries 720 -> 697 us, 12000 x 12000 1415 -> 1366; float32 up to 11 %). No gain: the operands of two blocks
+// read and multiplied before the first is looked at, half of the wavefronts a block behind, their priority raised, two stages per
+// barrier; worse: workgroups of four wavefronts with stages of 8 KB (+8 to 16 %) or of two.
 
 #include "common.h"
 
-#define KN_PLACES 16              // places of a pending run: one more than it holds (see knn_kernel)
+#define KN_PLACES 17              // places of a pending run: one more than it holds (see knn_kernel)
 #define KN_PEND (KN_PLACES - 1)
+#define KN_IDS 8                  // stages whose key ids are in LDS or on their way there, a power of two
 #define KN_RUN_BYTES (KN_PLACES * RA_WAVE * 8)      // pending runs of a wavefront
 
 typedef unsigned long long u64;
@@ -130,14 +136,13 @@ __device__ __forceinline__ void kn_sort_pending(double (&v)[N], int half) {
 template <int LN>
 __device__ __forceinline__ void knn_fold(double (&list)[LN], const uint32_t* run, int half, int fill) {
     static_assert(LN == 16 || LN == 32, "lists of up to 32 or up to 64 keys");
-    double p[KN_PLACES];
-    p[KN_PLACES - 1] = 0.0;
+    double p[KN_PEND];
 #pragma unroll
     for (int i = 0; i < KN_PEND; ++i) {
         const u64 k = knn_key(__uint_as_float(run[i * 128]), (int)run[i * 128 + 64]);
         p[i] = __builtin_bit_cast(double, i < fill ? k : 0ull);
     }
-    kn_sort_pending<KN_PLACES>(p, half);
+    kn_sort_pending<KN_PEND>(p, half);
     // list descending against pending ascending (none before its 32): the larger of each pair are the best 2 LN, a
     // bitonic sequence over the two lanes
     if constexpr (LN == 16) {
@@ -261,31 +266,14 @@ __device__ __forceinline__ void read_operand(const unsigned char* lds, const Ope
     }
 }
 
-// Stage copy: chunk x of a stage is 16 bytes of the stage's row x / (chunks per row); consecutive
-// threads take consecutive chunks, thread tid the chunks tid + i * THREADS, so a thread copies the
-// same 16-byte column of one row in every THREADS / (chunks per row) rows. The caller passes the
-// key id of the row (stream positions beyond N repeat the last one; their scores are masked
-// later). One chunk per call so that the values in flight stay in named registers.
-template <int DT>
-__device__ __forceinline__ u32x4 fetch_chunk(const char* Kh, int key_id, int column) {
-    constexpr int ROWB = DT == RA_BF16 ? 256 : 512;
-    return *reinterpret_cast<const u32x4*>(Kh + (size_t)key_id * ROWB + (size_t)column * 16);
-}
-template <int DT, int THREADS>
-__device__ __forceinline__ void store_chunk(unsigned char* buf, int tid, int i, const u32x4& v) {
-    constexpr int ROWB = DT == RA_BF16 ? 256 : 512, CPR = ROWB / 16;
-    const int x = tid + i * THREADS;
-    const int row = x / CPR, c = x % CPR;
-    *reinterpret_cast<u32x4*>(buf + row * ROWB + ((c ^ (row & 15)) << 4)) = v;
-}
-
 // grid: x = block of 32 * WAVES queries, y = graph (seq * n_q + h) - g0. The keys are the first
 // n_stream of the graph's stream order. With `scores` the lists' scores are written
 // too, for knn_filter.hip, which takes the rest of the stream; with `resume` (first stream position not
 // yet seen, per graph and block of resume_queries queries, a multiple of 32) the lists are read from L_out and scores and
 // the stream goes on from there.
-// LDS: the pending runs of the wavefronts, then two stage buffers of STAGE bytes, then the key ids of a stage per wavefront.
+// LDS: the key ids of KN_IDS stages, then kn_ring stage buffers of STAGE bytes, then the pending runs of the wavefronts.
 // LN: keys of its query's list that a lane holds (16 or 32).
+template <int DT> constexpr int kn_ring() { return DT == RA_BF16 ? 3 : 2; }      // stage buffers
 template <int DT, int WAVES, int LN, int STAGE>
 __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     const void* __restrict__ K, const void* __restrict__ Q, const u64* __restrict__ order,
@@ -293,17 +281,19 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     int32_t* __restrict__ L_out, float* __restrict__ scores, const int* __restrict__ resume, int resume_queries,
     int resume_blocks) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    constexpr int KN_THREADS = WAVES * RA_WAVE;
     constexpr int QPB = 32 * WAVES;
     constexpr int ROWB = DT == RA_BF16 ? 256 : 512;          // bytes of a key row
     constexpr int CPR = ROWB / 16;                            // 16-byte chunks per row
     constexpr int SROWS = STAGE / ROWB;              // key rows per stage
     constexpr int SBLK = SROWS / 32;                          // 32-key blocks per stage
-    constexpr int CPT = STAGE / 16 / KN_THREADS;     // chunks a thread copies per stage
-    static_assert(SBLK == 1 || SBLK == 2, "a stage holds one or two key blocks");
-    static_assert(CPT * KN_THREADS * 16 == STAGE, "threads must tile a stage");
-    static_assert(KN_THREADS % CPR == 0, "a thread keeps its 16-byte column");
-    unsigned char* stage_buf = lds_raw + WAVES * KN_RUN_BYTES;
+    constexpr int ND = STAGE / 1024 / WAVES;         // copies of 64 chunks that a wavefront does per stage
+    constexpr int RPD = 64 / CPR;                    // rows of one
+    constexpr int RING = kn_ring<DT>(), D = RING - 1, IDS = KN_IDS;      // D: stages a copy is ahead
+    static_assert(2 * D + 1 < IDS, "a stage's ids are there until it has been multiplied");
+    static_assert(IDS * 256 + RING * STAGE <= 1 << 16, "what is copied to LDS lies in its first 64 KB (16 bits of m0)");
+    static_assert(SROWS % 32 == 0 && SROWS <= 64, "a stage holds one or two key blocks");
+    static_assert(ND * WAVES * 1024 == STAGE, "wavefronts must tile a stage");
+    unsigned char* stage_buf = lds_raw + IDS * 256;
     const int tid = threadIdx.x, wv = tid / RA_WAVE, lane = tid % RA_WAVE;
     const int col = lane & 31, half = lane >> 5;
     const int graph = g0 + (int)blockIdx.y, seq = graph / n_q, h = graph % n_q, kvh = h / (n_q / n_kv);
@@ -315,7 +305,6 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     // on it would sit right behind the load and wait for it)
     const int* ord = reinterpret_cast<const int*>(order + (size_t)graph * order_stride);
     const int last_pos = (int)n_stream - 1;               // ids and stream positions fit 31 bits
-    auto stream_id = [&](int p) __attribute__((always_inline)) { return ord[2 * (size_t)(unsigned)(p < last_pos ? p : last_pos)]; };
 
     int64_t st0 = 0, my_st0 = 0;                   // first stage of the workgroup and of this wavefront
     if (resume) {
@@ -345,10 +334,9 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
         }
         list[i] = __builtin_bit_cast(double, k);
     }
-    uint32_t* run0 = reinterpret_cast<uint32_t*>(lds_raw + wv * KN_RUN_BYTES);
+    uint32_t* run0 = reinterpret_cast<uint32_t*>(stage_buf + RING * STAGE + wv * KN_RUN_BYTES);
     uint32_t* run = run0 + lane;
-    // the key ids of the stage's rows, where the lanes that keep some of them read them
-    int* my_ids = reinterpret_cast<int*>(stage_buf + 2 * STAGE) + wv * SROWS;
+    const int* ids_ring = reinterpret_cast<const int*>(lds_raw);       // [IDS][64] key ids of the stages' rows
 
     Operand<DT> b;                                 // (loads clamped: columns beyond M are never written)
     load_operand<DT>(Qh, q0 + col < M ? q0 + col : M - 1, half, b);
@@ -358,46 +346,32 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     float tau = knn_threshold<LN>(list, knn, half, lane);      // (the lowest number but for a resumed stream)
     int fill = 0;                                  // keys in this lane's pending run
 
-    static_assert(CPT == 2 || CPT == 4, "two or four chunks per thread and stage");
     const int64_t nstage = (n_stream + SROWS - 1) / SROWS;
-    struct Held { u32x4 c0, c1, c2, c3; };         // a thread's share of one stage, in registers
-    struct Rows { int r0, r1, r2, r3; };           // key ids of the rows that share comes from
-    constexpr int RSTEP = KN_THREADS / CPR;        // rows between two chunks of a thread
-    auto load_rows = [&](Rows& r, int64_t st) __attribute__((always_inline)) {
-        if (st >= nstage) st = nstage - 1;          // past the end: the last stage again, unused
-        const int p = (int)st * SROWS + tid / CPR;
-        r.r0 = stream_id(p);
-        r.r1 = stream_id(p + RSTEP);
-        if constexpr (CPT == 4) {
-            r.r2 = stream_id(p + 2 * RSTEP);
-            r.r3 = stream_id(p + 3 * RSTEP);
-        }
+    // The ids of a stage's rows come D stages before its rows; every wavefront copies them all (the same bytes), so that it needs
+    // to wait for its own only. Positions beyond the stream copy the last key again; those are masked or not multiplied.
+    const uint32_t lds_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_raw;
+    auto copy_ids = [&](int st) __attribute__((always_inline)) {
+        const int p = st * SROWS + (lane & (SROWS - 1));
+        const int* src = ord + 2 * (size_t)(unsigned)(p < last_pos ? p : last_pos);
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+                     ::"s"(__builtin_amdgcn_readfirstlane(lds_at + (st & (IDS - 1)) * 256)), "v"(src) : "m0", "memory");
     };
-    // lane l of every wavefront: the key id of row l of the stage (row l % 32 when a stage has 32)
-    auto stage_ids = [&](int64_t st) __attribute__((always_inline)) {
-        if (st >= nstage) st = nstage - 1;
-        return stream_id((int)st * SROWS + lane % SROWS);
-    };
-    auto fetch_stage = [&](Held& h, const Rows& r) __attribute__((always_inline)) {
-        h.c0 = fetch_chunk<DT>(Kh, r.r0, tid % CPR);
-        h.c1 = fetch_chunk<DT>(Kh, r.r1, tid % CPR);
-        if constexpr (CPT == 4) {
-            h.c2 = fetch_chunk<DT>(Kh, r.r2, tid % CPR);
-            h.c3 = fetch_chunk<DT>(Kh, r.r3, tid % CPR);
-        }
-    };
-    auto store_stage = [&](const Held& h, unsigned char* buf) __attribute__((always_inline)) {
-        store_chunk<DT, KN_THREADS>(buf, tid, 0, h.c0);
-        store_chunk<DT, KN_THREADS>(buf, tid, 1, h.c1);
-        if constexpr (CPT == 4) {
-            store_chunk<DT, KN_THREADS>(buf, tid, 2, h.c2);
-            store_chunk<DT, KN_THREADS>(buf, tid, 3, h.c3);
+    auto copy_rows = [&](int st, int buf) __attribute__((always_inline)) {      // buf: st % RING
+        int id[ND];
+#pragma unroll
+        for (int i = 0; i < ND; ++i) id[i] = ids_ring[(st & (IDS - 1)) * 64 + (wv * ND + i) * RPD + lane / CPR];
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+            const int row = (wv * ND + i) * RPD + lane / CPR;
+            const char* src = Kh + (size_t)(unsigned)id[i] * ROWB + (((lane & (CPR - 1)) ^ (row & 15)) << 4);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                         ::"s"(__builtin_amdgcn_readfirstlane(lds_at + IDS * 256 + buf * STAGE + (wv * ND + i) * 1024)), "v"(src)
+                         : "m0", "memory");
         }
     };
     // scores of one 32-key block against the wave's queries, then the selection
-    // (kb: the block's place in the stream; ids: stage_ids of its stage; first: its first row there)
-    auto process = [&](const Operand<DT>& a, int64_t kb, int ids, int first) __attribute__((always_inline)) {
-        f32x16 cs = block_scores<DT>(a, b);
+    // (kb: the block's place in the stream; block_ids: the ids of its rows)
+    auto process = [&](f32x16 cs, int64_t kb, const int* block_ids) __attribute__((always_inline)) {
         const int64_t kbase = kb * 32;
         if (kbase + 32 > n_stream) {               // ragged tail: rows beyond the stream never qualify
 #pragma unroll
@@ -410,22 +384,20 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
             gm[g] = fmaxf(fmaxf(cs[4 * g], cs[4 * g + 1]), fmaxf(cs[4 * g + 2], cs[4 * g + 3]));
         const float mx = fmaxf(fmaxf(gm[0], gm[1]), fmaxf(gm[2], gm[3]));
         if (__ballot(mx >= tau) == 0ull) return;
+        // a lane needs room for the keys of this block that reach its threshold (their number can
+        // only fall when a merge raises the threshold)
+        int n = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) n += cs[r] >= tau ? 1 : 0;
+        if (__ballot(fill + n > KN_PEND)) {
+            knn_fold<LN>(list, run, half, fill);
+            tau = knn_threshold<LN>(list, knn, half, lane);
+            fill = 0;
+        }
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             if (__ballot(gm[g] >= tau) == 0ull) continue;
-            // a lane needs room for the keys of this group that reach its threshold (their number can
-            // only fall when a merge raises the threshold)
-            if (__ballot(fill > KN_PEND - 4)) {
-                int n = 0;
-#pragma unroll
-                for (int r = 4 * g; r < 4 * g + 4; ++r) n += cs[r] >= tau ? 1 : 0;
-                if (__ballot(fill + n > KN_PEND)) {
-                    knn_fold<LN>(list, run, half, fill);
-                    tau = knn_threshold<LN>(list, knn, half, lane);
-                    fill = 0;
-                }
-            }
-            const int4 id4 = *reinterpret_cast<const int4*>(my_ids + first + 8 * g + 4 * half);
+            const int4 id4 = *reinterpret_cast<const int4*>(block_ids + 8 * g + 4 * half);
             const int id[4] = {id4.x, id4.y, id4.z, id4.w};
             // a lane writes every score to the next free place, and only one that belongs there makes the place taken
 #pragma unroll
@@ -437,72 +409,46 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
             }
         }
     };
-    // one stage of keys against the wave's queries
     OperandAt<DT> a_at;                            // where this lane's key operand sits in a stage buffer
     operand_offsets<DT>((int)(stage_buf - lds_raw), col, half, a_at);
-    auto multiply_stage = [&](int cur, int64_t st, int ids) __attribute__((always_inline)) {      // cur: byte offset of the stage buffer
-        if (st < my_st0) return;                    // (keys that this wavefront's queries have seen)
-        if (SROWS == 64 || lane < SROWS) my_ids[lane] = ids;
-        Operand<DT> a0;
-        read_operand<DT>(lds_raw, a_at, cur, a0);
-        if constexpr (SBLK == 2) {
-            Operand<DT> a1;
-            read_operand<DT>(lds_raw, a_at, cur + 32 * ROWB, a1);
-            process(a0, st * 2, ids, 0);
-            process(a1, st * 2 + 1, ids, 32);   // a block beyond the stream is all masked
-        } else {
-            process(a0, st, ids, 0);
+    const int first = (int)st0;
+#pragma unroll
+    for (int i = 0; i < D; ++i) copy_ids(first + i);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+        copy_ids(first + D + i);
+        copy_rows(first + i, i);
+    }
+    // Every turn starts the same number of copies, so that "all but those of the last D - 1 turns" are the rows of the next stage and
+    // the ids the next turn needs. The loop has one copy of its code (the merge is most of it, and the instruction
+    // cache of two compute units is 64 KB).
+    constexpr int LEFT = (D - 1) * (ND + 1);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(LEFT) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    int buf = 0;                                   // of stage st
+#pragma unroll 1
+    for (int st = first; st < (int)nstage; ++st) {
+        copy_ids(st + 2 * D);
+        copy_rows(st + D, buf == 0 ? RING - 1 : buf - 1);      // (over stage st - 1, which every wavefront is done with)
+        if (st >= (int)my_st0) {                   // (else: keys that this wavefront's queries have seen)
+#pragma unroll 1
+            for (int k = 0; k < SBLK; ++k) {
+                Operand<DT> a;
+                read_operand<DT>(lds_raw, a_at, buf * STAGE + k * 32 * ROWB, a);
+                // all its reads are on their way before the first product (float32: no registers for that)
+                if constexpr (DT == RA_BF16) __builtin_amdgcn_sched_barrier(0);
+                // (a block beyond the stream is all masked)
+                process(block_scores<DT>(a, b), (int64_t)st * SBLK + k, ids_ring + (st & (IDS - 1)) * 64 + 32 * k);
+            }
         }
-    };
-    // Every thread runs every stage (the barrier needs all of them). Key rows are requested two
-    // stages before they are multiplied: a stage sits in registers for one stage time, then in
-    // its LDS buffer for the next; the key ids of the rows to request are read two requests
-    // ahead, the ids a wavefront needs for the keys it keeps two stages ahead. Loads are never
-    // branched around (a conditional load makes every later wait conservative); past the end the
-    // last stage is fetched again and dropped. The lead-in ends with a use of everything it
-    // loaded (an empty asm statement that only reads the registers), so all its loads are complete
-    // there: the compiler orders the lead-in's loads as it likes, and any of them still in flight
-    // at the loop's entry would make the loop's waits count for that order.
-    Held ha, hb;
-    Rows ra, rb;
-    int ida, idb;
-    {
-        Rows r1, r2;
-        load_rows(ra, st0);
-        load_rows(r1, st0 + 1);
-        load_rows(r2, st0 + 2);
-        fetch_stage(ha, ra);
-        store_stage(ha, stage_buf);
-        ida = stage_ids(st0);
-        fetch_stage(ha, r1);
-        load_rows(ra, st0 + 3);
-        idb = stage_ids(st0 + 1);
-        fetch_stage(hb, r2);
-        load_rows(rb, st0 + 4);
-        if constexpr (CPT == 4)
-            asm volatile("; lead-in loads complete" ::"v"(ha.c0), "v"(ha.c1), "v"(ha.c2), "v"(ha.c3),
-                         "v"(hb.c0), "v"(hb.c1), "v"(hb.c2), "v"(hb.c3), "v"(ra.r0), "v"(ra.r1), "v"(ra.r2),
-                         "v"(ra.r3), "v"(rb.r0), "v"(rb.r1), "v"(rb.r2), "v"(rb.r3), "v"(ida), "v"(idb));
-        else
-            asm volatile("; lead-in loads complete" ::"v"(ha.c0), "v"(ha.c1), "v"(hb.c0), "v"(hb.c1),
-                         "v"(ra.r0), "v"(ra.r1), "v"(rb.r0), "v"(rb.r1), "v"(ida), "v"(idb));
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"i"(LEFT) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        buf = buf == RING - 1 ? 0 : buf + 1;
     }
-    __syncthreads();
-    for (int64_t st = st0; st < nstage; st += 2) {
-        multiply_stage(0, st, ida);
-        store_stage(ha, stage_buf + STAGE);             // stage st + 1
-        __syncthreads();
-        ida = stage_ids(st + 2);
-        fetch_stage(ha, ra);                            // stage st + 3
-        load_rows(ra, st + 5);
-        if (st + 1 >= nstage) break;
-        multiply_stage(STAGE, st + 1, idb);
-        store_stage(hb, stage_buf);                     // stage st + 2
-        __syncthreads();
-        idb = stage_ids(st + 3);
-        fetch_stage(hb, rb);                            // stage st + 4
-        load_rows(rb, st + 6);
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // nothing is left on its way to LDS
     // write ids and scores, best first, a query's list at a time, through the runs' place (word of rank e of query col at
     // 32 e + (col ^ e % 32): a rank of the 32 queries, like 32 ranks of a query, is in different banks)
     knn_fold<LN>(list, run, half, fill);
@@ -544,7 +490,7 @@ struct KnnCall {
 template <int DT, int WAVES, int LN, int STAGE>
 static ra_status knn_launch_as(const KnnCall& c) {
     constexpr int QPB = 32 * WAVES;
-    const size_t lds = WAVES * KN_RUN_BYTES + 2 * STAGE + WAVES * (STAGE / (DT == RA_BF16 ? 256 : 512)) * sizeof(int);
+    const size_t lds = WAVES * KN_RUN_BYTES + kn_ring<DT>() * STAGE + KN_IDS * 256;
     RA_LDS_OPT_IN((knn_kernel<DT, WAVES, LN, STAGE>), lds);
     const dim3 grid((unsigned)((c.M + QPB - 1) / QPB), (unsigned)c.n_graphs);
     hipLaunchKernelGGL((knn_kernel<DT, WAVES, LN, STAGE>), grid, dim3(WAVES * RA_WAVE), lds, c.st, c.K, c.Q,

@@ -456,6 +456,18 @@ def test_projection_of_lists_with_hubs(M, knn, hubs, per_list, others, form):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("N", [1, 2, 31, 33, 64, 65, 96, 129, 191, 193, 257, 449])
+def test_knn_streams_of_few_stages(dtype, N):
+    """Streams of one stage, of fewer than are copied ahead, and that end within one: every key in its place."""
+    knn = min(N, 33 if N % 2 else 32)
+    w = synth.make_integer_case(N, N=N, M=70, d=128, n_q=2, n_kv=1, dtype=dtype, knn=knn)
+    L = ra.ra_knn(w.K.to(DEV), w.Q_prefill.to(DEV), knn).cpu().numpy()
+    for h in range(2):
+        K, Q = to_np(w.K[0, 0]), to_np(w.Q_prefill[0, h])
+        assert np.array_equal(L[0, h], OM.knn_lists(Q, K, knn)[0])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("N,M,knn", [(129, 1, 1), (160, 255, 32), (255, 257, 64), (4097, 300, 48), (1024, 1025, 33),
                                      (70000, 96, 32)])
 def test_knn_through_8bit_products(dtype, N, M, knn):
