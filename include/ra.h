@@ -75,7 +75,7 @@ typedef struct {
  * lists are those of the exact products.
  * Allocates scratch memory and synchronises `stream` before returning to free it: 8 bytes per key and
  * query head, rounded up to a power of two of keys, and for the 8-bit copies, where they are used, 128
- * bytes per key and query head and 144 + 4 knn per query, for as many heads at a time as fit 1.5 GiB
+ * bytes per key and query head, 32 per 512 of them and 176 + 4 knn per query, for as many heads at a time as fit 1.5 GiB
  * (at least one head). When the device has no room for the copies the lists are made without them. */
 ra_status ra_knn(const void* K, const void* Q_prefill, ra_dtype dt,
                  int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,

@@ -77,10 +77,9 @@ __device__ __forceinline__ Row8<DT> load_row8_raw(const void* base, int64_t row,
     }
     return r;
 }
-// The same for long dense ranges that are streamed once: non-temporal where one instruction takes whole cache lines
-// (bf16: plain loads cost full attention over 100003 tokens 8 us of 75). A float32 row is two instructions that touch the same
-// lines, and the second would fetch them again (8 KV heads, 60001 tokens: 101 -> 96 us with plain loads; one
-// head, 100000 tokens: 42 -> 33).
+// The same for long dense ranges that are streamed once: non-temporal, except float32, whose rows are two instructions that
+// touch the same lines, and the second would fetch them again (layers in turn, us per layer: 8 KV heads, 60001 tokens 106 ->
+// 98, 20001 tokens 48 -> 42.5; one head, 400000 95 -> 86, 5000 15.4 -> 9.8). bf16 with plain loads: 100003 tokens 8 us longer.
 typedef unsigned int at_u32x4 __attribute__((ext_vector_type(4)));
 template <int DT>
 __device__ __forceinline__ Row8<DT> load_row8_stream(const void* base, int64_t row, int lane16) {
@@ -161,14 +160,12 @@ __device__ __forceinline__ void chunk_records(int tid, const float (&m)[NH], con
 
 // One chunk for NH query heads that share the same K/V rows.
 // A call covers `n_sub` sub-chunks of 64 rows (1 for the decode step; more when a
-// long dense range is streamed, so that the number of partial records stays small): chunk, chunk + n_chunks, ... The
-// workgroups of a head move through its rows side by side, as one front, which the memory serves better than as
-// many streams as there are workgroups (100003 tokens, 8 KV heads, bf16: the whole call 77.5 -> 75.5 us, and 74 with plain loads of K, below; three tiles in
-// flight instead of two +1.2, 640, 768 or 1024 workgroups instead of 504 +11, +4 and +6).
+// long dense range is streamed, so that the number of partial records stays small): chunk, chunk + step, ... (ra_launch_attend
+// says which. Three tiles in flight instead of two, and 640, 768 or 1024 workgroups instead of 504, were slower.)
 // Called by all AT_THREADS threads (it contains workgroup barriers), with AT_CHUNK_LDS_FLOATS at `smem`.
 template <int DT, int NH, bool COHERENT>
 __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void* Vh,
-                             const RowSrc& src, int chunk, int n_sub, int n_chunks, float scale, float* rec0,
+                             const RowSrc& src, int chunk, int n_sub, int step, float scale, float* rec0,
                              int64_t rec_stride, float* smem) {
     const int grp = tid >> 4, lane16 = tid & 15;
     float qv[NH][8], acc[NH][8], m[NH], l[NH];
@@ -187,7 +184,7 @@ __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void
     auto rows_of = [&](int sub, int64_t (&rid)[RPG]) {
         if (sub >= n_sub) sub = n_sub - 1;
 #pragma unroll
-        for (int i = 0; i < RPG; ++i) rid[i] = chunk_row(src, (chunk + sub * n_chunks) * AT_CH + grp + 16 * i);
+        for (int i = 0; i < RPG; ++i) rid[i] = chunk_row(src, (chunk + sub * step) * AT_CH + grp + 16 * i);
     };
     auto fetch = [&](const int64_t (&rid)[RPG], Row8<DT> (&kr)[RPG], Row8<DT> (&vr)[RPG]) {
 #pragma unroll
@@ -297,7 +294,7 @@ typedef __bf16 at_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float at_f32x4 __attribute__((ext_vector_type(4)));
 template <int NH, bool COHERENT>
 __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const void* Vh, const RowSrc& src,
-                                  int chunk, int n_sub, int n_chunks, float scale, float* rec0, int64_t rec_stride,
+                                  int chunk, int n_sub, int step, float scale, float* rec0, int64_t rec_stride,
                                   float* smem) {
     static_assert(NH >= 1 && NH <= 4, "the heads sit in the first four rows of the query operand");
     const int wv = tid >> 6, lane = tid & 63, n = lane & 15, c = lane >> 4, lane16 = n;
@@ -322,12 +319,14 @@ __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const
     struct Tile { int64_t rk; uint4 kb[4]; Row8<RA_BF16> vb[4]; };
     auto fetch = [&](int sub, Tile& t) {
         if (sub >= n_sub) sub = n_sub - 1;           // past the end: the last one again, unused
-        const int rb = (chunk + sub * n_chunks) * AT_CH + 16 * wv;
+        const int rb = (chunk + sub * step) * AT_CH + 16 * wv;
         t.rk = chunk_row(src, rb + n);
         const char* kp = reinterpret_cast<const char*>(Kh) + (size_t)(t.rk >= 0 ? t.rk : 0) * (RA_D * 2) + 16 * c;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            t.kb[j] = *reinterpret_cast<const uint4*>(kp + 64 * j);    // (half a line each: load_row8_stream)
+            // (two of these touch a line; plain loads: 0 to 3 us longer but where the pass before left the cache full)
+            const at_u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const at_u32x4*>(kp + 64 * j));
+            t.kb[j] = make_uint4(v.x, v.y, v.z, v.w);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {

@@ -517,17 +517,17 @@ static ra_status knn_launch(const KnnCall& c, ra_dtype dt) {
 // thirty-second of the stream and at least 4096. float32, whose products cost sixteen times as much: a sixty-fourth
 // and at least sixteen times a list's length. The filter pays where what it saves on N x M products exceeds what packing
 // N keys and M queries and the larger scratch allocation cost. Whole calls of ra_knn, lists of 32, ms without -> with:
-//   bf16, 32 heads: 8K keys x 8K queries 0.82 -> 1.05; 16K x 4K 0.78 -> 0.99, x 16K 2.55 -> 2.00; 32K x 4K 1.47 -> 1.37, x
-//     32K 8.7 -> 4.8; 128K x 2K 2.98 -> 3.33, x 32K 33.3 -> 13.1.
-//   bf16, fewer heads: 4 heads, 16K x 16K 0.42 -> 0.46; 8 heads, 64K x 64K 8.5 -> 4.0.
+//   bf16, 32 heads: 8K keys x 8K queries 0.78 -> 1.12; 16K x 4K 0.78 -> 1.04, x 16K 2.43 -> 2.10; 32K x 4K 1.38 -> 1.41, x
+//     32K 8.3 -> 4.6; 128K x 2K 2.92 -> 2.94, x 32K 31.9 -> 12.1.
+//   bf16, fewer heads: 4 heads, 16K x 16K 0.40 -> 0.48; 8 heads, 64K x 64K 8.1 -> 3.8.
 //   bf16, first keys 1024 / 2048 / 4096 / 8192: 32K x 32K x 32 4.83 / 4.86 / 4.91 / 5.34; 128K x 64K x 4 of the mixture law, lists
 //     of 48: 11.8 / 11.5 / 10.5 / 10.3.
-//   float32: 32 heads, 2K x 2K 0.40 -> 0.35, 4K x 4K 1.42 -> 0.59, 16K x 4K 4.9 -> 1.26; 8 heads, 8K x 8K 1.41 -> 0.50; one head with 512
-//     queries gains from 8K keys on (0.73 -> 0.44). First keys 512 / 1024 / 2048: 16K x 4K x 32 1.26 / 1.33 / 1.58; 64K x 8K x 8 2.11 /
-//     1.50 / 1.61; lists of 64, 16K x 8K x 8 2.81 / 2.58 / 2.70.
+//   float32: 32 heads, 2K x 2K 0.37 -> 0.35, 4K x 4K 1.24 -> 0.56, 16K x 4K 4.3 -> 1.23; 8 heads, 8K x 8K 1.18 -> 0.47; one head with 512
+//     queries gains from 8K keys on (0.65 -> 0.30). First keys 512 / as below / 2048: 16K x 4K x 32 1.23 / 1.25 / 1.52; 64K x 8K x 8
+//     1.46 / 1.47 / 1.55; lists of 64, 16K x 8K x 8 1.00 / 0.69 / 0.79.
 // What decides in bf16 is the number of queries in all heads together, about 100K from 48K keys on and 260K below; the
 // line takes the queries of one head below 48K keys (32 heads: the same) and none from there on, which
-// costs calls with few queries up to 0.4 ms. In float32 the number of products decides below 8K keys.
+// costs calls with few queries up to 0.1 ms. In float32 the number of products decides below 8K keys.
 static int64_t knn_first_keys(ra_dtype dt, int graphs, int64_t N, int64_t M, int knn) {
     if (g_knn_selection_override == RA_TEST_KNN_LDS) return N;
     if (g_knn_selection_override == RA_TEST_KNN_FILTER) return N > 128 ? 128 : N;

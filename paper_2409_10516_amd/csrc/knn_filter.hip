@@ -651,8 +651,8 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     };
 
     // ---- the stream. Every wavefront copies its operands to a ring of its own in LDS, eight of them ahead, straight
-    //      from memory (no register holds them on the way), and waits for nobody. 128K keys x 32 heads: 33 ms; with
-    //      stages of 128 keys that the workgroup shares in LDS 34 ms, loads to registers instead of the ring 42 ms.
+    //      from memory (no register holds them on the way), and waits for nobody. 128K keys x 32 heads, when it was made: 33 ms;
+    //      with stages of 128 keys that the workgroup shares in LDS 34 ms, loads to registers instead of the ring 42 ms.
     //      1M keys x 4 heads, where wavefronts have keys to score at different times: 36, 41 and 35 ms. Before
     //      (stages, whole products, no mean taken off): 51 and 41 ms.
     const unsigned char* K8g = K8 + (size_t)gl * rows8 * RA_D;
@@ -747,9 +747,9 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     };
     // the floors of the segment that opens at block blk; false when none of its keys can reach a threshold
     auto open_segment = [&]() __attribute__((always_inline)) -> bool {
-        // The wavefronts meet every 2048 keys, so that they stay in reach of each other's lines in the caches (1M keys x
-        // 4 heads: 38.2 -> 35.4 ms; x 4 heads of 16K queries, one set per wavefront: 30 -> 16 ms; a meeting every 512
-        // keys: 38.0 and 17 ms). A barrier waits for no wavefront that has ended.
+        // The wavefronts meet every 2048 keys, so that they stay in reach of each other's lines in the caches (whole
+        // calls, 1M keys x 4 heads of 64K queries: 43.4 -> 40.6 ms, of 16K queries, one set per wavefront: 30.1 -> 17.0; a meeting
+        // every 512 keys: 43.3 and 17.9). A barrier waits for no wavefront that has ended.
         if ((blk / KF_SEG_BLOCKS) % KF_MEET == 0) __builtin_amdgcn_s_barrier();
         const float4 g0 = seg_g[2 * (blk / KF_SEG_BLOCKS)], g1 = seg_g[2 * (blk / KF_SEG_BLOCKS) + 1];
         sg_x = g0.x; sg_e = g0.y; sg_b_max = g0.z; sg_b_min = g0.w; sg_x1 = g1.x; sg_x2 = g1.y; sg_x3 = g1.z;
@@ -920,8 +920,8 @@ ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const 
     const dim3 pgrid((unsigned)(nseg < 128 ? nseg : 128), (unsigned)n_graphs);
     const dim3 qgrid((unsigned)(M / 16 < 255 ? M / 16 + 1 : 256), (unsigned)n_graphs);
     int* res = reinterpret_cast<int*>(ws + l.resume);
-    // four query sets per wavefront (a key operand feeds four chains: 64 ms against 71 with two and 103
-    // with one, 128K keys x 32 heads) unless that leaves compute units without a workgroup
+    // four query sets per wavefront (a key operand feeds four chains: 39.9 ms against 47.1 with two and 69.9
+    // with one, 128K keys x 32 heads; 4 heads 5.7, 6.2 and 9.0) unless that leaves compute units without a workgroup
     auto blocks = [&](int nq) { return (M + KF_WAVES * 32 * nq - 1) / (KF_WAVES * 32 * nq); };
     const int NQ = blocks(4) * n_graphs * KF_WAVES >= 2048 ? 4 : blocks(2) * n_graphs * KF_WAVES >= 2048 ? 2 : 1;
     const dim3 grid((unsigned)blocks(NQ), (unsigned)n_graphs);
