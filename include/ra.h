@@ -2,7 +2,8 @@
  * libra — RetrievalAttention decode hot path and index build for AMD MI355X (gfx950).
  *
  * C ABI. Every tensor argument is a DEVICE pointer to contiguous row-major memory
- * owned by the caller unless the comment says "host". The library never frees or
+ * owned by the caller unless the comment says "host", aligned to its elements or better (ra_knn and the
+ * builds are slower with a K that is not 16-byte aligned). The library never frees or
  * retains caller tensors; an ra_index owns only its graph and its private workspace.
  * All device work is enqueued on `stream` (a hipStream_t passed as void*; NULL is the
  * default stream). Decode-path calls return without synchronising. Argument checks

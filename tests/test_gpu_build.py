@@ -468,6 +468,25 @@ def test_knn_streams_of_few_stages(dtype, N):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("N,M,knn", [(65, 40, 32), (515, 70, 33), (2600, 130, 64), (17000, 8200, 32)])
+def test_knn_of_views_at_odd_offsets(dtype, N, M, knn, knn_selection):
+    """Keys and queries that start at any element of their storage: the lists of aligned copies, bit for bit."""
+    if dtype == torch.float32 and M > 1000:
+        M = 600
+    K = torch.randn(2, 2, N, 128, device=DEV).to(dtype)
+    Q = torch.randn(2, 4, M, 128, device=DEV).to(dtype)
+    want = ra.ra_knn(K, Q, knn)
+    for at in (1, 2, 3, 4, 7):
+        def moved(t):
+            v = torch.empty(t.numel() + at, dtype=dtype, device=DEV)[at:].view(t.shape)
+            return v.copy_(t)
+        Ka, Qa = moved(K), moved(Q)
+        assert Ka.data_ptr() % 16 == at * K.element_size() % 16
+        assert torch.equal(ra.ra_knn(Ka, Qa, knn), want)
+        assert torch.equal(ra.ra_knn(Ka, Q, knn), want)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("N,M,knn", [(129, 1, 1), (160, 255, 32), (255, 257, 64), (4097, 300, 48), (1024, 1025, 33),
                                      (70000, 96, 32)])
 def test_knn_through_8bit_products(dtype, N, M, knn):
