@@ -480,7 +480,11 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     __shared__ int s_count[KF_WAVES][NQ];
     __shared__ u64 s_run[KF_WAVES][NQ][KF_RUN][RA_WAVE];
     __shared__ unsigned char s_fill[KF_WAVES][NQ][RA_WAVE];
-    __shared__ __align__(16) unsigned char s_ring[KF_WAVES][KF_RING * KF_OPERAND];
+    // What is copied to LDS has to lie in its first 64 KB (16 bits of m0). The compiler lays a kernel's arrays out by alignment, the
+    // largest first: no other may ask for as much. (In one struct with the rings first, or looked at when the kernel starts, the
+    // rare path's registers go to memory and 1M keys x 4 heads take 1.5 to 2 % longer.)
+    static_assert(KF_WAVES * KF_RING * KF_OPERAND <= 1 << 16, "the rings fit the first 64 KB of LDS");
+    __shared__ __align__(1024) unsigned char s_ring[KF_WAVES][KF_RING * KF_OPERAND];
     __shared__ __align__(16) float4 s_query[KF_WAVES][NQ][2][32];      // of KfQuery: [a, f, r, inv], [y1, y2, y3, tau]
     __shared__ float s_slack[KF_WAVES][NQ][32];
     __shared__ int s_kept, s_seen;                     // of the workgroup's sets: keys not ruled out, blocks looked at
