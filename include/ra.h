@@ -101,10 +101,11 @@ ra_status ra_build_index(const void* K, const void* Q_prefill, ra_dtype dt,
                          int deg, int knn, void* stream, ra_index** out);
 
 /* The same, and ra_project, with scratch memory of the caller's (device, 256-byte aligned, theirs again when the call
- * returns): what ra_build_workspace_bytes and ra_project_scratch_bytes say, which is 0 for sizes that are refused. With
- * workspace NULL the call allocates and frees it itself (freeing a piece of 150 MB or more is a quarter of a
- * millisecond); with too little it is refused, but a build that lacks no more than the 8-bit copies of ra_knn
- * goes on without them. */
+ * returns): what ra_build_workspace_bytes and ra_project_scratch_bytes say, which is 0 for sizes that
+ * are refused. The graphs are projected in groups of up to 1.5 GiB of it. With workspace NULL the call allocates and frees it
+ * itself (freeing a piece of 150 MB or more is a quarter of a millisecond, one of several gigabytes can be many). With less, or on a
+ * device that has no more, it goes on with what there is: without the 8-bit copies of ra_knn, with fewer graphs at a
+ * time; with less than the lists, the stream order of ra_knn and one graph take it is refused. */
 size_t ra_project_scratch_bytes(int n_graphs, int64_t N, int64_t M, int deg, int knn);
 ra_status ra_project_ws(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg, void* workspace,
                         size_t workspace_bytes, void* stream, int32_t* adj, int32_t* entry);

@@ -216,7 +216,7 @@ def _with_scratch(stream, need: int, call) -> None:
     """call(workspace, its bytes, stream) -> status, for a call that returns when the stream is done. Up to
     BUILD_POOLED_BYTES of scratch memory, for a call on the current stream, come from torch's allocator, which has the
     piece of the last call at hand: the library's own allocation and free are 0.3 of the 1.6 ms that a build for two
-    prompts of 5K tokens took with them. Larger calls don't notice, and leave no large piece with torch; where
+    prompts of 5K tokens took with them. Of a larger call they are a smaller part, and it leaves no large piece with torch; where
     torch finds no room, the library allocates as for those."""
     ws = None
     if stream is None and 0 < need <= BUILD_POOLED_BYTES:

@@ -366,7 +366,7 @@ extern "C" ra_status ra_knn(const void* K, const void* Q, ra_dtype dt, int n_seq
 
 extern "C" size_t ra_project_scratch_bytes(int n_graphs, int64_t N, int64_t M, int deg, int knn) {
     if (n_graphs < 1 || check_build_args(N, M, deg, knn, true) != RA_OK) return 0;
-    return ra_project_workspace_bytes(n_graphs, N, M, knn);
+    return ra_project_workspace_bytes(n_graphs, N, M, knn, false);
 }
 
 extern "C" ra_status ra_project_ws(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg, void* workspace,
@@ -374,12 +374,21 @@ extern "C" ra_status ra_project_ws(const int32_t* L, int n_graphs, int64_t N, in
     if (!L || !adj || !entry) RA_FAIL(RA_EINVAL, "NULL argument");
     if (n_graphs < 1) RA_FAIL(RA_EINVAL, "n_graphs must be positive");
     RA_TRY(check_build_args(N, M, deg, knn, true));
-    const size_t ws_bytes = ra_project_workspace_bytes(n_graphs, N, M, knn);
-    if (workspace && workspace_bytes < ws_bytes)
-        RA_FAIL(RA_ESHAPE, "workspace of %zu bytes, the projection needs %zu", workspace_bytes, ws_bytes);
+    const size_t most = ra_project_workspace_bytes(n_graphs, N, M, knn, false);
+    const size_t least = ra_project_workspace_bytes(n_graphs, N, M, knn, true);
+    if (workspace && workspace_bytes < least)
+        RA_FAIL(RA_ESHAPE, "workspace of %zu bytes, the projection needs %zu", workspace_bytes, least);
+    // (the scratch memory of a few graphs at a time says nothing about the whole any more)
+    int device = 0;
+    size_t total = 0;
+    RA_HIP(hipGetDevice(&device));
+    RA_HIP(hipDeviceTotalMem(&total, device));
+    if ((double)n_graphs * (double)N * deg * sizeof(int32_t) > (double)total)
+        RA_FAIL(RA_ENOMEM, "the adjacency of %d graphs of %lld keys is larger than the device's memory", n_graphs, (long long)N);
     void* ws = workspace;
-    if (!ws) RA_HIP(hipMalloc(&ws, ws_bytes));
-    ra_status rc = ra_launch_project(L, n_graphs, N, M, knn, deg, ws, (hipStream_t)stream, adj, entry);
+    size_t got = workspace_bytes;
+    if (!ws) RA_HIP(build_scratch(&ws, most, least, &got));
+    ra_status rc = ra_launch_project(L, n_graphs, N, M, knn, deg, ws, got, (hipStream_t)stream, adj, entry);
     hipError_t e = hipStreamSynchronize((hipStream_t)stream);
     if (!workspace) (void)hipFree(ws);
     if (rc != RA_OK) return rc;
@@ -393,12 +402,12 @@ extern "C" ra_status ra_project(const int32_t* L, int n_graphs, int64_t N, int64
 }
 
 // One piece of scratch memory: the lists, then the workspace of the two stages, which do not use it at
-// the same time. `plain`: without 8-bit copies of the keys.
-static size_t build_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn, bool plain, size_t* lists) {
+// the same time. `least`: what they can do with (no 8-bit copies of the keys, one graph projected at a time).
+static size_t build_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn, bool least, size_t* lists) {
     const int graphs = n_seq * n_q;
     *lists = ((size_t)graphs * M * knn * sizeof(int32_t) + 255) & ~(size_t)255;
-    const size_t knn_bytes = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, plain);
-    const size_t proj_bytes = ra_project_workspace_bytes(graphs, N, M, knn);
+    const size_t knn_bytes = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, least);
+    const size_t proj_bytes = ra_project_workspace_bytes(graphs, N, M, knn, least);
     return *lists + (knn_bytes > proj_bytes ? knn_bytes : proj_bytes);
 }
 
@@ -442,7 +451,7 @@ extern "C" ra_status ra_build_index_ws(const void* K, const void* Q, ra_dtype dt
     void* ws = reinterpret_cast<char*>(L) + l_bytes;
     ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, got - l_bytes, (hipStream_t)stream, L);
     if (rc == RA_OK)
-        rc = ra_launch_project(L, graphs, N, M, knn, deg, ws, (hipStream_t)stream, ix->adj, ix->entry);
+        rc = ra_launch_project(L, graphs, N, M, knn, deg, ws, got - l_bytes, (hipStream_t)stream, ix->adj, ix->entry);
     if (rc == RA_OK)
         rc = ra_launch_roots(ix->adj, ix->entry, graphs, N, deg, ix->roots, ix->root_cap, (hipStream_t)stream);
     // (also after a stage that could not be launched: what was launched before it uses the memory)

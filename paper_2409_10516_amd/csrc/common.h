@@ -171,9 +171,9 @@ const float* ra_knn_order_mean(const void* workspace, int graphs, int64_t N, int
 ra_status ra_launch_knn_order(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
                               int64_t N, int64_t M, void* workspace, hipStream_t st);
 
-size_t ra_project_workspace_bytes(int n_graphs, int64_t N, int64_t M, int knn);
+size_t ra_project_workspace_bytes(int n_graphs, int64_t N, int64_t M, int knn, bool least);
 ra_status ra_launch_project(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg,
-                            void* workspace, hipStream_t st, int32_t* adj, int32_t* entry);
+                            void* workspace, size_t workspace_bytes, hipStream_t st, int32_t* adj, int32_t* entry);
 
 // ---- device helpers ------------------------------------------------------------------
 #ifdef __HIPCC__

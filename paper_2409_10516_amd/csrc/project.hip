@@ -101,7 +101,8 @@ struct ProjLayout {
 };
 __host__ __device__ constexpr int row16(int knn) { return (knn + 7) & ~7; }      // (16-byte reads)
 
-static ProjLayout proj_layout(int n_graphs, int64_t N, int64_t M, int knn) {
+// n_graphs: graphs projected at one time; hubs false: without memory for the hubs' arrays (every key by the other kernels)
+static ProjLayout proj_layout(int n_graphs, int64_t N, int64_t M, int knn, bool hubs) {
     ProjLayout l;
     const int64_t cells = M * knn;
     l.cap = N < cells ? N : cells;
@@ -116,18 +117,26 @@ static ProjLayout proj_layout(int n_graphs, int64_t N, int64_t M, int knn) {
     l.o_inv = o; o += align256((size_t)cells * 4);
     const size_t narrow = (size_t)M * row16(knn) * 2;
     l.o_lp = o; o += align256(l.cap > PJ_LDS_TAB && (size_t)cells * 4 > narrow ? (size_t)cells * 4 : narrow);
+    const size_t lp_end = o;
     l.words = (M + 31) / 32;
-    l.n_slabs = cells < 32768 ? 0 : (int)(l.words / PJ_SLAB_WORDS < 1 ? 1 : l.words / PJ_SLAB_WORDS > PJ_MOST_SLABS ? PJ_MOST_SLABS : l.words / PJ_SLAB_WORDS);
+    l.n_slabs = !hubs || cells < 32768 ? 0 : (int)(l.words / PJ_SLAB_WORDS < 1 ? 1 : l.words / PJ_SLAB_WORDS > PJ_MOST_SLABS ? PJ_MOST_SLABS : l.words / PJ_SLAB_WORDS);
     l.with_hubs = !l.n_slabs ? 0 : cells < 1 << 20 ? cells / 256 : PJ_LDS_TAB;
     if (l.with_hubs > l.cap) l.with_hubs = l.cap;
     l.o_keys = o; o += align256((size_t)l.cap_pad * 8);
     // What the hubs take is no more than the inverted lists (half of them for the counts, 16 bytes a list, a slab of pairs per
-    // 2048 lists), and lies where there is room in what is not read any more by then: the bitmaps on pop, the pairs on cur
-    // and the counts on keys (freeing a larger workspace costs up to 8 us a megabyte).
+    // 2048 lists), and lies where there is room: behind the 16-bit lists, which is where a graph of more populated keys, which
+    // has no hubs, has the rest of its 32-bit ones, or in what is not read any more by then, the bitmaps on pop, the pairs on
+    // cur and the counts on keys (32 graphs of 128K lists of 32: 1.50 GB in all instead of 1.73).
+    size_t behind = l.o_lp + align256(narrow);
     auto hubs_on = [&](size_t at, size_t room, size_t bytes) {
         if (bytes <= room) return at;
-        at = o;
-        o += align256(bytes);
+        at = behind;
+        if (at + align256(bytes) <= lp_end) {
+            behind += align256(bytes);
+        } else {
+            at = o;
+            o += align256(bytes);
+        }
         return at;
     };
     if (l.n_slabs) {
@@ -152,10 +161,27 @@ static ProjLayout proj_layout(int n_graphs, int64_t N, int64_t M, int knn) {
     l.o_scratch = l.per_graph * n_graphs;
     return l;
 }
+static size_t proj_bytes(const ProjLayout& l, int n_graphs) { return l.o_scratch + (size_t)l.n_hub_wg * n_graphs * l.scratch_per_wg; }
 
-size_t ra_project_workspace_bytes(int n_graphs, int64_t N, int64_t M, int knn) {
-    const ProjLayout l = proj_layout(n_graphs, N, M, knn);
-    return l.o_scratch + (size_t)l.n_hub_wg * n_graphs * l.scratch_per_wg;
+// How many of the graphs are projected at one time, in `most` bytes (one, where there is no room for more). With 1.5 GiB a launch
+// still has the graphs of a layer of 128K, and a batch takes as long as in one piece, ra_project of 512 graphs: 32768 keys,
+// 4096 lists of 32 in 1.4 instead of 7.9 GB 5.13 -> 5.12 ms; 20000 keys, 8192 lists of 64 in 1.4 instead of 8.3 GB 10.2 -> 9.9 ms. (The
+// driver's own time for pieces of 4 GB and more is anything from half a millisecond to half a second.)
+#define PJ_MOST_BYTES ((size_t)3 << 29)
+static int proj_graphs_at_once(int n_graphs, int64_t N, int64_t M, int knn, bool hubs, size_t most) {
+    const size_t all = proj_layout(1, N, M, knn, hubs).per_graph * n_graphs;
+    int64_t calls = all / most < (size_t)n_graphs ? (int64_t)(all / most) + 1 : n_graphs;
+    while (true) {
+        const int64_t g = (n_graphs + calls - 1) / calls;
+        if (g == 1 || proj_bytes(proj_layout((int)g, N, M, knn, hubs), (int)g) <= most) return (int)g;
+        calls = (n_graphs + g - 2) / (g - 1);            // (as many as make it fewer at a time)
+    }
+}
+
+// least: what it can do with, one graph at a time and without the hubs' arrays
+size_t ra_project_workspace_bytes(int n_graphs, int64_t N, int64_t M, int knn, bool least) {
+    const int g = least ? 1 : proj_graphs_at_once(n_graphs, N, M, knn, true, PJ_MOST_BYTES);
+    return proj_bytes(proj_layout(g, N, M, knn, !least), g);
 }
 
 __device__ __forceinline__ ProjWs carve(char* ws, const ProjLayout& l, int g) {
@@ -1287,13 +1313,9 @@ static void project_rows(const ProjLayout& l, char* ws, int n_graphs, int64_t N,
                            knn, deg, adj);
 }
 
-ra_status ra_launch_project(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg,
-                            void* workspace, hipStream_t st, int32_t* adj, int32_t* entry) {
-    if (M * (int64_t)knn >= ((int64_t)1 << 31))
-        RA_FAIL(RA_EUNSUP, "M * knn must stay below 2^31 list cells");
-    if (n_graphs > 65535) RA_FAIL(RA_EUNSUP, "more than 65535 graphs");
-    const ProjLayout l = proj_layout(n_graphs, N, M, knn);
-    char* ws = (char*)workspace;
+// n_graphs graphs, no more than the layout is for
+static ra_status project_group(const ProjLayout& l, char* ws, const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn,
+                               int deg, hipStream_t st, int32_t* adj, int32_t* entry) {
     const int64_t cells = M * knn;
     const unsigned gx = 256;
     const unsigned zx = N < 256 * 256 ? (unsigned)((N + 255) / 256) : gx;
@@ -1324,4 +1346,22 @@ ra_status ra_launch_project(const int32_t* L, int n_graphs, int64_t N, int64_t M
     else project_rows<true>(l, ws, n_graphs, N, knn, deg, st, adj);
     RA_HIP(hipGetLastError());
     return RA_OK;
+}
+
+// workspace: what ra_project_workspace_bytes says. (With less, as many graphs at a time as fit, if need be without the
+// hubs' arrays: the same rows.)
+ra_status ra_launch_project(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg,
+                            void* workspace, size_t workspace_bytes, hipStream_t st, int32_t* adj, int32_t* entry) {
+    if (M * (int64_t)knn >= ((int64_t)1 << 31))
+        RA_FAIL(RA_EUNSUP, "M * knn must stay below 2^31 list cells");
+    if (n_graphs > 65535) RA_FAIL(RA_EUNSUP, "more than 65535 graphs");
+    const size_t most = workspace_bytes < PJ_MOST_BYTES ? workspace_bytes : PJ_MOST_BYTES;
+    const bool hubs = proj_bytes(proj_layout(1, N, M, knn, true), 1) <= workspace_bytes;
+    const int at_once = proj_graphs_at_once(n_graphs, N, M, knn, hubs, most);
+    const ProjLayout l = proj_layout(at_once, N, M, knn, hubs);
+    ra_status rc = RA_OK;
+    for (int g = 0; g < n_graphs && rc == RA_OK; g += at_once)
+        rc = project_group(l, (char*)workspace, L + (size_t)g * M * knn, n_graphs - g < at_once ? n_graphs - g : at_once, N, M,
+                           knn, deg, st, adj + (size_t)g * N * deg, entry + g);
+    return rc;
 }

@@ -64,6 +64,21 @@ def test_build_and_project_validation():
     assert L.ra_project(None, 1, 100, 10, 8, 8, None, _fake(), _fake()) == 1
 
 
+def test_scratch_memory_of_a_batch_is_bounded():
+    """The projection takes its graphs in groups: 512 graphs need no more than 1.5 GiB at a time, one that needs more by itself
+    what it needs, and a build of a batch its lists and the larger of its two stages."""
+    L = ra.lib()
+    most = 3 << 29
+    one = L.ra_project_scratch_bytes(1, 32768, 32768, 32, 32)
+    assert 0 < one < L.ra_project_scratch_bytes(512, 32768, 32768, 32, 32) <= most
+    assert L.ra_project_scratch_bytes(65535, 2000, 2000, 32, 32) <= most
+    for n, N, M, knn in [(32, 131072, 131072, 32), (32, 262144, 262144, 32), (512, 20000, 20000, 64), (7, 1 << 20, 65536, 48)]:
+        assert L.ra_project_scratch_bytes(n, N, M, 32, knn) <= most
+    assert L.ra_project_scratch_bytes(2, 1 << 24, 1 << 24, 32, 32) == L.ra_project_scratch_bytes(1, 1 << 24, 1 << 24, 32, 32) > most
+    lists = 16 * 32 * 32768 * 32 * 4
+    assert lists < L.ra_build_workspace_bytes(1, 16, 32, 8, 32768, 32768, 128, 32, 32) <= lists + most + (512 << 20)
+
+
 def test_decode_validation_without_index():
     L = ra.lib()
     rc = L.ra_decode_step(_fake(), None, _fake(), _fake(), 1, 100, 4, 8, 10, 20, 1, None, _fake(),

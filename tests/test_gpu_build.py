@@ -319,6 +319,37 @@ def test_build_in_the_callers_workspace(room):
     want.free()
 
 
+@pytest.mark.parametrize("n,M,knn,hubs,per_list,others", [
+    (7, 1500, 24, 100, 14, 400),        # hubs' arrays of their own
+    (5, 700, 64, 90, 24, 9000),         # more keys than 16-bit lists are for: 32-bit lists, counters in device memory
+    (5, 4000, 64, 90, 24, 7000),        # as many cells, fewer populated keys: the hubs' arrays behind the 16-bit lists
+])
+def test_projection_in_any_amount_of_memory(n, M, knn, hubs, per_list, others):
+    """Several graphs, all at a time, a few, one by one, and without memory for the hubs' arrays: the rows of each projected
+    alone; less is refused; the memory behind the workspace stays as it was."""
+    import re
+    lib, deg, N = ra.lib(), 32, 9500
+    L = np.stack([_hub_lists(np.random.default_rng(M + g), M, knn, hubs, per_list, others) for g in range(n)])
+    Ld = torch.from_numpy(np.ascontiguousarray(L)).to(DEV)
+    alone = [ra.ra_project(Ld[g:g + 1].contiguous(), N, deg) for g in range(n)]
+    want, entry = torch.cat([a for a, _ in alone]), torch.cat([e for _, e in alone])
+    st = torch.cuda.current_stream().cuda_stream
+    adj, ent = torch.empty_like(want), torch.empty_like(entry)
+    piece = torch.full((4096,), 77, dtype=torch.uint8, device=DEV)
+    assert lib.ra_project_ws(Ld.data_ptr(), n, N, M, knn, deg, piece.data_ptr(), 256, st, adj.data_ptr(), ent.data_ptr()) == 2
+    least = int(re.search(r"needs (\d+)", lib.ra_last_error().decode()).group(1))
+    one, full = (lib.ra_project_scratch_bytes(k, N, M, deg, knn) for k in (1, n))
+    assert 256 < least <= one < full
+    for have in sorted({least, max(least, one - 1), one, 2 * least, 3 * one, (full + one) // 2, full - 1, full, full + 4096}):
+        piece = torch.full((have + 4096,), 77, dtype=torch.uint8, device=DEV)
+        adj.fill_(-7)
+        ent.fill_(-7)
+        rc = lib.ra_project_ws(Ld.data_ptr(), n, N, M, knn, deg, piece.data_ptr(), have, st, adj.data_ptr(), ent.data_ptr())
+        assert rc == 0 and torch.equal(adj, want) and torch.equal(ent, entry), have
+        assert bool((piece[have:] == 77).all())
+    assert lib.ra_project_ws(Ld.data_ptr(), n, N, M, knn, deg, piece.data_ptr(), least - 1, st, adj.data_ptr(), ent.data_ptr()) == 2
+
+
 def test_build_argument_errors():
     w = synth.make_integer_case(1, N=64, M=16, d=128)
     Kd, Qd = w.K.to(DEV), w.Q_prefill.to(DEV)
