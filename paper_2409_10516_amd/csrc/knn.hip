@@ -432,7 +432,8 @@ __global__ __launch_bounds__(WAVES * RA_WAVE) void knn_kernel(
     // the ids the next turn needs. The loop has one copy of its code (the merge is most of it, and the instruction
     // cache of two compute units is 64 KB).
     constexpr int LEFT = DIRECT ? (D - 1) * (ND + 1) : 0;
-    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(LEFT) : "memory");
+    // (lgkmcnt: rows that went through registers are LDS writes, which the barrier does not wait for)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"i"(LEFT) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     int buf = 0;                                   // of stage st
