@@ -170,7 +170,8 @@ static size_t proj_bytes(const ProjLayout& l, int n_graphs) { return l.o_scratch
 #define PJ_MOST_BYTES ((size_t)3 << 29)
 static int proj_graphs_at_once(int n_graphs, int64_t N, int64_t M, int knn, bool hubs, size_t most) {
     const size_t all = proj_layout(1, N, M, knn, hubs).per_graph * n_graphs;
-    int64_t calls = all / most < (size_t)n_graphs ? (int64_t)(all / most) + 1 : n_graphs;
+    int64_t calls = all <= most ? 1 : (int64_t)((all - 1) / most) + 1;
+    if (calls > n_graphs) calls = n_graphs;
     while (true) {
         const int64_t g = (n_graphs + calls - 1) / calls;
         if (g == 1 || proj_bytes(proj_layout((int)g, N, M, knn, hubs), (int)g) <= most) return (int)g;

@@ -350,6 +350,22 @@ def test_projection_in_any_amount_of_memory(n, M, knn, hubs, per_list, others):
     assert lib.ra_project_ws(Ld.data_ptr(), n, N, M, knn, deg, piece.data_ptr(), least - 1, st, adj.data_ptr(), ent.data_ptr()) == 2
 
 
+@pytest.mark.parametrize("n,N,M", [(4, 600, 600), (2, 300, 300), (7, 900, 40)])
+def test_projection_of_a_small_batch_is_one_group(n, N, M):
+    """A workspace of as much as is asked for takes all graphs at once: the last one's part of it is written too."""
+    lib, deg, knn = ra.lib(), 32, 24
+    L = torch.randint(0, N, (n, M, knn), dtype=torch.int32, device=DEV)
+    one, full = (lib.ra_project_scratch_bytes(k, N, M, deg, knn) for k in (1, n))
+    assert full == n * one
+    piece = torch.full((full,), 77, dtype=torch.uint8, device=DEV)
+    adj, ent = torch.empty((n, N, deg), dtype=torch.int32, device=DEV), torch.empty(n, dtype=torch.int32, device=DEV)
+    assert lib.ra_project_ws(L.data_ptr(), n, N, M, knn, deg, piece.data_ptr(), full, torch.cuda.current_stream().cuda_stream,
+                             adj.data_ptr(), ent.data_ptr()) == 0
+    parts = piece.view(n, one)
+    assert all(bool((parts[g] != 77).any()) for g in range(n))
+    assert torch.equal(adj[n - 1:], ra.ra_project(L[n - 1:].contiguous(), N, deg)[0])
+
+
 def test_build_argument_errors():
     w = synth.make_integer_case(1, N=64, M=16, d=128)
     Kd, Qd = w.K.to(DEV), w.Q_prefill.to(DEV)
