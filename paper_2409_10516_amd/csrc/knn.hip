@@ -598,9 +598,11 @@ ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, in
         c.resume = nullptr;
         rc = knn_launch(c, dt);
         if (rc != RA_OK) return rc;
-        // what gives up in the filter goes on here up to the next place where it may pay again, then to the end
+        // What gives up in the filter goes on here up to an eighth of the stream, where it is tried again, then to the end. (With a
+        // trial after a thirty-second too, which only float32 streams of a multiple of 8192 keys had, 4 heads of the mixture law with
+        // 8192 queries: 64K keys 3.50 ms, without 3.25, 128K 5.01 and 4.83.)
         int64_t from = first;
-        for (int more : {32, 8, 1}) {
+        for (int more : {8, 1}) {
             const int64_t next = more == 1 ? N : first + (N / more - first + KN_FILTER_SEGMENT - 1) / KN_FILTER_SEGMENT * KN_FILTER_SEGMENT;
             if (more > 1 && (N / more < 2 * from || next >= N)) continue;
             rc = ra_launch_knn_filter(K, Q, dt, workspace, graphs, g0, c.n_graphs, n_q, n_kv, N, M, knn, first, from, maxabs, ws,
