@@ -348,12 +348,18 @@ ra_status ra_index_configure(ra_index* idx, int what, int64_t value);
  *                           stream through 8-bit products that rule keys out: RA_TEST_KNN_AUTO
  *                           (default: chosen by the sizes), RA_TEST_KNN_LDS (never),
  *                           RA_TEST_KNN_FILTER (from the 129th key on). Same lists either way.
+ *   RA_TEST_KNN_RESUME      (idx = NULL; process-wide) where the 8-bit products gave queries up: device pointer to
+ *                           RA_TEST_KNN_RESUME_INTS int32, to which each of their launches from now on adds, while there is
+ *                           room, a stream position per graph, workgroup of queries and wavefront (2^31 - 1: it came to
+ *                           the end); 0: no longer.
  *   RA_TEST_HELPERS_SILENT  (per handle) 1: the helper and seed workgroups of ra_decode_step are
  *                           launched but write nothing, so every head's bounded wait runs out and
  *                           the fall-back is taken; 0: normal. Synchronises the device and clears
  *                           the hand-over areas like RA_CFG_HELPERS. */
 #define RA_TEST_KNN_SELECTION 100
 #define RA_TEST_HELPERS_SILENT 101
+#define RA_TEST_KNN_RESUME 102
+#define RA_TEST_KNN_RESUME_INTS 65536
 #define RA_TEST_KNN_AUTO 0
 #define RA_TEST_KNN_FILTER 1
 #define RA_TEST_KNN_LDS 2

@@ -21,7 +21,8 @@ RA_F32, RA_BF16 = 0, 1
 RA_CFG_HELPERS, RA_CFG_HELPER_SPIN, RA_CFG_SEEDS, RA_CFG_SEED_SHARES = 0, 1, 2, 3
 RA_HELPERS_OFF, RA_HELPERS_ON = 0, 1
 # test-only settings (ra_test_configure)
-RA_TEST_KNN_SELECTION, RA_TEST_HELPERS_SILENT = 100, 101
+RA_TEST_KNN_SELECTION, RA_TEST_HELPERS_SILENT, RA_TEST_KNN_RESUME = 100, 101, 102
+RA_TEST_KNN_RESUME_INTS = 65536
 RA_TEST_KNN_AUTO, RA_TEST_KNN_FILTER, RA_TEST_KNN_LDS = 0, 1, 2
 BUILD_POOLED_BYTES = 256 << 20      # largest scratch memory of a build that comes from torch's allocator
 STATUS = {0: "RA_OK", 1: "RA_EINVAL", 2: "RA_ESHAPE", 3: "RA_EDTYPE", 4: "RA_ENOMEM",

@@ -223,6 +223,9 @@ extern "C" ra_status ra_test_configure(ra_index* ix, int what, int64_t value) {
                 RA_FAIL(RA_EINVAL, "knn selection %lld", (long long)value);
             ra_knn_set_selection_override((int)value);
             return RA_OK;
+        case RA_TEST_KNN_RESUME:
+            ra_knn_set_resume_copy(reinterpret_cast<int*>((uintptr_t)value));
+            return RA_OK;
         case RA_TEST_HELPERS_SILENT:
             if (!ix) RA_FAIL(RA_EINVAL, "index handle is NULL");
             if (value != 0 && value != 1) RA_FAIL(RA_EINVAL, "silent helpers %lld", (long long)value);

@@ -160,6 +160,7 @@ ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const 
                                const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
                                const int** resume, int* resume_queries, int* resume_blocks);
 void ra_knn_set_selection_override(int v);      // RA_TEST_KNN_AUTO / _FILTER / _LDS
+void ra_knn_set_resume_copy(int* to);           // RA_TEST_KNN_RESUME
 size_t ra_knn_workspace_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int knn, bool plain);
 int64_t ra_sort_padded(int64_t N);                 // the power of two (at least 2) ra_launch_sort wants
 ra_status ra_launch_sort(void* keys, size_t stride, int n_arrays, int64_t N_pad, const int32_t* counts,

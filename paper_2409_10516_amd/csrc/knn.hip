@@ -512,6 +512,20 @@ static ra_status knn_launch_as(const KnnCall& c) {
 // RA_TEST_KNN_SELECTION (ra_test_configure): whether the 8-bit products take the rest of the stream
 static int g_knn_selection_override = RA_TEST_KNN_AUTO;
 void ra_knn_set_selection_override(int v) { g_knn_selection_override = v; }
+// RA_TEST_KNN_RESUME: where to, and how much is there
+static int* g_knn_resume_copy = nullptr;
+static size_t g_knn_resume_copied = 0;
+void ra_knn_set_resume_copy(int* to) {
+    g_knn_resume_copy = to;
+    g_knn_resume_copied = 0;
+}
+static ra_status knn_copy_resume(const KnnCall& c) {
+    const size_t n = (size_t)c.n_graphs * c.resume_blocks;
+    if (!g_knn_resume_copy || g_knn_resume_copied + n > RA_TEST_KNN_RESUME_INTS) return RA_OK;
+    RA_HIP(hipMemcpyAsync(g_knn_resume_copy + g_knn_resume_copied, c.resume, n * sizeof(int), hipMemcpyDeviceToDevice, c.st));
+    g_knn_resume_copied += n;
+    return RA_OK;
+}
 
 // bf16: 8 wavefronts per workgroup (two per SIMD: registers). fp32 operands take twice the registers: 4 wavefronts.
 template <bool DIRECT>
@@ -607,6 +621,7 @@ ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, in
             if (more > 1 && (N / more < 2 * from || next >= N)) continue;
             rc = ra_launch_knn_filter(K, Q, dt, workspace, graphs, g0, c.n_graphs, n_q, n_kv, N, M, knn, first, from, maxabs, ws,
                                       st, L, &c.resume, &c.resume_queries, &c.resume_blocks);
+            if (rc == RA_OK) rc = knn_copy_resume(c);
             if (rc != RA_OK) return rc;
             c.n_stream = from = next;
             rc = knn_launch(c, dt);

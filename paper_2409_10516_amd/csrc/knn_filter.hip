@@ -384,11 +384,15 @@ __global__ __launch_bounds__(256) void kf_queries_kernel(const void* __restrict_
                                                          const uint32_t* __restrict__ k_top, int g0, int n_q,
                                                          int n_kv, int64_t M, int knn,
                                                          const float* __restrict__ scores, uint2* __restrict__ Q8,
-                                                         float4* __restrict__ qinfo) {
+                                                         float4* __restrict__ qinfo, int* __restrict__ resume, int waves,
+                                                         int wave_queries) {
     __shared__ __align__(16) unsigned char s_row[16][RA_D];
     const int gl = blockIdx.y, graph = g0 + gl, seq = graph / n_q, h = graph % n_q, kvh = h / (n_q / n_kv);
     const int tid = threadIdx.x, l16 = tid & 15;
     const size_t kv = (size_t)seq * n_kv + kvh;
+    // where the wavefronts of knn_filter_kernel begin: at the front, or, those without a query, at the end
+    for (int i = blockIdx.x * 256 + tid; i < waves; i += gridDim.x * 256)
+        resume[(size_t)gl * waves + i] = (int64_t)i * wave_queries < M ? 0 : 0x7fffffff;
     float sc[8], m[8], mm = 0.f;
     uint32_t mx[8];
     int at[8];
@@ -500,17 +504,14 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     int32_t* L_g = L + (size_t)graph * M * knn;
 
     // the stream position this wavefront goes on from: `from`, or where it gave up behind that (knn.hip has
-    // multiplied what lies between); nothing is left where it came to the end in a launch before
+    // multiplied what lies between); nothing is left where it came to the end in a launch before, or has no query
     int* my_resume = resume + ((size_t)gl * gridDim.x + blockIdx.x) * KF_WAVES + wv;
-    int begin = first;
-    if (from > first) {
-        begin = __builtin_amdgcn_readfirstlane(*my_resume);
-        if (begin < from) begin = from;
-        if (begin >= N) begin = -1;
-    }
+    int begin = __builtin_amdgcn_readfirstlane(*my_resume);
+    if (begin < from) begin = from;
+    if (begin >= N) begin = -1;
     if (tid == 0) s_kept = s_seen = 0;
     __syncthreads();
-    if (begin < 0) return;                             // (there is no barrier behind this one)
+    if (begin < 0) return;                             // (a barrier waits for no wavefront that has ended)
     i32x4 b[NQ][4];
 #pragma unroll
     for (int s = 0; s < NQ; ++s) {
@@ -529,6 +530,12 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
         // and with it the operands on their way to LDS, which it does not count)
         asm volatile("; queries loaded" ::"v"(b[s][0]), "v"(b[s][1]), "v"(b[s][2]), "v"(b[s][3]));
     }
+    // (A column without a query keeps no key: its threshold is infinity. With the last query's and no way to raise it, such columns,
+    // and wavefronts without a query, kept ever more keys and made their workgroup give up: 4 heads of the mixture law, 256K
+    // keys x 65537 queries 20.7 ms, now 19.7, 1M x 16385 29.7 and 29.2, float32 64K x 8193 4.25 and 3.91.)
+    if (q0 + 32 * NQ > M)
+        for (int s = 0; s < NQ; ++s)
+            if (half == 1 && q0 + 32 * s + col >= M) s_query[wv][s][1][col].w = INFINITY;
     kf_wave_sync();
     int kept = 0;                                      // keys that were not ruled out
 
@@ -655,7 +662,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     };
 
     // ---- the stream. Every wavefront copies its operands to a ring of its own in LDS, eight of them ahead, straight
-    //      from memory (no register holds them on the way), and waits for nobody. 128K keys x 32 heads, when it was made: 33 ms;
+    //      from memory (no register holds them on the way), and waits for the others only where they meet. 128K keys x 32 heads, when it was made: 33 ms;
     //      with stages of 128 keys that the workgroup shares in LDS 34 ms, loads to registers instead of the ring 42 ms.
     //      1M keys x 4 heads, where wavefronts have keys to score at different times: 36, 41 and 35 ms. Before
     //      (stages, whole products, no mean taken off): 51 and 41 ms.
@@ -753,7 +760,10 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     auto open_segment = [&]() __attribute__((always_inline)) -> bool {
         // The wavefronts meet every 2048 keys, so that they stay in reach of each other's lines in the caches (whole
         // calls, 1M keys x 4 heads of 64K queries: 43.4 -> 40.6 ms, of 16K queries, one set per wavefront: 30.1 -> 17.0; a meeting
-        // every 512 keys: 43.3 and 17.9). A barrier waits for no wavefront that has ended.
+        // every 512 keys: 43.3 and 17.9). A barrier waits for no wavefront that has ended. One that comes out of run() because nothing of a
+        // segment can reach a threshold opens that segment again, and where that is a meeting, takes its part in the next one, too:
+        // with others it is then a meeting ahead. (Opening it once: 128K keys x 32 heads 39.1 -> 39.8 ms, more registers in
+        // memory; 1M keys x 4 heads of 64K queries 39.1 -> 39.4, of 16385 29.1 -> 28.8.)
         if ((blk / KF_SEG_BLOCKS) % KF_MEET == 0) __builtin_amdgcn_s_barrier();
         const float4 g0 = seg_g[2 * (blk / KF_SEG_BLOCKS)], g1 = seg_g[2 * (blk / KF_SEG_BLOCKS) + 1];
         sg_x = g0.x; sg_e = g0.y; sg_b_max = g0.z; sg_b_min = g0.w; sg_x1 = g1.x; sg_x2 = g1.y; sg_x3 = g1.z;
@@ -944,7 +954,7 @@ ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const 
                                k_top);                                                                          \
             hipLaunchKernelGGL(kf_queries_kernel<DTV>, qgrid, dim3(256), 0, st, Q, mq, maxabs, place, k_top,    \
                                g0, n_q, n_kv, M, knn, scores, reinterpret_cast<uint2*>(ws + l.q8),              \
-                               reinterpret_cast<float4*>(ws + l.info));                                         \
+                               reinterpret_cast<float4*>(ws + l.info), res, (int)grid.x * KF_WAVES, 32 * NQ);   \
         }                                                                                                       \
         if (NQ == 4) KF_GO_N(DTV, 4); else if (NQ == 2) KF_GO_N(DTV, 2); else KF_GO_N(DTV, 1);                  \
     } while (0)

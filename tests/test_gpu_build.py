@@ -589,6 +589,62 @@ def test_knn_filter_gives_up(dtype, knn, N, ruled_out):
     assert np.array_equal(got, ref[np.arange(M) % 10])
 
 
+END = 0x7fffffff                                     # of a stream the 8-bit products came through
+
+
+def _half_streams(N, M, first_half, t):
+    """K [N][128] and Q [M][128] of whole numbers that are exact in 8 bits, and t by key. Most queries look at the second
+    half of the dimensions, which makes the stream order (place); those of `first_half` look at the first half, where
+    the key of place p scores t(p) sum |u|: equal ones tie, and two apart the bound tells them apart."""
+    rng = np.random.default_rng(32)
+    u = rng.integers(1, 128, 128) * rng.choice([-1, 1], 128)
+    u[[0, 64]] = 127
+    place = rng.permutation(N)                       # in the stream, up to the order of those that tie
+    level = np.where(place < 128, place // 16, 8 + (place - 128) * 190 // max(1, N - 128))
+    K = np.concatenate([np.repeat(t(place)[:, None], 64, 1), np.repeat(100 - level[:, None], 64, 1)], 1) * np.sign(u)
+    K[place == 5] = 127 * np.sign(u)
+    Q = np.where(first_half[:, None] == (np.arange(128) < 64)[None, :], u[None, :], 0)
+    return K, Q, place
+
+
+def _knn_with_resume(K, Q, dtype, heads, knn):
+    """Lists [heads][M][knn] with the 8-bit products from the 129th key on, and where each of their launches gave up:
+    [launches][heads][wavefronts]."""
+    from paper_2409_10516_amd import binding as B
+    Kd = torch.from_numpy(K).to(dtype).to(DEV)[None, None]
+    Qd = torch.from_numpy(Q).to(dtype).to(DEV).expand(1, heads, *Q.shape).contiguous()
+    stops = torch.full((B.RA_TEST_KNN_RESUME_INTS,), -1, dtype=torch.int32, device=DEV)
+    try:
+        ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_FILTER)
+        ra.ra_test_configure(B.RA_TEST_KNN_RESUME, stops.data_ptr())
+        got = ra.ra_knn(Kd, Qd, knn).cpu().numpy()[0]
+    finally:
+        ra.ra_test_configure(B.RA_TEST_KNN_RESUME, 0)
+        ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_AUTO)
+    stops = stops.cpu().numpy()
+    stops = stops[stops != -1]
+    # sets of 32 queries per wavefront: as many as leave 2048 wavefronts in the launch
+    M = Q.shape[0]
+    sets = next(n for n in (4, 2, 1) if n == 1 or -(-M // (256 * n)) * 8 * heads >= 2048)
+    waves = -(-M // (256 * sets)) * 8
+    return got, stops.reshape(-1, heads, waves), np.arange(waves) * 32 * sets < M
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("M,heads", [(300, 1), (257, 3), (33, 2), (600, 128), (300, 256)])
+def test_knn_filter_places_without_a_query(dtype, M, heads):
+    """What a workgroup has beyond its last query (whole wavefronts, sets, columns of a set) keeps no keys and makes nobody
+    give up: the last query, which would stand for all of them, finds its 16 keys in the first segment and rules out the rest,
+    all of which are above its threshold at the start."""
+    N, knn = 4200, 16
+    first_half = np.arange(M) == M - 1
+    K, Q, place = _half_streams(N, M, first_half, lambda p: np.where(p < 128, 30, np.where(p < 160, 40, 34)))
+    got, stops, live = _knn_with_resume(K, Q, dtype, heads, knn)
+    ref = OM.knn_lists(Q[[0, M - 1]], K, knn)[0]
+    assert np.array_equal(got, np.broadcast_to(ref[first_half.astype(int)], (heads, M, knn)))
+    assert (stops == END).all()
+
+
 # powers of two that queries and keys are multiplied by, down to where scores leave the normal range and up
 # to where squares do
 _SCALES = [(0, 0), (-84, 0), (0, -84), (-45, -45), (-59, -59), (-118, 0), (0, -110), (60, 40), (62, 62), (-126, 0),
