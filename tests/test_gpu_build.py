@@ -557,38 +557,6 @@ def test_knn_through_8bit_products(dtype, N, M, knn):
     knn_equivalent(L[B.RA_TEST_KNN_FILTER][1, 1][:40], OM.knn_lists(Qn, Kn, knn)[0], Qn, Kn)
 
 
-@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("knn", [32, 64])
-@pytest.mark.parametrize("N,ruled_out", [(384, 0), (385, 0), (511, 0), (900, 0), (1152, 256), (1153, 256), (2600, 256)])
-def test_knn_filter_gives_up(dtype, knn, N, ruled_out):
-    """Streams of which a workgroup cannot rule out an eighth: it stops after two stages of 128 keys, or, with
-    the first 256 keys ruled out, after eight, and the exact products go on from there. That they stop is
-    certain: for the queries that look at the first half of the dimensions (some in every set of 32) each
-    key past those 256 ties with the first part of the stream or beats it, and a key that reaches a
-    threshold may not be ruled out; the 256 score sum |u| below it and are exact in 8 bits. Nothing,
-    one key or many are left then, and the last keys of the stream are the best of all. Integer inputs:
-    the oracle's lists."""
-    from paper_2409_10516_amd import binding as B
-    rng = np.random.default_rng(32)
-    M = 300
-    u = rng.integers(1, 128, 128) * rng.choice([-1, 1], 128)
-    u[[0, 64]] = 127
-    place = rng.permutation(N)                       # in the stream
-    t = np.where(place < 128, 50, np.where(place < 128 + ruled_out, 49, np.where(place < N - 40, 50, 51 + place % 4)))
-    K = np.concatenate([np.repeat(t[:, None], 64, 1), np.repeat(100 - place[:, None] // 16, 64, 1)], 1) * np.sign(u)
-    K[place == 5] = 127 * np.sign(u)
-    first_half = np.arange(M) % 10 == 9              # (few: the mean query goes by the other half)
-    Q = np.where(first_half[:, None] == (np.arange(128) < 64)[None, :], u[None, :], 0)
-    try:
-        ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_FILTER)
-        got = ra.ra_knn(torch.from_numpy(K).to(dtype).to(DEV)[None, None],
-                        torch.from_numpy(Q).to(dtype).to(DEV)[None, None], knn).cpu().numpy()[0, 0]
-    finally:
-        ra.ra_test_configure(B.RA_TEST_KNN_SELECTION, B.RA_TEST_KNN_AUTO)
-    ref = OM.knn_lists(Q[:10], K, knn)[0]
-    assert np.array_equal(got, ref[np.arange(M) % 10])
-
-
 END = 0x7fffffff                                     # of a stream the 8-bit products came through
 
 
@@ -628,6 +596,41 @@ def _knn_with_resume(K, Q, dtype, heads, knn):
     sets = next(n for n in (4, 2, 1) if n == 1 or -(-M // (256 * n)) * 8 * heads >= 2048)
     waves = -(-M // (256 * sets)) * 8
     return got, stops.reshape(-1, heads, waves), np.arange(waves) * 32 * sets < M
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("N,knn,M,heads,form", [
+    (2600, 32, 300, 1, "ties"), (2639, 64, 257, 2, "ties"),            # tried again at 640, the earliest place it can stop at
+    (18000, 32, 300, 1, "ties"), (17999, 64, 300, 1, "ties"),          # ... at 2688, behind the last place it can
+    (18000, 32, 300, 1, "early"), (18001, 64, 90, 1, "early"),         # ... and comes to the end then
+    (18000, 64, 300, 1, "late"),                                       # keeps nothing for four segments
+    (5000, 32, 600, 128, "ties"), (5000, 33, 300, 256, "ties"),        # two and four sets of queries per wavefront
+])
+def test_knn_filter_gives_up(dtype, knn, N, M, heads, form):
+    """Streams that the bound cannot rule out much of: the workgroups give up, the exact products go on to an eighth of the
+    stream, where the 8-bit products are tried again, and from where they give up again to the end. That they give up is
+    certain: for the queries that look at the first half of the dimensions (one in every set of 32) each key ties with
+    the first part of the stream, and a key that reaches a threshold may not be ruled out; nor can it be before
+    wavefronts with half of a workgroup's sets have come through a segment of 512 keys, or one alone through as many as
+    make up for the others. Ties to the end, up to the 2500th key ("early") or from the 2176th on ("late"); the last keys of
+    the stream are the best of all. Whole numbers: the oracle's lists."""
+    first_half = (np.arange(M) % 32 == 31) | (np.arange(M) == M - 1)
+    low = {"ties": (0, 0), "early": (2500, N), "late": (128, 2176)}[form]
+    K, Q, place = _half_streams(N, M, first_half, lambda p: np.where(
+        p >= N - 40, 51 + p % 4, np.where((p >= low[0]) & (p < low[1]), 40, 50)))
+    got, stops, live = _knn_with_resume(K, Q, dtype, heads, knn)
+    ref = OM.knn_lists(Q[[0, M - 1]], K, knn)[0]
+    assert np.array_equal(got, np.broadcast_to(ref[first_half.astype(int)], (heads, M, knn)))
+    assert stops.shape[0] == 2 and (stops[:, :, ~live] == END).all()
+    a, b = stops[0][:, live], stops[1][:, live]
+    again = 128 + -(-(N // 8 - 128) // 512) * 512
+    earliest, most = (2176, 4736) if form == "late" else (640, 2176)
+    assert (a % 512 == 128).all() and a.min() >= earliest and a.max() <= most
+    assert N < 8192 or again == 2688
+    if form == "early":
+        assert (b == END).all()
+    else:
+        assert (b >= np.maximum(a, again) + 512).all() and (N < most + 2560 or b.max() <= most + 2048 + 512)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
