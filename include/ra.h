@@ -100,7 +100,7 @@ ra_status ra_build_index(const void* K, const void* Q_prefill, ra_dtype dt,
                          int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
                          int deg, int knn, void* stream, ra_index** out);
 
-/* The same, and ra_project, with scratch memory of the caller's (device, 256-byte aligned, theirs again when the call
+/* The same, and ra_project, with scratch memory of the caller's (device, 256-byte aligned or it is refused, theirs again when the call
  * returns): what ra_build_workspace_bytes and ra_project_scratch_bytes say, which is 0 for sizes that
  * are refused. The graphs are projected in groups of up to 1.5 GiB of it. With workspace NULL the call allocates and frees it
  * itself (freeing a piece of 150 MB or more is a quarter of a millisecond, one of several gigabytes can be many). With less, or on a

@@ -367,6 +367,13 @@ extern "C" ra_status ra_knn(const void* K, const void* Q, ra_dtype dt, int n_seq
     return RA_OK;
 }
 
+// (parts of it are read 16 bytes at a time and copied straight to LDS)
+static ra_status check_workspace(const void* workspace) {
+    if (reinterpret_cast<uintptr_t>(workspace) % 256)
+        RA_FAIL(RA_EINVAL, "the workspace is not 256-byte aligned");
+    return RA_OK;
+}
+
 extern "C" size_t ra_project_scratch_bytes(int n_graphs, int64_t N, int64_t M, int deg, int knn) {
     if (n_graphs < 1 || check_build_args(N, M, deg, knn, true) != RA_OK) return 0;
     return ra_project_workspace_bytes(n_graphs, N, M, knn, false);
@@ -381,6 +388,7 @@ extern "C" ra_status ra_project_ws(const int32_t* L, int n_graphs, int64_t N, in
     const size_t least = ra_project_workspace_bytes(n_graphs, N, M, knn, true);
     if (workspace && workspace_bytes < least)
         RA_FAIL(RA_ESHAPE, "workspace of %zu bytes, the projection needs %zu", workspace_bytes, least);
+    RA_TRY(check_workspace(workspace));
     // (the scratch memory of a few graphs at a time says nothing about the whole any more)
     int device = 0;
     size_t total = 0;
@@ -437,6 +445,7 @@ extern "C" ra_status ra_build_index_ws(const void* K, const void* Q, ra_dtype dt
     const size_t most = build_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false, &l_bytes);
     if (workspace && workspace_bytes < least)
         RA_FAIL(RA_ESHAPE, "workspace of %zu bytes, the build needs %zu", workspace_bytes, least);
+    RA_TRY(check_workspace(workspace));
     ra_index* ix = nullptr;
     RA_TRY(new_handle(n_seq, n_q, n_kv, N, deg, &ix));
     int32_t* L = reinterpret_cast<int32_t*>(workspace);

@@ -64,6 +64,19 @@ def test_build_and_project_validation():
     assert L.ra_project(None, 1, 100, 10, 8, 8, None, _fake(), _fake()) == 1
 
 
+@pytest.mark.parametrize("off", [1, 16, 128])
+def test_workspace_that_is_not_aligned_is_refused(off):
+    L = ra.lib()
+    need = L.ra_project_scratch_bytes(1, 100, 10, 8, 8)
+    ws = C.c_void_p(0x10000 + off)
+    assert L.ra_project_ws(_fake(), 1, 100, 10, 8, 8, ws, need, None, _fake(), _fake()) == 1
+    assert "aligned" in L.ra_last_error().decode()
+    h = C.c_void_p()
+    need = L.ra_build_workspace_bytes(1, 1, 4, 2, 100, 10, 128, 8, 8)
+    assert L.ra_build_index_ws(_fake(), _fake(), 1, 1, 4, 2, 100, 10, 128, 8, 8, ws, need, None, C.byref(h)) == 1
+    assert "aligned" in L.ra_last_error().decode() and not h.value
+
+
 def test_scratch_memory_of_a_batch_is_bounded():
     """The projection takes its graphs in groups: 512 graphs need no more than 1.5 GiB at a time, one that needs more by itself
     what it needs, and a build of a batch its lists and the larger of its two stages."""
