@@ -191,10 +191,14 @@ ra_status ra_launch_attend(const void* q, const void* K, const void* V, ra_dtype
     const int64_t records = (int64_t)(nS + nG) * n_q * n_seq;
     if (records > AT_TICKET_RECORDS) tickets = nullptr;
     // Workgroups of a long static range that take its chunks in turn read side by side, as one front per head, which the
-    // memory serves better than a stream of its own for each (bf16, 8 KV heads, layers in turn, us per layer: 60001 tokens 54.6
-    // -> 53.3, 100003 81.9 -> 78.2, 200000 141.3 -> 137.9, 4 sequences of 30011 92.5 -> 90.6), unless the heads lie a multiple of 1 MB
-    // apart, where their fronts meet in the same channels (65536 56.2 -> 57.3, 131072 96.5 -> 98.0, 16 of 32768 337 -> 342).
-    const int front = sub > 1 && ((size_t)N * RA_D * (dt == RA_BF16 ? 2 : 4)) % ((size_t)1 << 20) != 0;
+    // memory serves better than a stream of its own for each, unless the heads lie a multiple of 1 MB apart, where their fronts meet
+    // in the same channels; one head by itself meets none. Layers in turn, us per layer, streams of their own -> fronts. bf16, 8 KV
+    // heads: 60001 tokens 54.6 -> 53.0, 100003 79.0 -> 75.3, 200000 140.7 -> 137.5; near a multiple, 65537 56.6 -> 56.6, 66048
+    // 59.4 -> 58.2, 131200 97.8 -> 98.2; at one, 65536 54.2 -> 53.8, 131072 96.4 -> 96.7, 8 heads without groups 87.4 -> 89.0, 16
+    // sequences of 32768 339 -> 342. 16 sequences of other lengths go either way by 3 %, with where their tensors lie. One
+    // head: 131072 38.7 -> 38.3, 1M 105.6 -> 103.2, float32 262144 67.6 -> 65.5.
+    const bool apart = n_seq * n_kv == 1 || ((size_t)N * RA_D * (dt == RA_BF16 ? 2 : 4)) % ((size_t)1 << 20) != 0;
+    const int front = sub > 1 && apart;
     const AttendOut o{tickets, out, lse, o_omega, lse_omega, o_w, lse_w};
     const int g = sub > 1 ? long_heads(dt, G) : short_heads(dt, G, records);
     const dim3 grid(nS + g * nG, n_q / g, n_seq);

@@ -163,16 +163,18 @@ def test_full_attention_long_context_uses_few_records():
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n_kv", [2, 1])
 @pytest.mark.parametrize("N", [4097, 6144, 8192, 8255, 12289])
-def test_full_attention_chunks_in_turn_or_in_a_row(dtype, N):
-    """Workgroups take a head's chunks in turn, or, where the heads lie a multiple of 1 MB apart (every N that 4096, in
-    float32 2048, divides), in a row; last chunks of one row, of 63 and whole, more places than chunks. Every row counts:
+def test_full_attention_chunks_in_turn_or_in_a_row(dtype, N, n_kv):
+    """Workgroups take a head's chunks in turn, or, where there are several heads and they lie a multiple of 1 MB apart (every N
+    that 4096, in float32 2048, divides), in a row; last chunks of one row, of 63 and whole, more places than chunks. Every row counts:
     its weight is checked through the values."""
-    w = synth.make_llama_layer(N, N=N, M=8, T=1, n_q=4, n_kv=2, dtype=dtype)
+    w = synth.make_llama_layer(N, N=N, M=8, T=1, n_q=4, n_kv=n_kv, dtype=dtype)
     out, lse = ra.ra_full_attention(w.q_decode[0].to(DEV), w.K.to(DEV), w.V.to(DEV))
     out, lse = out.cpu().numpy(), lse.cpu().numpy()
     for h in (0, 3):
-        ro, rl = OA.full_attention(to_np(w.q_decode[0, 0, h]), to_np(w.K[0, h // 2]), to_np(w.V[0, h // 2]))
+        kv = h * n_kv // 4
+        ro, rl = OA.full_attention(to_np(w.q_decode[0, 0, h]), to_np(w.K[0, kv]), to_np(w.V[0, kv]))
         assert out_close(out[0, h], ro, tol_for(dtype)) and lse_close(lse[0, h], rl, tol_for(dtype))
 
 
