@@ -53,6 +53,7 @@
 #define PJ_TOUCH_B 1024
 #define PJ_TOUCH_C 2048
 #define PJ_HUBS 128               // most keys of a graph whose lists are kept as a bitmap
+#define PJ_FEW_HUBS 48            // ... and fewest
 #define PJ_SLAB_WORDS 64          // 32-list words of the bitmaps that a workgroup of the pair kernel takes, at least
 #define PJ_MOST_SLABS 16
 #define PJ_PAIR_T 192             // threads of the pair kernel
@@ -413,8 +414,9 @@ __device__ __forceinline__ int hash_limit(int H, int knn) {
     return lim;
 }
 // Hubs: the first positions of a graph of at most PJ_LDS_TAB populated keys, those in more than a 64th of the lists (and
-// too many for the wavefront kernels), up to PJ_HUBS of them. Fewer than 65 are not worth it: a hub's
-// row is then never settled by the others alone (pj_rows_kernel).
+// too many for the wavefront kernels), up to PJ_HUBS of them. Fewer than 48 are not worth it, with the other keys' counts to
+// write down for them: 8 graphs of 100000 lists of 32 with 8, 16, 32, 48 and 64 such keys, without -> with the bitmaps 2.94 ->
+// 2.96, 2.64 -> 2.64, 2.19 -> 2.21, 1.83 -> 1.63, 1.78 -> 1.63 ms.
 // pi, pos and popularity by position of the populated keys; the entry point; the number of hubs
 __global__ __launch_bounds__(256) void pj_pi_kernel(char* ws, ProjLayout l, int64_t M, int knn,
                                                     int32_t* __restrict__ entry) {
@@ -431,7 +433,7 @@ __global__ __launch_bounds__(256) void pj_pi_kernel(char* ws, ProjLayout l, int6
         w.pos[id] = t;
         const int pop = (int)(M - (int64_t)(k >> 32)), next = t + 1 < H ? (int)(M - (int64_t)(w.keys[t + 1] >> 32)) : 0;
         w.ppop[t] = pop;
-        if (l.n_slabs && H <= PJ_LDS_TAB && H - (t + 1) <= l.with_hubs && t >= 64 && t < PJ_HUBS && pop > hub_floor &&
+        if (l.n_slabs && H <= PJ_LDS_TAB && H - (t + 1) <= l.with_hubs && t >= PJ_FEW_HUBS - 1 && t < PJ_HUBS && pop > hub_floor &&
             (t + 1 == PJ_HUBS || next <= hub_floor))
             w.H[2] = t + 1;
 #pragma unroll

@@ -451,7 +451,8 @@ def _hub_lists(rng, M, knn, hubs, per_list, others):
 
 
 @pytest.mark.parametrize("M,knn,hubs,per_list,others,form", [
-    (5000, 24, 64, 14, 400, ""), (5000, 24, 65, 14, 400, ""),          # one too few, just enough for bitmaps
+    (5000, 24, 47, 14, 400, ""), (5000, 24, 48, 14, 400, ""),          # one too few, just enough for bitmaps
+    (5000, 24, 64, 14, 400, ""), (5000, 24, 65, 14, 400, ""),
     (5003, 21, 128, 14, 301, "none"), (5001, 24, 129, 14, 400, ""),    # as many as there are bitmaps, one more; places without a key
     (9000, 32, 100, 14, 924, "pad"), (9000, 33, 100, 20, 925, ""),     # 1024 and 1025 populated keys
     (5000, 24, 128, 14, 1200, ""),                                     # more other keys than their counts have room
