@@ -100,12 +100,18 @@ ra_status ra_build_index(const void* K, const void* Q_prefill, ra_dtype dt,
                          int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
                          int deg, int knn, void* stream, ra_index** out);
 
-/* The same, and ra_project, with scratch memory of the caller's (device, 256-byte aligned or it is refused, theirs again when the call
- * returns): what ra_build_workspace_bytes and ra_project_scratch_bytes say, which is 0 for sizes that
- * are refused. The graphs are projected in groups of up to 1.5 GiB of it. With workspace NULL the call allocates and frees it
- * itself (freeing a piece of 150 MB or more is a quarter of a millisecond, one of several gigabytes can be many). With less, or on a
- * device that has no more, it goes on with what there is: without the 8-bit copies of ra_knn, with fewer graphs at a
- * time; with less than the lists, the stream order of ra_knn and one graph take it is refused. */
+/* The same, ra_knn and ra_project with scratch memory of the caller's (device, 256-byte aligned or it is refused, theirs
+ * again when the call returns): what ra_build_workspace_bytes, ra_knn_scratch_bytes and ra_project_scratch_bytes say, which
+ * is 0 for sizes that are refused. The graphs are projected in groups of up to 1.5 GiB of it. With workspace NULL the call
+ * allocates and frees it itself: freeing a piece of 150 MB or more is a quarter of a millisecond, and where calls follow each other
+ * so fast that more than some 100 GB a second are freed and allocated again, the driver holds allocations up by tens of
+ * milliseconds, at times by seconds (a build of 7.4 ms with 0.7 GB took 32 on average). With less, or on a device that has no more, a
+ * call goes on with what there is: without the 8-bit copies of ra_knn, with fewer graphs at a time; with less than the
+ * lists, the stream order of ra_knn and one graph take it is refused. */
+size_t ra_knn_scratch_bytes(ra_dtype dt, int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d, int knn);
+ra_status ra_knn_ws(const void* K, const void* Q_prefill, ra_dtype dt,
+                    int n_seq, int n_q_heads, int n_kv_heads, int64_t N, int64_t M, int d,
+                    int knn, void* workspace, size_t workspace_bytes, void* stream, int32_t* L_out);
 size_t ra_project_scratch_bytes(int n_graphs, int64_t N, int64_t M, int deg, int knn);
 ra_status ra_project_ws(const int32_t* L, int n_graphs, int64_t N, int64_t M, int knn, int deg, void* workspace,
                         size_t workspace_bytes, void* stream, int32_t* adj, int32_t* entry);

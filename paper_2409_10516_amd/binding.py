@@ -24,7 +24,8 @@ RA_HELPERS_OFF, RA_HELPERS_ON = 0, 1
 RA_TEST_KNN_SELECTION, RA_TEST_HELPERS_SILENT, RA_TEST_KNN_RESUME = 100, 101, 102
 RA_TEST_KNN_RESUME_INTS = 65536
 RA_TEST_KNN_AUTO, RA_TEST_KNN_FILTER, RA_TEST_KNN_LDS = 0, 1, 2
-BUILD_POOLED_BYTES = 256 << 20      # largest scratch memory of a build that comes from torch's allocator
+BUILD_POOLED_BYTES = 4 << 30        # largest scratch memory of a build stage that comes from torch's allocator
+RA_ENOMEM = 4
 STATUS = {0: "RA_OK", 1: "RA_EINVAL", 2: "RA_ESHAPE", 3: "RA_EDTYPE", 4: "RA_ENOMEM",
           5: "RA_EHIP", 6: "RA_EUNSUP"}
 
@@ -54,6 +55,10 @@ def lib() -> C.CDLL:
     L.ra_project.argtypes = [vp, i32, i64, i64, i32, i32, vp, vp, vp]
     L.ra_build_index.argtypes = [vp, vp, i32, i32, i32, i32, i64, i64, i32, i32, i32, vp,
                                  C.POINTER(vp)]
+    L.ra_knn_ws.argtypes = [vp, vp, i32, i32, i32, i32, i64, i64, i32, i32, vp, C.c_size_t, vp, vp]
+    L.ra_knn_ws.restype = i32
+    L.ra_knn_scratch_bytes.argtypes = [i32, i32, i32, i32, i64, i64, i32, i32]
+    L.ra_knn_scratch_bytes.restype = C.c_size_t
     L.ra_project_ws.argtypes = [vp, i32, i64, i64, i32, i32, vp, C.c_size_t, vp, vp, vp]
     L.ra_project_ws.restype = i32
     L.ra_project_scratch_bytes.argtypes = [i32, i64, i64, i32, i32]
@@ -120,6 +125,16 @@ def _check(rc: int):
         raise RaError(rc, lib().ra_last_error().decode())
 
 
+def _room(fn, *args) -> int:
+    """fn(*args) -> status, for a call that may allocate: again without the pieces that torch keeps, where the device has no
+    room (a build leaves one of up to BUILD_POOLED_BYTES)."""
+    rc = fn(*args)
+    if rc == RA_ENOMEM:
+        torch.cuda.empty_cache()
+        rc = fn(*args)
+    return rc
+
+
 def _dt(t: torch.Tensor) -> int:
     if t.dtype == torch.float32:
         return RA_F32
@@ -180,7 +195,7 @@ class Index:
 
     def configure(self, what: int, value: int) -> None:
         """ra_index_configure: RA_CFG_HELPERS / RA_CFG_HELPER_SPIN / RA_CFG_SEEDS / RA_CFG_SEED_SHARES."""
-        _check(lib().ra_index_configure(self.handle, what, value))
+        _check(_room(lib().ra_index_configure, self.handle, what, value))
 
     def test_configure(self, what: int, value: int) -> None:
         """ra_test_configure on this handle (test-only settings)."""
@@ -203,22 +218,13 @@ def ra_test_configure(what: int, value: int) -> None:
     _check(lib().ra_test_configure(None, what, value))
 
 
-def ra_knn(K, Q_prefill, knn: int, stream=None) -> torch.Tensor:
-    _dev(K, Q_prefill)
-    n_seq, n_kv, N, d = K.shape
-    _, n_q, M, _ = Q_prefill.shape
-    L = torch.empty((n_seq, n_q, M, knn), dtype=torch.int32, device=K.device)
-    _check(lib().ra_knn(_ptr(K), _ptr(Q_prefill), _dt(K), n_seq, n_q, n_kv, N, M, d, knn,
-                        _stream(stream), _ptr(L)))
-    return L
-
-
 def _with_scratch(stream, need: int, call) -> None:
     """call(workspace, its bytes, stream) -> status, for a call that returns when the stream is done. Up to
     BUILD_POOLED_BYTES of scratch memory, for a call on the current stream, come from torch's allocator, which has the
-    piece of the last call at hand: the library's own allocation and free are 0.3 of the 1.6 ms that a build for two
-    prompts of 5K tokens took with them. Of a larger call they are a smaller part, and it leaves no large piece with torch; where
-    torch finds no room, the library allocates as for those."""
+    piece of the last call at hand and gives it back where torch needs it (or torch.cuda.empty_cache() is called). With the library's
+    own allocation and free, 0.3 ms are lost in a build for two prompts of 5K tokens (1.6 ms), and builds with 0.7 GB that
+    follow each other every 7 ms wait for the driver most of the time (32 ms each: above some 100 GB a second of freed and
+    allocated memory it stops for up to seconds). Where torch finds no room, the library allocates."""
     ws = None
     if stream is None and 0 < need <= BUILD_POOLED_BYTES:
         try:
@@ -226,11 +232,22 @@ def _with_scratch(stream, need: int, call) -> None:
         except torch.cuda.OutOfMemoryError:
             pass
     rc = call(None, 0, _stream(stream)) if ws is None else call(_ptr(ws), need, _stream(None))
-    if STATUS.get(rc) == "RA_ENOMEM":      # pieces that torch keeps, such as an earlier call's, may be what is missing
+    if rc == RA_ENOMEM:      # pieces that torch keeps, such as an earlier call's, may be what is missing
         del ws
         torch.cuda.empty_cache()
         rc = call(None, 0, _stream(stream))
     _check(rc)
+
+
+def ra_knn(K, Q_prefill, knn: int, stream=None) -> torch.Tensor:
+    _dev(K, Q_prefill)
+    n_seq, n_kv, N, d = K.shape
+    _, n_q, M, _ = Q_prefill.shape
+    L = torch.empty((n_seq, n_q, M, knn), dtype=torch.int32, device=K.device)
+    args = (_dt(K), n_seq, n_q, n_kv, N, M, d, knn)
+    _with_scratch(stream, lib().ra_knn_scratch_bytes(*args),
+                  lambda ws, room, st: lib().ra_knn_ws(_ptr(K), _ptr(Q_prefill), *args, ws, room, st, _ptr(L)))
+    return L
 
 
 def ra_project(L: torch.Tensor, N: int, deg: int, stream=None):
@@ -268,7 +285,7 @@ def ra_index_import(adj: torch.Tensor, entries: torch.Tensor, n_seq: int, n_q: i
     if g != n_seq * n_q or entries.numel() != g:
         raise ValueError("adj/entries do not match n_seq * n_q graphs")
     h = C.c_void_p()
-    _check(lib().ra_index_import(_ptr(adj), _ptr(entries), n_seq, n_q, n_kv, N, deg, C.byref(h)))
+    _check(_room(lib().ra_index_import, _ptr(adj), _ptr(entries), n_seq, n_q, n_kv, N, deg, C.byref(h)))
     return Index(h.value)
 
 
@@ -304,13 +321,13 @@ def ra_search(q, idx: Index, K, sink: int, window: int, topk: int, ef: int, expa
     st = _stats_tensor(n_seq, n_q, q.device) if with_stats else None
     if k8 is None:
         _dev(q, K)
-        _check(lib().ra_search(_ptr(q), idx.handle, _ptr(K), _dt(K), K.shape[2], sink, window, topk,
-                               ef, expand, _stream(stream), _ptr(ids), _ptr(st)))
+        _check(_room(lib().ra_search, _ptr(q), idx.handle, _ptr(K), _dt(K), K.shape[2], sink, window, topk,
+                     ef, expand, _stream(stream), _ptr(ids), _ptr(st)))
     else:
         K8, scale = k8
         _dev(q, K8, scale)
-        _check(lib().ra_search_q8(_ptr(q), idx.handle, _ptr(K8), _ptr(scale), _dt(q), K8.shape[2], sink,
-                                  window, topk, ef, expand, _stream(stream), _ptr(ids), _ptr(st)))
+        _check(_room(lib().ra_search_q8, _ptr(q), idx.handle, _ptr(K8), _ptr(scale), _dt(q), K8.shape[2], sink,
+                     window, topk, ef, expand, _stream(stream), _ptr(ids), _ptr(st)))
     return ids, st
 
 
@@ -342,8 +359,8 @@ def ra_attend(q, idx: Index, K, V, sink: int, window: int, ids: torch.Tensor, st
         extra = [torch.empty((n_seq, n_q, d), **f), torch.empty((n_seq, n_q), **f),
                  torch.empty((n_seq, n_q, d), **f), torch.empty((n_seq, n_q), **f)]
     fn = lib().ra_attend_noalloc if noalloc else lib().ra_attend
-    _check(fn(_ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), K.shape[2], sink, window,
-              topk, _ptr(ids), _stream(stream), _ptr(out), _ptr(lse), *[_ptr(t) for t in extra]))
+    _check(_room(fn, _ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), K.shape[2], sink, window,
+                 topk, _ptr(ids), _stream(stream), _ptr(out), _ptr(lse), *[_ptr(t) for t in extra]))
     return (out, lse, *extra) if partials else (out, lse)
 
 
@@ -373,23 +390,23 @@ def ra_decode_step(q, idx: Index, K, V, sink: int, window: int, topk: int, ef: i
         if topk_per_head.dtype != torch.int32 or tuple(topk_per_head.shape) != (n_seq, n_q) \
                 or not topk_per_head.is_contiguous():
             raise ValueError("topk_per_head must be a contiguous int32 tensor [n_seq][n_q]")
-        _check(lib().ra_decode_step_budgets(_ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), K.shape[2], sink,
-                                            window, topk, _ptr(topk_per_head), ef, expand, _stream(stream),
-                                            _ptr(out), _ptr(lse), _ptr(ids), _ptr(stats)))
+        _check(_room(lib().ra_decode_step_budgets, _ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), K.shape[2], sink,
+                     window, topk, _ptr(topk_per_head), ef, expand, _stream(stream),
+                     _ptr(out), _ptr(lse), _ptr(ids), _ptr(stats)))
     elif k8 is not None:
         K8, scale = k8
         _dev(K8, scale)
-        _check(lib().ra_decode_step_q8(_ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), _ptr(K8), _ptr(scale),
-                                       K.shape[2], sink, window, topk, ef, expand, _stream(stream),
-                                       _ptr(out), _ptr(lse), _ptr(ids), _ptr(stats)))
+        _check(_room(lib().ra_decode_step_q8, _ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), _ptr(K8), _ptr(scale),
+                     K.shape[2], sink, window, topk, ef, expand, _stream(stream),
+                     _ptr(out), _ptr(lse), _ptr(ids), _ptr(stats)))
     elif n_tokens is None:
-        _check(lib().ra_decode_step(_ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), K.shape[2], sink,
-                                    window, topk, ef, expand, _stream(stream), _ptr(out), _ptr(lse),
-                                    _ptr(ids), _ptr(stats)))
+        _check(_room(lib().ra_decode_step, _ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), K.shape[2], sink,
+                     window, topk, ef, expand, _stream(stream), _ptr(out), _ptr(lse),
+                     _ptr(ids), _ptr(stats)))
     else:
-        _check(lib().ra_decode_step_grown(_ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), n_tokens,
-                                          K.shape[2], sink, window, topk, ef, expand, _stream(stream),
-                                          _ptr(out), _ptr(lse), _ptr(ids), _ptr(stats)))
+        _check(_room(lib().ra_decode_step_grown, _ptr(q), idx.handle, _ptr(K), _ptr(V), _dt(K), n_tokens,
+                     K.shape[2], sink, window, topk, ef, expand, _stream(stream),
+                     _ptr(out), _ptr(lse), _ptr(ids), _ptr(stats)))
     return out, lse, ids, stats
 
 

@@ -348,30 +348,45 @@ static hipError_t build_scratch(void** p, size_t most, size_t least, size_t* got
     return e;
 }
 
-extern "C" ra_status ra_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
-                            int64_t N, int64_t M, int d, int knn, void* stream, int32_t* L_out) {
-    if (!K || !Q || !L_out) RA_FAIL(RA_EINVAL, "NULL argument");
-    RA_TRY(check_dtype(dt));
-    RA_TRY(check_heads(n_seq, n_q, n_kv));
-    RA_TRY(check_dim(d));
-    RA_TRY(check_build_args(N, M, 2, knn, false));
-    void* ws = nullptr;
-    size_t ws_bytes = 0;
-    RA_HIP(build_scratch(&ws, ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false),
-                         ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, true), &ws_bytes));
-    ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, ws_bytes, (hipStream_t)stream, L_out);
-    hipError_t e = hipStreamSynchronize((hipStream_t)stream);
-    (void)hipFree(ws);
-    if (rc != RA_OK) return rc;
-    RA_HIP(e);
-    return RA_OK;
-}
-
 // (parts of it are read 16 bytes at a time and copied straight to LDS)
 static ra_status check_workspace(const void* workspace) {
     if (reinterpret_cast<uintptr_t>(workspace) % 256)
         RA_FAIL(RA_EINVAL, "the workspace is not 256-byte aligned");
     return RA_OK;
+}
+
+extern "C" size_t ra_knn_scratch_bytes(ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M, int d, int knn) {
+    if (check_dtype(dt) != RA_OK || check_heads(n_seq, n_q, n_kv) != RA_OK || check_dim(d) != RA_OK ||
+        check_build_args(N, M, 2, knn, false) != RA_OK)
+        return 0;
+    return ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false);
+}
+
+extern "C" ra_status ra_knn_ws(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N, int64_t M,
+                               int d, int knn, void* workspace, size_t workspace_bytes, void* stream, int32_t* L_out) {
+    if (!K || !Q || !L_out) RA_FAIL(RA_EINVAL, "NULL argument");
+    RA_TRY(check_dtype(dt));
+    RA_TRY(check_heads(n_seq, n_q, n_kv));
+    RA_TRY(check_dim(d));
+    RA_TRY(check_build_args(N, M, 2, knn, false));
+    const size_t least = ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, true);
+    if (workspace && workspace_bytes < least)
+        RA_FAIL(RA_ESHAPE, "workspace of %zu bytes, the lists need %zu", workspace_bytes, least);
+    RA_TRY(check_workspace(workspace));
+    void* ws = workspace;
+    size_t ws_bytes = workspace_bytes;
+    if (!ws) RA_HIP(build_scratch(&ws, ra_knn_workspace_bytes(dt, n_seq, n_q, n_kv, N, M, knn, false), least, &ws_bytes));
+    ra_status rc = ra_launch_knn(K, Q, dt, n_seq, n_q, n_kv, N, M, knn, ws, ws_bytes, (hipStream_t)stream, L_out);
+    hipError_t e = hipStreamSynchronize((hipStream_t)stream);
+    if (!workspace) (void)hipFree(ws);
+    if (rc != RA_OK) return rc;
+    RA_HIP(e);
+    return RA_OK;
+}
+
+extern "C" ra_status ra_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, int n_q, int n_kv,
+                            int64_t N, int64_t M, int d, int knn, void* stream, int32_t* L_out) {
+    return ra_knn_ws(K, Q, dt, n_seq, n_q, n_kv, N, M, d, knn, nullptr, 0, stream, L_out);
 }
 
 extern "C" size_t ra_project_scratch_bytes(int n_graphs, int64_t N, int64_t M, int deg, int knn) {

@@ -71,6 +71,11 @@ def test_workspace_that_is_not_aligned_is_refused(off):
     ws = C.c_void_p(0x10000 + off)
     assert L.ra_project_ws(_fake(), 1, 100, 10, 8, 8, ws, need, None, _fake(), _fake()) == 1
     assert "aligned" in L.ra_last_error().decode()
+    need = L.ra_knn_scratch_bytes(1, 1, 4, 2, 100, 10, 128, 8)
+    assert L.ra_knn_ws(_fake(), _fake(), 1, 1, 4, 2, 100, 10, 128, 8, ws, need, None, _fake()) == 1
+    assert "aligned" in L.ra_last_error().decode()
+    assert L.ra_knn_ws(_fake(), _fake(), 1, 1, 4, 2, 100, 10, 128, 8, ws, 8, None, _fake()) == 2
+    assert L.ra_knn_scratch_bytes(1, 1, 4, 2, 100, 10, 128, 101) == 0
     h = C.c_void_p()
     need = L.ra_build_workspace_bytes(1, 1, 4, 2, 100, 10, 128, 8, 8)
     assert L.ra_build_index_ws(_fake(), _fake(), 1, 1, 4, 2, 100, 10, 128, 8, 8, ws, need, None, C.byref(h)) == 1

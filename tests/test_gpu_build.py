@@ -350,6 +350,30 @@ def test_projection_in_any_amount_of_memory(n, M, knn, hubs, per_list, others):
     assert lib.ra_project_ws(Ld.data_ptr(), n, N, M, knn, deg, piece.data_ptr(), least - 1, st, adj.data_ptr(), ent.data_ptr()) == 2
 
 
+def test_builds_in_a_row_take_the_same_scratch_memory():
+    """Builds with hundreds of megabytes of scratch memory, and the stages as their own calls: nothing is allocated or freed
+    for it by the second of two calls (drivers that have to take and give as much per call hold them up), and what the first
+    took goes back with torch.cuda.empty_cache()."""
+    N, M, n_q, knn = 100000, 300, 32, 16
+    w = synth.make_llama_layer(5, N, M, n_seq=1, n_q=n_q, n_kv=8, device=DEV)
+    lib = ra.lib()
+    need = lib.ra_build_workspace_bytes(1, 1, n_q, 8, N, M, 128, 32, knn)
+    assert 300 << 20 < need < 1 << 30 and lib.ra_knn_scratch_bytes(1, 1, n_q, 8, N, M, 128, knn) > 300 << 20
+    L = ra.ra_knn(w.K, w.Q_prefill, knn)
+    calls = [lambda: ra.ra_build_index(w.K, w.Q_prefill, 32, knn).free(), lambda: ra.ra_knn(w.K, w.Q_prefill, knn),
+             lambda: ra.ra_project(L.view(n_q, M, knn), N, 32)]
+    torch.cuda.empty_cache()
+    held = torch.cuda.memory_reserved()
+    for call in calls:
+        call()
+        before, free = torch.cuda.memory_stats()["num_device_alloc"], torch.cuda.mem_get_info()[0]
+        call()
+        assert torch.cuda.memory_stats()["num_device_alloc"] == before and torch.cuda.mem_get_info()[0] == free
+    assert torch.cuda.memory_reserved() - held >= need
+    torch.cuda.empty_cache()
+    assert torch.cuda.memory_reserved() == held
+
+
 @pytest.mark.parametrize("n,N,M", [(4, 600, 600), (2, 300, 300), (7, 900, 40)])
 def test_projection_of_a_small_batch_is_one_group(n, N, M):
     """A workspace of as much as is asked for takes all graphs at once: the last one's part of it is written too."""
