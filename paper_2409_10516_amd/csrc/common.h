@@ -157,7 +157,7 @@ ra_status ra_launch_knn_filter_scales(const void* K, ra_dtype dt, int n_seq_kv, 
                                       hipStream_t st);
 ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const void* order, int graphs, int g0,
                                int n_graphs, int n_q, int n_kv, int64_t N, int64_t M, int knn, int64_t first, int64_t from,
-                               const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
+                               int64_t end, const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
                                const int** resume, int* resume_queries, int* resume_blocks);
 void ra_knn_set_selection_override(int v);      // RA_TEST_KNN_AUTO / _FILTER / _LDS
 void ra_knn_set_resume_copy(int* to);           // RA_TEST_KNN_RESUME

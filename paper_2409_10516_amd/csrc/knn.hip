@@ -612,15 +612,17 @@ ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, in
         c.resume = nullptr;
         rc = knn_launch(c, dt);
         if (rc != RA_OK) return rc;
-        // What gives up in the filter goes on here up to an eighth of the stream, where it is tried again, then to the end. (With a
-        // trial after a thirty-second too, which only float32 streams of a multiple of 8192 keys had, 4 heads of the mixture law with
-        // 8192 queries: 64K keys 3.50 ms, without 3.25, 128K 5.01 and 4.83. What gives up again has paid for two trials: one float32
-        // head without a common component, 16K keys, 512 queries 2.25 ms, with one trial 2.17.)
+        // The filter goes to an eighth of the stream, then to the end; what gives up goes on here to the same place. (When only what had
+        // given up came back for the second part, the others having gone to the end at once, a launch of a few workgroups
+        // took as long again: 4 heads of the mixture law, 287754 keys, 64K queries, lists of 32 22.8 ms, now 17.0, and 1M keys 39.7 and 40.0. With a third
+        // part up to a thirty-second, which only float32 streams of a multiple of 8192 keys had, 8192 queries, 64K
+        // keys 3.50 ms, without 3.25, 128K 5.01 and 4.83. What gives up twice has paid for two trials: one float32 head without a common
+        // component, 16K keys, 512 queries 2.25 ms, with one trial 2.17.)
         int64_t from = first;
         for (int more : {8, 1}) {
             const int64_t next = more == 1 ? N : first + (N / more - first + KN_FILTER_SEGMENT - 1) / KN_FILTER_SEGMENT * KN_FILTER_SEGMENT;
             if (more > 1 && (N / more < 2 * from || next >= N)) continue;
-            rc = ra_launch_knn_filter(K, Q, dt, workspace, graphs, g0, c.n_graphs, n_q, n_kv, N, M, knn, first, from, maxabs, ws,
+            rc = ra_launch_knn_filter(K, Q, dt, workspace, graphs, g0, c.n_graphs, n_q, n_kv, N, M, knn, first, from, next, maxabs, ws,
                                       st, L, &c.resume, &c.resume_queries, &c.resume_blocks);
             if (rc == RA_OK) rc = knn_copy_resume(c);
             if (rc != RA_OK) return rc;

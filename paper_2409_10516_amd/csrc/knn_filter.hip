@@ -59,6 +59,8 @@ typedef int i32x16 __attribute__((ext_vector_type(16)));
 #define KF_PENDING 64              // keys a query set can have waiting to be scored (a batch is 32; a block may add to 31)
 #define KF_MEET 4                  // segments between two meetings of a workgroup's wavefronts
 #define KF_HOLD 16                 // segments at most between two trials of an earlier look
+#define KF_LINE_FIRST(dt) ((dt) == RA_BF16 ? 3 : 8)      // keys of 32 kept above which a workgroup gives up, in the first launch
+#define KF_LINE_LAST 12                                  // ... and in a second
 #define KF_RANK_SAMPLE 512         // queries whose variance ranks the dimensions (at most)
 
 template <int V> struct kf_int { static constexpr int value = V; };      // a compile-time number as an argument
@@ -479,7 +481,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     const void* __restrict__ K, const void* __restrict__ Q, const u64* __restrict__ order, int64_t order_stride,
     const unsigned char* __restrict__ K8, int64_t rows8, const unsigned char* __restrict__ Q8,
     const float4* __restrict__ qinfo, const KfSegment* __restrict__ seg, int nseg, int g0, int n_q, int n_kv, int64_t N,
-    int64_t M, int knn, int first, int from, float* scores, int32_t* L, int* resume) {
+    int64_t M, int knn, int first, int from, int end, int line, float* scores, int32_t* L, int* resume) {
     __shared__ int s_pend[KF_WAVES][NQ][KF_PENDING];
     __shared__ int s_count[KF_WAVES][NQ];
     __shared__ u64 s_run[KF_WAVES][NQ][KF_RUN][RA_WAVE];
@@ -508,7 +510,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     int* my_resume = resume + ((size_t)gl * gridDim.x + blockIdx.x) * KF_WAVES + wv;
     int begin = __builtin_amdgcn_readfirstlane(*my_resume);
     if (begin < from) begin = from;
-    if (begin >= N) begin = -1;
+    if (begin >= end) begin = -1;
     if (tid == 0) s_kept = s_seen = 0;
     __syncthreads();
     if (begin < 0) return;                             // (a barrier waits for no wavefront that has ended)
@@ -667,7 +669,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     //      1M keys x 4 heads, where wavefronts have keys to score at different times: 36, 41 and 35 ms. Before
     //      (stages, whole products, no mean taken off): 51 and 41 ms.
     const unsigned char* K8g = K8 + (size_t)gl * rows8 * RA_D;
-    const int nblocks = (int)((N - first + 31) / 32);
+    const int nblocks = (end - first + 31) / 32;
     const uint32_t ring_at = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)s_ring + wv * (KF_RING * KF_OPERAND));
     const unsigned char* ring = s_ring[wv];
@@ -737,12 +739,14 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
     };
     // Scoring a kept key costs about ten times what ruling it out does. Where the bound cannot tell the keys apart (at the
     // start of a stream whose queries have little in common, or all along: ties, a few dimensions that dwarf the
-    // others) they are better off in knn.hip's loop: when a workgroup's wavefronts have kept more than three keys in 32 (in
-    // float32, whose products cost sixteen times as much, more than eight), each stops at the end of its segment and
-    // leaves its queries' keys there. All of them, because that loop costs a workgroup's whole stream however few of
-    // its queries are left. Whole calls, 4 heads of the mixture law, lists of 48, lines at 1 / 2 / 3 / 4 in 32: 64K keys x
-    // 64K queries 7.8 / 7.8 / 8.0 / 9.8 ms, 128K 12.5 / 13.7 / 10.4 / 10.5, 256K 20.0 / 14.9 / 14.8 / 15.0; float32, 64K
-    // keys x 8K queries, 4 / 8 / 16 / 24 in 32: 7.7 / 3.2 / 5.6 / 3.4 ms.
+    // others) they are better off in knn.hip's loop: when a workgroup's wavefronts have kept more than `line` keys in 32, each stops
+    // at the end of its segment and leaves its queries' keys up to `end` there. All of them, because that loop costs a workgroup's
+    // whole stream however few of its queries are left. The line is three (in float32, whose products cost sixteen times
+    // as much, eight) up to an eighth of the stream, or where there is one launch, and twelve behind, where thresholds are near
+    // final and giving up means exact products to the end. Whole calls, 4 heads of the mixture law, lists of 48, lines at 1 / 2 / 3 / 4 in 32,
+    // ms: 64K keys x 64K queries 7.8 / 7.8 / 8.0 / 9.8, 128K 12.5 / 13.7 / 10.4 / 10.5, 256K 20.0 / 14.9 / 14.8 / 15.0; float32, 64K
+    // keys x 8K queries, 4 / 8 / 16 / 24 in 32: 7.7 / 3.2 / 5.6 / 3.4; behind the eighth 3 and 12: 81008 keys x 64K queries 13.1 and 7.5; one launch
+    // of 30000 keys x 30000 queries 3 / 8 / 16: 2.2 / 3.1 / 2.6.
     auto keeps_too_much = [&]() __attribute__((always_inline)) -> bool {
         const int seen = (blk - counted) * NQ;           // (blocks of 32 keys)
         int all_kept = 0, all_seen = 0;
@@ -754,7 +758,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
         counted = blk;
         all_kept = uniform(all_kept);
         all_seen = uniform(all_seen);
-        return all_seen >= KF_WAVES / 2 * KF_SEG_BLOCKS * NQ && (int64_t)all_kept > (int64_t)all_seen * (DT == RA_BF16 ? 3 : 8);
+        return all_seen >= KF_WAVES / 2 * KF_SEG_BLOCKS * NQ && (int64_t)all_kept > (int64_t)all_seen * line;
     };
     // the floors of the segment that opens at block blk; false when none of its keys can reach a threshold
     auto open_segment = [&]() __attribute__((always_inline)) -> bool {
@@ -868,7 +872,7 @@ __global__ __launch_bounds__(KF_THREADS, 2) void knn_filter_kernel(
         const u64 some = __ballot(fill > 0);
         fold(s, (uint32_t)some | (uint32_t)(some >> 32), tau, fill);
     }
-    if (lane == 0) *my_resume = stop < nblocks ? first + stop * 32 : 0x7fffffff;
+    if (lane == 0) *my_resume = stop < nblocks ? first + stop * 32 : end < N ? end : 0x7fffffff;
 }
 
 static int64_t kf_rows(int64_t N) { return (N + 31) & ~(int64_t)31; }
@@ -911,11 +915,11 @@ ra_status ra_launch_knn_filter_scales(const void* K, ra_dtype dt, int n_seq_kv, 
 
 // Graphs [g0, g0 + n_graphs) of the `graphs` that `order` holds: the rest of their streams from position
 // `from` on. L holds the lists of what came before, ra_knn_filter_scores(workspace, ...) their scores. The first
-// launch of a group of graphs (from == first) makes the 8-bit copies; later ones, whose `from` is a whole number of
-// segments on, are for the queries that gave up in one before (resume: where), for which knn.hip has gone on to `from`.
+// launch of a group of graphs (from == first) makes the 8-bit copies. Every launch ends at stream position `end`, a whole number of
+// segments on or N; what gives up before (resume: where) is knn.hip's up to there, and the next launch goes on from `end`.
 ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const void* order, int graphs, int g0,
                                int n_graphs, int n_q, int n_kv, int64_t N, int64_t M, int knn, int64_t first, int64_t from,
-                               const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
+                               int64_t end, const uint32_t* maxabs, void* workspace, hipStream_t st, int32_t* L,
                                const int** resume, int* resume_queries, int* resume_blocks) {
     const KfLayout l = kf_layout(n_graphs, N, M, knn);
     char* ws = reinterpret_cast<char*>(workspace);
@@ -934,6 +938,7 @@ ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const 
     const dim3 pgrid((unsigned)(nseg < 128 ? nseg : 128), (unsigned)n_graphs);
     const dim3 qgrid((unsigned)(M / 16 < 255 ? M / 16 + 1 : 256), (unsigned)n_graphs);
     int* res = reinterpret_cast<int*>(ws + l.resume);
+    const int line = from == first ? KF_LINE_FIRST(dt) : KF_LINE_LAST;
     // four query sets per wavefront (a key operand feeds four chains: 39.9 ms against 47.1 with two and 69.9
     // with one, 128K keys x 32 heads; 4 heads 5.7, 6.2 and 9.0) unless that leaves compute units without a workgroup
     auto blocks = [&](int nq) { return (M + KF_WAVES * 32 * nq - 1) / (KF_WAVES * 32 * nq); };
@@ -943,7 +948,7 @@ ra_status ra_launch_knn_filter(const void* K, const void* Q, ra_dtype dt, const 
     hipLaunchKernelGGL((knn_filter_kernel<DTV, NQV>), grid, dim3(KF_THREADS), 0, st, K, Q, ord, stride,         \
                        reinterpret_cast<unsigned char*>(ws + l.k8), rows8,                                      \
                        reinterpret_cast<unsigned char*>(ws + l.q8), reinterpret_cast<float4*>(ws + l.info),     \
-                       seg, nseg, g0, n_q, n_kv, N, M, knn, (int)first, (int)from, scores, L, res)
+                       seg, nseg, g0, n_q, n_kv, N, M, knn, (int)first, (int)from, (int)end, line, scores, L, res)
 #define KF_GO(DTV)                                                                                              \
     do {                                                                                                        \
         if (from == first) {                                                                                    \

@@ -625,15 +625,15 @@ def _knn_with_resume(K, Q, dtype, heads, knn):
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("N,knn,M,heads,form", [
-    (2600, 32, 300, 1, "ties"), (2639, 64, 257, 2, "ties"),            # tried again at 640, the earliest place it can stop at
-    (18000, 32, 300, 1, "ties"), (17999, 64, 300, 1, "ties"),          # ... at 2688, behind the last place it can
+    (2600, 32, 300, 1, "ties"), (2639, 64, 257, 2, "ties"),            # the second part is from 640 on, one segment behind
+    (18000, 32, 300, 1, "ties"), (17999, 64, 300, 1, "ties"),          # ... from 2688, five segments: gives up before
     (18000, 32, 300, 1, "early"), (18001, 64, 90, 1, "early"),         # ... and comes to the end then
-    (18000, 64, 300, 1, "late"),                                       # keeps nothing for four segments
+    (18000, 64, 300, 1, "late"),                                       # keeps nothing for four segments, gives up in the second part
     (5000, 32, 600, 128, "ties"), (5000, 33, 300, 256, "ties"),        # two and four sets of queries per wavefront
 ])
 def test_knn_filter_gives_up(dtype, knn, N, M, heads, form):
     """Streams that the bound cannot rule out much of: the workgroups give up, the exact products go on to an eighth of the
-    stream, where the 8-bit products are tried again, and from where they give up again to the end. That they give up is
+    stream, where all are tried again, and from where they give up again to the end. That they give up is
     certain: for the queries that look at the first half of the dimensions (one in every set of 32) each key ties with
     the first part of the stream, and a key that reaches a threshold may not be ruled out; nor can it be before
     wavefronts with half of a workgroup's sets have come through a segment of 512 keys, or one alone through as many as
@@ -649,13 +649,13 @@ def test_knn_filter_gives_up(dtype, knn, N, M, heads, form):
     assert stops.shape[0] == 2 and (stops[:, :, ~live] == END).all()
     a, b = stops[0][:, live], stops[1][:, live]
     again = 128 + -(-(N // 8 - 128) // 512) * 512
-    earliest, most = (2176, 4736) if form == "late" else (640, 2176)
-    assert (a % 512 == 128).all() and a.min() >= earliest and a.max() <= most
+    assert (a % 512 == 128).all() and a.min() >= (2176 if form == "late" else 640)
+    assert a.max() <= (again if form == "late" else min(again, 2176))
     assert N < 8192 or again == 2688
     if form == "early":
         assert (b == END).all()
     else:
-        assert (b >= np.maximum(a, again) + 512).all() and (N < most + 2560 or b.max() <= most + 2048 + 512)
+        assert (b >= again + 512).all() and (N < again + 2560 or b.max() <= again + 2560)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -664,13 +664,14 @@ def test_knn_filter_places_without_a_query(dtype, M, heads):
     """What a workgroup has beyond its last query (whole wavefronts, sets, columns of a set) keeps no keys and makes nobody
     give up: the last query, which would stand for all of them, finds its 16 keys in the first segment and rules out the rest,
     all of which are above its threshold at the start."""
-    N, knn = 4200, 16
+    N, knn = 18000, 16
     first_half = np.arange(M) == M - 1
     K, Q, place = _half_streams(N, M, first_half, lambda p: np.where(p < 128, 30, np.where(p < 160, 40, 34)))
     got, stops, live = _knn_with_resume(K, Q, dtype, heads, knn)
     ref = OM.knn_lists(Q[[0, M - 1]], K, knn)[0]
     assert np.array_equal(got, np.broadcast_to(ref[first_half.astype(int)], (heads, M, knn)))
-    assert (stops == END).all()
+    assert (stops[0][:, live] == 2688).all() and (stops[0][:, ~live] == END).all()         # (the end of the first part)
+    assert (stops[1] == END).all()
 
 
 # powers of two that queries and keys are multiplied by, down to where scores leave the normal range and up
