@@ -616,7 +616,7 @@ ra_status ra_launch_knn(const void* K, const void* Q, ra_dtype dt, int n_seq, in
         // given up came back for the second part, the others having gone to the end at once, a launch of a few workgroups
         // took as long again: 4 heads of the mixture law, 287754 keys, 64K queries, lists of 32 22.8 ms, now 17.0, and 1M keys 39.7 and 40.0. With a third
         // part up to a thirty-second, which only float32 streams of a multiple of 8192 keys had, 8192 queries, 64K
-        // keys 3.50 ms, without 3.25, 128K 5.01 and 4.83.
+        // keys 3.50 ms, without 3.25, 128K 5.01 and 4.83.)
         int64_t from = first;
         for (int more : {8, 1}) {
             const int64_t next = more == 1 ? N : first + (N / more - first + KN_FILTER_SEGMENT - 1) / KN_FILTER_SEGMENT * KN_FILTER_SEGMENT;
