@@ -337,7 +337,12 @@ int64_t ra_index_info(const ra_index* idx, int what);
  *                       relaxed agent-scope accesses, the same bounded wait (RA_CFG_HELPER_SPIN
  *                       polls per slot) and the same fall-back as the helpers' records: a head whose
  *                       keys do not arrive scores its set itself and the handle stops using shares
- *                       until RA_CFG_HELPERS or RA_CFG_SEED_SHARES is set again. */
+ *                       until RA_CFG_HELPERS or RA_CFG_SEED_SHARES is set again.
+ *                       0 also keeps ra_decode_step from sharing the steps of long walks: with few searches over a
+ *                       context whose visited sets do not fit on chip, and wide steps, each search has 8 or 16
+ *                       workgroups of its own in the launch that claim and score its steps' neighbours, with
+ *                       hand-overs, bounded waits and a fall-back (the search walks alone) of the same kind, and the
+ *                       same ids and counters. */
 #define RA_CFG_HELPERS 0
 #define RA_CFG_HELPER_SPIN 1
 #define RA_CFG_SEEDS 2

@@ -124,14 +124,18 @@ static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra
     auto aligned = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
     const size_t entry_at = aligned(ix->graph_bytes), roots_at = entry_at + aligned(graphs * sizeof(int32_t));
     const size_t coop_at = roots_at + aligned(graphs * ix->root_cap * sizeof(int32_t));
+    const size_t walk_at = coop_at + aligned(coop_bytes(ix));
+    const size_t parts = graphs < 256 ? ra_walk_parts((int)graphs, N) : 0;
+    ix->walk_bytes = parts ? (RA_WALK_OFF_WORDS + graphs * (RA_WALK_HEAD_WORDS + parts * RA_WALK_PART_WORDS)) * sizeof(*ix->walk) : 0;
     char* base = nullptr;
     hipError_t e = hipGetDevice(&ix->device);
-    if (e == hipSuccess) e = hipMalloc((void**)&base, coop_at + coop_bytes(ix));
+    if (e == hipSuccess) e = hipMalloc((void**)&base, walk_at + ix->walk_bytes);
     ix->adj = reinterpret_cast<int32_t*>(base);
     ix->entry = reinterpret_cast<int32_t*>(base + entry_at);
     ix->roots = reinterpret_cast<int32_t*>(base + roots_at);
     ix->coop = reinterpret_cast<unsigned long long*>(base + coop_at);
-    if (e == hipSuccess) e = hipMemset(ix->coop, 0, coop_bytes(ix));
+    if (parts) ix->walk = reinterpret_cast<unsigned long long*>(base + walk_at);
+    if (e == hipSuccess) e = hipMemset(ix->coop, 0, walk_at - coop_at + ix->walk_bytes);
     ix->coop_mode = RA_HELPERS_ON;
     ix->coop_spin = RA_HELPER_SPIN_DEFAULT;
     ix->seed_parts = RA_SEED_PARTS_DEFAULT;
@@ -167,6 +171,7 @@ extern "C" ra_status ra_index_configure(ra_index* ix, int what, int64_t value) {
             RA_HIP(hipDeviceSynchronize());
             RA_HIP(hipMemset(ix->coop, 0, coop_bytes(ix)));
             if (ix->seedx) RA_HIP(hipMemset(ix->seedx, 0, ix->seedx_bytes));
+            if (ix->walk) RA_HIP(hipMemset(ix->walk, 0, ix->walk_bytes));
             ix->coop_mode = (int)value;
             ix->coop_silent = 0;
             return RA_OK;
@@ -180,6 +185,7 @@ extern "C" ra_status ra_index_configure(ra_index* ix, int what, int64_t value) {
                 RA_FAIL(RA_EINVAL, "seed shares %lld: 0 or 2 .. %d", (long long)value, RA_SEED_PARTS_MAX);
             RA_HIP(hipDeviceSynchronize());
             if (ix->seedx) RA_HIP(hipMemset(ix->seedx, 0, ix->seedx_bytes));
+            if (ix->walk) RA_HIP(hipMemset(ix->walk, 0, ix->walk_bytes));
             ix->seed_parts = (int)value;
             return RA_OK;
         case RA_CFG_SEEDS: {
@@ -232,6 +238,7 @@ extern "C" ra_status ra_test_configure(ra_index* ix, int what, int64_t value) {
             RA_HIP(hipDeviceSynchronize());
             RA_HIP(hipMemset(ix->coop, 0, coop_bytes(ix)));
             if (ix->seedx) RA_HIP(hipMemset(ix->seedx, 0, ix->seedx_bytes));
+            if (ix->walk) RA_HIP(hipMemset(ix->walk, 0, ix->walk_bytes));
             ix->coop_silent = (int)value;
             return RA_OK;
         default:
@@ -249,7 +256,7 @@ extern "C" int64_t ra_index_info(const ra_index* ix, int what) {
         case 4: return ix->deg;
         case 5: return (int64_t)(ix->graph_bytes + (size_t)ix->n_seq * ix->n_q * 4 +
                                  ix->partials_bytes + ix->ids_bytes + ix->bitset_bytes + coop_bytes(ix) +
-                                 ix->seedx_bytes +
+                                 ix->seedx_bytes + ix->walk_bytes +
                                  (size_t)ix->n_seq * ix->n_q * (ix->root_cap + ix->seed_cap) * sizeof(int32_t));
         case 6: {
             if (ix->coop_mode != RA_HELPERS_ON || ix->coop_silent) return 0;
@@ -606,7 +613,7 @@ static ra_status decode_common(const void* q, const ra_index* idx, const void* K
     return ra_launch_decode(q, ix->adj, ix->entry, K, V, dt, ix->n_seq, ix->n_q, ix->n_kv, ix->N, N,
                             kv_stride, ix->deg, sink, window, topk, ef, expand, ix->bitset, ix->coop,
                             ix->coop_silent ? RA_HELPERS_SILENT_ : ix->coop_mode, ix->coop_spin, start, start_cap, K8, kscale,
-                            budgets, ix->n_seeds ? ix->seedx : nullptr, ix->seed_parts,
+                            budgets, ix->n_seeds ? ix->seedx : nullptr, ix->seed_parts, ix->walk,
                             (hipStream_t)stream, out, lse, ids, stats);
 }
 

@@ -80,6 +80,9 @@ struct ra_index {
     uint32_t* seedx;
     size_t seedx_bytes;
     int seed_parts;     // shares a head's start set is scored in by workgroups of their own (0: by the head)
+    // hand-over area of walks that share their steps (decode.hip), in the allocation of the graphs, or null
+    unsigned long long* walk;
+    size_t walk_bytes;
     // root sets: what the first two steps of every walk of a head visit ([n_seq*n_q][root_cap])
     int32_t* roots;
     int root_cap;
@@ -92,6 +95,15 @@ struct ra_index {
 #define RA_SEED_PARTS_DEFAULT 6
 #endif
 #define RA_SEEDX_KEYS_OFF 256  /* bytes in front of the keys of the seed hand-over area */
+#ifndef RA_WALK_PARTS_MAX
+#define RA_WALK_PARTS_MAX 16
+#endif
+#define RA_WALK_CELLS 4096     /* adjacency cells of a step of such a walk: the most a worker can have an answer for */
+#define RA_WALK_MIN_CELLS 2560 /* (see ra_launch_decode) */
+#define RA_WALK_MIN_KEYS (1 << 18)
+#define RA_WALK_OFF_WORDS 32   /* words in front of the areas: [0] "steps not shared", set by a head whose wait ran out */
+#define RA_WALK_HEAD_WORDS 272 /* 64-bit words of a head (its message), then of each of its workers (two answers) */
+#define RA_WALK_PART_WORDS (2 * (RA_WALK_CELLS + 8))
 #define RA_FLAT_SLICES 8       /* workgroups per head in the second pass of ra_flat_topk (one counter each) */
 #define RA_HELPERS_SILENT_ 2   /* launch-time helper mode behind RA_TEST_HELPERS_SILENT */
 #define RA_KEYS_I8 2          /* key type of a search over 8-bit keys (beside RA_F32, RA_BF16) */
@@ -125,14 +137,15 @@ ra_status ra_launch_attend_noalloc(const void* q, const void* K, const void* V, 
                                    const int32_t* ids, hipStream_t st, float* out, float* lse,
                                    float* o_omega, float* lse_omega, float* o_w, float* lse_w);
 
+int ra_walk_parts(int heads, int64_t N);   // workers of a walk that shares its steps, in launches of `heads` walks over N keys (0: none)
 bool ra_decode_needs_global_bitset(int64_t N, int deg, int ef, int expand, int topk);
 ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* entry, const void* K,
                            const void* V, ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t Ng, int64_t N,
                            int64_t kv_stride, int deg, int sink, int window, int topk, int ef, int expand,
                            uint32_t* bitset, unsigned long long* coop, int coop_mode, int coop_spin,
                            const int32_t* roots, int root_cap, const void* K8, const float* kscale,
-                           const int32_t* budgets, uint32_t* seedx, int seed_parts, hipStream_t st,
-                           float* out, float* lse, int32_t* ids, ra_stats* stats);
+                           const int32_t* budgets, uint32_t* seedx, int seed_parts, unsigned long long* walk,
+                           hipStream_t st, float* out, float* lse, int32_t* ids, ra_stats* stats);
 
 ra_status ra_launch_rerank(const void* q, const void* K, ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N,
                            const int32_t* cand, int n_cand, int topk, hipStream_t st, int32_t* ids);

@@ -259,6 +259,7 @@ struct SeedHook {
     bool seed_on;
     uint32_t seed_is_off;
     static constexpr bool kSeedShare = true;
+    static constexpr bool kShareSteps = false;
     __device__ __forceinline__ bool seeds_shared() const { return seed_on && seed_is_off == 0u; }
     // Keys c0 and c1 of the head's start set (c1 < 0: only c0, and k1 = k0), polled together a bounded
     // number of times, the slots zeroed for the next launch once the keys are taken; a key that did
@@ -283,10 +284,26 @@ struct SeedHook {
     __device__ __forceinline__ void seeds_missed() const { xwg_store(seed_off, 1u); }
 };
 
+// What a walk that shares its steps asks of the launch.
+struct WalkHook {
+    int spin, parts_log2;
+    u64* area;
+    uint32_t* off_word;
+    uint32_t is_off;
+    static constexpr bool kSeedShare = false;
+    static constexpr bool kShareSteps = true;
+    __device__ __forceinline__ bool steps_shared() const { return is_off == 0u; }
+    __device__ __forceinline__ void steps_missed() const { xwg_store(off_word, 1u); }
+};
+
 // BUDGETS: every head keeps its own number of ids (budgets[head]) instead of topk. A variant of
 // its own because the value lives through the whole walk: read in the common kernel, even behind a
 // test for a null pointer, it cost 1.5 % of the step.
-template <int DT, int KT, bool GBITS, int T, bool BUDGETS>
+// SHARE: the walks share their steps with 2^walk_log2 workers each (serve_walk). Workgroup x of the first
+// 8 * ceil(heads / 8) * (1 + workers) runs on the XCD of its head's others (x mod 8, if workgroups are dealt round-robin): the workers
+// of a head read the same adjacency rows, and a hand-over inside an XCD is a quarter shorter. The heads come first, then
+// the workers; helpers have the highest ids.
+template <int DT, int KT, bool GBITS, int T, bool BUDGETS, bool SHARE>
 __global__ __launch_bounds__(T) void decode_kernel(
     const void* __restrict__ q, const int32_t* __restrict__ adj, const int32_t* __restrict__ entry,
     const void* __restrict__ K, const void* __restrict__ V, int n_q, int n_kv, int64_t Ng, int64_t N,
@@ -296,27 +313,29 @@ __global__ __launch_bounds__(T) void decode_kernel(
     float* __restrict__ out, float* __restrict__ lse, u64* coop, int n_helpers, int coop_mode,
     int coop_spin, const int32_t* __restrict__ roots, int root_cap, const void* __restrict__ Ksearch,
     const float* __restrict__ kscale, const int32_t* __restrict__ budgets, uint32_t* seedx, int seed_parts,
-    int seed_stride, int helper_heads) {
+    int seed_stride, int helper_heads, int share_heads, u64* walk, int walk_log2) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int tid = threadIdx.x, grp = tid >> 4, lane16 = tid & 15;
     const size_t esz = DT == RA_BF16 ? 2 : 4;
     const int G = n_q / n_kv;
-    const int n_heads = ((int)gridDim.x - n_helpers) / (1 + seed_parts);
+    const int n_heads = SHARE ? share_heads : ((int)gridDim.x - n_helpers) / (1 + seed_parts);
+    const int walkers = SHARE ? (int)gridDim.x - n_helpers : 0;      // workgroups of heads and workers
+    const int helper = (int)blockIdx.x - walkers;
     // hand-over area: records, "helpers off" word (set by a head whose wait ran out); seed hand-over area: [0]
     // the "shares off" word, then (from byte RA_SEEDX_KEYS_OFF) seed_stride 64-bit keys per head, zero
     // between launches. Both words are asked for here, together, and looked at where they are needed: a
     // trip past the caches is a microsecond.
     uint32_t* helpers_off_word = reinterpret_cast<uint32_t*>(coop + (size_t)n_heads * RA_COOP_REC);
     const uint32_t helpers_off = xwg_load(helpers_off_word);
-    const uint32_t shares_off = xwg_load(seedx ? seedx : helpers_off_word);
-    if ((int)blockIdx.x < n_helpers) {
+    const uint32_t shares_off = xwg_load(SHARE ? reinterpret_cast<const uint32_t*>(walk) : seedx ? seedx : helpers_off_word);
+    if (SHARE ? helper >= 0 : helper < n_helpers) {
         // ---- helper workgroup of (sequence, KV head) blockIdx.x: attention over W for its G heads
         if (coop_mode == RA_HELPERS_SILENT_) return;
         // helper_heads of the group's G query heads per helper workgroup (G: one helper per group, W
         // read once; fewer where the launch leaves compute units idle: the helpers of a group then
         // run side by side on one XCD and share the rows in its L2)
         const int n_groups = n_heads / G;
-        const int g = (int)blockIdx.x % n_groups, part = (int)blockIdx.x / n_groups;
+        const int g = helper % n_groups, part = helper / n_groups;
         const char* Kg = reinterpret_cast<const char*>(K) + (size_t)g * kv_stride * RA_D * esz;
         const char* Vg = reinterpret_cast<const char*>(V) + (size_t)g * kv_stride * RA_D * esz;
         // G is 1, 2, 4 or 8 when helpers are on; 4 heads per pass over W (2 for fp32: registers)
@@ -331,6 +350,21 @@ __global__ __launch_bounds__(T) void decode_kernel(
         return;
     }
     u64* seed_keys_all = reinterpret_cast<u64*>(reinterpret_cast<char*>(seedx) + RA_SEEDX_KEYS_OFF);
+    int head;
+    auto walk_area = [&](int h) { return walk + RA_WALK_OFF_WORDS + (size_t)h * (RA_WALK_HEAD_WORDS + ((size_t)RA_WALK_PART_WORDS << walk_log2)); };
+    if constexpr (SHARE) {
+        // ---- the head (role 0), or one of its workers
+        const int per = 1 + (1 << walk_log2), j = (int)blockIdx.x >> 3, rows = (n_heads + 7) >> 3;
+        const int role = j / rows;                           // all heads, then all first workers, and so on
+        head = ((j - role * rows) << 3) + ((int)blockIdx.x & 7);
+        if (head >= n_heads || role >= per) return;
+        if (role > 0) {
+            if (coop_mode == RA_HELPERS_SILENT_ || shares_off != 0u) return;
+            serve_walk<DT, KT, T>(lds_raw, head, role - 1, walk_log2, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg, ef, expand,
+                                  roots, root_cap, kscale, walk_area(head), coop_spin);
+            return;
+        }
+    } else {
     if ((int)blockIdx.x < n_helpers + n_heads * seed_parts) {
         // ---- seed workgroup: one share of one head's start set (on the XCD of the head's workgroup
         //      when the number of heads is a multiple of 8)
@@ -341,7 +375,8 @@ __global__ __launch_bounds__(T) void decode_kernel(
                                     root_cap - 2, expand * deg, kscale, seed_keys_all + (size_t)hd * seed_stride);
         return;
     }
-    const int head = xcd_aware_head((int)blockIdx.x - n_helpers - n_heads * seed_parts, n_heads, G);
+    head = xcd_aware_head((int)blockIdx.x - n_helpers - n_heads * seed_parts, n_heads, G);
+    }
     const int seq = head / n_q, h = head % n_q, kvh = h / G;
     int32_t* lds_ids = reinterpret_cast<int32_t*>(lds_raw + ids_off);
     uint32_t* lds_word = reinterpret_cast<uint32_t*>(lds_ids + topk);
@@ -356,11 +391,16 @@ __global__ __launch_bounds__(T) void decode_kernel(
         const int b = budgets[head];
         take = b < 1 ? 1 : b > topk ? topk : b;
     }
-    const int cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
-                                          s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
-                                          lds_ids, roots, root_cap, kscale,
-                                          SeedHook{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx,
-                                                   seed_parts > 0, shares_off});
+    auto search = [&](const auto& hook) __attribute__((always_inline)) {
+        return run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
+                                            s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
+                                            lds_ids, roots, root_cap, kscale, hook);
+    };
+    int cnt;
+    if constexpr (SHARE)
+        cnt = search(WalkHook{coop_spin, walk_log2, walk_area(head), reinterpret_cast<uint32_t*>(walk), shares_off});
+    else
+        cnt = search(SeedHook{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx, seed_parts > 0, shares_off});
 #ifdef SR_PHASE_CLOCKS
     const long long t_attn = clock64();
 #endif
@@ -527,13 +567,20 @@ static int decode_compute_units() {
     return cached[dev] > 0 ? cached[dev] : 0;
 }
 
+// (below RA_WALK_MIN_KEYS the visited set of steps of up to RA_WALK_CELLS cells always fits LDS)
+int ra_walk_parts(int heads, int64_t N) {
+    if (N < RA_WALK_MIN_KEYS) return 0;
+    const int room = decode_compute_units() / heads - 2;         // (a head, and at most one helper per head)
+    return room >= RA_WALK_PARTS_MAX ? RA_WALK_PARTS_MAX : room >= 8 && RA_WALK_PARTS_MAX >= 8 ? 8 : 0;
+}
+
 ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* entry, const void* K,
                            const void* V, ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t Ng, int64_t N,
                            int64_t kv_stride, int deg, int sink, int window, int topk, int ef, int expand,
                            uint32_t* bitset, unsigned long long* coop, int coop_mode, int coop_spin,
                            const int32_t* roots, int root_cap, const void* K8, const float* kscale,
-                           const int32_t* budgets, uint32_t* seedx, int seed_parts, hipStream_t st,
-                           float* out, float* lse, int32_t* ids, ra_stats* stats) {
+                           const int32_t* budgets, uint32_t* seedx, int seed_parts, unsigned long long* walk,
+                           hipStream_t st, float* out, float* lse, int32_t* ids, ra_stats* stats) {
     // W = [0, s) u [wstart, N): the sink, the sliding window, and every token appended after the
     // index was built (wstart <= Ng); overlapping ranges make everything static
     int64_t s = sink < 0 ? 0 : sink, ww = window < 0 ? 0 : window;
@@ -576,17 +623,40 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
         if (parts < 2) parts = 0;
     }
     const int seed_stride = root_cap;
+    // Steps shared out (serve_walk): walks with the visited set in device memory, where there are compute units for 8 workers each
+    // and steps are wide, which takes a beam of some times `expand` entries to pick from. us per layer without -> with, cells of a
+    // step / beam: 4 heads of the mixture law, 1M keys, 3072 / 256 to 1024 134 -> 88, 209 -> 155, 424 -> 314; 1536 / 512 210 -> 182; 2M
+    // keys, float32, 3072 / 512 209 -> 173. 4 to 16 heads of the Llama-shaped law, whose steps find a hundred new keys, not a thousand:
+    // 4096 / 512 to 1024 76 -> 65, 132 -> 107, 16 heads 110 -> 84, 209 -> 152; 2048 / 256 to 1024 53 -> 53, 79 -> 80, 135 -> 130, 16
+    // heads 54 -> 55, 81 -> 78, 139 -> 157; 1024 / 1024 165 -> 203; 4096 / 64 32 -> 47. (With the visited set in LDS the head
+    // claims faster than workers could be asked to; scores alone shared out there: mixture law, 128K keys, 3072 / 256 104 -> 84, but
+    // Llama-shaped walks +5 to +10 %.) 8 workers are 1 to 3 % slower than 16.
+    int walk_log2 = 0;
+    const int cells = expand * deg;
+    if (walk && gb && roots && seed_parts > 0 && coop_mode != RA_HELPERS_OFF && !budgets && threads >= 512 && deg >= 2 &&
+        deg * (expand < ef / 4 ? expand : ef / 4) >= RA_WALK_MIN_CELLS && cells <= RA_WALK_CELLS) {
+        walk_log2 = 31 - __builtin_clz(ra_walk_parts(heads, Ng));
+        if (serve_lds_bytes(Ng, deg, expand, walk_log2) > lds) walk_log2 = 0;
+        else parts = 0;
+    }
+    const int walkers = walk_log2 ? (heads + 7) / 8 * 8 * (1 + (1 << walk_log2)) : 0;
     if (kscale && !K8) RA_FAIL(RA_EINVAL, "8-bit keys missing");
-#define RA_DC_GO_T(DTV, KTV, GB, TV) RA_DC_GO_TB(DTV, KTV, GB, TV, false)
-#define RA_DC_GO_TB(DTV, KTV, GB, TV, BU)                                                          \
+#define RA_DC_GO_AS(DTV, KTV, GB, TV, BU, SH)                                                      \
     do {                                                                                           \
-        RA_LDS_OPT_IN((decode_kernel<DTV, KTV, GB, TV, BU>), lds);                                 \
-        hipLaunchKernelGGL((decode_kernel<DTV, KTV, GB, TV, BU>),                                  \
-                           dim3(heads * (1 + parts) + n_helpers), dim3(TV),                        \
+        RA_LDS_OPT_IN((decode_kernel<DTV, KTV, GB, TV, BU, SH>), lds);                             \
+        hipLaunchKernelGGL((decode_kernel<DTV, KTV, GB, TV, BU, SH>),                              \
+                           dim3((SH ? walkers : heads * (1 + parts)) + n_helpers), dim3(TV),       \
                            lds, st, q, adj, entry, K, V, n_q, n_kv, Ng, N, kv_stride, wstart, deg, \
                            (int)s, topk, ef, expand, bitset, ids, stats, ids_off, scale, out, lse, \
                            coop, n_helpers, coop_mode, coop_spin, roots, root_cap, Ksearch,        \
-                           kscale, budgets, seedx, parts, seed_stride, helper_heads);              \
+                           kscale, budgets, seedx, parts, seed_stride, helper_heads, heads, walk,  \
+                           walk_log2);                                                             \
+    } while (0)
+#define RA_DC_GO_TB(DTV, KTV, GB, TV, BU) RA_DC_GO_AS(DTV, KTV, GB, TV, BU, false)
+#define RA_DC_GO_T(DTV, KTV, GB, TV)                                                               \
+    do {                                                                                           \
+        if (walk_log2) RA_DC_GO_AS(DTV, KTV, true, (TV < 512 ? 512 : TV), false, true);            \
+        else RA_DC_GO_AS(DTV, KTV, GB, TV, false, false);                                          \
     } while (0)
 #define RA_DC_GO(DTV, KTV, GB)                                                                     \
     do {                                                                                           \
@@ -616,6 +686,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
     }
 #undef RA_DC_GO_T
 #undef RA_DC_GO_TB
+#undef RA_DC_GO_AS
 #undef RA_DC_GO
     RA_HIP(hipGetLastError());
     return RA_OK;

@@ -389,6 +389,38 @@ __device__ __forceinline__ void touch_line(const void* p, uint32_t lds_off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_off), "v"(p) : "m0");
 }
 
+// Claims L neighbours per lane and appends those not visited before to cid, `n_claimed` of them so far; bit_word(id) is the word of the
+// visited set that has id's bit, wanted(id) whether id is to be claimed here. All claims are on their way before the first
+// result is looked at, and a wavefront appends with one atomic. (In the head's own steps this code next to the other cost the common
+// kernels 1 to 2 %, in registers, and gave the widest steps nothing.)
+template <int L, typename Word, typename Wanted>
+__device__ __forceinline__ void claim_cells(const int (&nb)[L], uint32_t n_keys, int flag, int lane, int* cid, int* n_claimed,
+                                            const Word& bit_word, const Wanted& wanted) {
+    uint32_t old[L];
+    u64 fresh[L];
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+        old[u] = ~0u;
+        if ((uint32_t)nb[u] < n_keys && wanted(nb[u]))
+            old[u] = __hip_atomic_fetch_or(bit_word(nb[u]), 1u << (nb[u] & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    int total = 0;
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+        fresh[u] = __builtin_amdgcn_ballot_w64(!((old[u] >> (nb[u] & 31)) & 1u));
+        total += __popcll(fresh[u]);
+    }
+    if (total == 0) return;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(n_claimed, total);
+    at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+        if ((fresh[u] >> lane) & 1ull) cid[at + __popcll(fresh[u] & ((1ull << lane) - 1ull))] = nb[u] | flag;
+        at += __popcll(fresh[u]);
+    }
+}
+
 // The whole search of one (sequence, query head) by one workgroup of T threads.
 // N is the number of keys the graph covers; the key rows of a (sequence, KV head) start every
 // kv_stride rows (kv_stride >= N: the cache may hold tokens appended after the index was built).
@@ -400,8 +432,12 @@ __device__ __forceinline__ void touch_line(const void* p, uint32_t lds_off) {
 // take_seed_keys(c0, c1, k0, k1) waits (bounded) for keys c0 and c1 of the set (c1 < 0: only c0; k1 is
 // then k0 again) and leaves 0 for one that did not come, and seeds_missed() is called by one thread
 // when some key did not.
+// kShareSteps says whether workers may take the claims and the scores of its steps (serve_walk below): then steps_shared()
+// says whether they do in this launch, with `parts_log2`, `spin` and the head's `area`, and steps_missed() is called by
+// one thread when an answer did not come.
 struct NoHook {
     static constexpr bool kSeedShare = false;
+    static constexpr bool kShareSteps = false;
 };
 
 // Words that cross workgroups inside one launch: relaxed agent-scope atomics, which go around the
@@ -489,6 +525,189 @@ __device__ __forceinline__ void score_seed_share(int head, int part, int parts, 
     }
 }
 
+// ---- Steps of a walk shared out over workgroups ----------------------------------------------------------
+// A walk whose visited set is in device memory is bound by what one compute unit can take in: it has some 330 cache lines on
+// their way at a time, whatever the load instructions are (a thousand scattered rows of 256 bytes: 5 ticks each from L2, 12 from
+// memory), and an atomic to the visited set takes four ticks. A launch of few searches has compute units to spare, so there a
+// head has 2^parts_log2 worker workgroups. Each owns a share of the keys (the 32-key words of the visited set in turn), claims
+// those of the start set and of all steps' neighbours that are its own, in an LDS bitset of its share, and scores them. What can enter the beam goes back to the head, which picks and merges. Beams are top-ef sets of unions, so no result
+// depends on who scored what. A hand-over (relaxed agent-scope stores, polled) takes 1000 to 1500 ticks one way.
+// A head has one message, which all its workers poll: words with a number of the message in the upper half, one more each time,
+// over all launches (SR_MSG_LAST keeps the last): [0] the number of picks (0: the walk has ended), [1], [2] the
+// worst beam entry that counts, then their ids. An answer, a worker's own: [0] bit 63, keys claimed << 32, keys that can enter the
+// beam, then those; answer 0, to no message, is the start set (the head sends nothing before it: all workers have read by then
+// where the numbers stand). Every word says itself whether it has come. Answers are zeroed by the head
+// when it has taken them, and have two places, used in turn: a word is written again two messages later, when the head has seen its zeroes
+// written (it waits for those of answer k when it has received k + 1: they are by then). Both are stored 64 words at a
+// time: keys stored as they were scored, a few words per instruction, took 2 to 3 us to arrive. All waits are bounded: a head whose
+// answers do not come walks alone from the start, and the handle shares no walk any more, so words that come late are
+// never taken for the next launch's.
+#define SR_VALID (1ull << 63)
+#define SR_MSG_LAST 0             // words of a head's part of the hand-over area
+#define SR_MSG_WORDS 8
+#define SR_ANSWERS_AT (SR_MSG_WORDS + 3 + RA_MAX_EXPAND + 5)
+#define SR_ANSWER_WORDS (RA_WALK_CELLS + 8)
+static_assert(SR_ANSWERS_AT == RA_WALK_HEAD_WORDS && 2 * SR_ANSWER_WORDS == RA_WALK_PART_WORDS, "the allocation's sizes");
+__device__ __forceinline__ u64* sr_answer(u64* area, int part, int k) { return area + SR_ANSWERS_AT + (2 * part + (k & 1)) * SR_ANSWER_WORDS; }
+
+// The rows of the n keys listed in cid (bit 31: enters the beam as expanded) scored, those that beat `worst` added to `kept`.
+template <int KT, int T>
+__device__ __forceinline__ void serve_rows(const char* Kh, const ScoreQuery<KT>& qv, const int* cid, int n, u64 worst, u64* kept,
+                                           int* n_kept) {
+    const int grp = threadIdx.x >> 4, lane16 = threadIdx.x & 15;
+    constexpr int PER = T / 16;
+    auto rows_at = [&](auto rows_c, int c0) __attribute__((always_inline)) {
+        constexpr int R = decltype(rows_c)::value;
+        RowBits<KT> rows[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int c = c0 + u * PER + grp;
+            rows[u] = load_key<KT>(Kh, cid[c < n ? c : 0] & 0x7fffffff, lane16);
+        }
+        const int cw = c0 + (lane16 & (R - 1)) * PER + grp;
+        const int idw = cid[cw < n ? cw : 0];
+        float part[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) part[u] = score_share<KT>(rows[u], qv);
+        const float sc = rows_tree<R>(part, lane16);
+        if (lane16 < R && cw < n) {
+            u64 key = make_key(sc, idw & 0x7fffffff);
+            if (idw < 0) key &= ~1ull;
+            if ((key >> 1) > worst) kept[atomicAdd(n_kept, 1)] = key;
+        }
+    };
+    int c0 = 0;
+    for (; n - c0 > 4 * PER; c0 += SR_UNROLL * PER) rows_at(sr_int<SR_UNROLL>{}, c0);
+    if (n - c0 > 2 * PER) rows_at(sr_int<4>{}, c0);
+    else if (n - c0 > PER) rows_at(sr_int<2>{}, c0);
+    else if (n - c0 > 0) rows_at(sr_int<1>{}, c0);
+}
+
+// LDS bytes of a worker.
+static inline size_t serve_lds_bytes(int64_t N, int deg, int expand, int parts_log2) {
+    return 64 + (size_t)expand * deg * 12 + (size_t)expand * 4 + ((((size_t)(N + 31) >> 5) >> parts_log2) + 1) * 4;
+}
+
+// Worker `part` of `head`. (deg >= 2: see the reciprocals of run_search.)
+template <int DT, int KT, int T>
+__device__ __forceinline__ void serve_walk(unsigned char* lds_raw, int head, int part, int parts_log2, const void* __restrict__ q,
+                                           const int32_t* __restrict__ adj, const int32_t* __restrict__ entry,
+                                           const void* __restrict__ K, int n_q, int n_kv, int64_t N, int64_t kv_stride, int deg,
+                                           int ef, int expand, const int32_t* __restrict__ roots, int root_cap,
+                                           const float* __restrict__ kscale, u64* area, int spin) {
+    const int tid = threadIdx.x, lane = tid & (RA_WAVE - 1), lane16 = tid & 15;
+    const int seq = head / n_q, h = head % n_q, kvh = h / (n_q / n_kv);
+    const size_t esz = DT == RA_BF16 ? 2 : 4;
+    const size_t ksz = KT == RA_KEYS_I8 ? 1 : KT == RA_BF16 ? 2 : 4;
+    const char* Kh = reinterpret_cast<const char*>(K) + ((size_t)seq * n_kv + kvh) * kv_stride * RA_D * ksz;
+    const int32_t* adj_h = adj + (size_t)head * N * deg;
+    const int maxc = expand * deg;
+    int* ctr = reinterpret_cast<int*>(lds_raw);      // [0] claimed, [1] kept, [2] picks, [3] a wait ran out, [4..5] worst
+    u64* worst_at = reinterpret_cast<u64*>(ctr + 4);
+    u64* kept = reinterpret_cast<u64*>(ctr + 16);
+    int* cid = reinterpret_cast<int*>(kept + maxc);
+    int* picks = cid + maxc;
+    uint32_t* bits = reinterpret_cast<uint32_t*>(picks + expand);
+    const uint32_t n_keys = (uint32_t)N, mask = (1u << parts_log2) - 1u;
+    ScoreQuery<KT> qv;
+    load_score_query<DT, KT>(reinterpret_cast<const char*>(q) + (size_t)head * RA_D * esz, lane16, qv);
+    if constexpr (KT == RA_KEYS_I8) {
+        const float* sc = kscale + ((size_t)seq * n_kv + kvh) * RA_D + lane16 * 8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qv.v[e] = __fmul_rn(qv.v[e], sc[e]);
+    }
+    const int e0 = entry[head];
+    const uint32_t last = (uint32_t)xwg_load(area + SR_MSG_LAST);
+    const u64* message = area + SR_MSG_WORDS;
+    const int32_t* root = roots + (size_t)head * root_cap;
+    const int n_root = root[0], n_first = root[1];
+    for (int i = tid; i < (int)((((N + 31) >> 5) >> parts_log2) + 1); i += T) bits[i] = 0u;
+    if (tid < 16) ctr[tid] = 0;
+    __syncthreads();
+    auto mine = [&](int id) __attribute__((always_inline)) { return (((uint32_t)id >> 5) & mask) == (uint32_t)part; };
+    auto word_of = [&](int id) __attribute__((always_inline)) { return bits + (((uint32_t)id >> 5) >> parts_log2); };
+    // the start set (run_search applies the same test)
+    if (n_root <= maxc && (n_first == 0 ? n_root >= 1 : n_first > 1 && expand >= n_first - 1 && ef >= n_first)) {
+        for (int c0 = 0; c0 < n_root; c0 += T) {
+            const int id[1] = {c0 + tid < n_root ? root[2 + c0 + tid] : -1};
+            claim_cells(id, n_keys, c0 + tid < n_first ? (int)0x80000000u : 0, lane, cid, ctr, word_of, mine);
+        }
+    } else if (tid == 0 && mine(e0)) {
+        *word_of(e0) |= 1u << (e0 & 31);             // (scored by the head)
+    }
+    const uint32_t deg_m = 0xffffffffu / (uint32_t)deg + 1u;
+    u64 worst = 0ull;
+    for (int k = 0;; ++k) {
+        __syncthreads();
+        const int n = __builtin_amdgcn_readfirstlane(ctr[0]);
+        serve_rows<KT, T>(Kh, qv, cid, n, worst, kept, &ctr[1]);
+        __syncthreads();
+        const int n_kept = __builtin_amdgcn_readfirstlane(ctr[1]);
+        u64* answer = sr_answer(area, part, k);
+        for (int i = tid; i <= n_kept; i += T) xwg_store(answer + i, i == 0 ? SR_VALID | (u64)n << 32 | (u64)n_kept : kept[i - 1]);
+        // ---- the next message
+        const uint32_t number = last + 1u + (uint32_t)k;
+        if (tid < expand) {
+            u64 w[3] = {0ull, 0ull, 0ull}, own = 0ull;
+            bool came = false;
+            for (int i = 0; i < spin; ++i) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    if ((uint32_t)(w[j] >> 32) != number) w[j] = xwg_load(message + j);
+                if ((uint32_t)(own >> 32) != number) own = xwg_load(message + 3 + tid);
+                came = (uint32_t)(w[0] >> 32) == number && (uint32_t)(w[1] >> 32) == number && (uint32_t)(w[2] >> 32) == number &&
+                       (tid >= (int)(uint32_t)w[0] || (uint32_t)(own >> 32) == number);
+                if (came) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (!came) ctr[3] = 1;
+            picks[tid] = (int)(uint32_t)own;
+            if (tid == 0) {
+                ctr[2] = (int)(uint32_t)w[0];
+                *worst_at = w[1] << 32 | (uint32_t)w[2];
+            }
+        }
+        __syncthreads();
+        const int np = __builtin_amdgcn_readfirstlane(ctr[3] ? 0 : ctr[2]);
+        if (np == 0) return;
+        if (tid == 0) {
+            ctr[0] = 0;
+            ctr[1] = 0;
+        }
+        worst = *worst_at;
+        const int cells = np * deg;
+        __syncthreads();
+        if ((deg & 3) == 0) {
+            // rows are 16-byte aligned: four cells per load
+            const int quads = cells >> 2;
+            for (int x0 = 0; x0 < quads; x0 += 2 * T) {
+                int nb[8];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int x = 4 * min(x0 + u * T + tid, quads - 1), xr = (int)__umulhi((uint32_t)x, deg_m);
+                    const int4 v = *reinterpret_cast<const int4*>(adj_h + (size_t)picks[xr] * deg + (x - xr * deg));
+                    nb[4 * u] = v.x; nb[4 * u + 1] = v.y; nb[4 * u + 2] = v.z; nb[4 * u + 3] = v.w;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) nb[u] = x0 + (u / 4) * T + tid < quads ? nb[u] : -1;
+                claim_cells(nb, n_keys, 0, lane, cid, ctr, word_of, mine);
+            }
+        } else {
+            for (int x0 = 0; x0 < cells; x0 += 4 * T) {
+                int nb[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int x = min(x0 + u * T + tid, cells - 1), xr = (int)__umulhi((uint32_t)x, deg_m);
+                    nb[u] = adj_h[(size_t)picks[xr] * deg + (x - xr * deg)];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) nb[u] = x0 + u * T + tid < cells ? nb[u] : -1;
+                claim_cells(nb, n_keys, 0, lane, cid, ctr, word_of, mine);
+            }
+        }
+    }
+}
+
 template <int DT, int KT, bool GBITS, int T, typename Hook>
 __device__ __forceinline__ int run_search(
     unsigned char* lds_raw, int head, const void* __restrict__ q, const int32_t* __restrict__ adj,
@@ -563,8 +782,17 @@ __device__ __forceinline__ int run_search(
         n_first = root[1];
         my_root = root[2 + (tid < root_cap - 2 ? tid : 0)];      // unconditional: same trip as the header
     }
+    bool sharing = false;            // claims and scores by the walk's workers (serve_walk)
+    if constexpr (Hook::kShareSteps) sharing = hook.steps_shared();
+    int n_posted = 0;
+    uint32_t last_message = 0u;
+    if constexpr (Hook::kShareSteps) last_message = (uint32_t)xwg_load(hook.area + SR_MSG_LAST);
+    int bn, n_visited, n_expanded, n_iters;
+    bool walked = true;
+    do {                             // (a second time, alone, when an answer did not come)
     // (the loads above are in flight while the LDS state is cleared)
-    for (int i = tid; i < nwords; i += T) bits[i] = 0u;
+    if (!sharing)
+        for (int i = tid; i < nwords; i += T) bits[i] = 0u;
     for (int i = tid; i < maxc + nhist; i += T) cnt[i] = 0;      // cnt, hist and hsum
     // A seed set (ra_launch_seeds) has the same layout with [1] = 0: the walk starts from all of its
     // keys at once, scored in one gather, the best ef of them in the beam and none of them expanded.
@@ -578,18 +806,19 @@ __device__ __forceinline__ int run_search(
 #ifdef SR_WAVE_CLOCKS
     if (head == 0 && tid == 0) sr_wave_ticks[1] = wall_clock64();
 #endif
-    int bn, n_visited, n_expanded, n_iters;
     bool first = fill;               // the coming step is that doubled first step
+    if (Hook::kShareSteps && tid == 0) ctr[C_MISSED] = 0;
     if (fill) {
-        for (int c = tid; c < n_root; c += T) {
-            const int id = c == tid ? my_root : root[2 + c];
-            cid[c] = id;
-            (void)claim_key(bits, id);
-        }
+        if (!sharing)
+            for (int c = tid; c < n_root; c += T) {
+                const int id = c == tid ? my_root : root[2 + c];
+                cid[c] = id;
+                (void)claim_key(bits, id);
+            }
         if (tid == 0) {
             urank[0] = 0;
-            cc[S_NCAND] = n_root;
-            cc[S_NKEEP] = n_root;            // every key of a start set is kept (scored below)
+            cc[S_NCAND] = sharing ? 0 : n_root;      // (then added up from the workers' answers)
+            cc[S_NKEEP] = sharing ? 0 : n_root;      // every key of a start set is kept (scored below)
             cc[S_NUNEXP] = 0;
             ctr[C_LO] = -1;                  // as unsigned: the largest value; see the pre-filter below
             ctr[C_HI] = 0;
@@ -610,7 +839,7 @@ __device__ __forceinline__ int run_search(
                 cc[S_NCAND] = 0;
                 cc[S_NKEEP] = 0;
                 cc[S_NUNEXP] = 1;
-                (void)claim_key(bits, e0);
+                if (!sharing) (void)claim_key(bits, e0);
             }
         }
         bn = 1; n_visited = 1; n_expanded = 0; n_iters = 0;
@@ -638,7 +867,73 @@ __device__ __forceinline__ int run_search(
 #ifdef SR_WAVE_CLOCKS
     if (head == 0 && tid == 0) sr_wave_ticks[2] = wall_clock64();      // claims made
 #endif
-    if (fill) {
+    // The workers' answers to the last message: the keys go to ckey. A worker's are taken by up to 64 threads, of one wavefront (the word
+    // that says how many there are is read by all of them before one zeroes it), each asking for a key together with that word. With the extremes of the ordered score bits.
+    auto collect = [&](uint32_t& lo, uint32_t& hi, int spin_shift) __attribute__((always_inline)) {
+        if constexpr (Hook::kShareSteps) {
+            const int spin = max(hook.spin >> spin_shift, 1), per_log2 = min((T == 1024 ? 10 : 9) - hook.parts_log2, 6);
+            const int per = 1 << per_log2, sub = tid & (per - 1);
+            if (tid >> (per_log2 + hook.parts_log2)) return;
+            u64* a = sr_answer(hook.area, tid >> per_log2, n_posted);
+            u64 n_word = 0ull, k0 = 0ull;
+            int n = 0;
+            bool came = false;
+            for (int i = 0; i < spin; ++i) {
+                if (n_word == 0ull) n_word = xwg_load(a);
+                if (k0 == 0ull) k0 = xwg_load(a + 1 + sub);
+                n = (int)(n_word & 0xffffffffull);
+                came = n_word != 0ull && (sub >= n || k0 != 0ull);
+                if (came) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (!came) {
+                ctr[C_MISSED] = 1;
+                n = 0;
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the zeroes in the answers before these are written
+            if (came && sub == 0) {
+                atomicAdd(&cc[S_NCAND], (int)((n_word >> 32) & 0x7fffffffull));
+                xwg_store(a, 0ull);
+            }
+            for (int i = sub; __builtin_amdgcn_ballot_w64(i < n) != 0ull; i += per) {
+                u64 k = i == sub && i < n ? k0 : 0ull;
+                for (int t = 0; t < spin && k == 0ull && i < n; ++t) k = xwg_load(a + 1 + i);
+                if (i < n && k == 0ull) ctr[C_MISSED] = 1;
+                const u64 m = __builtin_amdgcn_ballot_w64(k != 0ull);
+                int at = 0;
+                if (lane == 0 && m) at = atomicAdd(&cc[S_NKEEP], __popcll(m));
+                at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1ull));
+                if (k != 0ull) {
+                    xwg_store(a + 1 + i, 0ull);
+                    ckey[at] = k;
+                    const uint32_t so = (uint32_t)(k >> 32);
+                    lo = min(lo, so);
+                    hi = max(hi, so);
+                }
+            }
+        }
+    };
+    // the first np picks to the workers (0: the walk has ended)
+    auto post = [&](int np, u64 worst) __attribute__((always_inline)) {
+        if constexpr (Hook::kShareSteps) {
+            ++n_posted;
+            const u64 number = (u64)(last_message + (uint32_t)n_posted) << 32;
+            if (tid < np + 3)                // (at most RA_MAX_EXPAND + 3 words: one per thread)
+                xwg_store(hook.area + SR_MSG_WORDS + tid, number | (tid == 0 ? (uint32_t)np : tid == 1 ? (uint32_t)(worst >> 32) :
+                                                                    tid == 2 ? (uint32_t)worst : (uint32_t)picks[tid - 3]));
+        }
+    };
+    if (Hook::kShareSteps && sharing) {
+        uint32_t lo = 0xffffffffu, hi = 0u;
+        collect(lo, hi, 3);      // (workers that have not started by then may be long in coming)
+        if (fill) {
+            wave_min_max(lo, hi);
+            if (lane == RA_WAVE - 1) {
+                atomicMin(reinterpret_cast<unsigned int*>(&ctr[C_LO]), lo);
+                atomicMax(reinterpret_cast<unsigned int*>(&ctr[C_HI]), hi);
+            }
+        }
+    } else if (fill) {
         // ---- the start set is scored here, ahead of the loop, where few registers are live: twice
         //      the rows in flight of a step's gather (a seed set of a thousand keys is one trip to
         //      memory for 1024 threads). The beam is empty, so every key is kept; the first
@@ -800,6 +1095,19 @@ __device__ __forceinline__ int run_search(
             for (int i = tid; i < nhist; i += T) hist[i] = 0;
             hist_used = false;
         }
+        if (Hook::kShareSteps && sharing) {
+            // ---- the workers claim and score; their answers are waited for
+            if (!first) {
+                post(np, bn == ef ? (cur[bn - 1] >> 1) : 0ull);
+                uint32_t lo = 0xffffffffu, hi = 0u;
+                collect(lo, hi, 0);
+            }
+            __syncthreads();
+            walked = ctr[C_MISSED] == 0;
+            if (!walked) break;
+            n_visited += __builtin_amdgcn_readfirstlane(cc[S_NCAND]);
+            SR_TICK(1);
+        } else {
         // ---- read the picked adjacency rows (all loads issued before any is consumed),
         //      claim unvisited neighbours (the doubled first step has its candidates already)
         if (!first) {
@@ -893,6 +1201,7 @@ __device__ __forceinline__ int run_search(
             }
         }
         __syncthreads();
+        }
         int nk = __builtin_amdgcn_readfirstlane(cc[S_NKEEP]);
         SR_TICK(2);
         if (__builtin_expect(nk == 0, 0)) {               // uniform: nothing enters the beam
@@ -1229,6 +1538,20 @@ __device__ __forceinline__ int run_search(
         picked = true;
         first = false;
     }
+
+    if constexpr (Hook::kShareSteps)
+        if (sharing) {
+            post(0, 0ull);
+            if (tid == 0) xwg_store(hook.area + SR_MSG_LAST, (u64)(last_message + (uint32_t)n_posted));
+            if (!walked) {
+                if (tid == 0) hook.steps_missed();
+                sharing = false;
+                __syncthreads();
+                continue;
+            }
+        }
+    break;
+    } while (true);
 
     __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): no touch of this wavefront still has to land in LDS
     // ---- result: best-first beam entries outside the static set W = [0,s) u [N-w,N). A short list is the

@@ -785,3 +785,40 @@ def test_graphs_of_degree_one(expand):
                            to_np(q[0, 0]), to_np(K[0, 0]), to_np(V[0, 0]), adj[0], int(ent[0]), 2, 5, 10, ef, expand,
                            1e-5, exact=True, n_seeds=n_seeds)
     idx.free()
+
+
+@pytest.mark.parametrize("dtype,n_q,deg,expand,ef,seeds,q8", [
+    (torch.bfloat16, 1, 64, 64, 1024, 0, False),       # 4096 cells, the most a worker answers for; 16 workers
+    (torch.bfloat16, 20, 24, 128, 512, 1500, False),   # 8 workers, two rows of workgroups per compute die, seed sets
+    (torch.float32, 3, 63, 64, 1024, 0, False),        # rows of no multiple of four cells
+    (torch.float32, 2, 64, 48, 600, 0, False),         # fewer picks than the entry point has neighbours: no start set
+    (torch.bfloat16, 2, 48, 64, 512, 2048, True)])     # 8-bit keys
+def test_walks_that_share_their_steps(dtype, n_q, deg, expand, ef, seeds, q8):
+    """Walks whose visited set is in device memory claim and score through workers of their own in ra_decode_step:
+    ids and counters are those of ra_search, which walks alone, in repeated calls and when no worker answers."""
+    from paper_2409_10516_amd import binding as B
+    N, topk = 1_100_003, 100
+    g = torch.Generator(device=DEV).manual_seed(deg * 1000 + n_q)
+    adj = torch.randint(-1, N, (n_q, N, deg), generator=g, device=DEV, dtype=torch.int32)
+    adj[:, ::7, 5:] = -1
+    entry = torch.randint(0, N, (n_q,), generator=g, device=DEV, dtype=torch.int32)
+    idx = ra.ra_index_import(adj.cpu(), entry.cpu(), 1, n_q, 1)
+    del adj
+    K = torch.randn((1, 1, N, 128), generator=g, device=DEV).to(dtype)
+    V = torch.randn((1, 1, N, 128), generator=g, device=DEV).to(dtype)
+    q = torch.randn((3, 1, n_q, 128), generator=g, device=DEV).to(dtype)
+    idx.configure(B.RA_CFG_SEEDS, seeds)
+    k8 = ra.ra_quantize_keys(K) if q8 else None
+    more = {"k8": k8} if q8 else {}
+    alone = [ra.ra_search(q[t], idx, None if q8 else K, 4, 500, topk, ef, expand, **more) for t in range(3)]
+    assert all(st[..., 0].min() > 3000 for _, st in alone)
+    outs = []
+    for silent, spin in ((0, 20000), (1, 2), (0, 20000)):
+        idx.test_configure(B.RA_TEST_HELPERS_SILENT, silent)
+        idx.configure(B.RA_CFG_HELPER_SPIN, spin)
+        for t in (0, 1, 2, 0):
+            out, lse, ids, st = ra.ra_decode_step(q[t], idx, K, V, 4, 500, topk, ef, expand, **more)
+            assert torch.equal(ids, alone[t][0]) and torch.equal(st, alone[t][1]), (silent, t)
+            outs.append(out)
+    # the same sets attended to: float32 sums over some 600 rows in another order, values of norm about 1
+    assert all(torch.allclose(a, b, rtol=0, atol=1e-5) for a, b in zip(outs[:4], outs[4:8]))
