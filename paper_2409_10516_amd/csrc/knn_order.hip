@@ -11,7 +11,8 @@
 // Three steps per head, none of which can change a result:
 //   ko_meanq_kernel   sum of a strided sample of the head's prefill queries (fixed order)
 //   ko_proxy_kernel   64-bit sort keys [~ordered(<mean, k_i>):32][i:32], all ones beyond N
-//   ko_sort_*         bitonic sort, ascending: chunks in LDS, the wider exchanges in memory
+//   ko_sort_*         ascending sort: chunks by score in LDS, then a bitonic network over them, its wider exchanges
+//                     in memory
 // so entry p is the key of p-th largest inner product (lower id first among equals) and the KNN
 // kernel reads the id of stream position p as the low word of entry p, ready to use.
 #include "common.h"
@@ -21,6 +22,8 @@ typedef unsigned long long u64;
 #define KO_SAMPLE 4096            // prefill queries summed per head (at most)
 #define KO_CHUNK 8192             // sort keys a workgroup holds in LDS (64 KB)
 #define KO_THREADS 1024
+#define KO_BINS 2048              // of a chunk's scores
+#define KO_BIN_MOST 96            // keys in one bin that are still ordered by comparing them with each other
 
 template <int DT>
 __device__ __forceinline__ void ko_row8(const void* base, size_t at, float (&v)[8]) {
@@ -116,6 +119,123 @@ __device__ __forceinline__ int64_t ko_run(int64_t n) {
     return n <= 1 ? 1 : (int64_t)1 << (64 - __clzll((long long)(n - 1)));
 }
 
+// Stage k of the network, from distance half a chunk at most, on the chunk in LDS (filled, with a barrier after).
+__device__ __forceinline__ void ko_stage(u64* s, int chunk, int64_t base, int64_t k) {
+    const int j_top = k > chunk ? chunk / 2 : (int)(k / 2);
+    for (int j = j_top; j >= 1; j >>= 1) {
+        for (int t = threadIdx.x; t < chunk / 2; t += KO_THREADS) {
+            const int e = ((t & ~(j - 1)) << 1) | (t & (j - 1));      // bit j clear
+            ko_exchange(s, e, j, ((base + e) & k) == 0);
+        }
+        __syncthreads();
+    }
+}
+
+// grid: x = chunk, y = array of score keys (ko_proxy_kernel). Sorts each chunk, ascending or descending as the network over the
+// chunks wants it. The network's 91 exchanges of 8192 keys are 91 round trips through LDS and barriers (73 us for 64
+// arrays of 5003, now 13); here keys are dealt to 2048 equal-width bins of their score, and a key's place is the keys in earlier bins
+// plus the smaller keys of its own, of which there are about ten where scores are densest. A chunk
+// with a crowded bin (equal scores, a wide outlier), or whose scores' width is not finite, takes the network.
+__global__ __launch_bounds__(KO_THREADS) void ko_sort_scores_kernel(u64* __restrict__ keys, size_t stride, int chunk) {
+    extern __shared__ __align__(16) unsigned char ko_lds[];
+    constexpr int PER = KO_CHUNK / KO_THREADS, OWN = KO_BINS / KO_THREADS, WAVES = KO_THREADS / RA_WAVE;
+    u64* s = reinterpret_cast<u64*>(ko_lds);
+    int* start = reinterpret_cast<int*>(s + chunk);               // [KO_BINS + 1] counts, then first places
+    int* wave_sum = start + KO_BINS + 1;
+    unsigned* ends = reinterpret_cast<unsigned*>(wave_sum + WAVES);       // smallest and largest upper half; [2] a bin is crowded
+    const int tid = threadIdx.x, lane = tid % RA_WAVE, wv = tid / RA_WAVE;
+    const int64_t base = (int64_t)blockIdx.x * chunk;
+    u64* g = keys + (size_t)blockIdx.y * stride + base;
+    u64 k[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) k[r] = r * KO_THREADS + tid < chunk ? g[r * KO_THREADS + tid] : ~0ull;
+    for (int b = tid; b < KO_BINS; b += KO_THREADS) start[b] = 0;
+    if (tid < 3) ends[tid] = tid == 0 ? 0xffffffffu : 0u;
+    __syncthreads();
+    unsigned lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+        if (k[r] != ~0ull) {                                      // (places beyond N)
+            lo = min(lo, (unsigned)(k[r] >> 32));
+            hi = max(hi, (unsigned)(k[r] >> 32));
+        }
+    for (int d = RA_WAVE / 2; d >= 1; d >>= 1) {
+        lo = min(lo, (unsigned)__shfl_xor((int)lo, d));
+        hi = max(hi, (unsigned)__shfl_xor((int)hi, d));
+    }
+    if (lane == 0) {
+        atomicMin(&ends[0], lo);
+        atomicMax(&ends[1], hi);
+    }
+    __syncthreads();
+    if (ends[0] > ends[1]) return;                                // nothing but places beyond N
+    // the upper halves are complements: the smallest is the largest score. Every operation is monotone in the score, so a
+    // larger score is never in a later bin.
+    const float top = f32_from_ordered(~ends[0]), width = top - f32_from_ordered(~ends[1]);
+    const float to_bin = width > 0.f && width < INFINITY ? (float)(KO_BINS - 1) / width : 0.f;
+    int bin[PER], at[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const float b = (top - f32_from_ordered(~(uint32_t)(k[r] >> 32))) * to_bin;
+        bin[r] = b >= (float)(KO_BINS - 1) ? KO_BINS - 1 : b > 0.f ? (int)b : 0;
+        at[r] = k[r] != ~0ull ? atomicAdd(&start[bin[r]], 1) : 0;
+    }
+    __syncthreads();
+    int own[OWN], sum = 0;
+    bool crowded = false;
+#pragma unroll
+    for (int b = 0; b < OWN; ++b) {
+        own[b] = start[OWN * tid + b];
+        crowded = crowded || own[b] > KO_BIN_MOST;
+        sum += own[b];
+    }
+    int incl = sum;
+    for (int d = 1; d < RA_WAVE; d <<= 1) {
+        const int v = __shfl_up(incl, d);
+        if (lane >= d) incl += v;
+    }
+    if (lane == RA_WAVE - 1) wave_sum[wv] = incl;
+    if (crowded) ends[2] = 1u;
+    __syncthreads();
+    if (ends[2]) {                                                // (uniform)
+#pragma unroll
+        for (int r = 0; r < PER; ++r)
+            if (r * KO_THREADS + tid < chunk) s[r * KO_THREADS + tid] = k[r];
+        __syncthreads();
+        for (int64_t size = 2; size <= chunk; size <<= 1) ko_stage(s, chunk, base, size);
+        for (int e = tid; e < chunk; e += KO_THREADS) g[e] = s[e];
+        return;
+    }
+    int before = incl - sum;
+    for (int w = 0; w < wv; ++w) before += wave_sum[w];
+#pragma unroll
+    for (int b = 0; b < OWN; ++b) {
+        start[OWN * tid + b] = before;
+        before += own[b];
+    }
+    if (tid == KO_THREADS - 1) start[KO_BINS] = before;           // the chunk's keys
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+        if (k[r] != ~0ull) s[start[bin[r]] + at[r]] = k[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const int b0 = start[bin[r]], b1 = start[bin[r] + 1];
+        at[r] = b0;
+        for (int j = b0; j < b1; ++j) at[r] += s[j] < k[r] ? 1 : 0;
+    }
+    const int n = start[KO_BINS];
+    const bool descending = (base & chunk) != 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+        if (k[r] != ~0ull) s[descending ? chunk - 1 - at[r] : at[r]] = k[r];
+    for (int e = n + tid; e < chunk; e += KO_THREADS) s[descending ? chunk - 1 - e : e] = ~0ull;
+    __syncthreads();
+    for (int e = tid; e < chunk; e += KO_THREADS) g[e] = s[e];
+}
+
 // grid: x = chunk, y = array. k_first == 0: sorts the chunk (all k up to its length); otherwise
 // finishes stage k_first of the global network (j from half a chunk down to 1).
 __global__ __launch_bounds__(KO_THREADS) void ko_sort_chunk_kernel(u64* __restrict__ keys, size_t stride,
@@ -131,17 +251,7 @@ __global__ __launch_bounds__(KO_THREADS) void ko_sort_chunk_kernel(u64* __restri
     u64* g = keys + (size_t)blockIdx.y * stride + base;
     for (int e = threadIdx.x; e < chunk; e += KO_THREADS) s[e] = k_first || base + e < n ? g[e] : ~0ull;
     __syncthreads();
-    const int pairs = chunk / 2;
-    for (int64_t k = k_first ? k_first : 2; k_first ? k == k_first : k <= chunk; k <<= 1) {
-        const int j_top = k > chunk ? chunk / 2 : (int)(k / 2);
-        for (int j = j_top; j >= 1; j >>= 1) {
-            for (int t = threadIdx.x; t < pairs; t += KO_THREADS) {
-                const int e = ((t & ~(j - 1)) << 1) | (t & (j - 1));      // bit j clear
-                ko_exchange(s, e, j, ((base + e) & k) == 0);
-            }
-            __syncthreads();
-        }
-    }
+    for (int64_t k = k_first ? k_first : 2; k_first ? k == k_first : k <= chunk; k <<= 1) ko_stage(s, chunk, base, k);
     for (int e = threadIdx.x; e < chunk; e += KO_THREADS) g[e] = s[e];
 }
 
@@ -161,7 +271,8 @@ __global__ __launch_bounds__(KO_THREADS) void ko_sort_far_kernel(u64* __restrict
 }
 
 // Ascending sort of n_arrays arrays of 64-bit keys, `stride` keys apart, of N_pad (a power of two)
-// places each; `counts` (device, one int every count_stride): how many keys each holds, or null: N_pad.
+// places each; `counts` (device, one int every count_stride): how many keys each holds, or null: N_pad, and the keys'
+// upper halves are scores (ko_proxy_kernel). Chunks of keys with counts, popularities with few values each, take the network.
 ra_status ra_launch_sort(void* keys, size_t stride, int n_arrays, int64_t N_pad, const int32_t* counts,
                          size_t count_stride, hipStream_t st) {
     u64* k64 = reinterpret_cast<u64*>(keys);
@@ -170,8 +281,14 @@ ra_status ra_launch_sort(void* keys, size_t stride, int n_arrays, int64_t N_pad,
     const dim3 cgrid((unsigned)(N_pad / chunk), (unsigned)n_arrays);
     const dim3 fgrid((unsigned)((N_pad / 2 + KO_THREADS - 1) / KO_THREADS), (unsigned)n_arrays);
     RA_LDS_OPT_IN(ko_sort_chunk_kernel, lds);
-    hipLaunchKernelGGL(ko_sort_chunk_kernel, cgrid, dim3(KO_THREADS), lds, st, k64, stride, N_pad, chunk, (int64_t)0,
-                       counts, count_stride);
+    if (counts) {
+        hipLaunchKernelGGL(ko_sort_chunk_kernel, cgrid, dim3(KO_THREADS), lds, st, k64, stride, N_pad, chunk, (int64_t)0,
+                           counts, count_stride);
+    } else {
+        const size_t lds_scores = lds + (KO_BINS + 1 + KO_THREADS / RA_WAVE + 3) * sizeof(int);
+        RA_LDS_OPT_IN(ko_sort_scores_kernel, lds_scores);
+        hipLaunchKernelGGL(ko_sort_scores_kernel, cgrid, dim3(KO_THREADS), lds_scores, st, k64, stride, chunk);
+    }
     for (int64_t k = 2 * (int64_t)chunk; k <= N_pad; k <<= 1) {
         for (int64_t j = k / 2; j >= chunk; j >>= 1)
             hipLaunchKernelGGL(ko_sort_far_kernel, fgrid, dim3(KO_THREADS), 0, st, k64, stride, N_pad, k, j, counts,

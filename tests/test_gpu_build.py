@@ -94,6 +94,30 @@ def test_knn_monotone_stream(dtype, knn, rising, knn_selection):
     assert np.array_equal(L, np.broadcast_to(want, (M, knn)))
 
 
+@pytest.mark.parametrize("N", [1, 2, 1025, 8191, 8192, 8193, 20001])
+@pytest.mark.parametrize("scores", ["equal", "few", "outlier", "spread", "overflow"])
+def test_knn_stream_order_of_any_scores(N, scores):
+    """The stream order deals a chunk of up to 8192 keys to bins of their score: one bin holds all, crowded bins, all but
+    one key in one bin, no crowd, and a width that is not finite. Every key has to come out of it once: scores are
+    whole numbers (float32, exact), so the lists are the best by score, then by id."""
+    rng = np.random.default_rng(N)
+    M, knn = 33, min(16, N)
+    K = np.zeros((N, 128))
+    place = {"equal": np.zeros(N), "few": rng.integers(-2, 3, N), "outlier": (np.arange(N) == N // 2) * 4e6,
+             "spread": rng.integers(-4000, 4001, N), "overflow": rng.integers(-2, 3, N) * 2.0 ** 126}[scores]
+    K[:, 0] = place
+    K[:, 1] = rng.integers(-500, 501, N)
+    Q = np.zeros((M, 128))
+    Q[:, 0] = 2.0 if scores == "overflow" else 1.0            # (the mean query's products overflow; the last rows' do not)
+    Q[-3:, 0] = 0
+    Q[:, 1] = np.arange(M) % 3 - 1
+    L = ra.ra_knn(torch.from_numpy(K).float()[None, None].to(DEV), torch.from_numpy(Q).float()[None, None].to(DEV), knn)
+    L = L.cpu().numpy()[0, 0]
+    for j in range(M - 3 if scores == "overflow" else 0, M):
+        want = np.argsort(-(K @ Q[j]), kind="stable")[:knn]
+        assert np.array_equal(L[j][:len(want)], want) and np.all(L[j][len(want):] == -1), (scores, j)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("knn", [32, 48, 64])
 def test_knn_scores_that_are_no_numbers(dtype, knn):
