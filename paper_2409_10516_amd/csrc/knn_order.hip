@@ -22,6 +22,7 @@ typedef unsigned long long u64;
 #define KO_SAMPLE 4096            // prefill queries summed per head (at most)
 #define KO_CHUNK 8192             // sort keys a workgroup holds in LDS (64 KB)
 #define KO_THREADS 1024
+#define KO_MEAN_T 256             // 64 groups of 4 lanes
 #define KO_BINS 2048              // of a chunk's scores
 #define KO_BIN_MOST 96            // keys in one bin that are still ordered by comparing them with each other
 
@@ -38,14 +39,15 @@ __device__ __forceinline__ void ko_row8(const void* base, size_t at, float (&v)[
     }
 }
 
-// grid: x = head. 16 lanes per query row; lane group s sums samples s, s + 64, ... eight rows in flight
+// grid: x = head, y = quarter of the dimensions (a head's 4096 rows are what one compute unit takes in in 19 us). 4 lanes per
+// row; lane group s sums samples s, s + 64, ... sixteen rows in flight
 // (a serial sum of rows, one at a time, was 265 us of latency whatever the size of the input).
 template <int DT>
-__global__ __launch_bounds__(KO_THREADS) void ko_meanq_kernel(const void* __restrict__ Q, int64_t M,
-                                                              float* __restrict__ mq) {
-    constexpr int GROUPS = KO_THREADS / 16, FLY = 8;
-    __shared__ float part[GROUPS][RA_D];
-    const int graph = blockIdx.x, l16 = threadIdx.x & 15, s = threadIdx.x / 16;
+__global__ __launch_bounds__(KO_MEAN_T) void ko_meanq_kernel(const void* __restrict__ Q, int64_t M,
+                                                             float* __restrict__ mq) {
+    constexpr int GROUPS = KO_MEAN_T / 4, FLY = 16, DIMS = RA_D / 4;
+    __shared__ float part[GROUPS][DIMS];
+    const int graph = blockIdx.x, d0 = blockIdx.y * DIMS, l4 = threadIdx.x & 3, s = threadIdx.x / 4;
     const int n_s = M < KO_SAMPLE ? (int)M : KO_SAMPLE;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int k0 = s; k0 < n_s; k0 += FLY * GROUPS) {
@@ -54,7 +56,7 @@ __global__ __launch_bounds__(KO_THREADS) void ko_meanq_kernel(const void* __rest
         for (int u = 0; u < FLY; ++u) {
             const int k = k0 + u * GROUPS < n_s ? k0 + u * GROUPS : k0;
             const int64_t j = M <= KO_SAMPLE ? k : (int64_t)k * M / KO_SAMPLE;
-            ko_row8<DT>(Q, ((size_t)graph * M + j) * RA_D + 8 * l16, v[u]);
+            ko_row8<DT>(Q, ((size_t)graph * M + j) * RA_D + d0 + 8 * l4, v[u]);
         }
 #pragma unroll
         for (int u = 0; u < FLY; ++u)
@@ -63,12 +65,12 @@ __global__ __launch_bounds__(KO_THREADS) void ko_meanq_kernel(const void* __rest
                 for (int c = 0; c < 8; ++c) acc[c] += v[u][c];
     }
 #pragma unroll
-    for (int c = 0; c < 8; ++c) part[s][8 * l16 + c] = acc[c];
+    for (int c = 0; c < 8; ++c) part[s][8 * l4 + c] = acc[c];
     __syncthreads();
-    if (threadIdx.x < RA_D) {
+    if (threadIdx.x < DIMS) {
         float t = 0.f;
         for (int i = 0; i < GROUPS; ++i) t += part[i][threadIdx.x];
-        mq[(size_t)graph * RA_D + threadIdx.x] = t;
+        mq[(size_t)graph * RA_D + d0 + threadIdx.x] = t;
     }
 }
 
@@ -329,11 +331,11 @@ ra_status ra_launch_knn_order(const void* K, const void* Q, ra_dtype dt, int n_s
     float* mq = reinterpret_cast<float*>(keys + (size_t)graphs * N_pad);
     const dim3 pgrid((unsigned)((N_pad + KO_THREADS / 16 - 1) / (KO_THREADS / 16)), (unsigned)graphs);
     if (dt == RA_BF16) {
-        hipLaunchKernelGGL(ko_meanq_kernel<RA_BF16>, dim3(graphs), dim3(KO_THREADS), 0, st, Q, M, mq);
+        hipLaunchKernelGGL(ko_meanq_kernel<RA_BF16>, dim3(graphs, 4), dim3(KO_MEAN_T), 0, st, Q, M, mq);
         hipLaunchKernelGGL(ko_proxy_kernel<RA_BF16>, pgrid, dim3(KO_THREADS), 0, st, K, mq, n_q, n_kv, N,
                            N_pad, keys);
     } else {
-        hipLaunchKernelGGL(ko_meanq_kernel<RA_F32>, dim3(graphs), dim3(KO_THREADS), 0, st, Q, M, mq);
+        hipLaunchKernelGGL(ko_meanq_kernel<RA_F32>, dim3(graphs, 4), dim3(KO_MEAN_T), 0, st, Q, M, mq);
         hipLaunchKernelGGL(ko_proxy_kernel<RA_F32>, pgrid, dim3(KO_THREADS), 0, st, K, mq, n_q, n_kv, N,
                            N_pad, keys);
     }
