@@ -758,6 +758,34 @@ def test_root_set_much_larger_than_the_beam(dtype):
         idx.free()
 
 
+@pytest.mark.parametrize("deg,expand,ef", [(32, 32, 64), (32, 32, 500), (31, 33, 64), (24, 256, 25), (64, 64, 900)])
+@pytest.mark.parametrize("spread", [1, 1000])
+def test_root_sets_ordered_by_bins(deg, expand, ef, spread):
+    """Root sets beyond the pre-filter's limit (float32) are ordered through bins of their scores where a step has 1024 cells or more
+    (31 * 33 are 1023), with ties by the dozen (spread 1) and with all but one key in the lowest bins (spread 1000).
+    Integer inputs, so ids and counters are the oracle's."""
+    rng = np.random.default_rng(deg * expand + ef)
+    N = 3000
+    adj = np.stack([rng.permutation(N)[:deg] for _ in range(N)]).astype(np.int32)[None]
+    adj[0, ::5, 3] = -1
+    ent = np.array([17], np.int32)
+    first = [int(x) for x in adj[0][17] if x >= 0]
+    root = {17, *first, *(int(x) for a in first for x in adj[0][a] if x >= 0)}
+    assert len(root) > ef + 64 and expand >= len(first)
+    K = rng.integers(-1, 2, size=(1, 1, N, 128)).astype(np.float32)
+    K[0, 0, first[0]] *= spread
+    K = torch.from_numpy(K)
+    V = torch.from_numpy(rng.standard_normal((1, 1, N, 128)).astype(np.float32))
+    q = torch.from_numpy(rng.integers(-1, 2, size=(1, 1, 128)).astype(np.float32))
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.from_numpy(ent), 1, 1, 1)
+    out, lse, ids, st = ra.ra_decode_step(q.to(DEV), idx, K.to(DEV), V.to(DEV), 2, 5, 20, ef, expand)
+    ids_s, st_s = ra.ra_search(q.to(DEV), idx, K.to(DEV), 2, 5, 20, ef, expand)
+    assert torch.equal(ids_s, ids) and torch.equal(st_s, st)
+    decode_matches(out[0, 0].cpu().numpy(), float(lse[0, 0]), ids[0, 0].tolist(), st[0, 0].tolist(), to_np(q[0, 0]),
+                   to_np(K[0, 0]), to_np(V[0, 0]), adj[0], 17, 2, 5, 20, ef, expand, 1e-5, exact=True)
+    idx.free()
+
+
 @pytest.mark.parametrize("expand", [2, 8, 256])
 def test_graphs_of_degree_one(expand):
     """The smallest degree an imported graph can have: one adjacency cell per pick. A walk has several picks
