@@ -22,6 +22,7 @@ typedef unsigned long long u64;
 #define KO_SAMPLE 4096            // prefill queries summed per head (at most)
 #define KO_CHUNK 8192             // sort keys a workgroup holds in LDS (64 KB)
 #define KO_THREADS 1024
+#define KO_FLY 4                  // key rows in flight per 16 lanes
 #define KO_MEAN_T 256             // 64 groups of 4 lanes
 #define KO_BINS 2048              // of a chunk's scores
 #define KO_BIN_MOST 96            // keys in one bin that are still ordered by comparing them with each other
@@ -39,7 +40,7 @@ __device__ __forceinline__ void ko_row8(const void* base, size_t at, float (&v)[
     }
 }
 
-// grid: x = head, y = quarter of the dimensions (a head's 4096 rows are what one compute unit takes in in 19 us). 4 lanes per
+// grid: x = head, y = quarter of the dimensions (64 heads x 4096 rows: 19 us with one workgroup per head, now 14). 4 lanes per
 // row; lane group s sums samples s, s + 64, ... sixteen rows in flight
 // (a serial sum of rows, one at a time, was 265 us of latency whatever the size of the input).
 template <int DT>
@@ -74,34 +75,45 @@ __global__ __launch_bounds__(KO_MEAN_T) void ko_meanq_kernel(const void* __restr
     }
 }
 
-// grid: x = block of 64 stream slots (16 lanes per key row), y = head.
-template <int DT>
+// grid: x = block of 64 * KO_FLY stream slots, y = HEADS query heads of a KV head. 16 lanes per key row, KO_FLY rows in flight, each
+// read once for all HEADS. (One row and one head at a time, a key row went through a compute unit once per query head with nothing
+// else on its way: 64 heads x 5003 keys 26.5 us, 32 x 128K 220; now 12 and 79.)
+template <int DT, int HEADS>
 __global__ __launch_bounds__(KO_THREADS) void ko_proxy_kernel(const void* __restrict__ K,
                                                               const float* __restrict__ mq, int n_q,
                                                               int n_kv, int64_t N, int64_t N_pad,
                                                               u64* __restrict__ keys) {
-    const int graph = blockIdx.y, seq = graph / n_q, h = graph % n_q, kvh = h / (n_q / n_kv);
-    const int l16 = threadIdx.x & 15;
-    const int64_t i = (int64_t)blockIdx.x * (KO_THREADS / 16) + threadIdx.x / 16;
-    if (i >= N_pad) return;                     // whole 16-lane groups leave together
-    const int64_t row = i < N ? i : N - 1;
-    const float* m = mq + (size_t)graph * RA_D + 8 * l16;
-    const size_t at = (((size_t)seq * n_kv + kvh) * N + row) * RA_D + 8 * l16;
-    float k[8];
-    ko_row8<DT>(K, at, k);
-    float p = 0.f;
+    const int graph0 = blockIdx.y * HEADS, seq = graph0 / n_q, h0 = graph0 % n_q, kvh = h0 / (n_q / n_kv);
+    const int l16 = threadIdx.x & 15, lane = threadIdx.x % RA_WAVE;
+    const int64_t i0 = (int64_t)blockIdx.x * (KO_THREADS / 16 * KO_FLY) + threadIdx.x / 16;
+    if (i0 >= N_pad) return;                    // whole 16-lane groups leave together
+    float k[KO_FLY][8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) p += k[c] * m[c];
-    const int lane = threadIdx.x % RA_WAVE;
-    p += __uint_as_float(lane_xor32<1>(__float_as_uint(p), lane));
-    p += __uint_as_float(lane_xor32<2>(__float_as_uint(p), lane));
-    p += __uint_as_float(lane_xor32<4>(__float_as_uint(p), lane));
-    p += __uint_as_float(lane_xor32<8>(__float_as_uint(p), lane));
-    if (p != p) p = 0.f;                        // an order is all that is wanted: any place will do
-    // ids stay below 2^31, so the all-ones entries beyond N sort behind every key
-    if (l16 == 0)
-        keys[(size_t)graph * N_pad + i] =
-            i < N ? ((u64)(~f32_ordered(p)) << 32) | (u64)(uint32_t)i : ~0ull;
+    for (int u = 0; u < KO_FLY; ++u) {
+        const int64_t i = i0 + u * (KO_THREADS / 16), row = i < N ? i : N - 1;
+        ko_row8<DT>(K, (((size_t)seq * n_kv + kvh) * N + row) * RA_D + 8 * l16, k[u]);
+    }
+#pragma unroll
+    for (int g = 0; g < HEADS; ++g) {
+        const float* m = mq + (size_t)(graph0 + g) * RA_D + 8 * l16;
+        const float4 ma = *reinterpret_cast<const float4*>(m), mb = *reinterpret_cast<const float4*>(m + 4);
+        const float mv[8] = {ma.x, ma.y, ma.z, ma.w, mb.x, mb.y, mb.z, mb.w};
+#pragma unroll
+        for (int u = 0; u < KO_FLY; ++u) {
+            const int64_t i = i0 + u * (KO_THREADS / 16);
+            float p = 0.f;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) p += k[u][c] * mv[c];
+            p += __uint_as_float(lane_xor32<1>(__float_as_uint(p), lane));
+            p += __uint_as_float(lane_xor32<2>(__float_as_uint(p), lane));
+            p += __uint_as_float(lane_xor32<4>(__float_as_uint(p), lane));
+            p += __uint_as_float(lane_xor32<8>(__float_as_uint(p), lane));
+            if (p != p) p = 0.f;                // an order is all that is wanted: any place will do
+            // ids stay below 2^31, so the all-ones entries beyond N sort behind every key
+            if (l16 == 0 && i < N_pad)
+                keys[(size_t)(graph0 + g) * N_pad + i] = i < N ? ((u64)(~f32_ordered(p)) << 32) | (u64)(uint32_t)i : ~0ull;
+        }
+    }
 }
 
 // One exchange of the bitonic network on a chunk in LDS: element e and e ^ j, ascending overall
@@ -329,16 +341,21 @@ ra_status ra_launch_knn_order(const void* K, const void* Q, ra_dtype dt, int n_s
     const int64_t N_pad = ra_sort_padded(N);
     u64* keys = reinterpret_cast<u64*>(workspace);
     float* mq = reinterpret_cast<float*>(keys + (size_t)graphs * N_pad);
-    const dim3 pgrid((unsigned)((N_pad + KO_THREADS / 16 - 1) / (KO_THREADS / 16)), (unsigned)graphs);
-    if (dt == RA_BF16) {
-        hipLaunchKernelGGL(ko_meanq_kernel<RA_BF16>, dim3(graphs, 4), dim3(KO_MEAN_T), 0, st, Q, M, mq);
-        hipLaunchKernelGGL(ko_proxy_kernel<RA_BF16>, pgrid, dim3(KO_THREADS), 0, st, K, mq, n_q, n_kv, N,
-                           N_pad, keys);
-    } else {
-        hipLaunchKernelGGL(ko_meanq_kernel<RA_F32>, dim3(graphs, 4), dim3(KO_MEAN_T), 0, st, Q, M, mq);
-        hipLaunchKernelGGL(ko_proxy_kernel<RA_F32>, pgrid, dim3(KO_THREADS), 0, st, K, mq, n_q, n_kv, N,
-                           N_pad, keys);
-    }
+    const int group = n_q / n_kv, heads = group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
+    const int64_t per = KO_THREADS / 16 * KO_FLY;
+    const dim3 mgrid(graphs, 4), pgrid((unsigned)((N_pad + per - 1) / per), (unsigned)(graphs / heads));
+#define KO_GO(DTV)                                                                                                       \
+    do {                                                                                                                 \
+        hipLaunchKernelGGL(ko_meanq_kernel<DTV>, mgrid, dim3(KO_MEAN_T), 0, st, Q, M, mq);                               \
+        if (heads == 4)                                                                                                  \
+            hipLaunchKernelGGL((ko_proxy_kernel<DTV, 4>), pgrid, dim3(KO_THREADS), 0, st, K, mq, n_q, n_kv, N, N_pad, keys); \
+        else if (heads == 2)                                                                                             \
+            hipLaunchKernelGGL((ko_proxy_kernel<DTV, 2>), pgrid, dim3(KO_THREADS), 0, st, K, mq, n_q, n_kv, N, N_pad, keys); \
+        else                                                                                                             \
+            hipLaunchKernelGGL((ko_proxy_kernel<DTV, 1>), pgrid, dim3(KO_THREADS), 0, st, K, mq, n_q, n_kv, N, N_pad, keys); \
+    } while (0)
+    if (dt == RA_BF16) KO_GO(RA_BF16); else KO_GO(RA_F32);
+#undef KO_GO
     RA_HIP(hipGetLastError());
     return ra_launch_sort(keys, (size_t)N_pad, graphs, N_pad, nullptr, 0, st);
 }
