@@ -406,6 +406,13 @@ __device__ __forceinline__ void flat_finish(FlatLds& lds, const void* q, const v
     const int tid = threadIdx.x;
     uint32_t* kh = keys + (size_t)head * N;
     unsigned c = 0u, bad = 0u, start[FL_SLICES + 1], cj[FL_SLICES];
+    // the first EARLY entries of every list are asked for together with the lists' lengths: one trip past the caches, and what
+    // lies beyond a length is not looked at
+    constexpr unsigned EARLY = FL_SEL_T / FL_SLICES;
+    const int my_j = tid / (int)EARLY;
+    const unsigned my_e = (unsigned)tid % EARLY;
+    const uint32_t* my_at = kh + (size_t)my_j * (N / FL_SLICES) + (2 * (int64_t)my_e + 1 < N / FL_SLICES ? 2 * my_e : 0);
+    const uint32_t my_key = xwg_load(my_at), my_id = xwg_load(my_at + 1);
 #pragma unroll
     for (int j = 0; j < FL_SLICES; ++j) cj[j] = xwg_load(cand_count + head * FL_SLICES + j);
 #pragma unroll
@@ -417,14 +424,23 @@ __device__ __forceinline__ void flat_finish(FlatLds& lds, const void* q, const v
     start[FL_SLICES] = c;
     int n = -1;
     if (!bad && c >= (unsigned)topk && c <= FL_CAND) {
-        // entry i of the eight lists laid end to end (all loads in one trip)
-        for (unsigned i = tid; i < c; i += FL_SEL_T) {
+        unsigned my_start = 0u, my_n = 0u, longest = 0u;
+#pragma unroll
+        for (int j = 0; j < FL_SLICES; ++j) {
+            my_start = j == my_j ? start[j] : my_start;
+            my_n = j == my_j ? cj[j] : my_n;
+            longest = cj[j] > longest ? cj[j] : longest;
+        }
+        if (my_e < my_n) lds.sel[my_start + my_e] = ((unsigned long long)my_key << 32) | (0xffffffffu - my_id);
+        // the rest: entry i of the eight lists laid end to end (all loads in one trip)
+        for (unsigned i = longest > EARLY ? tid : c; i < c; i += FL_SEL_T) {
             int j = 0;
 #pragma unroll
             for (int x = 1; x < FL_SLICES; ++x) j += i >= start[x] ? 1 : 0;
             unsigned first = 0u;
 #pragma unroll
             for (int x = 1; x < FL_SLICES; ++x) first = j == x ? start[x] : first;
+            if (i - first < EARLY) continue;
             const uint32_t* e = kh + (size_t)j * (N / FL_SLICES) + 2 * (size_t)(i - first);
             const uint32_t key = xwg_load(e), id = xwg_load(e + 1);
             lds.sel[i] = ((unsigned long long)key << 32) | (0xffffffffu - id);
@@ -502,13 +518,8 @@ __global__ __launch_bounds__(FL_SEL_T) void flat_rescore_kernel(
         for_tiles([&](int64_t, uint32_t v) {
             if (v) { lo = v < lo ? v : lo; hi = v > hi ? v : hi; }
         });
-#pragma unroll
-        for (int d = 1; d < RA_WAVE; d <<= 1) {
-            const uint32_t ol = __shfl_xor(lo, d), oh = __shfl_xor(hi, d);
-            lo = ol < lo ? ol : lo;
-            hi = oh > hi ? oh : hi;
-        }
-        if (lane == 0) { atomicMin(&s_lo, lo); atomicMax(&s_hi, hi); }
+        wave_min_max(lo, hi);
+        if (lane == RA_WAVE - 1) { atomicMin(&s_lo, lo); atomicMax(&s_hi, hi); }
     }
     __syncthreads();
     const float lo_f = f32_from_ordered(s_lo);
@@ -535,16 +546,12 @@ __global__ __launch_bounds__(FL_SEL_T) void flat_rescore_kernel(
     __syncthreads();
     const int bstar = (int)s_prefix;
     if (bstar > 0) {
-        uint32_t m = 0xffffffffu;
+        uint32_t m = 0xffffffffu, none = 0u;
         for_tiles([&](int64_t, uint32_t v) {
             if (bin_of(v) >= bstar) m = v < m ? v : m;
         });
-#pragma unroll
-        for (int d = 1; d < RA_WAVE; d <<= 1) {
-            const uint32_t o = __shfl_xor(m, d);
-            m = o < m ? o : m;
-        }
-        if (lane == 0) atomicMin(&s_t0, m);
+        wave_min_max(m, none);
+        if (lane == RA_WAVE - 1) atomicMin(&s_t0, m);
     }
     __syncthreads();
     const uint32_t T0 = bstar > 0 ? s_t0 : 0u;
