@@ -406,8 +406,9 @@ __device__ __forceinline__ void flat_finish(FlatLds& lds, const void* q, const v
     const int tid = threadIdx.x;
     uint32_t* kh = keys + (size_t)head * N;
     unsigned c = 0u, bad = 0u, start[FL_SLICES + 1], cj[FL_SLICES];
-    // the first EARLY entries of every list are asked for together with the lists' lengths: one trip past the caches, and what
-    // lies beyond a length is not looked at
+    // The first EARLY entries of every list are asked for together with the lists' lengths, and what lies beyond a length is not
+    // looked at: one trip past the caches less in the pass' chain (top-100 by scan at 128K with attention 65.4 -> 64.9 us). They
+    // lie inside the list's place, or its first entry is read instead.
     constexpr unsigned EARLY = FL_SEL_T / FL_SLICES;
     const int my_j = tid / (int)EARLY;
     const unsigned my_e = (unsigned)tid % EARLY;

@@ -233,6 +233,24 @@ def test_gather_probe_reads_the_hashed_rows(rows_in_buf, n_rows, seed):
         ra.ra_hbm_gather_probe(buf, 0, out)
 
 
+@pytest.mark.parametrize("N,topk", [(1024, 16), (1031, 16), (65536, 100), (65536, 300), (65536, 700)])
+def test_flat_topk_with_all_candidates_in_one_slice(N, topk):
+    """The second pass takes tiles by their number modulo 8, and the first 128 candidates of a slice's list are read ahead
+    of its length: here one slice has them all, up to more than its list holds. Whole numbers: exact, ties by id."""
+    rng = np.random.default_rng(N + topk)
+    K = rng.integers(-3, 4, size=(N, 128)).astype(np.float32)
+    ids = np.arange(N)
+    K[:, 0] = np.where((ids // 8) % 8 == 3, rng.integers(100, 5000, N), 0)
+    q = np.zeros((2, 128), np.float32)
+    q[:, 0] = 1.0
+    q[1, 5] = 2.0
+    got = ra.ra_flat_topk(torch.from_numpy(q)[None].to(DEV), torch.from_numpy(K)[None, None].to(DEV), 2, 9, topk)
+    for h in range(2):
+        score = K.astype(np.float64) @ q[h]
+        score[:2] = score[N - 9:] = -np.inf
+        assert got[0, h].tolist() == np.argsort(-score, kind="stable")[:topk].tolist()
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("n_seq,n_q,n_kv,topk", [(1, 32, 4, 300), (1, 33, 33, 20), (9, 8, 1, 257)])
 def test_flat_topk_where_the_order_of_candidates_is_found(n_seq, n_q, n_kv, topk, dtype):
