@@ -282,7 +282,12 @@ ra_status ra_decode_step_q8(const void* q, const ra_index* idx, const void* K, c
  * 7 the seed-set size in use (RA_CFG_SEEDS; 0: single entry point),
  * 8 whether ra_decode_step may score the seed sets in workgroups of their own (RA_CFG_SEED_SHARES;
  *   1 / 0: off, no seed sets, helpers off, or a head's wait for its keys ran out; synchronises the
- *   device). */
+ *   device). A launch whose walks share their steps (9) has the seed sets scored by the workers.
+ * 9 whether ra_decode_step may share the steps of its walks out over workgroups (see RA_CFG_SEED_SHARES; 1 / 0: too
+ *   few keys or too many searches for it, switched off, or a head's wait for an answer ran out; synchronises the
+ *   device),
+ * 10 messages the handle's first search has sent to its workers so far, modulo 2^32: one for every step that was shared, one when
+ *   the walk ended (0 where 9 can only be 0; synchronises the device). */
 int64_t ra_index_info(const ra_index* idx, int what);
 
 /* Settings of the handle's decode path (host side; synchronises the device).

@@ -190,6 +190,8 @@ class Index:
     device_bytes = property(lambda s: s.info(5))
     helpers_active = property(lambda s: s.info(6) == 1)
     seed_shares_active = property(lambda s: s.info(8) == 1)
+    shared_steps_active = property(lambda s: s.info(9) == 1)
+    shared_messages = property(lambda s: s.info(10))
 
     n_seeds = property(lambda s: s.info(7))
 

@@ -280,6 +280,23 @@ extern "C" int64_t ra_index_info(const ra_index* ix, int what) {
                 return -1;
             return off == 0u;
         }
+        case 9: {
+            // 1 while the walks may share their steps and no head's wait for an answer has run out
+            if (!ix->walk || ix->seed_parts < 2 || ix->coop_mode != RA_HELPERS_ON || ix->coop_silent) return 0;
+            uint32_t off = 1u;
+            if (hipDeviceSynchronize() != hipSuccess ||
+                hipMemcpy(&off, ix->walk, sizeof(off), hipMemcpyDeviceToHost) != hipSuccess)
+                return -1;
+            return off == 0u;
+        }
+        case 10: {
+            if (!ix->walk) return 0;
+            uint32_t sent = 0u;
+            if (hipDeviceSynchronize() != hipSuccess ||
+                hipMemcpy(&sent, ix->walk + RA_WALK_OFF_WORDS, sizeof(sent), hipMemcpyDeviceToHost) != hipSuccess)
+                return -1;
+            return sent;
+        }
         default: return -1;
     }
 }

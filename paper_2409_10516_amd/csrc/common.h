@@ -102,7 +102,7 @@ struct ra_index {
 #define RA_WALK_MIN_CELLS 2560 /* (see ra_launch_decode) */
 #define RA_WALK_MIN_KEYS (1 << 18)
 #define RA_WALK_OFF_WORDS 32   /* words in front of the areas: [0] "steps not shared", set by a head whose wait ran out */
-#define RA_WALK_HEAD_WORDS 272 /* 64-bit words of a head (its message), then of each of its workers (two answers) */
+#define RA_WALK_HEAD_WORDS 272 /* 64-bit words of a head (number of its last message, its message), then of each of its workers (two answers) */
 #define RA_WALK_PART_WORDS (2 * (RA_WALK_CELLS + 8))
 #define RA_FLAT_SLICES 8       /* workgroups per head in the second pass of ra_flat_topk (one counter each) */
 #define RA_HELPERS_SILENT_ 2   /* launch-time helper mode behind RA_TEST_HELPERS_SILENT */

@@ -817,13 +817,15 @@ def test_graphs_of_degree_one(expand):
 
 @pytest.mark.parametrize("dtype,n_q,deg,expand,ef,seeds,q8", [
     (torch.bfloat16, 1, 64, 64, 1024, 0, False),       # 4096 cells, the most a worker answers for; 16 workers
-    (torch.bfloat16, 20, 24, 128, 512, 1500, False),   # 8 workers, two rows of workgroups per compute die, seed sets
+    (torch.bfloat16, 20, 24, 128, 512, 1500, False),   # 8 workers, three rows of workgroups per compute die, seed sets
     (torch.float32, 3, 63, 64, 1024, 0, False),        # rows of no multiple of four cells
     (torch.float32, 2, 64, 48, 600, 0, False),         # fewer picks than the entry point has neighbours: no start set
     (torch.bfloat16, 2, 48, 64, 512, 2048, True)])     # 8-bit keys
 def test_walks_that_share_their_steps(dtype, n_q, deg, expand, ef, seeds, q8):
     """Walks whose visited set is in device memory claim and score through workers of their own in ra_decode_step:
-    ids and counters are those of ra_search, which walks alone, in repeated calls and when no worker answers."""
+    ids and counters are those of ra_search, which walks alone, in repeated calls and when no worker answers. The
+    first search's messages say that its steps were shared: one each, and one when the walk ended (a start set's
+    step, and the first two of a walk from a root set, need none)."""
     from paper_2409_10516_amd import binding as B
     N, topk = 1_100_003, 100
     g = torch.Generator(device=DEV).manual_seed(deg * 1000 + n_q)
@@ -844,9 +846,16 @@ def test_walks_that_share_their_steps(dtype, n_q, deg, expand, ef, seeds, q8):
     for silent, spin in ((0, 20000), (1, 2), (0, 20000)):
         idx.test_configure(B.RA_TEST_HELPERS_SILENT, silent)
         idx.configure(B.RA_CFG_HELPER_SPIN, spin)
+        assert idx.shared_steps_active == (not silent)
         for t in (0, 1, 2, 0):
+            sent = idx.shared_messages
             out, lse, ids, st = ra.ra_decode_step(q[t], idx, K, V, 4, 500, topk, ef, expand, **more)
             assert torch.equal(ids, alone[t][0]) and torch.equal(st, alone[t][1]), (silent, t)
             outs.append(out)
+            iters = int(st[0, 0, 2])
+            if not silent:
+                assert idx.shared_steps_active and iters - 1 <= idx.shared_messages - sent <= iters + 1, (t, iters)
+            elif t:                                        # (the first of these calls has missed its answers)
+                assert idx.shared_messages == sent
     # the same sets attended to: float32 sums over some 600 rows in another order, values of norm about 1
     assert all(torch.allclose(a, b, rtol=0, atol=1e-5) for a, b in zip(outs[:4], outs[4:8]))
