@@ -567,10 +567,14 @@ static int decode_compute_units() {
     return cached[dev] > 0 ? cached[dev] : 0;
 }
 
-// (below RA_WALK_MIN_KEYS the visited set of steps of up to RA_WALK_CELLS cells always fits LDS)
+// (below RA_WALK_MIN_KEYS the visited set of steps of up to RA_WALK_CELLS cells always fits LDS). A head and its workers are on one
+// XCD, and one of their workgroups fills a compute unit: of every eighth head an XCD has the head, at most one helper and
+// the workers, all of which have to run at once, or heads wait for workers that have no compute unit. On 256 compute units 16
+// workers for up to 8 heads, 8 for up to 24. (Counted over the whole device, 9 to 14 heads had 34 workgroups for an XCD's 32
+// compute units: their first wait ran out and steps were shared no more.)
 int ra_walk_parts(int heads, int64_t N) {
     if (N < RA_WALK_MIN_KEYS) return 0;
-    const int room = decode_compute_units() / heads - 2;         // (a head, and at most one helper per head)
+    const int room = decode_compute_units() / 8 / ((heads + 7) / 8) - 2;
     return room >= RA_WALK_PARTS_MAX ? RA_WALK_PARTS_MAX : room >= 8 && RA_WALK_PARTS_MAX >= 8 ? 8 : 0;
 }
 

@@ -859,3 +859,26 @@ def test_walks_that_share_their_steps(dtype, n_q, deg, expand, ef, seeds, q8):
                 assert idx.shared_messages == sent
     # the same sets attended to: float32 sums over some 600 rows in another order, values of norm about 1
     assert all(torch.allclose(a, b, rtol=0, atol=1e-5) for a, b in zip(outs[:4], outs[4:8]))
+
+
+@pytest.mark.parametrize("n_q,shared", [(8, True), (9, True), (12, True), (14, True), (24, True), (25, False)])
+def test_workers_of_shared_steps_all_run_at_once(n_q, shared):
+    """A search and its workers are on one compute die (an eighth of the compute units), with the helpers: no launch
+    may have more of them there than units, or a search would wait for a worker that waits for it to end. Numbers of
+    searches on either side of 8, 16 and 24, which make 2, 3 and 4 searches on one die."""
+    N, deg, expand, ef, topk = 800_001, 24, 128, 1024, 64
+    g = torch.Generator(device=DEV).manual_seed(n_q)
+    adj = torch.randint(0, N, (n_q, N, deg), generator=g, device=DEV, dtype=torch.int32)
+    idx = ra.ra_index_import(adj.cpu(), torch.zeros(n_q, dtype=torch.int32), 1, n_q, n_q)
+    del adj
+    K = torch.randn((1, n_q, N, 128), generator=g, device=DEV, dtype=torch.bfloat16)
+    q = torch.randn((1, n_q, 128), generator=g, device=DEV, dtype=torch.bfloat16)
+    want, st_want = ra.ra_search(q, idx, K, 4, 500, topk, ef, expand)
+    assert idx.shared_steps_active == shared
+    for _ in range(5):
+        sent = idx.shared_messages
+        out, lse, ids, st = ra.ra_decode_step(q, idx, K, K, 4, 500, topk, ef, expand)
+        assert torch.equal(ids, want) and torch.equal(st, st_want)
+        assert idx.shared_steps_active == shared               # no wait ran out
+        assert (idx.shared_messages > sent) == shared
+    idx.free()
