@@ -126,6 +126,7 @@ static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra
     const size_t coop_at = roots_at + aligned(graphs * ix->root_cap * sizeof(int32_t));
     const size_t walk_at = coop_at + aligned(coop_bytes(ix));
     const size_t parts = graphs < 256 ? ra_walk_parts((int)graphs, N) : 0;
+    ix->walk_parts = (int)parts;
     ix->walk_bytes = parts ? (RA_WALK_OFF_WORDS + graphs * (RA_WALK_HEAD_WORDS + parts * RA_WALK_PART_WORDS)) * sizeof(*ix->walk) : 0;
     char* base = nullptr;
     hipError_t e = hipGetDevice(&ix->device);
@@ -630,7 +631,7 @@ static ra_status decode_common(const void* q, const ra_index* idx, const void* K
     return ra_launch_decode(q, ix->adj, ix->entry, K, V, dt, ix->n_seq, ix->n_q, ix->n_kv, ix->N, N,
                             kv_stride, ix->deg, sink, window, topk, ef, expand, ix->bitset, ix->coop,
                             ix->coop_silent ? RA_HELPERS_SILENT_ : ix->coop_mode, ix->coop_spin, start, start_cap, K8, kscale,
-                            budgets, ix->n_seeds ? ix->seedx : nullptr, ix->seed_parts, ix->walk,
+                            budgets, ix->n_seeds ? ix->seedx : nullptr, ix->seed_parts, ix->walk, ix->walk_parts,
                             (hipStream_t)stream, out, lse, ids, stats);
 }
 

@@ -83,6 +83,7 @@ struct ra_index {
     // hand-over area of walks that share their steps (decode.hip), in the allocation of the graphs, or null
     unsigned long long* walk;
     size_t walk_bytes;
+    int walk_parts;     // workers per search that it has room for
     // root sets: what the first two steps of every walk of a head visit ([n_seq*n_q][root_cap])
     int32_t* roots;
     int root_cap;
@@ -144,7 +145,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
                            int64_t kv_stride, int deg, int sink, int window, int topk, int ef, int expand,
                            uint32_t* bitset, unsigned long long* coop, int coop_mode, int coop_spin,
                            const int32_t* roots, int root_cap, const void* K8, const float* kscale,
-                           const int32_t* budgets, uint32_t* seedx, int seed_parts, unsigned long long* walk,
+                           const int32_t* budgets, uint32_t* seedx, int seed_parts, unsigned long long* walk, int walk_parts,
                            hipStream_t st, float* out, float* lse, int32_t* ids, ra_stats* stats);
 
 ra_status ra_launch_rerank(const void* q, const void* K, ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N,

@@ -583,7 +583,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
                            int64_t kv_stride, int deg, int sink, int window, int topk, int ef, int expand,
                            uint32_t* bitset, unsigned long long* coop, int coop_mode, int coop_spin,
                            const int32_t* roots, int root_cap, const void* K8, const float* kscale,
-                           const int32_t* budgets, uint32_t* seedx, int seed_parts, unsigned long long* walk,
+                           const int32_t* budgets, uint32_t* seedx, int seed_parts, unsigned long long* walk, int walk_parts,
                            hipStream_t st, float* out, float* lse, int32_t* ids, ra_stats* stats) {
     // W = [0, s) u [wstart, N): the sink, the sliding window, and every token appended after the
     // index was built (wstart <= Ng); overlapping ranges make everything static
@@ -639,7 +639,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
     const int cells = expand * deg;
     if (walk && gb && roots && seed_parts > 0 && coop_mode != RA_HELPERS_OFF && !budgets && threads >= 512 && deg >= 2 &&
         deg * (expand < ef / 4 ? expand : ef / 4) >= RA_WALK_MIN_CELLS && cells <= RA_WALK_CELLS) {
-        walk_log2 = 31 - __builtin_clz(ra_walk_parts(heads, Ng));
+        walk_log2 = 31 - __builtin_clz(walk_parts);
         if (serve_lds_bytes(Ng, deg, expand, walk_log2) > lds) walk_log2 = 0;
         else parts = 0;
     }
