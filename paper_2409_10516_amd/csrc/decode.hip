@@ -289,21 +289,33 @@ struct WalkHook {
     int spin, parts_log2;
     u64* area;
     uint32_t* off_word;
-    uint32_t is_off;
     static constexpr bool kSeedShare = false;
     static constexpr bool kShareSteps = true;
-    __device__ __forceinline__ bool steps_shared() const { return is_off == 0u; }
     __device__ __forceinline__ void steps_missed() const { xwg_store(off_word, 1u); }
+};
+
+// What the launch adds for walks that share their steps (serve_walk): `heads` of them with 2^parts_log2 workers each, areas from
+// `words`. A type of its own, so that the common kernel has neither the arguments nor the code.
+struct NoWalk {
+    static constexpr bool kShare = false;
+};
+struct SharedWalk {
+    static constexpr bool kShare = true;
+    u64* words;
+    int heads, parts_log2;
+    __device__ __forceinline__ uint32_t* off_word() const { return reinterpret_cast<uint32_t*>(words); }
+    __device__ __forceinline__ u64* area(int head) const {
+        return words + RA_WALK_OFF_WORDS + (size_t)head * (RA_WALK_HEAD_WORDS + ((size_t)RA_WALK_PART_WORDS << parts_log2));
+    }
 };
 
 // BUDGETS: every head keeps its own number of ids (budgets[head]) instead of topk. A variant of
 // its own because the value lives through the whole walk: read in the common kernel, even behind a
 // test for a null pointer, it cost 1.5 % of the step.
-// SHARE: the walks share their steps with 2^walk_log2 workers each (serve_walk). Workgroup x of the first
-// 8 * ceil(heads / 8) * (1 + workers) runs on the XCD of its head's others (x mod 8, if workgroups are dealt round-robin): the workers
-// of a head read the same adjacency rows, and a hand-over inside an XCD is a quarter shorter. The heads come first, then
-// the workers; helpers have the highest ids.
-template <int DT, int KT, bool GBITS, int T, bool BUDGETS, bool SHARE>
+// With a SharedWalk, workgroup x of the first 8 * ceil(heads / 8) * (1 + workers) runs on the XCD of its head's others (x mod 8, if
+// workgroups are dealt round-robin): the workers of a head read the same adjacency rows, and a hand-over inside an XCD is a
+// quarter shorter. The heads come first, then the workers; helpers have the highest ids.
+template <int DT, int KT, bool GBITS, int T, bool BUDGETS, typename Walk>
 __global__ __launch_bounds__(T) void decode_kernel(
     const void* __restrict__ q, const int32_t* __restrict__ adj, const int32_t* __restrict__ entry,
     const void* __restrict__ K, const void* __restrict__ V, int n_q, int n_kv, int64_t Ng, int64_t N,
@@ -313,22 +325,28 @@ __global__ __launch_bounds__(T) void decode_kernel(
     float* __restrict__ out, float* __restrict__ lse, u64* coop, int n_helpers, int coop_mode,
     int coop_spin, const int32_t* __restrict__ roots, int root_cap, const void* __restrict__ Ksearch,
     const float* __restrict__ kscale, const int32_t* __restrict__ budgets, uint32_t* seedx, int seed_parts,
-    int seed_stride, int helper_heads, int share_heads, u64* walk, int walk_log2) {
+    int seed_stride, int helper_heads, Walk walk) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int tid = threadIdx.x, grp = tid >> 4, lane16 = tid & 15;
     const size_t esz = DT == RA_BF16 ? 2 : 4;
     const int G = n_q / n_kv;
-    const int n_heads = SHARE ? share_heads : ((int)gridDim.x - n_helpers) / (1 + seed_parts);
-    const int walkers = SHARE ? (int)gridDim.x - n_helpers : 0;      // workgroups of heads and workers
-    const int helper = (int)blockIdx.x - walkers;
+    int n_heads, helper = (int)blockIdx.x;                   // (helper: in [0, n_helpers) of a helper workgroup)
+    if constexpr (Walk::kShare) {
+        n_heads = walk.heads;
+        helper -= (int)gridDim.x - n_helpers;
+    } else {
+        n_heads = ((int)gridDim.x - n_helpers) / (1 + seed_parts);
+    }
     // hand-over area: records, "helpers off" word (set by a head whose wait ran out); seed hand-over area: [0]
     // the "shares off" word, then (from byte RA_SEEDX_KEYS_OFF) seed_stride 64-bit keys per head, zero
     // between launches. Both words are asked for here, together, and looked at where they are needed: a
     // trip past the caches is a microsecond.
     uint32_t* helpers_off_word = reinterpret_cast<uint32_t*>(coop + (size_t)n_heads * RA_COOP_REC);
     const uint32_t helpers_off = xwg_load(helpers_off_word);
-    const uint32_t shares_off = xwg_load(SHARE ? reinterpret_cast<const uint32_t*>(walk) : seedx ? seedx : helpers_off_word);
-    if (SHARE ? helper >= 0 : helper < n_helpers) {
+    uint32_t* shares_off_word = seedx ? seedx : helpers_off_word;
+    if constexpr (Walk::kShare) shares_off_word = walk.off_word();
+    const uint32_t shares_off = xwg_load(shares_off_word);
+    if (Walk::kShare ? helper >= 0 : helper < n_helpers) {
         // ---- helper workgroup of (sequence, KV head) blockIdx.x: attention over W for its G heads
         if (coop_mode == RA_HELPERS_SILENT_) return;
         // helper_heads of the group's G query heads per helper workgroup (G: one helper per group, W
@@ -351,31 +369,29 @@ __global__ __launch_bounds__(T) void decode_kernel(
     }
     u64* seed_keys_all = reinterpret_cast<u64*>(reinterpret_cast<char*>(seedx) + RA_SEEDX_KEYS_OFF);
     int head;
-    auto walk_area = [&](int h) { return walk + RA_WALK_OFF_WORDS + (size_t)h * (RA_WALK_HEAD_WORDS + ((size_t)RA_WALK_PART_WORDS << walk_log2)); };
-    if constexpr (SHARE) {
-        // ---- the head (role 0), or one of its workers
-        const int per = 1 + (1 << walk_log2), j = (int)blockIdx.x >> 3, rows = (n_heads + 7) >> 3;
-        const int role = j / rows;                           // all heads, then all first workers, and so on
+    if constexpr (Walk::kShare) {
+        // ---- the head (role 0), or one of its workers: all heads, then all first workers, and so on
+        const int rows = (n_heads + 7) >> 3, j = (int)blockIdx.x >> 3, role = j / rows;
         head = ((j - role * rows) << 3) + ((int)blockIdx.x & 7);
-        if (head >= n_heads || role >= per) return;
+        if (head >= n_heads || role > 1 << walk.parts_log2) return;
         if (role > 0) {
             if (coop_mode == RA_HELPERS_SILENT_ || shares_off != 0u) return;
-            serve_walk<DT, KT, T>(lds_raw, head, role - 1, walk_log2, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg, ef, expand,
-                                  roots, root_cap, kscale, walk_area(head), coop_spin);
+            serve_walk<DT, KT, T>(lds_raw, head, role - 1, walk.parts_log2, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg, ef, expand,
+                                  roots, root_cap, kscale, walk.area(head), coop_spin);
             return;
         }
     } else {
-    if ((int)blockIdx.x < n_helpers + n_heads * seed_parts) {
-        // ---- seed workgroup: one share of one head's start set (on the XCD of the head's workgroup
-        //      when the number of heads is a multiple of 8)
-        if (coop_mode == RA_HELPERS_SILENT_ || shares_off != 0u) return;
-        const int i = (int)blockIdx.x - n_helpers;
-        const int part = i / n_heads, hd = xcd_aware_head(i % n_heads, n_heads, G);
-        score_seed_share<DT, KT, T>(hd, part, seed_parts, q, Ksearch, n_q, n_kv, kv_stride, roots, root_cap,
-                                    root_cap - 2, expand * deg, kscale, seed_keys_all + (size_t)hd * seed_stride);
-        return;
-    }
-    head = xcd_aware_head((int)blockIdx.x - n_helpers - n_heads * seed_parts, n_heads, G);
+        if ((int)blockIdx.x < n_helpers + n_heads * seed_parts) {
+            // ---- seed workgroup: one share of one head's start set (on the XCD of the head's workgroup
+            //      when the number of heads is a multiple of 8)
+            if (coop_mode == RA_HELPERS_SILENT_ || shares_off != 0u) return;
+            const int i = (int)blockIdx.x - n_helpers;
+            const int part = i / n_heads, hd = xcd_aware_head(i % n_heads, n_heads, G);
+            score_seed_share<DT, KT, T>(hd, part, seed_parts, q, Ksearch, n_q, n_kv, kv_stride, roots, root_cap,
+                                        root_cap - 2, expand * deg, kscale, seed_keys_all + (size_t)hd * seed_stride);
+            return;
+        }
+        head = xcd_aware_head((int)blockIdx.x - n_helpers - n_heads * seed_parts, n_heads, G);
     }
     const int seq = head / n_q, h = head % n_q, kvh = h / G;
     int32_t* lds_ids = reinterpret_cast<int32_t*>(lds_raw + ids_off);
@@ -391,16 +407,24 @@ __global__ __launch_bounds__(T) void decode_kernel(
         const int b = budgets[head];
         take = b < 1 ? 1 : b > topk ? topk : b;
     }
-    auto search = [&](const auto& hook) __attribute__((always_inline)) {
-        return run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
-                                            s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
-                                            lds_ids, roots, root_cap, kscale, hook);
-    };
-    int cnt;
-    if constexpr (SHARE)
-        cnt = search(WalkHook{coop_spin, walk_log2, walk_area(head), reinterpret_cast<uint32_t*>(walk), shares_off});
-    else
-        cnt = search(SeedHook{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx, seed_parts > 0, shares_off});
+    int cnt = -1;
+    if constexpr (Walk::kShare) {
+        if (shares_off == 0u)
+            cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
+                                               s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
+                                               lds_ids, roots, root_cap, kscale,
+                                               WalkHook{coop_spin, walk.parts_log2, walk.area(head), walk.off_word()});
+        if (cnt < 0)                                         // alone: the workers have not answered, now or earlier
+            cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
+                                               s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
+                                               lds_ids, roots, root_cap, kscale, NoHook{});
+    } else {
+        cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
+                                           s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
+                                           lds_ids, roots, root_cap, kscale,
+                                           SeedHook{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx,
+                                                    seed_parts > 0, shares_off});
+    }
 #ifdef SR_PHASE_CLOCKS
     const long long t_attn = clock64();
 #endif
@@ -643,24 +667,25 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
         if (serve_lds_bytes(Ng, deg, expand, walk_log2) > lds) walk_log2 = 0;
         else parts = 0;
     }
-    const int walkers = walk_log2 ? (heads + 7) / 8 * 8 * (1 + (1 << walk_log2)) : 0;
     if (kscale && !K8) RA_FAIL(RA_EINVAL, "8-bit keys missing");
-#define RA_DC_GO_AS(DTV, KTV, GB, TV, BU, SH)                                                      \
+#define RA_DC_GO_AS(DTV, KTV, GB, TV, BU, WALK, GRID, ...)                                         \
     do {                                                                                           \
-        RA_LDS_OPT_IN((decode_kernel<DTV, KTV, GB, TV, BU, SH>), lds);                             \
-        hipLaunchKernelGGL((decode_kernel<DTV, KTV, GB, TV, BU, SH>),                              \
-                           dim3((SH ? walkers : heads * (1 + parts)) + n_helpers), dim3(TV),       \
+        RA_LDS_OPT_IN((decode_kernel<DTV, KTV, GB, TV, BU, WALK>), lds);                           \
+        hipLaunchKernelGGL((decode_kernel<DTV, KTV, GB, TV, BU, WALK>),                            \
+                           dim3((GRID) + n_helpers), dim3(TV),                                     \
                            lds, st, q, adj, entry, K, V, n_q, n_kv, Ng, N, kv_stride, wstart, deg, \
                            (int)s, topk, ef, expand, bitset, ids, stats, ids_off, scale, out, lse, \
                            coop, n_helpers, coop_mode, coop_spin, roots, root_cap, Ksearch,        \
-                           kscale, budgets, seedx, parts, seed_stride, helper_heads, heads, walk,  \
-                           walk_log2);                                                             \
+                           kscale, budgets, seedx, parts, seed_stride, helper_heads, __VA_ARGS__); \
     } while (0)
-#define RA_DC_GO_TB(DTV, KTV, GB, TV, BU) RA_DC_GO_AS(DTV, KTV, GB, TV, BU, false)
+#define RA_DC_GO_TB(DTV, KTV, GB, TV, BU) RA_DC_GO_AS(DTV, KTV, GB, TV, BU, NoWalk, heads * (1 + parts), NoWalk{})
 #define RA_DC_GO_T(DTV, KTV, GB, TV)                                                               \
     do {                                                                                           \
-        if (walk_log2) RA_DC_GO_AS(DTV, KTV, true, (TV < 512 ? 512 : TV), false, true);            \
-        else RA_DC_GO_AS(DTV, KTV, GB, TV, false, false);                                          \
+        if (walk_log2)                                                                             \
+            RA_DC_GO_AS(DTV, KTV, true, (TV < 512 ? 512 : TV), false, SharedWalk,                  \
+                        (heads + 7) / 8 * 8 * (1 + (1 << walk_log2)), SharedWalk{walk, heads, walk_log2}); \
+        else                                                                                       \
+            RA_DC_GO_TB(DTV, KTV, GB, TV, false);                                                  \
     } while (0)
 #define RA_DC_GO(DTV, KTV, GB)                                                                     \
     do {                                                                                           \

@@ -432,9 +432,9 @@ __device__ __forceinline__ void claim_cells(const int (&nb)[L], uint32_t n_keys,
 // take_seed_keys(c0, c1, k0, k1) waits (bounded) for keys c0 and c1 of the set (c1 < 0: only c0; k1 is
 // then k0 again) and leaves 0 for one that did not come, and seeds_missed() is called by one thread
 // when some key did not.
-// kShareSteps says whether workers may take the claims and the scores of its steps (serve_walk below): then steps_shared()
-// says whether they do in this launch, with `parts_log2`, `spin` and the head's `area`, and steps_missed() is called by
-// one thread when an answer did not come.
+// kShareSteps says whether workers take the claims and the scores of its steps (serve_walk below), with `parts_log2`, `spin`
+// and the head's `area`. When an answer does not come, steps_missed() is called by one thread and the search returns
+// -1, with no ids and no counters written.
 struct NoHook {
     static constexpr bool kSeedShare = false;
     static constexpr bool kShareSteps = false;
@@ -782,16 +782,11 @@ __device__ __forceinline__ int run_search(
         n_first = root[1];
         my_root = root[2 + (tid < root_cap - 2 ? tid : 0)];      // unconditional: same trip as the header
     }
-    bool sharing = false;            // claims and scores by the walk's workers (serve_walk)
-    if constexpr (Hook::kShareSteps) sharing = hook.steps_shared();
-    int n_posted = 0;
+    int n_posted = 0;                // (kShareSteps: claims and scores are the workers', serve_walk)
     uint32_t last_message = 0u;
     if constexpr (Hook::kShareSteps) last_message = (uint32_t)xwg_load(hook.area + SR_MSG_LAST);
-    int bn, n_visited, n_expanded, n_iters;
-    bool walked = true;
-    do {                             // (a second time, alone, when an answer did not come)
     // (the loads above are in flight while the LDS state is cleared)
-    if (!sharing)
+    if constexpr (!Hook::kShareSteps)
         for (int i = tid; i < nwords; i += T) bits[i] = 0u;
     for (int i = tid; i < maxc + nhist; i += T) cnt[i] = 0;      // cnt, hist and hsum
     // A seed set (ra_launch_seeds) has the same layout with [1] = 0: the walk starts from all of its
@@ -806,10 +801,11 @@ __device__ __forceinline__ int run_search(
 #ifdef SR_WAVE_CLOCKS
     if (head == 0 && tid == 0) sr_wave_ticks[1] = wall_clock64();
 #endif
+    int bn, n_visited, n_expanded, n_iters;
     bool first = fill;               // the coming step is that doubled first step
     if (Hook::kShareSteps && tid == 0) ctr[C_MISSED] = 0;
     if (fill) {
-        if (!sharing)
+        if constexpr (!Hook::kShareSteps)
             for (int c = tid; c < n_root; c += T) {
                 const int id = c == tid ? my_root : root[2 + c];
                 cid[c] = id;
@@ -817,8 +813,8 @@ __device__ __forceinline__ int run_search(
             }
         if (tid == 0) {
             urank[0] = 0;
-            cc[S_NCAND] = sharing ? 0 : n_root;      // (then added up from the workers' answers)
-            cc[S_NKEEP] = sharing ? 0 : n_root;      // every key of a start set is kept (scored below)
+            cc[S_NCAND] = Hook::kShareSteps ? 0 : n_root;    // (then added up from the workers' answers)
+            cc[S_NKEEP] = Hook::kShareSteps ? 0 : n_root;    // every key of a start set is kept (scored below)
             cc[S_NUNEXP] = 0;
             ctr[C_LO] = -1;                  // as unsigned: the largest value; see the pre-filter below
             ctr[C_HI] = 0;
@@ -839,7 +835,7 @@ __device__ __forceinline__ int run_search(
                 cc[S_NCAND] = 0;
                 cc[S_NKEEP] = 0;
                 cc[S_NUNEXP] = 1;
-                if (!sharing) (void)claim_key(bits, e0);
+                if constexpr (!Hook::kShareSteps) (void)claim_key(bits, e0);
             }
         }
         bn = 1; n_visited = 1; n_expanded = 0; n_iters = 0;
@@ -923,7 +919,7 @@ __device__ __forceinline__ int run_search(
                                                                     tid == 2 ? (uint32_t)worst : (uint32_t)picks[tid - 3]));
         }
     };
-    if (Hook::kShareSteps && sharing) {
+    if constexpr (Hook::kShareSteps) {
         uint32_t lo = 0xffffffffu, hi = 0u;
         collect(lo, hi, 3);      // (workers that have not started by then may be long in coming)
         if (fill) {
@@ -1095,7 +1091,7 @@ __device__ __forceinline__ int run_search(
             for (int i = tid; i < nhist; i += T) hist[i] = 0;
             hist_used = false;
         }
-        if (Hook::kShareSteps && sharing) {
+        if constexpr (Hook::kShareSteps) {
             // ---- the workers claim and score; their answers are waited for
             if (!first) {
                 post(np, bn == ef ? (cur[bn - 1] >> 1) : 0ull);
@@ -1103,8 +1099,7 @@ __device__ __forceinline__ int run_search(
                 collect(lo, hi, 0);
             }
             __syncthreads();
-            walked = ctr[C_MISSED] == 0;
-            if (!walked) break;
+            if (ctr[C_MISSED]) break;
             n_visited += __builtin_amdgcn_readfirstlane(cc[S_NCAND]);
             SR_TICK(1);
         } else {
@@ -1580,21 +1575,17 @@ __device__ __forceinline__ int run_search(
         first = false;
     }
 
-    if constexpr (Hook::kShareSteps)
-        if (sharing) {
-            post(0, 0ull);
-            if (tid == 0) xwg_store(hook.area + SR_MSG_LAST, (u64)(last_message + (uint32_t)n_posted));
-            if (!walked) {
-                if (tid == 0) hook.steps_missed();
-                sharing = false;
-                __syncthreads();
-                continue;
-            }
-        }
-    break;
-    } while (true);
-
+    if constexpr (Hook::kShareSteps) {
+        post(0, 0ull);
+        if (tid == 0) xwg_store(hook.area + SR_MSG_LAST, (u64)(last_message + (uint32_t)n_posted));
+    }
     __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): no touch of this wavefront still has to land in LDS
+    if constexpr (Hook::kShareSteps)
+        if (ctr[C_MISSED]) {                 // (uniform: written before the last barrier)
+            if (tid == 0) hook.steps_missed();
+            __syncthreads();
+            return -1;
+        }
     // ---- result: best-first beam entries outside the static set W = [0,s) u [N-w,N). A short list is the
     //      first wavefront's alone (the others wait at the closing barrier); of a long one (a wavefront
     //      would be 32 rounds over 2048 entries) every wavefront takes rounds, T entries at a time.
