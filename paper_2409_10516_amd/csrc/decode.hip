@@ -249,6 +249,17 @@ __device__ __forceinline__ void static_helper(unsigned char* lds_raw, const void
     }
 }
 
+// "Helpers off" and "shares off" as this wavefront has read them, and the words in LDS where the workgroup's first thread leaves
+// what it has read for all ([1] and [2]).
+struct OffWords {
+    uint32_t helpers, shares;
+    uint32_t* lds;
+    __device__ __forceinline__ void note() const {
+        lds[1] = helpers;
+        lds[2] = shares;
+    }
+};
+
 // What the walk asks of the fused launch (see NoHook): the keys of its start set, scored by other workgroups.
 struct SeedHook {
     int spin;
@@ -257,10 +268,11 @@ struct SeedHook {
     u64* seed_keys;
     uint32_t* seed_off;
     bool seed_on;
-    uint32_t seed_is_off;
+    OffWords off;
     static constexpr bool kSeedShare = true;
     static constexpr bool kShareSteps = false;
-    __device__ __forceinline__ bool seeds_shared() const { return seed_on && seed_is_off == 0u; }
+    __device__ __forceinline__ void note_off_words() const { off.note(); }
+    __device__ __forceinline__ bool seeds_shared() const { return seed_on && off.lds[2] == 0u; }
     // Keys c0 and c1 of the head's start set (c1 < 0: only c0, and k1 = k0), polled together a bounded
     // number of times, the slots zeroed for the next launch once the keys are taken; a key that did
     // not come reads 0. A poll is a trip to memory (agent-scope loads go around the caches); more
@@ -289,8 +301,11 @@ struct WalkHook {
     int spin, parts_log2;
     u64* area;
     uint32_t* off_word;
+    OffWords off;
     static constexpr bool kSeedShare = false;
     static constexpr bool kShareSteps = true;
+    __device__ __forceinline__ void note_off_words() const { off.note(); }
+    __device__ __forceinline__ bool steps_shared() const { return off.lds[2] == 0u; }
     __device__ __forceinline__ void steps_missed() const { xwg_store(off_word, 1u); }
 };
 
@@ -375,9 +390,9 @@ __global__ __launch_bounds__(T) void decode_kernel(
         head = ((j - role * rows) << 3) + ((int)blockIdx.x & 7);
         if (head >= n_heads || role > 1 << walk.parts_log2) return;
         if (role > 0) {
-            if (coop_mode == RA_HELPERS_SILENT_ || shares_off != 0u) return;
+            if (coop_mode == RA_HELPERS_SILENT_) return;
             serve_walk<DT, KT, T>(lds_raw, head, role - 1, walk.parts_log2, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg, ef, expand,
-                                  roots, root_cap, kscale, walk.area(head), coop_spin);
+                                  roots, root_cap, kscale, walk.area(head), shares_off, coop_spin);
             return;
         }
     } else {
@@ -407,13 +422,13 @@ __global__ __launch_bounds__(T) void decode_kernel(
         const int b = budgets[head];
         take = b < 1 ? 1 : b > topk ? topk : b;
     }
-    int cnt = -1;
+    const OffWords off{helpers_off, shares_off, lds_word};
+    int cnt;
     if constexpr (Walk::kShare) {
-        if (shares_off == 0u)
-            cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
-                                               s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
-                                               lds_ids, roots, root_cap, kscale,
-                                               WalkHook{coop_spin, walk.parts_log2, walk.area(head), walk.off_word()});
+        cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
+                                           s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
+                                           lds_ids, roots, root_cap, kscale,
+                                           WalkHook{coop_spin, walk.parts_log2, walk.area(head), walk.off_word(), off});
         if (cnt < 0)                                         // alone: the workers have not answered, now or earlier
             cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
                                                s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
@@ -423,7 +438,7 @@ __global__ __launch_bounds__(T) void decode_kernel(
                                            s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
                                            lds_ids, roots, root_cap, kscale,
                                            SeedHook{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx,
-                                                    seed_parts > 0, shares_off});
+                                                    seed_parts > 0, off});
     }
 #ifdef SR_PHASE_CLOCKS
     const long long t_attn = clock64();
@@ -432,7 +447,7 @@ __global__ __launch_bounds__(T) void decode_kernel(
     //      them). The helper's record is asked for behind the first rows, so that its trip past the caches
     //      is over when they have been attended to (asking for a ready word first, when the walk had
     //      ended, and then for the record took a microsecond of every step).
-    const bool helpers = n_helpers > 0 && helpers_off == 0u;
+    const bool helpers = n_helpers > 0 && lds_word[1] == 0u;
     u64* rec = coop + (size_t)head * RA_COOP_REC;
     u64 w_mx = 0ull, w_l = 0ull, w_a = 0ull;
     LaneQuery<DT> ql;
@@ -561,7 +576,7 @@ static size_t decode_lds_bytes(int64_t N, int deg, int ef, int expand, int topk,
     if (b > a) a = b;
     a = (a + 15) & ~(size_t)15;
     *ids_off = (int)a;
-    return a + (size_t)topk * sizeof(int32_t) + 16;        // ids, then a word for the record that did not come
+    return a + (size_t)topk * sizeof(int32_t) + 16;        // ids, then words for the record that did not come and for OffWords
 }
 
 bool ra_decode_needs_global_bitset(int64_t N, int deg, int ef, int expand, int topk) {

@@ -427,17 +427,20 @@ __device__ __forceinline__ void claim_cells(const int (&nb)[L], uint32_t n_keys,
 // `lds_raw` is the workgroup's dynamic LDS (ra_search_lds_bytes of it). Writes ids/stats of
 // `head`; when `lds_ids` is not null the ids are also left there (LDS) for a fused consumer.
 // Returns the number of valid ids. Ends with the whole workgroup past a barrier.
-// A caller's hook into run_search: kSeedShare says whether the start set of a seeded walk may be scored by other workgroups of
+// A caller's hook into run_search: note_off_words() is called by one thread ahead of a barrier of the set-up, for words that
+// another workgroup may set at any moment: the wavefronts of a workgroup must not decide by what each of them has read (they
+// would part at the barriers behind the decision), but by what one thread has read and left in LDS. kSeedShare says whether the start set of a seeded walk may be scored by other workgroups of
 // the launch (score_seed_share below): then seeds_shared() says whether it is in this launch,
 // take_seed_keys(c0, c1, k0, k1) waits (bounded) for keys c0 and c1 of the set (c1 < 0: only c0; k1 is
 // then k0 again) and leaves 0 for one that did not come, and seeds_missed() is called by one thread
 // when some key did not.
-// kShareSteps says whether workers take the claims and the scores of its steps (serve_walk below), with `parts_log2`, `spin`
-// and the head's `area`. When an answer does not come, steps_missed() is called by one thread and the search returns
-// -1, with no ids and no counters written.
+// kShareSteps says whether workers take the claims and the scores of its steps (serve_walk below) if steps_shared(), with
+// `parts_log2`, `spin` and the head's `area`. If not, and when an answer does not come, upon which steps_missed() is called by
+// one thread, the search returns -1, with no ids and no counters written.
 struct NoHook {
     static constexpr bool kSeedShare = false;
     static constexpr bool kShareSteps = false;
+    __device__ __forceinline__ void note_off_words() const {}
 };
 
 // Words that cross workgroups inside one launch: relaxed agent-scope atomics, which go around the
@@ -594,7 +597,7 @@ __device__ __forceinline__ void serve_walk(unsigned char* lds_raw, int head, int
                                            const int32_t* __restrict__ adj, const int32_t* __restrict__ entry,
                                            const void* __restrict__ K, int n_q, int n_kv, int64_t N, int64_t kv_stride, int deg,
                                            int ef, int expand, const int32_t* __restrict__ roots, int root_cap,
-                                           const float* __restrict__ kscale, u64* area, int spin) {
+                                           const float* __restrict__ kscale, u64* area, uint32_t is_off, int spin) {
     const int tid = threadIdx.x, lane = tid & (RA_WAVE - 1), lane16 = tid & 15;
     const int seq = head / n_q, h = head % n_q, kvh = h / (n_q / n_kv);
     const size_t esz = DT == RA_BF16 ? 2 : 4;
@@ -602,7 +605,7 @@ __device__ __forceinline__ void serve_walk(unsigned char* lds_raw, int head, int
     const char* Kh = reinterpret_cast<const char*>(K) + ((size_t)seq * n_kv + kvh) * kv_stride * RA_D * ksz;
     const int32_t* adj_h = adj + (size_t)head * N * deg;
     const int maxc = expand * deg;
-    int* ctr = reinterpret_cast<int*>(lds_raw);      // [0] claimed, [1] kept, [2] picks, [3] a wait ran out, [4..5] worst
+    int* ctr = reinterpret_cast<int*>(lds_raw);      // [0] claimed, [1] kept, [2] picks, [3] steps are not shared, or a wait ran out, [4..5] worst
     u64* worst_at = reinterpret_cast<u64*>(ctr + 4);
     u64* kept = reinterpret_cast<u64*>(ctr + 16);
     int* cid = reinterpret_cast<int*>(kept + maxc);
@@ -622,8 +625,9 @@ __device__ __forceinline__ void serve_walk(unsigned char* lds_raw, int head, int
     const int32_t* root = roots + (size_t)head * root_cap;
     const int n_root = root[0], n_first = root[1];
     for (int i = tid; i < (int)((((N + 31) >> 5) >> parts_log2) + 1); i += T) bits[i] = 0u;
-    if (tid < 16) ctr[tid] = 0;
+    if (tid < 16) ctr[tid] = tid == 3 ? (int)is_off : 0;
     __syncthreads();
+    if (ctr[3]) return;
     auto mine = [&](int id) __attribute__((always_inline)) { return (((uint32_t)id >> 5) & mask) == (uint32_t)part; };
     auto word_of = [&](int id) __attribute__((always_inline)) { return bits + (((uint32_t)id >> 5) >> parts_log2); };
     // the start set (run_search applies the same test)
@@ -858,8 +862,11 @@ __device__ __forceinline__ int run_search(
     // candidates a step keeps, touched while they are merged, and the rows of the beam entries that
     // are next in line after the coming step's picks. The words land in a spare piece of LDS and are
     // read by nothing (touch_line).
+    if (tid == 0) hook.note_off_words();
     __syncthreads();
     SR_TICK(13);
+    if constexpr (Hook::kShareSteps)
+        if (!hook.steps_shared()) return -1;
 #ifdef SR_WAVE_CLOCKS
     if (head == 0 && tid == 0) sr_wave_ticks[2] = wall_clock64();      // claims made
 #endif

@@ -882,3 +882,34 @@ def test_workers_of_shared_steps_all_run_at_once(n_q, shared):
         assert idx.shared_steps_active == shared               # no wait ran out
         assert (idx.shared_messages > sent) == shared
     idx.free()
+
+
+@pytest.mark.parametrize("n_q,n_kv,N,seeds,ef", [
+    (64, 16, 20_003, 1024, 256),           # helpers, seed shares
+    (512, 128, 3_001, 256, 128),           # more searches than compute units: some start when others have given up
+    (20, 20, 800_001, 2048, 1024)])        # shared steps
+def test_hand_overs_switched_off_in_the_middle_of_a_launch(n_q, n_kv, N, seeds, ef):
+    """With a wait of one poll, some heads of a launch give up and set the words that switch hand-overs off while other
+    workgroups read them: whatever a workgroup has read, ids, counters and outputs are the same. (A word is
+    one workgroup's decision: its wavefronts must not differ in it.)"""
+    from paper_2409_10516_amd import binding as B
+    deg, expand, topk = 24, 128, 64
+    g = torch.Generator(device=DEV).manual_seed(n_q)
+    adj = torch.randint(0, N, (n_q, N, deg), generator=g, device=DEV, dtype=torch.int32)
+    idx = ra.ra_index_import(adj.cpu(), torch.zeros(n_q, dtype=torch.int32), 1, n_q, n_kv)
+    del adj
+    K = torch.randn((1, n_kv, N, 128), generator=g, device=DEV, dtype=torch.bfloat16)
+    q = torch.randn((1, n_q, 128), generator=g, device=DEV, dtype=torch.bfloat16)
+    idx.configure(B.RA_CFG_SEEDS, seeds)
+    call = lambda: ra.ra_decode_step(q, idx, K, K, 4, 500, topk, ef, expand)
+    idx.configure(B.RA_CFG_HELPERS, B.RA_HELPERS_OFF)
+    out, lse, ids, st = call()
+    idx.configure(B.RA_CFG_HELPER_SPIN, 1)
+    for _ in range(30):
+        idx.configure(B.RA_CFG_HELPERS, B.RA_HELPERS_ON)       # forgets the waits that ran out
+        for _ in range(2):
+            o, l, i, s = call()
+            assert torch.equal(i, ids) and torch.equal(s, st)
+            # the same sets attended to: float32 sums over some 570 rows in another order, values of norm about 1
+            assert torch.allclose(o, out, rtol=0, atol=1e-5) and torch.allclose(l, lse, rtol=1e-5, atol=1e-5)
+    idx.free()
