@@ -872,9 +872,9 @@ __device__ __forceinline__ int run_search(
 #endif
     // The workers' answers to the last message: the keys go to ckey. A worker's are taken by up to 64 threads, of one wavefront (the word
     // that says how many there are is read by all of them before one zeroes it), each asking for a key together with that word. With the extremes of the ordered score bits.
-    auto collect = [&](uint32_t& lo, uint32_t& hi, int spin_shift) __attribute__((always_inline)) {
+    auto collect = [&](uint32_t& lo, uint32_t& hi) __attribute__((always_inline)) {
         if constexpr (Hook::kShareSteps) {
-            const int spin = max(hook.spin >> spin_shift, 1), per_log2 = min((T == 1024 ? 10 : 9) - hook.parts_log2, 6);
+            const int spin = hook.spin, per_log2 = min((T == 1024 ? 10 : 9) - hook.parts_log2, 6);
             const int per = 1 << per_log2, sub = tid & (per - 1);
             if (tid >> (per_log2 + hook.parts_log2)) return;
             u64* a = sr_answer(hook.area, tid >> per_log2, n_posted);
@@ -928,7 +928,7 @@ __device__ __forceinline__ int run_search(
     };
     if constexpr (Hook::kShareSteps) {
         uint32_t lo = 0xffffffffu, hi = 0u;
-        collect(lo, hi, 3);      // (workers that have not started by then may be long in coming)
+        collect(lo, hi);
         if (fill) {
             wave_min_max(lo, hi);
             if (lane == RA_WAVE - 1) {
@@ -1103,7 +1103,7 @@ __device__ __forceinline__ int run_search(
             if (!first) {
                 post(np, bn == ef ? (cur[bn - 1] >> 1) : 0ull);
                 uint32_t lo = 0xffffffffu, hi = 0u;
-                collect(lo, hi, 0);
+                collect(lo, hi);
             }
             __syncthreads();
             if (ctr[C_MISSED]) break;
