@@ -1207,6 +1207,8 @@ __device__ __forceinline__ int run_search(
         int nk = __builtin_amdgcn_readfirstlane(cc[S_NKEEP]);
         SR_TICK(2);
         if (__builtin_expect(nk == 0, 0)) {               // uniform: nothing enters the beam
+            // (with workers all of this step's counters are read behind one barrier: before the next step clears them)
+            if constexpr (Hook::kShareSteps) __syncthreads();
             picked = false;
             continue;
         }
