@@ -287,7 +287,8 @@ ra_status ra_decode_step_q8(const void* q, const ra_index* idx, const void* K, c
  *   few keys or too many searches for it, switched off, or a head's wait for an answer ran out; synchronises the
  *   device),
  * 10 messages the handle's first search has sent to its workers so far, modulo 2^32: one for every step that was shared, one when
- *   the walk ended (0 where 9 can only be 0; synchronises the device). */
+ *   the walk ended (0 where 9 can only be 0; synchronises the device),
+ * 11 launches of ra_decode_step so far whose walks were to share their steps (one for a launch that is being recorded). */
 int64_t ra_index_info(const ra_index* idx, int what);
 
 /* Settings of the handle's decode path (host side; synchronises the device).
@@ -346,8 +347,9 @@ int64_t ra_index_info(const ra_index* idx, int what);
  *                       0 also keeps ra_decode_step from sharing the steps of long walks: with few searches over a
  *                       context whose visited sets do not fit on chip, and wide steps, each search has 8 or 16
  *                       workgroups of its own in the launch that claim and score its steps' neighbours, with
- *                       hand-overs, bounded waits and a fall-back (the search walks alone) of the same kind, and the
- *                       same ids and counters. */
+ *                       hand-overs, bounded waits and a fall-back of the same kind (the search walks alone; later calls
+ *                       are made as if steps could not be shared, recorded ones walk alone with their seed
+ *                       sets scored by the search), and the same ids and counters. */
 #define RA_CFG_HELPERS 0
 #define RA_CFG_HELPER_SPIN 1
 #define RA_CFG_SEEDS 2

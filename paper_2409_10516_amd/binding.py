@@ -192,6 +192,7 @@ class Index:
     seed_shares_active = property(lambda s: s.info(8) == 1)
     shared_steps_active = property(lambda s: s.info(9) == 1)
     shared_messages = property(lambda s: s.info(10))
+    shared_launches = property(lambda s: s.info(11))
 
     n_seeds = property(lambda s: s.info(7))
 

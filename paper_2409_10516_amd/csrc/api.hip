@@ -112,6 +112,14 @@ static uint32_t* attend_tickets(const ra_index* ix) {
     return reinterpret_cast<uint32_t*>(ix->coop + heads * RA_COOP_REC) + 1;
 }
 
+// the hand-over area of walks that share their steps starts from zero, and with it what is known of waits (the device is idle)
+static ra_status clear_walk(ra_index* ix) {
+    if (!ix->walk) return RA_OK;
+    RA_HIP(hipMemset(ix->walk, 0, ix->walk_bytes));
+    __atomic_store_n(ix->walk_missed, 0u, __ATOMIC_RELAXED);
+    return RA_OK;
+}
+
 static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra_index** out) {
     ra_index* ix = new (std::nothrow) ra_index();
     if (!ix) RA_FAIL(RA_ENOMEM, "host allocation failed");
@@ -125,7 +133,13 @@ static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra
     const size_t entry_at = aligned(ix->graph_bytes), roots_at = entry_at + aligned(graphs * sizeof(int32_t));
     const size_t coop_at = roots_at + aligned(graphs * ix->root_cap * sizeof(int32_t));
     const size_t walk_at = coop_at + aligned(coop_bytes(ix));
-    const size_t parts = graphs < 256 ? ra_walk_parts((int)graphs, N) : 0;
+    size_t parts = graphs < 256 ? ra_walk_parts((int)graphs, N) : 0;
+    if (parts && hipHostMalloc((void**)&ix->walk_missed, sizeof(*ix->walk_missed), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        ix->walk_missed = nullptr;
+        parts = 0;
+    }
+    if (parts) *ix->walk_missed = 0u;
     ix->walk_parts = (int)parts;
     ix->walk_bytes = parts ? (RA_WALK_OFF_WORDS + graphs * (RA_WALK_HEAD_WORDS + parts * RA_WALK_PART_WORDS)) * sizeof(*ix->walk) : 0;
     char* base = nullptr;
@@ -144,6 +158,7 @@ static ra_status new_handle(int n_seq, int n_q, int n_kv, int64_t N, int deg, ra
         ra_set_error("allocating the graph (%zu B) failed: %s", ix->graph_bytes, hipGetErrorString(e));
         (void)hipGetLastError();
         if (base) (void)hipFree(base);
+        if (ix->walk_missed) (void)hipHostFree(ix->walk_missed);
         delete ix;
         return e == hipErrorOutOfMemory ? RA_ENOMEM : RA_EHIP;
     }
@@ -159,6 +174,7 @@ extern "C" void ra_index_free(ra_index* ix) {
     if (ix->bitset) (void)hipFree(ix->bitset);
     if (ix->seeds) (void)hipFree(ix->seeds);
     if (ix->seedx) (void)hipFree(ix->seedx);
+    if (ix->walk_missed) (void)hipHostFree(ix->walk_missed);
     delete ix;
 }
 
@@ -172,7 +188,7 @@ extern "C" ra_status ra_index_configure(ra_index* ix, int what, int64_t value) {
             RA_HIP(hipDeviceSynchronize());
             RA_HIP(hipMemset(ix->coop, 0, coop_bytes(ix)));
             if (ix->seedx) RA_HIP(hipMemset(ix->seedx, 0, ix->seedx_bytes));
-            if (ix->walk) RA_HIP(hipMemset(ix->walk, 0, ix->walk_bytes));
+            RA_TRY(clear_walk(ix));
             ix->coop_mode = (int)value;
             ix->coop_silent = 0;
             return RA_OK;
@@ -186,7 +202,7 @@ extern "C" ra_status ra_index_configure(ra_index* ix, int what, int64_t value) {
                 RA_FAIL(RA_EINVAL, "seed shares %lld: 0 or 2 .. %d", (long long)value, RA_SEED_PARTS_MAX);
             RA_HIP(hipDeviceSynchronize());
             if (ix->seedx) RA_HIP(hipMemset(ix->seedx, 0, ix->seedx_bytes));
-            if (ix->walk) RA_HIP(hipMemset(ix->walk, 0, ix->walk_bytes));
+            RA_TRY(clear_walk(ix));
             ix->seed_parts = (int)value;
             return RA_OK;
         case RA_CFG_SEEDS: {
@@ -239,7 +255,7 @@ extern "C" ra_status ra_test_configure(ra_index* ix, int what, int64_t value) {
             RA_HIP(hipDeviceSynchronize());
             RA_HIP(hipMemset(ix->coop, 0, coop_bytes(ix)));
             if (ix->seedx) RA_HIP(hipMemset(ix->seedx, 0, ix->seedx_bytes));
-            if (ix->walk) RA_HIP(hipMemset(ix->walk, 0, ix->walk_bytes));
+            RA_TRY(clear_walk(ix));
             ix->coop_silent = (int)value;
             return RA_OK;
         default:
@@ -298,6 +314,7 @@ extern "C" int64_t ra_index_info(const ra_index* ix, int what) {
                 return -1;
             return sent;
         }
+        case 11: return ix->walk_launches;
         default: return -1;
     }
 }
@@ -628,11 +645,14 @@ static ra_status decode_common(const void* q, const ra_index* idx, const void* K
         RA_TRY(grow((void**)&ix->bitset, &ix->bitset_bytes, heads * ((ix->N + 31) >> 5) * 4));
     int start_cap;
     const int32_t* start = start_sets(ix, &start_cap);
+    // (a wait that has run out is final, on the device by the area's off word, which launches under way and recorded ones
+    // look at; here, once it is known, the launches that follow are those of walks that do not share, seed shares and all)
+    const bool share = ix->walk && __atomic_load_n(ix->walk_missed, __ATOMIC_RELAXED) == 0u;
     return ra_launch_decode(q, ix->adj, ix->entry, K, V, dt, ix->n_seq, ix->n_q, ix->n_kv, ix->N, N,
                             kv_stride, ix->deg, sink, window, topk, ef, expand, ix->bitset, ix->coop,
                             ix->coop_silent ? RA_HELPERS_SILENT_ : ix->coop_mode, ix->coop_spin, start, start_cap, K8, kscale,
-                            budgets, ix->n_seeds ? ix->seedx : nullptr, ix->seed_parts, ix->walk, ix->walk_parts,
-                            (hipStream_t)stream, out, lse, ids, stats);
+                            budgets, ix->n_seeds ? ix->seedx : nullptr, ix->seed_parts, share ? ix->walk : nullptr, ix->walk_parts,
+                            ix->walk_missed, &ix->walk_launches, (hipStream_t)stream, out, lse, ids, stats);
 }
 
 extern "C" ra_status ra_decode_step_grown(const void* q, const ra_index* idx, const void* K,

@@ -84,6 +84,8 @@ struct ra_index {
     unsigned long long* walk;
     size_t walk_bytes;
     int walk_parts;     // workers per search that it has room for
+    uint32_t* walk_missed;      // host memory: not 0 when a head's wait for its workers has run out
+    int64_t walk_launches;      // launches whose walks were to share their steps
     // root sets: what the first two steps of every walk of a head visit ([n_seq*n_q][root_cap])
     int32_t* roots;
     int root_cap;
@@ -146,6 +148,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
                            uint32_t* bitset, unsigned long long* coop, int coop_mode, int coop_spin,
                            const int32_t* roots, int root_cap, const void* K8, const float* kscale,
                            const int32_t* budgets, uint32_t* seedx, int seed_parts, unsigned long long* walk, int walk_parts,
+                           uint32_t* walk_missed, int64_t* walk_launches,
                            hipStream_t st, float* out, float* lse, int32_t* ids, ra_stats* stats);
 
 ra_status ra_launch_rerank(const void* q, const void* K, ra_dtype dt, int n_seq, int n_q, int n_kv, int64_t N,

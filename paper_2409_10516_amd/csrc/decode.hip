@@ -301,22 +301,27 @@ struct WalkHook {
     int spin, parts_log2;
     u64* area;
     uint32_t* off_word;
+    uint32_t* missed;       // in host memory
     OffWords off;
     static constexpr bool kSeedShare = false;
     static constexpr bool kShareSteps = true;
     __device__ __forceinline__ void note_off_words() const { off.note(); }
     __device__ __forceinline__ bool steps_shared() const { return off.lds[2] == 0u; }
-    __device__ __forceinline__ void steps_missed() const { xwg_store(off_word, 1u); }
+    __device__ __forceinline__ void steps_missed() const {
+        xwg_store(off_word, 1u);
+        __hip_atomic_store(missed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 };
 
 // What the launch adds for walks that share their steps (serve_walk): `heads` of them with 2^parts_log2 workers each, areas from
-// `words`. A type of its own, so that the common kernel has neither the arguments nor the code.
+// `words`, `missed` in host memory. A type of its own, so that the common kernel has neither the arguments nor the code.
 struct NoWalk {
     static constexpr bool kShare = false;
 };
 struct SharedWalk {
     static constexpr bool kShare = true;
     u64* words;
+    uint32_t* missed;
     int heads, parts_log2;
     __device__ __forceinline__ uint32_t* off_word() const { return reinterpret_cast<uint32_t*>(words); }
     __device__ __forceinline__ u64* area(int head) const {
@@ -428,7 +433,7 @@ __global__ __launch_bounds__(T) void decode_kernel(
         cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
                                            s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
                                            lds_ids, roots, root_cap, kscale,
-                                           WalkHook{coop_spin, walk.parts_log2, walk.area(head), walk.off_word(), off});
+                                           WalkHook{coop_spin, walk.parts_log2, walk.area(head), walk.off_word(), walk.missed, off});
         if (cnt < 0)                                         // alone: the workers have not answered, now or earlier
             cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
                                                s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
@@ -623,7 +628,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
                            uint32_t* bitset, unsigned long long* coop, int coop_mode, int coop_spin,
                            const int32_t* roots, int root_cap, const void* K8, const float* kscale,
                            const int32_t* budgets, uint32_t* seedx, int seed_parts, unsigned long long* walk, int walk_parts,
-                           hipStream_t st, float* out, float* lse, int32_t* ids, ra_stats* stats) {
+                           uint32_t* walk_missed, int64_t* walk_launches, hipStream_t st, float* out, float* lse, int32_t* ids, ra_stats* stats) {
     // W = [0, s) u [wstart, N): the sink, the sliding window, and every token appended after the
     // index was built (wstart <= Ng); overlapping ranges make everything static
     int64_t s = sink < 0 ? 0 : sink, ww = window < 0 ? 0 : window;
@@ -680,7 +685,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
         deg * (expand < ef / 4 ? expand : ef / 4) >= RA_WALK_MIN_CELLS && cells <= RA_WALK_CELLS) {
         walk_log2 = 31 - __builtin_clz(walk_parts);
         if (serve_lds_bytes(Ng, deg, expand, walk_log2) > lds) walk_log2 = 0;
-        else parts = 0;
+        else { parts = 0; ++*walk_launches; }
     }
     if (kscale && !K8) RA_FAIL(RA_EINVAL, "8-bit keys missing");
 #define RA_DC_GO_AS(DTV, KTV, GB, TV, BU, WALK, GRID, ...)                                         \
@@ -698,7 +703,8 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
     do {                                                                                           \
         if (walk_log2)                                                                             \
             RA_DC_GO_AS(DTV, KTV, true, (TV < 512 ? 512 : TV), false, SharedWalk,                  \
-                        (heads + 7) / 8 * 8 * (1 + (1 << walk_log2)), SharedWalk{walk, heads, walk_log2}); \
+                        (heads + 7) / 8 * 8 * (1 + (1 << walk_log2)),                              \
+                        SharedWalk{walk, walk_missed, heads, walk_log2});                          \
         else                                                                                       \
             RA_DC_GO_TB(DTV, KTV, GB, TV, false);                                                  \
     } while (0)

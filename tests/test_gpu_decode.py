@@ -913,3 +913,60 @@ def test_hand_overs_switched_off_in_the_middle_of_a_launch(n_q, n_kv, N, seeds, 
             # the same sets attended to: float32 sums over some 570 rows in another order, values of norm about 1
             assert torch.allclose(o, out, rtol=0, atol=1e-5) and torch.allclose(l, lse, rtol=1e-5, atol=1e-5)
     idx.free()
+
+
+def test_shared_steps_recorded_and_after_a_wait_that_ran_out():
+    """Steps are shared in a recorded launch as in others. Once a head has waited in vain, the launches that follow are
+    those of walks that do not share, recorded ones walk alone, and setting RA_CFG_HELPERS starts over: the same ids,
+    counters and outputs throughout."""
+    from paper_2409_10516_amd import binding as B
+    N, deg, expand, ef, topk, n_q = 800_001, 24, 128, 1024, 64, 4
+    g = torch.Generator(device=DEV).manual_seed(5)
+    adj = torch.randint(0, N, (n_q, N, deg), generator=g, device=DEV, dtype=torch.int32)
+    idx = ra.ra_index_import(adj.cpu(), torch.zeros(n_q, dtype=torch.int32), 1, n_q, 1)
+    del adj
+    K = torch.randn((1, 1, N, 128), generator=g, device=DEV, dtype=torch.bfloat16)
+    q = torch.randn((1, n_q, 128), generator=g, device=DEV, dtype=torch.bfloat16)
+    idx.configure(B.RA_CFG_SEEDS, 2048)
+    ids, st = ra.ra_search(q, idx, K, 4, 500, topk, ef, expand)
+    call = lambda: ra.ra_decode_step(q, idx, K, K, 4, 500, topk, ef, expand)
+    base = call()
+
+    def same(r):
+        assert torch.equal(r[2], ids) and torch.equal(r[3], st)
+        # the same sets attended to: float32 sums over some 570 rows in another order, values of norm about 1
+        assert torch.allclose(r[0], base[0], rtol=0, atol=1e-5) and torch.allclose(r[1], base[1], rtol=1e-5, atol=1e-5)
+
+    same(base)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        recorded = call()
+
+    def replayed():
+        for r in recorded:
+            r.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        same(recorded)
+
+    assert idx.shared_launches == 2
+    for _ in range(3):
+        sent = idx.shared_messages
+        replayed()
+        assert idx.shared_steps_active and idx.shared_messages > sent
+        same(call())
+    idx.configure(B.RA_CFG_HELPER_SPIN, 1)
+    same(call())
+    assert not idx.shared_steps_active
+    idx.configure(B.RA_CFG_HELPER_SPIN, 20000)
+    launches, sent = idx.shared_launches, idx.shared_messages
+    for _ in range(3):
+        same(call())
+        replayed()
+    assert idx.shared_launches == launches and idx.shared_messages == sent and not idx.shared_steps_active
+    idx.configure(B.RA_CFG_HELPERS, B.RA_HELPERS_ON)
+    assert idx.shared_steps_active
+    same(call())
+    replayed()
+    assert idx.shared_launches == launches + 1 and idx.shared_steps_active and idx.shared_messages > 0
+    idx.free()
