@@ -314,7 +314,9 @@ def main():
         ms_per_step = 1e3 * wall / steps
         decode_ms_region = ev0.elapsed_time(ev1) / (steps * len(layers))
         helpers_still_on = all(L["idx"].helpers_active for L in layers) if a.helpers else False
-        seed_shares_on = all(L["idx"].seed_shares_active for L in layers) if a.helpers else False
+        # (walks that share their steps have their workers score the start set)
+        steps_shared = all(L["idx"].shared_steps_active and L["idx"].shared_launches for L in layers)
+        seed_shares_on = all(L["idx"].seed_shares_active for L in layers) and not steps_shared if a.helpers else False
 
         # spread of the step latency (a separate pass: one event pair per step, each step waited for)
         lat = []
@@ -416,7 +418,8 @@ def main():
                          "visited_per_search": visited / heads, "expanded_per_search": expanded / heads,
                          "iters_per_search": iters / heads,
                          "helper_workgroups_active_after_timed_region": helpers_still_on,
-                         "seed_workgroups_active_after_timed_region": seed_shares_on},
+                         "seed_workgroups_active_after_timed_region": seed_shares_on,
+                         "walk_workers_active_after_timed_region": steps_shared},
             "build": {"seconds": t_build, "generate_seconds": t_gen,
                       "knn_TFLOPs_incl_projection": build_flop / max(t_build, 1e-9) / 1e12, "knn_kernel": knn_rec},
         }
