@@ -678,7 +678,10 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
     // 4096 / 512 to 1024 76 -> 65, 132 -> 107, 16 heads 110 -> 84, 209 -> 152; 2048 / 256 to 1024 53 -> 53, 79 -> 80, 135 -> 130, 16
     // heads 54 -> 55, 81 -> 78, 139 -> 157; 1024 / 1024 165 -> 203; 4096 / 64 32 -> 47. (With the visited set in LDS the head
     // claims faster than workers could be asked to; scores alone shared out there: mixture law, 128K keys, 3072 / 256 104 -> 84, but
-    // Llama-shaped walks +5 to +10 %.) 8 workers are 1 to 3 % slower than 16.
+    // Llama-shaped walks +5 to +10 %.) 8 workers are 1 to 3 % slower than 16. Inside the lines, both laws, 2 to 24 heads, 0.8 to
+    // 1.5M keys, degree 32 and 64, with and without seed sets, no setting of 200 is slower than alone (1.04 to 1.73 times as fast, 24
+    // heads 1.04 to 1.63). The upper line, RA_WALK_CELLS, is the size of an answer's place and the number of heads what 8
+    // workers each leave room for: wider steps and fewer workers have not been measured.
     int walk_log2 = 0;
     const int cells = expand * deg;
     if (walk && gb && roots && seed_parts > 0 && coop_mode != RA_HELPERS_OFF && !budgets && threads >= 512 && deg >= 2 &&

@@ -544,7 +544,9 @@ __device__ __forceinline__ void score_seed_share(int head, int part, int parts, 
 // written (it waits for those of answer k when it has received k + 1: they are by then). Both are stored 64 words at a
 // time: keys stored as they were scored, a few words per instruction, took 2 to 3 us to arrive. All waits are bounded: a head whose
 // answers do not come walks alone from the start, and the handle shares no walk any more, so words that come late are
-// never taken for the next launch's.
+// never taken for the next launch's. (That walk is a search of its own in the kernel: with both in one, behind a flag, the kernel of
+// bf16 keys and 1024 threads had 128 VGPRs and 112 bytes of scratch memory per lane instead of 114 and none, and
+// 1M keys took 1.5 % longer.)
 #define SR_VALID (1ull << 63)
 #define SR_MSG_LAST 0             // words of a head's part of the hand-over area
 #define SR_MSG_WORDS 8
@@ -1230,8 +1232,9 @@ __device__ __forceinline__ int run_search(
         // is quadratic in the survivors (about ef of them), for the one step where it is large;
         // beam, picks and counters come out as the merge would leave them. Of a seed set all entries are unexpanded: the
         // unexpanded entries above a key are its position. Of a root set those that enter as expanded are counted by bin,
-        // too (ROOT_BINS). One float32 head, a root set of a thousand keys, ef 128: 46.8 -> 44.6 us; root sets that need no filter,
-        // about 230 keys, are merged faster by counting: 39.3 against 40.3 us. Not in the kernels of bf16 and 8-bit keys: the code
+        // too (ROOT_BINS). One float32 head, a root set of a thousand keys, ef 128, timed in turn with and without: 1.6 to
+        // 2.2 of 43.5 to 46.3 us less (six times, on devices that differ by 5 %), for 4 more bytes of scratch memory per
+        // lane in the kernel of 1024 threads; root sets that need no filter, about 230 keys, are merged faster by counting: 39.3 against 40.3 us. Not in the kernels of bf16 and 8-bit keys: the code
         // alone costs their walks from seed sets more (four layers of 128K 95 -> 96.2, 16 sequences of 32K 48.2 -> 49.5 us).
         constexpr bool ROOT_BINS = KT == RA_F32;
         bool bucketed = false;
