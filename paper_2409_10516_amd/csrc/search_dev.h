@@ -427,7 +427,7 @@ __device__ __forceinline__ void claim_cells(const int (&nb)[L], uint32_t n_keys,
 // `lds_raw` is the workgroup's dynamic LDS (ra_search_lds_bytes of it). Writes ids/stats of
 // `head`; when `lds_ids` is not null the ids are also left there (LDS) for a fused consumer.
 // Returns the number of valid ids. Ends with the whole workgroup past a barrier.
-// A caller's hook into run_search: note_off_words() is called by one thread ahead of a barrier of the set-up, for words that
+// A caller's hook into run_search: note_off_words() is called by one thread ahead of the first barrier, for words that
 // another workgroup may set at any moment: the wavefronts of a workgroup must not decide by what each of them has read (they
 // would part at the barriers behind the decision), but by what one thread has read and left in LDS. kSeedShare says whether the start set of a seeded walk may be scored by other workgroups of
 // the launch (score_seed_share below): then seeds_shared() says whether it is in this launch,
@@ -802,8 +802,11 @@ __device__ __forceinline__ int run_search(
     const bool seeded = root && n_first == 0;
     const bool fill = root && n_root <= maxc &&
                       (seeded ? n_root >= 1 : n_first > 1 && expand >= n_first - 1 && ef >= n_first);
+    if (tid == 0) hook.note_off_words();
     __syncthreads();                                             // the LDS state is cleared
     SR_TICK(12);
+    bool seeds_shared = false;               // (asked for here: the claims cover the trip to LDS)
+    if constexpr (Hook::kSeedShare) seeds_shared = hook.seeds_shared();
 #ifdef SR_WAVE_CLOCKS
     if (head == 0 && tid == 0) sr_wave_ticks[1] = wall_clock64();
 #endif
@@ -864,7 +867,6 @@ __device__ __forceinline__ int run_search(
     // candidates a step keeps, touched while they are merged, and the rows of the beam entries that
     // are next in line after the coming step's picks. The words land in a spare piece of LDS and are
     // read by nothing (touch_line).
-    if (tid == 0) hook.note_off_words();
     __syncthreads();
     SR_TICK(13);
     if constexpr (Hook::kShareSteps)
@@ -974,7 +976,7 @@ __device__ __forceinline__ int run_search(
         };
         bool shared = false;
         if constexpr (Hook::kSeedShare) {
-            if (seeded && hook.seeds_shared()) {
+            if (seeded && seeds_shared) {
                 // the keys come from other workgroups of the launch: every thread takes those of its
                 // positions as they arrive; if one does not, the set is scored here after all
                 bool came = true;
