@@ -370,8 +370,8 @@ ra_status ra_index_configure(ra_index* idx, int what, int64_t value);
  *                           RA_TEST_KNN_RESUME_INTS int32, to which each of their launches from now on adds, while there is
  *                           room, a stream position per graph, workgroup of queries and wavefront (2^31 - 1: it came to
  *                           the end); 0: no longer.
- *   RA_TEST_HELPERS_SILENT  (per handle) 1: the helper and seed workgroups of ra_decode_step are
- *                           launched but write nothing, so every head's bounded wait runs out and
+ *   RA_TEST_HELPERS_SILENT  (per handle) 1: the helper and seed workgroups of ra_decode_step, and the workers of shared
+ *                           steps, are launched but write nothing, so every head's bounded wait runs out and
  *                           the fall-back is taken; 0: normal. Synchronises the device and clears
  *                           the hand-over areas like RA_CFG_HELPERS. */
 #define RA_TEST_KNN_SELECTION 100
