@@ -19,10 +19,9 @@
 // atomic-or (which also removes duplicates), their key rows are gathered by 16-lane
 // groups (16 B per lane; four rows per wavefront load), scored, filtered against the
 // beam's worst entry, and merged into the beam by rank: a kept candidate's place is the
-// number of beam entries above it (binary search) plus the number of candidates above it
+// number of beam entries above it (a search) plus the number of candidates above it
 // (counted); a beam entry's place is its index plus a prefix sum over the candidates' slots.
-// No sort, no serial insertion, and the next step's picks fall out of the same numbers. (A step that
-// keeps few candidates finds the same places without the counters.) The
+// No sort, no serial insertion, and the next step's picks fall out of the same numbers. The
 // beam after a step is the top-ef of a set union, so it does not depend on the order in which
 // candidates were claimed.
 //
@@ -52,6 +51,9 @@ enum { S_NCAND = 0, S_NKEEP = 1, S_NUNEXP = 2 };      // of the three words at C
 #define SR_TOUCH_BYTES (4 * RA_WAVE) // where touched words land (touch_line)
 #define SR_PREFILTER_SLACK 64     // a step that keeps more than ef + this many candidates drops the hopeless ones first
 #define SR_PREFILTER_REGS 8       // ... when a thread can hold its share of them (nk <= 8 T)
+#define SR_NARROW 16              // a merge of up to this many candidates takes one phase (half as many with 1024 threads)
+#define SR_DIRECT 64              // a merge of more candidates than this goes through buckets
+#define SR_MERGE_REGS 2           // ... when a thread can hold its share of them
 
 typedef unsigned long long u64;
 
@@ -285,17 +287,6 @@ __device__ __forceinline__ float rows_tree(float (&a)[R], int lane16) {
     return a[0];
 }
 
-// number of entries of the descending array arr[0..n) that beat k (flag bit ignored)
-__device__ __forceinline__ int count_better(const u64* arr, int n, u64 k) {
-    int lo = 0, hi = n;
-    const u64 kk = k | 1ull;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if ((arr[mid] | 1ull) > kk) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
 // Inclusive prefix sum over the 64 lanes of a wavefront (all lanes active): shifts inside each
 // row of 16 lanes, then lane 15 of a row added to the next row, then lane 31 to the upper half.
 template <int CTRL, int ROW_MASK>
@@ -328,41 +319,7 @@ __device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
     min_max_step<0x143, 0xC>(lo, hi);
 }
 
-// number of the first min(n, 16) entries of arr that are larger than k and whose not-yet-expanded flag is clear
-__device__ __forceinline__ int count_above16_expanded(const u64* arr, int n, u64 k) {
-    u64 v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = arr[u];
-    int cnt = 0;
-#pragma unroll
-    for (int u = 0; u < 16; ++u) cnt += (u < n && v[u] > k && !(v[u] & 1ull)) ? 1 : 0;
-    return cnt;
-}
-
-// number of the 16 entries at arr that are larger than k
-__device__ __forceinline__ int count_above16_full(const u64* arr, u64 k) {
-    u64 v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = arr[u];
-    int cnt = 0;
-#pragma unroll
-    for (int u = 0; u < 16; ++u) cnt += v[u] > k ? 1 : 0;
-    return cnt;
-}
-
 static_assert(RA_MAX_EF + RA_MAX_EXPAND * RA_MAX_DEG < 65536, "ranks and merge counts are kept in 16 bits");
-
-// number of the first min(n, 16) entries of arr that are larger than k; all 16 are read (the
-// caller's buffer has 16 entries of slack) so that the loads go out together.
-__device__ __forceinline__ int count_above16(const u64* arr, int n, u64 k) {
-    u64 v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = arr[u];
-    int cnt = 0;
-#pragma unroll
-    for (int u = 0; u < 16; ++u) cnt += (u < n && v[u] > k) ? 1 : 0;
-    return cnt;
-}
 
 // Workgroup -> (sequence, query head). Consecutive workgroup ids are dealt round-robin to the 8
 // XCDs, each with its own L2. The query heads of a GQA group read the same key and value rows, so
@@ -746,9 +703,9 @@ __device__ __forceinline__ int run_search(
     u64* ckey = nxt + ef;            // [maxc + 16] candidates that passed the beam threshold
     int* cid = reinterpret_cast<int*>(ckey + maxc + 16);  // [maxc] claimed neighbour ids
     int* cnt = cid + maxc;           // [maxc] merge counters of the candidates, zero between steps
-    int* hist = cnt + maxc;          // [ef + 1] candidates per beam slot, zero when a wide merge begins
+    int* hist = cnt + maxc;          // [ef + 1] candidates per beam slot, zero when a merge begins
     int* hsum = hist + ef + 1;       // [(ef + 64) / 64] candidates per 64 beam slots, likewise
-    const int nhist = ef + 1 + (ef + 64) / 64;
+    const int nsum = (ef + 64) / 64, nhist = ef + 1 + nsum;
     int* picks = hist + nhist;       // [expand]
     int* ctr = picks + expand;
     // A step's counters: candidates claimed and kept, and the unexpanded entries of the beam it starts
@@ -795,6 +752,7 @@ __device__ __forceinline__ int run_search(
     if constexpr (!Hook::kShareSteps)
         for (int i = tid; i < nwords; i += T) bits[i] = 0u;
     for (int i = tid; i < maxc + nhist; i += T) cnt[i] = 0;      // cnt, hist and hsum
+    for (int i = tid; i < 2 * ef; i += T) cur[i] = 0ull;         // both beams (what follows a beam's last entry is zero)
     // A seed set (ra_launch_seeds) has the same layout with [1] = 0: the walk starts from all of its
     // keys at once, scored in one gather, the best ef of them in the beam and none of them expanded.
     // That is a start of its own, not a shortcut for steps of the single-entry walk: no step is
@@ -1098,9 +1056,11 @@ __device__ __forceinline__ int run_search(
                 ctr[C_NSURV] = 0;
             }
         }
-        if (hist_used) {
+        if (__builtin_expect(hist_used, 0)) {
             for (int i = tid; i < nhist; i += T) hist[i] = 0;
             hist_used = false;
+        } else if (HSUM && tid < nsum) {
+            hsum[tid] = 0;
         }
         if constexpr (Hook::kShareSteps) {
             // ---- the workers claim and score; their answers are waited for
@@ -1377,211 +1337,255 @@ __device__ __forceinline__ int run_search(
 
         // ---- merge by rank into the other beam buffer, truncating at ef. The final position of
         //      an element of (beam u kept candidates) is the number of elements that beat it.
-        //      A candidate: the beam entries above it (binary search in the sorted beam: its slot)
-        //      plus the candidates above it (counted, 16 comparisons per task, tasks spread over
-        //      the workgroup). A beam entry: its index plus the candidates whose slot is at or
-        //      before it, a prefix sum over the histogram of slots. The same numbers give the
-        //      count of *unexpanded* elements above each element (every candidate is unexpanded;
-        //      for the beam's part urank has it), so the next step's picks, the elements with
+        //      A candidate: the beam entries above it (its slot) plus the candidates above it. A beam entry: its
+        //      index plus the candidates whose slot is at or before it, a prefix sum over the histogram of
+        //      slots. The same numbers give the count of *unexpanded* elements above each element (every
+        //      candidate is unexpanded; for the beam's part urank has it), so the next step's picks, the elements with
         //      fewer than `expand` unexpanded ones above them, fall out of the merge.
-        //      Few candidates (NARROW, and not many among any 64 beam entries) take the shorter way below.
-        constexpr int NARROW = 64;                           // one candidate per lane
-        const bool narrow = !first && nk <= NARROW && nk <= 16 + bn / 16;
-        auto sum16 = [&](int v) __attribute__((always_inline)) {       // over the 16 lanes of the group, in each of them
-            v += dpp_i32<0xB1>(v);
-            v += dpp_i32<0x4E>(v);
-            v += dpp_i32<0x141>(v);
-            return v + dpp_i32<0x140>(v);
+        //      What bounds it is instructions: a wavefront or two per SIMD run a few hundred of them, 4 to 8 ticks each,
+        //      16 for a comparison of 64 bits, 30 to 60 for a branch that lanes take apart or a test of two conditions
+        //      (from vector to scalar unit and back), against 64 for a trip to LDS and 20 for a barrier. So places are
+        //      searched and stored without branches, and three ways of counting the candidates above a candidate
+        //      share the rest. Ticks of a merge of 65 to 116 candidates into 256 entries with 512 threads 3400 -> 2500, of 100
+        //      into 2048 with 1024 threads 5200 -> 3900, of 350 into 512 15000 -> 5800, of 4 into 256 1240 -> 950;
+        //      the calls: 50K keys, 2 sequences 38.4 -> 35.6 us, top-2000 185 -> 172, 1M keys 120 -> 114.6, one node per
+        //      step, ef 256 397 -> 378. (Four lanes per candidate, 16-way search and all, were slower than one lane: three
+        //      times the instructions.)
+        const int bn_new = bn + nk < ef ? bn + nk : ef;
+        // An element of the new beam at its place: key, position, unexpanded elements above it. What it does not have to
+        // store goes to the piece that touched words land in: an address chosen by a lane costs it 4 ticks, a branch 30
+        // to 60. (An element past position ef has at least as many unexpanded ones above it as there are picks.) Of a
+        // wavefront's 64 beam entries there is seldom one that is picked, and one is the last: branches for all lanes.
+        auto place = [&](u64 k, int pos, int ur, auto beam) __attribute__((always_inline)) {
+            constexpr bool BEAM = decltype(beam)::value != 0;
+            const int un = (int)(uint32_t)k & 1;
+            const bool pick = (uint32_t)(ur | (un - 1)) < (uint32_t)expand, last = pos == bn_new - 1;
+            if (!BEAM || __builtin_amdgcn_ballot_w64(pick)) *(pick ? picks + ur : reinterpret_cast<int*>(lds_raw)) = key_id(k);
+            k ^= pick ? 1ull : 0ull;
+            *(pos < ef ? nxt + pos : reinterpret_cast<u64*>(lds_raw)) = k;
+            *(pos < ef ? urank_nxt + pos : reinterpret_cast<uint16_t*>(lds_raw)) = (uint16_t)ur;
+            // (the last one has counted all)
+            if (!BEAM || __builtin_amdgcn_ballot_w64(last)) *(last ? cc_nxt + S_NUNEXP : reinterpret_cast<int*>(lds_raw)) = ur + un;
         };
-        // number of beam entries above k (the same for the 16 lanes of a group): a 16-way search, two
-        // dependent reads for a beam of up to 256 entries and three for a longer one; and the unexpanded
-        // ones of them (this step's picks, the first unexpanded entries, are marked expanded by now)
-        auto search16 = [&](u64 k, int& b, int& ub) __attribute__((always_inline)) {
-            b = 0;
-            if (bn > 256) {
-                const int at = lane16 * 256 + 255;
-                b = 256 * sum16(at < bn && cur[at < bn ? at : 0] > k ? 1 : 0);
-            }
-            const int at = b + lane16 * 16 + 15;
-            b += 16 * sum16(at < bn && cur[at < bn ? at : 0] > k ? 1 : 0);
-            const int last = b + lane16;
-            const u64 e = cur[last < bn ? last : 0];
-            ub = (int)urank[b] - np;
-            ub = ub > 0 ? ub : 0;
-            const int up = last < bn && e > k ? 1 : 0;
-            const int n = sum16(up + ((up & (int)e) << 16));         // (low half: above; high half: of them unexpanded)
-            ub += n >> 16;
-            b += n & 0xffff;
+        auto touch_row = [&](int id) __attribute__((always_inline)) {
+            touch_line(reinterpret_cast<const char*>(adj_h) + (u64)(uint32_t)id * (uint32_t)(deg * 4), touch_off);
         };
-        if (__builtin_expect(narrow, 1)) {
-            // ---- a step that keeps few candidates is merged without counters in LDS and without a barrier
-            //      in between: 16 lanes find a candidate's place (its beam slot by a 16-way search,
-            //      two or three dependent reads; the candidates above it by one comparison per lane and 16
-            //      of them), and a wavefront finds its 64 beam entries' places from the candidates held
-            //      one per lane: those above all of the 64 count for every entry, those inside their
-            //      range are compared one by one (45 ticks each, so a beam of 256 takes this way up to 32
-            //      candidates: with 48, 16 picks per step ran 4 % slower, with 16 no faster).
-            //      The wide merge below is three chains of LDS round trips and a barrier whatever the
-            //      number of candidates: 3900 ticks of a step that this does in 1450.
-            const int wn = T / RA_WAVE - 1 - wv;              // the last wavefronts take the first candidates
-            if (tid < nk) touch_line(adj_h + (size_t)key_id(ckey[tid]) * deg, touch_off);
-            for (int c0 = wn * 4; c0 < nk; c0 += T / 16) {
-                const int c = c0 + (lane >> 4);
-                const bool live = c < nk;
-                const u64 k = ckey[live ? c : 0];
-                u64 other[NARROW / 16];
+        // beam entries above k, by a binary search of the same steps for every lane. (Entries from bn on are zero, and the last
+        // one of a full beam is below every kept candidate, so index ef - 1 stands for all that follow.)
+        typedef const __attribute__((address_space(3))) u64* lds_u64;
+        const uint32_t cur_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)cur, cur_last = cur_at + (uint32_t)(ef - 1) * 8u;
+        auto beam_above = [&](u64 k) __attribute__((always_inline)) {
+            uint32_t at = cur_at - 8u;                        // of the entry before the b-th
+            auto halve = [&](uint32_t half) __attribute__((always_inline)) {
+                const uint32_t mid = at + half * 8u;
+                at = *(lds_u64)(uintptr_t)min(mid, cur_last) > k ? mid : at;
+            };
+            static_assert(RA_MAX_EF <= 2048, "eleven steps");
+            const int most = bn < ef ? bn : bn - 1;
+            if (most >= 256) {
+                if (most >= 512) {
+                    if (most >= 1024) halve(1024);
+                    halve(512);
+                }
+                halve(256);
+            }
 #pragma unroll
-                for (int i = 0; i < NARROW / 16; ++i) other[i] = ckey[i * 16 + lane16 < nk ? i * 16 + lane16 : 0];
-                int b, ub;                                    // beam entries above it; the unexpanded ones of them
-                search16(k, b, ub);
-                int above = 0;
+            for (int half = 128; half > 0; half >>= 1) halve(half);
+            return (int)((at + 8u - cur_at) >> 3);
+        };
+        // (this step's picks, the first unexpanded entries, are marked expanded by now)
+        auto unexpanded_above = [&](int b) __attribute__((always_inline)) { return max((int)urank[b] - np, 0); };
+        // zeroes behind the candidates, written by each wavefront that reads them
+        if (!bucketed) ckey[nk + lane16] = 0ull;
+        // of 16 candidates those above k, and (ROOTS: of a root set's start) in the high half the expanded ones of them
+        auto count16 = [&](int at, u64 k, auto roots_c) __attribute__((always_inline)) {
+            u64 v[16];
 #pragma unroll
-                for (int i = 0; i < NARROW / 16; ++i) above += i * 16 + lane16 < nk && other[i] > k ? 1 : 0;
-                above = sum16(above);
-                const int pos = b + above;
-                const bool un = live && lane16 == 0 && pos < ef;
-                const u64 um = __builtin_amdgcn_ballot_w64(un);
-                if (lane == 0 && um) atomicAdd(&cc_nxt[S_NUNEXP], __popcll(um));
-                if (un) {
-                    const int ur = above + ub;
-                    const bool pick = ur < expand;
-                    if (pick) picks[ur] = key_id(k);
-                    nxt[pos] = pick ? k & ~1ull : k;
-                    urank_nxt[pos] = (uint16_t)ur;
+            for (int u = 0; u < 16; ++u) v[u] = ckey[at + u];
+            int n = 0;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const int up = v[u] > k ? 1 : 0;
+                n += up;
+                if constexpr (decltype(roots_c)::value != 0) n += (up & ~(int)(uint32_t)v[u]) << 16;
+            }
+            return n;
+        };
+        // a beam entry with c candidates above it
+        auto place_entry = [&](int e, u64 k, int ub, int c) __attribute__((always_inline)) {
+            const int ur = c + ub, un = (int)(uint32_t)k & 1;
+            place(k, e + c, ur, sr_int<1>{});
+            const bool next = (uint32_t)((ur - expand) | (un - 1)) < (uint32_t)expand;           // in line after those picks
+            if (__builtin_amdgcn_ballot_w64(next)) touch_row(next ? key_id(k) : e0);
+        };
+        // Places of the beam entries of this wavefront's 64s; left(h, before) says what stays in the histogram. What is behind
+        // the last entry is zero and moves behind the new last one.
+        auto place_beam = [&](auto left) __attribute__((always_inline)) {
+            const int end = min(bn + 1, ef);
+            if constexpr (HSUM) {
+                // two of them at a time: the counts of both in one sum
+                const int sums = wave_incl_scan(hsum[min(lane, nsum - 1)]);
+                for (int base = __builtin_amdgcn_readfirstlane(wv * RA_WAVE); base < end; base += 2 * T) {
+                    const int e = base + lane, ec = min(e, ef - 1), f = e + T, fc = min(f, ef - 1);
+                    const bool two = base + T < end;
+                    int* hp = hist + min(e, ef);
+                    int* hq = hist + min(f, ef);
+                    const int h = *hp;
+                    const u64 k = cur[ec];
+                    const int ub = unexpanded_above(ec);
+                    int g = 0, uf = 0;
+                    u64 kf = 0ull;
+                    if (two) {
+                        g = *hq;
+                        kf = cur[fc];
+                        uf = unexpanded_above(fc);
+                    }
+                    const int both = wave_incl_scan(h | g << 16);
+                    const int c = (both & 0xffff) + (base ? __builtin_amdgcn_readlane(sums, base / RA_WAVE - 1) : 0);
+                    *hp = left(h, c - h);
+                    place_entry(e, k, ub, c);
+                    if (two) {
+                        const int cf = (int)((uint32_t)both >> 16) + __builtin_amdgcn_readlane(sums, (base + T) / RA_WAVE - 1);
+                        *hq = left(g, cf - g);
+                        place_entry(f, kf, uf, cf);
+                    }
+                }
+            } else {
+                for (int base = __builtin_amdgcn_readfirstlane(wv * RA_WAVE); base < end; base += T) {
+                    const int e = base + lane, ec = min(e, ef - 1);
+                    int* hp = hist + min(e, ef);
+                    const int h = *hp;
+                    const u64 k = cur[ec];
+                    const int ub = unexpanded_above(ec);
+                    int earlier = 0;
+                    for (int x = 0; x < base; x += RA_WAVE) earlier += hist[x + lane] & 0xffff;
+                    const int c = wave_incl_scan(h) + __builtin_amdgcn_readlane(wave_incl_scan(earlier), RA_WAVE - 1);
+                    *hp = left(h, c - h);
+                    place_entry(e, k, ub, c);
                 }
             }
-            for (int e0 = wv * RA_WAVE; e0 < bn; e0 += T) {
-                const int e = e0 + lane;
-                u64 k = cur[e < bn ? e : bn - 1];
-                const int ub = (int)urank[e < bn ? e : bn - 1] - np;
-                const uint32_t klo = (uint32_t)k, khi = (uint32_t)(k >> 32);
-                const u64 hi = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)khi, 0) << 32) |
-                               (uint32_t)__builtin_amdgcn_readlane((int)klo, 0);
-                const u64 lo = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)khi, RA_WAVE - 1) << 32) |
-                               (uint32_t)__builtin_amdgcn_readlane((int)klo, RA_WAVE - 1);
-                const u64 ck = ckey[lane < nk ? lane : 0];
-                const u64 all = __builtin_amdgcn_ballot_w64(lane < nk && ck > hi);
-                u64 inside = __builtin_amdgcn_ballot_w64(lane < nk && ck > lo) & ~all;
-                int c = __popcll(all);
-                const int clo = (int)(uint32_t)ck, chi = (int)(uint32_t)(ck >> 32);
-                while (inside) {
-                    const int l = __builtin_ctzll(inside);
-                    inside &= inside - 1ull;
-                    const u64 x = ((u64)(uint32_t)__builtin_amdgcn_readlane(chi, l) << 32) |
-                                  (uint32_t)__builtin_amdgcn_readlane(clo, l);
-                    c += x > k ? 1 : 0;
-                }
-                const int pos = e + c, ur = c + (ub > 0 ? ub : 0);
-                const bool un = e < bn && pos < ef && (k & 1ull);
-                const u64 um = __builtin_amdgcn_ballot_w64(un);
-                if (lane == 0 && um) atomicAdd(&cc_nxt[S_NUNEXP], __popcll(um));
-                if (un && ur < expand) {
-                    picks[ur] = key_id(k);
-                    k &= ~1ull;
-                } else if (un && ur < 2 * expand) {           // next in line after those picks
-                    touch_line(adj_h + (size_t)key_id(k) * deg, touch_off);
-                }
-                if (e < bn && pos < ef) {
-                    nxt[pos] = k;
-                    urank_nxt[pos] = (uint16_t)ur;
-                }
+        };
+        if (bucketed) {
+        } else if (__builtin_expect(!first && nk <= (T == 1024 ? SR_NARROW / 2 : SR_NARROW), 1)) {
+            // ---- few candidates, one phase: 16 lanes find a candidate's place (its slot by a 16-way search, two or three
+            //      dependent reads; the candidates above it by one comparison per lane), and a beam entry is compared
+            //      with every candidate.
+            static_assert(SR_NARROW == 16, "a candidate per lane of a group");
+            auto count_group = [&](bool up) __attribute__((always_inline)) {         // lanes of the group of 16 that say so
+                const u64 m = __builtin_amdgcn_ballot_w64(up);
+                return __popc((lane & 32 ? (uint32_t)(m >> 32) : (uint32_t)m) >> (lane & 16) & 0xffffu);
+            };
+            for (int c0 = __builtin_amdgcn_readfirstlane((T / RA_WAVE - 1 - wv) * 4); c0 < nk; c0 += T / 16) {
+                // (the groups past the last candidate do what the last one's does)
+                const u64 k = ckey[min(c0 + (lane >> 4), nk - 1)];
+                const u64 other = ckey[lane16];
+                int b = 0;
+                if (bn > 256) b = 256 * count_group(cur[min(lane16 * 256 + 255, ef - 1)] > k);
+                b += 16 * count_group(cur[min(b + lane16 * 16 + 15, ef - 1)] > k);
+                const u64 e = cur[min(b + lane16, ef - 1)];
+                int ub = unexpanded_above(b);
+                const bool up = e > k;
+                b += count_group(up);
+                ub += count_group(up && (e & 1ull));
+                const int n = count_group(lane16 < nk && other > k);
+                place(k, b + n, n + ub, sr_int<0>{});
+                touch_row(key_id(k));
             }
-        } else if (!bucketed) {
-            const int E = bn + nk;
-            const int nch = (nk + 15) >> 4;
-            const int items = nk * nch;
-            hist_used = true;
-            if (tid < nk) touch_line(adj_h + (size_t)key_id(ckey[tid]) * deg, touch_off);
-            for (int c = tid; c < nk; c += T) {
-                const int b = count_better(cur, bn, ckey[c]);
-                if (b) atomicAdd(&cnt[c], b << 16);           // high half: beam entries above it
-                atomicAdd(&hist[b], 1);
-                if constexpr (HSUM) atomicAdd(&hsum[b >> 6], 1);
+            for (int base = __builtin_amdgcn_readfirstlane(wv * RA_WAVE); base < bn; base += T) {
+                const int e = base + lane, ec = min(e, ef - 1);
+                const u64 k = cur[ec];
+                const int ub = unexpanded_above(ec);
+                int c = 0;
+                for (int i0 = 0; i0 < nk; i0 += 8) {
+                    u64 v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = ckey[i0 + u];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) c += v[u] > k ? 1 : 0;
+                }
+                place_entry(e, k, ub, c);
             }
+        } else if (!first && nk > SR_DIRECT && nk <= SR_MERGE_REGS * T) {
+            // ---- many: dealt into buckets by slot, and counted inside a bucket. (us per layer if from 17, 33, 65 and 129
+            //      candidates on: top-2000 165.6, 165.6, 165.8, 173; 64K keys, 16 picks, ef 128 32.1, 30.8, 30.1, 30.1; two sequences
+            //      of 50K keys 35.0, 34.9, 34.7, 35.2.)
+            u64 mine[SR_MERGE_REGS];
+            int at[SR_MERGE_REGS], o[SR_MERGE_REGS];
+#pragma unroll
+            for (int r = 0; r < SR_MERGE_REGS; ++r)
+                if (r * T + tid < nk) {
+                    mine[r] = ckey[r * T + tid];
+                    touch_row(key_id(mine[r]));
+                    at[r] = beam_above(mine[r]);
+                    if constexpr (HSUM) atomicAdd(&hsum[at[r] >> 6], 1);
+                    o[r] = atomicAdd(&hist[at[r]], 1);
+                }
+            __syncthreads();
             SR_TICK(8);
-            const float inv_nk = 1.0f / (float)nk;
-            // (tasks are dealt from the last thread down: the first threads, busy with the binary
-            // searches above, get the fewest)
-            for (int a = T - 1 - tid; a < items; a += T) {
-                // a = ch * nk + c without an integer division: the float quotient is off by at most one
-                int ch = (int)((float)a * inv_nk), c = a - ch * nk;
-                if (c < 0) { --ch; c += nk; }
-                if (c >= nk) { ++ch; c -= nk; }
-                const int above = ch + 1 < nch ? count_above16_full(ckey + ch * 16, ckey[c])
-                                               : count_above16(ckey + ch * 16, nk - ch * 16, ckey[c]);
-                if (above) atomicAdd(&cnt[c], above);
-                if (first && n_first > 0) {
-                    // the doubled first step has expanded candidates too: how many of those beat
-                    // this one goes into the counter's high half (the beam is empty, so it is free)
-                    const int exp_above = count_above16_expanded(ckey + ch * 16, nk - ch * 16, ckey[c]);
-                    if (exp_above) atomicAdd(&cnt[c], exp_above << 16);
-                }
-            }
+            hist_used = true;
+            place_beam([&](int h, int before) __attribute__((always_inline)) { return h | before << 16; });
+            __syncthreads();
             SR_TICK(9);
+#pragma unroll
+            for (int r = 0; r < SR_MERGE_REGS; ++r)
+                if (r * T + tid < nk) ckey[(hist[at[r]] >> 16) + o[r]] = mine[r];
             __syncthreads();
             SR_TICK(3);
-            SR_TICK(10);
-            for (int e0 = 0; e0 < E; e0 += T) {                   // T elements per round
-                const int e = e0 + tid;
-                // candidates above beam entry e: inclusive prefix sum of hist, by wavefront, each
-                // adding up the part of hist before its own 64 entries itself (no second barrier)
-                int cbeam = 0;
-                if (e0 + wv * RA_WAVE < bn) {                     // this wavefront has beam entries
-                    int before = 0;
-                    if constexpr (HSUM) {
-                        if (lane < e0 / RA_WAVE + wv) before = hsum[lane];      // (there are such sums: e < bn)
-                    } else {
-                        for (int x = 0; x < e0 / RA_WAVE + wv; ++x) before += hist[x * RA_WAVE + lane];
-                    }
-                    before = __builtin_amdgcn_readlane(wave_incl_scan(before), RA_WAVE - 1);
-                    cbeam = before + wave_incl_scan(e < bn ? hist[e] : 0);
+#pragma unroll
+            for (int r = 0; r < SR_MERGE_REGS; ++r)
+                if (r * T + tid < nk) {
+                    const int hb = hist[at[r]], beg = hb >> 16, n = hb & 0xffff;
+                    int c = beg, j0 = 0;
+                    // (past the bucket's end its last key again, taken off below)
+                    do {
+                        u64 other[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) other[i] = ckey[beg + min(j0 + i, n - 1)];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) c += other[i] > mine[r] ? 1 : 0;
+                        j0 += 4;
+                    } while (__builtin_amdgcn_ballot_w64(j0 < n));
+                    c -= ckey[beg + n - 1] > mine[r] ? j0 - n : 0;
+                    place(mine[r], at[r] + c, c + unexpanded_above(at[r]), sr_int<0>{});
                 }
-                bool un = false;
-                if (e < E) {
-                    const bool beam = e < bn;
-                    u64 k;
-                    int c, b;                                     // candidates / beam entries above
-                    if (beam) {
-                        k = cur[e];
-                        c = cbeam;
-                        b = e;
-                    } else {
-                        const int both = cnt[e - bn];
-                        cnt[e - bn] = 0;
-                        k = ckey[e - bn];
-                        c = both & 0xffff;
-                        b = both >> 16;
-                    }
-                    int pos, ur;                                  // ur: unexpanded elements above this one
-                    if (first) {                                  // empty beam; b counts expanded candidates above
-                        pos = c;
-                        ur = c - b;
-                        b = 0;
-                    } else {
-                        pos = b + c;
-                        const int ub = (int)urank[b] - np;        // this step's picks are expanded now
-                        ur = c + (ub > 0 ? ub : 0);
-                    }
-                    un = pos < ef && (k & 1ull);
-                    if (un && ur < expand) {
-                        picks[ur] = key_id(k);
-                        k &= ~1ull;
-                    }
-                    else if (beam && un && ur < 2 * expand) {     // next in line after those picks
-                        touch_line(adj_h + (size_t)key_id(k) * deg, touch_off);
-                    }
-                    if (pos < ef) {
-                        nxt[pos] = k;
-                        urank_nxt[pos] = (uint16_t)ur;
-                    }
+        } else {
+            // ---- the candidates above a candidate are counted, 16 at a time for 64 candidates, by the first wavefronts,
+            //      while the last ones find the slots
+            for (int c = T - 1 - tid; c < nk; c += T) {
+                const u64 k = ckey[c];
+                touch_row(key_id(k));
+                if (!first) {
+                    const int b = beam_above(k);
+                    if constexpr (HSUM) atomicAdd(&hsum[b >> 6], 1);
+                    atomicAdd(&hist[b], 1);
+                    atomicAdd(&cnt[c], b << 16);              // high half: beam entries above it
                 }
-                const u64 um = __ballot(un);
-                if (lane == 0 && um) atomicAdd(&cc_nxt[S_NUNEXP], __popcll(um));
+            }
+            const int chunks = (nk + 15) >> 4;
+            int t = __builtin_amdgcn_readfirstlane(wv);
+            for (int g0 = 0; g0 < nk; g0 += RA_WAVE, t -= chunks)
+                for (; t < chunks; t += T / RA_WAVE) {
+                    const int c = min(g0 + lane, nk - 1);
+                    const u64 k = ckey[c];
+                    const int n = first && n_first > 0 ? count16(t * 16, k, sr_int<1>{}) : count16(t * 16, k, sr_int<0>{});
+                    if (g0 + lane < nk && n) atomicAdd(&cnt[c], n);
+                }
+            __syncthreads();
+            SR_TICK(8);
+            if (!first) place_beam([&](int h, int) __attribute__((always_inline)) { return HSUM ? 0 : h; });
+            hist_used = hist_used || !HSUM;      // (others read it too)
+            SR_TICK(9);
+            for (int c = T - 1 - tid; c < nk; c += T) {
+                const int both = cnt[c], n = both & 0xffff, b = both >> 16;
+                cnt[c] = 0;
+                const u64 k = ckey[c];
+                const int ub = first ? -b : unexpanded_above(b);
+                place(k, first ? n : b + n, n + ub, sr_int<0>{});
             }
         }
         __syncthreads();
         SR_TICK(4);
-        bn = bn + nk < ef ? bn + nk : ef;
+        bn = bn_new;
         u64* t = cur; cur = nxt; nxt = t;
         uint16_t* tu = urank; urank = urank_nxt; urank_nxt = tu;
         int* tc = cc; cc = cc_nxt; cc_nxt = tc;

@@ -326,6 +326,31 @@ def test_merges_at_the_limits_of_beam_and_candidates(ef):
         assert st[0, 0].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]]
 
 
+@pytest.mark.parametrize("distinct", [1, 3, 40, 3000])
+@pytest.mark.parametrize("ef,expand,deg", [(20, 1, 9), (64, 16, 4), (100, 64, 40), (255, 33, 31), (257, 40, 40), (300, 64, 40),
+                                           (700, 4, 40), (1300, 64, 40), (2048, 256, 12)])
+def test_merges_of_any_size(ef, expand, deg, distinct):
+    """Merges of one to some thousand candidates, by every way there is and into beams of every length on the way, of keys that
+    all differ, that share a few scores, or that all have the same (a slot then holds every candidate, and more of them
+    than the threads keep): ids and counters as the oracle has them, exactly, for integer inputs over a random graph."""
+    rng, N = np.random.default_rng(ef + distinct), 3000
+    K = rng.integers(-4, 5, size=(distinct, 128))[rng.integers(0, distinct, size=N) if distinct < N else np.arange(N)]
+    adj = rng.integers(-1, N, size=(2, N, deg)).astype(np.int32)
+    ent, q, topk = np.array([5, N - 1], np.int32), rng.integers(-4, 5, size=(2, 128)), min(ef, 50)
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.from_numpy(ent), 1, 2, 1)
+    Kd = torch.from_numpy(K).to(torch.bfloat16).reshape(1, 1, N, 128).to(DEV)
+    qd = torch.from_numpy(q).to(torch.bfloat16).reshape(1, 2, 128).to(DEV)
+    W = OA.static_ids(N, 4, 100)
+    ids, st = ra.ra_search(qd, idx, Kd, 4, 100, topk, ef, expand)
+    _, _, ids_d, st_d = ra.ra_decode_step(qd, idx, Kd, Kd, 4, 100, topk, ef, expand)
+    assert torch.equal(ids, ids_d) and torch.equal(st, st_d)
+    for h in range(2):
+        ref, rst = OS.greedy_search(q[h].astype(np.float32), K.astype(np.float32), adj[h], int(ent[h]), ef, topk, expand, exclude=W)
+        assert ids[0, h].tolist() == ref.tolist()
+        assert st[0, h].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]]
+    idx.free()
+
+
 @pytest.mark.parametrize("n_q,n_kv,dtype", [(8, 1, torch.bfloat16), (4, 2, torch.bfloat16), (8, 1, torch.float32),
                                             (4, 1, torch.float32)])
 def test_decode_step_other_group_sizes(n_q, n_kv, dtype):
