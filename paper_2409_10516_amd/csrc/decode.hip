@@ -44,16 +44,6 @@ struct Softmax8 {          // a lane's share of an online-softmax state: 8 of th
     float m, l, acc[8];
 };
 
-__device__ __forceinline__ void sm_merge(Softmax8& a, float mo, float lo, const float* acco) {
-    const float mn = fmaxf(a.m, mo);
-    if (mn == -INFINITY) return;                    // both empty
-    const float ca = expf(a.m - mn), co = expf(mo - mn);
-    a.l = a.l * ca + lo * co;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) a.acc[e] = a.acc[e] * ca + acco[e] * co;
-    a.m = mn;
-}
-
 // exp for the softmax weights: the hardware exponential for bf16 data (its error, about 1e-6
 // relative for the exponents that matter, is far below the bf16 inputs'), the library one for fp32.
 template <int DT>
@@ -123,16 +113,19 @@ template <> struct LaneQuery<RA_F32> {
     }
 };
 
-// x of lane ^ 16 or lane ^ 32, by the vector unit's row and half exchanges (a shuffle is a trip through LDS:
-// the twenty of a combination were a sixth of the attention over 100 rows).
-__device__ __forceinline__ float lane_xor_rows(float x, int d, int lane) {
-    const unsigned v = __float_as_uint(x);
-    if (d == 16) {
-        const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        return __uint_as_float((lane & 16) ? p[0] : p[1]);
-    }
-    const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return __uint_as_float((lane & 32) ? p[0] : p[1]);
+// The largest, or the sum, of x over lanes lane ^ {0, 16, 32, 48}, by the vector unit's row and half exchanges (a shuffle is a trip
+// through LDS): of a register swapped with itself one result has the value of each pair's first lane, the other the second's.
+__device__ __forceinline__ float rows_max(float x) {
+    auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+__device__ __forceinline__ float rows_sum(float x) {
+    auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
 
 // Combine the online-softmax states of the lane groups of a workgroup of T threads into one (max,
@@ -142,21 +135,19 @@ __device__ __forceinline__ float lane_xor_rows(float x, int d, int lane) {
 template <int T>
 __device__ __forceinline__ void sm_combine(Softmax8 st, float* lds, int tid, float& mx, float& l, float& a) {
     const int lane = tid & (RA_WAVE - 1), wv = tid / RA_WAVE;
+    // one maximum for the wavefront, one exponential per lane, sums (an empty state has the sum 0 and exp(-inf) = 0)
+    const float m = rows_max(st.m);
+    const float c = expf(st.m - (m > -INFINITY ? m : 0.f));
+    st.l = rows_sum(st.l * c);
 #pragma unroll
-    for (int d = 16; d <= 32; d <<= 1) {
-        const float mo = lane_xor_rows(st.m, d, lane), lo = lane_xor_rows(st.l, d, lane);
-        float ao[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ao[e] = lane_xor_rows(st.acc[e], d, lane);
-        sm_merge(st, mo, lo, ao);
-    }
+    for (int e = 0; e < 8; ++e) st.acc[e] = rows_sum(st.acc[e] * c);
     float* sm = lds;                                         // [16]
     float* sl = sm + T / RA_WAVE;                   // [16]
     float* sa = sl + T / RA_WAVE;                   // [16][128]
     __syncthreads();                                         // whatever was in `lds` is dead
     if (lane < 16) {
         if (lane == 0) {
-            sm[wv] = st.m;
+            sm[wv] = m;
             sl[wv] = st.l;
         }
 #pragma unroll
@@ -468,31 +459,45 @@ __global__ __launch_bounds__(T) void decode_kernel(
         for (int e = 0; e < 8; ++e) st.acc[e] = 0.f;
         if (R <= 0) behind();
         for (int r0 = 0; r0 < R; r0 += (T / 16) * DC_ROWS) {
-            int64_t rid[DC_ROWS];
             RowBits<DT> kb[DC_ROWS], vb[DC_ROWS];
+            float z[DC_ROWS];
 #pragma unroll
             for (int u = 0; u < DC_ROWS; ++u) {
                 if (r0 + u * (T / 16) >= R) break;          // uniform: no group has a row in this slot
-                const int r = r0 + u * (T / 16) + grp;
-                const int64_t id = r < R ? row_id(r) : -1;
-                rid[u] = id;
-                const int64_t safe = id >= 0 ? id : 0;      // loads stay unconditional
-                kb[u] = load_key<DT>(Kh, safe, lane16);
-                vb[u] = load_key<DT>(Vh, safe, lane16);
+                const int64_t id = row_id(min(r0 + u * (T / 16) + grp, R - 1));
+                kb[u] = load_key<DT>(Kh, id, lane16);
+                vb[u] = load_key<DT>(Vh, id, lane16);
             }
             if (r0 == 0) behind();
+            // the logits, their maximum, then one rescaling of the sums for all of them (row by row, with a branch around the
+            // rescaling, 100 rows took 3700 ticks)
+            float m = st.m;
 #pragma unroll
             for (int u = 0; u < DC_ROWS; ++u) {
-                if (r0 + u * (T / 16) >= R) break;
-                if (rid[u] < 0) continue;
+                z[u] = -INFINITY;
+                if (r0 + u * (T / 16) >= R) continue;
                 float dot = ql.dot(kb[u]);
                 dot += at_dpp<0xB1>(dot);
                 dot += at_dpp<0x4E>(dot);
                 dot += at_dpp<0x141>(dot);
                 dot += at_dpp<0x140>(dot);
+                z[u] = r0 + u * (T / 16) + grp < R ? dot * scale : -INFINITY;
+                m = fmaxf(m, z[u]);
+            }
+            const float m0 = m > -INFINITY ? m : 0.f, corr = sm_exp<DT>(st.m - m0);        // (exp(-inf) = 0: no row yet)
+            st.m = m;
+            st.l *= corr;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) st.acc[e] *= corr;
+#pragma unroll
+            for (int u = 0; u < DC_ROWS; ++u) {
+                if (r0 + u * (T / 16) >= R) break;
+                const float p = sm_exp<DT>(z[u] - m0);
                 float v[8];
                 row_floats<DT>(vb[u], v);
-                sm_row<DT>(st, dot * scale, v);
+                st.l += p;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) st.acc[e] = fmaf(p, v[e], st.acc[e]);
             }
         }
         return st;
@@ -510,7 +515,8 @@ __global__ __launch_bounds__(T) void decode_kernel(
             }
         });
     float mx, l, a;
-    sm_combine<T>(st_om, reinterpret_cast<float*>(lds_raw), tid, mx, l, a);
+    float* const scratch = reinterpret_cast<float*>(lds_raw + SR_TOUCH_BYTES);       // (touched words may still land in front of it)
+    sm_combine<T>(st_om, scratch, tid, mx, l, a);
     // ---- the record, waited for a bounded number of polls; without it, W by this workgroup itself, and
     //      no helpers in later launches
     float mw = -INFINITY, lw = 0.f, aw = 0.f;
@@ -536,7 +542,7 @@ __global__ __launch_bounds__(T) void decode_kernel(
         if (!have_w) {
             if (tid == 0) xwg_store(helpers_off_word, 1u);
             const Softmax8 st_w = attend_rows(n_w, w_row, []() {});
-            sm_combine<T>(st_w, reinterpret_cast<float*>(lds_raw), tid, mw, lw, aw);
+            sm_combine<T>(st_w, scratch, tid, mw, lw, aw);
         }
     }
     // ---- Eq. 4-5: the two sets re-scaled to one maximum
@@ -549,12 +555,13 @@ __global__ __launch_bounds__(T) void decode_kernel(
         }
         const bool empty = !(l > 0.f);
         out[(size_t)head * RA_D + tid] = empty ? 0.f : a / l;
-        if (tid == 0) lse[head] = empty ? -INFINITY : m2 + logf(l);
+        if (tid == RA_WAVE) lse[head] = empty ? -INFINITY : m2 + logf(l);         // (by the second wavefront: the first has the record's last words)
         if (have_w) {                                        // taken: the next launch starts from zero
             xwg_store(rec + 2 + tid, 0ull);
             if (tid < 2) xwg_store(rec + tid, 0ull);
         }
     }
+    end_touches();
 #ifdef SR_PHASE_CLOCKS
     if (tid == 0 && head < 64) sr_phase_ticks[head * SR_NITER * SR_NPHASE + 7] += clock64() - t_attn;
 #endif
@@ -578,7 +585,7 @@ extern "C" int ra_dbg_phase_ticks(long long* host) {
 
 static size_t decode_lds_bytes(int64_t N, int deg, int ef, int expand, int topk, bool gb, int* ids_off) {
     size_t a = search_lds_bytes(N, deg, ef, expand, gb);
-    const size_t b = (size_t)(SR_THREADS / RA_WAVE) * (RA_D + 2) * sizeof(float);
+    const size_t b = SR_TOUCH_BYTES + (size_t)(SR_THREADS / RA_WAVE) * (RA_D + 2) * sizeof(float);
     if (b > a) a = b;
     a = (a + 15) & ~(size_t)15;
     *ids_off = (int)a;

@@ -11,6 +11,7 @@ __global__ __launch_bounds__(T) void search_kernel(
     extern __shared__ __align__(16) unsigned char lds_raw[];
     run_search<DT, KT, GBITS, T>(lds_raw, xcd_aware_head(blockIdx.x, gridDim.x, n_q / n_kv), q, adj, entry, K, n_q, n_kv, N, N, deg, s, w, topk, topk, ef,
                           expand, gbits, ids, stats, nullptr, roots, root_cap, kscale, NoHook());
+    end_touches();
 }
 
 // Root sets (see run_search): per head [0] the number of ids, [1] 1 + the number of the entry

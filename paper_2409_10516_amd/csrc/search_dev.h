@@ -341,10 +341,12 @@ __device__ __forceinline__ uint32_t claim_key(uint32_t* bits, int id) {
 // Brings p's line into this XCD's L2 (p 4-byte aligned, in bounds): a load of one word that goes straight to
 // LDS, to 4 bytes per lane at lds_off that nothing reads, so that no register waits for it. (Ordinary loads
 // whose words fed a test that never held were waited for when the walk's loop turned: 700 of 7500 ticks
-// of a step that expands 16 nodes.) A wavefront waits for its own before the search ends.
+// of a step that expands 16 nodes.) A wavefront waits for its own before it ends.
 __device__ __forceinline__ void touch_line(const void* p, uint32_t lds_off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_off), "v"(p) : "m0");
 }
+
+__device__ __forceinline__ void end_touches() { __builtin_amdgcn_s_waitcnt(0x0F70); }      // vmcnt(0)
 
 // Claims L neighbours per lane and appends those not visited before to cid, `n_claimed` of them so far; bit_word(id) is the word of the
 // visited set that has id's bit, wanted(id) whether id is to be claimed here. All claims are on their way before the first
@@ -383,7 +385,8 @@ __device__ __forceinline__ void claim_cells(const int (&nb)[L], uint32_t n_keys,
 // kv_stride rows (kv_stride >= N: the cache may hold tokens appended after the index was built).
 // `lds_raw` is the workgroup's dynamic LDS (ra_search_lds_bytes of it). Writes ids/stats of
 // `head`; when `lds_ids` is not null the ids are also left there (LDS) for a fused consumer.
-// Returns the number of valid ids. Ends with the whole workgroup past a barrier.
+// Returns the number of valid ids. Ends with the whole workgroup past a barrier. Touched words may still be on their way to the first
+// SR_TOUCH_BYTES of lds_raw: the caller leaves these alone, and every wavefront waits for its loads before it ends (end_touches).
 // A caller's hook into run_search: note_off_words() is called by one thread ahead of the first barrier, for words that
 // another workgroup may set at any moment: the wavefronts of a workgroup must not decide by what each of them has read (they
 // would part at the barriers behind the decision), but by what one thread has read and left in LDS. kSeedShare says whether the start set of a seeded walk may be scored by other workgroups of
@@ -819,7 +822,6 @@ __device__ __forceinline__ int run_search(
     const int xs0 = min(tid - xr0 * deg, deg - 1), xs1 = min(tid + T - xr1 * deg, deg - 1);
     const int gi0 = min(grp, maxc - 1), gi1 = min(grp + T / 16, maxc - 1);
     int pk0 = e0, pk1 = e0;          // the picks of those cells
-    bool picked = true;              // the merge of the last step already chose this step's picks
     // Adjacency rows likely to be expanded soon are touched ahead of time (one word of the row's
     // first line), so that the row is in this XCD's L2 when its step reads it: the rows of the
     // candidates a step keeps, touched while they are merged, and the rows of the beam entries that
@@ -988,52 +990,18 @@ __device__ __forceinline__ int run_search(
     for (;;) {
         SR_TICK_ITER(n_iters);
         int np;
+        int unexpanded = 0;          // entries of the beam left unexpanded by this step
         if (__builtin_expect(first, 0)) {
             np = 0;                  // nothing of the (empty) beam is expanded: see the set-up
-        } else if (__builtin_expect(!picked, 0)) {
-            // ---- pick the `expand` best unexpanded entries: the beam is sorted, so the picks are
-            //      the first `expand` set flags in beam order. T entries per round, one per
-            //      thread: ballot prefix inside a wavefront, wavefront totals through LDS, the
-            //      rounds before it carried in `total`. The round loop also covers index bn, one
-            //      past the end, whose rank is the number of unexpanded entries in all.
-            int total = 0;
-            for (int e0 = 0; e0 <= bn; e0 += T) {
-                const int e = e0 + tid;
-                const u64 mykey = e < bn ? cur[e] : 0ull;
-                const bool un = (mykey & 1ull) != 0;
-                const u64 unmask = __ballot(un);
-                if (lane == 0) wtot[wv] = __popcll(unmask);
-                if (tid == 0) {
-                    cc[S_NCAND] = 0;
-                    cc[S_NKEEP] = 0;
-                }
-                __syncthreads();
-                int before = total;
-                for (int x = 0; x < T / RA_WAVE; ++x) {
-                    const int c = wtot[x];
-                    if (x < wv) before += c;
-                    total += c;
-                }
-                const int rank = before + __popcll(unmask & ((1ull << lane) - 1ull));
-                if (e <= bn) urank[e] = (uint16_t)rank;
-                if (un && rank < expand) {
-                    picks[rank] = key_id(mykey);
-                    cur[e] = mykey & ~1ull;
-                }
-                __syncthreads();
-            }
-            np = total < expand ? total : expand;
-            if (np == 0) break;
-            pk0 = picks[xr0];
-            pk1 = picks[xr1];
         } else {
-            // the merge left the picks in place and counted the unexpanded entries
+            // the last merge (or the set-up) left the picks in place and counted the unexpanded entries
             pk0 = picks[xr0];            // (past the last pick: some earlier one or anything, not used)
             pk1 = picks[xr1];
             const int total = __builtin_amdgcn_readfirstlane(cc[S_NUNEXP]);
             np = total < expand ? total : expand;
             if (__builtin_expect(np == 0, 0)) break;
             if (tid == 0) urank[bn] = (uint16_t)total;
+            unexpanded = total - np;
         }
         SR_TICK(0);
         if (first) {
@@ -1170,12 +1138,10 @@ __device__ __forceinline__ int run_search(
         }
         int nk = __builtin_amdgcn_readfirstlane(cc[S_NKEEP]);
         SR_TICK(2);
-        if (__builtin_expect(nk == 0, 0)) {               // uniform: nothing enters the beam
-            // (with workers all of this step's counters are read behind one barrier: before the next step clears them)
-            if constexpr (Hook::kShareSteps) __syncthreads();
-            picked = false;
-            continue;
-        }
+        // (uniform) Nothing enters the beam, and nothing is left to expand. (Of a step that keeps nothing, but has something
+        // left, the merge of few candidates finds the next picks: a pass of its own over the beam took 1400 ticks where this
+        // takes 700, and ended every walk. One node per step over 64K keys, ef 256: 380 -> 330 us.)
+        if (nk == 0 && unexpanded == 0) break;
         // ---- pre-filter. At most ef of the kept candidates can enter the beam, and the merge below
         //      ranks them against each other at a cost quadratic in their number. A step that keeps
         //      many more than ef (a seed set scored at once) first drops those that cannot be among
@@ -1589,7 +1555,6 @@ __device__ __forceinline__ int run_search(
         u64* t = cur; cur = nxt; nxt = t;
         uint16_t* tu = urank; urank = urank_nxt; urank_nxt = tu;
         int* tc = cc; cc = cc_nxt; cc_nxt = tc;
-        picked = true;
         first = false;
     }
 
@@ -1597,82 +1562,52 @@ __device__ __forceinline__ int run_search(
         post(0, 0ull);
         if (tid == 0) xwg_store(hook.area + SR_MSG_LAST, (u64)(last_message + (uint32_t)n_posted));
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): no touch of this wavefront still has to land in LDS
     if constexpr (Hook::kShareSteps)
         if (ctr[C_MISSED]) {                 // (uniform: written before the last barrier)
             if (tid == 0) hook.steps_missed();
             __syncthreads();
             return -1;
         }
-    // ---- result: best-first beam entries outside the static set W = [0,s) u [N-w,N). A short list is the
-    //      first wavefront's alone (the others wait at the closing barrier); of a long one (a wavefront
-    //      would be 32 rounds over 2048 entries) every wavefront takes rounds, T entries at a time.
-    if (topk <= 256) {
-    if (tid < RA_WAVE) {
-        int32_t* out = ids + (size_t)head * topk;
-        int cnt = 0;
-        // (a row of ids has topk cells; this head returns at most `take` <= topk of them)
-        for (int base = 0; base < bn && cnt < take; base += RA_WAVE) {
-            const int i = base + tid;
-            const int id = i < bn ? key_id(cur[i]) : -1;
-            const bool ok = i < bn && id >= s && id < N - w;
-            const u64 mask = __ballot(ok);
-            const int pos = cnt + __popcll(mask & ((1ull << tid) - 1ull));
-            if (ok && pos < take) {
-                out[pos] = id;
-                if (lds_ids) lds_ids[pos] = id;
-            }
-            cnt += __popcll(mask);
+    // ---- result: best-first beam entries outside the static set W = [0,s) u [N-w,N), T entries at a time. (A row of ids has
+    //      topk cells; this head returns at most `take` <= topk of them. 100 ids of 256 entries: 900 ticks, 1300 by the first
+    //      wavefront alone.)
+    int32_t* out = ids + (size_t)head * topk;
+    const uint32_t eligible = (uint32_t)max((int)N - w - s, 0);
+    int found = 0;
+    for (int base = 0; base < bn && found < take; base += T) {          // (uniform)
+        const int i = base + tid;
+        const int at = i < bn ? key_id(cur[min(i, ef - 1)]) - s : -1;
+        const bool ok = (uint32_t)at < eligible;
+        const u64 mask = __builtin_amdgcn_ballot_w64(ok);
+        if (base) __syncthreads();                                     // (wtot read)
+        wtot[wv] = __popcll(mask);                                     // (the same from every lane)
+        __syncthreads();
+        const int upto = wave_incl_scan(lane < T / RA_WAVE ? wtot[lane] : 0);
+        const int before = __builtin_amdgcn_readfirstlane(wv) ? __builtin_amdgcn_readlane(upto, __builtin_amdgcn_readfirstlane(wv) - 1) : 0;
+        const int pos = ok ? found + before + __popcll(mask & ((1ull << lane) - 1ull)) : take;
+        if (pos < take) {
+            out[pos] = at + s;
+            if (lds_ids) lds_ids[pos] = at + s;
         }
-        if (cnt > take) cnt = take;
-        for (int i = cnt + tid; i < topk; i += RA_WAVE) {
-            out[i] = -1;
-            if (lds_ids) lds_ids[i] = -1;
-        }
-        if (tid == 0) ctr[C_BIN] = cnt;
+        found += __builtin_amdgcn_readlane(upto, T / RA_WAVE - 1);
     }
-    } else {
-        int32_t* out = ids + (size_t)head * topk;
-        int cnt = 0;
-        for (int base = 0; base < bn && cnt < take; base += T) {        // (uniform)
-            const int i = base + tid;
-            const int id = i < bn ? key_id(cur[i]) : -1;
-            const bool ok = i < bn && id >= s && id < N - w;
-            const u64 mask = __ballot(ok);
-            if (lane == 0) wtot[wv] = __popcll(mask);
-            __syncthreads();
-            int pos = cnt;
-            for (int x = 0; x < T / RA_WAVE; ++x) {
-                const int c = wtot[x];
-                if (x < wv) pos += c;
-                cnt += c;
-            }
-            pos += __popcll(mask & ((1ull << lane) - 1ull));
-            if (ok && pos < take) {
-                out[pos] = id;
-                if (lds_ids) lds_ids[pos] = id;
-            }
-            __syncthreads();
-        }
-        if (cnt > take) cnt = take;
-        for (int i = cnt + tid; i < topk; i += T) {
-            out[i] = -1;
-            if (lds_ids) lds_ids[i] = -1;
-        }
-        if (tid == 0) ctr[C_BIN] = cnt;
+    if (found > take) found = take;
+    for (int i = found + tid; i < topk; i += T) {
+        out[i] = -1;
+        if (lds_ids) lds_ids[i] = -1;
     }
     if (stats && tid == 0) {
         ra_stats st;
         st.n_visited = n_visited;
         st.n_expanded = n_expanded;
         st.n_iters = n_iters;
-        st.n_returned = ctr[C_BIN];
+        st.n_returned = found;
         stats[head] = st;
     }
     __syncthreads();
     SR_TICK(6);
     SR_TICK_FLUSH;
-    return ctr[C_BIN];
+    return found;
 }
 
 
