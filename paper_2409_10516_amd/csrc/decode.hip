@@ -328,7 +328,7 @@ struct SharedWalk {
 // workgroups are dealt round-robin): the workers of a head read the same adjacency rows, and a hand-over inside an XCD is a
 // quarter shorter. The heads come first, then the workers; helpers have the highest ids.
 template <int DT, int KT, bool GBITS, int T, bool BUDGETS, typename Walk>
-__global__ __launch_bounds__(T) void decode_kernel(
+__global__ __launch_bounds__(T, SR_WAVES(KT, T)) void decode_kernel(
     const void* __restrict__ q, const int32_t* __restrict__ adj, const int32_t* __restrict__ entry,
     const void* __restrict__ K, const void* __restrict__ V, int n_q, int n_kv, int64_t Ng, int64_t N,
     int64_t kv_stride, int64_t wstart, int deg, int s, int topk, int ef, int expand,

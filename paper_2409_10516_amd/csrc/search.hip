@@ -2,7 +2,7 @@
 #include "search_dev.h"
 
 template <int DT, int KT, bool GBITS, int T>
-__global__ __launch_bounds__(T) void search_kernel(
+__global__ __launch_bounds__(T, SR_WAVES(KT, T)) void search_kernel(
     const void* __restrict__ q, const int32_t* __restrict__ adj, const int32_t* __restrict__ entry,
     const void* __restrict__ K, int n_q, int n_kv, int64_t N, int deg, int s, int w, int topk,
     int ef, int expand, uint32_t* __restrict__ gbits, int32_t* __restrict__ ids,
