@@ -215,16 +215,17 @@ extern "C" ra_status ra_index_configure(ra_index* ix, int what, int64_t value) {
                 return RA_OK;
             }
             const size_t graphs = (size_t)ix->n_seq * ix->n_q;
-            if (n + 2 > ix->seed_cap) {
+            const int row = ra_seed_row_words(n, ix->deg);
+            if (row > ix->seed_cap) {
                 if (ix->seeds) RA_HIP(hipFree(ix->seeds));
                 ix->seeds = nullptr;
                 ix->seed_cap = 0;
                 ix->n_seeds = 0;
-                RA_HIP(hipMalloc((void**)&ix->seeds, graphs * (size_t)(n + 2) * sizeof(int32_t)));
-                ix->seed_cap = n + 2;
+                RA_HIP(hipMalloc((void**)&ix->seeds, graphs * (size_t)row * sizeof(int32_t)));
+                ix->seed_cap = row;
                 if (ix->seedx) RA_HIP(hipFree(ix->seedx));
                 ix->seedx = nullptr;
-                ix->seedx_bytes = RA_SEEDX_KEYS_OFF + graphs * (size_t)(n + 2) * sizeof(uint64_t);
+                ix->seedx_bytes = RA_SEEDX_KEYS_OFF + graphs * (size_t)n * sizeof(uint64_t);
                 RA_HIP(hipMalloc((void**)&ix->seedx, ix->seedx_bytes));
                 RA_HIP(hipMemset(ix->seedx, 0, ix->seedx_bytes));
             }

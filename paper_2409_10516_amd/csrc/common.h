@@ -72,11 +72,11 @@ struct ra_index {
     int coop_mode;      // RA_HELPERS_*
     int coop_spin;      // polls of a record's words before a head gives up on its helper
     int coop_silent;    // test-only (RA_TEST_HELPERS_SILENT): helpers are launched but write nothing
-    // seed sets (RA_CFG_SEEDS): [n_seq*n_q][seed_cap] in the layout of the root sets, or null
+    // seed sets (RA_CFG_SEEDS): [n_seq*n_q][seed_cap] in the layout of the root sets and with masks (search_dev.h), or null
     int32_t* seeds;
     int n_seeds, seed_cap;
     // seed hand-over area of the fused decode kernel (allocated with the seed sets): one "shares
-    // off" word, then from byte RA_SEEDX_KEYS_OFF seed_cap 64-bit keys per head, zero between launches
+    // off" word, then from byte RA_SEEDX_KEYS_OFF 64-bit keys per head, as many as a set has places, zero between launches
     uint32_t* seedx;
     size_t seedx_bytes;
     int seed_parts;     // shares a head's start set is scored in by workgroups of their own (0: by the head)
@@ -121,7 +121,8 @@ ra_status ra_launch_quantize(const void* K, ra_dtype dt, int n_groups, int64_t N
                              int8_t* K8, float* scale);
 ra_status ra_launch_roots(const int32_t* adj, const int32_t* entry, int heads, int64_t N, int deg,
                           int32_t* roots, int cap, hipStream_t st);
-// seed sets: per head [0] the number of ids, [1] 0, then the ids (cap >= 2 + n_seeds ints per head)
+// seed sets: per head [0] the number of ids, [1] 0, then the ids and their masks (cap = ra_seed_row_words of n_seeds or more)
+int ra_seed_row_words(int n_seeds, int deg);
 ra_status ra_launch_seeds(const int32_t* adj, const int32_t* entry, int heads, int64_t N, int deg,
                           int n_seeds, int32_t* seeds, int cap, hipStream_t st);
 size_t ra_search_lds_bytes(int64_t N, int deg, int ef, int expand, bool global_bitset);

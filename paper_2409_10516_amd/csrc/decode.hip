@@ -400,7 +400,7 @@ __global__ __launch_bounds__(T, SR_WAVES(KT, T)) void decode_kernel(
             const int i = (int)blockIdx.x - n_helpers;
             const int part = i / n_heads, hd = xcd_aware_head(i % n_heads, n_heads, G);
             score_seed_share<DT, KT, T>(hd, part, seed_parts, q, Ksearch, n_q, n_kv, kv_stride, roots, root_cap,
-                                        root_cap - 2, expand * deg, kscale, seed_keys_all + (size_t)hd * seed_stride);
+                                        seed_stride, expand * deg, kscale, seed_keys_all + (size_t)hd * seed_stride);
             return;
         }
         head = xcd_aware_head((int)blockIdx.x - n_helpers - n_heads * seed_parts, n_heads, G);
@@ -678,7 +678,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
         if (parts > RA_SEED_PARTS_MAX) parts = RA_SEED_PARTS_MAX;
         if (parts < 2) parts = 0;
     }
-    const int seed_stride = root_cap;
+    const int seed_stride = seed_places(root_cap, deg);
     // Steps shared out (serve_walk): walks with the visited set in device memory, where there are compute units for 8 workers each
     // and steps are wide, which takes a beam of some times `expand` entries to pick from. us per layer without -> with, cells of a
     // step / beam: 4 heads of the mixture law, 1M keys, 3072 / 256 to 1024 134 -> 88, 209 -> 155, 424 -> 314; 1536 / 512 210 -> 182; 2M

@@ -22,8 +22,9 @@ __global__ __launch_bounds__(T, SR_WAVES(KT, T)) void search_kernel(
 // place is kept; prefix sums over the kept ones give the order.
 #define RT_THREADS 1024
 #define RT_SLOTS 8192             // at most RA_MAX_DEG + 1 + RA_MAX_DEG^2 = 4161 ids
+__device__ __forceinline__ uint32_t rt_hash(int id) { return ((uint32_t)id * 2654435761u) >> 19; }
 __device__ __forceinline__ int rt_slot(int* ids, int id) {
-    uint32_t h = ((uint32_t)id * 2654435761u) >> 19;
+    uint32_t h = rt_hash(id);
     while (true) {                                       // (the table is never more than half full)
         const int seen = atomicCAS(&ids[h], -1, id);
         if (seen == -1 || seen == id) return (int)h;
@@ -116,7 +117,8 @@ ra_status ra_launch_roots(const int32_t* adj, const int32_t* entry, int heads, i
 // every adjacency row span from the entry point (position p has its children at 2p + 1 and 2p + 2;
 // for a projected graph this is the head of the popularity order). Positions without a node and
 // nodes already listed at an earlier position are dropped, the order kept. Layout of a root set
-// with [1] = 0: no id enters the beam as expanded. One workgroup per head; a set-up step.
+// with [1] = 0: no id enters the beam as expanded. Behind the ids their masks (seed_mask_words). One workgroup per head; a set-up
+// step.
 #define SD_THREADS 1024
 __global__ __launch_bounds__(SD_THREADS) void seeds_kernel(const int32_t* __restrict__ adj,
                                                            const int32_t* __restrict__ entry, int64_t N,
@@ -167,7 +169,11 @@ __global__ __launch_bounds__(SD_THREADS) void seeds_kernel(const int32_t* __rest
             if (x < wv) before += wsum[x];
             total += wsum[x];
         }
-        if (k) out[2 + before + __popcll(m & ((1ull << lane) - 1ull))] = pos[p];
+        if (k) {
+            const int at = before + __popcll(m & ((1ull << lane) - 1ull));
+            out[2 + at] = pos[p];
+            tab_at[at] = pos[p];                             // (not read any more otherwise)
+        }
         base = total;
         __syncthreads();
     }
@@ -175,11 +181,34 @@ __global__ __launch_bounds__(SD_THREADS) void seeds_kernel(const int32_t* __rest
         out[0] = base;
         out[1] = 0;
     }
+    // the masks: a wavefront per row, eight rows on their way
+    int32_t* masks = out + 2 + seed_places(cap, deg);
+    constexpr int W = SD_THREADS / RA_WAVE, ROWS = 8;
+    const int lane = tid & (RA_WAVE - 1), wv = tid / RA_WAVE;
+    for (int c0 = wv; c0 < base; c0 += W * ROWS) {
+        int nb[ROWS];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u)
+            nb[u] = lane < deg ? adj_h[(size_t)tab_at[min(c0 + u * W, base - 1)] * deg + lane] : -1;
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            bool fresh = nb[u] >= 0 && nb[u] < N;
+            for (uint32_t h = rt_hash(nb[u]); fresh && tab_id[h] != -1; h = (h + 1u) & (RT_SLOTS - 1)) fresh = tab_id[h] != nb[u];
+            const unsigned long long m = __ballot(fresh);
+            const int c = c0 + u * W;
+            if (c < base) {
+                if (deg <= 32) { if (lane == 0) masks[c] = (int)(uint32_t)m; }
+                else if (lane < 2) masks[2 * c + lane] = (int)(uint32_t)(m >> (32 * lane));
+            }
+        }
+    }
 }
+
+int ra_seed_row_words(int n_seeds, int deg) { return seed_row_words(n_seeds, deg); }
 
 ra_status ra_launch_seeds(const int32_t* adj, const int32_t* entry, int heads, int64_t N, int deg,
                           int n_seeds, int32_t* seeds, int cap, hipStream_t st) {
-    if (n_seeds < 1 || n_seeds > RA_MAX_SEEDS || cap < 2 + n_seeds) RA_FAIL(RA_EINVAL, "seed set buffer too small");
+    if (n_seeds < 1 || n_seeds > RA_MAX_SEEDS || seed_places(cap, deg) < n_seeds) RA_FAIL(RA_EINVAL, "seed set buffer too small");
     hipLaunchKernelGGL(seeds_kernel, dim3(heads), dim3(SD_THREADS), 0, st, adj, entry, N, deg, n_seeds, seeds, cap);
     RA_HIP(hipGetLastError());
     return RA_OK;

@@ -36,7 +36,7 @@
 
 #define SR_THREADS 1024          // largest workgroup; the kernels are also built for 512 and 256 threads
 // Wavefronts per SIMD that the kernels leave registers for: two workgroups of 512 threads, or four of 256, share a compute unit, in
-// float32 three of 256. (Where searches outnumber the compute units, that is what counts: with 130 registers per lane in place
+// float32 three of 256. (Where searches outnumber the compute units, that is what counts: with 136 registers per lane in place
 // of 128, 448 searches of 33K keys, ef 512, took 206 us instead of 134.)
 #define SR_WAVES(KT, T) ((KT) != RA_F32 || (T) == 1024 ? 4 : 3)
 #define SR_LDS_LIMIT RA_LDS_LIMIT
@@ -58,6 +58,8 @@ enum { S_NCAND = 0, S_NKEEP = 1, S_NUNEXP = 2 };      // of the three words at C
 #define SR_NARROW 16              // a merge of up to this many candidates takes one phase (half as many with 1024 threads)
 #define SR_DIRECT 64              // a merge of more candidates than this goes through buckets
 #define SR_MERGE_REGS 2           // ... when a thread can hold its share of them
+#define SR_LIST_AT (T <= 512 ? 768 : T)       // words of cid in front of the new cells of a seed set's first picks
+#define SR_FRESH_CELLS 16         // a pick with more new cells than this has its whole row read, and so have all others
 
 typedef unsigned long long u64;
 
@@ -322,6 +324,12 @@ __device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
     min_max_step<0x142, 0xA>(lo, hi);        // lane 15 of a row into the next one, then lane 31 to the upper half
     min_max_step<0x143, 0xC>(lo, hi);
 }
+
+// A head's row of the seed sets: [0] the number of ids, [1] 0, then places for n ids, then for n masks of 32 or, where the degree is
+// above 32, 64 bits (lower half first): of the cells of the id's adjacency row, those whose neighbour is no member of the set.
+__host__ __device__ static inline int seed_mask_words(int deg) { return deg > 32 ? 2 : 1; }
+__host__ __device__ static inline int seed_row_words(int n, int deg) { return 2 + n * (1 + seed_mask_words(deg)); }
+__host__ __device__ static inline int seed_places(int row_words, int deg) { return (row_words - 2) / (1 + seed_mask_words(deg)); }
 
 static_assert(RA_MAX_EF + RA_MAX_EXPAND * RA_MAX_DEG < 65536, "ranks and merge counts are kept in 16 bits");
 
@@ -721,6 +729,7 @@ __device__ __forceinline__ int run_search(
     int* cc = ctr + C_STEP;
     int* cc_nxt = ctr + C_STEP2;
     bool hist_used = false;
+    bool masked = false;             // cnt holds the masks of the seed set the walk starts from, until its first step behind that
     int* wtot = ctr + C_WTOT;
     // urank[i], i in [0, bn]: unexpanded entries among the first i of the beam, as of the last pick
     // but before its picks were marked expanded (two buffers, swapped with the beam's)
@@ -746,11 +755,20 @@ __device__ __forceinline__ int run_search(
     // top ef of them, the entry point and its neighbours marked expanded. Same beam, same visited
     // set, same counters as the two steps taken one after the other.
     const int32_t* root = roots ? roots + (size_t)head * root_cap : nullptr;
-    int n_root = 0, n_first = 0, my_root = -1;
+    int n_root = 0, n_first = 0;
+    // (of a thread's first ids, and of a seed set their masks, unconditional: same trip as the header)
+    constexpr int AHEAD = 4;
+    int my_root[AHEAD] = {}, my_mask[AHEAD] = {};
+    const int mask_words = seed_mask_words(deg), masks_at = 2 + seed_places(root_cap, deg);
     if (root) {
         n_root = root[0];
         n_first = root[1];
-        my_root = root[2 + (tid < root_cap - 2 ? tid : 0)];      // unconditional: same trip as the header
+        if constexpr (!Hook::kShareSteps)
+#pragma unroll
+            for (int r = 0; r < AHEAD; ++r) {
+                my_root[r] = root[2 + min(tid + r * T, root_cap - 3)];
+                my_mask[r] = root[min(masks_at + (tid + r * T) * mask_words, root_cap - 1)];
+            }
     }
     int n_posted = 0;                // (kShareSteps: claims and scores are the workers', serve_walk)
     uint32_t last_message = 0u;
@@ -775,16 +793,31 @@ __device__ __forceinline__ int run_search(
 #ifdef SR_WAVE_CLOCKS
     if (head == 0 && tid == 0) sr_wave_ticks[1] = wall_clock64();
 #endif
+    // with masks: new cells (pick, cell) of the first picks, up to T of them, and the places in the seed set of the survivors of the
+    // pre-filter, behind what that and a step's claims of that few cells use of cid
+    static_assert(SR_LIST_AT >= 768 && SR_LIST_AT >= T && RA_MAX_EXPAND * 64 <= 65536, "a pick and a cell of its row in 16 bits");
+    uint16_t* fresh_cells = reinterpret_cast<uint16_t*>(cid + SR_LIST_AT);
+    uint16_t* seed_at = fresh_cells + T;
     int bn, n_visited, n_expanded, n_iters;
     bool first = fill;               // the coming step is that doubled first step
     if (Hook::kShareSteps && tid == 0) ctr[C_MISSED] = 0;
     if (fill) {
-        if constexpr (!Hook::kShareSteps)
-            for (int c = tid; c < n_root; c += T) {
-                const int id = c == tid ? my_root : root[2 + c];
+        if constexpr (!Hook::kShareSteps) {
+            masked = seeded && n_root > ef + SR_PREFILTER_SLACK && n_root <= SR_PREFILTER_REGS * T && n_root * mask_words <= maxc &&
+                     maxc >= SR_LIST_AT + (n_root + T + 1) / 2;
+            auto enter = [&](int c, int id, int m) __attribute__((always_inline)) {
                 cid[c] = id;
                 (void)claim_key(bits, id);
-            }
+                if (masked) {
+                    cnt[c] = m;
+                    if (mask_words == 2) cnt[n_root + c] = root[masks_at + 2 * c + 1];
+                }
+            };
+#pragma unroll
+            for (int r = 0; r < AHEAD; ++r)
+                if (tid + r * T < n_root) enter(tid + r * T, my_root[r], my_mask[r]);
+            for (int c = tid + AHEAD * T; c < n_root; c += T) enter(c, root[2 + c], masked ? root[masks_at + c * mask_words] : 0);
+        }
         if (tid == 0) {
             urank[0] = 0;
             cc[S_NCAND] = Hook::kShareSteps ? 0 : n_root;    // (then added up from the workers' answers)
@@ -794,6 +827,7 @@ __device__ __forceinline__ int run_search(
             ctr[C_HI] = 0;
             ctr[C_NSURV] = 0;
             ctr[C_MISSED] = 0;
+            wtot[0] = 0;                     // (new cells of the first picks; the results use it otherwise)
         }
         bn = 0; n_visited = 0; n_expanded = 0; n_iters = 0;
     } else {
@@ -1059,7 +1093,22 @@ __device__ __forceinline__ int run_search(
             };
             // out-of-range cells read a cell of the entry row: loads without a branch around them can all be
             // issued before the first is consumed
-            if (__builtin_expect(cells <= 2 * T, 1)) {
+            // The step behind a seed set: nearly all neighbours of its keys are keys of the set (128K keys, 2048 of them: 19 of
+            // 8192 cells are new), and which are not is known from the graph alone (the masks), so where they are few, only
+            // those are read and claimed.
+            bool few = false;
+            if (__builtin_expect(masked, 0)) {
+                const int n = __builtin_amdgcn_readfirstlane(wtot[0]);
+                few = n <= T;
+                if (tid < n && few) {
+                    const int e = fresh_cells[tid];
+                    claim(adj_h[(size_t)picks[e >> 6] * deg + (e & 63)]);        // (no more than T are new: cid up to the list)
+                }
+                for (int c = tid; c < n_root * mask_words; c += T) cnt[c] = 0;
+                masked = false;
+            }
+            if (few) {
+            } else if (__builtin_expect(cells <= 2 * T, 1)) {
                 const int v0 = adj_h[(size_t)(tid < cells ? pk0 : e0) * deg + xs0];
                 int v1 = -1;
                 if (cells > T) v1 = adj_h[(size_t)(tid + T < cells ? pk1 : e0) * deg + xs1];
@@ -1244,8 +1293,11 @@ __device__ __forceinline__ int run_search(
                 const int nsurv = ctr[C_NSURV];              // >= ef
 #pragma unroll
                 for (int r = 0; r < SR_PREFILTER_REGS; ++r)
-                    if (r * T + tid < nk && bin[r] >= bstar)
-                        ckey[cid[256 + bin[r]] + atomicAdd(&cid[512 + bin[r]], 1)] = mine[r];
+                    if (r * T + tid < nk && bin[r] >= bstar) {
+                        const int at = cid[256 + bin[r]] + atomicAdd(&cid[512 + bin[r]], 1);
+                        ckey[at] = mine[r];
+                        if (masked) seed_at[at] = (uint16_t)(r * T + tid);
+                    }
                 __syncthreads();
                 auto bin_of = [&](u64 k) __attribute__((always_inline)) {
                     const float b = (f32_from_ordered((uint32_t)(k >> 32)) - lo_f) * to_bin;
@@ -1260,7 +1312,17 @@ __device__ __forceinline__ int run_search(
                         if (pos < ef) {
                             if (pos < expand) {              // this step's picks: the first `expand` entries
                                 picks[pos] = key_id(k);
-                                touch_line(adj_h + (size_t)key_id(k) * deg, touch_off);
+                                u64 m = ~0ull;
+                                if (masked) {                // its new cells join the list, if they are few
+                                    const int c = seed_at[p];
+                                    m = (uint32_t)cnt[c] | (deg > 32 ? (u64)(uint32_t)cnt[n_root + c] << 32 : 0ull);
+                                    const int n = __popcll(m);
+                                    int at = n == 0 ? 0 : atomicAdd(wtot, n > SR_FRESH_CELLS ? T + 1 : n);
+                                    if (n <= SR_FRESH_CELLS)
+                                        for (u64 left = m; left && at < T; left &= left - 1ull, ++at)
+                                            fresh_cells[at] = (uint16_t)(pos << 6 | (__ffsll((long long)left) - 1));
+                                }
+                                if (m) touch_line(adj_h + (size_t)key_id(k) * deg, touch_off);
                                 k &= ~1ull;
                             }
                             nxt[pos] = k;

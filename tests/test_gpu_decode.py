@@ -995,3 +995,46 @@ def test_shared_steps_recorded_and_after_a_wait_that_ran_out():
     replayed()
     assert idx.shared_launches == launches + 1 and idx.shared_steps_active and idx.shared_messages > 0
     idx.free()
+
+
+@pytest.mark.parametrize("deg,R,ef,expand,k,heads", [
+    (24, 512, 256, 64, 0, 1), (32, 512, 256, 64, 8, 1), (32, 512, 256, 64, 9, 1), (33, 512, 256, 64, 3, 1),
+    (64, 512, 256, 32, 16, 1), (64, 511, 256, 32, 17, 1), (32, 700, 512, 64, 16, 1), (32, 700, 512, 64, 17, 2),
+    (32, 321, 256, 64, 4, 400), (32, 320, 256, 64, 4, 400), (24, 600, 100, 64, 30, 1)])
+def test_first_step_behind_a_seed_set(deg, R, ef, expand, k, heads):
+    """The step behind a seed set reads and claims only the cells that lead out of the set where these are few (at
+    most one per thread, at most 16 of a pick), else all: k cells of every seed lead out (the most there can be where k
+    exceeds the degree), to keys that several cells name. Integer keys, so ids and counters are the oracle's. Workgroups
+    of 512, 1024 (ef 512) and 256 threads (400 heads), masks of 32 and 64 bits, sets at and below the size that is filtered."""
+    from paper_2409_10516_amd import binding as B
+    rng = np.random.default_rng(deg * 1000 + k)
+    N, k = 1500, min(k, deg - 2)
+    adj = np.full((heads, N, deg), -1, np.int32)
+    t = np.arange(N)
+    for j in (0, 1):                                         # the heap, as far as it stays in the set
+        adj[:, :, j] = np.where(2 * t + 1 + j < R, 2 * t + 1 + j, -1)
+    inside = rng.integers(0, R, size=(heads, N, deg - 2 - k))
+    adj[:, :, 2:deg - k] = np.where(inside == t[None, :, None], -1, inside)
+    out = rng.integers(R, N + 50, size=(heads, N, k))       # (some are no keys)
+    out = np.where(out == t[None, :, None], R, out)
+    adj[:, :, deg - k:] = np.where(out >= N, -1, out)
+    adj[:, R, :] = np.where(adj[:, R, :] == R, -1, adj[:, R, :])
+    cols = 2 + rng.permutation(deg - 2)                      # cells that lead out anywhere in the row
+    adj[:, :, 2:] = adj[:, :, cols]
+    ent = np.zeros(heads, np.int32)
+    K = torch.from_numpy(rng.integers(-4, 5, size=(1, 1, N, 128)).astype(np.float32)).bfloat16()
+    V = torch.from_numpy(rng.standard_normal((1, 1, N, 128)).astype(np.float32)).bfloat16()
+    q = torch.from_numpy(rng.integers(-4, 5, size=(1, heads, 128)).astype(np.float32)).bfloat16()
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.from_numpy(ent), 1, heads, 1)
+    for n in (R, R - 1, R):                                  # (a set in the place of a longer one)
+        idx.configure(B.RA_CFG_SEEDS, n)
+        ids, st = ra.ra_search(q.to(DEV), idx, K.to(DEV), 4, 20, 50, ef, expand)
+        _, _, ids_d, st_d = ra.ra_decode_step(q.to(DEV), idx, K.to(DEV), V.to(DEV), 4, 20, 50, ef, expand)
+        assert torch.equal(ids, ids_d) and torch.equal(st, st_d)
+        for h in sorted({0, heads // 2, heads - 1}):
+            seeds = OS.backbone_seeds(adj[h], 0, n)
+            ref, rst = OS.greedy_search(to_np(q[0, h]), to_np(K[0, 0]), adj[h], 0, ef, 50, expand, seeds=seeds,
+                                        exclude=OA.static_ids(N, 4, 20))
+            assert ids[0, h].tolist() == ref.tolist(), (n, h)
+            assert st[0, h].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]], (n, h)
+    idx.free()
