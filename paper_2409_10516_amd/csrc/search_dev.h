@@ -55,10 +55,11 @@ enum { S_NCAND = 0, S_NKEEP = 1, S_NUNEXP = 2 };      // of the three words at C
 #define SR_TOUCH_BYTES (4 * RA_WAVE) // where touched words land (touch_line)
 #define SR_PREFILTER_SLACK 64     // a step that keeps more than ef + this many candidates drops the hopeless ones first
 #define SR_PREFILTER_REGS 8       // ... when a thread can hold its share of them (nk <= 8 T)
+#define SR_START_REGS 8           // keys of a start set that a thread can hold
 #define SR_NARROW 16              // a merge of up to this many candidates takes one phase (half as many with 1024 threads)
 #define SR_DIRECT 64              // a merge of more candidates than this goes through buckets
 #define SR_MERGE_REGS 2           // ... when a thread can hold its share of them
-#define SR_LIST_AT (T <= 512 ? 768 : T)       // words of cid in front of the new cells of a seed set's first picks
+#define SR_LIST_AT (T <= 512 ? 512 : T)       // words of cid in front of the new cells of a seed set's first picks
 #define SR_FRESH_CELLS 16         // a pick with more new cells than this has its whole row read, and so have all others
 
 typedef unsigned long long u64;
@@ -795,16 +796,16 @@ __device__ __forceinline__ int run_search(
 #endif
     // with masks: new cells (pick, cell) of the first picks, up to T of them, and the places in the seed set of the survivors of the
     // pre-filter, behind what that and a step's claims of that few cells use of cid
-    static_assert(SR_LIST_AT >= 768 && SR_LIST_AT >= T && RA_MAX_EXPAND * 64 <= 65536, "a pick and a cell of its row in 16 bits");
+    static_assert(SR_LIST_AT >= 512 && SR_LIST_AT >= T && RA_MAX_EXPAND * 64 <= 65536, "a pick and a cell of its row in 16 bits");
     uint16_t* fresh_cells = reinterpret_cast<uint16_t*>(cid + SR_LIST_AT);
     uint16_t* seed_at = fresh_cells + T;
+    // whether a start set is ordered through bins (below)
+    auto start_bins = [&]() __attribute__((always_inline)) { return n_root > SR_DIRECT && n_root <= SR_START_REGS * T && maxc >= 512; };
     int bn, n_visited, n_expanded, n_iters;
-    bool first = fill;               // the coming step is that doubled first step
     if (Hook::kShareSteps && tid == 0) ctr[C_MISSED] = 0;
     if (fill) {
         if constexpr (!Hook::kShareSteps) {
-            masked = seeded && n_root > ef + SR_PREFILTER_SLACK && n_root <= SR_PREFILTER_REGS * T && n_root * mask_words <= maxc &&
-                     maxc >= SR_LIST_AT + (n_root + T + 1) / 2;
+            masked = seeded && start_bins() && n_root * mask_words <= maxc && maxc >= SR_LIST_AT + (n_root + T + 1) / 2;
             auto enter = [&](int c, int id, int m) __attribute__((always_inline)) {
                 cid[c] = id;
                 (void)claim_key(bits, id);
@@ -820,16 +821,14 @@ __device__ __forceinline__ int run_search(
         }
         if (tid == 0) {
             urank[0] = 0;
-            cc[S_NCAND] = Hook::kShareSteps ? 0 : n_root;    // (then added up from the workers' answers)
-            cc[S_NKEEP] = Hook::kShareSteps ? 0 : n_root;    // every key of a start set is kept (scored below)
-            cc[S_NUNEXP] = 0;
+            for (int i = 0; i < 3; ++i) cc[i] = cc_nxt[i] = 0;
             ctr[C_LO] = -1;                  // as unsigned: the largest value; see the pre-filter below
             ctr[C_HI] = 0;
-            ctr[C_NSURV] = 0;
             ctr[C_MISSED] = 0;
             wtot[0] = 0;                     // (new cells of the first picks; the results use it otherwise)
         }
-        bn = 0; n_visited = 0; n_expanded = 0; n_iters = 0;
+        // (of a root set the entry point's step and its neighbours' step; of a seed set none)
+        bn = 0; n_visited = n_root; n_expanded = n_first; n_iters = seeded ? 0 : 2;
     } else {
         if (grp == 0) {
             const RowBits<KT> r = load_key<KT>(Kh, e0, lane16);
@@ -859,7 +858,6 @@ __device__ __forceinline__ int run_search(
     const int xr1 = min((int)__umulhi((uint32_t)(tid + T) + 1u, deg_f), expand - 1);
     const int xs0 = min(tid - xr0 * deg, deg - 1), xs1 = min(tid + T - xr1 * deg, deg - 1);
     const int gi0 = min(grp, maxc - 1), gi1 = min(grp + T / 16, maxc - 1);
-    int pk0 = e0, pk1 = e0;          // the picks of those cells
     // Adjacency rows likely to be expanded soon are touched ahead of time (one word of the row's
     // first line), so that the row is in this XCD's L2 when its step reads it: the rows of the
     // candidates a step keeps, touched while they are merged, and the rows of the beam entries that
@@ -1025,42 +1023,192 @@ __device__ __forceinline__ int run_search(
 #endif
     SR_TICK(5);
 
+    // An element of a new beam of bn_new at its place: key, position, unexpanded elements above it. What it does not have to
+    // store goes to the piece that touched words land in: an address chosen by a lane costs it 4 ticks, a branch 30
+    // to 60. (An element past position ef has at least as many unexpanded ones above it as there are picks.) Of a
+    // wavefront's 64 beam entries there is seldom one that is picked, and one is the last: branches for all lanes.
+    auto place_in = [&](int bn_new, u64 k, int pos, int ur, auto beam) __attribute__((always_inline)) {
+        constexpr bool BEAM = decltype(beam)::value != 0;
+        const int un = (int)(uint32_t)k & 1;
+        const bool pick = (uint32_t)(ur | (un - 1)) < (uint32_t)expand, last = pos == bn_new - 1;
+        if (!BEAM || __builtin_amdgcn_ballot_w64(pick)) *(pick ? picks + ur : reinterpret_cast<int*>(lds_raw)) = key_id(k);
+        k ^= pick ? 1ull : 0ull;
+        *(pos < ef ? nxt + pos : reinterpret_cast<u64*>(lds_raw)) = k;
+        *(pos < ef ? urank_nxt + pos : reinterpret_cast<uint16_t*>(lds_raw)) = (uint16_t)ur;
+        // (the last one has counted all)
+        if (!BEAM || __builtin_amdgcn_ballot_w64(last)) *(last ? cc_nxt + S_NUNEXP : reinterpret_cast<int*>(lds_raw)) = ur + un;
+    };
+    auto touch_row = [&](int id) __attribute__((always_inline)) {
+        touch_line(reinterpret_cast<const char*>(adj_h) + (u64)(uint32_t)id * (uint32_t)(deg * 4), touch_off);
+    };
+    // of 16 candidates those above k, and (ROOTS: of a start set) in the high half the expanded ones of them
+    auto count16 = [&](int at, u64 k, auto roots_c) __attribute__((always_inline)) {
+        u64 v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = ckey[at + u];
+        int n = 0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int up = v[u] > k ? 1 : 0;
+            n += up;
+            if constexpr (decltype(roots_c)::value != 0) n += (up & ~(int)(uint32_t)v[u]) << 16;
+        }
+        return n;
+    };
+    auto swap_beams = [&]() __attribute__((always_inline)) {
+        u64* t = cur; cur = nxt; nxt = t;
+        uint16_t* tu = urank; urank = urank_nxt; urank_nxt = tu;
+        int* tc = cc; cc = cc_nxt; cc_nxt = tc;
+    };
+
+    // ---- The first beam: the best ef of a start set, ahead of the loop, so that the loop has nothing of it (a test per phase and the
+    //      registers of this part cost walks without seed sets up to 5 %). The scores are cut into 256 equal-width bins between the
+    //      smallest and the largest; a key's place is the number of keys in higher bins plus the number of larger ones in its own,
+    //      which are few and stored side by side. Of a bin the number of keys and, in the high half, of those that enter as
+    //      expanded; a key's number in its bin is what its count returned, and every wavefront adds the bins up for itself, to the
+    //      same words, so there are three barriers. Bins below the highest one that holds the ef-th key are left out. The claimed ids
+    //      (cid) are dead by now: the bins are there, their sums behind. Counting (few keys, little LDS) is quadratic.
+    //      (Inside the loop, with five barriers, and for sets to be filtered only, seed sets and float32; calls in turn, us: four layers of 128K
+    //      81.8 -> 78.5, 16 sequences of 32K 41.2 -> 39.7, one float32 head 31.8 -> 29.9, 64K keys in 8 bits 20.0 -> 18.4, one
+    //      node per step 329 -> 322.)
+    if (fill) {
+        __syncthreads();                     // keys, their extremes
+        const bool bins = start_bins();
+        const int bn_new = n_root < ef ? n_root : ef;
+        bool missed = false;
+        if constexpr (Hook::kShareSteps) missed = ctr[C_MISSED] != 0;        // (the loop ends at once then: no picks)
+        if (bins && !missed) {
+            if (tid < 256) cid[tid] = 0;
+            __syncthreads();
+            const float lo_f = f32_from_ordered((uint32_t)ctr[C_LO]);
+            const float width = f32_from_ordered((uint32_t)ctr[C_HI]) - lo_f;
+            // bin = (score - lowest) * 255 / (highest - lowest), truncated: every operation is
+            // monotone in the score, so a larger score never lands in a lower bin. Non-finite
+            // scores (from non-finite inputs) leave the factor at zero: one bin, everything survives.
+            const float to_bin = width > 0.f && width < INFINITY ? 255.0f / width : 0.f;
+            auto bin_of = [&](u64 k) __attribute__((always_inline)) {
+                const float b = (f32_from_ordered((uint32_t)(k >> 32)) - lo_f) * to_bin;
+                return b >= 255.f ? 255 : b > 0.f ? (int)b : 0;
+            };
+            u64 mine[SR_START_REGS];
+            int bin[SR_START_REGS];          // a key's, and from bit 8 its number in it
+#pragma unroll
+            for (int r = 0; r < SR_START_REGS; ++r)
+                if (r * T < n_root) mine[r] = ckey[min(r * T + tid, n_root - 1)];
+#pragma unroll
+            for (int r = 0; r < SR_START_REGS; ++r) {
+                if (r * T >= n_root) break;
+                bin[r] = bin_of(mine[r]);
+                if (r * T + tid < n_root)
+                    bin[r] |= (atomicAdd(&cid[bin[r]], 1 + ((int)(~(uint32_t)mine[r] & 1u) << 16)) & 0xffff) << 8;
+            }
+            __syncthreads();
+            // lane l owns bins 4l .. 4l + 3; keys in the bins from b up = total - (those below b), in both halves
+            const int b0 = cid[4 * lane], b1 = cid[4 * lane + 1], b2 = cid[4 * lane + 2], b3 = cid[4 * lane + 3];
+            const int incl = wave_incl_scan(b0 + b1 + b2 + b3);
+            const int above3 = __builtin_amdgcn_readlane(incl, RA_WAVE - 1) - incl;
+            const int above2 = above3 + b3, above1 = above2 + b2, above0 = above1 + b1;
+            cid[256 + 4 * lane + 3] = above3;
+            cid[256 + 4 * lane + 2] = above2;
+            cid[256 + 4 * lane + 1] = above1;
+            cid[256 + 4 * lane] = above0;
+            // the highest bin such that it and those above hold ef keys (all, where there are fewer)
+            const int from3 = above2 & 0xffff, from2 = above1 & 0xffff, from1 = above0 & 0xffff, from0 = (above0 + b0) & 0xffff;
+            const int best = from3 >= bn_new ? 3 : from2 >= bn_new ? 2 : from1 >= bn_new ? 1 : from0 >= bn_new ? 0 : -1;
+            const int from_best = best == 3 ? from3 : best == 2 ? from2 : best == 1 ? from1 : from0;
+            const int top = 63 - __clzll(__builtin_amdgcn_ballot_w64(best >= 0));
+            const int bstar = 4 * top + __builtin_amdgcn_readlane(best, top), nsurv = __builtin_amdgcn_readlane(from_best, top);
+#pragma unroll
+            for (int r = 0; r < SR_START_REGS; ++r) {
+                if (r * T >= n_root) break;
+                if (r * T + tid < n_root && (bin[r] & 255) >= bstar) {
+                    const int at = (cid[256 + (bin[r] & 255)] & 0xffff) + (bin[r] >> 8);
+                    ckey[at] = mine[r];
+                    if (masked) seed_at[at] = (uint16_t)(r * T + tid);
+                }
+            }
+            __syncthreads();
+            for (int p = tid; p < nsurv; p += T) {
+                const u64 k = ckey[p];
+                const int kb = bin_of(k), above = cid[256 + kb], bs = above & 0xffff, n = cid[kb] & 0xffff;
+                int pos = bs, ur = bs - (above >> 16), j0 = 0;
+                // (past the bucket's end its last key again, taken off below)
+                do {
+                    u64 other[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) other[i] = ckey[bs + min(j0 + i, n - 1)];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int up = other[i] > k ? 1 : 0;
+                        pos += up;
+                        ur += up & (int)other[i];            // (the low bit: not expanded)
+                    }
+                    j0 += 4;
+                } while (__builtin_amdgcn_ballot_w64(j0 < n));
+                const u64 end = ckey[bs + n - 1];
+                const int twice = end > k ? j0 - n : 0;
+                pos -= twice;
+                ur -= (int)end & 1 ? twice : 0;
+                u64 m = ~0ull;
+                if (masked && pos < min(ef, expand)) {       // a pick's new cells join the list, if they are few
+                    const int c = seed_at[p];
+                    m = (uint32_t)cnt[c] | (deg > 32 ? (u64)(uint32_t)cnt[n_root + c] << 32 : 0ull);
+                    const int cells = __popcll(m);
+                    int at = cells == 0 ? 0 : atomicAdd(wtot, cells > SR_FRESH_CELLS ? T + 1 : cells);
+                    if (cells <= SR_FRESH_CELLS)
+                        for (u64 left = m; left && at < T; left &= left - 1ull, ++at)
+                            fresh_cells[at] = (uint16_t)(pos << 6 | (__ffsll((long long)left) - 1));
+                }
+                if ((k & 1ull) && ur < expand && m) touch_row(key_id(k));
+                place_in(bn_new, k, pos, ur, sr_int<0>{});
+            }
+        } else if (!missed) {
+            ckey[n_root + lane16] = 0ull;    // zeroes behind the candidates, written by each wavefront that reads them
+            for (int c = T - 1 - tid; c < n_root; c += T) touch_row(key_id(ckey[c]));
+            const int chunks = (n_root + 15) >> 4;
+            int t = __builtin_amdgcn_readfirstlane(wv);
+            for (int g0 = 0; g0 < n_root; g0 += RA_WAVE, t -= chunks)
+                for (; t < chunks; t += T / RA_WAVE) {
+                    const int c = min(g0 + lane, n_root - 1);
+                    const int n = count16(t * 16, ckey[c], sr_int<1>{});
+                    if (g0 + lane < n_root && n) atomicAdd(&cnt[c], n);
+                }
+            __syncthreads();
+            for (int c = T - 1 - tid; c < n_root; c += T) {
+                const int both = cnt[c], n = both & 0xffff;
+                cnt[c] = 0;
+                place_in(bn_new, ckey[c], n, n - (both >> 16), sr_int<0>{});
+            }
+        }
+        __syncthreads();
+        if (!missed) {
+            bn = bn_new;
+            swap_beams();
+        }
+    }
+    SR_TICK(14);
+
     for (;;) {
         SR_TICK_ITER(n_iters);
-        int np;
-        int unexpanded = 0;          // entries of the beam left unexpanded by this step
-        if (__builtin_expect(first, 0)) {
-            np = 0;                  // nothing of the (empty) beam is expanded: see the set-up
-        } else {
-            // the last merge (or the set-up) left the picks in place and counted the unexpanded entries
-            pk0 = picks[xr0];            // (past the last pick: some earlier one or anything, not used)
-            pk1 = picks[xr1];
-            const int total = __builtin_amdgcn_readfirstlane(cc[S_NUNEXP]);
-            np = total < expand ? total : expand;
-            if (__builtin_expect(np == 0, 0)) break;
-            if (tid == 0) urank[bn] = (uint16_t)total;
-            unexpanded = total - np;
-        }
+        // the last merge (or the set-up) left the picks in place and counted the unexpanded entries
+        const int pk0 = picks[xr0];          // the picks of a thread's first two cells (past the last pick: some earlier one or
+        const int pk1 = picks[xr1];          // anything, not used)
+        const int total = __builtin_amdgcn_readfirstlane(cc[S_NUNEXP]);
+        const int np = total < expand ? total : expand;
+        if (__builtin_expect(np == 0, 0)) break;
+        if (tid == 0) urank[bn] = (uint16_t)total;
+        const int unexpanded = total - np;   // entries of the beam left unexpanded by this step
         SR_TICK(0);
-        if (first) {
-            if (!seeded) {
-                n_iters = 2;         // the entry point's step and its neighbours' step
-                n_expanded = n_first;
-            }
-        } else {
-            ++n_iters;
-            n_expanded += np;
-        }
+        ++n_iters;
+        n_expanded += np;
 
         if (tid == 0) {                      // (read for the last time before the barrier that ended the last merge)
             cc_nxt[S_NCAND] = 0;
             cc_nxt[S_NKEEP] = 0;
             cc_nxt[S_NUNEXP] = 0;
-            if (!first) {                    // (a start set's extremes were collected while it was scored)
-                ctr[C_LO] = -1;
-                ctr[C_HI] = 0;
-                ctr[C_NSURV] = 0;
-            }
+            ctr[C_LO] = -1;
+            ctr[C_HI] = 0;
+            ctr[C_NSURV] = 0;
         }
         if (__builtin_expect(hist_used, 0)) {
             for (int i = tid; i < nhist; i += T) hist[i] = 0;
@@ -1070,19 +1218,17 @@ __device__ __forceinline__ int run_search(
         }
         if constexpr (Hook::kShareSteps) {
             // ---- the workers claim and score; their answers are waited for
-            if (!first) {
-                post(np, bn == ef ? (cur[bn - 1] >> 1) : 0ull);
-                uint32_t lo = 0xffffffffu, hi = 0u;
-                collect(lo, hi);
-            }
+            post(np, bn == ef ? (cur[bn - 1] >> 1) : 0ull);
+            uint32_t lo = 0xffffffffu, hi = 0u;
+            collect(lo, hi);
             __syncthreads();
             if (ctr[C_MISSED]) break;
             n_visited += __builtin_amdgcn_readfirstlane(cc[S_NCAND]);
             SR_TICK(1);
         } else {
         // ---- read the picked adjacency rows (all loads issued before any is consumed),
-        //      claim unvisited neighbours (the doubled first step has its candidates already)
-        if (!first) {
+        //      claim unvisited neighbours
+        {
             const int cells = np * deg;
             auto claim = [&](int nb) __attribute__((always_inline)) {
                 if (nb >= 0 && nb < N) {
@@ -1173,7 +1319,7 @@ __device__ __forceinline__ int run_search(
             const int cw = c0 + (lane16 & (R - 1)) * PER + grp;  // the candidate this lane will keep or drop
             gather_ids(rows_c, cidv, cw, cid[cw < nc ? cw : 0]);
         };
-        if (!first) {                                        // (a start set is scored already)
+        {
             // as few trips to memory as there can be: the last one takes the number of rows in flight that
             // covers what is left (a trip is 1300 ticks or more, a re-read of the entry row nothing)
             if (__builtin_expect(nc <= 2 * PER, 1)) {
@@ -1197,30 +1343,13 @@ __device__ __forceinline__ int run_search(
         if (nk == 0 && unexpanded == 0) break;
         // ---- pre-filter. At most ef of the kept candidates can enter the beam, and the merge below
         //      ranks them against each other at a cost quadratic in their number. A step that keeps
-        //      many more than ef (a seed set scored at once) first drops those that cannot be among
-        //      its best ef: the scores are cut into 256 equal-width bins between the smallest and
-        //      the largest, a histogram finds the highest bin b such that the bins
-        //      from b up hold at least ef candidates, and only those survive, compacted in place.
+        //      many more than ef first drops those that cannot be among its best ef: a histogram of bins as for a
+        //      start set finds the highest bin b such that the bins from b up hold at least ef candidates, and only those
+        //      survive, compacted in place.
         //      Everything dropped is below at least ef survivors; which survive does not depend on
         //      the order of the candidates. The claimed ids (cid) are dead by now: their first 256
         //      words are the histogram.
-        // A start set (empty beam, every key kept) goes one step further: the same
-        // bins also order the survivors. A survivor's place among the kept keys is the number of
-        // keys in higher bins (a suffix sum over the histogram) plus its rank inside its own bin,
-        // found by comparing it with the few keys that share the bin: the survivors are dealt into
-        // buckets by bin (ckey is free: every thread holds its keys in registers), and each one
-        // then counts the larger keys of its bucket. That replaces the merge below, whose counting
-        // is quadratic in the survivors (about ef of them), for the one step where it is large;
-        // beam, picks and counters come out as the merge would leave them. Of a seed set all entries are unexpanded: the
-        // unexpanded entries above a key are its position. Of a root set those that enter as expanded are counted by bin,
-        // too (ROOT_BINS). One float32 head, a root set of a thousand keys, ef 128, timed in turn with and without: 1.6 to
-        // 2.2 of 43.5 to 46.3 us less (six times, on devices that differ by 5 %), for 4 more bytes of scratch memory per
-        // lane in the kernel of 1024 threads; root sets that need no filter, about 230 keys, are merged faster by counting: 39.3 against 40.3 us. Not in the kernels of bf16 and 8-bit keys: the code
-        // alone costs their walks from seed sets more (four layers of 128K 95 -> 96.2, 16 sequences of 32K 48.2 -> 49.5 us).
-        constexpr bool ROOT_BINS = KT == RA_F32;
-        bool bucketed = false;
         if (__builtin_expect(nk > ef + SR_PREFILTER_SLACK, 0) && nk <= SR_PREFILTER_REGS * T && maxc >= 256) {
-            const bool buckets = first && (seeded ? maxc >= 768 : ROOT_BINS && maxc >= 1024);
             u64 mine[SR_PREFILTER_REGS];
             uint32_t lo = 0xffffffffu, hi = 0u;
 #pragma unroll
@@ -1233,19 +1362,14 @@ __device__ __forceinline__ int run_search(
                     hi = sc > hi ? sc : hi;
                 }
             }
-            if (!first) {                    // (a start set's extremes are known already)
-                wave_min_max(lo, hi);
-                if (lane == RA_WAVE - 1) {
-                    atomicMin(reinterpret_cast<unsigned int*>(&ctr[C_LO]), lo);
-                    atomicMax(reinterpret_cast<unsigned int*>(&ctr[C_HI]), hi);
-                }
+            wave_min_max(lo, hi);
+            if (lane == RA_WAVE - 1) {
+                atomicMin(reinterpret_cast<unsigned int*>(&ctr[C_LO]), lo);
+                atomicMax(reinterpret_cast<unsigned int*>(&ctr[C_HI]), hi);
             }
-            if (tid < 256) { cid[tid] = 0; if (buckets) { cid[512 + tid] = 0; if (ROOT_BINS && !seeded) cid[768 + tid] = 0; } }    // counts; bucket fill; expanded
+            if (tid < 256) cid[tid] = 0;
             __syncthreads();
-            // bin = (score - lowest) * 255 / (highest - lowest), truncated: every operation is
-            // monotone in the score, so a larger score never lands in a lower bin. Non-finite
-            // scores (from non-finite inputs) leave the factor at zero: one bin, everything survives.
-            const float lo_f = f32_from_ordered((uint32_t)ctr[C_LO]);
+            const float lo_f = f32_from_ordered((uint32_t)ctr[C_LO]);        // (bins as of a start set)
             const float width = f32_from_ordered((uint32_t)ctr[C_HI]) - lo_f;
             const float to_bin = width > 0.f && width < INFINITY ? 255.0f / width : 0.f;
             int bin[SR_PREFILTER_REGS];
@@ -1253,117 +1377,25 @@ __device__ __forceinline__ int run_search(
             for (int r = 0; r < SR_PREFILTER_REGS; ++r) {
                 const float b = (f32_from_ordered((uint32_t)(mine[r] >> 32)) - lo_f) * to_bin;
                 bin[r] = b >= 255.f ? 255 : b > 0.f ? (int)b : 0;
-                if (r * T + tid < nk) {
-                    atomicAdd(&cid[bin[r]], 1);
-                    if (ROOT_BINS && buckets && !seeded && !(mine[r] & 1ull)) atomicAdd(&cid[768 + bin[r]], 1);
-                }
+                if (r * T + tid < nk) atomicAdd(&cid[bin[r]], 1);
             }
             __syncthreads();
             if (wv == 0) {
-                // lane l owns bins 4l .. 4l + 3; candidates in the bins from b up = total - (those below b)
                 const int b0 = cid[4 * lane], b1 = cid[4 * lane + 1], b2 = cid[4 * lane + 2], b3 = cid[4 * lane + 3];
                 const int incl = wave_incl_scan(b0 + b1 + b2 + b3);
                 const int total = __builtin_amdgcn_readlane(incl, RA_WAVE - 1);
                 const int from3 = total - incl + b3, from2 = from3 + b2, from1 = from2 + b1, from0 = from1 + b0;
                 const int best = from3 >= ef ? 3 : from2 >= ef ? 2 : from1 >= ef ? 1 : from0 >= ef ? 0 : -1;
-                const u64 has = __ballot(best >= 0);          // never empty: bin 0 and up hold all nk > ef
-                if (lane == 63 - __clzll(has)) {
-                    ctr[C_BIN] = 4 * lane + best;
-                    if (buckets) ctr[C_NSURV] = best == 3 ? from3 : best == 2 ? from2 : best == 1 ? from1 : from0;
-                }
-                if (buckets) {                               // keys in the bins above each bin
-                    cid[256 + 4 * lane + 3] = from3 - b3;
-                    cid[256 + 4 * lane + 2] = from2 - b2;
-                    cid[256 + 4 * lane + 1] = from1 - b1;
-                    cid[256 + 4 * lane] = from0 - b0;
-                    if (ROOT_BINS && !seeded) {              // expanded ones of them
-                        const int x0 = cid[768 + 4 * lane], x1 = cid[769 + 4 * lane], x2 = cid[770 + 4 * lane], x3 = cid[771 + 4 * lane];
-                        const int xi = wave_incl_scan(x0 + x1 + x2 + x3);
-                        const int above3 = __builtin_amdgcn_readlane(xi, RA_WAVE - 1) - xi;
-                        cid[771 + 4 * lane] = above3;
-                        cid[770 + 4 * lane] = above3 + x3;
-                        cid[769 + 4 * lane] = above3 + x3 + x2;
-                        cid[768 + 4 * lane] = above3 + x3 + x2 + x1;
-                    }
-                }
+                const u64 has = __ballot(best >= 0);
+                if (lane == 63 - __clzll(has)) ctr[C_BIN] = 4 * lane + best;
             }
             __syncthreads();
             const int bstar = ctr[C_BIN];
-            if (buckets) {
-                const int nsurv = ctr[C_NSURV];              // >= ef
-#pragma unroll
-                for (int r = 0; r < SR_PREFILTER_REGS; ++r)
-                    if (r * T + tid < nk && bin[r] >= bstar) {
-                        const int at = cid[256 + bin[r]] + atomicAdd(&cid[512 + bin[r]], 1);
-                        ckey[at] = mine[r];
-                        if (masked) seed_at[at] = (uint16_t)(r * T + tid);
-                    }
-                __syncthreads();
-                auto bin_of = [&](u64 k) __attribute__((always_inline)) {
-                    const float b = (f32_from_ordered((uint32_t)(k >> 32)) - lo_f) * to_bin;
-                    return b >= 255.f ? 255 : b > 0.f ? (int)b : 0;
-                };
-                if (!ROOT_BINS || seeded) {
-                    for (int p = tid; p < nsurv; p += T) {
-                        u64 k = ckey[p];
-                        const int kb = bin_of(k), bs = cid[256 + kb], be = bs + cid[kb];
-                        int pos = bs;
-                        for (int j = bs; j < be; ++j) pos += ckey[j] > k ? 1 : 0;
-                        if (pos < ef) {
-                            if (pos < expand) {              // this step's picks: the first `expand` entries
-                                picks[pos] = key_id(k);
-                                u64 m = ~0ull;
-                                if (masked) {                // its new cells join the list, if they are few
-                                    const int c = seed_at[p];
-                                    m = (uint32_t)cnt[c] | (deg > 32 ? (u64)(uint32_t)cnt[n_root + c] << 32 : 0ull);
-                                    const int n = __popcll(m);
-                                    int at = n == 0 ? 0 : atomicAdd(wtot, n > SR_FRESH_CELLS ? T + 1 : n);
-                                    if (n <= SR_FRESH_CELLS)
-                                        for (u64 left = m; left && at < T; left &= left - 1ull, ++at)
-                                            fresh_cells[at] = (uint16_t)(pos << 6 | (__ffsll((long long)left) - 1));
-                                }
-                                if (m) touch_line(adj_h + (size_t)key_id(k) * deg, touch_off);
-                                k &= ~1ull;
-                            }
-                            nxt[pos] = k;
-                            urank_nxt[pos] = (uint16_t)pos;
-                        }
-                    }
-                    if (tid == 0) cc_nxt[S_NUNEXP] = ef;     // every entry of the new beam (nsurv >= ef)
-                } else {
-                    for (int p = tid; p < nsurv; p += T) {
-                        u64 k = ckey[p];
-                        const int kb = bin_of(k), bs = cid[256 + kb], be = bs + cid[kb];
-                        int pos = bs, ur = bs - cid[768 + kb];
-                        for (int j = bs; j < be; ++j) {
-                            const u64 other = ckey[j];
-                            const int above = other > k ? 1 : 0;
-                            pos += above;
-                            ur += above & (int)other;        // (the low bit: not expanded)
-                        }
-                        if (pos < ef) {
-                            if (!(k & 1ull)) atomicAdd(&cc_nxt[S_NUNEXP], -1);
-                            else if (ur < expand) {          // this step's picks: the first `expand` unexpanded entries
-                                picks[ur] = key_id(k);
-                                touch_line(adj_h + (size_t)key_id(k) * deg, touch_off);
-                                k &= ~1ull;
-                            }
-                            nxt[pos] = k;
-                            urank_nxt[pos] = (uint16_t)ur;
-                        }
-                    }
-                    if (tid == 0) atomicAdd(&cc_nxt[S_NUNEXP], ef);
-                }
-                nk = nsurv;
-                bucketed = true;
-            }
-            if (!bucketed) {
 #pragma unroll
             for (int r = 0; r < SR_PREFILTER_REGS; ++r)
                 if (r * T + tid < nk && bin[r] >= bstar) ckey[atomicAdd(&ctr[C_NSURV], 1)] = mine[r];
             __syncthreads();
             nk = ctr[C_NSURV];
-            }
         }
         SR_TICK(11);
 
@@ -1384,24 +1416,7 @@ __device__ __forceinline__ int run_search(
         //      step, ef 256 397 -> 378. (Four lanes per candidate, 16-way search and all, were slower than one lane: three
         //      times the instructions.)
         const int bn_new = bn + nk < ef ? bn + nk : ef;
-        // An element of the new beam at its place: key, position, unexpanded elements above it. What it does not have to
-        // store goes to the piece that touched words land in: an address chosen by a lane costs it 4 ticks, a branch 30
-        // to 60. (An element past position ef has at least as many unexpanded ones above it as there are picks.) Of a
-        // wavefront's 64 beam entries there is seldom one that is picked, and one is the last: branches for all lanes.
-        auto place = [&](u64 k, int pos, int ur, auto beam) __attribute__((always_inline)) {
-            constexpr bool BEAM = decltype(beam)::value != 0;
-            const int un = (int)(uint32_t)k & 1;
-            const bool pick = (uint32_t)(ur | (un - 1)) < (uint32_t)expand, last = pos == bn_new - 1;
-            if (!BEAM || __builtin_amdgcn_ballot_w64(pick)) *(pick ? picks + ur : reinterpret_cast<int*>(lds_raw)) = key_id(k);
-            k ^= pick ? 1ull : 0ull;
-            *(pos < ef ? nxt + pos : reinterpret_cast<u64*>(lds_raw)) = k;
-            *(pos < ef ? urank_nxt + pos : reinterpret_cast<uint16_t*>(lds_raw)) = (uint16_t)ur;
-            // (the last one has counted all)
-            if (!BEAM || __builtin_amdgcn_ballot_w64(last)) *(last ? cc_nxt + S_NUNEXP : reinterpret_cast<int*>(lds_raw)) = ur + un;
-        };
-        auto touch_row = [&](int id) __attribute__((always_inline)) {
-            touch_line(reinterpret_cast<const char*>(adj_h) + (u64)(uint32_t)id * (uint32_t)(deg * 4), touch_off);
-        };
+        auto place = [&](u64 k, int pos, int ur, auto beam) __attribute__((always_inline)) { place_in(bn_new, k, pos, ur, beam); };
         // beam entries above k, by a binary search of the same steps for every lane. (Entries from bn on are zero, and the last
         // one of a full beam is below every kept candidate, so index ef - 1 stands for all that follow.)
         typedef const __attribute__((address_space(3))) u64* lds_u64;
@@ -1428,21 +1443,7 @@ __device__ __forceinline__ int run_search(
         // (this step's picks, the first unexpanded entries, are marked expanded by now)
         auto unexpanded_above = [&](int b) __attribute__((always_inline)) { return max((int)urank[b] - np, 0); };
         // zeroes behind the candidates, written by each wavefront that reads them
-        if (!bucketed) ckey[nk + lane16] = 0ull;
-        // of 16 candidates those above k, and (ROOTS: of a root set's start) in the high half the expanded ones of them
-        auto count16 = [&](int at, u64 k, auto roots_c) __attribute__((always_inline)) {
-            u64 v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = ckey[at + u];
-            int n = 0;
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int up = v[u] > k ? 1 : 0;
-                n += up;
-                if constexpr (decltype(roots_c)::value != 0) n += (up & ~(int)(uint32_t)v[u]) << 16;
-            }
-            return n;
-        };
+        ckey[nk + lane16] = 0ull;
         // a beam entry with c candidates above it
         auto place_entry = [&](int e, u64 k, int ub, int c) __attribute__((always_inline)) {
             const int ur = c + ub, un = (int)(uint32_t)k & 1;
@@ -1497,8 +1498,7 @@ __device__ __forceinline__ int run_search(
                 }
             }
         };
-        if (bucketed) {
-        } else if (__builtin_expect(!first && nk <= (T == 1024 ? SR_NARROW / 2 : SR_NARROW), 1)) {
+        if (__builtin_expect(nk <= (T == 1024 ? SR_NARROW / 2 : SR_NARROW), 1)) {
             // ---- few candidates, one phase: 16 lanes find a candidate's place (its slot by a 16-way search, two or three
             //      dependent reads; the candidates above it by one comparison per lane), and a beam entry is compared
             //      with every candidate.
@@ -1537,7 +1537,7 @@ __device__ __forceinline__ int run_search(
                 }
                 place_entry(e, k, ub, c);
             }
-        } else if (!first && nk > SR_DIRECT && nk <= SR_MERGE_REGS * T) {
+        } else if (nk > SR_DIRECT && nk <= SR_MERGE_REGS * T) {
             // ---- many: dealt into buckets by slot, and counted inside a bucket. (us per layer if from 17, 33, 65 and 129
             //      candidates on: top-2000 165.6, 165.6, 165.8, 173; 64K keys, 16 picks, ef 128 32.1, 30.8, 30.1, 30.1; two sequences
             //      of 50K keys 35.0, 34.9, 34.7, 35.2.)
@@ -1586,12 +1586,10 @@ __device__ __forceinline__ int run_search(
             for (int c = T - 1 - tid; c < nk; c += T) {
                 const u64 k = ckey[c];
                 touch_row(key_id(k));
-                if (!first) {
-                    const int b = beam_above(k);
-                    if constexpr (HSUM) atomicAdd(&hsum[b >> 6], 1);
-                    atomicAdd(&hist[b], 1);
-                    atomicAdd(&cnt[c], b << 16);              // high half: beam entries above it
-                }
+                const int b = beam_above(k);
+                if constexpr (HSUM) atomicAdd(&hsum[b >> 6], 1);
+                atomicAdd(&hist[b], 1);
+                atomicAdd(&cnt[c], b << 16);                  // high half: beam entries above it
             }
             const int chunks = (nk + 15) >> 4;
             int t = __builtin_amdgcn_readfirstlane(wv);
@@ -1599,29 +1597,25 @@ __device__ __forceinline__ int run_search(
                 for (; t < chunks; t += T / RA_WAVE) {
                     const int c = min(g0 + lane, nk - 1);
                     const u64 k = ckey[c];
-                    const int n = first && n_first > 0 ? count16(t * 16, k, sr_int<1>{}) : count16(t * 16, k, sr_int<0>{});
+                    const int n = count16(t * 16, k, sr_int<0>{});
                     if (g0 + lane < nk && n) atomicAdd(&cnt[c], n);
                 }
             __syncthreads();
             SR_TICK(8);
-            if (!first) place_beam([&](int h, int) __attribute__((always_inline)) { return HSUM ? 0 : h; });
+            place_beam([&](int h, int) __attribute__((always_inline)) { return HSUM ? 0 : h; });
             hist_used = hist_used || !HSUM;      // (others read it too)
             SR_TICK(9);
             for (int c = T - 1 - tid; c < nk; c += T) {
                 const int both = cnt[c], n = both & 0xffff, b = both >> 16;
                 cnt[c] = 0;
                 const u64 k = ckey[c];
-                const int ub = first ? -b : unexpanded_above(b);
-                place(k, first ? n : b + n, n + ub, sr_int<0>{});
+                place(k, b + n, n + unexpanded_above(b), sr_int<0>{});
             }
         }
         __syncthreads();
         SR_TICK(4);
         bn = bn_new;
-        u64* t = cur; cur = nxt; nxt = t;
-        uint16_t* tu = urank; urank = urank_nxt; urank_nxt = tu;
-        int* tc = cc; cc = cc_nxt; cc_nxt = tc;
-        first = false;
+        swap_beams();
     }
 
     if constexpr (Hook::kShareSteps) {

@@ -1038,3 +1038,37 @@ def test_first_step_behind_a_seed_set(deg, R, ef, expand, k, heads):
             assert ids[0, h].tolist() == ref.tolist(), (n, h)
             assert st[0, h].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]], (n, h)
     idx.free()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("deg,expand,ef,n_seeds", [
+    (8, 8, 100, 64), (8, 63, 100, 65), (8, 64, 100, 65), (8, 64, 16, 500), (32, 64, 700, 600), (32, 64, 600, 601),
+    (32, 64, 64, 2048), (32, 128, 1100, 2048), (8, 64, 300, 0), (24, 32, 48, 0), (64, 64, 256, 0), (64, 66, 128, 0)])
+def test_first_beam_of_a_start_set(dtype, deg, expand, ef, n_seeds):
+    """The first beam of a walk: a seed set or (n_seeds 0) a root set, some of whose keys enter as expanded, ordered by counting
+    (64 keys or less, less than 512 words for the bins) or through bins, of fewer, as many and more keys than the beam holds,
+    with scores that tie in crowds (keys are copies of 40 rows). Integer keys: ids and counters are the oracle's."""
+    from paper_2409_10516_amd import binding as B
+    rng = np.random.default_rng(deg + 7 * n_seeds)
+    N, heads = 5000, 2
+    adj = rng.integers(0, N, size=(heads, N, deg)).astype(np.int32)
+    t = np.arange(N)
+    for j in (0, 1):
+        adj[:, :, j] = np.where(2 * t + 1 + j < N, 2 * t + 1 + j, -1)
+    adj[adj == t[None, :, None]] = -1
+    K = rng.integers(-3, 4, size=(40, 128))[rng.integers(0, 40, size=N)].astype(np.float32)
+    q = rng.integers(-3, 4, size=(1, heads, 128)).astype(np.float32)
+    Kd = torch.from_numpy(K[None, None]).to(dtype).to(DEV)
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.zeros(heads, dtype=torch.int32), 1, heads, 1)
+    idx.configure(B.RA_CFG_SEEDS, n_seeds)
+    topk = min(ef, 40)
+    qd = torch.from_numpy(q).to(dtype).to(DEV)
+    ids, st = ra.ra_search(qd, idx, Kd, 4, 20, topk, ef, expand)
+    _, _, ids_d, st_d = ra.ra_decode_step(qd, idx, Kd, Kd, 4, 20, topk, ef, expand)
+    assert torch.equal(ids, ids_d) and torch.equal(st, st_d)
+    for h in range(heads):
+        seeds = OS.backbone_seeds(adj[h], 0, n_seeds) if n_seeds else None
+        ref, rst = OS.greedy_search(q[0, h], K, adj[h], 0, ef, topk, expand, seeds=seeds, exclude=OA.static_ids(N, 4, 20))
+        assert ids[0, h].tolist() == ref.tolist()
+        assert st[0, h].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]]
+    idx.free()
