@@ -253,7 +253,7 @@ struct OffWords {
 };
 
 // What the walk asks of the fused launch (see NoHook): the keys of its start set, scored by other workgroups.
-struct SeedHook {
+template <int DT> struct SeedHook {
     int spin;
     // this head's keys in the seed hand-over area, the area's "shares off" word, whether the launch
     // has seed workgroups
@@ -263,6 +263,13 @@ struct SeedHook {
     OffWords off;
     static constexpr bool kSeedShare = true;
     static constexpr bool kShareSteps = false;
+    // value rows
+    const char* V;
+    static constexpr bool kValues = DT == RA_BF16;
+    static constexpr int value_lines = DT == RA_BF16 ? 2 : 4;
+    __device__ __forceinline__ void touch_value(int id, int line, uint32_t lds) const {
+        touch_line(V + ((size_t)(uint32_t)id * value_lines + line) * 128, lds);
+    }
     __device__ __forceinline__ void note_off_words() const { off.note(); }
     __device__ __forceinline__ bool seeds_shared() const { return seed_on && __builtin_amdgcn_readfirstlane((int)off.lds[2]) == 0; }
     // Keys c0 and c1 of the head's start set (c1 < 0: only c0, and k1 = k0), polled together a bounded
@@ -297,6 +304,7 @@ struct WalkHook {
     OffWords off;
     static constexpr bool kSeedShare = false;
     static constexpr bool kShareSteps = true;
+    static constexpr bool kValues = false;
     __device__ __forceinline__ void note_off_words() const { off.note(); }
     __device__ __forceinline__ bool steps_shared() const { return __builtin_amdgcn_readfirstlane((int)off.lds[2]) == 0; }
     __device__ __forceinline__ void steps_missed() const {
@@ -434,8 +442,8 @@ __global__ __launch_bounds__(T, SR_WAVES(KT, T)) void decode_kernel(
         cnt = run_search<DT, KT, GBITS, T>(lds_raw, head, q, adj, entry, Ksearch, n_q, n_kv, Ng, kv_stride, deg,
                                            s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
                                            lds_ids, roots, root_cap, kscale,
-                                           SeedHook{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx,
-                                                    seed_parts > 0, off});
+                                           SeedHook<DT>{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx,
+                                                    seed_parts > 0, off, Vh});
     }
 #ifdef SR_PHASE_CLOCKS
     const long long t_attn = clock64();

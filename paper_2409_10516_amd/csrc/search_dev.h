@@ -410,9 +410,12 @@ __device__ __forceinline__ void claim_cells(const int (&nb)[L], uint32_t n_keys,
 // kShareSteps says whether workers take the claims and the scores of its steps (serve_walk below) if steps_shared(), with
 // `parts_log2`, `spin` and the head's `area`. If not, and when an answer does not come, upon which steps_missed() is called by
 // one thread, the search returns -1, with no ids and no counters written.
+// kValues says whether the caller reads rows of its own of the ids found: then touch_value(id, line, off) brings a line of
+// such a row into this XCD's L2 (see touch_line).
 struct NoHook {
     static constexpr bool kSeedShare = false;
     static constexpr bool kShareSteps = false;
+    static constexpr bool kValues = false;
     __device__ __forceinline__ void note_off_words() const {}
 };
 
@@ -1160,6 +1163,11 @@ __device__ __forceinline__ int run_search(
                             fresh_cells[at] = (uint16_t)(pos << 6 | (__ffsll((long long)left) - 1));
                 }
                 if ((k & 1ull) && ur < expand && m) touch_row(key_id(k));
+                if constexpr (Hook::kValues)
+                    // (Of a seed set's best nearly all are among those found. Four layers of 128K 80.5 -> 78.6 us; nothing where the head
+                    // scores its set itself. At the step that expands all that is left, in any walk: -0.5 to -1.5 %.)
+                    if (seeds_shared && seeded && pos < take)
+                        for (int line = 0; line < hook.value_lines; ++line) hook.touch_value(key_id(k), line, touch_off);
                 place_in(bn_new, k, pos, ur, sr_int<0>{});
             }
         } else if (!missed) {
