@@ -457,7 +457,8 @@ __global__ __launch_bounds__(T, SR_WAVES(KT, T)) void decode_kernel(
     u64 w_mx = 0ull, w_l = 0ull, w_a = 0ull;
     LaneQuery<DT> ql;
     ql.load(reinterpret_cast<const char*>(q) + (size_t)head * RA_D * esz, lane16);
-    constexpr int DC_ROWS = DT == RA_BF16 ? 6 : 3;       // rows in flight per 16-lane group
+    // rows in flight per 16-lane group: a hundred in one trip with 256 threads, too (16 sequences of 32K 45.6 -> 44.9 us)
+    constexpr int DC_ROWS = DT == RA_BF16 ? (T == 256 ? 7 : 6) : 3;
     // attention over the R rows row_id(0 ..) of K and V; `behind` is called once, after the first loads
     auto attend_rows = [&](int R, auto row_id, auto behind) __attribute__((always_inline)) {
         Softmax8 st;
