@@ -108,6 +108,15 @@ __device__ __forceinline__ void row8_floats(const Row8<DT>& r, float* o) {
 template <int DT>
 __device__ __forceinline__ float at_exp(float x) { return DT == RA_BF16 ? __expf(x) : expf(x); }
 
+// the largest x of a row of 16 lanes, and what lane j holds
+__device__ __forceinline__ float max16(float x) {
+    x = fmaxf(x, at_dpp<0xB1>(x));
+    x = fmaxf(x, at_dpp<0x4E>(x));
+    x = fmaxf(x, at_dpp<0x141>(x));
+    return fmaxf(x, at_dpp<0x140>(x));
+}
+__device__ __forceinline__ float lane_f32(float x, int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j)); }
+
 // The closing step of a chunk: the (max, sum, weighted sum) states of the workgroup's 16 lane groups,
 // each lane holding 8 of the 128 outputs of its group, become one partial record per head.
 // COHERENT: the record is read by another workgroup of the same launch (relaxed agent-scope stores, which go
@@ -136,16 +145,16 @@ __device__ __forceinline__ void chunk_records(int tid, const float (&m)[NH], con
         for (int e = 0; e < 8; ++e) sa[grp * RA_D + lane16 * 8 + e] = acc[g][e];
         __syncthreads();
         if (tid < RA_D) {
-            float mx = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) mx = fmaxf(mx, sm[j]);
+            // (a lane works out the weight of one group's state; each weight is then read from its lane)
+            const float own_m = sm[lane16], own_l = sl[lane16], mx = max16(own_m);
             float a = 0.f, ll = 0.f;
             if (mx > -INFINITY) {
+                const float own = expf(own_m - mx);
 #pragma unroll
                 for (int j = 0; j < 16; ++j) {
-                    const float wgt = expf(sm[j] - mx);
+                    const float wgt = lane_f32(own, j);
                     a = fmaf(sa[j * RA_D + tid], wgt, a);
-                    ll = fmaf(sl[j], wgt, ll);
+                    ll = fmaf(lane_f32(own_l, j), wgt, ll);
                 }
             }
             float* rec = rec0 + g * rec_stride;
@@ -424,30 +433,27 @@ __device__ __forceinline__ void merge_accumulate(const float* rec, int nS, int n
                                                  float (&A)[2]) {
     const int P = nS + nG;
     for (int i0 = slice * 16; i0 < P; i0 += n_slices * 16) {
-        float rm[16], rl[16], ra[16];
+        // (a lane asks for the maximum and the sum of one record and works out its weight; each is then read from its lane)
+        const int own = i0 + (int)(threadIdx.x & 15);
+        const float rm = rec_load<COHERENT>(rec + min(own, P - 1) * AT_RS + RA_D);
+        const float rl = rec_load<COHERENT>(rec + min(own, P - 1) * AT_RS + RA_D + 1);
+        float ra[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int i = i0 + u < P ? i0 + u : P - 1;
-            rm[u] = rec_load<COHERENT>(rec + i * AT_RS + RA_D);
-            rl[u] = rec_load<COHERENT>(rec + i * AT_RS + RA_D + 1);
-            ra[u] = rec_load<COHERENT>(rec + i * AT_RS + t);
-        }
+        for (int u = 0; u < 16; ++u) ra[u] = rec_load<COHERENT>(rec + min(i0 + u, P - 1) * AT_RS + t);
 #pragma unroll
         for (int set = 0; set < 2; ++set) {
             const int lo = set == 0 ? 0 : nS, hi = set == 0 ? nS : P;
-            float cm = M[set];
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (i0 + u >= lo && i0 + u < hi) cm = fmaxf(cm, rm[u]);
+            const float cm = fmaxf(M[set], max16(own >= lo && own < hi ? rm : -INFINITY));
             if (cm > -INFINITY) {
                 const float corr = expf(M[set] - cm);      // 0 while the set's max is still -inf
+                const float weight = expf(rm - cm);
                 float a = A[set] * corr, l = L[set] * corr;
 #pragma unroll
                 for (int u = 0; u < 16; ++u) {
                     if (i0 + u >= lo && i0 + u < hi) {
-                        const float wgt = expf(rm[u] - cm);
+                        const float wgt = lane_f32(weight, u);
                         a = fmaf(ra[u], wgt, a);
-                        l = fmaf(rl[u], wgt, l);
+                        l = fmaf(lane_f32(rl, u), wgt, l);
                     }
                 }
                 M[set] = cm; L[set] = l; A[set] = a;
