@@ -635,53 +635,98 @@ __global__ __launch_bounds__(256) void pj_backbone_kernel(char* ws, ProjLayout l
 //     units apart and the rounding of the double division (under 2^-10 of a unit) cannot close the gap;
 //     equal fractions round alike, and then the larger c is first.
 //   WIDE: k = floor(c / d * 2^62) exactly (d < 2^31), c on its own.
+//   PACKED: all of it in k: [floor(c / d * 2^(2b + 1)) : 2b + 2][c][~position], where that is at most 64 bits (d < 2^b: two units
+//     apart, and the division's rounding is below 2^-10 of a unit). Comparing and moving it is half the instructions, of which
+//     a row of a few hundred candidates is some thousand: with it, and the first 64 not merged into nothing, keys of up to 256
+//     cells of 1M x 4 graphs 2.04 -> 1.58 ms, 64 graphs of 350 populated keys 48.6 -> 37.0 us. (The classes of more cells, whose
+//     tables leave few wavefronts per compute unit, are as they were: trips to memory.)
 // Zero: no candidate (a real one has c >= 1, k > 0).
-template <bool WIDE> struct Cand { u64 k; uint32_t pos; };
-template <> struct Cand<true> { u64 k; uint32_t c, pos; };
+enum { CAND_NARROW = 0, CAND_WIDE = 1, CAND_PACKED = 2 };
+template <int V> struct pj_int { static constexpr int value = V; };      // a compile-time number as an argument
+template <int MODE> struct Cand { u64 k; uint32_t pos; };
+template <> struct Cand<CAND_WIDE> { u64 k; uint32_t c, pos; };
+template <> struct Cand<CAND_PACKED> { u64 k; };
+// fields of a packed candidate: whether they fit, for counts of up to c_bits bits
+struct CandPack {
+    int d_bits, c_bits, pos_bits;
+    __device__ __forceinline__ CandPack(int most_pop, int c_bits_, int H)
+        : d_bits(33 - __clz(most_pop)), c_bits(c_bits_), pos_bits(32 - __clz(H)) {}      // (d is below twice the largest popularity)
+    __device__ __forceinline__ bool fits() const { return d_bits <= 20 && 2 * d_bits + 2 + c_bits + pos_bits <= 64; }
+    __device__ __forceinline__ CandPack() : d_bits(0), c_bits(0), pos_bits(0) {}
+    __device__ __forceinline__ uint32_t pos_mask() const { return (1u << pos_bits) - 1u; }
+};
 
-template <bool WIDE>
-__device__ __forceinline__ Cand<WIDE> cand_none() {
-    Cand<WIDE> x;
+template <int MODE>
+__device__ __forceinline__ Cand<MODE> cand_none() {
+    Cand<MODE> x;
     x.k = 0ull;
-    x.pos = 0x7fffffffu;
-    if constexpr (WIDE) x.c = 0u;
+    if constexpr (MODE != CAND_PACKED) x.pos = 0x7fffffffu;
+    if constexpr (MODE == CAND_WIDE) x.c = 0u;
     return x;
 }
-template <bool WIDE>
-__device__ __forceinline__ Cand<WIDE> cand_make(uint32_t c, uint32_t pa, uint32_t pb, uint32_t pos) {
-    Cand<WIDE> x;
+template <int MODE>
+__device__ __forceinline__ Cand<MODE> cand_make(uint32_t c, uint32_t pa, uint32_t pb, uint32_t pos, const CandPack& pack) {
+    Cand<MODE> x;
     const uint32_t d = pa + pb - c;
-    if constexpr (WIDE) {
+    if constexpr (MODE == CAND_WIDE) {
         const u64 hi = ((u64)c << 31) / d, rem = ((u64)c << 31) % d;
         x.k = (hi << 31) + (rem << 31) / d;
         x.c = c;
+    } else if constexpr (MODE == CAND_PACKED) {
+        const u64 ratio = (u64)__builtin_amdgcn_ldexp((double)c / (double)d, 2 * pack.d_bits + 1);
+        x.k = ratio << (pack.c_bits + pack.pos_bits) | (u64)c << pack.pos_bits | (u64)(pos ^ pack.pos_mask());
     } else {
         x.k = ((u64)((double)c / (double)d * 4398046511104.0) << 21) | (u64)c;
     }
-    x.pos = pos;
+    if constexpr (MODE != CAND_PACKED) x.pos = pos;
     return x;
 }
-template <bool WIDE>
-__device__ __forceinline__ bool cand_before(const Cand<WIDE>& x, const Cand<WIDE>& y) {
-    if (x.k != y.k) return x.k > y.k;
-    if constexpr (WIDE)
-        if (x.c != y.c) return x.c > y.c;
-    return x.pos < y.pos;
+template <int MODE>
+__device__ __forceinline__ bool cand_before(const Cand<MODE>& x, const Cand<MODE>& y) {
+    if constexpr (MODE == CAND_PACKED) return x.k > y.k;
+    else {
+        if (x.k != y.k) return x.k > y.k;
+        if constexpr (MODE == CAND_WIDE)
+            if (x.c != y.c) return x.c > y.c;
+        return x.pos < y.pos;
+    }
 }
 // one compare-exchange step of a bitonic network over the 64 lanes: partner lane ^ J; the lane
 // keeps the better of the two when keep_best, else the worse
-template <int J, bool WIDE>
-__device__ __forceinline__ Cand<WIDE> cand_exchange(const Cand<WIDE>& v, bool keep_best, int lane) {
-    Cand<WIDE> o;
+template <int J, int MODE>
+__device__ __forceinline__ Cand<MODE> cand_exchange(const Cand<MODE>& v, bool keep_best, int lane) {
+    Cand<MODE> o;
     o.k = ((u64)lane_xor32<J>((uint32_t)(v.k >> 32), lane) << 32) | (u64)lane_xor32<J>((uint32_t)v.k, lane);
-    o.pos = lane_xor32<J>(v.pos, lane);
-    if constexpr (WIDE) o.c = lane_xor32<J>(v.c, lane);
+    if constexpr (MODE != CAND_PACKED) o.pos = lane_xor32<J>(v.pos, lane);
+    if constexpr (MODE == CAND_WIDE) o.c = lane_xor32<J>(v.c, lane);
     return (cand_before(o, v) == keep_best) ? o : v;
 }
+// what lane `from` holds
+template <int MODE>
+__device__ __forceinline__ Cand<MODE> cand_lane(const Cand<MODE>& v, int from) {
+    Cand<MODE> o;
+    o.k = __shfl(v.k, from);
+    if constexpr (MODE != CAND_PACKED) o.pos = __shfl(v.pos, from);
+    if constexpr (MODE == CAND_WIDE) o.c = __shfl(v.c, from);
+    return o;
+}
+// Lanes that keep the better one in the exchange with lane ^ j of runs of k lanes (descending and ascending in turn, the first as
+// `desc` says), as a constant of the scalar unit: as comparisons of the lane's number, the compiler keeps all 28 of a row's over
+// the loop, in more scalar registers than there are.
+constexpr u64 cand_keepers(int k, int j, bool desc) {
+    u64 m = 0ull;
+    for (int l = 0; l < 64; ++l)
+        if ((((l & j) == 0) == ((l & k) == 0)) == desc) m |= 1ull << l;
+    return m;
+}
 // 64 candidates, one per lane, into rank order (DESC: lane 0 the best; else lane 63 the best)
-template <bool DESC, bool WIDE>
-__device__ __forceinline__ Cand<WIDE> cand_sort64(Cand<WIDE> v, int lane) {
-#define PJ_STEP(K_, J_) v = cand_exchange<J_>(v, (((lane & J_) == 0) == ((lane & K_) == 0)) == DESC, lane);
+template <bool DESC, int MODE>
+__device__ __forceinline__ Cand<MODE> cand_sort64(Cand<MODE> v, int lane) {
+#define PJ_STEP(K_, J_)                                                                     \
+    do {                                                                                    \
+        constexpr u64 keepers = cand_keepers(K_, J_, DESC);                                 \
+        v = cand_exchange<J_>(v, __builtin_amdgcn_inverse_ballot_w64(keepers), lane);       \
+    } while (0);
     PJ_STEP(2, 1)
     PJ_STEP(4, 2) PJ_STEP(4, 1)
     PJ_STEP(8, 4) PJ_STEP(8, 2) PJ_STEP(8, 1)
@@ -692,15 +737,15 @@ __device__ __forceinline__ Cand<WIDE> cand_sort64(Cand<WIDE> v, int lane) {
     return v;
 }
 // the better 64 of `best` (descending) and of v (ascending), descending
-template <bool WIDE>
-__device__ __forceinline__ Cand<WIDE> cand_merge64(Cand<WIDE> best, const Cand<WIDE>& v, int lane) {
+template <int MODE>
+__device__ __forceinline__ Cand<MODE> cand_merge64(Cand<MODE> best, const Cand<MODE>& v, int lane) {
     if (cand_before(v, best)) best = v;                // bitonic: the best 64 of the 128
-    best = cand_exchange<32>(best, (lane & 32) == 0, lane);
-    best = cand_exchange<16>(best, (lane & 16) == 0, lane);
-    best = cand_exchange<8>(best, (lane & 8) == 0, lane);
-    best = cand_exchange<4>(best, (lane & 4) == 0, lane);
-    best = cand_exchange<2>(best, (lane & 2) == 0, lane);
-    best = cand_exchange<1>(best, (lane & 1) == 0, lane);
+    best = cand_exchange<32>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 32, true)), lane);
+    best = cand_exchange<16>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 16, true)), lane);
+    best = cand_exchange<8>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 8, true)), lane);
+    best = cand_exchange<4>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 4, true)), lane);
+    best = cand_exchange<2>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 2, true)), lane);
+    best = cand_exchange<1>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 1, true)), lane);
     return best;
 }
 
@@ -711,9 +756,10 @@ __device__ __forceinline__ Cand<WIDE> cand_merge64(Cand<WIDE> best, const Cand<W
 // bisection over its bits finds a value that at least 64 and hardly more of them reach, and only
 // those (a margin of a few units below it covers the float32 division) get the exact key and are
 // sorted. `surv` holds 128 ints of LDS.
-template <int CH, bool WIDE, class Get>
-__device__ __forceinline__ void select_best(Cand<WIDE>& best, int n, uint32_t pa, const int32_t* ppop, int* surv,
-                                            int lane, Get get) {
+template <int CH, int MODE, class Get>
+__device__ __forceinline__ void select_best(Cand<MODE>& best, int n, uint32_t pa, const int32_t* ppop, int* surv,
+                                            int lane, Get get, const CandPack& pack = CandPack()) {
+    bool none = __builtin_amdgcn_readfirstlane((int)(best.k != 0ull)) == 0;          // (the first lane holds the best)
     for (int base = 0; base < n; base += 64 * CH) {
         const int m = n - base < 64 * CH ? n - base : 64 * CH;
         uint32_t f[CH];
@@ -748,20 +794,25 @@ __device__ __forceinline__ void select_best(Cand<WIDE>& best, int n, uint32_t pa
         }
         int have = 0;
         auto rank = [&](int take) __attribute__((always_inline)) {
-            Cand<WIDE> v = cand_none<WIDE>();
+            Cand<MODE> v = cand_none<MODE>();
             if (lane < take) {
                 uint32_t pos = 0u, c = 0u;
                 get(surv[lane], pos, c);
-                v = cand_make<WIDE>(c, pa, (uint32_t)ppop[pos], pos);
+                v = cand_make<MODE>(c, pa, (uint32_t)ppop[pos], pos, pack);
             }
-            Cand<WIDE> last;
+            Cand<MODE> last;
             last.k = ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(best.k >> 32), 63) << 32) |
                      (u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best.k, 63);
-            last.pos = (uint32_t)__builtin_amdgcn_readlane((int)best.pos, 63);
-            if constexpr (WIDE) last.c = (uint32_t)__builtin_amdgcn_readlane((int)best.c, 63);
+            if constexpr (MODE != CAND_PACKED) last.pos = (uint32_t)__builtin_amdgcn_readlane((int)best.pos, 63);
+            if constexpr (MODE == CAND_WIDE) last.c = (uint32_t)__builtin_amdgcn_readlane((int)best.c, 63);
             if (__ballot(cand_before(v, last)) == 0ull) return;            // nothing here makes the 64
             v = cand_sort64<false>(v, lane);
-            best = cand_merge64(best, v, lane);
+            if (none) {                                      // (uniform) the first of them: the same, best first
+                none = false;
+                best = cand_lane(v, 63 - lane);
+            } else {
+                best = cand_merge64(best, v, lane);
+            }
         };
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
@@ -789,18 +840,21 @@ __device__ __forceinline__ void select_best(Cand<WIDE>& best, int n, uint32_t pa
 // Row of the key at position t: its backbone children pi[2t+1], pi[2t+2], then the ranked
 // candidates (lane l of `best` holds the l-th best) that are not among the children, until deg
 // entries; -1 beyond. One wavefront.
-template <bool WIDE>
-__device__ __forceinline__ void write_row(int32_t* row, const Cand<WIDE>& best, int t, const int32_t* pi, int64_t N,
-                                          int deg, int lane) {
+template <int MODE>
+__device__ __forceinline__ void write_row(int32_t* row, const Cand<MODE>& best, int t, const int32_t* pi, int64_t N,
+                                          int deg, int lane, const CandPack& pack = CandPack()) {
     const int64_t ch = 2 * (int64_t)t + 1;
     int nk = (int)(N - ch < 0 ? 0 : N - ch < 2 ? N - ch : 2);
     if (nk > deg) nk = deg;
-    const bool keep = best.k != 0ull && lane < deg && ((int64_t)best.pos < ch || (int64_t)best.pos >= ch + nk);
+    uint32_t pos;
+    if constexpr (MODE == CAND_PACKED) pos = ((uint32_t)best.k & pack.pos_mask()) ^ pack.pos_mask();
+    else pos = best.pos;
+    const bool keep = best.k != 0ull && lane < deg && ((int64_t)pos < ch || (int64_t)pos >= ch + nk);
     const u64 km = __ballot(keep);
     const int at = nk + __popcll(km & ((1ull << lane) - 1ull));
     const int total = nk + __popcll(km);
     if (lane < nk) row[lane] = pi[ch + lane];
-    if (keep && at < deg) row[at] = pi[best.pos];
+    if (keep && at < deg) row[at] = pi[pos];
     if (lane >= total && lane < deg) row[lane] = -1;
 }
 
@@ -886,8 +940,8 @@ __device__ __forceinline__ int large_end(const ProjWs& w, int H) {
 }
 
 // the best 64 of a workgroup's wavefronts, and the row of the key at position t
-template <int T, bool WIDE>
-__device__ __forceinline__ void finish_row(Cand<WIDE> best, Cand<WIDE> (*s_best)[64], int32_t* adj_g, int t,
+template <int T, int MODE>
+__device__ __forceinline__ void finish_row(Cand<MODE> best, Cand<MODE> (*s_best)[64], int32_t* adj_g, int t,
                                            const ProjWs& w, int64_t N, int deg) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     // pairs of wavefronts, then pairs of those
@@ -908,11 +962,11 @@ __device__ __forceinline__ void finish_row(Cand<WIDE> best, Cand<WIDE> (*s_best)
 // never waited for (a returning add per cell, to notice first touches, was bound by its latency: 7.0
 // against 2.9 ms at 128K), and the candidates are the non-zero words.
 // grid: x = graph, y = worker of the graph
-template <bool WIDE>
+template <int MODE>
 __global__ __launch_bounds__(PJ_ROW_T) void pj_rows_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
                                                            int32_t* __restrict__ adj) {
     constexpr int WV = PJ_ROW_T / 64;
-    __shared__ Cand<WIDE> s_best[WV][64];
+    __shared__ Cand<MODE> s_best[WV][64];
     __shared__ int s_surv[WV][128];
     __shared__ uint32_t tab[PJ_LDS_TAB];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -934,7 +988,7 @@ __global__ __launch_bounds__(PJ_ROW_T) void pj_rows_kernel(char* ws, ProjLayout 
         __syncthreads();
         if (tid < nh) w.with_hubs[(size_t)(t - nh) * PJ_HUBS + tid] = tab[tid];
         // a wavefront ranks its share of the positions (chunks of 64 dealt in turn)
-        Cand<WIDE> best = cand_none<WIDE>();
+        Cand<MODE> best = cand_none<MODE>();
         const int chunks = (H + 63) / 64, mine = (chunks - wv + WV - 1) / WV;
         select_best<8>(best, mine * 64, (uint32_t)pa, w.ppop, s_surv[wv], lane,
                        [&](int x, uint32_t& pos, uint32_t& c) {
@@ -951,11 +1005,11 @@ __global__ __launch_bounds__(PJ_ROW_T) void pj_rows_kernel(char* ws, ProjLayout 
 // word. A key with more cells than the table takes is done in passes over its lists, each counting the
 // positions of its own residue. What fits neither way (too many passes, count and position beyond 32
 // bits, a crowd in one residue) is left to pj_rows_hub_kernel: its first positions, or the overflow list.
-template <bool WIDE>
+template <int MODE>
 __global__ __launch_bounds__(PJ_HASH_T) void pj_rows_hash_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
                                                                  int32_t* __restrict__ adj) {
     constexpr int WV = PJ_HASH_T / 64;
-    __shared__ Cand<WIDE> s_best[WV][64];
+    __shared__ Cand<MODE> s_best[WV][64];
     __shared__ int s_surv[WV][128];
     __shared__ uint32_t tab[PJ_HASH_TAB];
     __shared__ int s_over;
@@ -983,7 +1037,7 @@ __global__ __launch_bounds__(PJ_HASH_T) void pj_rows_hash_kernel(char* ws, ProjL
         while (slots < PJ_HASH_TAB && slots < 2 * pa * knn) slots <<= 1;
         const int quarter = slots / WV;
         uint32_t* part = passes > 1 ? mine : tab + wv * quarter;
-        Cand<WIDE> best = cand_none<WIDE>();
+        Cand<MODE> best = cand_none<MODE>();
         for (int r = 0; r < passes; ++r) {
             walk_lists<8>(inv, w.lp, 0, pa, knn, e, r0, rstep, [&](int p) {
                 // residue classes of a multiplicative hash: neighbouring positions spread out
@@ -1029,11 +1083,11 @@ __global__ __launch_bounds__(PJ_HASH_T) void pj_rows_hash_kernel(char* ws, ProjL
 // The keys pj_rows_hash_kernel leaves: counters of positions below PJ_LDS_TAB in LDS, of the others in
 // device memory (adds that return nothing), then every counter is looked at.
 // grid: x = graph, y = worker
-template <bool WIDE>
+template <int MODE>
 __global__ __launch_bounds__(PJ_HUB_T) void pj_rows_hub_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
                                                                int32_t* __restrict__ adj) {
     constexpr int WV = PJ_HUB_T / 64;
-    __shared__ Cand<WIDE> s_best[WV][64];
+    __shared__ Cand<MODE> s_best[WV][64];
     __shared__ int s_surv[WV][128];
     __shared__ uint32_t tab[PJ_LDS_TAB];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -1061,7 +1115,7 @@ __global__ __launch_bounds__(PJ_HUB_T) void pj_rows_hub_kernel(char* ws, ProjLay
         });
         __builtin_amdgcn_s_waitcnt(0);                       // the adds have been made before anyone reads
         __syncthreads();
-        Cand<WIDE> best = cand_none<WIDE>();
+        Cand<MODE> best = cand_none<MODE>();
         const int chunks = (H + 63) / 64, mine = (chunks - wv + WV - 1) / WV;
         select_best<16>(best, mine * 64, (uint32_t)pa, w.ppop, s_surv[wv], lane,
                         [&](int y, uint32_t& pos, uint32_t& c) {
@@ -1088,7 +1142,7 @@ __global__ __launch_bounds__(PJ_HUB_T) void pj_rows_hub_kernel(char* ws, ProjLay
 // compute unit holds more wavefronts, whose trips to memory (list numbers, lists, popularities) hide
 // behind each other.
 // grid: x = graph, y = worker
-template <int TOUCH, int BELOW, bool WIDE>
+template <int TOUCH, int BELOW, int MODE>
 __global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_small_kernel(
     char* ws, ProjLayout l, int64_t N, int knn, int deg, int32_t* __restrict__ adj) {
     constexpr int SLOTS = 2 * TOUCH;
@@ -1108,53 +1162,60 @@ __global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_small_kernel(
     pj_wave_sync();
     const int t0 = w.H[3 + (TOUCH == PJ_TOUCH_A ? PJ_CLASS_A : TOUCH == PJ_TOUCH_B ? PJ_CLASS_B : PJ_CLASS_C)];
     const int t1 = BELOW == 0 ? H : w.H[3 + (BELOW == PJ_TOUCH_A ? PJ_CLASS_A : PJ_CLASS_B)];
-    for (int t = t0 + blockIdx.y * PJ_SMALL_WAVES + wv; t < t1; t += gridDim.y * PJ_SMALL_WAVES) {
-        const int a = w.pi[t];
-        const int pa = w.ppop[t];
-        int slots = 128;
-        while (slots < 2 * pa * knn) slots <<= 1;        // <= SLOTS by small_limit()
-        auto bump = [&](int p) {
-            if (p != t) lds_table_bump(slot, slots, (uint32_t)p + 1u, 7);
-        };
-        if (H <= PJ_LDS_TAB)
-            walk_narrow<4, 64>(w.inv + w.off[a], reinterpret_cast<const uint16_t*>(w.lp), pa, row16(knn), lane, bump);
-        else
-            walk_lists<4>(w.inv + w.off[a], w.lp, 0, pa, knn, e, lane / kp, lpp, bump);
-        pj_wave_sync();
-        // pack the table in place: entry q moves to the number of entries before it
-        int nc = 0;
-        for (int q0 = 0; q0 < slots; q0 += 64) {
-            const uint32_t v = slot[q0 + lane];
-            slot[q0 + lane] = 0u;
-            const u64 m = __ballot(v != 0u);
-            if (v != 0u) slot[nc + __popcll(m & ((1ull << lane) - 1ull))] = v;
-            nc += __popcll(m);
-        }
-        pj_wave_sync();
-        if (nh) {                                            // (uniform)
-            int* row = s_surv[wv];
-            row[lane] = row[64 + lane] = 0;
+    auto rows = [&](auto mode_c, const CandPack& pack) __attribute__((always_inline)) {
+        constexpr int M = decltype(mode_c)::value;
+        for (int t = t0 + blockIdx.y * PJ_SMALL_WAVES + wv; t < t1; t += gridDim.y * PJ_SMALL_WAVES) {
+            const int a = w.pi[t];
+            const int pa = w.ppop[t];
+            int slots = 128;
+            while (slots < 2 * pa * knn) slots <<= 1;        // <= SLOTS by small_limit()
+            auto bump = [&](int p) {
+                if (p != t) lds_table_bump(slot, slots, (uint32_t)p + 1u, 7);
+            };
+            if (H <= PJ_LDS_TAB)
+                walk_narrow<4, 64>(w.inv + w.off[a], reinterpret_cast<const uint16_t*>(w.lp), pa, row16(knn), lane, bump);
+            else
+                walk_lists<4>(w.inv + w.off[a], w.lp, 0, pa, knn, e, lane / kp, lpp, bump);
             pj_wave_sync();
-            for (int x = lane; x < nc; x += 64) {
-                const uint32_t v = slot[x];
-                if ((int)(v >> 7) <= nh) row[(v >> 7) - 1u] = (int)(v & 127u);
+            // pack the table in place: entry q moves to the number of entries before it
+            int nc = 0;
+            for (int q0 = 0; q0 < slots; q0 += 64) {
+                const uint32_t v = slot[q0 + lane];
+                slot[q0 + lane] = 0u;
+                const u64 m = __ballot(v != 0u);
+                if (v != 0u) slot[nc + __popcll(m & ((1ull << lane) - 1ull))] = v;
+                nc += __popcll(m);
             }
             pj_wave_sync();
-            for (int x = lane; x < nh; x += 64) w.with_hubs[(size_t)(t - nh) * PJ_HUBS + x] = (uint32_t)row[x];
+            if (nh) {                                            // (uniform)
+                int* row = s_surv[wv];
+                row[lane] = row[64 + lane] = 0;
+                pj_wave_sync();
+                for (int x = lane; x < nc; x += 64) {
+                    const uint32_t v = slot[x];
+                    if ((int)(v >> 7) <= nh) row[(v >> 7) - 1u] = (int)(v & 127u);
+                }
+                pj_wave_sync();
+                for (int x = lane; x < nh; x += 64) w.with_hubs[(size_t)(t - nh) * PJ_HUBS + x] = (uint32_t)row[x];
+                pj_wave_sync();
+            }
+            Cand<M> best = cand_none<M>();
+            select_best<(TOUCH + 63) / 64 < 16 ? (TOUCH + 63) / 64 : 16>(
+                best, nc, (uint32_t)pa, w.ppop, s_surv[wv], lane, [&](int x, uint32_t& pos, uint32_t& c) {
+                    const uint32_t v = slot[x];
+                    pos = (v >> 7) - 1u;
+                    c = v & 127u;
+                }, pack);
             pj_wave_sync();
+            for (int x = lane; x < nc; x += 64) slot[x] = 0u;       // the table is empty again
+            pj_wave_sync();
+            write_row(adj_g + (size_t)a * deg, best, t, w.pi, N, deg, lane, pack);
         }
-        Cand<WIDE> best = cand_none<WIDE>();
-        select_best<(TOUCH + 63) / 64 < 16 ? (TOUCH + 63) / 64 : 16>(
-            best, nc, (uint32_t)pa, w.ppop, s_surv[wv], lane, [&](int x, uint32_t& pos, uint32_t& c) {
-                const uint32_t v = slot[x];
-                pos = (v >> 7) - 1u;
-                c = v & 127u;
-            });
-        pj_wave_sync();
-        for (int x = lane; x < nc; x += 64) slot[x] = 0u;       // the table is empty again
-        pj_wave_sync();
-        write_row(adj_g + (size_t)a * deg, best, t, w.pi, N, deg, lane);
-    }
+    };
+    if (t0 >= t1) return;
+    const CandPack pack(w.ppop[0], 7, H);
+    if (pack.fits()) rows(pj_int<CAND_PACKED>{}, pack);
+    else rows(pj_int<MODE>{}, pack);
 }
 
 // Rows of the keys with at most PJ_WAVE_LISTS lists in a graph of at most PJ_WAVE_TAB populated keys, one per wavefront,
@@ -1164,7 +1225,7 @@ __global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_small_kernel(
 // PJ_WAVE_SMALL_TAB the smaller keys stay the small kernels': looking through a table of H counters for a key of a few
 // lists costs more than a hash table (the same 32 graphs: 0.60 ms here, without them 0.30, and 0.22 there).
 // grid: x = graph, y = worker
-template <int TAB, int ABOVE, bool WIDE>
+template <int TAB, int ABOVE, int MODE>
 __global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_wave_kernel(char* ws, ProjLayout l, int64_t N, int knn,
                                                                            int deg, int32_t* __restrict__ adj) {
     __shared__ uint32_t s_tab[PJ_SMALL_WAVES][TAB];
@@ -1179,45 +1240,51 @@ __global__ __launch_bounds__(PJ_SMALL_WAVES * 64) void pj_rows_wave_kernel(char*
     for (int x = lane; x < H; x += 64) tab[x] = 0u;
     pj_wave_sync();
     const int t_end = TAB == PJ_WAVE_SMALL_TAB ? H : w.H[3 + PJ_CLASS_C];
-    for (int t = large_end(w, H) + blockIdx.y * PJ_SMALL_WAVES + wv; t < t_end; t += gridDim.y * PJ_SMALL_WAVES) {
-        const int a = w.pi[t];
-        const int pa = w.ppop[t];
-        walk_narrow<4, 64>(w.inv + w.off[a], reinterpret_cast<const uint16_t*>(w.lp), pa, row16(knn), lane,
-                           [&](int p) { atomicAdd(&tab[p], 1u); });
-        pj_wave_sync();
-        if (lane == 0) tab[t] = 0u;                          // the key itself
-        pj_wave_sync();
-        for (int x = lane; x < nh; x += 64) w.with_hubs[(size_t)(t - nh) * PJ_HUBS + x] = tab[x];
-        // pack the table in place, position and count in a word (a count is at most PJ_WAVE_LISTS x 64)
-        static_assert(PJ_WAVE_TAB <= 1 << 12 && PJ_WAVE_LISTS * 64 < 1 << 20, "a position and a count share a word");
-        int nc = 0;
-        for (int q0 = 0; q0 < H; q0 += 64) {
-            const int q = q0 + lane;
-            const uint32_t c = q < H ? tab[q] : 0u;
-            if (q < H) tab[q] = 0u;
-            const u64 m = __ballot(c != 0u);
-            if (c != 0u) tab[nc + __popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)q << 20 | c;
-            nc += __popcll(m);
+    auto rows = [&](auto mode_c, const CandPack& pack) __attribute__((always_inline)) {
+        constexpr int M = decltype(mode_c)::value;
+        for (int t = large_end(w, H) + blockIdx.y * PJ_SMALL_WAVES + wv; t < t_end; t += gridDim.y * PJ_SMALL_WAVES) {
+            const int a = w.pi[t];
+            const int pa = w.ppop[t];
+            walk_narrow<4, 64>(w.inv + w.off[a], reinterpret_cast<const uint16_t*>(w.lp), pa, row16(knn), lane,
+                               [&](int p) { atomicAdd(&tab[p], 1u); });
+            pj_wave_sync();
+            if (lane == 0) tab[t] = 0u;                          // the key itself
+            pj_wave_sync();
+            for (int x = lane; x < nh; x += 64) w.with_hubs[(size_t)(t - nh) * PJ_HUBS + x] = tab[x];
+            // pack the table in place, position and count in a word (a count is at most PJ_WAVE_LISTS x 64)
+            static_assert(PJ_WAVE_TAB <= 1 << 12 && PJ_WAVE_LISTS * 64 < 1 << 20, "a position and a count share a word");
+            int nc = 0;
+            for (int q0 = 0; q0 < H; q0 += 64) {
+                const int q = q0 + lane;
+                const uint32_t c = q < H ? tab[q] : 0u;
+                if (q < H) tab[q] = 0u;
+                const u64 m = __ballot(c != 0u);
+                if (c != 0u) tab[nc + __popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)q << 20 | c;
+                nc += __popcll(m);
+            }
+            pj_wave_sync();
+            Cand<M> best = cand_none<M>();
+            select_best<8>(best, nc, (uint32_t)pa, w.ppop, s_surv[wv], lane, [&](int x, uint32_t& pos, uint32_t& c) {
+                const uint32_t v = tab[x];
+                pos = v >> 20;
+                c = v & 0xfffffu;
+            }, pack);
+            pj_wave_sync();
+            for (int x = lane; x < nc; x += 64) tab[x] = 0u;
+            pj_wave_sync();
+            write_row(adj_g + (size_t)a * deg, best, t, w.pi, N, deg, lane, pack);
         }
-        pj_wave_sync();
-        Cand<WIDE> best = cand_none<WIDE>();
-        select_best<8>(best, nc, (uint32_t)pa, w.ppop, s_surv[wv], lane, [&](int x, uint32_t& pos, uint32_t& c) {
-            const uint32_t v = tab[x];
-            pos = v >> 20;
-            c = v & 0xfffffu;
-        });
-        pj_wave_sync();
-        for (int x = lane; x < nc; x += 64) tab[x] = 0u;
-        pj_wave_sync();
-        write_row(adj_g + (size_t)a * deg, best, t, w.pi, N, deg, lane);
-    }
+    };
+    const CandPack pack(w.ppop[0], 15, H);                  // (a count is at most PJ_WAVE_LISTS x 64)
+    if (pack.fits()) rows(pj_int<CAND_PACKED>{}, pack);
+    else rows(pj_int<MODE>{}, pack);
 }
 
 // Rows of the hubs, one per wavefront: their counts with each other are pj_pairs_kernel's, those with the other keys what
 // these found on their own walks. 32 graphs of 128K lists 0.08 ms; a walk per hub, over the front of each of its lists' rows
 // only, and only where the other hubs did not settle its row, 1.0 ms; over whole rows 1.7.
 // grid: x = graph, y = workers
-template <bool WIDE>
+template <int MODE>
 __global__ __launch_bounds__(PJ_ROW_T) void pj_rows_hubs_kernel(char* ws, ProjLayout l, int64_t N, int knn, int deg,
                                                                 int32_t* __restrict__ adj) {
     constexpr int WV = PJ_ROW_T / 64;
@@ -1273,7 +1340,7 @@ __global__ __launch_bounds__(PJ_ROW_T) void pj_rows_hubs_kernel(char* ws, ProjLa
     if (t >= nh) return;
     if (lane == 0) s_with[wv][t] = 0u;                       // the key itself
     pj_wave_sync();
-    Cand<WIDE> best = cand_none<WIDE>();
+    Cand<MODE> best = cand_none<MODE>();
     select_best<8>(best, H, (uint32_t)w.ppop[t], w.ppop, s_surv[wv], lane, [&](int x, uint32_t& pos, uint32_t& c) {
         pos = (uint32_t)x;
         c = x < nh ? s_with[wv][x] : w.with_hubs[(size_t)(x - nh) * PJ_HUBS + t];
@@ -1281,7 +1348,7 @@ __global__ __launch_bounds__(PJ_ROW_T) void pj_rows_hubs_kernel(char* ws, ProjLa
     write_row(adj + ((size_t)blockIdx.x * N + w.pi[t]) * deg, best, t, w.pi, N, deg, lane);
 }
 
-template <bool WIDE>
+template <int MODE>
 static void project_rows(const ProjLayout& l, char* ws, int n_graphs, int64_t N, int knn, int deg, hipStream_t st,
                          int32_t* adj) {
     // workgroups that fill the part: 4 per compute unit by position, 2 of the hash kernel, 2, 4 and 8 of the small
@@ -1289,30 +1356,30 @@ static void project_rows(const ProjLayout& l, char* ws, int n_graphs, int64_t N,
     auto wgs = [&](int all) { return (unsigned)(n_graphs >= all ? 1 : all / n_graphs); };
     // (a key of many lists takes its workgroup long: enough workers that no other key waits behind one)
     const dim3 threads(PJ_SMALL_WAVES * 64);
-    hipLaunchKernelGGL(pj_rows_kernel<WIDE>, dim3(n_graphs, wgs(4096) < 128 ? wgs(4096) : 128u), dim3(PJ_ROW_T), 0, st,
+    hipLaunchKernelGGL(pj_rows_kernel<MODE>, dim3(n_graphs, wgs(4096) < 128 ? wgs(4096) : 128u), dim3(PJ_ROW_T), 0, st,
                        ws, l, N, knn, deg, adj);
-    hipLaunchKernelGGL((pj_rows_wave_kernel<PJ_WAVE_SMALL_TAB, 0, WIDE>), dim3(n_graphs, wgs(4096)), threads, 0, st, ws, l,
+    hipLaunchKernelGGL((pj_rows_wave_kernel<PJ_WAVE_SMALL_TAB, 0, MODE>), dim3(n_graphs, wgs(4096)), threads, 0, st, ws, l,
                        N, knn, deg, adj);
     if (l.cap > PJ_WAVE_SMALL_TAB)
-        hipLaunchKernelGGL((pj_rows_wave_kernel<PJ_WAVE_TAB, PJ_WAVE_SMALL_TAB, WIDE>), dim3(n_graphs, wgs(1024)), threads, 0,
+        hipLaunchKernelGGL((pj_rows_wave_kernel<PJ_WAVE_TAB, PJ_WAVE_SMALL_TAB, MODE>), dim3(n_graphs, wgs(1024)), threads, 0,
                            st, ws, l, N, knn, deg, adj);
     if (l.cap > PJ_LDS_TAB) {
-        hipLaunchKernelGGL(pj_rows_hash_kernel<WIDE>, dim3(n_graphs, wgs(2048)), dim3(PJ_HASH_T), 0, st, ws, l, N,
+        hipLaunchKernelGGL(pj_rows_hash_kernel<MODE>, dim3(n_graphs, wgs(2048)), dim3(PJ_HASH_T), 0, st, ws, l, N,
                            knn, deg, adj);
-        hipLaunchKernelGGL(pj_rows_hub_kernel<WIDE>, dim3(n_graphs, l.n_hub_wg), dim3(PJ_HUB_T), 0, st, ws, l, N,
+        hipLaunchKernelGGL(pj_rows_hub_kernel<MODE>, dim3(n_graphs, l.n_hub_wg), dim3(PJ_HUB_T), 0, st, ws, l, N,
                            knn, deg, adj);
     }
     if (l.cap > PJ_WAVE_SMALL_TAB) {
-        hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_C, PJ_TOUCH_B, WIDE>), dim3(n_graphs, wgs(512)), threads, 0, st,
+        hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_C, PJ_TOUCH_B, MODE>), dim3(n_graphs, wgs(512)), threads, 0, st,
                            ws, l, N, knn, deg, adj);
-        hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_B, PJ_TOUCH_A, WIDE>), dim3(n_graphs, wgs(1024)), threads, 0, st,
+        hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_B, PJ_TOUCH_A, MODE>), dim3(n_graphs, wgs(1024)), threads, 0, st,
                            ws, l, N, knn, deg, adj);
-        hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_A, 0, WIDE>), dim3(n_graphs, wgs(4096)), threads, 0, st, ws, l,
+        hipLaunchKernelGGL((pj_rows_small_kernel<PJ_TOUCH_A, 0, MODE>), dim3(n_graphs, wgs(4096)), threads, 0, st, ws, l,
                            N, knn, deg, adj);
     }
     // (after the other rows: it reads their counts)
     if (l.n_slabs)
-        hipLaunchKernelGGL(pj_rows_hubs_kernel<WIDE>, dim3(n_graphs, PJ_HUBS * 64 / PJ_ROW_T), dim3(PJ_ROW_T), 0, st, ws, l, N,
+        hipLaunchKernelGGL(pj_rows_hubs_kernel<MODE>, dim3(n_graphs, PJ_HUBS * 64 / PJ_ROW_T), dim3(PJ_ROW_T), 0, st, ws, l, N,
                            knn, deg, adj);
 }
 
@@ -1345,8 +1412,8 @@ static ra_status project_group(const ProjLayout& l, char* ws, const int32_t* L, 
         hipLaunchKernelGGL(pj_backbone_kernel<4>, dim3(zx, n_graphs), dim3(256), 0, st, ws, l, N, deg, adj);
     else
         hipLaunchKernelGGL(pj_backbone_kernel<1>, dim3(zx, n_graphs), dim3(256), 0, st, ws, l, N, deg, adj);
-    if (M <= (1 << 19)) project_rows<false>(l, ws, n_graphs, N, knn, deg, st, adj);
-    else project_rows<true>(l, ws, n_graphs, N, knn, deg, st, adj);
+    if (M <= (1 << 19)) project_rows<CAND_NARROW>(l, ws, n_graphs, N, knn, deg, st, adj);
+    else project_rows<CAND_WIDE>(l, ws, n_graphs, N, knn, deg, st, adj);
     RA_HIP(hipGetLastError());
     return RA_OK;
 }

@@ -826,3 +826,27 @@ def test_knn_without_room_for_the_8bit_copies():
     finally:
         full.clear()
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("M", [131071, 131072])
+@pytest.mark.parametrize("H", [900, 135000])
+def test_projection_candidates_in_one_word(M, H):
+    """A ranked candidate's overlap, count and position share 64 bits where the largest popularity and the number of populated
+    keys allow it (one key in all of 131071 lists), and do not beyond (131072): the same rows, of keys with a hundred lists in
+    a small graph and with a few in one of 135000 populated keys. Many equal overlaps; -1 in some rows."""
+    rng = np.random.default_rng(H)
+    N, deg = H + 10, 24
+    L = np.zeros((M, 3), np.int32)
+    L[:, 1] = 1 + rng.integers(0, 8, size=M) if H < 1000 else 1 + rng.permutation(M) % (H - 1)
+    L[:, 2] = 9 + rng.integers(0, H - 9, size=M) if H < 1000 else 1 + (rng.permutation(M) + M) % (H - 1)
+    same = L[:, 1] == L[:, 2]
+    L[same, 2] = L[same, 2] % (H - 1) + 1
+    pop = np.bincount(L.ravel(), minlength=N)
+    assert pop[0] == M and ((pop > 0).sum() >= 131072 if H > 1000 else 800 < (pop > 0).sum() < 1024)
+    rows = np.arange(N) if H < 1000 else rng.choice(N, 500, replace=False)
+    adj, entry = ra.ra_project(torch.from_numpy(L[None]).to(DEV), N, deg)
+    radj, rent = OP.project(L, N, deg, rows=rows)
+    assert int(entry[0]) == rent
+    adj = adj[0].cpu().numpy()
+    for a in rows:
+        assert np.array_equal(adj[a], radj[a]), (a, adj[a], radj[a])
