@@ -158,3 +158,23 @@ def test_rerank_recovers_the_recall_of_the_8bit_walk():
     assert np.mean(r_rr) >= np.mean(r_q8) and np.mean(r_rr) >= np.mean(r_plain) - 0.01, (
         np.mean(r_plain), np.mean(r_q8), np.mean(r_rr))
     idx.free()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("shape,offset", [((1, 1, 1), 0), ((2, 3, 63), 0), ((1, 2, 65), 1), ((1, 1, 70001), 0), ((3, 700, 5), 0), ((1, 1, 4099), 3)])
+def test_quantize_keys_of_any_number_and_alignment(dtype, shape, offset):
+    """Rows in numbers that leave a part of a workgroup's pass, many heads of few rows, keys that are not 16-byte aligned;
+    a zero column and halves that round to even: the oracle's bytes and scales."""
+    n = shape[0] * shape[1] * shape[2] * 128
+    g = torch.Generator().manual_seed(n + offset)
+    flat = torch.randn(n + offset, generator=g).to(dtype)
+    K = flat[offset:].view(*shape, 128)
+    K[..., 5] = 0
+    K[..., 7] = (torch.arange(shape[2]) % 255 - 127).to(dtype) / 2
+    base = flat.to(DEV)
+    Kd = base[offset:].view(*shape, 128)
+    K8, scale = ra.ra_quantize_keys(Kd)
+    for s in range(shape[0]):
+        for h in range(0, shape[1], 97 if shape[1] > 10 else 1):
+            k8, sc = OQ.quantize_keys(K[s, h].float().numpy())
+            assert np.array_equal(scale[s, h].cpu().numpy(), sc) and np.array_equal(K8[s, h].cpu().numpy(), k8)
