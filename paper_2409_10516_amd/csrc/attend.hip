@@ -64,12 +64,12 @@ __global__ __launch_bounds__(AT_THREADS) void attend_partial_kernel(
             attend_chunk_mfma<G, TICKETS>(threadIdx.x, qg, Kh, Vh, src, first_chunk, n_sub, step, scale, rec_g + (size_t)x * AT_RS,
                                           (int64_t)P * AT_RS, smem);
         else
-            attend_chunk<DT, G, TICKETS>(threadIdx.x, qg, Kh, Vh, src, first_chunk, n_sub, step, scale, rec_g + (size_t)x * AT_RS,
+            attend_chunk<DT, G, TICKETS, LONG>(threadIdx.x, qg, Kh, Vh, src, first_chunk, n_sub, step, scale, rec_g + (size_t)x * AT_RS,
                                          (int64_t)P * AT_RS, smem);
     } else {
         const int t = x - nS, g = t / nG, c = t % nG;
         RowSrc src{ids + ((size_t)seq * n_q + h0 + g) * topk, N, 0, 0, topk};
-        attend_chunk<DT, 1, TICKETS>(threadIdx.x, qg + (size_t)g * RA_D * esz, Kh, Vh, src, c, 1, 1, scale,
+        attend_chunk<DT, 1, TICKETS, false>(threadIdx.x, qg + (size_t)g * RA_D * esz, Kh, Vh, src, c, 1, 1, scale,
                                      rec_g + ((size_t)g * P + nS + c) * AT_RS, 0, smem);
         first = g;
         n_mine = 1;

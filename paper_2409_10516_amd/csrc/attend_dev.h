@@ -172,7 +172,7 @@ __device__ __forceinline__ void chunk_records(int tid, const float (&m)[NH], con
 // long dense range is streamed, so that the number of partial records stays small): chunk, chunk + step, ... (ra_launch_attend
 // says which. Three tiles in flight instead of two, and 640, 768 or 1024 workgroups instead of 504, were slower.)
 // Called by all AT_THREADS threads (it contains workgroup barriers), with AT_CHUNK_LDS_FLOATS at `smem`.
-template <int DT, int NH, bool COHERENT>
+template <int DT, int NH, bool COHERENT, bool LONG>
 __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void* Vh,
                              const RowSrc& src, int chunk, int n_sub, int step, float scale, float* rec0,
                              int64_t rec_stride, float* smem) {
@@ -199,7 +199,7 @@ __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void
 #pragma unroll
         for (int i = 0; i < RPG; ++i) {
             const int64_t row = rid[i] >= 0 ? rid[i] : 0;
-            if (n_sub > 1) {                    // a long dense range, streamed once
+            if (LONG) {                         // a long dense range, streamed once
                 kr[i] = load_row8_stream<DT>(Kh, row, lane16);
                 vr[i] = load_row8_stream<DT>(Vh, row, lane16);
             } else {
@@ -208,11 +208,13 @@ __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void
             }
         }
     };
+    // (of a dense range)
+    auto whole = [&](int sub) { return (chunk + sub * step + 1) * AT_CH <= src.count; };
     // One sub-chunk: the RPG logits of every head first (independent chains the compiler can
     // interleave), then one move of the running maximum per head and sub-chunk, then the weighted
     // sums. No branch separates the rows: the dependent latencies of one (row, head) hide behind
     // the others' work.
-    auto consume = [&](const int64_t (&rid)[RPG], const Row8<DT> (&kr)[RPG], const Row8<DT> (&vr)[RPG]) {
+    auto consume = [&](bool all, const int64_t (&rid)[RPG], const Row8<DT> (&kr)[RPG], const Row8<DT> (&vr)[RPG]) {
         float z[NH][RPG];
 #pragma unroll
         for (int i = 0; i < RPG; ++i) {
@@ -251,14 +253,29 @@ __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[g][e] *= corr;
         }
-#pragma unroll
-        for (int i = 0; i < RPG; ++i) {
+        // A place that has no row has the weight zero, and stays out, since 0 * inf is not zero: by a test per row behind a test for
+        // all, or, with eight heads, where that costs registers (122 -> 131 us), by zeroes. us per call, all rows added -> this: the
+        // decode step's sets, 32 heads on 8, bf16 8.6 -> 8.65, 16 sequences 24.6 -> 24.4; float32 8.7 -> 8.8 and 33.1 -> 31.5; long
+        // float32 ranges, 5000 rows 7.8 -> 8.1, 200001 45.4 -> 46.0, eight heads, 65536 rows 66.1 -> 68.3. (Zeroes in all of them, as
+        // soon as the rows have come: 5000 rows 8.9.)
+        auto add_row = [&](int i, bool zero) __attribute__((always_inline)) {
             float vv[8];
             row8_floats<DT>(vr[i], vv);
+            if (zero)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) vv[e] = rid[i] >= 0 ? vv[e] : 0.f;
 #pragma unroll
             for (int g = 0; g < NH; ++g)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) acc[g][e] = fmaf(p[g][i], vv[e], acc[g][e]);
+        };
+        if (NH == 8 ? __builtin_expect(all, 1) : all) {
+#pragma unroll
+            for (int i = 0; i < RPG; ++i) add_row(i, false);
+        } else {
+#pragma unroll
+            for (int i = 0; i < RPG; ++i)
+                if (NH == 8 || rid[i] >= 0) add_row(i, NH == 8);
         }
     };
     {
@@ -267,18 +284,21 @@ __device__ void attend_chunk(int tid, const void* q0, const void* Kh, const void
         int sub = 0;
         rows_of(sub, rid_a);
         fetch(rid_a, k_a, v_a);
-        if (n_sub == 1) {                     // the decode step's short sets: nothing to run ahead of
-            consume(rid_a, k_a, v_a);
+        if (!LONG) {                          // the decode step's short sets: nothing to run ahead of
+            bool all = true;
+#pragma unroll
+            for (int i = 0; i < RPG; ++i) all = all && rid_a[i] >= 0;
+            consume(__builtin_amdgcn_ballot_w64(!all) == 0ull, rid_a, k_a, v_a);
             sub = n_sub;
         }
         for (; sub < n_sub; sub += 2) {
             rows_of(sub + 1, rid_b);
             fetch(rid_b, k_b, v_b);
-            consume(rid_a, k_a, v_a);
+            consume(whole(sub), rid_a, k_a, v_a);
             if (sub + 1 >= n_sub) break;
             rows_of(sub + 2, rid_a);
             fetch(rid_a, k_a, v_a);
-            consume(rid_b, k_b, v_b);
+            consume(whole(sub + 1), rid_b, k_b, v_b);
         }
     }
     chunk_records<NH, COHERENT>(tid, m, l, acc, rec0, rec_stride, smem);
@@ -340,10 +360,10 @@ __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int64_t rv = chunk_row(src, rb + 4 * i + c);
-            t.vb[i] = load_row8_stream<RA_BF16>(Vh, rv >= 0 ? rv : 0, lane16);    // a missing row's weight is 0
+            t.vb[i] = load_row8_stream<RA_BF16>(Vh, rv >= 0 ? rv : 0, lane16);
         }
     };
-    auto consume = [&](const Tile& t) {
+    auto consume = [&](Tile& t) {
         at_f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -372,9 +392,12 @@ __device__ void attend_chunk_mfma(int tid, const void* q0, const void* Kh, const
             p[h] = z > -INFINITY ? __expf(z - m[h]) : 0.f;
             lpart[h] += p[h];
         }
+        // (rows that are missing: weight zero and, since 0 * inf is not, values of zero; 5000 rows of one head 8.0 -> 8.15 us)
+        const uint32_t have = (uint32_t)__builtin_amdgcn_ballot_w64(t.rk >= 0) & 0xffffu;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float vv[8];
+            if (have != 0xffffu) t.vb[i].a = (have >> (4 * i + c)) & 1u ? t.vb[i].a : make_uint4(0u, 0u, 0u, 0u);
             row8_floats<RA_BF16>(t.vb[i], vv);
 #pragma unroll
             for (int h = 0; h < NH; ++h) {

@@ -60,3 +60,47 @@ def test_infinite_values_in_the_last_rows(dtype, n_q, n_kv, deg, expand, ef, top
         _same(out[0, h].cpu().numpy(), ref, tol_for(dtype))
         assert lse_close(float(lse[0, h]), rl, tol_for(dtype))
     idx.free()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n_seq,n_q,n_kv,window,topk", [(1, 2, 2, 70, 9), (2, 32, 8, 500, 64), (1, 8, 1, 100, 130), (20, 32, 4, 640, 100),
+                                                        (1, 4, 1, 4100, 40), (1, 8, 1, 4100, 40)])
+def test_values_of_a_row_that_is_not_attended_to(n_seq, n_q, n_kv, window, topk, dtype):
+    """Places without a row, in the last chunk of a set, in a list padded with -1, and in a long range's last tile, read row 0: with
+    no sink it is in neither set, and the infinity and the NaN in its value row are in no result. One in a row that is attended to
+    is. Chunks of one head and of several, a long range's on the matrix cores and on the vector units."""
+    rng = np.random.default_rng(n_seq * n_q + topk)
+    N, lists = 5000, torch.full((n_seq, n_q, topk), -1, dtype=torch.int32)
+    K, V, q = (_small(rng, *s).to(dtype) for s in ((n_seq, n_kv, N, 128), (n_seq, n_kv, N, 128), (n_seq, n_q, 128)))
+    for s in range(n_seq):
+        for h in range(n_q):
+            n = topk - (h % 3)
+            lists[s, h, :n] = 1 + torch.from_numpy(rng.permutation(N - window - 1)[:n])
+    V[:, :, 0, 5] = np.inf
+    V[:, :, 0, 6] = np.nan
+    V[:, :, N - 1, 100] = -np.inf
+    idx = ra.ra_index_import(torch.full((n_seq * n_q, N, 1), -1, dtype=torch.int32), torch.zeros(n_seq * n_q, dtype=torch.int32),
+                             n_seq, n_q, n_kv)
+    for noalloc in (False, True) if n_seq * n_q * (window + topk) < 20000 else (False,):
+        out, lse = ra.ra_attend(q.to(DEV), idx, K.to(DEV), V.to(DEV), 0, window, lists.to(DEV), noalloc=noalloc)
+        for s, h in [(0, 0), (0, n_q - 1), (n_seq - 1, 1)]:
+            rows = np.concatenate([OA.static_ids(N, 0, window), lists[s, h][lists[s, h] >= 0].numpy()])
+            ref, rl = OA.partial_attention(to_np(q[s, h]), to_np(K[s, h * n_kv // n_q]), to_np(V[s, h * n_kv // n_q]), rows)
+            _same(out[s, h].cpu().numpy(), ref, tol_for(dtype))
+            assert lse_close(float(lse[s, h]), rl, tol_for(dtype))
+    idx.free()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n_q,n_kv", [(1, 1), (2, 1), (4, 1), (8, 1), (3, 1)])
+def test_full_attention_with_infinite_values(n_q, n_kv, dtype):
+    """Infinities in the first and the last of 4321 value rows (a last chunk with places that read row 0)."""
+    rng, N = np.random.default_rng(n_q), 4321
+    K, V, q = (_small(rng, *s).to(dtype) for s in ((1, n_kv, N, 128), (1, n_kv, N, 128), (1, n_q, 128)))
+    V[0, 0, 0, 9] = np.inf
+    V[0, 0, N - 1, 64] = -np.inf
+    out, lse = ra.ra_full_attention(q.to(DEV), K.to(DEV), V.to(DEV))
+    for h in range(n_q):
+        ref, rl = OA.full_attention(to_np(q[0, h]), to_np(K[0, 0]), to_np(V[0, 0]))
+        _same(out[0, h].cpu().numpy(), ref, tol_for(dtype))
+        assert lse_close(float(lse[0, h]), rl, tol_for(dtype))
