@@ -270,7 +270,7 @@ template <int DT> struct SeedHook {
     OffWords off;
     static constexpr bool kSeedShare = true;
     static constexpr bool kShareSteps = false;
-    // value rows
+    // value rows (where they start between two words, from the next one on: touch_line takes whole words, and any of a line will do)
     const char* V;
     static constexpr bool kValues = DT == RA_BF16;
     static constexpr int value_lines = DT == RA_BF16 ? 2 : 4;
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(T, SR_WAVES(KT, T)) void decode_kernel(
                                            s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
                                            lds_ids, roots, root_cap, kscale,
                                            SeedHook<DT>{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx,
-                                                    seed_parts > 0, off, Vh});
+                                                    seed_parts > 0, off, Vh + ((uintptr_t)Vh & 2)});
     }
 #ifdef SR_PHASE_CLOCKS
     const long long t_attn = clock64();

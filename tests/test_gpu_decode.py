@@ -1072,3 +1072,34 @@ def test_first_beam_of_a_start_set(dtype, deg, expand, ef, n_seeds):
         assert ids[0, h].tolist() == ref.tolist()
         assert st[0, h].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]]
     idx.free()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("seeds,ef,heads", [(1024, 256, 8), (2048, 300, 8), (700, 128, 4), (0, 128, 8)])
+def test_decode_step_of_views_at_odd_offsets(dtype, seeds, ef, heads):
+    """Queries, keys and values that start at any element of their storage (in bfloat16 also between two words): what aligned
+    copies give, bit for bit, with the start sets scored by workgroups of their own, and by the head."""
+    from paper_2409_10516_amd import binding as B
+    rng = np.random.default_rng(seeds + ef)
+    N, deg = 3000, 32
+    adj = rng.integers(0, N, size=(heads, N, deg)).astype(np.int32)
+    t = np.arange(N)
+    for j in (0, 1):
+        adj[:, :, j] = np.where(2 * t + 1 + j < N, 2 * t + 1 + j, -1)
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.zeros(heads, dtype=torch.int32), 1, heads, 2)
+    idx.configure(B.RA_CFG_SEEDS, seeds)
+    q, K, V = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)).to(dtype).to(DEV)
+               for s in ((1, heads, 128), (1, 2, N, 128), (1, 2, N, 128)))
+    want = ra.ra_decode_step(q, idx, K, V, 4, 50, 60, ef, 64)
+    for offset in (1, 3, 6):
+        views = []
+        for x in (q, K, V):
+            flat = torch.zeros(x.numel() + 8, dtype=dtype, device=DEV)
+            views.append(flat[offset:offset + x.numel()].view(x.shape))
+            views[-1].copy_(x)
+        for shares in (6, 0):
+            idx.configure(B.RA_CFG_SEED_SHARES, shares)
+            got = ra.ra_decode_step(views[0], idx, views[1], views[2], 4, 50, 60, ef, 64)
+            assert all(torch.equal(a, b) for a, b in zip(got, want)), (offset, shares)
+            assert idx.seed_shares_active == (seeds > 0 and shares > 0)
+    idx.free()
