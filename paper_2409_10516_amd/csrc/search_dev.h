@@ -56,11 +56,15 @@ enum { S_NCAND = 0, S_NKEEP = 1, S_NUNEXP = 2 };      // of the three words at C
 #define SR_PREFILTER_SLACK 64     // a step that keeps more than ef + this many candidates drops the hopeless ones first
 #define SR_PREFILTER_REGS 8       // ... when a thread can hold its share of them (nk <= 8 T)
 #define SR_START_REGS 8           // keys of a start set that a thread can hold
-#define SR_NARROW 16              // a merge of up to this many candidates takes one phase (half as many with 1024 threads)
-#define SR_DIRECT 64              // a merge of more candidates than this goes through buckets
+// A merge of up to SR_NARROW candidates takes one phase, with 1024 threads of up to twice as many; one of more than SR_DIRECT goes
+// through buckets. (Geometric means over settings of 32 heads of 32K keys. Up to 512 threads, 170 settings: limits 8 and 32 instead
+// of 16 +1.4 and -0.3 %. 1024 threads, 66 settings, beams of 384 to 2048: 24 and 64 instead of 32 +0.5 and +1.7 %; 8, with every
+// candidate compared with every entry, +7 %. Buckets from 33 and 129 candidates on: +1.8 and -0.7 %, up to 512 threads 0 and 0 %.)
+#define SR_NARROW 16
+#define SR_DIRECT 64
 #define SR_MERGE_REGS 2           // ... when a thread can hold its share of them
 #define SR_LIST_AT (T <= 512 ? 512 : T)       // words of cid in front of the new cells of a seed set's first picks
-#define SR_FRESH_CELLS 16         // a pick with more new cells than this has its whole row read, and so have all others
+#define SR_FRESH_CELLS 16         // a pick with more new cells than this has its whole row read, and so have all others (4, 64: the same times)
 
 typedef unsigned long long u64;
 
@@ -111,6 +115,11 @@ template <int V> struct sr_int { static constexpr int value = V; };      // a co
 
 __device__ __forceinline__ u64 make_key(float score, int id) {
     return ((u64)f32_ordered(score) << 32) | ((u64)(uint32_t)(0x7fffffff - id) << 1) | 1ull;
+}
+// what lane l holds
+__device__ __forceinline__ u64 lane_key(u64 k, int l) {
+    return (u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(k >> 32), l) << 32 |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)k, l);
 }
 __device__ __forceinline__ int key_id(u64 k) { return 0x7fffffff - (int)((uint32_t)k >> 1); }
 
@@ -1506,11 +1515,12 @@ __device__ __forceinline__ int run_search(
                 }
             }
         };
-        if (__builtin_expect(nk <= (T == 1024 ? SR_NARROW / 2 : SR_NARROW), 1)) {
+        constexpr int NARROW = T == 1024 ? 2 * SR_NARROW : SR_NARROW;
+        if (__builtin_expect(nk <= NARROW, 1)) {
             // ---- few candidates, one phase: 16 lanes find a candidate's place (its slot by a 16-way search, two or three
-            //      dependent reads; the candidates above it by one comparison per lane), and a beam entry is compared
-            //      with every candidate.
-            static_assert(SR_NARROW == 16, "a candidate per lane of a group");
+            //      dependent reads; the candidates above it by one or two comparisons per lane), and a beam entry is compared
+            //      with every candidate, or in a wide beam with those in the range of its wavefront's 64 entries.
+            static_assert(SR_NARROW == 16 && NARROW <= RA_WAVE, "a candidate or two per lane of a group, one per lane of a wavefront");
             auto count_group = [&](bool up) __attribute__((always_inline)) {         // lanes of the group of 16 that say so
                 const u64 m = __builtin_amdgcn_ballot_w64(up);
                 return __popc((lane & 32 ? (uint32_t)(m >> 32) : (uint32_t)m) >> (lane & 16) & 0xffffu);
@@ -1518,7 +1528,7 @@ __device__ __forceinline__ int run_search(
             for (int c0 = __builtin_amdgcn_readfirstlane((T / RA_WAVE - 1 - wv) * 4); c0 < nk; c0 += T / 16) {
                 // (the groups past the last candidate do what the last one's does)
                 const u64 k = ckey[min(c0 + (lane >> 4), nk - 1)];
-                const u64 other = ckey[lane16];
+                const u64 other = ckey[lane16], other2 = NARROW > 16 ? ckey[lane16 + 16] : 0ull;
                 int b = 0;
                 if (bn > 256) b = 256 * count_group(cur[min(lane16 * 256 + 255, ef - 1)] > k);
                 b += 16 * count_group(cur[min(b + lane16 * 16 + 15, ef - 1)] > k);
@@ -1527,7 +1537,8 @@ __device__ __forceinline__ int run_search(
                 const bool up = e > k;
                 b += count_group(up);
                 ub += count_group(up && (e & 1ull));
-                const int n = count_group(lane16 < nk && other > k);
+                int n = count_group(lane16 < nk && other > k);
+                if (NARROW > 16 && nk > 16) n += count_group(lane16 + 16 < nk && other2 > k);
                 place(k, b + n, n + ub, sr_int<0>{});
                 touch_row(key_id(k));
             }
@@ -1536,12 +1547,24 @@ __device__ __forceinline__ int run_search(
                 const u64 k = cur[ec];
                 const int ub = unexpanded_above(ec);
                 int c = 0;
-                for (int i0 = 0; i0 < nk; i0 += 8) {
-                    u64 v[8];
+                if constexpr (T == 1024) {
+                    // (A candidate per lane; those above all 64 entries count for each, those among them are compared in turn. us per
+                    // layer, every candidate compared with every entry and, behind the eighth, two phases -> this: 1024 / 12 nodes of
+                    // degree 32 per step 230 -> 193, 1500 / 16 280 -> 237, 2048 / 8 719 -> 589, float32 2048 / 16 418 -> 348.)
+                    const u64 own = lane < nk ? ckey[lane] : 0ull;
+                    const u64 first = lane_key(k, 0), last = lane_key(k, RA_WAVE - 1);
+                    const u64 above = __builtin_amdgcn_ballot_w64(own > first);
+                    c = __popcll(above);
+                    for (u64 among = __builtin_amdgcn_ballot_w64(own > last) & ~above; among; among &= among - 1ull)
+                        c += lane_key(own, __builtin_ctzll(among)) > k ? 1 : 0;
+                } else {
+                    for (int i0 = 0; i0 < nk; i0 += 8) {
+                        u64 v[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = ckey[i0 + u];
+                        for (int u = 0; u < 8; ++u) v[u] = ckey[i0 + u];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) c += v[u] > k ? 1 : 0;
+                        for (int u = 0; u < 8; ++u) c += v[u] > k ? 1 : 0;
+                    }
                 }
                 place_entry(e, k, ub, c);
             }

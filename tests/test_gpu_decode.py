@@ -1103,3 +1103,43 @@ def test_decode_step_of_views_at_odd_offsets(dtype, seeds, ef, heads):
             assert all(torch.equal(a, b) for a, b in zip(got, want)), (offset, shares)
             assert idx.seed_shares_active == (seeds > 0 and shares > 0)
     idx.free()
+
+
+def _kept_per_step(q, K, adj, entry, ef, expand):
+    """How many candidates each step of the walk keeps: all new ones while the beam is not full, then those better than its worst
+    entry. (Score descending, id ascending; for integer inputs.)"""
+    score = K @ q
+    order = lambda i: (-score[i], i)
+    beam, seen, done, kept = [entry], {entry}, set(), []
+    while True:
+        picks = [i for i in beam if i not in done][:expand]
+        if not picks:
+            return kept
+        done.update(picks)
+        new = sorted({int(j) for i in picks for j in adj[i] if 0 <= j < len(K)} - seen, key=order)
+        seen.update(new)
+        new = [j for j in new if len(beam) < ef or order(j) < order(beam[-1])]
+        kept.append(len(new))
+        beam = sorted(beam + new, key=order)[:ef]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("ef,expand,deg", [(300, 8, 33), (513, 9, 31), (1100, 5, 52), (2048, 3, 24)])
+def test_merges_of_few_candidates_into_wide_beams(ef, expand, deg, dtype):
+    """Workgroups of 1024 threads: merges of up to 16, of 17 to 32, of up to 64 and of more candidates, into beams of every length
+    up to the widest; many scores tie. Integer keys: the oracle's ids and counters."""
+    rng, N = np.random.default_rng(ef), 6000
+    K = rng.integers(-3, 4, size=(N, 128)).astype(np.float32)
+    adj = rng.integers(0, N, size=(1, N, deg)).astype(np.int32)
+    q = rng.integers(-3, 4, size=128).astype(np.float32)
+    kept = _kept_per_step(q, K, adj[0], 11, ef, expand)
+    assert all(any(lo <= n <= hi for n in kept) for lo, hi in ((1, 8), (9, 16), (17, 32), (33, 64), (65, 999)))
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.tensor([11], dtype=torch.int32), 1, 1, 1)
+    Kd, qd = torch.from_numpy(K)[None, None].to(dtype).to(DEV), torch.from_numpy(q)[None, None].to(dtype).to(DEV)
+    ids, st = ra.ra_search(qd, idx, Kd, 4, 20, 200, ef, expand)
+    _, _, ids_d, st_d = ra.ra_decode_step(qd, idx, Kd, Kd, 4, 20, 200, ef, expand)
+    assert torch.equal(ids, ids_d) and torch.equal(st, st_d)
+    ref, rst = OS.greedy_search(q, K, adj[0], 11, ef, 200, expand, exclude=OA.static_ids(N, 4, 20))
+    assert ids[0, 0].tolist() == ref.tolist()
+    assert st[0, 0].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]]
+    idx.free()
