@@ -711,8 +711,10 @@ __device__ __forceinline__ Cand<MODE> cand_lane(const Cand<MODE>& v, int from) {
     return o;
 }
 // Lanes that keep the better one in the exchange with lane ^ j of runs of k lanes (descending and ascending in turn, the first as
-// `desc` says), as a constant of the scalar unit: as comparisons of the lane's number, the compiler keeps all 28 of a row's over
-// the loop, in more scalar registers than there are.
+// `desc` says). For packed candidates, whose row's other instructions are few, as a constant of the scalar unit: as comparisons of the
+// lane's number, the compiler keeps all 28 of a row's over the loop, in more scalar registers than there are. (In the kernels of
+// the other forms, constants, and the test below for the first 64, make the walks over a key's lists 1 to 11 % longer: 2 graphs of 8000 keys
+// in 300000 lists of 48 5.20 -> 5.58 ms.)
 constexpr u64 cand_keepers(int k, int j, bool desc) {
     u64 m = 0ull;
     for (int l = 0; l < 64; ++l)
@@ -722,11 +724,11 @@ constexpr u64 cand_keepers(int k, int j, bool desc) {
 // 64 candidates, one per lane, into rank order (DESC: lane 0 the best; else lane 63 the best)
 template <bool DESC, int MODE>
 __device__ __forceinline__ Cand<MODE> cand_sort64(Cand<MODE> v, int lane) {
-#define PJ_STEP(K_, J_)                                                                     \
-    do {                                                                                    \
-        constexpr u64 keepers = cand_keepers(K_, J_, DESC);                                 \
-        v = cand_exchange<J_>(v, __builtin_amdgcn_inverse_ballot_w64(keepers), lane);       \
-    } while (0);
+#define PJ_STEP(K_, J_)                                                                                              \
+    if constexpr (MODE == CAND_PACKED)                                                                              \
+        v = cand_exchange<J_>(v, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(K_, J_, DESC)), lane);             \
+    else                                                                                                            \
+        v = cand_exchange<J_>(v, (((lane & J_) == 0) == ((lane & K_) == 0)) == DESC, lane);
     PJ_STEP(2, 1)
     PJ_STEP(4, 2) PJ_STEP(4, 1)
     PJ_STEP(8, 4) PJ_STEP(8, 2) PJ_STEP(8, 1)
@@ -740,12 +742,11 @@ __device__ __forceinline__ Cand<MODE> cand_sort64(Cand<MODE> v, int lane) {
 template <int MODE>
 __device__ __forceinline__ Cand<MODE> cand_merge64(Cand<MODE> best, const Cand<MODE>& v, int lane) {
     if (cand_before(v, best)) best = v;                // bitonic: the best 64 of the 128
-    best = cand_exchange<32>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 32, true)), lane);
-    best = cand_exchange<16>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 16, true)), lane);
-    best = cand_exchange<8>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 8, true)), lane);
-    best = cand_exchange<4>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 4, true)), lane);
-    best = cand_exchange<2>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 2, true)), lane);
-    best = cand_exchange<1>(best, __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, 1, true)), lane);
+#define PJ_STEP(J_)                                                                                                  \
+    best = cand_exchange<J_>(best, MODE == CAND_PACKED ? __builtin_amdgcn_inverse_ballot_w64(cand_keepers(64, J_, true)) \
+                                                       : (lane & J_) == 0, lane);
+    PJ_STEP(32) PJ_STEP(16) PJ_STEP(8) PJ_STEP(4) PJ_STEP(2) PJ_STEP(1)
+#undef PJ_STEP
     return best;
 }
 
@@ -807,7 +808,7 @@ __device__ __forceinline__ void select_best(Cand<MODE>& best, int n, uint32_t pa
             if constexpr (MODE == CAND_WIDE) last.c = (uint32_t)__builtin_amdgcn_readlane((int)best.c, 63);
             if (__ballot(cand_before(v, last)) == 0ull) return;            // nothing here makes the 64
             v = cand_sort64<false>(v, lane);
-            if (none) {                                      // (uniform) the first of them: the same, best first
+            if (MODE == CAND_PACKED && none) {               // (uniform) the first of them: the same, best first
                 none = false;
                 best = cand_lane(v, 63 - lane);
             } else {
