@@ -273,7 +273,7 @@ template <int DT> struct SeedHook {
     // value rows (where they start between two words, from the next one on: touch_line takes whole words, and any of a line will do)
     const char* V;
     static constexpr bool kValues = DT == RA_BF16;
-    static constexpr int value_lines = DT == RA_BF16 ? 2 : 4;
+    static constexpr int value_lines = 2;
     __device__ __forceinline__ void touch_value(int id, int line, uint32_t lds) const {
         touch_line(V + ((size_t)(uint32_t)id * value_lines + line) * 128, lds);
     }

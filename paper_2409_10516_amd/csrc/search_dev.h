@@ -201,11 +201,6 @@ __device__ __forceinline__ float dpp_f32(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
-template <int CTRL>
-__device__ __forceinline__ int dpp_i32(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
-}
-
 // The fixed-order inner product described in the file header, in two parts: a lane's share (its 8
 // dimensions, summed left to right), then the pairwise tree over the 16 lanes of the group.
 typedef __bf16 sr_bf16x2 __attribute__((ext_vector_type(2)));
@@ -334,6 +329,21 @@ __device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
     min_max_step<0x142, 0xA>(lo, hi);        // lane 15 of a row into the next one, then lane 31 to the upper half
     min_max_step<0x143, 0xC>(lo, hi);
 }
+
+// 256 equal-width bins of scores between the smallest and the largest: bin = (score - lowest) * 255 / (highest - lowest), truncated.
+// Every operation is monotone in the score, so a larger score never lands in a lower bin. Non-finite scores (from non-finite inputs)
+// leave the factor at zero: one bin.
+struct ScoreBins {
+    float lowest, to_bin;
+    __device__ __forceinline__ ScoreBins(uint32_t lo, uint32_t hi) : lowest(f32_from_ordered(lo)) {
+        const float width = f32_from_ordered(hi) - lowest;
+        to_bin = width > 0.f && width < INFINITY ? 255.0f / width : 0.f;
+    }
+    __device__ __forceinline__ int bin(u64 key) const {
+        const float b = (f32_from_ordered((uint32_t)(key >> 32)) - lowest) * to_bin;
+        return b >= 255.f ? 255 : b > 0.f ? (int)b : 0;
+    }
+};
 
 // A head's row of the seed sets: [0] the number of ids, [1] 0, then places for n ids, then for n masks of 32 or, where the degree is
 // above 32, 64 bits (lower half first): of the cells of the id's adjacency row, those whose neighbour is no member of the set.
@@ -806,8 +816,8 @@ __device__ __forceinline__ int run_search(
 #ifdef SR_WAVE_CLOCKS
     if (head == 0 && tid == 0) sr_wave_ticks[1] = wall_clock64();
 #endif
-    // with masks: new cells (pick, cell) of the first picks, up to T of them, and the places in the seed set of the survivors of the
-    // pre-filter, behind what that and a step's claims of that few cells use of cid
+    // with masks: new cells (pick, cell) of the first picks, up to T of them, and the places in the seed set of the keys
+    // that the first beam is made of, behind what that and a step's claims of that few cells use of cid
     static_assert(SR_LIST_AT >= 512 && SR_LIST_AT >= T && RA_MAX_EXPAND * 64 <= 65536, "a pick and a cell of its row in 16 bits");
     uint16_t* fresh_cells = reinterpret_cast<uint16_t*>(cid + SR_LIST_AT);
     uint16_t* seed_at = fresh_cells + T;
@@ -834,7 +844,7 @@ __device__ __forceinline__ int run_search(
         if (tid == 0) {
             urank[0] = 0;
             for (int i = 0; i < 3; ++i) cc[i] = cc_nxt[i] = 0;
-            ctr[C_LO] = -1;                  // as unsigned: the largest value; see the pre-filter below
+            ctr[C_LO] = -1;                  // as unsigned: the largest value; see the first beam below
             ctr[C_HI] = 0;
             ctr[C_MISSED] = 0;
             wtot[0] = 0;                     // (new cells of the first picks; the results use it otherwise)
@@ -883,8 +893,8 @@ __device__ __forceinline__ int run_search(
     if (head == 0 && tid == 0) sr_wave_ticks[2] = wall_clock64();      // claims made
 #endif
     // The workers' answers to the last message: the keys go to ckey. A worker's are taken by up to 64 threads, of one wavefront (the word
-    // that says how many there are is read by all of them before one zeroes it), each asking for a key together with that word. With the extremes of the ordered score bits.
-    auto collect = [&](uint32_t& lo, uint32_t& hi) __attribute__((always_inline)) {
+    // that says how many there are is read by all of them before one zeroes it), each asking for a key together with that word. got(score): the ordered score bits of a key that has come.
+    auto collect = [&](auto got) __attribute__((always_inline)) {
         if constexpr (Hook::kShareSteps) {
             const int spin = hook.spin, per_log2 = min((T == 1024 ? 10 : 9) - hook.parts_log2, 6);
             const int per = 1 << per_log2, sub = tid & (per - 1);
@@ -921,9 +931,7 @@ __device__ __forceinline__ int run_search(
                 if (k != 0ull) {
                     xwg_store(a + 1 + i, 0ull);
                     ckey[at] = k;
-                    const uint32_t so = (uint32_t)(k >> 32);
-                    lo = min(lo, so);
-                    hi = max(hi, so);
+                    got((uint32_t)(k >> 32));
                 }
             }
         }
@@ -940,7 +948,10 @@ __device__ __forceinline__ int run_search(
     };
     if constexpr (Hook::kShareSteps) {
         uint32_t lo = 0xffffffffu, hi = 0u;
-        collect(lo, hi);
+        collect([&](uint32_t score) __attribute__((always_inline)) {
+            lo = min(lo, score);
+            hi = max(hi, score);
+        });
         if (fill) {
             wave_min_max(lo, hi);
             if (lane == RA_WAVE - 1) {
@@ -954,7 +965,7 @@ __device__ __forceinline__ int run_search(
         //      memory for 1024 threads). The beam is empty, so every key is kept; the first
         //      n_first of a root set enter as expanded.
         constexpr int SEED_ROWS = KT == RA_F32 ? SR_UNROLL : 16;
-        uint32_t lo = 0xffffffffu, hi = 0u;                  // of the ordered score bits (see the pre-filter)
+        uint32_t lo = 0xffffffffu, hi = 0u;                  // of the ordered score bits (see the first beam)
         // R rows per 16-lane group with no branch between them: the ids leave LDS in one batch, the
         // rows are all requested before the first is scored, and each is scored as it arrives
         auto score_rows = [&](auto rows_c, int c0) __attribute__((always_inline)) {
@@ -1092,16 +1103,7 @@ __device__ __forceinline__ int run_search(
         if (bins && !missed) {
             if (tid < 256) cid[tid] = 0;
             __syncthreads();
-            const float lo_f = f32_from_ordered((uint32_t)ctr[C_LO]);
-            const float width = f32_from_ordered((uint32_t)ctr[C_HI]) - lo_f;
-            // bin = (score - lowest) * 255 / (highest - lowest), truncated: every operation is
-            // monotone in the score, so a larger score never lands in a lower bin. Non-finite
-            // scores (from non-finite inputs) leave the factor at zero: one bin, everything survives.
-            const float to_bin = width > 0.f && width < INFINITY ? 255.0f / width : 0.f;
-            auto bin_of = [&](u64 k) __attribute__((always_inline)) {
-                const float b = (f32_from_ordered((uint32_t)(k >> 32)) - lo_f) * to_bin;
-                return b >= 255.f ? 255 : b > 0.f ? (int)b : 0;
-            };
+            const ScoreBins score_bins((uint32_t)ctr[C_LO], (uint32_t)ctr[C_HI]);
             u64 mine[SR_START_REGS];
             int bin[SR_START_REGS];          // a key's, and from bit 8 its number in it
 #pragma unroll
@@ -1110,7 +1112,7 @@ __device__ __forceinline__ int run_search(
 #pragma unroll
             for (int r = 0; r < SR_START_REGS; ++r) {
                 if (r * T >= n_root) break;
-                bin[r] = bin_of(mine[r]);
+                bin[r] = score_bins.bin(mine[r]);
                 if (r * T + tid < n_root)
                     bin[r] |= (atomicAdd(&cid[bin[r]], 1 + ((int)(~(uint32_t)mine[r] & 1u) << 16)) & 0xffff) << 8;
             }
@@ -1142,7 +1144,7 @@ __device__ __forceinline__ int run_search(
             __syncthreads();
             for (int p = tid; p < nsurv; p += T) {
                 const u64 k = ckey[p];
-                const int kb = bin_of(k), above = cid[256 + kb], bs = above & 0xffff, n = cid[kb] & 0xffff;
+                const int kb = score_bins.bin(k), above = cid[256 + kb], bs = above & 0xffff, n = cid[kb] & 0xffff;
                 int pos = bs, ur = bs - (above >> 16), j0 = 0;
                 // (past the bucket's end its last key again, taken off below)
                 do {
@@ -1236,8 +1238,7 @@ __device__ __forceinline__ int run_search(
         if constexpr (Hook::kShareSteps) {
             // ---- the workers claim and score; their answers are waited for
             post(np, bn == ef ? (cur[bn - 1] >> 1) : 0ull);
-            uint32_t lo = 0xffffffffu, hi = 0u;
-            collect(lo, hi);
+            collect([](uint32_t) {});
             __syncthreads();
             if (ctr[C_MISSED]) break;
             n_visited += __builtin_amdgcn_readfirstlane(cc[S_NCAND]);
@@ -1386,14 +1387,11 @@ __device__ __forceinline__ int run_search(
             }
             if (tid < 256) cid[tid] = 0;
             __syncthreads();
-            const float lo_f = f32_from_ordered((uint32_t)ctr[C_LO]);        // (bins as of a start set)
-            const float width = f32_from_ordered((uint32_t)ctr[C_HI]) - lo_f;
-            const float to_bin = width > 0.f && width < INFINITY ? 255.0f / width : 0.f;
+            const ScoreBins score_bins((uint32_t)ctr[C_LO], (uint32_t)ctr[C_HI]);
             int bin[SR_PREFILTER_REGS];
 #pragma unroll
             for (int r = 0; r < SR_PREFILTER_REGS; ++r) {
-                const float b = (f32_from_ordered((uint32_t)(mine[r] >> 32)) - lo_f) * to_bin;
-                bin[r] = b >= 255.f ? 255 : b > 0.f ? (int)b : 0;
+                bin[r] = score_bins.bin(mine[r]);
                 if (r * T + tid < nk) atomicAdd(&cid[bin[r]], 1);
             }
             __syncthreads();
