@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import paper_2409_10516_amd as ra
-from oracle import attention as OA
+from oracle import attention as OA, search as OS
 from paper_2409_10516_amd import binding as B
 from tests.util import out_close, lse_close, to_np, tol_for
 
@@ -104,3 +104,89 @@ def test_full_attention_with_infinite_values(n_q, n_kv, dtype):
         ref, rl = OA.full_attention(to_np(q[0, h]), to_np(K[0, 0]), to_np(V[0, 0]))
         _same(out[0, h].cpu().numpy(), ref, tol_for(dtype))
         assert lse_close(float(lse[0, h]), rl, tol_for(dtype))
+
+
+def _ranked(q, rows):
+    """Inner products whose infinities the oracle's walk can subtract: beyond every finite one, equal among themselves."""
+    with np.errstate(invalid="ignore"):
+        s = np.asarray(rows, np.float64) @ np.asarray(q, np.float64)
+    assert not np.isnan(s).any()
+    return np.clip(s, -1e6, 1e6)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("plus,minus", [(0.01, 0.0), (0.0, 0.3), (0.3, 0.3), (1.0, 0.0), (0.0, 1.0)])
+@pytest.mark.parametrize("deg,expand,ef,n_seeds,heads", [
+    (8, 1, 40, 0, 1), (32, 40, 64, 0, 1), (32, 40, 1100, 0, 1), (33, 7, 16, 0, 1), (32, 64, 256, 2048, 1), (8, 64, 16, 500, 1),
+    (8, 20, 100, 64, 1), (16, 32, 100, 400, 400), (64, 9, 300, 0, 1)])
+def test_walks_over_infinite_scores(deg, expand, ef, n_seeds, heads, plus, minus, dtype):
+    """Keys whose score is an infinity, some, many and all of them: in start sets (their bins have no width then), in steps that
+    keep few, many and more candidates than the beam holds. They rank above and below all others, ties by id: the oracle's
+    walk. The attention over what is found: minus infinity has no weight."""
+    rng = np.random.default_rng(deg + ef + int(10 * plus) + int(100 * minus))
+    N = 3000
+    adj = rng.integers(0, N, size=(1, N, deg)).astype(np.int32)
+    t = np.arange(N)
+    for j in (0, 1):
+        adj[:, :, j] = np.where(2 * t + 1 + j < N, 2 * t + 1 + j, -1)
+    K = rng.integers(-3, 4, size=(N, 128)).astype(np.float32)
+    q = rng.integers(1, 4, size=128).astype(np.float32)
+    kind = rng.random(N)
+    K[kind < plus, 17] = np.inf
+    K[kind > 1 - minus, 99] = -np.inf
+    K[(kind < plus) & (kind > 1 - minus), 99] = 0
+    V = rng.standard_normal((N, 128)).astype(np.float32)
+    idx = ra.ra_index_import(torch.from_numpy(np.repeat(adj, heads, 0)), torch.zeros(heads, dtype=torch.int32), 1, heads, 1)
+    idx.configure(B.RA_CFG_SEEDS, n_seeds)
+    Kd, Vd = (torch.from_numpy(x)[None, None].to(dtype).to(DEV) for x in (K, V))
+    qd = torch.from_numpy(q).to(dtype).repeat(1, heads, 1).to(DEV)
+    topk = min(ef, 50)
+    ids, st = ra.ra_search(qd, idx, Kd, 4, 20, topk, ef, expand)
+    out, lse, ids_d, st_d = ra.ra_decode_step(qd, idx, Kd, Vd, 4, 20, topk, ef, expand)
+    assert torch.equal(ids, ids_d) and torch.equal(st, st_d)
+    seeds = OS.backbone_seeds(adj[0], 0, n_seeds) if n_seeds else None
+    W = OA.static_ids(N, 4, 20)
+    ref, rst = OS.greedy_search(q, K, adj[0], 0, ef, topk, expand, exclude=W, seeds=seeds, score_fn=_ranked)
+    for h in (0, heads - 1):
+        assert ids[0, h].tolist() == ref.tolist()
+        assert st[0, h].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]]
+    rows = np.concatenate([W, ref[ref >= 0]])
+    scores = _ranked(q, K[rows])
+    if scores.max() < 1e6 and scores.max() > -1e6:
+        Vn = to_np(Vd[0, 0])
+        ro, rl = OA.partial_attention(q, np.where(np.isinf(K), -1e30, K), Vn, rows)
+        assert out_close(out[0, 0].cpu().numpy(), ro, tol_for(dtype)) and lse_close(float(lse[0, 0]), rl, tol_for(dtype))
+    idx.free()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("deg,expand,ef,n_seeds", [(8, 1, 40, 0), (32, 40, 64, 0), (32, 64, 256, 2048), (64, 9, 300, 0), (8, 20, 100, 64)])
+@pytest.mark.parametrize("where", ["some keys", "all keys", "query"])
+def test_walks_over_scores_that_are_no_numbers(where, deg, expand, ef, n_seeds, dtype):
+    """NaN in keys or in the query: the walk ends, counts what it has seen, and returns ids that are distinct, in range and
+    outside the static set."""
+    rng = np.random.default_rng(deg + ef)
+    N = 2500
+    adj = rng.integers(0, N, size=(1, N, deg)).astype(np.int32)
+    t = np.arange(N)
+    for j in (0, 1):
+        adj[:, :, j] = np.where(2 * t + 1 + j < N, 2 * t + 1 + j, -1)
+    K = rng.integers(-3, 4, size=(N, 128)).astype(np.float32)
+    q = rng.integers(-3, 4, size=128).astype(np.float32)
+    if where == "query":
+        q[5] = np.nan
+    else:
+        K[:: 1 if where == "all keys" else 7, 60] = np.nan
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.zeros(1, dtype=torch.int32), 1, 1, 1)
+    idx.configure(B.RA_CFG_SEEDS, n_seeds)
+    Kd, qd = torch.from_numpy(K)[None, None].to(dtype).to(DEV), torch.from_numpy(q)[None, None].to(dtype).to(DEV)
+    topk = min(ef, 50)
+    ids, st = ra.ra_search(qd, idx, Kd, 4, 20, topk, ef, expand)
+    _, _, ids_d, st_d = ra.ra_decode_step(qd, idx, Kd, Kd, 4, 20, topk, ef, expand)
+    assert torch.equal(ids, ids_d) and torch.equal(st, st_d)
+    got, (visited, expanded, iters, returned) = ids[0, 0].cpu().numpy(), st[0, 0].tolist()
+    real = got[got >= 0]
+    assert len(real) == returned and len(set(real.tolist())) == returned and (got[returned:] == -1).all()
+    assert not set(real.tolist()) & set(OA.static_ids(N, 4, 20).tolist()) and real.max(initial=0) < N
+    assert ef <= visited <= N and ef <= expanded <= visited and iters >= 1
+    idx.free()
