@@ -1143,3 +1143,65 @@ def test_merges_of_few_candidates_into_wide_beams(ef, expand, deg, dtype):
     assert ids[0, 0].tolist() == ref.tolist()
     assert st[0, 0].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]]
     idx.free()
+
+
+@pytest.mark.parametrize("ef,expand,deg,heads", [(16, 5, 64, 1), (64, 9, 60, 1), (300, 16, 64, 1), (16, 8, 33, 400)])
+def test_steps_that_keep_far_more_than_the_beam_holds(ef, expand, deg, heads):
+    """A step, not a start set, whose kept candidates outnumber the beam by more than 64: all but the best are dropped ahead of
+    the merge. Keys that lie farther from the entry point score higher, so that nearly all of a step's are kept, with crowds of equal
+    scores. Workgroups of 512, 1024 and 256 threads."""
+    rng, N = np.random.default_rng(ef + deg), 1200
+    level = np.minimum(np.arange(N) // 40, 9)
+    adj = np.stack([rng.permutation(np.flatnonzero(level >= min(level[i] + 1, 9)))[:deg] for i in range(N)]).astype(np.int32)
+    K = rng.integers(-1, 2, size=(N, 128)).astype(np.float32)
+    K[:, 0] = 3 * level + 3
+    q = rng.integers(-1, 2, size=128).astype(np.float32)
+    q[0] = 60.0
+    assert expand < deg and expand * deg >= 256                  # (no root set is listed for so few nodes per step)
+    assert max(_kept_per_step(q, K, adj, 7, ef, expand)) > ef + 64
+    idx = ra.ra_index_import(torch.from_numpy(np.repeat(adj[None], heads, 0)), torch.full((heads,), 7, dtype=torch.int32), 1, heads, 1)
+    Kd = torch.from_numpy(K)[None, None].bfloat16().to(DEV)
+    qd = torch.from_numpy(q).bfloat16().repeat(1, heads, 1).to(DEV)
+    topk = min(ef, 40)
+    ids, st = ra.ra_search(qd, idx, Kd, 4, 20, topk, ef, expand)
+    _, _, ids_d, st_d = ra.ra_decode_step(qd, idx, Kd, Kd, 4, 20, topk, ef, expand)
+    assert torch.equal(ids, ids_d) and torch.equal(st, st_d)
+    ref, rst = OS.greedy_search(q, K, adj, 7, ef, topk, expand, exclude=OA.static_ids(N, 4, 20))
+    for h in (0, heads - 1):
+        assert ids[0, h].tolist() == ref.tolist()
+        assert st[0, h].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]]
+    idx.free()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n_seeds,deg,expand,ef", [
+    (64, 8, 64, 100), (65, 8, 63, 100), (65, 8, 64, 100), (65, 7, 73, 100), (300, 32, 20, 200), (512, 32, 16, 200),
+    (512, 32, 32, 200), (513, 32, 33, 200), (1000, 40, 64, 200), (2048, 32, 64, 300), (0, 24, 25, 48), (0, 24, 24, 48)])
+def test_start_sets_at_the_limits_of_their_order(dtype, n_seeds, deg, expand, ef):
+    """Start sets of 64 and 65 keys (counted, and ordered through bins), steps of 504 to 512 cells (bins from 512 on), sets with room
+    for their masks and the list of new cells and without, a root set that fits its step and one that does not. Scores that tie in
+    crowds, and one key far above the others, which leaves these in few bins. Integer keys: the oracle's ids and counters."""
+    from paper_2409_10516_amd import binding as B
+    rng = np.random.default_rng(n_seeds + deg + expand)
+    N = 4000
+    adj = rng.integers(0, N, size=(1, N, deg)).astype(np.int32)
+    t = np.arange(N)
+    for j in (0, 1):
+        adj[:, :, j] = np.where(2 * t + 1 + j < N, 2 * t + 1 + j, -1)
+    adj[adj == t[None, :, None]] = -1
+    q = rng.integers(-3, 4, size=(1, 1, 128)).astype(np.float32)
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.zeros(1, dtype=torch.int32), 1, 1, 1)
+    idx.configure(B.RA_CFG_SEEDS, n_seeds)
+    for far in (1, 500):
+        K = rng.integers(-3, 4, size=(60, 128))[rng.integers(0, 60, size=N)].astype(np.float32)
+        K[1] = far * np.sign(q[0, 0])
+        Kd, qd = torch.from_numpy(K)[None, None].to(dtype).to(DEV), torch.from_numpy(q).to(dtype).to(DEV)
+        K = to_np(Kd[0, 0])
+        ids, st = ra.ra_search(qd, idx, Kd, 4, 20, 40, ef, expand)
+        _, _, ids_d, st_d = ra.ra_decode_step(qd, idx, Kd, Kd, 4, 20, 40, ef, expand)
+        assert torch.equal(ids, ids_d) and torch.equal(st, st_d)
+        seeds = OS.backbone_seeds(adj[0], 0, n_seeds) if n_seeds else None
+        ref, rst = OS.greedy_search(q[0, 0], K, adj[0], 0, ef, 40, expand, seeds=seeds, exclude=OA.static_ids(N, 4, 20))
+        assert ids[0, 0].tolist() == ref.tolist(), far
+        assert st[0, 0].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]], far
+    idx.free()

@@ -178,3 +178,24 @@ def test_quantize_keys_of_any_number_and_alignment(dtype, shape, offset):
         for h in range(0, shape[1], 97 if shape[1] > 10 else 1):
             k8, sc = OQ.quantize_keys(K[s, h].float().numpy())
             assert np.array_equal(scale[s, h].cpu().numpy(), sc) and np.array_equal(K8[s, h].cpu().numpy(), k8)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,offset", [(127, 0), (1025, 0), (130, 1)])
+def test_halves_round_to_even(dtype, rows, offset):
+    """Quotients halfway between two whole numbers: columns whose largest value is 127 have a scale of one and
+    hold +-0.5, 1.5, ... 126.5 (exact in both types). Wide loads and keys that are not 16-byte aligned."""
+    n = torch.arange(rows)
+    col = ((n % 127) + 0.5) * (1 - 2 * (n % 2))
+    K = torch.stack([torch.roll(col, c) for c in range(128)], dim=1)
+    K[0] = 127 * (1 - 2 * (torch.arange(128) % 2)).float()
+    x = K.numpy().astype(np.float32)
+    away = np.sign(x) * np.floor(np.abs(x) + 0.5)
+    assert np.array_equal(K.to(dtype).float().numpy(), x) and (np.rint(x) != away).any(axis=0).all()
+    flat = torch.zeros(rows * 128 + 8, dtype=dtype, device=DEV)
+    view = flat[offset:offset + rows * 128].view(1, 1, rows, 128)
+    view.copy_(K.to(dtype)[None, None])
+    K8, scale = ra.ra_quantize_keys(view)
+    k8, sc = OQ.quantize_keys(x)
+    assert (sc == 1).all() and np.array_equal(scale[0, 0].cpu().numpy(), sc)
+    assert np.array_equal(K8[0, 0].cpu().numpy(), k8) and np.array_equal(k8, np.clip(np.rint(x), -127, 127))
