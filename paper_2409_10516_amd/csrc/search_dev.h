@@ -1703,24 +1703,24 @@ __device__ __forceinline__ int run_search(
 // Threads per search, of a launch of `heads` searches whose steps read up to `cells` adjacency cells. Merges
 // and barriers, which make up a narrow walk's steps, go faster with fewer threads; gathers and merges of wide
 // beams with more; and where searches outnumber the compute units (256), several small workgroups share one.
-// Measured on the fused launch (us per layer, 32 searches over 128K keys unless said; start sets of 1024
-// where a step has 1024 cells or more):
-//   ef <= 256, up to 384 searches: 512 threads. ef 256, 2048 cells: 26.0 (1024 threads 29.3, 256 threads 32.4);
-//     128 searches of 32K keys 28.8 (32.5, 33.9), 384 of them 44.0 (64.5, 45.1).
-//   ef <= 256, more searches: 256 threads. 512 searches of 32K keys, ef 128: 44.8 (512 threads 50.9), ef 256: 54.6 (58.3).
-//   At most 64 cells and 384 searches (one node per step, mostly): one size down. Degree 32, ef 128: 180 with 256
-//     threads (512: 191), ef 48: 78 (84); ef 512: 902 with 512 (1024: 989, 256: 923), ef 1024: 2134 (2691), ef 2048: 5521
-//     (6167); degree 64: ef 1024: 2191 (2801), ef 2048: 5898 (6956). Over 48 cells 512 threads: degree 64, ef 256: 369 (256: 402).
-//   ef 257 .. 1024 and at most 256 cells: 512. Four nodes of degree 32, ef 1024: 604 (1024: 670); eight: 329 (342), ef 300: 86 (93).
-//   ef 257 .. 1024 and more cells: 1024. ef 1024, 2048 cells: 123 (512: 137); ef 512: 39.5 (40.9).
+// Measured on the fused launch (us per layer, 32 searches over 128K keys of degree 32 unless said; start sets of 1024
+// where a step has 1024 cells or more; 256 / 512 / 1024 threads):
+//   ef <= 256, up to 384 searches: 512 threads. ef 256, 2048 cells: 30.6 / 24.5 / 24.8, 256 cells 70.9 / 63.5 / 69.2; ef 128, 2048
+//     cells 22.9 / 18.0 / 18.8; 128 searches of 32K keys, ef 256 29.5 / 24.8 / 26.0, 384 of them 38.1 / 38.7 / 52.6.
+//   ef <= 256, more searches: 256 threads. 512 searches of 32K keys, ef 128: 40.8 / 47.6 / 63.6, ef 256: 47.0 / 51.7 / 70.1.
+//   At most 64 cells and 384 searches (one node per step, mostly): one size down. ef 48: 66.9 / 68.2 / 79.3, ef 128: 159.7 / 161.0 /
+//     181.1; ef 300: 397 / 363 / 407, ef 512: 725 / 666 / 698. Over 48 cells 512 threads: degree 64, ef 256: 330 / 319 / 355.
+//   ef 257 .. 1024 and at most 256 cells: 512. Four nodes, ef 300: 134 / 120 / 130, ef 384: 172 / 154 / 162.
+//   ef 257 .. 1024 and more cells: 1024. ef 1024, 2048 cells: 114 / 84 / 68; ef 512: 52 / 41 / 35, 512 cells 96 / 81 / 78.
 //     More than 256 searches, ef up to 512: 512 again, two of which share a compute unit. 320 searches of 32K
-//     keys, ef 512: 66 (1024: 91), ef 384: 51 (77); 512 searches: 79 (115) and 67 (99).
-//   ef above 1024: 1024. 2048 cells: 174 (512: 254); 128 cells: 1417 (1491).
-// Where the lines are not the best ones (same measurement): ef 256 with at most 48 cells (403; 512 threads would take
-// 371) and ef up to 128 with 64 cells (192; 256: 178); eight nodes of degree 32 with ef 512 (152; 1024: 147); ef 384
-// with 2048 cells (35.7; 512: 33.0); 256 searches, which with their helpers outnumber the compute units, at ef 384 and
-// 512 (61 and 69; 512: 48 and 60); more than 256 searches with ef 1024 (320 searches: 242; 512: 196) or with ef 2048
-// and 128 cells (2814; 512: 1764).
+//     keys, ef 512: 61 / 57 / 75, ef 384: 45 / 43 / 62; 384 searches 63 / 58 / 82 and 47 / 45 / 64.
+//   ef above 1024: 1024. 2048 cells: 320 / 217 / 140; 128 cells: 1672 / 1290 / 1107.
+// Where the lines are not the best ones (same measurement, 256 / 512 / 1024 threads): ef 512 and 1024 with up to 256 cells (the
+// latter from 32 cells on; 1024: 350 / 294 / 272, 512: 145 / 130 / 125), and ef 2048 with at most 64 (3052 / 2360 / 2068), which 1024 threads
+// walk 4 to 14 % faster since they merge up to 32 candidates in one phase; ef 256 with at most 48 cells (322 / 311 / 346); ef 300 with 512 cells
+// (57 / 48.5 / 52); 129 to 256 searches with ef 300 to 512, which with their helpers outnumber the compute units (256 of 32K keys, ef
+// 384: 43.5 / 41.5 / 51.4); more than 256 searches with ef 1024 (320: 135 / 112 / 152) or with ef 2048 (128 cells: 1813 / 1548 / 2324); 512 searches
+// with ef 300 and 384 (57 / 61 / 83).
 static inline int search_threads(int heads, int ef, int cells) {
     if (cells <= 64 && heads <= 384) return ef > 256 || cells > 48 ? 512 : 256;
     if (ef > 1024) return 1024;
