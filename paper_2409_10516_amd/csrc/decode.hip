@@ -85,12 +85,8 @@ __device__ __forceinline__ void row_floats(const RowBits<DT>& r, float* f) {
     }
 }
 
-// zeroes in the place of a lane's share of a row
-template <int DT>
-__device__ __forceinline__ void clear_row(RowBits<DT>& r, bool clear) {
-    r.a = clear ? make_uint4(0u, 0u, 0u, 0u) : r.a;
-    if (DT == RA_F32) r.b = clear ? make_uint4(0u, 0u, 0u, 0u) : r.b;
-}
+// a row of zeroes
+__device__ static const uint4 no_row[RA_D / 4] = {};
 
 // A lane's 8 query values in the form the attention logits want them: bf16 pairs stay packed and
 // go through the two-element dot instruction (exact products, float32 sums), fp32 uses fma.
@@ -485,18 +481,12 @@ __global__ __launch_bounds__(T, SR_WAVES(KT, T)) void decode_kernel(
                 if (r0 + u * (T / 16) >= R) break;          // uniform: no group has a row in this slot
                 const int64_t id = row_id(min(r0 + u * (T / 16) + grp, R - 1));
                 kb[u] = load_key<DT>(Kh, id, lane16);
-                vb[u] = load_key<DT>(Vh, id, lane16);
+                // (a group without a row has the weight zero, and values of zero, since 0 * inf is not: clearing what it has loaded took
+                // four layers of 128K 1.1 % longer, this 0.1 %)
+                vb[u] = load_key<DT>(r0 + u * (T / 16) + grp < R ? Vh + id * (RA_D * (DT == RA_BF16 ? 2 : 4))
+                                                                 : reinterpret_cast<const char*>(no_row), 0, lane16);
             }
             if (r0 == 0) behind();
-            // The last slot has groups without a row, which have loaded the last row again: their weight is zero, and so are their
-            // values, since 0 * inf is not. (0.1 us; a test per slot where the values are added up costs as much, one there for all
-            // slots twice that.)
-            const int whole = (R - r0) / (T / 16);
-            if (whole < DC_ROWS) {
-#pragma unroll
-                for (int u = 0; u < DC_ROWS; ++u)
-                    if (u == whole) clear_row<DT>(vb[u], r0 + u * (T / 16) + grp >= R);
-            }
             // the logits, their maximum, then one rescaling of the sums for all of them (row by row, with a branch around the
             // rescaling, 100 rows took 3700 ticks)
             float m = st.m;
