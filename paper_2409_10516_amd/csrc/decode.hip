@@ -678,7 +678,7 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
     const int threads = search_threads(heads, ef, expand * deg);
     // One helper per query head instead of one per KV head where the launch leaves compute units idle
     // (few searches): with 512 threads a helper's pass over W for a whole group ends later than a
-    // short walk does (128K layer: 26.5 against 27.25 us). The helpers of a group run side by side on
+    // short walk does (128K layer: 17.6 against 19.5 us). The helpers of a group run side by side on
     // one XCD and find each other's rows in its L2.
     int helper_heads = n_q / n_kv;
     if (n_helpers > 0 && threads >= 512 && 2 * heads <= decode_compute_units()) {
@@ -699,10 +699,11 @@ ra_status ra_launch_decode(const void* q, const int32_t* adj, const int32_t* ent
     const int seed_stride = seed_places(root_cap, deg);
     // Steps shared out (serve_walk): walks with the visited set in device memory, where there are compute units for 8 workers each
     // and steps are wide, which takes a beam of some times `expand` entries to pick from. us per layer without -> with, cells of a
-    // step / beam: 4 heads of the mixture law, 1M keys, 3072 / 256 to 1024 134 -> 88, 209 -> 155, 424 -> 314; 1536 / 512 210 -> 182; 2M
-    // keys, float32, 3072 / 512 209 -> 173. 4 to 16 heads of the Llama-shaped law, whose steps find a hundred new keys, not a thousand:
-    // 4096 / 512 to 1024 76 -> 65, 132 -> 107, 16 heads 110 -> 84, 209 -> 152; 2048 / 256 to 1024 53 -> 53, 79 -> 80, 135 -> 130, 16
-    // heads 54 -> 55, 81 -> 78, 139 -> 157; 1024 / 1024 165 -> 203; 4096 / 64 32 -> 47. (With the visited set in LDS the head
+    // step / beam: 4 heads of the mixture law, 1M keys, 3072 / 256 to 1024 105 -> 68, 166 -> 101, 292 -> 171; 2M keys, float32, 3072 / 512
+    // 260 -> 113. 4 and 16 heads of the Llama-shaped law, whose steps find a hundred new keys, not a thousand: 4096 / 512 and 1024
+    // 71 -> 56, 106 -> 80, 16 heads 72 -> 57, 117 -> 85. Below the lines, before the walk's merges were changed: mixture law 1536 / 512 210 ->
+    // 182; the other 2048 / 256 to 1024 53 -> 53, 79 -> 80, 135 -> 130, 16 heads 54 -> 55, 81 -> 78, 139 -> 157; 1024 / 1024 165 -> 203; 4096 / 64
+    // 32 -> 47. (With the visited set in LDS the head
     // claims faster than workers could be asked to; scores alone shared out there: mixture law, 128K keys, 3072 / 256 104 -> 84, but
     // Llama-shaped walks +5 to +10 %.) 8 workers are 1 to 3 % slower than 16. Inside the lines, both laws, 2 to 24 heads, 0.8 to
     // 1.5M keys, degree 32 and 64, with and without seed sets, no setting of 200 is slower than alone (1.04 to 1.73 times as fast, 24
