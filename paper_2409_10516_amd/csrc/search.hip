@@ -117,7 +117,7 @@ ra_status ra_launch_roots(const int32_t* adj, const int32_t* entry, int heads, i
 // every adjacency row span from the entry point (position p has its children at 2p + 1 and 2p + 2;
 // for a projected graph this is the head of the popularity order). Positions without a node and
 // nodes already listed at an earlier position are dropped, the order kept. Layout of a root set
-// with [1] = 0: no id enters the beam as expanded. Behind the ids their masks (seed_mask_words). One workgroup per head; a set-up
+// with [1] = 0: no id enters the beam as expanded. Behind the ids their masks (seed_masks_kernel). One workgroup per head; a set-up
 // step.
 #define SD_THREADS 1024
 __global__ __launch_bounds__(SD_THREADS) void seeds_kernel(const int32_t* __restrict__ adj,
@@ -169,11 +169,7 @@ __global__ __launch_bounds__(SD_THREADS) void seeds_kernel(const int32_t* __rest
             if (x < wv) before += wsum[x];
             total += wsum[x];
         }
-        if (k) {
-            const int at = before + __popcll(m & ((1ull << lane) - 1ull));
-            out[2 + at] = pos[p];
-            tab_at[at] = pos[p];                             // (not read any more otherwise)
-        }
+        if (k) out[2 + before + __popcll(m & ((1ull << lane) - 1ull))] = pos[p];
         base = total;
         __syncthreads();
     }
@@ -181,22 +177,40 @@ __global__ __launch_bounds__(SD_THREADS) void seeds_kernel(const int32_t* __rest
         out[0] = base;
         out[1] = 0;
     }
-    // the masks: a wavefront per row, eight rows on their way
-    int32_t* masks = out + 2 + seed_places(cap, deg);
-    constexpr int W = SD_THREADS / RA_WAVE, ROWS = 8;
-    const int lane = tid & (RA_WAVE - 1), wv = tid / RA_WAVE;
-    for (int c0 = wv; c0 < base; c0 += W * ROWS) {
+}
+
+// The masks of listed seed sets (seed_mask_words): the set's ids in a table again, a wavefront per row, four rows on their way. A head's
+// rows are dealt to gridDim.y workgroups, since one waits for its trips to memory: the call that sets up 32 heads of 2048 seeds of degree 32 takes
+// 32 us, 76 with the masks made by the listing's workgroup, and 20 without masks; 512 heads 119, 130 and 36.
+__global__ __launch_bounds__(SD_THREADS) void seed_masks_kernel(const int32_t* __restrict__ adj, int64_t N, int deg,
+                                                                int32_t* __restrict__ seeds, int cap) {
+    __shared__ int tab_id[RT_SLOTS];
+    __shared__ int ids[RA_MAX_SEEDS];
+    const int tid = threadIdx.x, lane = tid & (RA_WAVE - 1), wv = tid / RA_WAVE, head = blockIdx.x;
+    const int32_t* adj_h = adj + (size_t)head * N * deg;
+    int32_t* set = seeds + (size_t)head * cap;
+    const int n = set[0];
+    for (int x = tid; x < RT_SLOTS; x += SD_THREADS) tab_id[x] = -1;
+    __syncthreads();
+    for (int c = tid; c < n; c += SD_THREADS) {
+        ids[c] = set[2 + c];
+        (void)rt_slot(tab_id, ids[c]);
+    }
+    __syncthreads();
+    int32_t* masks = set + 2 + seed_places(cap, deg);
+    constexpr int ROWS = 4;
+    const int W = (int)gridDim.y * (SD_THREADS / RA_WAVE);       // wavefronts of the head
+    for (int c0 = (int)blockIdx.y * (SD_THREADS / RA_WAVE) + wv; c0 < n; c0 += W * ROWS) {
         int nb[ROWS];
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u)
-            nb[u] = lane < deg ? adj_h[(size_t)tab_at[min(c0 + u * W, base - 1)] * deg + lane] : -1;
+        for (int u = 0; u < ROWS; ++u) nb[u] = lane < deg ? adj_h[(size_t)ids[min(c0 + u * W, n - 1)] * deg + lane] : -1;
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
             bool fresh = nb[u] >= 0 && nb[u] < N;
             for (uint32_t h = rt_hash(nb[u]); fresh && tab_id[h] != -1; h = (h + 1u) & (RT_SLOTS - 1)) fresh = tab_id[h] != nb[u];
             const unsigned long long m = __ballot(fresh);
             const int c = c0 + u * W;
-            if (c < base) {
+            if (c < n) {
                 if (deg <= 32) { if (lane == 0) masks[c] = (int)(uint32_t)m; }
                 else if (lane < 2) masks[2 * c + lane] = (int)(uint32_t)(m >> (32 * lane));
             }
@@ -210,6 +224,10 @@ ra_status ra_launch_seeds(const int32_t* adj, const int32_t* entry, int heads, i
                           int n_seeds, int32_t* seeds, int cap, hipStream_t st) {
     if (n_seeds < 1 || n_seeds > RA_MAX_SEEDS || seed_places(cap, deg) < n_seeds) RA_FAIL(RA_EINVAL, "seed set buffer too small");
     hipLaunchKernelGGL(seeds_kernel, dim3(heads), dim3(SD_THREADS), 0, st, adj, entry, N, deg, n_seeds, seeds, cap);
+    RA_HIP(hipGetLastError());
+    // (workgroups that fill the part, up to eight for a head)
+    const int parts = heads >= 512 ? 1 : heads <= 64 ? 8 : 512 / heads;
+    hipLaunchKernelGGL(seed_masks_kernel, dim3(heads, parts), dim3(SD_THREADS), 0, st, adj, N, deg, seeds, cap);
     RA_HIP(hipGetLastError());
     return RA_OK;
 }

@@ -1205,3 +1205,31 @@ def test_start_sets_at_the_limits_of_their_order(dtype, n_seeds, deg, expand, ef
         assert ids[0, 0].tolist() == ref.tolist(), far
         assert st[0, 0].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]], far
     idx.free()
+
+
+@pytest.mark.parametrize("heads,R,deg", [(1, 65, 32), (2, 129, 40), (64, 300, 32), (90, 257, 33), (300, 200, 32), (520, 100, 24)])
+def test_masks_of_seed_sets_in_many_and_few_heads(heads, R, deg):
+    """The masks of a head's set are listed by eight workgroups, by fewer or by one, as there are heads; sets of fewer ids than these have wavefronts,
+    and ragged ones. A mask with a cell too many or too few would change the keys that the first step visits: some
+    cells of its picks lead out of the set. Integer keys: the oracle's ids and counters, in every head of its own graph."""
+    from paper_2409_10516_amd import binding as B
+    rng = np.random.default_rng(heads + R)
+    N, ef, expand = 900, 64, 64
+    adj = rng.integers(0, R, size=(heads, N, deg)).astype(np.int32)
+    lead = rng.random((heads, N, deg)) < 8.0 / (64 * deg)    # (few enough to be listed, over the picks of a step)
+    adj[lead] = rng.integers(R, N, size=int(lead.sum()))
+    t = np.arange(N)
+    for j in (0, 1):
+        adj[:, :, j] = np.where(2 * t + 1 + j < R, 2 * t + 1 + j, -1)
+    adj[adj == t[None, :, None]] = -1
+    K = rng.integers(-4, 5, size=(N, 128)).astype(np.float32)
+    q = rng.integers(-4, 5, size=(1, heads, 128)).astype(np.float32)
+    idx = ra.ra_index_import(torch.from_numpy(adj), torch.zeros(heads, dtype=torch.int32), 1, heads, 1)
+    idx.configure(B.RA_CFG_SEEDS, R)
+    ids, st = ra.ra_search(torch.from_numpy(q).bfloat16().to(DEV), idx, torch.from_numpy(K)[None, None].bfloat16().to(DEV), 4, 20, 30, ef, expand)
+    for h in sorted({0, heads // 3, heads // 2, heads - 1}):
+        ref, rst = OS.greedy_search(q[0, h], K, adj[h], 0, ef, 30, expand, seeds=OS.backbone_seeds(adj[h], 0, R), exclude=OA.static_ids(N, 4, 20))
+        assert ids[0, h].tolist() == ref.tolist(), h
+        assert st[0, h].tolist() == [rst["n_visited"], rst["n_expanded"], rst["n_iters"], rst["n_returned"]], h
+        assert rst["n_visited"] > R
+    idx.free()
