@@ -269,12 +269,12 @@ template <int DT> struct SeedHook {
     OffWords off;
     static constexpr bool kSeedShare = true;
     static constexpr bool kShareSteps = false;
-    // value rows (where they start between two words, from the next one on: touch_line takes whole words, and any of a line will do)
+    // value rows
     const char* V;
     static constexpr bool kValues = DT == RA_BF16;
     static constexpr int value_lines = 2;
     __device__ __forceinline__ void touch_value(int id, int line, uint32_t lds) const {
-        touch_line(V + ((size_t)(uint32_t)id * value_lines + line) * 128, lds);
+        touch_line_of_halves(V + ((size_t)(uint32_t)id * value_lines + line) * 128, lds);       // (V: aligned to its elements)
     }
     __device__ __forceinline__ void note_off_words() const { off.note(); }
     __device__ __forceinline__ bool seeds_shared() const { return seed_on && __builtin_amdgcn_readfirstlane((int)off.lds[2]) == 0; }
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(T, SR_WAVES(KT, T)) void decode_kernel(
                                            s, (int)(Ng - wstart), topk, take, ef, expand, gbits, ids, stats,
                                            lds_ids, roots, root_cap, kscale,
                                            SeedHook<DT>{coop_spin, seed_keys_all + (size_t)head * seed_stride, seedx,
-                                                    seed_parts > 0, off, Vh + ((uintptr_t)Vh & 2)});
+                                                    seed_parts > 0, off, Vh});
     }
 #ifdef SR_PHASE_CLOCKS
     const long long t_attn = clock64();

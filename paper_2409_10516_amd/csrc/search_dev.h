@@ -378,6 +378,11 @@ __device__ __forceinline__ void touch_line(const void* p, uint32_t lds_off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_off), "v"(p) : "m0");
 }
 
+// The same for p that is only 2-byte aligned.
+__device__ __forceinline__ void touch_line_of_halves(const void* p, uint32_t lds_off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_ushort %1, off" ::"s"(lds_off), "v"(p) : "m0");
+}
+
 __device__ __forceinline__ void end_touches() { __builtin_amdgcn_s_waitcnt(0x0F70); }      // vmcnt(0)
 
 // Claims L neighbours per lane and appends those not visited before to cid, `n_claimed` of them so far; bit_word(id) is the word of the
